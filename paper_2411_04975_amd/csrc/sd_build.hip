@@ -7,7 +7,10 @@
 // of suffixes that start with w: COUNT(w) is the width of the range, its children are the
 // runs of equal token at offset |w| inside it, and suffixes that stop at w sit first in it.
 //
-// The sort is prefix doubling: positions are first ordered by their leading two tokens (one
+// The sort is the one by codes of sd_suffix.hip.  The one in this file is for what that leaves: text
+// that repeats itself too often, inputs whose positions and tokens need more bits than its entries
+// have, and streams that are being captured, on which the host cannot ask how it went.
+// It is prefix doubling: positions are first ordered by their leading two tokens (one
 // radix sort), then each round orders them by the pair (rank of the first h tokens, rank of
 // the next h tokens), which doubles the compared length until it reaches D.  Ranks are group
 // numbers of the previous round, a group being numbered by the place where it starts.  A
@@ -495,6 +498,20 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
     return cur;
 }
 
+// Sorts by codes (sd_suffix.hip) into sa, and with tok1 also writes second-token column, samples
+// and bucket table.  SD_ERR_STATE: the text repeats itself too often for that, or the stream cannot
+// be waited for, which is how the host hears about it; the outputs then hold nothing.
+static sd_status code_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa,
+                                       int32_t *tok1, bool new_intervals, hipStream_t st) {
+    if (!sd_code_fits(N, c->cfg.vocab) || !stream_can_wait(st)) return SD_ERR_STATE;
+    *c->h_flag = 0;
+    if (new_intervals || !c->code_ready) sd_code_intervals(c, text, N, st);
+    c->code_ready = true;
+    sd_code_sort(c, text, N, sa, tok1, c->h_flag, st);
+    if (hipStreamSynchronize(st) != hipSuccess) return SD_ERR_HIP;
+    return *const_cast<volatile int32_t *>(c->h_flag) ? SD_ERR_STATE : SD_OK;
+}
+
 sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t *d_offsets,
                                int32_t n_seq, int64_t n_tokens, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
@@ -509,6 +526,8 @@ sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t
         SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_layout_marks, dim3(nblk(m)), dim3(TB), 0, d_offsets, n_seq, N, c->g_text);
     }
     if (N > 0) {
+        const sd_status rc = code_sorted_positions(c, c->g_text, N, c->g_sa, c->g_tok1, true, st);
+        if (rc != SD_ERR_STATE) return rc;
         const int cur = build_sorted_positions(c, c->g_text, N, c->g_tok1, st);
         if (cur < 0) return SD_ERR_HIP;
         // The sorted positions are the suffix array: the buffer they are in becomes g_sa and the
@@ -540,8 +559,10 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
         int64_t m = n_seq > SD_TEXT_PAD ? n_seq : SD_TEXT_PAD;
         SD_LAUNCH(c, SD_K_INSERT, st, k_layout_marks, dim3(nblk(m)), dim3(TB), 0, d_offsets, n_seq, M, ntext);
     }
-    const int cur = build_sorted_positions(c, ntext, M, nullptr, st);
-    if (cur < 0) return SD_ERR_HIP;
+    int cur = 0;
+    const sd_status rc = code_sorted_positions(c, ntext, M, (int32_t *)c->b_vals[0], nullptr, false, st);
+    if (rc == SD_ERR_STATE) cur = build_sorted_positions(c, ntext, M, nullptr, st);
+    if ((rc != SD_OK && rc != SD_ERR_STATE) || cur < 0) return SD_ERR_HIP;
     // b_vals[cur]: new positions in order; b_flags: their ranks in the old array; merged arrays
     // go to b_vals[1 - cur] and b_rank, which then change places with g_sa and g_tok1
     uint32_t *dsa = c->b_vals[cur], *rank = c->b_flags;

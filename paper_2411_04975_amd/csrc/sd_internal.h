@@ -59,6 +59,14 @@ struct sd_ctx {
     uint32_t *b_partials = nullptr;  // scan partial sums
     int64_t b_hist_cap = 0, b_partials_cap = 0;
 
+    // suffix sorting by codes (sd_suffix.hip)
+    uint32_t *code_cdf = nullptr;       // [vocab + 2]: lower end of each token code's interval
+    uint32_t *code_cnt = nullptr;       // [copies][vocab + 1]: counts of a sample, zero between builds
+    uint32_t *code_partials = nullptr;
+    bool code_ready = false;            // code_cdf holds the intervals of some text
+    uint32_t *b_starts = nullptr;       // first entry of every bucket
+    int32_t *h_flag = nullptr;          // pinned: the text was too repetitive for the codes
+
     // ---- per-request contexts -----------------------------------------
     int32_t *r_text = nullptr;       // [max_batch_slots][r_stride], SD_END_TOKEN after the context
     int32_t *r_len = nullptr;        // [max_batch_slots]
@@ -91,6 +99,14 @@ struct sd_ctx {
 };
 
 // ---- launchers implemented in the other translation units ---------------
+// suffix sorting by codes: room for its tables, intervals from a sample of a text, the sort
+void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words);
+bool sd_code_fits(int64_t N, int32_t vocab);
+int64_t sd_code_parts(int32_t vocab);  // words of code_partials
+int sd_code_copies(int32_t vocab);     // of code_cnt
+void sd_code_intervals(sd_ctx *c, const int32_t *text, int64_t N, hipStream_t st);
+void sd_code_sort(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa, int32_t *tok1, int32_t *flag,
+                  hipStream_t st);
 // radix sort of (key, value) pairs on bits [0, nbits); result ends in keys[out_idx]/vals[out_idx]
 // every kernel of the sort returns at once if run_if is given and *run_if == 0 (device memory)
 int sd_sort_pairs(sd_ctx *c, int64_t n, int nbits, int in_idx, hipStream_t st,

@@ -1,0 +1,971 @@
+// Suffix sorting by order-preserving codes: the usual way into the global index.
+//
+// Every position gets a 32-bit code of the tokens that follow it, such that codes rise with the
+// suffixes' order: the code is the lower end of an interval of [0, 2^32) that starts as the
+// interval of the first token (as wide as that token is frequent, by a sample) and shrinks to
+// the part of the next token inside it, and so on until it is a few units wide (two tokens where
+// every token is rare, a dozen where they are frequent).  That is arithmetic coding, so codes
+// are spread evenly whatever the tokens' frequencies are, and two things follow.  Splitting by
+// leading code bits gives buckets of like size, at most two passes over 8-byte entries; and
+// inside a bucket, which a workgroup orders in LDS, an entry's code nearly gives its place.
+// What is left are groups of suffixes that agree on all that the code has seen, copies of one
+// another as a rule, and a wave orders those by reading their tokens until they differ or D
+// tokens are compared.
+//
+// An entry is 64 bits: the code without the bits of the first split, the code of the suffix's
+// second token, the position.  Equal codes mean equal first tokens, so that entries compare as
+// numbers; and the second-token column of the index comes from the entries: only suffixes that
+// tie are ever looked up in the text.
+//
+// Bound: the memory system.  Per position 68 bytes in order (text read twice, code written and
+// read, entries written and read once per pass, suffix array and second tokens written), and
+// for each one that ties one or two random cache lines, which are what costs: 10M gathers of 16 or
+// 64 bytes from a 40 MB text take 185 or 237 us, a copy of 680 MB 135 us.
+//
+// Buckets that are too large for a workgroup raise a flag (thousands of suffixes that share some
+// twenty bits of code: a token over and over, one preamble in front of thousands of documents),
+// and the caller takes prefix doubling instead (sd_build.hip), whose cost does not depend on that.
+//
+// Build of 10M tokens copied from templates 1.68 -> 0.65 ms, of 10M of a Zipf law 2.89 -> 0.40 ms, of
+// 100M copied 20.7 -> 7.0 ms, against prefix doubling for everything.
+#include "sd_internal.h"
+
+namespace {
+
+constexpr int CT = 512;            // threads of a workgroup, everywhere in this file
+constexpr int CW = CT / SD_WAVE;
+constexpr int CODE_LOOK = 16;      // tokens that a code depends on, at most
+constexpr int MAX_BITS = 10;       // of one split
+constexpr int MAX_BINS = 1 << MAX_BITS;
+
+typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t tok2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// exclusive prefix sum of one value per thread over the workgroup, and the total; two barriers
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wave /*[CW]*/,
+                                                    uint32_t *total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) s_wave[w] = inc;
+    __syncthreads();
+    uint32_t base = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < CW; i++) {
+        const uint32_t t = s_wave[i];
+        if (i < w) base += t;
+        tot += t;
+    }
+    __syncthreads();
+    *total = tot;
+    return base + inc - v;
+}
+
+// ---- the tokens' intervals ------------------------------------------------------------------
+// Counts of a sample of the text: C runs of 64 tokens, evenly spread.  A workgroup counts its
+// runs in an LDS table first: a frequent token would otherwise be tens of thousands of atomic
+// additions to one address, at some 30 ns each.
+// What it found goes into one of several copies of the counts: frequent tokens lie next to each
+// other in many vocabularies, and additions to one line queue up just the same (10M tokens of a
+// Zipf law: 75 us with one copy).
+constexpr int64_t SAMPLE_MIN = 4096;   // runs: a bin of a 256-way split sees 1000 of their tokens
+constexpr int SAMPLE_ONE_IN = 64;      // a token that goes unseen has a few hundred occurrences at most
+constexpr int64_t SAMPLE_MAX = 32768;  // 16 * 64 * SAMPLE_MAX + 4 * 2^24, the weights' total, is below 2^27
+constexpr int RUNS_PER_WG = 16;
+constexpr int TABLE = 2048;
+
+__global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ text, int64_t N,
+                                                    int64_t runs, int64_t C, uint32_t *__restrict__ counts,
+                                                    int copies, int32_t n_codes) {
+    __shared__ uint32_t s_tag[TABLE], s_num[TABLE];
+    constexpr uint32_t FREE = 0xffffffffu;
+    for (int i = threadIdx.x; i < TABLE; i += CT) { s_tag[i] = FREE; s_num[i] = 0; }
+    __syncthreads();
+    uint32_t *cnt = counts + (int64_t)(blockIdx.x & (unsigned)(copies - 1)) * n_codes;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t tok[RUNS_PER_WG / CW];
+#pragma unroll
+    for (int k = 0; k < RUNS_PER_WG / CW; k++) {
+        const int64_t run = (int64_t)blockIdx.x * RUNS_PER_WG + k * CW + w;
+        const int64_t p = run < C ? (run * runs / C) * 64 + lane : N;
+        tok[k] = p < N ? text[p] : -2;
+    }
+#pragma unroll
+    for (int k = 0; k < RUNS_PER_WG / CW; k++) {
+        if (tok[k] == -2) continue;
+        const uint32_t code = (uint32_t)(tok[k] + 1);
+        uint32_t h = (code * 2654435761u) >> 21;
+        int probe = 0;
+        for (; probe < 16; probe++) {
+            const uint32_t old = atomicCAS(&s_tag[h], FREE, code);
+            if (old == FREE || old == code) { atomicAdd(&s_num[h], 1u); break; }
+            h = (h + 1) & (TABLE - 1);
+        }
+        if (probe == 16) atomicAdd(&cnt[code], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < TABLE; i += CT)
+        if (s_num[i]) atomicAdd(&cnt[s_tag[i]], s_num[i]);
+}
+
+// A token that the sample has not seen gets a quarter of the weight of one sighting: among 1e5
+// tokens of like frequency an eighth goes unseen by two draws per token, and the suffixes that
+// start with such a token share its interval.
+constexpr int CDF_ITEMS = 2, CDF_TILE = CT * CDF_ITEMS;
+
+// weight[c], in place of the first copy's count; clears the other copies
+__global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ counts, int copies,
+                                                     int32_t n_codes, uint32_t *__restrict__ partials) {
+    __shared__ uint32_t s_wave[CW];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < CDF_ITEMS; k++) {
+        const int32_t c = (int32_t)blockIdx.x * CDF_TILE + k * CT + (int32_t)threadIdx.x;
+        if (c < n_codes) {
+            uint32_t n = counts[c];
+            for (int q = 1; q < copies; q++) {
+                n += counts[(int64_t)q * n_codes + c];
+                counts[(int64_t)q * n_codes + c] = 0;
+            }
+            n = 16u * n + 4u;
+            counts[c] = n;
+            sum += n;
+        }
+    }
+    uint32_t tot;
+    (void)block_excl_scan(sum, s_wave, &tot);
+    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+}
+
+// cdf[c] = lower end of the interval of code c; clears the first copy.  Ends are multiples of
+// 2^CDF_QUANTUM (and no interval is empty, the weights' total being below 2^27): an entry may
+// lack that many of its code's last bits, and the rest still names the first token.
+constexpr int CDF_QUANTUM = 5;
+__global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, int32_t n_codes,
+                                                 const uint32_t *__restrict__ partials,
+                                                 uint32_t *__restrict__ cdf) {
+    __shared__ uint32_t s_wave[CW];
+    uint32_t below = 0, all = 0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += CT) {
+        const uint32_t v = partials[i];
+        all += v;
+        if (i < (int)blockIdx.x) below += v;
+    }
+    const int32_t c0 = (int32_t)blockIdx.x * CDF_TILE + (int32_t)threadIdx.x * CDF_ITEMS;
+    uint32_t wgt[CDF_ITEMS], sum = 0, tot;
+#pragma unroll
+    for (int k = 0; k < CDF_ITEMS; k++) {
+        wgt[k] = 0;
+        if (c0 + k < n_codes) {
+            wgt[k] = weight[c0 + k];
+            weight[c0 + k] = 0;
+        }
+        sum += wgt[k];
+    }
+    uint32_t total, base;
+    (void)block_excl_scan(all, s_wave, &total);
+    (void)block_excl_scan(below, s_wave, &base);
+    uint32_t at = base + block_excl_scan(sum, s_wave, &tot);
+#pragma unroll
+    for (int k = 0; k < CDF_ITEMS; k++) {
+        if (c0 + k <= n_codes)
+            cdf[c0 + k] = (uint32_t)((uint64_t)at * 0x7ffffffull / total) << CDF_QUANTUM;
+        at += wgt[k];
+    }
+}
+
+// ---- codes of all positions, and how many fall into each bin of the first split per tile -----
+constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
+
+template <int ITEMS>
+__global__ __launch_bounds__(CT) void k_code_keys(const int32_t *__restrict__ text, int64_t N,
+                                                  const uint32_t *__restrict__ cdf,
+                                                  uint32_t *__restrict__ keys, int shift, int bins,
+                                                  uint32_t *__restrict__ hist, int64_t ntiles) {
+    __shared__ uint2 s_code[KEY_ROUND + CODE_LOOK];  // (lower end, width) of each token's interval
+    __shared__ uint32_t s_hist[MAX_BINS];
+    const int tid = threadIdx.x;
+    for (int i = tid; i < bins; i += CT) s_hist[i] = 0;
+    for (int r = 0; r < ITEMS / 4; r++) {
+        const int64_t base = ((int64_t)blockIdx.x * ITEMS + r * 4) * CT;
+        if (base >= N) break;
+        __syncthreads();
+        // (the text carries more than CODE_LOOK end markers behind position N - 1)
+        for (int i = tid; i < KEY_ROUND + CODE_LOOK; i += CT) {
+            uint2 v = make_uint2(0u, 1u);
+            if (base + i < N + CODE_LOOK) {
+                // (both ends in one load: the lanes of a wave ask for 64 lines of the table)
+                const u32x2 ends = *reinterpret_cast<const u32x2 *>(cdf + (text[base + i] + 1));
+                v = make_uint2(ends.x, ends.y - ends.x);
+            }
+            s_code[i] = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int p = k * CT + tid;
+            if (base + p >= N) break;
+            uint2 c = s_code[p];
+            uint64_t low = (uint64_t)c.x << 32;
+            uint32_t width = c.y;
+            for (int j = 1; j < CODE_LOOK && width > 3u; j++) {
+                c = s_code[p + j];
+                low += (uint64_t)width * c.x;
+                width = (uint32_t)(((uint64_t)width * c.y) >> 32);
+            }
+            const uint32_t key = (uint32_t)(low >> 32);
+            keys[base + p] = key;
+            atomicAdd(&s_hist[key >> shift], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < bins; i += CT) hist[(int64_t)i * ntiles + blockIdx.x] = s_hist[i];
+}
+
+// one workgroup per bin: exclusive prefix sums along the bin's row of the (bin, tile) table
+__global__ __launch_bounds__(CT) void k_code_rowscan(uint32_t *__restrict__ hist, int64_t ntiles,
+                                                     uint32_t *__restrict__ total) {
+    __shared__ uint32_t s_wave[CW];
+    constexpr int PER = 4;
+    uint32_t *row = hist + (int64_t)blockIdx.x * ntiles;
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < ntiles; base += CT * PER) {
+        const int64_t i0 = base + (int64_t)threadIdx.x * PER;
+        uint32_t v[PER], sum = 0, tot;
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            v[k] = i0 + k < ntiles ? row[i0 + k] : 0u;
+            sum += v[k];
+        }
+        uint32_t ex = carry + block_excl_scan(sum, s_wave, &tot);
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            if (i0 + k < ntiles) row[i0 + k] = ex;
+            ex += v[k];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// ---- splitting entries by a digit of the code --------------------------------------------------
+// The bits of an entry, from the lowest: position, code of the second token, code of the suffix
+// without its first bits1 bits and perhaps without a few of its last ones.
+struct entry_shape {
+    int bits1, bits2;         // of the code: split off by the first and by the second split
+    int pos_bits, tok_bits;
+    int key_bits, key_drop;   // of the code: in the entry, and left out below
+};
+
+// Orders the tile's entries by digit in LDS, then writes them out as runs of neighbouring lanes.
+// Entries of a digit leave in whatever order their LDS additions happen: nothing relies on it.
+// (ITEMS = 12: two workgroups share a compute unit.)
+template <int ITEMS>
+struct split_lds {
+    uint64_t entry[CT * ITEMS];
+    uint16_t digit[CT * ITEMS];
+    uint32_t cnt[MAX_BINS], to[MAX_BINS];
+    uint32_t wave[CW];
+};
+
+// `to` holds where the tile's first entry of each digit goes
+template <int ITEMS>
+__device__ __forceinline__ void split_tile(split_lds<ITEMS> &s, const uint64_t (&e)[ITEMS],
+                                           const uint32_t (&digit)[ITEMS], int cnt, int bins,
+                                           uint64_t *__restrict__ out) {
+    const int tid = threadIdx.x;
+    for (int i = tid; i < bins; i += CT) s.cnt[i] = 0;
+    __syncthreads();
+    uint32_t rank[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++)
+        if (k * CT + tid < cnt) rank[k] = atomicAdd(&s.cnt[digit[k]], 1u);
+    __syncthreads();
+    {
+        const int d = 2 * tid;  // MAX_BINS / CT digits per thread
+        const uint32_t a = d < bins ? s.cnt[d] : 0u, b = d + 1 < bins ? s.cnt[d + 1] : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan(a + b, s.wave, &tot);
+        if (d < bins) { s.cnt[d] = ex; s.to[d] -= ex; }
+        if (d + 1 < bins) { s.cnt[d + 1] = ex + a; s.to[d + 1] -= ex + a; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++)
+        if (k * CT + tid < cnt) {
+            const uint32_t at = s.cnt[digit[k]] + rank[k];
+            s.entry[at] = e[k];
+            s.digit[at] = (uint16_t)digit[k];
+        }
+    __syncthreads();
+#pragma unroll 4
+    for (int k = 0; k < ITEMS; k++) {
+        const int j = k * CT + tid;
+        if (j < cnt) out[s.to[s.digit[j]] + (uint32_t)j] = s.entry[j];
+    }
+}
+
+// First split: codes in position order -> entries.  `starts`, if given, receives the bins' places
+// (there is no second split), starts[bins] = N.
+template <int ITEMS>
+__global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ keys,
+                                                   const int32_t *__restrict__ text, int64_t N, entry_shape f,
+                                                   const uint32_t *__restrict__ hist,
+                                                   const uint32_t *__restrict__ total, int64_t ntiles,
+                                                   uint64_t *__restrict__ out, uint32_t *__restrict__ starts) {
+    __shared__ split_lds<ITEMS> s;
+    const int tid = threadIdx.x, bins = 1 << f.bits1;
+    const int64_t base = (int64_t)blockIdx.x * (CT * ITEMS);
+    const int cnt = (int)(N - base < CT * ITEMS ? N - base : CT * ITEMS);
+    uint64_t e[ITEMS];
+    uint32_t digit[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const int j = k * CT + tid;
+        const uint32_t key = j < cnt ? keys[base + j] : 0u;
+        const uint32_t tok = j < cnt ? (uint32_t)(text[base + j + 1] + 1) : 0u;
+        digit[k] = key >> (32 - f.bits1);
+        const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
+        e[k] = (((rest << f.tok_bits) | tok) << f.pos_bits) | (uint64_t)(base + j);
+    }
+    {
+        const int d = 2 * tid;
+        const uint32_t a = d < bins ? total[d] : 0u, b = d + 1 < bins ? total[d + 1] : 0u;
+        const uint32_t ha = d < bins ? hist[(int64_t)d * ntiles + blockIdx.x] : 0u;
+        const uint32_t hb = d + 1 < bins ? hist[(int64_t)(d + 1) * ntiles + blockIdx.x] : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan(a + b, s.wave, &tot);
+        if (d < bins) s.to[d] = ex + ha;
+        if (d + 1 < bins) s.to[d + 1] = ex + a + hb;
+        if (starts && blockIdx.x == 0) {
+            if (d < bins) starts[d] = ex;
+            if (d + 1 < bins) starts[d + 1] = ex + a;
+            if (tid == 0) starts[bins] = (uint32_t)N;
+        }
+    }
+    split_tile<ITEMS>(s, e, digit, cnt, bins, out);
+}
+
+// A bin of the first split: where it starts and how long it is.
+struct bin_place { uint32_t start, size; };
+__device__ __forceinline__ bin_place first_bin(const uint32_t *__restrict__ total, int bin,
+                                               uint32_t *s_wave) {
+    uint32_t v = 0, tot;
+    for (int i = threadIdx.x; i < bin; i += CT) v += total[i];
+    (void)block_excl_scan(v, s_wave, &tot);
+    return {tot, total[bin]};
+}
+
+constexpr int SPLIT2_ITEMS = 12, SPLIT2_TILE = CT * SPLIT2_ITEMS;
+
+// Second split, inside every bin of the first one (blockIdx.y; the bin's tiles are shared out
+// over blockIdx.x).  The counts of bin b lie at row_of(b): (digit, tile of the bin).
+__device__ __forceinline__ int64_t row_of(bin_place p, int bin, int bins2) {
+    return ((int64_t)(p.start / SPLIT2_TILE) + bin) * bins2;  // tiles of the bins before, at most
+}
+
+__global__ __launch_bounds__(CT) void k_code_hist2(const uint64_t *__restrict__ in,
+                                                   const uint32_t *__restrict__ total, int shift,
+                                                   int bins2, uint32_t *__restrict__ hist2) {
+    __shared__ uint32_t s_hist[MAX_BINS], s_wave[CW];
+    const int bin = blockIdx.y, tid = threadIdx.x;
+    const bin_place p = first_bin(total, bin, s_wave);
+    const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+    const uint32_t mask = (uint32_t)bins2 - 1u;
+    uint32_t *row = hist2 + row_of(p, bin, bins2);
+    for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+        for (int i = tid; i < bins2; i += CT) s_hist[i] = 0;
+        __syncthreads();
+        const uint32_t j0 = (uint32_t)t * SPLIT2_TILE;
+        uint64_t e[SPLIT2_ITEMS];
+#pragma unroll
+        for (int k = 0; k < SPLIT2_ITEMS; k++) {
+            const uint32_t j = j0 + k * CT + tid;
+            e[k] = j < p.size ? in[(int64_t)p.start + j] : 0ull;
+        }
+#pragma unroll
+        for (int k = 0; k < SPLIT2_ITEMS; k++)
+            if (j0 + k * CT + tid < p.size) atomicAdd(&s_hist[(uint32_t)(e[k] >> shift) & mask], 1u);
+        __syncthreads();
+        for (int i = tid; i < bins2; i += CT) row[(int64_t)i * nt + t] = s_hist[i];
+        __syncthreads();
+    }
+}
+
+// one workgroup per bin of the first split: places of its (digit, tile) counts, and of its buckets
+__global__ __launch_bounds__(CT) void k_code_scan2(const uint32_t *__restrict__ total, int bins2,
+                                                   uint32_t *__restrict__ hist2,
+                                                   uint32_t *__restrict__ starts, int64_t N) {
+    __shared__ uint32_t s_wave[CW];
+    constexpr int PER = 4;
+    const int bin = blockIdx.x, tid = threadIdx.x;
+    const bin_place p = first_bin(total, bin, s_wave);
+    const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+    const int n = bins2 * nt;
+    uint32_t *row = hist2 + row_of(p, bin, bins2), *my_starts = starts + (int64_t)bin * bins2;
+    if (bin == (int)gridDim.x - 1 && tid == 0) starts[(int64_t)gridDim.x * bins2] = (uint32_t)N;
+    if (nt == 0)
+        for (int i = tid; i < bins2; i += CT) my_starts[i] = p.start;
+    uint32_t carry = p.start;
+    for (int base = 0; base < n; base += CT * PER) {
+        const int i0 = base + tid * PER;
+        uint32_t v[PER], sum = 0, tot;
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            v[k] = i0 + k < n ? row[i0 + k] : 0u;
+            sum += v[k];
+        }
+        uint32_t ex = carry + block_excl_scan(sum, s_wave, &tot);
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            if (i0 + k < n) {
+                row[i0 + k] = ex;
+                if ((i0 + k) % nt == 0) my_starts[(i0 + k) / nt] = ex;
+            }
+            ex += v[k];
+        }
+        carry += tot;
+    }
+}
+
+__global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__ in,
+                                                    const uint32_t *__restrict__ total, int shift,
+                                                    int bins2, const uint32_t *__restrict__ hist2,
+                                                    uint64_t *__restrict__ out) {
+    __shared__ split_lds<SPLIT2_ITEMS> s;
+    const int bin = blockIdx.y, tid = threadIdx.x;
+    const bin_place p = first_bin(total, bin, s.wave);
+    const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+    const uint32_t *row = hist2 + row_of(p, bin, bins2);
+    for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+        const uint32_t j0 = (uint32_t)t * SPLIT2_TILE;
+        const int cnt = (int)(p.size - j0 < SPLIT2_TILE ? p.size - j0 : SPLIT2_TILE);
+        uint64_t e[SPLIT2_ITEMS];
+        uint32_t digit[SPLIT2_ITEMS];
+#pragma unroll
+        for (int k = 0; k < SPLIT2_ITEMS; k++) {
+            const int j = k * CT + tid;
+            e[k] = j < cnt ? in[(int64_t)p.start + j0 + j] : 0ull;
+        }
+#pragma unroll
+        for (int k = 0; k < SPLIT2_ITEMS; k++) digit[k] = (uint32_t)(e[k] >> shift) & ((uint32_t)bins2 - 1u);
+        __syncthreads();  // (the tile before is written out)
+        for (int i = tid; i < bins2; i += CT) s.to[i] = row[(int64_t)i * nt + t];
+        split_tile<SPLIT2_ITEMS>(s, e, digit, cnt, bins2, out);
+    }
+}
+
+// ---- ordering whole buckets in LDS ------------------------------------------------------------
+// A workgroup takes the buckets that start in its SORT_TILE entries: codes are spread evenly, so
+// one count over equal parts of the buckets' code ranges puts every entry within a few places of
+// its own, and counting the lower entries of its part there.  From there on a wave takes care of
+// its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
+// one place of the list, whole groups together, shows the next TOK tokens of every entry to the
+// wave through LDS, counts for each entry the group's members that sort before it, moves the
+// positions to their new places, does so for another TOK tokens (which came with the same
+// gather), and keeps on the list what still ties.
+//
+// Tokens are compared as two 64-bit words: three of 21 bits each, two of 32 for vocabularies
+// beyond that.
+constexpr int SORT_TILE = 2048;
+constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
+constexpr int SORT_PARTS = 4096;
+constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
+constexpr int SORT_ITEMS = SORT_CAP / CT;
+static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
+
+template <int TOK>
+struct token_words { uint64_t a, b; };
+template <int TOK>
+__device__ __forceinline__ token_words<TOK> words_at(const int32_t *__restrict__ p, int32_t *second) {
+    const tok4 t = *reinterpret_cast<const tok4 *>(p);
+    *second = t.y;
+    if (TOK == 4)
+        return {((uint64_t)(uint32_t)(t.x + 1) << 32) | (uint32_t)(t.y + 1),
+                ((uint64_t)(uint32_t)(t.z + 1) << 32) | (uint32_t)(t.w + 1)};
+    const tok2 u = *reinterpret_cast<const tok2 *>(p + 4);
+    return {((uint64_t)(uint32_t)(t.x + 1) << 42) | ((uint64_t)(uint32_t)(t.y + 1) << 21) | (uint32_t)(t.z + 1),
+            ((uint64_t)(uint32_t)(t.w + 1) << 42) | ((uint64_t)(uint32_t)(u.x + 1) << 21) | (uint32_t)(u.y + 1)};
+}
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
+// 64 bits of a bit row from bit s on, and the bit behind them
+__device__ __forceinline__ uint64_t bits_from(const uint32_t *row, int s, bool *next) {
+    const int i = s >> 5, sh = s & 31;
+    const uint32_t m2 = row[i + 2];
+    uint64_t m = (((uint64_t)row[i + 1] << 32) | row[i]) >> sh;
+    if (sh) m |= (uint64_t)m2 << (64 - sh);
+    *next = (m2 >> sh) & 1u;
+    return uniform64(m);
+}
+
+// first index in [0, n) of a rising table with table[index] >= key, n if there is none; whole wave
+__device__ __forceinline__ int wave_lower_bound(const uint32_t *__restrict__ table, int n, uint64_t key) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int step = (hi - lo + 63) >> 6;
+        const int i = lo + lane * step;
+        const int c = __popcll(__ballot(i < hi && table[i < hi ? i : lo] < key));
+        if (c == 0) break;
+        const int to = lo + c * step;
+        lo = to - step + 1;
+        hi = to < hi ? to : hi;
+    }
+    return lo;
+}
+
+template <int TOK>
+__global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
+                                                  const uint32_t *__restrict__ starts, int64_t N, entry_shape f,
+                                                  const int32_t *__restrict__ text, int32_t D,
+                                                  const uint32_t *__restrict__ cdf, int32_t n_codes,
+                                                  int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
+                                                  int32_t *__restrict__ samples,
+                                                  int32_t *__restrict__ bucket, int32_t *too_long) {
+    __shared__ uint64_t s_entry[SORT_CAP];         // later positions by place, and lists
+    __shared__ uint4 s_area[SORT_PARTS / 8];       // counts per part, two per word; later windows
+    __shared__ uint32_t s_start[SORT_BUCKETS + 1];  // places of the workgroup's buckets
+    __shared__ uint32_t s_first[SORT_CAP / 32 + 4];  // bit per place: a group starts here
+    __shared__ uint32_t s_done[SORT_CAP / 32];       // bit per place: see below
+    __shared__ uint64_t s_class[2][SORT_CAP / 64 + 2 * CW];
+    __shared__ uint32_t s_wave[CW];
+    __shared__ int s_range[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int bits = f.bits1 + f.bits2, down = 32 - bits, low_bits = f.pos_bits + f.tok_bits;
+    if (w < 2) {  // buckets that start at or behind the two ends of the workgroup's entries
+        const int b = wave_lower_bound(starts, (1 << bits) + 1, ((uint64_t)blockIdx.x + w) * SORT_TILE);
+        if (lane == 0) s_range[w] = b > 1 << bits ? 1 << bits : b;
+    }
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(s_area);
+    s_area[tid] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < SORT_CAP / 32 + 4) s_first[tid] = 0;
+    if (tid < SORT_CAP / 32) s_done[tid] = 0;
+    __syncthreads();
+    const int b0 = s_range[0], nb = s_range[1] - b0;
+    const int64_t a = starts[b0], z = starts[b0 + nb];
+    if (nb == 0) return;
+    if (nb > SORT_BUCKETS || z - a > SORT_CAP) {
+        if (tid == 0) *too_long = 1;
+        return;
+    }
+    const int n = (int)(z - a);
+    uint64_t e[SORT_ITEMS];
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++) {
+        const int j = k * CT + tid;
+        e[k] = j < n ? in[a + j] : 0ull;
+    }
+    for (int i = tid; i <= nb; i += CT) s_start[i] = (uint32_t)(starts[b0 + i] - a);
+    if (bucket && (w & 3) == 2) {  // tokens whose intervals start in this workgroup's part of the codes
+        const int c = wave_lower_bound(cdf, n_codes + 1, (uint64_t)(b0 + (w > 3 ? nb : 0)) << down);
+        if (lane == 0) s_range[2 + (w > 3)] = c;
+    }
+    __syncthreads();
+    // parts: 2^fine per bucket
+    const int in_bucket = f.key_bits - f.bits2;
+    int fine = 31 - __builtin_clz(SORT_PARTS / nb);
+    if (fine > in_bucket) fine = in_bucket;
+    const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
+    uint32_t part[SORT_ITEMS], rank[SORT_ITEMS];
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++) {
+        const int j = k * CT + tid;
+        if (j < n) {
+            int lo = 0, hi = nb;  // last bucket that starts at or before place j
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_start[mid] <= (uint32_t)j) lo = mid; else hi = mid;
+            }
+            part[k] = ((uint32_t)lo << fine) + (((uint32_t)(e[k] >> low_bits) & key_mask) >> (in_bucket - fine));
+            const uint32_t sh = (part[k] & 1u) * 16u;
+            rank[k] = (atomicAdd(&cnt[part[k] >> 1], 1u << sh) >> sh) & 0xffffu;
+        }
+    }
+    for (int i = tid; i <= nb; i += CT) {
+        const uint32_t p = s_start[i];  // (a bucket's first place; the last one ends the last group)
+        atomicOr(&s_first[p >> 5], 1u << (p & 31));
+    }
+    __syncthreads();
+    {
+        const uint4 q = s_area[tid];
+        const uint32_t v[4] = {q.x, q.y, q.z, q.w};
+        uint32_t sum = 0, tot, o[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) sum += (v[k] & 0xffffu) + (v[k] >> 16);
+        uint32_t at = block_excl_scan(sum, s_wave, &tot);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint32_t mid = at + (v[k] & 0xffffu);
+            o[k] = at | (mid << 16);
+            at = mid + (v[k] >> 16);
+        }
+        s_area[tid] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+    __syncthreads();
+    auto part_start = [&](uint32_t p) -> int { return p < SORT_PARTS ? (int)((cnt[p >> 1] >> ((p & 1u) * 16u)) & 0xffffu) : n; };
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++)
+        if (k * CT + tid < n) s_entry[part_start(part[k]) + rank[k]] = e[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++)
+        if (k * CT + tid < n) {
+            const int lo = part_start(part[k]), hi = part_start(part[k] + 1);
+            int less = 0;
+            for (int i = lo; i < hi; i++) less += s_entry[i] < e[k] ? 1 : 0;
+            rank[k] = (uint32_t)(lo + less);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++)
+        if (k * CT + tid < n) s_entry[rank[k]] = e[k];
+    __syncthreads();
+    if (bucket) {
+        // bucket[c] = first place whose suffix starts with a token code >= c: the entries before
+        // it are those with codes below the interval of c
+        for (int c = s_range[2] + tid; c < s_range[3]; c += CT) {
+            const uint32_t end = cdf[c];
+            const uint32_t key = ((end & (uint32_t)((1ull << down) - 1ull)) >> f.key_drop);  // inside the bucket
+            const uint32_t p = (((end >> down) - (uint32_t)b0) << fine) + (key >> (in_bucket - fine));
+            int at = part_start(p);
+            const int to = part_start(p + 1);
+            while (at < to && ((uint32_t)(s_entry[at] >> low_bits) & key_mask) < key) at++;
+            bucket[c] = (int32_t)(a + at);
+        }
+        if (z == N && tid == 0) bucket[n_codes] = (int32_t)N;
+    }
+    uint32_t pos_k[SORT_ITEMS];
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++) {
+        const int j = k * CT + tid;
+        if (k * CT >= n) break;
+        const uint64_t v = j < n ? s_entry[j] : 0ull;
+        const uint64_t before = j > 0 && j < n ? s_entry[j - 1] : 0ull;
+        const uint64_t m = __ballot(j < n && (v >> f.pos_bits) != (before >> f.pos_bits));
+        if (lane < 2 && (uint32_t)(m >> (32 * lane))) atomicOr(&s_first[(j >> 6) * 2 + lane], (uint32_t)(m >> (32 * lane)));
+        pos_k[k] = (uint32_t)(v & ((1ull << f.pos_bits) - 1ull));
+        if (tok1 && j < n) {
+            const int32_t second = (int32_t)((uint32_t)(v >> f.pos_bits) & ((1u << f.tok_bits) - 1u)) - 1;
+            tok1[a + j] = second;
+            if (((a + j) & 15) == 0) samples[(a + j) >> 4] = second;
+        }
+    }
+    __syncthreads();
+    uint32_t *s_pos = reinterpret_cast<uint32_t *>(s_entry);
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++)
+        if (k * CT + tid < n) s_pos[k * CT + tid] = pos_k[k];
+    __syncthreads();
+
+    // from here on the waves are on their own
+    auto next_first = [&](int x) {  // first group start at or behind place x <= n
+        int i = x >> 5;
+        uint32_t v = s_first[i] & (0xffffffffu << (x & 31));
+        while (v == 0) v = s_first[++i];
+        return __builtin_amdgcn_readfirstlane(i * 32 + __builtin_ctz(v));
+    };
+    auto set_first = [&](int x) { atomicOr(&s_first[x >> 5], 1u << (x & 31)); };
+    auto is_first = [&](int x) { return (s_first[x >> 5] >> (x & 31)) & 1u; };
+    const int share = (n + CW - 1) / CW;
+    const int s_begin = next_first(w * share < n ? w * share : n);
+    const int s_end = next_first((w + 1) * share < n ? (w + 1) * share : n);
+    uint4 *win = s_area + w * 64;
+    uint16_t *list = reinterpret_cast<uint16_t *>(s_pos + SORT_CAP) + s_begin;
+    // place of this lane's entry among its group's lanes [lo, hi), with the group it gets there
+    struct placed { int to, less, before, same; };
+    auto place_by = [&](const token_words<TOK> &x, int lo, int hi) {  // (x is in the wave's window)
+        placed r = {lane, 0, 0, 0};
+        for (int j = lo; j < hi; j++) {
+            const uint4 o = win[j];
+            const uint64_t oa = ((uint64_t)o.y << 32) | o.x, ob = ((uint64_t)o.w << 32) | o.z;
+            const bool ea = oa == x.a, eb = ob == x.b;
+            r.less += oa < x.a || (ea && ob < x.b) ? 1 : 0;
+            r.same += ea && eb ? 1 : 0;
+            r.before += ea && eb && j < lane ? 1 : 0;
+        }
+        if (lo < hi) r.to = lo + r.less + r.before;
+        return r;
+    };
+    auto show = [&](int at, const token_words<TOK> &x) {
+        win[at] = make_uint4((uint32_t)x.a, (uint32_t)(x.a >> 32), (uint32_t)x.b, (uint32_t)(x.b >> 32));
+    };
+    // Orders the groups `first` (bits: lanes where one starts) of a window of len lanes by the 2 TOK
+    // tokens x, y of every lane's entry; lane q holds place `at`.  Moves the positions in s_pos, marks
+    // new groups in s_first; true where the place's group has more than one entry still.
+    auto order = [&](uint64_t first, int len, int at, uint32_t pos, const token_words<TOK> &x,
+                     const token_words<TOK> &y, int &to) {
+        bool open = false;
+        to = lane;
+        int lo = 0, hi = 0;
+        auto group = [&]() {
+            if (lane < len) {
+                lo = 63 - __builtin_clzll(first & ((2ull << lane) - 1ull));
+                const uint64_t behind = lane == 63 ? 0ull : first >> (lane + 1);
+                hi = behind ? lane + 1 + __builtin_ctzll(behind) : 64;
+                hi = hi < len ? hi : len;
+            }
+            open = hi - lo > 1;
+        };
+        group();
+        if (!__any(open)) return false;
+        show(lane, x);
+        wave_sync();
+        placed r = place_by(x, open ? lo : 0, open ? hi : 0);
+        to = r.to;
+        wave_sync();
+        show(to, y);
+        if (open) {
+            s_pos[at + to - lane] = pos;
+            if (r.before == 0 && r.less > 0) set_first(at + to - lane);
+        }
+        wave_sync();
+        first = __ballot(lane < len && is_first(at));
+        group();
+        if (!__any(open)) return false;
+        const uint4 o = win[lane];
+        pos = s_pos[at];
+        const token_words<TOK> v = {((uint64_t)o.y << 32) | o.x, ((uint64_t)o.w << 32) | o.z};
+        r = place_by(v, open ? lo : 0, open ? hi : 0);
+        wave_sync();
+        if (open) {
+            s_pos[at + r.to - lane] = pos;
+            if (r.before == 0 && r.less > 0) set_first(at + r.to - lane);
+        }
+        wave_sync();
+        return lane < len && !(is_first(at) && is_first(at + 1));
+    };
+
+    // A group too long for a window, places [p, p + k), is split in three by the 2 TOK tokens from
+    // h on: entries below, at and above those of its middle entry, each in the order that they
+    // had.  The middle part is done with these tokens, which s_done notes at its first place.
+    auto split_group = [&](int p, int k, int h) {
+        uint64_t *below = s_class[0] + s_begin / 64 + w, *equal = s_class[1] + s_begin / 64 + w;
+        int32_t unused;
+        const int32_t *mid = text + (int64_t)s_pos[p + k / 2] + h;
+        const token_words<TOK> mx = words_at<TOK>(mid, &unused), my = words_at<TOK>(mid + TOK, &unused);
+        int nl = 0, ne = 0;
+        for (int c = 0; c < k; c += 64) {
+            bool lt = false, eq = false;
+            if (c + lane < k) {
+                const uint32_t pos = s_pos[p + c + lane];
+                const int32_t *q = text + (int64_t)pos + h;
+                const token_words<TOK> x = words_at<TOK>(q, &unused), y = words_at<TOK>(q + TOK, &unused);
+                const bool e1 = x.a == mx.a, e2 = x.b == mx.b, e3 = y.a == my.a, e4 = y.b == my.b;
+                lt = !e1 ? x.a < mx.a : !e2 ? x.b < mx.b : !e3 ? y.a < my.a : y.b < my.b;
+                eq = e1 && e2 && e3 && e4;
+                sa[a + p + c + lane] = (int32_t)pos;  // (kept there while the group is moved)
+            }
+            const uint64_t bl = __ballot(lt), be = __ballot(eq);
+            if (lane == 0) { below[c >> 6] = bl; equal[c >> 6] = be; }
+            nl += __popcll(bl);
+            ne += __popcll(be);
+        }
+        wave_sync();
+        int l = 0, q = nl, g = nl + ne;
+        for (int c = 0; c < k; c += 64) {
+            const uint64_t all = k - c < 64 ? (1ull << (k - c)) - 1ull : ~0ull;
+            const uint64_t bl = below[c >> 6], be = equal[c >> 6], ba = all & ~(bl | be), lt = (1ull << lane) - 1ull;
+            if (c + lane < k) {
+                const uint32_t pos = (uint32_t)sa[a + p + c + lane];
+                const bool il = (bl >> lane) & 1ull, ie = (be >> lane) & 1ull;
+                s_pos[p + (il ? l + __popcll(bl & lt) : ie ? q + __popcll(be & lt) : g + __popcll(ba & lt))] = pos;
+            }
+            l += __popcll(bl);
+            q += __popcll(be);
+            g += __popcll(ba);
+        }
+        if (lane == 0) {
+            if (nl > 0) set_first(p + nl);
+            if (nl + ne < k) set_first(p + nl + ne);
+            atomicOr(&s_done[(p + nl) >> 5], 1u << ((p + nl) & 31));
+        }
+        wave_sync();
+    };
+
+    int m = 0;  // places on the list
+    for (int s = s_begin; s < s_end; s += 64) {
+        bool next;
+        const uint64_t first = bits_from(s_first, s, &next);
+        const uint64_t alone = first & ((first >> 1) | ((uint64_t)next << 63));
+        const int len = s_end - s < 64 ? s_end - s : 64;
+        const uint64_t open = ~alone & (len == 64 ? ~0ull : (1ull << len) - 1ull);
+        if ((open >> lane) & 1ull) list[m + __popcll(open & ((1ull << lane) - 1ull))] = (uint16_t)(s + lane);
+        m += __popcll(open);
+    }
+    for (int h = 2; m > 0 && h < D; h += 2 * TOK) {  // (entries that tie agree on two tokens)
+        int out = 0;
+        wave_sync();
+        for (int at = 0; at < m;) {
+            int len = m - at < 64 ? m - at : 64;
+            const int place = lane < len ? list[at + lane] : 0;
+            const uint64_t first = __ballot(lane < len && is_first(place));
+            if (len == 64 && at + 64 < m && !is_first(list[at + 64])) len = 63 - __builtin_clzll(first);
+            len = __builtin_amdgcn_readfirstlane(len);
+            if (len == 0) {
+                const int p = __builtin_amdgcn_readfirstlane(place), k = next_first(p + 1) - p;
+                if (!((s_done[p >> 5] >> (p & 31)) & 1u)) {
+                    split_group(p, k, h);
+                    continue;
+                }
+                wave_sync();
+                if (lane == 0) s_done[p >> 5] &= ~(1u << (p & 31));
+                for (int c = lane; c < k; c += 64) list[out + c] = (uint16_t)(p + c);
+                out += k;
+                at += k;
+                wave_sync();
+                continue;
+            }
+            uint32_t pos = 0;
+            token_words<TOK> x = {0, 0}, y = {0, 0};
+            if (lane < len) {
+                pos = s_pos[place];
+                int32_t unused;
+                x = words_at<TOK>(text + (int64_t)pos + h, &unused);
+                y = words_at<TOK>(text + (int64_t)pos + h + TOK, &unused);
+            }
+            int to;
+            const bool open = order(first, len, place, pos, x, y, to);
+            const uint64_t om = __ballot(open);
+            if (open) list[out + __popcll(om & ((1ull << lane) - 1ull))] = (uint16_t)place;
+            out += __popcll(om);
+            at += len;
+        }
+        m = out;
+    }
+    wave_sync();
+    for (int s = s_begin + lane; s < s_end; s += 64) sa[a + s] = (int32_t)s_pos[s];
+}
+
+// ---- host side --------------------------------------------------------------------------------
+// Leading code bits that are split off: buckets of 128 to 256 entries, so that the share of a
+// workgroup of k_code_sort, whole buckets, is SORT_TILE give or take one of them, and a bucket may
+// be ten times as large as the average before it no longer fits.  Up to 10 bits go in one
+// split; small inputs take buckets of up to 512 for that (a split is three launches).
+// Tiles of 6144 entries leave as runs of 24 entries per bin and more; small inputs take tiles of
+// 2048 so that they are spread over more compute units.
+struct split_plan {
+    int bits1, bits2;
+    bool small_tiles;
+};
+split_plan plan_for(int64_t N) {
+    int bits = 1;
+    while (bits < 2 * MAX_BITS && (N >> bits) > 256) bits++;
+    split_plan p;
+    p.bits1 = bits;
+    p.bits2 = 0;
+    if (bits > MAX_BITS) {
+        if ((N >> MAX_BITS) <= 512) p.bits1 = MAX_BITS;
+        else { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
+    }
+    p.small_tiles = N <= (1 << 20);
+    return p;
+}
+constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
+
+}  // namespace
+
+// Room that the tables of an input of up to `cap` positions take: words of b_hist and b_starts.
+void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words) {
+    int64_t h = 0, s = 0;
+    const int64_t sizes[] = {cap, 1 << 20, (int64_t)512 << MAX_BITS};
+    for (int64_t n : sizes) {
+        if (n > cap) n = cap;
+        const split_plan p = plan_for(n);
+        const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
+        int64_t x = ((n + tile - 1) / tile + 1) << p.bits1;
+        if (p.bits2) x += (n / SPLIT2_TILE + (1ll << p.bits1) + 1) << p.bits2;
+        h = x > h ? x : h;
+        const int64_t y = (1ll << (p.bits1 + p.bits2)) + 1;
+        s = y > s ? y : s;
+    }
+    *hist_words = h + MAX_BINS;
+    *start_words = s;
+}
+
+int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
+int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? 8 : 1; }
+
+void sd_code_intervals(sd_ctx *c, const int32_t *text, int64_t N, hipStream_t st) {
+    const int64_t runs = (N + 63) / 64;
+    int64_t C = runs / SAMPLE_ONE_IN > SAMPLE_MIN ? runs / SAMPLE_ONE_IN : SAMPLE_MIN;
+    if (C > SAMPLE_MAX) C = SAMPLE_MAX;
+    if (C > runs) C = runs;
+    const int32_t n_codes = c->cfg.vocab + 1;
+    const int copies = sd_code_copies(c->cfg.vocab);
+    const unsigned parts = (unsigned)sd_code_parts(c->cfg.vocab);  // the last one also writes cdf[n_codes]
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_sample, dim3((unsigned)((C + RUNS_PER_WG - 1) / RUNS_PER_WG)), dim3(CT), 0,
+              text, N, runs, C, c->code_cnt, copies, n_codes);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_weights, dim3(parts), dim3(CT), 0, c->code_cnt, copies, n_codes,
+              c->code_partials);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_cdf, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
+              c->code_partials, c->code_cdf);
+}
+
+// An entry's 64 bits: whether they hold what is needed of an input.
+static bool shape_for(int64_t N, int32_t vocab, entry_shape *f) {
+    const split_plan p = plan_for(N);
+    f->bits1 = p.bits1;
+    f->bits2 = p.bits2;
+    f->pos_bits = sd_bits_for((uint64_t)(N - 1));
+    f->tok_bits = sd_bits_for((uint64_t)vocab);
+    f->key_bits = 64 - f->pos_bits - f->tok_bits;
+    if (f->key_bits > 32 - p.bits1) f->key_bits = 32 - p.bits1;
+    f->key_drop = 32 - p.bits1 - f->key_bits;
+    return f->key_drop <= CDF_QUANTUM;
+}
+
+bool sd_code_fits(int64_t N, int32_t vocab) {
+    entry_shape f;
+    return shape_for(N, vocab, &f);
+}
+
+// Sorts the N >= 1 positions of `text` into sa; with tok1 also writes the second-token column, its
+// samples and the bucket table.  *flag (pinned host memory, zero before) becomes 1 if the text is too
+// repetitive: then the outputs are not complete.
+void sd_code_sort(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa, int32_t *tok1, int32_t *flag,
+                  hipStream_t st) {
+    const split_plan p = plan_for(N);
+    entry_shape f;
+    (void)shape_for(N, c->cfg.vocab, &f);
+    const int bins1 = 1 << f.bits1, bins2 = 1 << f.bits2;
+    const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
+    const int64_t ntiles = (N + tile - 1) / tile;
+    uint32_t *keys = c->b_flags;
+    uint64_t *ent1 = c->b_keys[0], *ent2 = c->b_keys[1];
+    uint32_t *hist = c->b_hist, *total = hist + ntiles * bins1, *hist2 = total + bins1;
+    const dim3 grid1((unsigned)ntiles), block(CT);
+    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_code_keys<SMALL_ITEMS> : k_code_keys<LARGE_ITEMS>),
+              grid1, block, 0, text, N, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles);
+    SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_rowscan, dim3(bins1), block, 0, hist, ntiles, total);
+    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (p.small_tiles ? k_code_split<SMALL_ITEMS> : k_code_split<LARGE_ITEMS>),
+              grid1, block, 0, keys, text, N, f, hist, total, ntiles, ent1,
+              p.bits2 ? (uint32_t *)nullptr : c->b_starts);
+    if (p.bits2) {
+        const int64_t per_bin = (N >> p.bits1) / SPLIT2_TILE + 1;
+        const dim3 grid2((unsigned)(per_bin + per_bin / 4), (unsigned)bins1);
+        const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
+        SD_LAUNCH(c, SD_K_SORT_HIST, st, k_code_hist2, grid2, block, 0, ent1, total, shift, bins2, hist2);
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_scan2, dim3(bins1), block, 0, total, bins2, hist2, c->b_starts, N);
+        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, total, shift, bins2, hist2, ent2);
+        ent1 = ent2;
+    }
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
+              dim3((unsigned)((N + SORT_TILE - 1) / SORT_TILE)), block, 0, ent1, c->b_starts, N, f, text,
+              c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s,
+              tok1 ? c->g_bucket : (int32_t *)nullptr, flag);
+}

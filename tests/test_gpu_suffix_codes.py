@@ -1,0 +1,80 @@
+"""The suffix sort by codes (csrc/sd_suffix.hip) at the sizes where it changes its way: one or two
+splits, small and large tiles, groups of ties on either side of a wave's window, buckets that no
+longer fit a workgroup (prefix doubling takes over), and token codes of more than 21 bits.
+The index must be a permutation of the positions that is ordered on D tokens."""
+import numpy as np
+import pytest
+
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(g, docs, D):
+    import paper_2411_04975_amd as sd
+    text, sa = sd.sd_debug_read_global(g.ctx)
+    want = np.concatenate([np.concatenate([d, [-1]]) for d in docs]).astype(np.int32)
+    assert np.array_equal(text, want)
+    N = len(want)
+    assert np.array_equal(np.sort(sa), np.arange(N))
+    pad = np.concatenate([text, np.full(D, -1, np.int32)])
+    a, b = sa[:-1].astype(np.int64), sa[1:].astype(np.int64)
+    for k in range(D):
+        x, y = pad[a + k], pad[b + k]
+        assert not np.any(x > y), k
+        same = (x == y) & (x >= 0)
+        a, b = a[same], b[same]
+
+
+def _text(rng, n, vocab, copies):
+    """n tokens: pieces of a pool, every pool token `copies` times on average, one in 20 replaced."""
+    pool = rng.integers(0, vocab, max(n // copies, 40)).astype(np.int32)
+    parts, have = [], 0
+    while have < n:
+        a = int(rng.integers(0, len(pool) - 20))
+        parts.append(pool[a:a + int(rng.integers(16, 256))])
+        have += len(parts[-1])
+    t = np.concatenate(parts)[:n].copy()
+    mut = rng.random(n) < 0.05
+    t[mut] = rng.integers(0, vocab, int(mut.sum()))
+    return t
+
+
+@pytest.mark.parametrize("n,vocab,copies", [
+    (1, 50, 1), (2, 50, 1), (254, 50, 1), (257, 900, 3), (2047, 30000, 3), (2049, 30000, 3),
+    (6150, 5, 40), (100_003, 128256, 4), (524_200, 128256, 3), (524_400, 300, 3),
+    (1_048_500, 128256, 9), (1_048_700, 152064, 5), (40_000, 1 << 24, 2), (40_000, (1 << 21) - 2, 2)])
+def test_sizes(n, vocab, copies):
+    rng = np.random.default_rng(n + copies)
+    D = 24
+    t = _text(rng, n, vocab, copies)
+    cuts = np.sort(rng.integers(0, n + 1, n // 700 + 1))
+    docs = np.split(t, cuts)
+    new = np.split(_text(rng, n // 3 + 1, vocab, copies), [n // 7])
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n + n // 3 + 1 + len(docs) + len(new))
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+        g.insert_global(new)
+        _check(g, docs + new, D)
+        g.build_global(new)  # the intervals of another text, in the same context
+        _check(g, new, D)
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("times", [63, 64, 65, 130, 700, 1900, 5000])
+def test_repeated_phrase(times):
+    """A phrase of 40 tokens in front of `times` documents that go on differently, two of them alike."""
+    rng = np.random.default_rng(times)
+    D, vocab = 48, 3000
+    phrase = rng.integers(0, vocab, 40).astype(np.int32)
+    docs = [np.concatenate([phrase, rng.integers(0, vocab, int(rng.integers(0, 9))).astype(np.int32)])
+            for _ in range(times)]
+    docs[0] = docs[-1]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in docs))
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
