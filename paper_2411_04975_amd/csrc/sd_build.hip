@@ -29,64 +29,6 @@
 namespace {
 
 constexpr int TB = 256;
-// tokens per thread of k_layout_text
-inline int layout_items(int64_t n_tokens) { return n_tokens >= (1 << 20) ? 16 : 1; }
-
-// text[i + doc(i)] = tokens[i]: document j is shifted right by j to make room for one end
-// marker after each earlier document.
-__global__ __launch_bounds__(TB) void k_layout_text(const int32_t *__restrict__ tokens,
-                                                    const int64_t *__restrict__ offs, int32_t n_seq,
-                                                    int64_t n_tokens, int32_t *__restrict__ text,
-                                                    int32_t vocab, int32_t *err, int items) {
-    // The tokens of a workgroup (`items` per thread: many for a corpus, one for the few
-    // documents of an insertion) lie in a few neighbouring documents: two threads find the
-    // documents of its first and last token among all of them (a chain of dependent loads that
-    // the whole workgroup waits for: hence long tiles for long inputs); the offsets of the
-    // documents between go to LDS, where everyone else searches.
-    constexpr int LDS_DOCS = 128;
-    __shared__ int32_t s_doc[2];
-    __shared__ int64_t s_offs[LDS_DOCS];
-    const int64_t i0 = (int64_t)blockIdx.x * TB * items;
-    const int64_t i1 = i0 + (int64_t)TB * items - 1 < n_tokens - 1 ? i0 + (int64_t)TB * items - 1 : n_tokens - 1;
-    if (threadIdx.x < 2) {
-        const int64_t q = threadIdx.x ? i1 : i0;
-        int32_t lo = 0, hi = n_seq;  // largest j with offs[j] <= q, in [lo, hi)
-        while (hi - lo > 1) {
-            int32_t mid = (lo + hi) >> 1;
-            if (offs[mid] <= q) lo = mid; else hi = mid;
-        }
-        s_doc[threadIdx.x] = lo;
-    }
-    __syncthreads();
-    const int32_t d0 = s_doc[0], d1 = s_doc[1];
-    const bool in_lds = d1 - d0 < LDS_DOCS;
-    if (in_lds && (int)threadIdx.x <= d1 - d0) s_offs[threadIdx.x] = offs[d0 + threadIdx.x];
-    __syncthreads();
-    for (int k = 0; k < items; k++) {
-        const int64_t i = i0 + (int64_t)k * TB + threadIdx.x;
-        if (i >= n_tokens) break;
-        // largest j with offs[j] <= i
-        int32_t lo = d0, hi = d1 + 1;  // answer in [lo, hi)
-        while (hi - lo > 1) {
-            int32_t mid = (lo + hi) >> 1;
-            if ((in_lds ? s_offs[mid - d0] : offs[mid]) <= i) lo = mid; else hi = mid;
-        }
-        int32_t t = tokens[i];
-        if (t < 0 || t >= vocab) {
-            atomicOr(&err[SD_DEVERR_TOKEN], 1);
-            t = 0;
-        }
-        text[i + lo] = t;
-    }
-}
-
-__global__ __launch_bounds__(TB) void k_layout_marks(const int64_t *__restrict__ offs, int32_t n_seq,
-                                                     int64_t N, int32_t *__restrict__ text) {
-    int64_t j = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (j < n_seq) text[offs[j + 1] + j] = SD_END_TOKEN;
-    if (j < SD_TEXT_PAD) text[N + j] = SD_END_TOKEN;
-}
-
 __global__ __launch_bounds__(TB) void k_init_keys(const int32_t *__restrict__ text, int64_t N,
                                                   int tok_bits, uint64_t *__restrict__ keys,
                                                   uint32_t *__restrict__ vals) {
@@ -498,16 +440,22 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
     return cur;
 }
 
-// Sorts by codes (sd_suffix.hip) into sa, and with tok1 also writes second-token column, samples
-// and bucket table.  SD_ERR_STATE: the text repeats itself too often for that, or the stream cannot
-// be waited for, which is how the host hears about it; the outputs then hold nothing.
-static sd_status code_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa,
-                                       int32_t *tok1, bool new_intervals, hipStream_t st) {
-    if (!sd_code_fits(N, c->cfg.vocab) || !stream_can_wait(st)) return SD_ERR_STATE;
+// Lays the documents out in `text` and sorts by codes (sd_suffix.hip) into sa, with tok1 also writing
+// second-token column, samples and bucket table.  SD_ERR_STATE: not sorted, because the text
+// repeats itself too often, the entries do not fit, or the stream cannot be waited for, which is
+// how the host hears about it.
+static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
+                                 int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
+                                 bool new_intervals, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq;
+    if (N == 0 || !sd_code_fits(N, c->cfg.vocab) || !stream_can_wait(st)) {
+        sd_layout(c, tokens, offs, n_seq, n_tokens, text, st);
+        return SD_ERR_STATE;
+    }
     *c->h_flag = 0;
-    if (new_intervals || !c->code_ready) sd_code_intervals(c, text, N, st);
+    if (new_intervals || !c->code_ready) sd_code_intervals(c, tokens, n_seq, n_tokens, st);
     c->code_ready = true;
-    sd_code_sort(c, text, N, sa, tok1, c->h_flag, st);
+    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, c->h_flag, st);
     if (hipStreamSynchronize(st) != hipSuccess) return SD_ERR_HIP;
     return *const_cast<volatile int32_t *>(c->h_flag) ? SD_ERR_STATE : SD_OK;
 }
@@ -519,15 +467,10 @@ sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t
     c->g_N = N;
     c->g_tokens = n_tokens;
     c->g_docs = n_seq;
-    if (n_tokens > 0)
-        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_layout_text, dim3(nblk((n_tokens + layout_items(n_tokens) - 1) / layout_items(n_tokens))), dim3(TB), 0, d_tokens, d_offsets, n_seq, n_tokens, c->g_text, vocab, c->d_err, layout_items(n_tokens));
-    {
-        int64_t m = n_seq > SD_TEXT_PAD ? n_seq : SD_TEXT_PAD;
-        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_layout_marks, dim3(nblk(m)), dim3(TB), 0, d_offsets, n_seq, N, c->g_text);
-    }
+    const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, c->g_text, c->g_sa,
+                                         c->g_tok1, true, st);
+    if (rc != SD_ERR_STATE) return rc;
     if (N > 0) {
-        const sd_status rc = code_sorted_positions(c, c->g_text, N, c->g_sa, c->g_tok1, true, st);
-        if (rc != SD_ERR_STATE) return rc;
         const int cur = build_sorted_positions(c, c->g_text, N, c->g_tok1, st);
         if (cur < 0) return SD_ERR_HIP;
         // The sorted positions are the suffix array: the buffer they are in becomes g_sa and the
@@ -553,14 +496,9 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     const int32_t vocab = c->cfg.vocab;
     if (M == 0) return SD_OK;
     int32_t *ntext = c->g_text + N;
-    if (n_tokens > 0)
-        SD_LAUNCH(c, SD_K_INSERT, st, k_layout_text, dim3(nblk((n_tokens + layout_items(n_tokens) - 1) / layout_items(n_tokens))), dim3(TB), 0, d_tokens, d_offsets, n_seq, n_tokens, ntext, vocab, c->d_err, layout_items(n_tokens));
-    {
-        int64_t m = n_seq > SD_TEXT_PAD ? n_seq : SD_TEXT_PAD;
-        SD_LAUNCH(c, SD_K_INSERT, st, k_layout_marks, dim3(nblk(m)), dim3(TB), 0, d_offsets, n_seq, M, ntext);
-    }
     int cur = 0;
-    const sd_status rc = code_sorted_positions(c, ntext, M, (int32_t *)c->b_vals[0], nullptr, false, st);
+    const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, ntext,
+                                         (int32_t *)c->b_vals[0], nullptr, false, st);
     if (rc == SD_ERR_STATE) cur = build_sorted_positions(c, ntext, M, nullptr, st);
     if ((rc != SD_OK && rc != SD_ERR_STATE) || cur < 0) return SD_ERR_HIP;
     // b_vals[cur]: new positions in order; b_flags: their ranks in the old array; merged arrays

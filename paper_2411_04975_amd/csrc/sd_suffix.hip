@@ -17,7 +17,7 @@
 // numbers; and the second-token column of the index comes from the entries: only suffixes that
 // tie are ever looked up in the text.
 //
-// Bound: the memory system.  Per position 68 bytes in order (text read twice, code written and
+// Bound: the memory system.  Per position 72 bytes in order (tokens read, text and code written and
 // read, entries written and read once per pass, suffix array and second tokens written), and
 // for each one that ties one or two random cache lines, which are what costs: 10M gathers of 16 or
 // 64 bytes from a 40 MB text take 185 or 237 us, a copy of 680 MB 135 us.
@@ -71,8 +71,25 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wave
     return base + inc - v;
 }
 
+// first index in [0, n) with at(index) >= key, n if there is none, of a rising sequence; whole wave
+template <typename AT>
+__device__ __forceinline__ int wave_lower_bound(AT at, int n, int64_t key) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int step = (int)(((int64_t)hi - lo + 63) >> 6);
+        const int64_t i = (int64_t)lo + (int64_t)lane * step;
+        const int c = __popcll(__ballot(i < hi && at((int)(i < hi ? i : lo)) < key));
+        if (c == 0) break;
+        const int64_t to = (int64_t)lo + (int64_t)c * step;
+        lo = (int)(to - step + 1);
+        hi = to < hi ? (int)to : hi;
+    }
+    return lo;
+}
+
 // ---- the tokens' intervals ------------------------------------------------------------------
-// Counts of a sample of the text: C runs of 64 tokens, evenly spread.  A workgroup counts its
+// Counts of a sample of the tokens: C runs of 64 of them, evenly spread.  A workgroup counts its
 // runs in an LDS table first: a frequent token would otherwise be tens of thousands of atomic
 // additions to one address, at some 30 ns each.
 // What it found goes into one of several copies of the counts: frequent tokens lie next to each
@@ -84,8 +101,8 @@ constexpr int64_t SAMPLE_MAX = 32768;  // 16 * 64 * SAMPLE_MAX + 4 * 2^24, the w
 constexpr int RUNS_PER_WG = 16;
 constexpr int TABLE = 2048;
 
-__global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ text, int64_t N,
-                                                    int64_t runs, int64_t C, uint32_t *__restrict__ counts,
+__global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ tokens, int64_t n_tokens,
+                                                    int32_t vocab, int64_t runs, int64_t C, uint32_t *__restrict__ counts,
                                                     int copies, int32_t n_codes) {
     __shared__ uint32_t s_tag[TABLE], s_num[TABLE];
     constexpr uint32_t FREE = 0xffffffffu;
@@ -97,8 +114,9 @@ __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ 
 #pragma unroll
     for (int k = 0; k < RUNS_PER_WG / CW; k++) {
         const int64_t run = (int64_t)blockIdx.x * RUNS_PER_WG + k * CW + w;
-        const int64_t p = run < C ? (run * runs / C) * 64 + lane : N;
-        tok[k] = p < N ? text[p] : -2;
+        const int64_t p = run < C ? (run * runs / C) * 64 + lane : n_tokens;
+        tok[k] = p < n_tokens ? tokens[p] : -2;
+        if (p < n_tokens && (tok[k] < 0 || tok[k] >= vocab)) tok[k] = 0;  // (as it goes into the text)
     }
 #pragma unroll
     for (int k = 0; k < RUNS_PER_WG / CW; k++) {
@@ -123,9 +141,10 @@ __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ 
 // start with such a token share its interval.
 constexpr int CDF_ITEMS = 2, CDF_TILE = CT * CDF_ITEMS;
 
-// weight[c], in place of the first copy's count; clears the other copies
+// weight[c], in place of the first copy's count (of the end marker: `ends`); clears the other copies
 __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ counts, int copies,
-                                                     int32_t n_codes, uint32_t *__restrict__ partials) {
+                                                     int32_t n_codes, uint32_t ends,
+                                                     uint32_t *__restrict__ partials) {
     __shared__ uint32_t s_wave[CW];
     uint32_t sum = 0;
 #pragma unroll
@@ -137,7 +156,7 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
                 n += counts[(int64_t)q * n_codes + c];
                 counts[(int64_t)q * n_codes + c] = 0;
             }
-            n = 16u * n + 4u;
+            n = 16u * (c == 0 ? ends : n) + 4u;
             counts[c] = n;
             sum += n;
         }
@@ -184,32 +203,94 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
     }
 }
 
-// ---- codes of all positions, and how many fall into each bin of the first split per tile -----
+// ---- the text, the codes of its positions, and the first split's bins per tile ------------------
+// text = documents one after the other, an end marker behind each and SD_TEXT_PAD more behind the
+// last: document j starts at offs[j] + j.  The tile's documents are looked up once, in the offsets
+// in memory, and each position then among these in LDS.  What takes the time is the gather of the
+// intervals (one line of the L2 per position; 10M from a 512 KB table: 46 us), so the text is written
+// on the way (10M tokens, 128k of them different: 73 us together; text and codes by kernels of
+// their own took 53 and 55).
 constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
+constexpr int LDS_DOCS = 1024;
 
-template <int ITEMS>
-__global__ __launch_bounds__(CT) void k_code_keys(const int32_t *__restrict__ text, int64_t N,
-                                                  const uint32_t *__restrict__ cdf,
-                                                  uint32_t *__restrict__ keys, int shift, int bins,
-                                                  uint32_t *__restrict__ hist, int64_t ntiles) {
-    __shared__ uint2 s_code[KEY_ROUND + CODE_LOOK];  // (lower end, width) of each token's interval
-    __shared__ uint32_t s_hist[MAX_BINS];
+template <int ITEMS, bool CODES>
+__global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ tokens,
+                                               const int64_t *__restrict__ offs, int32_t n_seq,
+                                               int64_t n_tokens, int32_t *__restrict__ text, int32_t vocab,
+                                               int32_t *err, const uint32_t *__restrict__ cdf,
+                                               uint32_t *__restrict__ keys, int shift, int bins,
+                                               uint32_t *__restrict__ hist, int64_t ntiles, int per_chunk,
+                                               uint32_t *__restrict__ sums) {
+    __shared__ uint2 s_code[CODES ? KEY_ROUND + CODE_LOOK : 1];  // (lower end, width) of each token's interval
+    __shared__ uint32_t s_hist[CODES ? MAX_BINS : 1];
+    __shared__ int32_t s_start[LDS_DOCS + 1];  // documents' starts, counted from the tile's
+    __shared__ int32_t s_doc[2];
     const int tid = threadIdx.x;
-    for (int i = tid; i < bins; i += CT) s_hist[i] = 0;
-    for (int r = 0; r < ITEMS / 4; r++) {
-        const int64_t base = ((int64_t)blockIdx.x * ITEMS + r * 4) * CT;
-        if (base >= N) break;
-        __syncthreads();
-        // (the text carries more than CODE_LOOK end markers behind position N - 1)
-        for (int i = tid; i < KEY_ROUND + CODE_LOOK; i += CT) {
-            uint2 v = make_uint2(0u, 1u);
-            if (base + i < N + CODE_LOOK) {
-                // (both ends in one load: the lanes of a wave ask for 64 lines of the table)
-                const u32x2 ends = *reinterpret_cast<const u32x2 *>(cdf + (text[base + i] + 1));
-                v = make_uint2(ends.x, ends.y - ends.x);
-            }
-            s_code[i] = v;
+    const int64_t N = n_tokens + n_seq, tile0 = (int64_t)blockIdx.x * (CT * ITEMS);
+    auto start_of = [&](int32_t j) -> int64_t { return j <= n_seq ? offs[j] + j : N + 1; };
+    if (tid < 128 && tile0 < N) {  // documents of the tile's first position and of its last one
+        int64_t p = tid < 64 ? tile0 : tile0 + CT * ITEMS + CODE_LOOK - 1;
+        if (p > N - 1) p = N - 1;
+        const int j = wave_lower_bound([&](int i) { return offs[i] + i; }, n_seq, p + 1) - 1;
+        if ((tid & 63) == 0) s_doc[tid >> 6] = j < 0 ? 0 : j;
+    }
+    if (CODES)
+        for (int i = tid; i < bins; i += CT) s_hist[i] = 0;
+    __syncthreads();
+    const int32_t d0 = tile0 < N ? s_doc[0] : 0, nd = tile0 < N ? s_doc[1] - d0 + 1 : 0;
+    if (nd <= LDS_DOCS)
+        for (int i = tid; i <= nd; i += CT) {
+            const int64_t at = start_of(d0 + i) - tile0;
+            s_start[i] = at < -1 ? -1 : at > (1 << 30) ? 1 << 30 : (int32_t)at;
         }
+    __syncthreads();
+    // token at text position p (-1: end marker)
+    auto token_at = [&](int64_t p) -> int32_t {
+        if (p >= N) return SD_END_TOKEN;
+        int32_t lo = 0, hi = nd;  // last document that starts at or before p
+        int64_t next;
+        if (nd <= LDS_DOCS) {
+            const int32_t q = (int32_t)(p - tile0);
+            while (hi - lo > 1) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (s_start[mid] <= q) lo = mid; else hi = mid;
+            }
+            next = tile0 + s_start[lo + 1];
+        } else {
+            while (hi - lo > 1) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (start_of(d0 + mid) <= p) lo = mid; else hi = mid;
+            }
+            next = start_of(d0 + lo + 1);
+        }
+        const int64_t i = p - (d0 + lo);
+        return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
+    };
+    for (int r = 0; r < ITEMS / 4; r++) {
+        const int64_t base = tile0 + r * KEY_ROUND;
+        if (base >= N + SD_TEXT_PAD) break;
+        int32_t tok[5];
+#pragma unroll
+        for (int k = 0; k < 4; k++) tok[k] = token_at(base + k * CT + tid);
+        tok[4] = CODES && tid < CODE_LOOK ? token_at(base + KEY_ROUND + tid) : SD_END_TOKEN;
+#pragma unroll
+        for (int k = 0; k < 5; k++)
+            if (tok[k] != SD_END_TOKEN && (tok[k] < 0 || tok[k] >= vocab)) {
+                atomicOr(&err[SD_DEVERR_TOKEN], 1);
+                tok[k] = 0;
+            }
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (base + k * CT + tid < N + SD_TEXT_PAD) text[base + k * CT + tid] = tok[k];
+        if (!CODES) continue;
+        u32x2 ends[5];  // (both ends in one load)
+#pragma unroll
+        for (int k = 0; k < 5; k++)
+            if (k < 4 || tid < CODE_LOOK) ends[k] = *reinterpret_cast<const u32x2 *>(cdf + (tok[k] + 1));
+        __syncthreads();  // (the round before is done with the intervals)
+#pragma unroll
+        for (int k = 0; k < 5; k++)
+            if (k < 4 || tid < CODE_LOOK) s_code[k * CT + tid] = make_uint2(ends[k].x, ends[k].y - ends[k].x);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; k++) {
@@ -228,34 +309,58 @@ __global__ __launch_bounds__(CT) void k_code_keys(const int32_t *__restrict__ te
             atomicAdd(&s_hist[key >> shift], 1u);
         }
     }
+    if (!CODES || blockIdx.x >= ntiles) return;
     __syncthreads();
-    for (int i = tid; i < bins; i += CT) hist[(int64_t)i * ntiles + blockIdx.x] = s_hist[i];
+    uint32_t *row = hist + (int64_t)blockIdx.x * bins, *sum = sums + (int64_t)(blockIdx.x / per_chunk) * bins;
+    for (int i = tid; i < bins; i += CT) {
+        const uint32_t v = s_hist[i];
+        row[i] = v;
+        if (v) atomicAdd(&sum[i], v);
+    }
 }
 
-// one workgroup per bin: exclusive prefix sums along the bin's row of the (bin, tile) table
-__global__ __launch_bounds__(CT) void k_code_rowscan(uint32_t *__restrict__ hist, int64_t ntiles,
-                                                     uint32_t *__restrict__ total) {
+// Places instead of counts in the (tile, bin) table.  A workgroup takes a chunk of tiles, a thread
+// one or two bins: what lies before the chunk is known from the chunks' sums.  Workgroup 0 also
+// writes where the bins start.  (The table lies tile by tile: with a row per bin the tiles' stores
+// and loads were 4 bytes to a line, a quarter of the time of the 100M-entry split.)
+constexpr int MAX_CHUNKS = 256, MIN_PER_CHUNK = 32;
+
+__global__ __launch_bounds__(CT) void k_code_places(uint32_t *__restrict__ hist, int bins, int64_t ntiles,
+                                                    int per_chunk, const uint32_t *__restrict__ sums,
+                                                    int chunks, uint32_t *__restrict__ starts, uint32_t N) {
     __shared__ uint32_t s_wave[CW];
-    constexpr int PER = 4;
-    uint32_t *row = hist + (int64_t)blockIdx.x * ntiles;
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < ntiles; base += CT * PER) {
-        const int64_t i0 = base + (int64_t)threadIdx.x * PER;
-        uint32_t v[PER], sum = 0, tot;
+    uint32_t before[2] = {0, 0}, all[2] = {0, 0};
 #pragma unroll
-        for (int k = 0; k < PER; k++) {
-            v[k] = i0 + k < ntiles ? row[i0 + k] : 0u;
-            sum += v[k];
+    for (int q = 0; q < 2; q++) {
+        const int d = 2 * (int)threadIdx.x + q;
+        if (d >= bins) continue;
+#pragma unroll 8
+        for (int i = 0; i < chunks; i++) {
+            const uint32_t v = sums[(int64_t)i * bins + d];
+            all[q] += v;
+            before[q] += i < (int)blockIdx.x ? v : 0u;
         }
-        uint32_t ex = carry + block_excl_scan(sum, s_wave, &tot);
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            if (i0 + k < ntiles) row[i0 + k] = ex;
-            ex += v[k];
-        }
-        carry += tot;
     }
-    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+    uint32_t tot;
+    const uint32_t ex = block_excl_scan(all[0] + all[1], s_wave, &tot);
+    const int64_t t0 = (int64_t)blockIdx.x * per_chunk;
+    const int n = (int)(ntiles - t0 < per_chunk ? ntiles - t0 : per_chunk);
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int d = 2 * (int)threadIdx.x + q;
+        if (d >= bins) continue;
+        const uint32_t start = ex + (q ? all[0] : 0u);
+        if (blockIdx.x == 0) starts[d] = start;
+        uint32_t at = start + before[q];
+        uint32_t *col = hist + t0 * bins + d;
+#pragma unroll 8
+        for (int i = 0; i < n; i++) {
+            const uint32_t v = col[(int64_t)i * bins];
+            col[(int64_t)i * bins] = at;
+            at += v;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) starts[bins] = N;
 }
 
 // ---- splitting entries by a digit of the code --------------------------------------------------
@@ -315,14 +420,12 @@ __device__ __forceinline__ void split_tile(split_lds<ITEMS> &s, const uint64_t (
     }
 }
 
-// First split: codes in position order -> entries.  `starts`, if given, receives the bins' places
-// (there is no second split), starts[bins] = N.
+// First split: codes in position order -> entries.  Clears the chunks' sums for the next input.
 template <int ITEMS>
 __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ keys,
                                                    const int32_t *__restrict__ text, int64_t N, entry_shape f,
-                                                   const uint32_t *__restrict__ hist,
-                                                   const uint32_t *__restrict__ total, int64_t ntiles,
-                                                   uint64_t *__restrict__ out, uint32_t *__restrict__ starts) {
+                                                   const uint32_t *__restrict__ hist, int chunks,
+                                                   uint32_t *__restrict__ sums, uint64_t *__restrict__ out) {
     __shared__ split_lds<ITEMS> s;
     const int tid = threadIdx.x, bins = 1 << f.bits1;
     const int64_t base = (int64_t)blockIdx.x * (CT * ITEMS);
@@ -338,48 +441,33 @@ __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ 
         const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
         e[k] = (((rest << f.tok_bits) | tok) << f.pos_bits) | (uint64_t)(base + j);
     }
-    {
-        const int d = 2 * tid;
-        const uint32_t a = d < bins ? total[d] : 0u, b = d + 1 < bins ? total[d + 1] : 0u;
-        const uint32_t ha = d < bins ? hist[(int64_t)d * ntiles + blockIdx.x] : 0u;
-        const uint32_t hb = d + 1 < bins ? hist[(int64_t)(d + 1) * ntiles + blockIdx.x] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan(a + b, s.wave, &tot);
-        if (d < bins) s.to[d] = ex + ha;
-        if (d + 1 < bins) s.to[d + 1] = ex + a + hb;
-        if (starts && blockIdx.x == 0) {
-            if (d < bins) starts[d] = ex;
-            if (d + 1 < bins) starts[d + 1] = ex + a;
-            if (tid == 0) starts[bins] = (uint32_t)N;
-        }
+    for (int i = tid; i < bins; i += CT) {
+        s.to[i] = hist[(int64_t)blockIdx.x * bins + i];
+        if ((int)blockIdx.x < chunks) sums[(int64_t)blockIdx.x * bins + i] = 0;
     }
     split_tile<ITEMS>(s, e, digit, cnt, bins, out);
 }
 
 // A bin of the first split: where it starts and how long it is.
 struct bin_place { uint32_t start, size; };
-__device__ __forceinline__ bin_place first_bin(const uint32_t *__restrict__ total, int bin,
-                                               uint32_t *s_wave) {
-    uint32_t v = 0, tot;
-    for (int i = threadIdx.x; i < bin; i += CT) v += total[i];
-    (void)block_excl_scan(v, s_wave, &tot);
-    return {tot, total[bin]};
+__device__ __forceinline__ bin_place first_bin(const uint32_t *__restrict__ starts1, int bin) {
+    return {starts1[bin], starts1[bin + 1] - starts1[bin]};
 }
 
 constexpr int SPLIT2_ITEMS = 12, SPLIT2_TILE = CT * SPLIT2_ITEMS;
 
 // Second split, inside every bin of the first one (blockIdx.y; the bin's tiles are shared out
-// over blockIdx.x).  The counts of bin b lie at row_of(b): (digit, tile of the bin).
+// over blockIdx.x).  The counts of bin b lie at row_of(b): (tile of the bin, digit).
 __device__ __forceinline__ int64_t row_of(bin_place p, int bin, int bins2) {
     return ((int64_t)(p.start / SPLIT2_TILE) + bin) * bins2;  // tiles of the bins before, at most
 }
 
 __global__ __launch_bounds__(CT) void k_code_hist2(const uint64_t *__restrict__ in,
-                                                   const uint32_t *__restrict__ total, int shift,
+                                                   const uint32_t *__restrict__ starts1, int shift,
                                                    int bins2, uint32_t *__restrict__ hist2) {
-    __shared__ uint32_t s_hist[MAX_BINS], s_wave[CW];
+    __shared__ uint32_t s_hist[MAX_BINS];
     const int bin = blockIdx.y, tid = threadIdx.x;
-    const bin_place p = first_bin(total, bin, s_wave);
+    const bin_place p = first_bin(starts1, bin);
     const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
     const uint32_t mask = (uint32_t)bins2 - 1u;
     uint32_t *row = hist2 + row_of(p, bin, bins2);
@@ -397,54 +485,51 @@ __global__ __launch_bounds__(CT) void k_code_hist2(const uint64_t *__restrict__ 
         for (int k = 0; k < SPLIT2_ITEMS; k++)
             if (j0 + k * CT + tid < p.size) atomicAdd(&s_hist[(uint32_t)(e[k] >> shift) & mask], 1u);
         __syncthreads();
-        for (int i = tid; i < bins2; i += CT) row[(int64_t)i * nt + t] = s_hist[i];
+        for (int i = tid; i < bins2; i += CT) row[(int64_t)t * bins2 + i] = s_hist[i];
         __syncthreads();
     }
 }
 
-// one workgroup per bin of the first split: places of its (digit, tile) counts, and of its buckets
-__global__ __launch_bounds__(CT) void k_code_scan2(const uint32_t *__restrict__ total, int bins2,
-                                                   uint32_t *__restrict__ hist2,
-                                                   uint32_t *__restrict__ starts, int64_t N) {
+// one workgroup per bin of the first split: places of its tiles' digits, and of its buckets
+__global__ __launch_bounds__(CT) void k_code_places2(const uint32_t *__restrict__ starts1, int bins2,
+                                                     uint32_t *__restrict__ hist2,
+                                                     uint32_t *__restrict__ starts, uint32_t N) {
     __shared__ uint32_t s_wave[CW];
-    constexpr int PER = 4;
-    const int bin = blockIdx.x, tid = threadIdx.x;
-    const bin_place p = first_bin(total, bin, s_wave);
+    const int bin = blockIdx.x;
+    const bin_place p = first_bin(starts1, bin);
     const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
-    const int n = bins2 * nt;
-    uint32_t *row = hist2 + row_of(p, bin, bins2), *my_starts = starts + (int64_t)bin * bins2;
-    if (bin == (int)gridDim.x - 1 && tid == 0) starts[(int64_t)gridDim.x * bins2] = (uint32_t)N;
-    if (nt == 0)
-        for (int i = tid; i < bins2; i += CT) my_starts[i] = p.start;
-    uint32_t carry = p.start;
-    for (int base = 0; base < n; base += CT * PER) {
-        const int i0 = base + tid * PER;
-        uint32_t v[PER], sum = 0, tot;
+    uint32_t *row = hist2 + row_of(p, bin, bins2);
+    uint32_t all[2] = {0, 0}, tot;
 #pragma unroll
-        for (int k = 0; k < PER; k++) {
-            v[k] = i0 + k < n ? row[i0 + k] : 0u;
-            sum += v[k];
-        }
-        uint32_t ex = carry + block_excl_scan(sum, s_wave, &tot);
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            if (i0 + k < n) {
-                row[i0 + k] = ex;
-                if ((i0 + k) % nt == 0) my_starts[(i0 + k) / nt] = ex;
-            }
-            ex += v[k];
-        }
-        carry += tot;
+    for (int q = 0; q < 2; q++) {
+        const int d = 2 * (int)threadIdx.x + q;
+        if (d >= bins2) continue;
+#pragma unroll 8
+        for (int i = 0; i < nt; i++) all[q] += row[(int64_t)i * bins2 + d];
     }
+    uint32_t at = p.start + block_excl_scan(all[0] + all[1], s_wave, &tot);
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int d = 2 * (int)threadIdx.x + q;
+        if (d >= bins2) continue;
+        starts[(int64_t)bin * bins2 + d] = at;
+#pragma unroll 8
+        for (int i = 0; i < nt; i++) {
+            const uint32_t v = row[(int64_t)i * bins2 + d];
+            row[(int64_t)i * bins2 + d] = at;
+            at += v;
+        }
+    }
+    if (bin == (int)gridDim.x - 1 && threadIdx.x == 0) starts[(int64_t)gridDim.x * bins2] = N;
 }
 
 __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__ in,
-                                                    const uint32_t *__restrict__ total, int shift,
+                                                    const uint32_t *__restrict__ starts1, int shift,
                                                     int bins2, const uint32_t *__restrict__ hist2,
                                                     uint64_t *__restrict__ out) {
     __shared__ split_lds<SPLIT2_ITEMS> s;
     const int bin = blockIdx.y, tid = threadIdx.x;
-    const bin_place p = first_bin(total, bin, s.wave);
+    const bin_place p = first_bin(starts1, bin);
     const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
     const uint32_t *row = hist2 + row_of(p, bin, bins2);
     for (int t = blockIdx.x; t < nt; t += gridDim.x) {
@@ -460,7 +545,7 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 #pragma unroll
         for (int k = 0; k < SPLIT2_ITEMS; k++) digit[k] = (uint32_t)(e[k] >> shift) & ((uint32_t)bins2 - 1u);
         __syncthreads();  // (the tile before is written out)
-        for (int i = tid; i < bins2; i += CT) s.to[i] = row[(int64_t)i * nt + t];
+        for (int i = tid; i < bins2; i += CT) s.to[i] = row[(int64_t)t * bins2 + i];
         split_tile<SPLIT2_ITEMS>(s, e, digit, cnt, bins2, out);
     }
 }
@@ -513,22 +598,6 @@ __device__ __forceinline__ uint64_t bits_from(const uint32_t *row, int s, bool *
     return uniform64(m);
 }
 
-// first index in [0, n) of a rising table with table[index] >= key, n if there is none; whole wave
-__device__ __forceinline__ int wave_lower_bound(const uint32_t *__restrict__ table, int n, uint64_t key) {
-    const int lane = threadIdx.x & 63;
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int step = (hi - lo + 63) >> 6;
-        const int i = lo + lane * step;
-        const int c = __popcll(__ballot(i < hi && table[i < hi ? i : lo] < key));
-        if (c == 0) break;
-        const int to = lo + c * step;
-        lo = to - step + 1;
-        hi = to < hi ? to : hi;
-    }
-    return lo;
-}
-
 template <int TOK>
 __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
                                                   const uint32_t *__restrict__ starts, int64_t N, entry_shape f,
@@ -548,7 +617,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, low_bits = f.pos_bits + f.tok_bits;
     if (w < 2) {  // buckets that start at or behind the two ends of the workgroup's entries
-        const int b = wave_lower_bound(starts, (1 << bits) + 1, ((uint64_t)blockIdx.x + w) * SORT_TILE);
+        const int b = wave_lower_bound([&](int i) { return (int64_t)starts[i]; }, (1 << bits) + 1, ((int64_t)blockIdx.x + w) * SORT_TILE);
         if (lane == 0) s_range[w] = b > 1 << bits ? 1 << bits : b;
     }
     uint32_t *cnt = reinterpret_cast<uint32_t *>(s_area);
@@ -572,7 +641,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     }
     for (int i = tid; i <= nb; i += CT) s_start[i] = (uint32_t)(starts[b0 + i] - a);
     if (bucket && (w & 3) == 2) {  // tokens whose intervals start in this workgroup's part of the codes
-        const int c = wave_lower_bound(cdf, n_codes + 1, (uint64_t)(b0 + (w > 3 ? nb : 0)) << down);
+        const int c = wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)(b0 + (w > 3 ? nb : 0)) << down);
         if (lane == 0) s_range[2 + (w > 3)] = c;
     }
     __syncthreads();
@@ -852,10 +921,11 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
 }
 
 // ---- host side --------------------------------------------------------------------------------
-// Leading code bits that are split off: buckets of 128 to 256 entries, so that the share of a
+// Leading code bits that are split off: buckets of 256 to 512 entries, so that the share of a
 // workgroup of k_code_sort, whole buckets, is SORT_TILE give or take one of them, and a bucket may
-// be ten times as large as the average before it no longer fits.  Up to 10 bits go in one
-// split; small inputs take buckets of up to 512 for that (a split is three launches).
+// be five times as large as the average before it no longer fits.  (Buckets half that size: 100M
+// entries then take a split of 1024 ways, whose runs are 6 entries; 0.83 instead of 0.70 ms.)
+// Up to 10 bits go in one split (three launches).
 // Tiles of 6144 entries leave as runs of 24 entries per bin and more; small inputs take tiles of
 // 2048 so that they are spread over more compute units.
 struct split_plan {
@@ -864,14 +934,11 @@ struct split_plan {
 };
 split_plan plan_for(int64_t N) {
     int bits = 1;
-    while (bits < 2 * MAX_BITS && (N >> bits) > 256) bits++;
+    while (bits < 2 * MAX_BITS && (N >> bits) > 512) bits++;
     split_plan p;
     p.bits1 = bits;
     p.bits2 = 0;
-    if (bits > MAX_BITS) {
-        if ((N >> MAX_BITS) <= 512) p.bits1 = MAX_BITS;
-        else { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
-    }
+    if (bits > MAX_BITS) { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
     p.small_tiles = N <= (1 << 20);
     return p;
 }
@@ -879,41 +946,56 @@ constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 
 }  // namespace
 
-// Room that the tables of an input of up to `cap` positions take: words of b_hist and b_starts.
-void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words) {
+// Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts, code_sums.
+void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words) {
     int64_t h = 0, s = 0;
     const int64_t sizes[] = {cap, 1 << 20, (int64_t)512 << MAX_BITS};
     for (int64_t n : sizes) {
         if (n > cap) n = cap;
         const split_plan p = plan_for(n);
         const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
-        int64_t x = ((n + tile - 1) / tile + 1) << p.bits1;
+        int64_t x = ((n + tile - 1) / tile) << p.bits1;
         if (p.bits2) x += (n / SPLIT2_TILE + (1ll << p.bits1) + 1) << p.bits2;
         h = x > h ? x : h;
         const int64_t y = (1ll << (p.bits1 + p.bits2)) + 1;
         s = y > s ? y : s;
     }
-    *hist_words = h + MAX_BINS;
+    *hist_words = h + MAX_BINS + 1;
     *start_words = s;
+    *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
 }
 
 int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
 int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? 8 : 1; }
 
-void sd_code_intervals(sd_ctx *c, const int32_t *text, int64_t N, hipStream_t st) {
-    const int64_t runs = (N + 63) / 64;
+void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int32_t n_seq, int64_t n_tokens, hipStream_t st) {
+    const int64_t runs = (n_tokens + 63) / 64;
     int64_t C = runs / SAMPLE_ONE_IN > SAMPLE_MIN ? runs / SAMPLE_ONE_IN : SAMPLE_MIN;
     if (C > SAMPLE_MAX) C = SAMPLE_MAX;
     if (C > runs) C = runs;
+    int64_t ends = n_tokens > 0 ? (int64_t)((double)n_seq * (double)(C * 64) / (double)n_tokens) + 1 : 1;
+    if (ends > (1 << 20)) ends = 1 << 20;
     const int32_t n_codes = c->cfg.vocab + 1;
     const int copies = sd_code_copies(c->cfg.vocab);
     const unsigned parts = (unsigned)sd_code_parts(c->cfg.vocab);  // the last one also writes cdf[n_codes]
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_sample, dim3((unsigned)((C + RUNS_PER_WG - 1) / RUNS_PER_WG)), dim3(CT), 0,
-              text, N, runs, C, c->code_cnt, copies, n_codes);
+    if (C > 0)
+        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_sample, dim3((unsigned)((C + RUNS_PER_WG - 1) / RUNS_PER_WG)), dim3(CT), 0,
+                  tokens, n_tokens, c->cfg.vocab, runs, C, c->code_cnt, copies, n_codes);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_weights, dim3(parts), dim3(CT), 0, c->code_cnt, copies, n_codes,
-              c->code_partials);
+              (uint32_t)ends, c->code_partials);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_cdf, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
               c->code_partials, c->code_cdf);
+}
+
+static dim3 layout_grid(int64_t N, int items) { return dim3((unsigned)((N + SD_TEXT_PAD + CT * items - 1) / (CT * items))); }
+
+void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
+               int32_t *text, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq;
+    const bool small = plan_for(N).small_tiles;
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (small ? k_layout<SMALL_ITEMS, false> : k_layout<LARGE_ITEMS, false>),
+              layout_grid(N, small ? SMALL_ITEMS : LARGE_ITEMS), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
+              c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (uint32_t *)nullptr, 0, 0, (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr);
 }
 
 // An entry's 64 bits: whether they hold what is needed of an input.
@@ -934,11 +1016,12 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
-// Sorts the N >= 1 positions of `text` into sa; with tok1 also writes the second-token column, its
+// Lays the documents out in `text` and sorts its N >= 1 positions into sa; with tok1 also writes the second-token column, its
 // samples and the bucket table.  *flag (pinned host memory, zero before) becomes 1 if the text is too
-// repetitive: then the outputs are not complete.
-void sd_code_sort(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa, int32_t *tok1, int32_t *flag,
-                  hipStream_t st) {
+// repetitive: then only the text is complete.
+void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
+                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *flag, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq;
     const split_plan p = plan_for(N);
     entry_shape f;
     (void)shape_for(N, c->cfg.vocab, &f);
@@ -947,21 +1030,26 @@ void sd_code_sort(sd_ctx *c, const int32_t *text, int64_t N, int32_t *sa, int32_
     const int64_t ntiles = (N + tile - 1) / tile;
     uint32_t *keys = c->b_flags;
     uint64_t *ent1 = c->b_keys[0], *ent2 = c->b_keys[1];
-    uint32_t *hist = c->b_hist, *total = hist + ntiles * bins1, *hist2 = total + bins1;
+    uint32_t *hist = c->b_hist, *starts1 = f.bits2 ? hist + ntiles * bins1 : c->b_starts;
+    uint32_t *hist2 = hist + ntiles * bins1 + bins1 + 1;
+    int per_chunk = (int)((ntiles + MAX_CHUNKS - 1) / MAX_CHUNKS);
+    if (per_chunk < MIN_PER_CHUNK) per_chunk = MIN_PER_CHUNK;
+    const int chunks = (int)((ntiles + per_chunk - 1) / per_chunk);
     const dim3 grid1((unsigned)ntiles), block(CT);
-    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_code_keys<SMALL_ITEMS> : k_code_keys<LARGE_ITEMS>),
-              grid1, block, 0, text, N, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles);
-    SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_rowscan, dim3(bins1), block, 0, hist, ntiles, total);
+    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_layout<SMALL_ITEMS, true> : k_layout<LARGE_ITEMS, true>),
+              layout_grid(N, p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS), block, 0, tokens, offs, n_seq, n_tokens, text,
+              c->cfg.vocab, c->d_err, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles, per_chunk, c->code_sums);
+    SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
+              c->code_sums, chunks, starts1, (uint32_t)N);
     SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (p.small_tiles ? k_code_split<SMALL_ITEMS> : k_code_split<LARGE_ITEMS>),
-              grid1, block, 0, keys, text, N, f, hist, total, ntiles, ent1,
-              p.bits2 ? (uint32_t *)nullptr : c->b_starts);
+              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, ent1);
     if (p.bits2) {
         const int64_t per_bin = (N >> p.bits1) / SPLIT2_TILE + 1;
         const dim3 grid2((unsigned)(per_bin + per_bin / 4), (unsigned)bins1);
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
-        SD_LAUNCH(c, SD_K_SORT_HIST, st, k_code_hist2, grid2, block, 0, ent1, total, shift, bins2, hist2);
-        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_scan2, dim3(bins1), block, 0, total, bins2, hist2, c->b_starts, N);
-        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, total, shift, bins2, hist2, ent2);
+        SD_LAUNCH(c, SD_K_SORT_HIST, st, k_code_hist2, grid2, block, 0, ent1, starts1, shift, bins2, hist2);
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places2, dim3(bins1), block, 0, starts1, bins2, hist2, c->b_starts, (uint32_t)N);
+        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, shift, bins2, hist2, ent2);
         ent1 = ent2;
     }
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
