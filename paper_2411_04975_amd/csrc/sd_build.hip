@@ -446,7 +446,7 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 // how the host hears about it.
 static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
                                  int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
-                                 bool new_intervals, hipStream_t st) {
+                                 int32_t *bucket, bool new_intervals, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     if (N == 0 || !sd_code_fits(N, c->cfg.vocab) || !stream_can_wait(st)) {
         sd_layout(c, tokens, offs, n_seq, n_tokens, text, st);
@@ -455,8 +455,8 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
     *c->h_flag = 0;
     if (new_intervals || !c->code_ready) sd_code_intervals(c, tokens, n_seq, n_tokens, st);
     c->code_ready = true;
-    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, c->h_flag, st);
-    if (hipStreamSynchronize(st) != hipSuccess) return SD_ERR_HIP;
+    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, c->h_flag, c->code_asked, st);
+    if (hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;  // (the sort is still running)
     return *const_cast<volatile int32_t *>(c->h_flag) ? SD_ERR_STATE : SD_OK;
 }
 
@@ -468,7 +468,7 @@ sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t
     c->g_tokens = n_tokens;
     c->g_docs = n_seq;
     const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, c->g_text, c->g_sa,
-                                         c->g_tok1, true, st);
+                                         c->g_tok1, c->g_bucket, true, st);
     if (rc != SD_ERR_STATE) return rc;
     if (N > 0) {
         const int cur = build_sorted_positions(c, c->g_text, N, c->g_tok1, st);
@@ -498,7 +498,7 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     int32_t *ntext = c->g_text + N;
     int cur = 0;
     const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, ntext,
-                                         (int32_t *)c->b_vals[0], nullptr, false, st);
+                                         (int32_t *)c->b_vals[0], nullptr, nullptr, false, st);
     if (rc == SD_ERR_STATE) cur = build_sorted_positions(c, ntext, M, nullptr, st);
     if ((rc != SD_OK && rc != SD_ERR_STATE) || cur < 0) return SD_ERR_HIP;
     // b_vals[cur]: new positions in order; b_flags: their ranks in the old array; merged arrays

@@ -66,6 +66,8 @@ struct sd_ctx {
     uint32_t *code_sums = nullptr;      // [chunks of tiles][bins], zero between builds
     bool code_ready = false;            // code_cdf holds the intervals of some text
     uint32_t *b_starts = nullptr;       // first entry of every bucket
+    uint32_t *b_ranges = nullptr;       // what each workgroup of the sort in LDS takes
+    hipEvent_t code_asked = nullptr;    // where h_flag is known
     int32_t *h_flag = nullptr;          // pinned: the text was too repetitive for the codes
 
     // ---- per-request contexts -----------------------------------------
@@ -101,13 +103,15 @@ struct sd_ctx {
 
 // ---- launchers implemented in the other translation units ---------------
 // suffix sorting by codes: room for its tables, intervals from a sample of the tokens, the sort
-void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words);
+void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
+                  int64_t *range_words);
 bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int32_t n_seq, int64_t n_tokens, hipStream_t st);
 void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
-                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *flag, hipStream_t st);
+                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, int32_t *flag,
+                  hipEvent_t asked, hipStream_t st);
 // the documents' text alone
 void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                int32_t *text, hipStream_t st);

@@ -551,7 +551,7 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 }
 
 // ---- ordering whole buckets in LDS ------------------------------------------------------------
-// A workgroup takes the buckets that start in its SORT_TILE entries: codes are spread evenly, so
+// A workgroup takes the buckets that start in its tile of the entries: codes are spread evenly, so
 // one count over equal parts of the buckets' code ranges puts every entry within a few places of
 // its own, and counting the lower entries of its part there.  From there on a wave takes care of
 // its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
@@ -562,12 +562,52 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 //
 // Tokens are compared as two 64-bit words: three of 21 bits each, two of 32 for vocabularies
 // beyond that.
-constexpr int SORT_TILE = 2048;
+constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072;
 constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
 constexpr int SORT_PARTS = 4096;
 constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
+
+// What the tile's workgroup will take, and whether it can.  A wave finds where a tile's buckets
+// start; the eighth wave of a workgroup looks at the next workgroup's first tile.  (On its own, before
+// the sort: the host hears from it while the sort is running.)
+struct sort_range {
+    uint32_t bucket;   // first bucket that starts in the tile or behind it
+    uint32_t filled;   // the last one that starts there: it is not empty
+    uint32_t at;       // its place
+    uint32_t code;     // first token whose interval starts in `bucket` or behind it
+};
+
+__global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__ starts, int64_t N, int bits,
+                                                    int tile, int tiles, const uint32_t *__restrict__ cdf,
+                                                    int32_t n_codes, sort_range *__restrict__ ranges,
+                                                    int32_t *too_long) {
+    __shared__ sort_range s_range[CW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
+    const int t = (int)blockIdx.x * (CW - 1) + w;
+    if (t <= tiles) {
+        auto start = [&](int i) { return (int64_t)starts[i]; };
+        const int b = t == tiles ? buckets : wave_lower_bound(start, buckets, (int64_t)t * tile);
+        const uint32_t at = starts[b];
+        int filled = b;
+        if (b < buckets) {
+            const uint64_t m = __ballot(b + 1 + lane > buckets || starts[b + 1 + lane] > at);
+            filled = m ? b + __builtin_ctzll(m) : wave_lower_bound(start, buckets, (int64_t)at + 1) - 1;
+        }
+        const int c = t == tiles ? n_codes + 1
+                                 : wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)b << (32 - bits));
+        if (lane == 0) {
+            s_range[w] = {(uint32_t)b, (uint32_t)filled, at, (uint32_t)c};
+            if (w < CW - 1 || t == tiles) ranges[t] = s_range[w];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < CW - 1 && (int)blockIdx.x * (CW - 1) + (int)threadIdx.x < tiles) {
+        const sort_range r = s_range[threadIdx.x], z = s_range[threadIdx.x + 1];
+        if (z.bucket > r.bucket && (z.at - r.at > SORT_CAP || z.bucket - r.filled > SORT_BUCKETS)) *too_long = 1;
+    }
+}
 
 template <int TOK>
 struct token_words { uint64_t a, b; };
@@ -600,12 +640,12 @@ __device__ __forceinline__ uint64_t bits_from(const uint32_t *row, int s, bool *
 
 template <int TOK>
 __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
-                                                  const uint32_t *__restrict__ starts, int64_t N, entry_shape f,
+                                                  const uint32_t *__restrict__ starts,
+                                                  const sort_range *__restrict__ ranges, int64_t N, entry_shape f,
                                                   const int32_t *__restrict__ text, int32_t D,
                                                   const uint32_t *__restrict__ cdf, int32_t n_codes,
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
-                                                  int32_t *__restrict__ samples,
-                                                  int32_t *__restrict__ bucket, int32_t *too_long) {
+                                                  int32_t *__restrict__ samples, int32_t *__restrict__ bucket) {
     __shared__ uint64_t s_entry[SORT_CAP];         // later positions by place, and lists
     __shared__ uint4 s_area[SORT_PARTS / 8];       // counts per part, two per word; later windows
     __shared__ uint32_t s_start[SORT_BUCKETS + 1];  // places of the workgroup's buckets
@@ -613,25 +653,21 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     __shared__ uint32_t s_done[SORT_CAP / 32];       // bit per place: see below
     __shared__ uint64_t s_class[2][SORT_CAP / 64 + 2 * CW];
     __shared__ uint32_t s_wave[CW];
-    __shared__ int s_range[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int bits = f.bits1 + f.bits2, down = 32 - bits, low_bits = f.pos_bits + f.tok_bits;
-    if (w < 2) {  // buckets that start at or behind the two ends of the workgroup's entries
-        const int b = wave_lower_bound([&](int i) { return (int64_t)starts[i]; }, (1 << bits) + 1, ((int64_t)blockIdx.x + w) * SORT_TILE);
-        if (lane == 0) s_range[w] = b > 1 << bits ? 1 << bits : b;
+    const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
+    const sort_range here_r = ranges[blockIdx.x], next_r = ranges[blockIdx.x + 1];
+    const int b0 = (int)here_r.filled, nb = (int)next_r.bucket - b0;
+    const int64_t a = here_r.at, z = next_r.at;
+    if (next_r.bucket == here_r.bucket || nb > SORT_BUCKETS || z - a > SORT_CAP) return;  // (nothing, or given up)
+    if (z == a) {  // nothing but empty buckets
+        if (bucket)
+            for (int c = (int)here_r.code + tid; c < (int)next_r.code; c += CT) bucket[c] = (int32_t)a;
+        return;
     }
     uint32_t *cnt = reinterpret_cast<uint32_t *>(s_area);
     s_area[tid] = make_uint4(0u, 0u, 0u, 0u);
     if (tid < SORT_CAP / 32 + 4) s_first[tid] = 0;
     if (tid < SORT_CAP / 32) s_done[tid] = 0;
-    __syncthreads();
-    const int b0 = s_range[0], nb = s_range[1] - b0;
-    const int64_t a = starts[b0], z = starts[b0 + nb];
-    if (nb == 0) return;
-    if (nb > SORT_BUCKETS || z - a > SORT_CAP) {
-        if (tid == 0) *too_long = 1;
-        return;
-    }
     const int n = (int)(z - a);
     uint64_t e[SORT_ITEMS];
 #pragma unroll
@@ -640,10 +676,6 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
         e[k] = j < n ? in[a + j] : 0ull;
     }
     for (int i = tid; i <= nb; i += CT) s_start[i] = (uint32_t)(starts[b0 + i] - a);
-    if (bucket && (w & 3) == 2) {  // tokens whose intervals start in this workgroup's part of the codes
-        const int c = wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)(b0 + (w > 3 ? nb : 0)) << down);
-        if (lane == 0) s_range[2 + (w > 3)] = c;
-    }
     __syncthreads();
     // parts: 2^fine per bucket
     const int in_bucket = f.key_bits - f.bits2;
@@ -707,8 +739,12 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     if (bucket) {
         // bucket[c] = first place whose suffix starts with a token code >= c: the entries before
         // it are those with codes below the interval of c
-        for (int c = s_range[2] + tid; c < s_range[3]; c += CT) {
+        for (int c = (int)here_r.code + tid; c < (int)next_r.code; c += CT) {
             const uint32_t end = cdf[c];
+            if ((int)(end >> down) < b0) {
+                bucket[c] = (int32_t)a;
+                continue;
+            }
             const uint32_t key = ((end & (uint32_t)((1ull << down) - 1ull)) >> f.key_drop);  // inside the bucket
             const uint32_t p = (((end >> down) - (uint32_t)b0) << fine) + (key >> (in_bucket - fine));
             int at = part_start(p);
@@ -716,7 +752,6 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             while (at < to && ((uint32_t)(s_entry[at] >> low_bits) & key_mask) < key) at++;
             bucket[c] = (int32_t)(a + at);
         }
-        if (z == N && tid == 0) bucket[n_codes] = (int32_t)N;
     }
     uint32_t pos_k[SORT_ITEMS];
 #pragma unroll
@@ -942,12 +977,23 @@ split_plan plan_for(int64_t N) {
     p.small_tiles = N <= (1 << 20);
     return p;
 }
+// Entries per workgroup of k_code_sort, three of which fit a compute unit: as many whole rounds of
+// workgroups as N makes at SORT_TILE_MIN, rounded down (2.2M entries: one round instead of 1.4).
+int sort_tile_for(int64_t N, int n_cu) {
+    const int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
+    int64_t rounds = N / (slots * SORT_TILE_MIN);
+    if (rounds < 1) rounds = 1;
+    const int64_t t = (N + rounds * slots - 1) / (rounds * slots);
+    return (int)(t < SORT_TILE_MIN ? SORT_TILE_MIN : t > SORT_TILE_MAX ? SORT_TILE_MAX : t);
+}
 constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 
 }  // namespace
 
-// Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts, code_sums.
-void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words) {
+// Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts, code_sums and
+// b_ranges.
+void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
+                  int64_t *range_words) {
     int64_t h = 0, s = 0;
     const int64_t sizes[] = {cap, 1 << 20, (int64_t)512 << MAX_BITS};
     for (int64_t n : sizes) {
@@ -963,6 +1009,7 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *hist_words = h + MAX_BINS + 1;
     *start_words = s;
     *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
+    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)(sizeof(sort_range) / 4);
 }
 
 int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
@@ -1016,11 +1063,13 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
-// Lays the documents out in `text` and sorts its N >= 1 positions into sa; with tok1 also writes the second-token column, its
-// samples and the bucket table.  *flag (pinned host memory, zero before) becomes 1 if the text is too
-// repetitive: then only the text is complete.
+// Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
+// given, receives the second-token column, bucket the table of first places by token code.
+// *flag (pinned host memory, zero before) becomes 1 if the text is too repetitive: then only the text
+// is complete.  `asked` is recorded where that is known.
 void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
-                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *flag, hipStream_t st) {
+                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, int32_t *flag,
+                  hipEvent_t asked, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     const split_plan p = plan_for(N);
     entry_shape f;
@@ -1052,8 +1101,12 @@ void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
         SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, shift, bins2, hist2, ent2);
         ent1 = ent2;
     }
+    const int sort_tile = sort_tile_for(N, c->n_cu), tiles = (int)((N + sort_tile - 1) / sort_tile);
+    sort_range *ranges = reinterpret_cast<sort_range *>(c->b_ranges);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((tiles + 1 + CW - 2) / (CW - 1))), block, 0,
+              c->b_starts, N, f.bits1 + f.bits2, sort_tile, tiles, c->code_cdf, c->cfg.vocab + 1, ranges, flag);
+    (void)hipEventRecord(asked, st);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
-              dim3((unsigned)((N + SORT_TILE - 1) / SORT_TILE)), block, 0, ent1, c->b_starts, N, f, text,
-              c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s,
-              tok1 ? c->g_bucket : (int32_t *)nullptr, flag);
+              dim3((unsigned)tiles), block, 0, ent1, c->b_starts, ranges, N, f, text, c->cfg.D, c->code_cdf,
+              c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
