@@ -63,6 +63,7 @@ struct sd_ctx {
     uint32_t *code_cdf = nullptr;       // [vocab + 2]: lower end of each token code's interval
     uint32_t *code_cnt = nullptr;       // [copies][vocab + 1]: counts of a sample, zero between builds
     uint32_t *code_partials = nullptr;
+    int32_t *code_bucket = nullptr;     // [vocab + 2]: bucket table of the documents of an insertion
     uint32_t *code_sums = nullptr;      // [chunks of tiles][bins], zero between builds
     bool code_ready = false;            // code_cdf holds the intervals of some text
     uint32_t *b_starts = nullptr;       // first entry of every bucket

@@ -78,3 +78,27 @@ def test_repeated_phrase(times):
         _check(g, docs, D)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("n_old,n_new,spread", [
+    (1, 1, 1), (1, 3000, 1), (2047, 7, 1), (2048, 4000, 0), (2049, 300, 1), (9000, 2500, 0), (70_001, 5, 1)])
+def test_insert_places(n_old, n_new, spread):
+    """Around the tiles of the merge; without `spread` all new suffixes go between two old ones."""
+    rng = np.random.default_rng(n_old)
+    D, vocab = 16, 4000
+    old = rng.integers(0, vocab, n_old).astype(np.int32)
+    if spread:
+        new = rng.integers(0, vocab, n_new).astype(np.int32)
+    else:
+        old[old == 2000] = 1999
+        new = np.full(n_new, 2000, np.int32)
+        new[::3] = 2001
+        old[old == 2001] = 1999
+    docs, more = [old], np.array_split(new, 2)
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n_old + n_new + 3)
+    try:
+        g.build_global(docs)
+        g.insert_global(more)
+        _check(g, docs + more, D)
+    finally:
+        g.close()
