@@ -10,7 +10,7 @@
 //
 // On the suffix array a tree node of depth d is a maximal run of neighbouring suffixes that
 // share d tokens.  lcp[i] = number of tokens suffix i shares with suffix i-1 (at most D, end
-// markers excluded), len[i] = min(D, tokens before its end marker).  Entry i opens a run of two
+// markers excluded), len[i] = tokens before its end marker.  Entry i opens a run of two
 // or more suffixes at exactly the depths d in (lcp[i], lcp[i+1]]; runs of one suffix add
 // nothing to either sum.  For falling d the run's end only moves right, so one forward walk
 // per entry finds all its runs.  S of a run is its width minus the suffixes that stop at depth
@@ -22,66 +22,92 @@ namespace {
 
 constexpr int TB = 256;
 
-// lenpos[p] = min(D, tokens from text position p up to its end marker).  A wave takes 64
-// neighbouring positions and reads the text behind them 64 tokens at a time: one ballot per
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// wsum += min(D, tokens from text position p up to its end marker) over all positions.  A wave takes
+// 64 neighbouring positions and reads the text behind them 64 tokens at a time: one ballot per
 // chunk marks the end markers, and every lane looks up the first one at or behind its own
 // position.  The text carries SD_TEXT_PAD >= 64 + D end markers behind position N - 1, so the
-// chunks a wave may touch (up to position base + 63 + D) exist.
-__global__ __launch_bounds__(TB) void k_len_pos(const int32_t *__restrict__ text, int64_t N, int32_t D,
-                                                uint8_t *__restrict__ lenpos) {
+// chunks a wave may touch (up to position base + 63 + D) exist.  A fixed number of workgroups
+// strides over the text: the total is a single address.
+__global__ __launch_bounds__(TB) void k_len_sum(const int32_t *__restrict__ text, int64_t N, int32_t D,
+                                                unsigned long long *wsum) {
     const int lane = threadIdx.x & 63;
-    const int64_t base = (int64_t)blockIdx.x * TB + (threadIdx.x - lane);
-    if (base >= N) return;  // the whole wave
-    int k = -1;             // distance to the first end marker, once known
-    for (int c = 0; c * 64 < 64 + D; c++) {
-        const unsigned long long m = __ballot(text[base + c * 64 + lane] < 0);
-        if (k < 0) {
-            // markers of chunk c at or behind this lane's position
-            const unsigned long long mm = c == 0 ? (m >> lane) << lane : m;
-            if (mm) k = c * 64 + __builtin_ctzll(mm) - lane;
+    unsigned long long w = 0;
+    for (int64_t base = (int64_t)blockIdx.x * TB + (threadIdx.x - lane); base < N; base += (int64_t)gridDim.x * TB) {
+        int k = -1;  // distance to the first end marker, once known
+        for (int c = 0; c * 64 < 64 + D; c++) {
+            const unsigned long long m = __ballot(text[base + c * 64 + lane] < 0);
+            if (k < 0) {
+                // markers of chunk c at or behind this lane's position
+                const unsigned long long mm = c == 0 ? (m >> lane) << lane : m;
+                if (mm) k = c * 64 + __builtin_ctzll(mm) - lane;
+            }
+            if (__all(k >= 0 || (c + 1) * 64 - lane > D)) break;
         }
-        if (__all(k >= 0)) break;
+        if (k < 0 || k > D) k = D;
+        if (base + lane < N) w += (unsigned long long)k;
     }
-    if (k < 0 || k > D) k = D;
-    if (base + lane < N) lenpos[base + lane] = (uint8_t)k;
+    const double wd = wave_sum((double)w);  // far below 2^53: exact
+    __shared__ double part[TB / 64];
+    if (lane == 0) part[threadIdx.x >> 6] = wd;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int q = 0; q < TB / 64; q++) t += part[q];
+        if (t != 0.0) atomicAdd(wsum, (unsigned long long)t);
+    }
 }
 
 typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
 
+// lcp[i], and len[i] where the compares with i's neighbours meet its end marker (D elsewhere): the
+// walk below asks only whether a suffix stops at a depth d < D that it shares with a neighbour.
+// Bound: gathers of text lines, one per suffix and 16 tokens.  A lane loads its own suffix only and
+// has the one before from the lane below, so a wave's 64 lanes give 62 entries: the first lane is the
+// last entry of the wave before, the last one the first entry of the wave behind.
+constexpr int LCP_OUT = 62;
+
 __global__ __launch_bounds__(TB) void k_lcp_len(const int32_t *__restrict__ text,
-                                                const int32_t *__restrict__ sa,
-                                                const uint8_t *__restrict__ lenpos, int64_t N,
+                                                const int32_t *__restrict__ sa, int64_t N, int32_t D,
                                                 uint8_t *__restrict__ lcp, uint8_t *__restrict__ len) {
-    int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= N) return;
-    const int32_t p = sa[i];
-    const int L = lenpos[p];
-    int k = 0;
-    if (i > 0) {
-        // the neighbour's end marker differs from every token of w: no bound of its own needed
-        // (four tokens of either suffix per step, loaded as one 16-byte word at 4-byte
-        // alignment; what lies behind a suffix's end is text or padding and is not looked at)
-        const int32_t *w = text + p, *v = text + sa[i - 1];
-        while (k < L) {
-            const tok4 a = *reinterpret_cast<const tok4 *>(w + k), b = *reinterpret_cast<const tok4 *>(v + k);
-            const int left = L - k;
-            int same = 0;
-            if (a.x == b.x) {
-                same = 1;
-                if (left > 1 && a.y == b.y) {
-                    same = 2;
-                    if (left > 2 && a.z == b.z) {
-                        same = 3;
-                        if (left > 3 && a.w == b.w) same = 4;
-                    }
-                }
-            }
-            k += same;
-            if (same < 4) break;
+    const int lane = threadIdx.x & 63;
+    const int64_t i = ((int64_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6)) * LCP_OUT - 1 + lane;
+    const bool here = i >= 0 && i < N;
+    const int32_t *w = text + (here ? sa[i] : 0);
+    bool open = here && i > 0 && lane > 0;  // the compare with the entry before goes on
+    int l = 0, L = D;
+    for (int k = 0; k < D; k += 16) {
+        const unsigned long long m = __ballot(open);
+        if (m == 0) break;
+        // this lane's tokens are asked for by itself or by the lane above
+        tok4 t[4] = {};
+        if (((m | m >> 1) >> lane) & 1ull) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) t[q] = *reinterpret_cast<const tok4 *>(w + k + 4 * q);
+        }
+        uint32_t end = 0, differ = 0;
+#pragma unroll
+        for (int q = 0; q < 16; q++) {
+            const int32_t a = t[q >> 2][q & 3], b = __shfl_up(a, 1);
+            end |= (uint32_t)(a < 0) << q;
+            differ |= (uint32_t)(a != b) << q;
+        }
+        differ |= end;
+        if (end && L == D && k + __builtin_ctz(end) < D) L = k + __builtin_ctz(end);
+        if (open) {
+            l = k + (differ ? __builtin_ctz(differ) : 16);
+            open = !differ;
         }
     }
-    lcp[i] = (uint8_t)k;
-    len[i] = (uint8_t)L;
+    if (here && lane > 0 && lane <= LCP_OUT) {
+        lcp[i] = (uint8_t)(l < D ? l : D);
+        len[i] = (uint8_t)L;
+    }
 }
 
 // first index j' in [j, lim] with j' == lim or lcp[j'] < d; lcp is 16-byte aligned and the walk
@@ -109,37 +135,28 @@ __device__ __forceinline__ int64_t run_end(const uint8_t *__restrict__ lcp, int6
     return lim;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// acc[0] += sum of S log2 S, acc[1] += sum of COUNT log2 COUNT (runs of two or more),
-// wsum += sum of len
+// acc[0] += sum of S log2 S, acc[1] += sum of COUNT log2 COUNT (runs of two or more)
 __global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text,
                                                 const int32_t *__restrict__ sa,
                                                 const int32_t *__restrict__ tok1,
                                                 const int32_t *__restrict__ bucket,
                                                 const uint8_t *__restrict__ lcp,
                                                 const uint8_t *__restrict__ len, int64_t N, int32_t D,
-                                                double *acc, unsigned long long *wsum) {
+                                                double *acc) {
     double sS = 0.0, sC = 0.0;
-    unsigned long long w = 0;
-    // a fixed number of workgroups strides over the entries: the three totals are single
+    // a fixed number of workgroups strides over the entries: the two totals are single
     // addresses, and one atomic per wave of a grid as long as the array would queue up on them
     for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < N; i += (int64_t)gridDim.x * TB) {
-        w += len[i];
         const int lo = lcp[i], hi = i + 1 < N ? lcp[i + 1] : 0;
         if (hi > lo) {
-            // every run entry i opens lies inside the bucket of its first token
-            const int64_t bend = bucket[text[sa[i]] + 2];
             const int Li = len[i];
             int64_t j = i + 1;
             int d = hi;
             while (d > lo) {
+                // (few runs are that shallow, and finding the bucket is a gather)
+                const int64_t bend = d <= 2 ? bucket[text[sa[i]] + 2] : N;
                 if (d == 1) {
-                    j = bend;  // a run of depth 1 is the whole bucket
+                    j = bend;  // a run of depth 1 is the whole bucket of its first token
                 } else if (d == 2) {
                     // second tokens rise along the bucket: the run ends where they pass tok1[i]
                     const int32_t t1 = tok1[i];
@@ -184,24 +201,20 @@ __global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text
     }
     sS = wave_sum(sS);
     sC = wave_sum(sC);
-    double wd = wave_sum((double)w);  // far below 2^53: exact
-    __shared__ double part[3][TB / 64];
+    __shared__ double part[2][TB / 64];
     if ((threadIdx.x & 63) == 0) {
         part[0][threadIdx.x >> 6] = sS;
         part[1][threadIdx.x >> 6] = sC;
-        part[2][threadIdx.x >> 6] = wd;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        sS = sC = wd = 0.0;
+        sS = sC = 0.0;
         for (int q = 0; q < TB / 64; q++) {
             sS += part[0][q];
             sC += part[1][q];
-            wd += part[2][q];
         }
         if (sS != 0.0) atomicAdd(&acc[0], sS);
         if (sC != 0.0) atomicAdd(&acc[1], sC);
-        if (wd != 0.0) atomicAdd(wsum, (unsigned long long)wd);
     }
 }
 
@@ -214,17 +227,16 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
     double acc[2] = {0.0, 0.0};
     unsigned long long wsum = 0;
     if (N > 0) {
-        // N <= g_cap bytes each, in two build buffers of 4 g_cap bytes: lcp (16-byte aligned) in
-        // one, lenpos and len in the halves of the other
-        uint8_t *lcp = reinterpret_cast<uint8_t *>(c->b_flags);
-        uint8_t *lenpos = reinterpret_cast<uint8_t *>(c->b_gid2), *len = lenpos + 2 * c->g_cap;
+        // N <= g_cap bytes each, in two build buffers (16-byte aligned)
+        uint8_t *lcp = reinterpret_cast<uint8_t *>(c->b_flags), *len = reinterpret_cast<uint8_t *>(c->b_gid2);
         sd_fill_i32(reinterpret_cast<int32_t *>(c->d_entropy), 6, 0, st);
-        hipLaunchKernelGGL(k_len_pos, dim3(nblk(N)), dim3(TB), 0, st, c->g_text, N, c->cfg.D, lenpos);
-        hipLaunchKernelGGL(k_lcp_len, dim3(nblk(N)), dim3(TB), 0, st, c->g_text, c->g_sa, lenpos, N,
-                           lcp, len);
-        hipLaunchKernelGGL(k_entropy, dim3(nblk(N) < 4096u ? nblk(N) : 4096u), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
-                           c->g_bucket, lcp, len, N, c->cfg.D, c->d_entropy,
+        hipLaunchKernelGGL(k_len_sum, dim3(nblk(N) < 2048u ? nblk(N) : 2048u), dim3(TB), 0, st, c->g_text, N, c->cfg.D,
                            reinterpret_cast<unsigned long long *>(c->d_entropy + 2));
+        const int64_t per_block = TB / 64 * LCP_OUT;
+        hipLaunchKernelGGL(k_lcp_len, dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st, c->g_text, c->g_sa, N,
+                           c->cfg.D, lcp, len);
+        hipLaunchKernelGGL(k_entropy, dim3(nblk(N) < 4096u ? nblk(N) : 4096u), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
+                           c->g_bucket, lcp, len, N, c->cfg.D, c->d_entropy);
         if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;
         double host[3];
         if (hipMemcpyAsync(host, c->d_entropy, sizeof(host), hipMemcpyDeviceToHost, st) != hipSuccess ||
