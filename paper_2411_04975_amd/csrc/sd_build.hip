@@ -205,7 +205,10 @@ typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
 // Bound: dependent loads (suffix array, then text), so RANK_LANES lanes look for a suffix's place side
 // by side, each at a suffix of its own: a bucket of 17 takes two rounds instead of five, and its
 // tokens come eight at a time (32k new suffixes into 2.2M: 39 -> 14 us).
+// A workgroup strides over the new suffixes: a grid of RANK_LANES lanes for each of them would pass
+// the 2^32 threads of a launch at 2^29 suffixes.  RANK_BLOCKS is 32 rounds of what the chip holds.
 constexpr int RANK_LANES = 8;
+constexpr unsigned RANK_BLOCKS = 1u << 16;
 
 __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ text,
                                                     const int32_t *__restrict__ sa, int64_t N,
@@ -213,51 +216,54 @@ __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ 
                                                     const uint32_t *__restrict__ dsa, int64_t M,
                                                     int64_t base, int32_t D,
                                                     uint32_t *__restrict__ rank) {
-    const int64_t j = ((int64_t)blockIdx.x * TB + threadIdx.x) / RANK_LANES;
     const int g = threadIdx.x & (RANK_LANES - 1), first = (threadIdx.x & 63) - g;
-    const int32_t *w = text + base + (j < M ? dsa[j] : 0);
-    const int32_t c0 = w[0] + 1;  // token code, 0 for the end marker
-    int64_t lo = bucket[c0], hi = j < M ? bucket[c0 + 1] : lo;  // old suffixes with the same first token
-    while (__any(lo < hi)) {
-        // probes divide [lo, hi) evenly; up to RANK_LANES suffixes are probed one by one
-        const int64_t len = hi - lo;
-        const bool few = len <= RANK_LANES;
-        const int64_t i = few ? lo + g : lo + len * (g + 1) / (RANK_LANES + 1);
-        bool before = false;  // old suffix i sorts before, or ties with, the new one
-        if (i < hi && lo < hi) {
-            const int32_t *v = text + sa[i];
-            int cmp = 0;  // sign of (old suffix - new suffix) on the first D tokens
-            for (int k = 0; k < D; k += 8) {
-                // (what lies behind a suffix's end marker is text or padding and is not looked at)
-                const tok4 a0 = *reinterpret_cast<const tok4 *>(v + k), a1 = *reinterpret_cast<const tok4 *>(v + k + 4);
-                const tok4 b0 = *reinterpret_cast<const tok4 *>(w + k), b1 = *reinterpret_cast<const tok4 *>(w + k + 4);
-                const int32_t as[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                const int32_t bs[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                bool done = false;
+    constexpr int PER_BLOCK = TB / RANK_LANES;
+    for (int64_t j0 = (int64_t)blockIdx.x * PER_BLOCK; j0 < M; j0 += (int64_t)gridDim.x * PER_BLOCK) {
+        const int64_t j = j0 + threadIdx.x / RANK_LANES;
+        const int32_t *w = text + base + (j < M ? dsa[j] : 0);
+        const int32_t c0 = w[0] + 1;  // token code, 0 for the end marker
+        int64_t lo = bucket[c0], hi = j < M ? bucket[c0 + 1] : lo;  // old suffixes with the same first token
+        while (__any(lo < hi)) {
+            // probes divide [lo, hi) evenly; up to RANK_LANES suffixes are probed one by one
+            const int64_t len = hi - lo;
+            const bool few = len <= RANK_LANES;
+            const int64_t i = few ? lo + g : lo + len * (g + 1) / (RANK_LANES + 1);
+            bool before = false;  // old suffix i sorts before, or ties with, the new one
+            if (i < hi && lo < hi) {
+                const int32_t *v = text + sa[i];
+                int cmp = 0;  // sign of (old suffix - new suffix) on the first D tokens
+                for (int k = 0; k < D; k += 8) {
+                    // (what lies behind a suffix's end marker is text or padding and is not looked at)
+                    const tok4 a0 = *reinterpret_cast<const tok4 *>(v + k), a1 = *reinterpret_cast<const tok4 *>(v + k + 4);
+                    const tok4 b0 = *reinterpret_cast<const tok4 *>(w + k), b1 = *reinterpret_cast<const tok4 *>(w + k + 4);
+                    const int32_t as[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                    const int32_t bs[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+                    bool done = false;
 #pragma unroll
-                for (int q = 0; q < 8; q++) {
-                    if (done || k + q >= D) continue;
-                    if (as[q] != bs[q]) { cmp = as[q] < bs[q] ? -1 : 1; done = true; }
-                    else if (as[q] == SD_END_TOKEN) done = true;
+                    for (int q = 0; q < 8; q++) {
+                        if (done || k + q >= D) continue;
+                        if (as[q] != bs[q]) { cmp = as[q] < bs[q] ? -1 : 1; done = true; }
+                        else if (as[q] == SD_END_TOKEN) done = true;
+                    }
+                    if (done) break;
                 }
-                if (done) break;
+                before = cmp <= 0;
             }
-            before = cmp <= 0;
-        }
-        const uint64_t m = (__ballot(before) >> first) & ((1ull << RANK_LANES) - 1ull);
-        const int n = __popcll(m);  // (the probes rise: the first n are the ones before)
-        if (lo < hi) {
-            if (few) {
-                lo += n;
-                hi = lo;
-            } else {
-                const int64_t l = lo;
-                if (n > 0) lo = l + len * n / (RANK_LANES + 1) + 1;
-                if (n < RANK_LANES) hi = l + len * (n + 1) / (RANK_LANES + 1);
+            const uint64_t m = (__ballot(before) >> first) & ((1ull << RANK_LANES) - 1ull);
+            const int n = __popcll(m);  // (the probes rise: the first n are the ones before)
+            if (lo < hi) {
+                if (few) {
+                    lo += n;
+                    hi = lo;
+                } else {
+                    const int64_t l = lo;
+                    if (n > 0) lo = l + len * n / (RANK_LANES + 1) + 1;
+                    if (n < RANK_LANES) hi = l + len * (n + 1) / (RANK_LANES + 1);
+                }
             }
         }
+        if (g == 0 && j < M) rank[j] = (uint32_t)lo;
     }
-    if (g == 0 && j < M) rank[j] = (uint32_t)lo;
 }
 
 // Moves old and new entries to their places, and brings the bucket table up to date where new_bucket
@@ -559,10 +565,14 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     // go to b_vals[1 - cur] and b_rank, which then change places with g_sa and g_tok1
     uint32_t *dsa = c->b_vals[cur], *rank = c->b_flags;
     int32_t *sa_out = (int32_t *)c->b_vals[1 - cur], *tok1_out = (int32_t *)c->b_rank;
-    SD_LAUNCH(c, SD_K_INSERT, st, k_insert_rank, dim3(nblk(M * RANK_LANES)), dim3(TB), 0, c->g_text, c->g_sa, N, c->g_bucket, dsa, M, N, c->cfg.D, rank);
+    const int64_t rank_blocks = (M + TB / RANK_LANES - 1) / (TB / RANK_LANES);
+    SD_LAUNCH(c, SD_K_INSERT, st, k_insert_rank, dim3(rank_blocks < RANK_BLOCKS ? (unsigned)rank_blocks : RANK_BLOCKS), dim3(TB), 0,
+              c->g_text, c->g_sa, N, c->g_bucket, dsa, M, N, c->cfg.D, rank);
+    if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;  // (the merge relies on the ranks: the index stays as it was)
     SD_LAUNCH(c, SD_K_INSERT, st, k_insert_merge, dim3(nblk(M) + (unsigned)((N + MERGE_TILE - 1) / MERGE_TILE)), dim3(TB), 0,
               c->g_sa, c->g_tok1, N, c->g_text, dsa, rank, M, N, sa_out, tok1_out, c->g_tok1s,
               rc == SD_OK ? new_bucket : (int32_t *)nullptr, vocab + 2, c->g_bucket, (uint32_t)nblk(M));
+    if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;
     c->b_vals[1 - cur] = (uint32_t *)c->g_sa;
     c->b_rank = (uint32_t *)c->g_tok1;
     c->g_sa = sa_out;

@@ -102,3 +102,41 @@ def test_insert_places(n_old, n_new, spread):
         _check(g, docs + more, D)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("n_new", [2_097_100, 2_097_200, 536_871_500])
+def test_insert_ranks_in_strides(n_new):
+    """More new suffixes than one sweep of the ranking's grid (2^21), and more than 2^29: eight lanes
+    for each of those would be more threads than a launch may have.  Looked at on the GPU: every
+    position once, and neighbours in order on 8 tokens (a sample of them in the largest case)."""
+    import torch
+    import paper_2411_04975_amd as sd
+    dev, D, vocab, n_old = torch.device("cuda", 0), 8, 128256, 1000
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_new)
+
+    def doc(n):
+        return (torch.randint(0, vocab, (n,), generator=g, device=dev, dtype=torch.int32),
+                torch.tensor([0, n], dtype=torch.int64, device=dev))
+    N = n_old + n_new + 2
+    ctx = sd.sd_create(vocab, D, 4, 1.0, 0.1, 1, 16, N, 0)
+    try:
+        old, new = doc(n_old), doc(n_new)
+        sd.sd_index_build(ctx, sd.SD_SCOPE_GLOBAL, None, *old, n_old)
+        sd.sd_index_insert(ctx, *new, n_new)
+        text, sa = (torch.from_numpy(x).to(dev) for x in sd.sd_debug_read_global(ctx))
+    finally:
+        sd.sd_destroy(ctx)
+    assert sa.numel() == N
+    seen = torch.zeros(N, dtype=torch.uint8, device=dev)
+    for at in range(0, N, 1 << 26):
+        seen[sa[at:at + (1 << 26)].long()] = 1
+    assert bool(seen.all())
+    i = torch.randint(0, N - 1, (min(N - 1, 1 << 22),), generator=g, device=dev)
+    a, b = sa[i].long(), sa[i + 1].long()
+    pad = torch.cat((text, torch.full((D,), -1, dtype=torch.int32, device=dev)))
+    for k in range(D):
+        x, y = pad[a + k], pad[b + k]
+        assert not bool((x > y).any()), k
+        same = (x == y) & (x >= 0)
+        a, b = a[same], b[same]
