@@ -503,17 +503,27 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 // second-token column, samples and bucket table.  SD_ERR_STATE: not sorted, because the text
 // repeats itself too often, the entries do not fit, or the stream cannot be waited for, which is
 // how the host hears about it.
+// The tokens' intervals serve until there is twice as much text as they were sampled from: an index that
+// starts empty and grows by insertion would otherwise keep those of its first document, and codes
+// made with the intervals of other text fall into few buckets.  The sample (three launches, 15 to
+// 20 us) is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
 static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
                                  int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
-                                 int32_t *bucket, bool new_intervals, hipStream_t st) {
+                                 int32_t *bucket, int64_t old, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     if (N == 0 || !sd_code_fits(N, c->cfg.vocab) || !stream_can_wait(st)) {
         sd_layout(c, tokens, offs, n_seq, n_tokens, text, st);
         return SD_ERR_STATE;
     }
     *c->h_flag = 0;
-    if (new_intervals || !c->code_ready) sd_code_intervals(c, tokens, n_seq, n_tokens, st);
-    c->code_ready = true;
+    const int64_t seen = old > N ? old : N;
+    if (c->code_seen == 0 || seen >= 2 * c->code_seen) {
+        if (old > N)
+            sd_code_intervals(c, c->g_text, c->g_docs, old, st);
+        else
+            sd_code_intervals(c, tokens, n_seq, n_tokens, st);
+        c->code_seen = seen;
+    }
     sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, c->h_flag, c->code_asked, st);
     if (hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;  // (the sort is still running)
     return *const_cast<volatile int32_t *>(c->h_flag) ? SD_ERR_STATE : SD_OK;
@@ -526,8 +536,9 @@ sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t
     c->g_N = N;
     c->g_tokens = n_tokens;
     c->g_docs = n_seq;
+    c->code_seen = 0;  // (the intervals are those of other text)
     const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, c->g_text, c->g_sa,
-                                         c->g_tok1, c->g_bucket, true, st);
+                                         c->g_tok1, c->g_bucket, 0, st);
     if (rc != SD_ERR_STATE) return rc;
     if (N > 0) {
         const int cur = build_sorted_positions(c, c->g_text, N, c->g_tok1, st);
@@ -558,7 +569,7 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     int cur = 0;
     int32_t *new_bucket = c->code_bucket;  // first places among the new suffixes
     const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, ntext,
-                                         (int32_t *)c->b_vals[0], nullptr, new_bucket, false, st);
+                                         (int32_t *)c->b_vals[0], nullptr, new_bucket, N, st);
     if (rc == SD_ERR_STATE) cur = build_sorted_positions(c, ntext, M, nullptr, st);
     if ((rc != SD_OK && rc != SD_ERR_STATE) || cur < 0) return SD_ERR_HIP;
     // b_vals[cur]: new positions in order; b_flags: their ranks in the old array; merged arrays

@@ -65,7 +65,7 @@ struct sd_ctx {
     uint32_t *code_partials = nullptr;
     int32_t *code_bucket = nullptr;     // [vocab + 2]: bucket table of the documents of an insertion
     uint32_t *code_sums = nullptr;      // [chunks of tiles][bins], zero between builds
-    bool code_ready = false;            // code_cdf holds the intervals of some text
+    int64_t code_seen = 0;              // positions of the text that code_cdf was sampled from; 0: of none
     uint32_t *b_starts = nullptr;       // first entry of every bucket
     uint32_t *b_ranges = nullptr;       // what each workgroup of the sort in LDS takes
     hipEvent_t code_asked = nullptr;    // where h_flag is known
@@ -109,7 +109,7 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
 bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
-void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int32_t n_seq, int64_t n_tokens, hipStream_t st);
+void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);
 void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, int32_t *flag,
                   hipEvent_t asked, hipStream_t st);

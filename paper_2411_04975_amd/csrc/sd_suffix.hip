@@ -116,7 +116,8 @@ __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ 
         const int64_t run = (int64_t)blockIdx.x * RUNS_PER_WG + k * CW + w;
         const int64_t p = run < C ? (run * runs / C) * 64 + lane : n_tokens;
         tok[k] = p < n_tokens ? tokens[p] : -2;
-        if (p < n_tokens && (tok[k] < 0 || tok[k] >= vocab)) tok[k] = 0;  // (as it goes into the text)
+        if (tok[k] < 0) tok[k] = -2;       // (end markers of a text)
+        if (tok[k] >= vocab) tok[k] = 0;  // (as it goes into the text)
     }
 #pragma unroll
     for (int k = 0; k < RUNS_PER_WG / CW; k++) {
@@ -1015,7 +1016,9 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
 int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
 int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? 8 : 1; }
 
-void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int32_t n_seq, int64_t n_tokens, hipStream_t st) {
+// `tokens`: n_seq documents' tokens one after the other, or a text that holds them (its end markers
+// are not counted).
+void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st) {
     const int64_t runs = (n_tokens + 63) / 64;
     int64_t C = runs / SAMPLE_ONE_IN > SAMPLE_MIN ? runs / SAMPLE_ONE_IN : SAMPLE_MIN;
     if (C > SAMPLE_MAX) C = SAMPLE_MAX;

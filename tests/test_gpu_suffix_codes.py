@@ -140,3 +140,30 @@ def test_insert_ranks_in_strides(n_new):
         assert not bool((x > y).any()), k
         same = (x == y) & (x >= 0)
         a, b = a[same], b[same]
+
+
+@pytest.mark.parametrize("batches", [[120_000], [6000] * 20 + [50_000]])
+def test_intervals_follow_an_index_that_grows(batches):
+    """An index that starts with 2000 tokens of a wide vocabulary and grows by documents of two tokens:
+    with the first document's intervals a code sees four tokens of those, and 120,000 (50,000)
+    suffixes share 16 codes, more than a bucket may hold.  The last insertion has to be sorted by
+    codes alone: one split, where a fall-back is made of radix sort passes."""
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(len(batches))
+    D, vocab = 24, 1000
+    docs = [rng.integers(0, vocab, 2000).astype(np.int32)]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(batches) + 3000)
+    try:
+        g.insert_global(docs)
+        for n in batches:
+            new = [rng.integers(5, 7, n).astype(np.int32)]
+            sd.sd_debug_profile(g.ctx, 1)
+            sd.sd_debug_profile_read(g.ctx)
+            g.insert_global(new)
+            launches = sd.sd_debug_profile_read(g.ctx)
+            sd.sd_debug_profile(g.ctx, 0)
+            docs += new
+        assert launches["sort_scatter"]["launches"] == 1
+        _check(g, docs, D)
+    finally:
+        g.close()
