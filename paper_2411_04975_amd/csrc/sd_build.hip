@@ -7,9 +7,9 @@
 // of suffixes that start with w: COUNT(w) is the width of the range, its children are the
 // runs of equal token at offset |w| inside it, and suffixes that stop at w sit first in it.
 //
-// The sort is the one by codes of sd_suffix.hip.  The one in this file is for what that leaves: text
-// that repeats itself too often, inputs whose positions and tokens need more bits than its entries
-// have, and streams that are being captured, on which the host cannot ask how it went.
+// The sort is the one by codes of sd_suffix.hip.  The one in this file is for inputs whose positions
+// and tokens need more bits than its entries have, and for streams that are being captured, on
+// which the host cannot ask what text that repeats itself has left to be done.
 // It is prefix doubling: positions are first ordered by their leading two tokens (one
 // radix sort), then each round orders them by the pair (rank of the first h tokens, rank of
 // the next h tokens), which doubles the compared length until it reaches D.  Ranks are group
@@ -500,9 +500,8 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 }
 
 // Lays the documents out in `text` and sorts by codes (sd_suffix.hip) into sa, with tok1 also writing
-// second-token column, samples and bucket table.  SD_ERR_STATE: not sorted, because the text
-// repeats itself too often, the entries do not fit, or the stream cannot be waited for, which is
-// how the host hears about it.
+// second-token column, samples and bucket table.  SD_ERR_STATE: not sorted, because the entries do not
+// fit, or the stream cannot be waited for, which is how the host hears whether anything is left.
 // The tokens' intervals serve until there is twice as much text as they were sampled from: an index that
 // starts empty and grows by insertion would otherwise keep those of its first document, and codes
 // made with the intervals of other text fall into few buckets.  The sample (three launches, 15 to
@@ -524,9 +523,9 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
             sd_code_intervals(c, tokens, n_seq, n_tokens, st);
         c->code_seen = seen;
     }
-    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, c->h_flag, c->code_asked, st);
+    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st);
     if (hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;  // (the sort is still running)
-    return *const_cast<volatile int32_t *>(c->h_flag) ? SD_ERR_STATE : SD_OK;
+    return *const_cast<volatile int32_t *>(c->h_flag) ? sd_code_rest(c, N, text, sa, tok1, bucket, st) : SD_OK;
 }
 
 sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t *d_offsets,
@@ -568,13 +567,13 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     int32_t *ntext = c->g_text + N;
     int cur = 0;
     int32_t *new_bucket = c->code_bucket;  // first places among the new suffixes
-    const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, ntext,
-                                         (int32_t *)c->b_vals[0], nullptr, new_bucket, N, st);
+    int32_t *new_sa = c->g_sa + N;         // (the room behind the old ones is enough)
+    const sd_status rc = layout_and_sort(c, d_tokens, d_offsets, n_seq, n_tokens, ntext, new_sa, nullptr, new_bucket, N, st);
     if (rc == SD_ERR_STATE) cur = build_sorted_positions(c, ntext, M, nullptr, st);
     if ((rc != SD_OK && rc != SD_ERR_STATE) || cur < 0) return SD_ERR_HIP;
-    // b_vals[cur]: new positions in order; b_flags: their ranks in the old array; merged arrays
+    // dsa: new positions in order; b_flags: their ranks in the old array; merged arrays
     // go to b_vals[1 - cur] and b_rank, which then change places with g_sa and g_tok1
-    uint32_t *dsa = c->b_vals[cur], *rank = c->b_flags;
+    uint32_t *dsa = rc == SD_OK ? (uint32_t *)new_sa : c->b_vals[cur], *rank = c->b_flags;
     int32_t *sa_out = (int32_t *)c->b_vals[1 - cur], *tok1_out = (int32_t *)c->b_rank;
     const int64_t rank_blocks = (M + TB / RANK_LANES - 1) / (TB / RANK_LANES);
     SD_LAUNCH(c, SD_K_INSERT, st, k_insert_rank, dim3(rank_blocks < RANK_BLOCKS ? (unsigned)rank_blocks : RANK_BLOCKS), dim3(TB), 0,

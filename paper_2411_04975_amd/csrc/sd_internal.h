@@ -68,8 +68,10 @@ struct sd_ctx {
     int64_t code_seen = 0;              // positions of the text that code_cdf was sampled from; 0: of none
     uint32_t *b_starts = nullptr;       // first entry of every bucket
     uint32_t *b_ranges = nullptr;       // what each workgroup of the sort in LDS takes
+    uint32_t *rest_table = nullptr;     // by bucket: which of those that are sorted by prefix doubling
+    uint32_t *rest_to = nullptr;        // by tile of positions: how many lie in those before it
     hipEvent_t code_asked = nullptr;    // where h_flag is known
-    int32_t *h_flag = nullptr;          // pinned: the text was too repetitive for the codes
+    int32_t *h_flag = nullptr;          // pinned, 8 words: what the sort in LDS leaves to be done
 
     // ---- per-request contexts -----------------------------------------
     int32_t *r_text = nullptr;       // [max_batch_slots][r_stride], SD_END_TOKEN after the context
@@ -105,14 +107,15 @@ struct sd_ctx {
 // ---- launchers implemented in the other translation units ---------------
 // suffix sorting by codes: room for its tables, intervals from a sample of the tokens, the sort
 void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
-                  int64_t *range_words);
+                  int64_t *range_words, int64_t *rest_words);
 bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);
 void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
-                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, int32_t *flag,
-                  hipEvent_t asked, hipStream_t st);
+                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);
+// what that left undone, if h_flag says so
+sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);
 // the documents' text alone
 void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                int32_t *text, hipStream_t st);
@@ -127,6 +130,10 @@ int sd_sort_pairs(sd_ctx *c, int64_t n, int nbits, int in_idx, hipStream_t st,
 void sd_group_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64_t n,
                     uint32_t *rank, uint32_t *gid, const uint32_t *gid_old, hipStream_t st,
                     const int32_t *run_if = nullptr);
+// rank[vals[i]] = 1 + place[first entry of the run of equal keys that keys[i] belongs to], where
+// that differs from keys[i] >> old_shift (0: everywhere)
+void sd_place_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64_t n, const uint32_t *place,
+                    int old_shift, uint32_t *rank, hipStream_t st);
 
 sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t *d_offsets,
                                int32_t n_seq, int64_t n_tokens, hipStream_t st);

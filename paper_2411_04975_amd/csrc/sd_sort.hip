@@ -271,6 +271,9 @@ __global__ __launch_bounds__(SC_THREADS) void k_scanmax_partials(uint32_t *parti
 // (gid_old; places keep their group from round to round, the build only reorders inside
 // groups), only those entries are written to `rank` (by position: a random 4-byte store each).  Two passes over the keys: the last group start of every
 // tile, a prefix maximum over the tiles, then numbers and stores.
+// With `place` the array is a part of a longer one, entry i of it at place[i] there: the number is
+// 1 + the place of the group's first entry, and the number that an entry had before is in its key,
+// from bit old_shift on (0: it had none).
 __global__ __launch_bounds__(SC_THREADS) void k_rank_tile_last(const uint64_t *__restrict__ keys,
                                                                int64_t n,
                                                                uint32_t *__restrict__ partials,
@@ -309,6 +312,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_rank_apply(const uint64_t *__res
                                                            uint32_t *__restrict__ rank,
                                                            uint32_t *__restrict__ gid,
                                                            const uint32_t *__restrict__ gid_old,
+                                                           const uint32_t *__restrict__ place, int old_shift,
                                                            const int32_t *__restrict__ run_if) {
     constexpr int NW = SC_THREADS / 64;
     static_assert(SC_ITEMS * NW == 64, "one wave scans the parts of a tile");
@@ -363,7 +367,11 @@ __global__ __launch_bounds__(SC_THREADS) void k_rank_apply(const uint64_t *__res
         const int64_t i = base + (int64_t)k * SC_THREADS + t;
         const uint32_t carry = s_tot[k * NW + w];
         const uint32_t g = inc[k] > carry ? inc[k] : carry;
-        if (i < n) {
+        if (i >= n) continue;
+        if (place) {
+            const uint32_t at = place[g - 1u] + 1u;
+            if (old_shift == 0 || (uint32_t)(key[k] >> old_shift) != at) rank[vals[i]] = at;
+        } else {
             if (!gid_old || gid_old[i] != g) rank[vals[i]] = g;
             gid[i] = g;
         }
@@ -382,9 +390,20 @@ void sd_group_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64
                        c->b_partials, run_if);
     hipLaunchKernelGGL(k_scanmax_partials, dim3(1), dim3(SC_THREADS), 0, st, c->b_partials, nt, run_if);
     hipLaunchKernelGGL(k_rank_apply, dim3((unsigned)nt), dim3(SC_THREADS), 0, st, keys, vals, n,
-                       c->b_partials, rank, gid, gid_old, run_if);
+                       c->b_partials, rank, gid, gid_old, (const uint32_t *)nullptr, 0, run_if);
 }
 
+void sd_place_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64_t n, const uint32_t *place,
+                    int old_shift, uint32_t *rank, hipStream_t st) {
+    if (n <= 0) return;
+    const int64_t nt = (n + SC_TILE - 1) / SC_TILE;
+    const int32_t *always = nullptr;
+    sd_span sp(c, SD_K_SORT_SCAN, st);
+    hipLaunchKernelGGL(k_rank_tile_last, dim3((unsigned)nt), dim3(SC_THREADS), 0, st, keys, n, c->b_partials, always);
+    hipLaunchKernelGGL(k_scanmax_partials, dim3(1), dim3(SC_THREADS), 0, st, c->b_partials, nt, always);
+    hipLaunchKernelGGL(k_rank_apply, dim3((unsigned)nt), dim3(SC_THREADS), 0, st, keys, vals, n, c->b_partials, rank,
+                       (uint32_t *)nullptr, (const uint32_t *)nullptr, place, old_shift, always);
+}
 
 // (Passes that a device-side switch may turn into no-ops are timed under "other build kernels",
 // so that the sort kernels' own figures hold real passes only.)

@@ -22,9 +22,9 @@
 // for each one that ties one or two random cache lines, which are what costs: 10M gathers of 16 or
 // 64 bytes from a 40 MB text take 185 or 237 us, a copy of 680 MB 135 us.
 //
-// Buckets that are too large for a workgroup raise a flag (thousands of suffixes that share some
-// twenty bits of code: a token over and over, one preamble in front of thousands of documents),
-// and the caller takes prefix doubling instead (sd_build.hip), whose cost does not depend on that.
+// Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
+// code: a token over and over, one preamble in front of thousands of documents) are left when all others
+// are sorted, and go through prefix doubling on their own.
 //
 // Build of 10M tokens copied from templates 1.68 -> 0.65 ms, of 10M of a Zipf law 2.89 -> 0.40 ms, of
 // 100M copied 20.7 -> 7.0 ms, against prefix doubling for everything.
@@ -570,25 +570,36 @@ constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
 
-// What the tile's workgroup will take, and whether it can.  A wave finds where a tile's buckets
-// start; the eighth wave of a workgroup looks at the next workgroup's first tile.  (On its own, before
-// the sort: the host hears from it while the sort is running.)
+// What a workgroup takes: whole buckets, and the part of the bucket table that they answer for.
 struct sort_range {
-    uint32_t bucket;   // first bucket that starts in the tile or behind it
-    uint32_t filled;   // the last one that starts there: it is not empty
-    uint32_t at;       // its place
-    uint32_t code;     // first token whose interval starts in `bucket` or behind it
+    uint32_t bucket, end;      // buckets [bucket, end), the first of them not empty; none where `at` is `end_at`
+    uint32_t at, end_at;       // their entries
+    uint32_t code, end_code;   // tokens whose intervals start in these buckets or in empty ones around them
 };
+__device__ __forceinline__ bool sortable(const sort_range &r) {
+    return r.at == r.end_at || (r.end - r.bucket <= (uint32_t)SORT_BUCKETS && r.end_at - r.at <= (uint32_t)SORT_CAP);
+}
 
+// The range of a tile: the buckets that start in it.  Only the last of them can reach beyond the tile, so
+// where they are too many for a workgroup that bucket is kept apart as a range of its own (`last`; empty
+// otherwise), and only if it is too long by itself, or the buckets in front of it are spread over
+// more than SORT_BUCKETS, something is left that no workgroup takes.  *rest tells the host that
+// there is more to do than k_code_sort over `first`.
+// A wave finds where a tile's buckets start; the eighth wave of a workgroup looks at the next workgroup's
+// first tile.  (On its own, before the sort: the host hears from it while the sort is running.)
 __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__ starts, int64_t N, int bits,
                                                     int tile, int tiles, const uint32_t *__restrict__ cdf,
-                                                    int32_t n_codes, sort_range *__restrict__ ranges,
-                                                    int32_t *too_long) {
-    __shared__ sort_range s_range[CW];
+                                                    int32_t n_codes, sort_range *__restrict__ first,
+                                                    sort_range *__restrict__ last, int32_t *rest) {
+    struct bound { uint32_t bucket, filled, at, code; };  // first bucket that starts in the tile or behind it; the last one that starts there
+    __shared__ bound s_bound[CW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
     const int t = (int)blockIdx.x * (CW - 1) + w;
+    auto start = [&](int i) { return (int64_t)starts[i]; };
+    auto code_of = [&](int b) {  // first token whose interval starts in bucket b or behind it
+        return (uint32_t)wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)b << (32 - bits));
+    };
     if (t <= tiles) {
-        auto start = [&](int i) { return (int64_t)starts[i]; };
         const int b = t == tiles ? buckets : wave_lower_bound(start, buckets, (int64_t)t * tile);
         const uint32_t at = starts[b];
         int filled = b;
@@ -596,18 +607,26 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
             const uint64_t m = __ballot(b + 1 + lane > buckets || starts[b + 1 + lane] > at);
             filled = m ? b + __builtin_ctzll(m) : wave_lower_bound(start, buckets, (int64_t)at + 1) - 1;
         }
-        const int c = t == tiles ? n_codes + 1
-                                 : wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)b << (32 - bits));
-        if (lane == 0) {
-            s_range[w] = {(uint32_t)b, (uint32_t)filled, at, (uint32_t)c};
-            if (w < CW - 1 || t == tiles) ranges[t] = s_range[w];
-        }
+        const uint32_t c = t == tiles ? (uint32_t)(n_codes + 1) : code_of(b);
+        if (lane == 0) s_bound[w] = {(uint32_t)b, (uint32_t)filled, at, c};
     }
     __syncthreads();
-    if (threadIdx.x < CW - 1 && (int)blockIdx.x * (CW - 1) + (int)threadIdx.x < tiles) {
-        const sort_range r = s_range[threadIdx.x], z = s_range[threadIdx.x + 1];
-        if (z.bucket > r.bucket && (z.at - r.at > SORT_CAP || z.bucket - r.filled > SORT_BUCKETS)) *too_long = 1;
+    if (w == CW - 1 || t >= tiles) return;
+    const bound r = s_bound[w], z = s_bound[w + 1];
+    sort_range f = {r.filled, z.bucket, r.at, z.at, r.code, z.code}, l = {z.bucket, z.bucket, z.at, z.at, z.code, z.code};
+    if (z.bucket == r.bucket) f = {r.bucket, r.bucket, r.at, r.at, r.code, r.code};
+    if (!sortable(f)) {
+        const uint32_t b = (uint32_t)wave_lower_bound(start, buckets, (int64_t)z.at) - 1;  // of the last entry
+        f.end = b + 1;
+        if (f.end_at - f.at > (uint32_t)SORT_CAP) {
+            l = {b, b + 1, starts[b], z.at, code_of((int)b), z.code};
+            f.end_at = l.at;
+            f.end_code = l.code;
+            f.end = f.at == l.at ? f.bucket : (uint32_t)wave_lower_bound(start, buckets, (int64_t)l.at);
+        }
+        if (lane == 0 && (l.at != l.end_at || !sortable(f))) *rest = 1;
     }
+    if (lane == 0) { first[t] = f; last[t] = l; }
 }
 
 template <int TOK>
@@ -656,13 +675,13 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     __shared__ uint32_t s_wave[CW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
-    const sort_range here_r = ranges[blockIdx.x], next_r = ranges[blockIdx.x + 1];
-    const int b0 = (int)here_r.filled, nb = (int)next_r.bucket - b0;
-    const int64_t a = here_r.at, z = next_r.at;
-    if (next_r.bucket == here_r.bucket || nb > SORT_BUCKETS || z - a > SORT_CAP) return;  // (nothing, or given up)
+    const sort_range range = ranges[blockIdx.x];
+    const int b0 = (int)range.bucket, nb = (int)range.end - b0;
+    const int64_t a = range.at, z = range.end_at;
+    if (!sortable(range)) return;
     if (z == a) {  // nothing but empty buckets
         if (bucket)
-            for (int c = (int)here_r.code + tid; c < (int)next_r.code; c += CT) bucket[c] = (int32_t)a;
+            for (int c = (int)range.code + tid; c < (int)range.end_code; c += CT) bucket[c] = (int32_t)a;
         return;
     }
     uint32_t *cnt = reinterpret_cast<uint32_t *>(s_area);
@@ -740,10 +759,10 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     if (bucket) {
         // bucket[c] = first place whose suffix starts with a token code >= c: the entries before
         // it are those with codes below the interval of c
-        for (int c = (int)here_r.code + tid; c < (int)next_r.code; c += CT) {
+        for (int c = (int)range.code + tid; c < (int)range.end_code; c += CT) {
             const uint32_t end = cdf[c];
-            if ((int)(end >> down) < b0) {
-                bucket[c] = (int32_t)a;
+            if ((int)(end >> down) < b0 || (int)(end >> down) >= b0 + nb) {
+                bucket[c] = (int32_t)((int)(end >> down) < b0 ? a : z);
                 continue;
             }
             const uint32_t key = ((end & (uint32_t)((1ull << down) - 1ull)) >> f.key_drop);  // inside the bucket
@@ -956,6 +975,212 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     for (int s = s_begin + lane; s < s_end; s += 64) sa[a + s] = (int32_t)s_pos[s];
 }
 
+// ---- what no workgroup takes --------------------------------------------------------------------
+// Thousands of suffixes that share all bits of code that the splits look at (a preamble in front of
+// thousands of documents, one token over and over).  They are sorted by prefix doubling, but they alone:
+// every other position has its place by now, and that is its rank.  The entries of these ranges are
+// numbered 0..S in the order of their places.  A round orders them by (rank of the first h tokens,
+// rank of the h tokens behind them), where a rank is 1 + the place at which the group of suffixes starts
+// that agree so far: two by two tokens from what code and second token say, D after the last round.
+// Keys are built in position order, so that ranks are read in order and ties keep the positions' order.
+// Bound: the radix sort's passes over 12-byte pairs (sd_sort.hip), six or seven a round; per position of
+// the whole text a rank is stored (a random store) and a code read once a round.  Builds, against prefix
+// doubling for the whole text: 10M tokens, half of them 10,000 copies of one preamble, 6.1 -> 3.3 ms; 10M
+// copied from templates with a preamble of 400 in front of 5000 documents 5.8 -> 2.3; 100M so 70 -> 14.5.
+struct rest_range {
+    sort_range r;
+    uint32_t sub;   // number of its first entry
+    uint32_t ord;   // number of its first bucket among those of all these ranges
+};
+enum { REST_ANY = 0, REST_RANGES, REST_LONG, REST_ENTRIES, REST_BUCKETS };  // words of h_flag
+
+// Lists, in order, the ranges that k_code_sort can take and has not, and those that it cannot.  One workgroup.
+__global__ __launch_bounds__(CT) void k_rest_lists(const sort_range *__restrict__ first,
+                                                   const sort_range *__restrict__ last, int tiles,
+                                                   sort_range *__restrict__ more, rest_range *__restrict__ rest,
+                                                   uint32_t *__restrict__ out) {
+    __shared__ uint32_t s_wave[CW];
+    uint32_t n_more = 0, n_rest = 0, sub = 0, ord = 0;
+    for (int base = 0; base < tiles; base += CT) {
+        const int t = base + (int)threadIdx.x;
+        sort_range r[2] = {};
+        if (t < tiles) { r[0] = first[t]; r[1] = last[t]; }
+        const bool is_rest[2] = {!sortable(r[0]), !sortable(r[1])}, is_more = r[1].at != r[1].end_at && !is_rest[1];
+        uint32_t entries = 0, buckets = 0, tot;
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+            if (is_rest[q]) { entries += r[q].end_at - r[q].at; buckets += r[q].end - r[q].bucket; }
+        const uint32_t at_more = n_more + block_excl_scan(is_more, s_wave, &tot);
+        n_more += tot;
+        uint32_t at_rest = n_rest + block_excl_scan((uint32_t)is_rest[0] + (uint32_t)is_rest[1], s_wave, &tot);
+        n_rest += tot;
+        uint32_t at_sub = sub + block_excl_scan(entries, s_wave, &tot);
+        sub += tot;
+        uint32_t at_ord = ord + block_excl_scan(buckets, s_wave, &tot);
+        ord += tot;
+        if (is_more) more[at_more] = r[1];
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+            if (is_rest[q]) {
+                rest[at_rest++] = {r[q], at_sub, at_ord};
+                at_sub += r[q].end_at - r[q].at;
+                at_ord += r[q].end - r[q].bucket;
+            }
+    }
+    if (threadIdx.x == 0) {
+        out[REST_RANGES] = n_more;
+        out[REST_LONG] = n_rest;
+        out[REST_ENTRIES] = sub;
+        out[REST_BUCKETS] = ord;
+    }
+}
+
+// last of n ranges whose key(range) is <= v, -1 if there is none
+template <typename KEY>
+__device__ __forceinline__ int last_range(const rest_range *__restrict__ rest, int n, uint32_t v, KEY key) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (key(rest[mid]) <= v) lo = mid + 1; else hi = mid;
+    }
+    return lo - 1;
+}
+
+// table[b] = 1 + number of bucket b among those of the ranges, 0: in none
+__global__ __launch_bounds__(CT) void k_rest_table(const rest_range *__restrict__ rest, int n, int buckets,
+                                                   uint32_t *__restrict__ table) {
+    const int b = (int)blockIdx.x * CT + (int)threadIdx.x;
+    if (b >= buckets) return;
+    const int j = last_range(rest, n, (uint32_t)b, [](const rest_range &x) { return x.r.bucket; });
+    table[b] = j >= 0 && (uint32_t)b < rest[j].r.end ? rest[j].ord + ((uint32_t)b - rest[j].r.bucket) + 1u : 0u;
+}
+
+// place[i] of the i-th entry of the ranges
+__global__ __launch_bounds__(CT) void k_rest_places(const rest_range *__restrict__ rest, int n, uint32_t S,
+                                                    uint32_t *__restrict__ place) {
+    const int64_t i = (int64_t)blockIdx.x * CT + threadIdx.x;
+    if (i >= S) return;
+    const int j = last_range(rest, n, (uint32_t)i, [](const rest_range &x) { return x.sub; });
+    place[i] = rest[j].r.at + ((uint32_t)i - rest[j].sub);
+}
+
+// rank[position] = 1 + place, for the places that are in no range
+__global__ __launch_bounds__(CT) void k_rest_others(const rest_range *__restrict__ rest, int n,
+                                                    const int32_t *__restrict__ sa, int64_t N,
+                                                    uint32_t *__restrict__ rank) {
+    const int64_t i = (int64_t)blockIdx.x * CT + threadIdx.x;
+    if (i >= N) return;
+    const int j = last_range(rest, n, (uint32_t)i, [](const rest_range &x) { return x.r.at; });
+    if (j < 0 || (uint32_t)i >= rest[j].r.end_at) rank[sa[i]] = (uint32_t)i + 1u;
+}
+
+// The positions in the ranges, in order: how many there are in a tile of positions, and the pairs of
+// key and position, where tile t's go from to[t] on.
+constexpr int REST_ITEMS = 8, REST_TILE = CT * REST_ITEMS;
+static_assert(REST_ITEMS * CW == 64, "one wave adds up the parts of a tile");
+
+__global__ __launch_bounds__(CT) void k_rest_count(const uint32_t *__restrict__ codes, int64_t N, int down,
+                                                   const uint32_t *__restrict__ table, uint32_t *__restrict__ to) {
+    __shared__ uint32_t s_wave[CW];
+    const int64_t base = (int64_t)blockIdx.x * REST_TILE;
+    uint32_t n = 0, tot;
+#pragma unroll
+    for (int k = 0; k < REST_ITEMS; k++) {
+        const int64_t p = base + k * CT + threadIdx.x;
+        n += p < N && table[codes[p] >> down] ? 1u : 0u;
+    }
+    (void)block_excl_scan(n, s_wave, &tot);
+    if (threadIdx.x == 0) to[blockIdx.x] = tot;
+}
+
+// exclusive prefix sum in place; one workgroup
+__global__ __launch_bounds__(CT) void k_rest_scan(uint32_t *__restrict__ to, int64_t n) {
+    __shared__ uint32_t s_wave[CW];
+    uint32_t sum = 0, tot;
+    for (int64_t base = 0; base < n; base += CT) {
+        const int64_t i = base + threadIdx.x;
+        const uint32_t v = i < n ? to[i] : 0u, ex = block_excl_scan(v, s_wave, &tot);
+        if (i < n) to[i] = sum + ex;
+        sum += tot;
+    }
+}
+
+// h = 0: key = (bucket's number, the code's bits behind the bucket's, code of the second token);
+// otherwise (rank[p], rank[p + h])
+__global__ __launch_bounds__(CT) void k_rest_keys(const uint32_t *__restrict__ codes, int64_t N, int down,
+                                                  const uint32_t *__restrict__ table,
+                                                  const uint32_t *__restrict__ to,
+                                                  const int32_t *__restrict__ text, int tok_bits,
+                                                  const uint32_t *__restrict__ rank, int64_t h, int rank_bits,
+                                                  uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+    __shared__ uint32_t s_at[REST_ITEMS * CW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * REST_TILE;
+    uint64_t key[REST_ITEMS], in[REST_ITEMS];
+#pragma unroll
+    for (int k = 0; k < REST_ITEMS; k++) {
+        const int64_t p = base + k * CT + threadIdx.x;
+        const uint32_t code = p < N ? codes[p] : 0u, ord = p < N ? table[code >> down] : 0u;
+        in[k] = __ballot(ord != 0);
+        key[k] = 0;
+        if (ord && h == 0)
+            key[k] = ((((uint64_t)(ord - 1u) << down) | (code & (uint32_t)((1ull << down) - 1ull))) << tok_bits) | (uint32_t)(text[p + 1] + 1);
+        else if (ord)
+            key[k] = ((uint64_t)rank[p] << rank_bits) | (p + h < N ? rank[p + h] : 0u);
+        if (lane == 0) s_at[k * CW + w] = (uint32_t)__popcll(in[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const uint32_t v = s_at[threadIdx.x];
+        uint32_t inc = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(inc, o);
+            if (lane >= o) inc += u;
+        }
+        s_at[threadIdx.x] = to[blockIdx.x] + inc - v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < REST_ITEMS; k++)
+        if ((in[k] >> lane) & 1ull) {
+            const uint32_t at = s_at[k * CW + w] + (uint32_t)__popcll(in[k] & ((1ull << lane) - 1ull));
+            keys[at] = key[k];
+            vals[at] = (uint32_t)(base + k * CT + threadIdx.x);
+        }
+}
+
+__global__ __launch_bounds__(CT) void k_rest_write(const uint32_t *__restrict__ vals,
+                                                   const uint32_t *__restrict__ place, uint32_t S,
+                                                   const int32_t *__restrict__ text, int32_t *__restrict__ sa,
+                                                   int32_t *__restrict__ tok1, int32_t *__restrict__ samples) {
+    const int64_t i = (int64_t)blockIdx.x * CT + threadIdx.x;
+    if (i >= S) return;
+    const uint32_t at = place[i], p = vals[i];
+    sa[at] = (int32_t)p;
+    if (tok1) {
+        const int32_t second = text[(int64_t)p + 1];
+        tok1[at] = second;
+        if ((at & 15u) == 0) samples[at >> 4] = second;
+    }
+}
+
+// The ranges' part of the bucket table.
+__global__ __launch_bounds__(CT) void k_rest_bucket(const rest_range *__restrict__ rest, int n, int32_t entries,
+                                                    const int32_t *__restrict__ text,
+                                                    const int32_t *__restrict__ sa, int32_t *__restrict__ bucket) {
+    const int32_t c = (int32_t)blockIdx.x * CT + (int32_t)threadIdx.x;
+    if (c >= entries) return;
+    const int j = last_range(rest, n, (uint32_t)c, [](const rest_range &x) { return x.r.code; });
+    if (j < 0 || (uint32_t)c >= rest[j].r.end_code) return;
+    int64_t lo = rest[j].r.at, hi = rest[j].r.end_at;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (text[sa[mid]] + 1 < c) lo = mid + 1; else hi = mid;
+    }
+    bucket[c] = (int32_t)lo;
+}
+
 // ---- host side --------------------------------------------------------------------------------
 // Leading code bits that are split off: buckets of 256 to 512 entries, so that the share of a
 // workgroup of k_code_sort, whole buckets, is SORT_TILE give or take one of them, and a bucket may
@@ -991,10 +1216,10 @@ constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 
 }  // namespace
 
-// Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts, code_sums and
-// b_ranges.
+// Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts (and of
+// rest_table), code_sums, b_ranges and rest_to.
 void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
-                  int64_t *range_words) {
+                  int64_t *range_words, int64_t *rest_words) {
     int64_t h = 0, s = 0;
     const int64_t sizes[] = {cap, 1 << 20, (int64_t)512 << MAX_BITS};
     for (int64_t n : sizes) {
@@ -1010,7 +1235,8 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *hist_words = h + MAX_BINS + 1;
     *start_words = s;
     *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
-    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)(sizeof(sort_range) / 4);
+    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)((3 * sizeof(sort_range) + 2 * sizeof(rest_range)) / 4);
+    *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
 
 int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
@@ -1066,13 +1292,36 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
+// The tables of ranges, in b_ranges.
+struct sort_tables {
+    int tile, tiles;
+    sort_range *first, *last, *more;
+    rest_range *rest;
+};
+static sort_tables tables_for(const sd_ctx *c, int64_t N) {
+    sort_tables t;
+    t.tile = sort_tile_for(N, c->n_cu);
+    t.tiles = (int)((N + t.tile - 1) / t.tile);
+    t.rest = reinterpret_cast<rest_range *>(c->b_ranges);
+    t.first = reinterpret_cast<sort_range *>(t.rest + 2 * (int64_t)t.tiles);
+    t.last = t.first + t.tiles;
+    t.more = t.last + t.tiles;
+    return t;
+}
+
+static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_range *ranges, int n, int64_t N, entry_shape f,
+                        const int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
+              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, ranges, N, f, text, c->cfg.D, c->code_cdf,
+              c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
+}
+
 // Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
 // given, receives the second-token column, bucket the table of first places by token code.
-// *flag (pinned host memory, zero before) becomes 1 if the text is too repetitive: then only the text
-// is complete.  `asked` is recorded where that is known.
+// h_flag (pinned host memory, its first word zero before) becomes 1 if the text is so repetitive that
+// sd_code_rest has to follow.  code_asked is recorded where that is known.
 void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
-                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, int32_t *flag,
-                  hipEvent_t asked, hipStream_t st) {
+                  int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     const split_plan p = plan_for(N);
     entry_shape f;
@@ -1104,12 +1353,48 @@ void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
         SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, shift, bins2, hist2, ent2);
         ent1 = ent2;
     }
-    const int sort_tile = sort_tile_for(N, c->n_cu), tiles = (int)((N + sort_tile - 1) / sort_tile);
-    sort_range *ranges = reinterpret_cast<sort_range *>(c->b_ranges);
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((tiles + 1 + CW - 2) / (CW - 1))), block, 0,
-              c->b_starts, N, f.bits1 + f.bits2, sort_tile, tiles, c->code_cdf, c->cfg.vocab + 1, ranges, flag);
-    (void)hipEventRecord(asked, st);
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
-              dim3((unsigned)tiles), block, 0, ent1, c->b_starts, ranges, N, f, text, c->cfg.D, c->code_cdf,
-              c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
+    const sort_tables t = tables_for(c, N);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
+              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.first, t.last, c->h_flag);
+    (void)hipEventRecord(c->code_asked, st);
+    sort_ranges(c, ent1, t.first, t.tiles, N, f, text, sa, tok1, bucket, st);
+}
+
+// The ranges that sd_code_sort's workgroups have not taken; waits for the stream.
+sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
+    entry_shape f;
+    (void)shape_for(N, c->cfg.vocab, &f);
+    const sort_tables t = tables_for(c, N);
+    const dim3 block(CT);
+    auto grid = [](int64_t n, int per) { return dim3((unsigned)((n + per - 1) / per)); };
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_lists, dim3(1), block, 0, t.first, t.last, t.tiles, t.more, t.rest, (uint32_t *)c->h_flag);
+    if (hipEventRecord(c->code_asked, st) != hipSuccess || hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;
+    const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
+    const int ranges = (int)told[REST_RANGES], n = (int)told[REST_LONG];
+    const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
+    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t.more, ranges, N, f, text, sa, tok1, bucket, st);
+    if (n == 0) return SD_OK;
+    const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
+    uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;
+    const int64_t tiles = (N + REST_TILE - 1) / REST_TILE;
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_table, grid((int64_t)1 << bits, CT), block, 0, t.rest, n, 1 << bits, table);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_count, dim3((unsigned)tiles), block, 0, codes, N, down, table, to);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_scan, dim3(1), block, 0, to, tiles);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_places, grid(S, CT), block, 0, t.rest, n, S, place);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_others, grid(N, CT), block, 0, t.rest, n, sa, N, rank);
+    int key_bits = sd_bits_for((uint64_t)(buckets - 1)) + down + f.tok_bits, cur = 0;
+    for (int64_t h = 0;;) {
+        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_keys, dim3((unsigned)tiles), block, 0, codes, N, down, table, to,
+                  text, f.tok_bits, rank, h, rank_bits, c->b_keys[0], c->b_vals[0]);
+        cur = sd_sort_pairs(c, S, key_bits, 0, st);
+        const int64_t next = h ? 2 * h : 2;
+        if (next >= c->cfg.D) break;
+        sd_place_ranks(c, c->b_keys[cur], c->b_vals[cur], S, place, h ? rank_bits : 0, rank, st);
+        h = next;
+        key_bits = 2 * rank_bits;
+    }
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_write, grid(S, CT), block, 0, c->b_vals[cur], place, S, text, sa, tok1, c->g_tok1s);
+    if (bucket)
+        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_bucket, grid((int64_t)c->cfg.vocab + 2, CT), block, 0, t.rest, n, c->cfg.vocab + 2, text, sa, bucket);
+    return SD_OK;
 }
