@@ -63,7 +63,7 @@ def test_sizes(n, vocab, copies):
         g.close()
 
 
-@pytest.mark.parametrize("times", [63, 64, 65, 130, 700, 1900, 5000])
+@pytest.mark.parametrize("times", [63, 64, 65, 130, 511, 512, 513, 700, 1900, 4096, 4097, 5000])
 def test_repeated_phrase(times):
     """A phrase of 40 tokens in front of `times` documents that go on differently, two of them alike."""
     rng = np.random.default_rng(times)
@@ -233,7 +233,7 @@ def _device_preambles(times, n):
     return tokens.reshape(-1), torch.arange(0, n + 1, 1000, dtype=torch.int64, device=dev)
 
 
-@pytest.mark.parametrize("times", [500, 10_000])
+@pytest.mark.parametrize("times", [500, 2000, 3333, 10_000])
 def test_repeated_text_costs_no_more_than_doubling(times):
     """A build of 10M tokens with `times` equal prefixes against the same build replayed from a graph,
     which has to go through prefix doubling alone, whatever the text is (a graph cannot ask how it
