@@ -219,7 +219,8 @@ def test_buckets_beyond_a_workgroup(name, insert):
 
 
 def _device_preambles(times, n):
-    """n tokens on the GPU: documents of 500 that `times` of them have in common and 500 of their own."""
+    """n tokens on the GPU: documents of 500 that `times` of them have in common and 500 of their own;
+    times = 0: one token over and over."""
     import torch
     dev = torch.device("cuda", 0)
     g = torch.Generator(device=dev)
@@ -227,13 +228,15 @@ def _device_preambles(times, n):
 
     def ints(*shape):
         return torch.randint(0, 128256, shape, generator=g, device=dev, dtype=torch.int32)
-    docs = n // 1000
+    docs, offsets = n // 1000, torch.arange(0, n + 1, 1000, dtype=torch.int64, device=dev)
+    if times == 0:
+        return torch.full((n,), 4711, dtype=torch.int32, device=dev), offsets
     heads = ints(-(-docs // times), 500)
     tokens = torch.cat((heads[torch.arange(docs, device=dev) % len(heads)], ints(docs, 500)), 1)
-    return tokens.reshape(-1), torch.arange(0, n + 1, 1000, dtype=torch.int64, device=dev)
+    return tokens.reshape(-1), offsets
 
 
-@pytest.mark.parametrize("times", [500, 2000, 3333, 10_000])
+@pytest.mark.parametrize("times", [500, 2000, 3333, 10_000, 0])
 def test_repeated_text_costs_no_more_than_doubling(times):
     """A build of 10M tokens with `times` equal prefixes against the same build replayed from a graph,
     which has to go through prefix doubling alone, whatever the text is (a graph cannot ask how it
