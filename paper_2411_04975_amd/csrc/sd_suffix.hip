@@ -465,20 +465,22 @@ constexpr int SPLIT2_ITEMS = 12, SPLIT2_TILE = CT * SPLIT2_ITEMS;
 // The counts of tile number g lie in row g: (g, digit).
 __device__ __forceinline__ int first_tile(uint32_t start, int bin) { return (int)(start / SPLIT2_TILE) + bin; }
 
-struct bin_tile { int bin, tile, cnt; int64_t at; };  // tile of the bin; entries, 0: no such tile; where they start
+struct bin_tile { int64_t at; int cnt; };  // the entries; none: no such tile
 __device__ __forceinline__ bin_tile tile_of(const uint32_t *__restrict__ starts1, int bins1) {
+    __shared__ uint32_t s_first[2], s_size;
     const int g = (int)blockIdx.x;
-    int before = 0;
-    for (int b = threadIdx.x; b < MAX_BINS; b += CT)
-        before += __syncthreads_count(b < bins1 && first_tile(starts1[b], b) <= g);
-    bin_tile r;
-    r.bin = before - 1;
-    const bin_place p = first_bin(starts1, r.bin);
-    r.tile = g - first_tile(p.start, r.bin);
-    const int64_t left = (int64_t)p.size - (int64_t)r.tile * SPLIT2_TILE;
-    r.cnt = left <= 0 ? 0 : left < SPLIT2_TILE ? (int)left : SPLIT2_TILE;
-    r.at = (int64_t)p.start + (int64_t)r.tile * SPLIT2_TILE;
-    return r;
+    for (int b = threadIdx.x; b < bins1; b += CT) {
+        const bin_place p = first_bin(starts1, b);
+        const int f = first_tile(p.start, b);
+        if (f <= g && g < first_tile(p.start + p.size, b + 1)) {  // (of one bin: numbers rise)
+            s_first[0] = p.start;
+            s_first[1] = (uint32_t)(g - f);
+            s_size = p.size;
+        }
+    }
+    __syncthreads();
+    const int64_t skip = (int64_t)s_first[1] * SPLIT2_TILE, left = (int64_t)s_size - skip;
+    return {(int64_t)s_first[0] + skip, left <= 0 ? 0 : left < SPLIT2_TILE ? (int)left : SPLIT2_TILE};
 }
 
 __global__ __launch_bounds__(CT) void k_code_hist2(const uint64_t *__restrict__ in,
@@ -584,19 +586,32 @@ __device__ __forceinline__ bool sortable(const sort_range &r) {
     return r.at == r.end_at || (r.end - r.bucket <= (uint32_t)SORT_BUCKETS && r.end_at - r.at <= (uint32_t)SORT_CAP);
 }
 
-// The range of a tile: the buckets that start in it.  Only the last of them can reach beyond the tile, so
-// where they are too many for a workgroup that bucket is kept apart as a range of its own (`last`; empty
-// otherwise), and only if it is too long by itself, or the buckets in front of it are spread over
-// more than SORT_BUCKETS, something is left that no workgroup takes.  *rest tells the host that
-// there is more to do than k_code_sort over `first`.
+// Where a tile starts, which takes the buckets that start in it.
+struct sort_bound {
+    uint32_t bucket;   // first bucket that starts in the tile or behind it
+    uint32_t filled;   // the last one that starts there: it is not empty
+    uint32_t at;       // its place
+    uint32_t code;     // first token whose interval starts in `bucket` or behind it
+};
+__device__ __forceinline__ sort_range between(const sort_bound &r, const sort_bound &z) {
+    if (z.bucket == r.bucket) return {r.bucket, r.bucket, r.at, r.at, r.code, r.code};
+    return {r.filled, z.bucket, r.at, z.at, r.code, z.code};
+}
+// Only a tile's last bucket can reach beyond it, so where a tile's buckets are too many entries for a
+// workgroup that bucket is kept apart as a range of its own, `last` (empty otherwise).  Only if it is too
+// long by itself, or the buckets in front of it are spread over more than SORT_BUCKETS, something
+// is left that no workgroup takes.
+struct sort_cut { sort_range first, last; };  // of a tile that is not sortable as it is
+
+// The tiles' bounds, and the cuts where they are needed; *rest tells the host that there is more to do
+// than k_code_sort over the tiles.
 // A wave finds where a tile's buckets start; the eighth wave of a workgroup looks at the next workgroup's
 // first tile.  (On its own, before the sort: the host hears from it while the sort is running.)
 __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__ starts, int64_t N, int bits,
                                                     int tile, int tiles, const uint32_t *__restrict__ cdf,
-                                                    int32_t n_codes, sort_range *__restrict__ first,
-                                                    sort_range *__restrict__ last, int32_t *rest) {
-    struct bound { uint32_t bucket, filled, at, code; };  // first bucket that starts in the tile or behind it; the last one that starts there
-    __shared__ bound s_bound[CW];
+                                                    int32_t n_codes, sort_bound *__restrict__ bounds,
+                                                    sort_cut *__restrict__ cuts, int32_t *rest) {
+    __shared__ sort_bound s_bound[CW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
     const int t = (int)blockIdx.x * (CW - 1) + w;
     auto start = [&](int i) { return (int64_t)starts[i]; };
@@ -612,25 +627,29 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
             filled = m ? b + __builtin_ctzll(m) : wave_lower_bound(start, buckets, (int64_t)at + 1) - 1;
         }
         const uint32_t c = t == tiles ? (uint32_t)(n_codes + 1) : code_of(b);
-        if (lane == 0) s_bound[w] = {(uint32_t)b, (uint32_t)filled, at, c};
+        if (lane == 0) {
+            s_bound[w] = {(uint32_t)b, (uint32_t)filled, at, c};
+            if (w < CW - 1 || t == tiles) bounds[t] = s_bound[w];
+        }
     }
     __syncthreads();
     if (w == CW - 1 || t >= tiles) return;
-    const bound r = s_bound[w], z = s_bound[w + 1];
-    sort_range f = {r.filled, z.bucket, r.at, z.at, r.code, z.code}, l = {z.bucket, z.bucket, z.at, z.at, z.code, z.code};
-    if (z.bucket == r.bucket) f = {r.bucket, r.bucket, r.at, r.at, r.code, r.code};
-    if (!sortable(f)) {
-        const uint32_t b = (uint32_t)wave_lower_bound(start, buckets, (int64_t)z.at) - 1;  // of the last entry
-        f.end = b + 1;
-        if (f.end_at - f.at > (uint32_t)SORT_CAP) {
-            l = {b, b + 1, starts[b], z.at, code_of((int)b), z.code};
-            f.end_at = l.at;
-            f.end_code = l.code;
-            f.end = f.at == l.at ? f.bucket : (uint32_t)wave_lower_bound(start, buckets, (int64_t)l.at);
-        }
-        if (lane == 0 && (l.at != l.end_at || !sortable(f))) *rest = 1;
+    const sort_bound z = s_bound[w + 1];
+    sort_range f = between(s_bound[w], z);
+    if (sortable(f)) return;
+    const uint32_t b = (uint32_t)wave_lower_bound(start, buckets, (int64_t)z.at) - 1;  // of the last entry
+    sort_range l = {b, b, z.at, z.at, z.code, z.code};
+    f.end = b + 1;
+    if (f.end_at - f.at > (uint32_t)SORT_CAP) {
+        l = {b, b + 1, starts[b], z.at, code_of((int)b), z.code};
+        f.end_at = l.at;
+        f.end_code = l.code;
+        f.end = f.at == l.at ? f.bucket : (uint32_t)wave_lower_bound(start, buckets, (int64_t)l.at);
     }
-    if (lane == 0) { first[t] = f; last[t] = l; }
+    if (lane == 0) {
+        cuts[t] = {f, l};
+        if (l.at != l.end_at || !sortable(f)) *rest = 1;
+    }
 }
 
 template <int TOK>
@@ -689,10 +708,12 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
     }
 }
 
-template <int TOK>
+template <int TOK, bool MORE>
 __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
                                                   const uint32_t *__restrict__ starts,
-                                                  const sort_range *__restrict__ ranges, int64_t N, entry_shape f,
+                                                  const sort_bound *__restrict__ bounds,
+                                                  const sort_cut *__restrict__ cuts,
+                                                  const sort_range *__restrict__ more, entry_shape f,
                                                   const int32_t *__restrict__ text, int32_t D,
                                                   const uint32_t *__restrict__ cdf, int32_t n_codes,
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
@@ -708,10 +729,13 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     __shared__ int32_t s_n_long;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
-    const sort_range range = ranges[blockIdx.x];
+    sort_range range = MORE ? more[blockIdx.x] : between(bounds[blockIdx.x], bounds[blockIdx.x + 1]);
+    if (!MORE && __builtin_expect(!sortable(range), 0)) {
+        range = cuts[blockIdx.x].first;
+        if (!sortable(range)) return;
+    }
     const int b0 = (int)range.bucket, nb = (int)range.end - b0;
     const int64_t a = range.at, z = range.end_at;
-    if (!sortable(range)) return;
     if (z == a) {  // nothing but empty buckets
         if (bucket)
             for (int c = (int)range.code + tid; c < (int)range.end_code; c += CT) bucket[c] = (int32_t)a;
@@ -768,10 +792,10 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             const uint32_t mid = at + (v[k] & 0xffffu);
             o[k] = at | (mid << 16);
             at = mid + (v[k] >> 16);
-#pragma unroll
-            for (int q = 0; q < 2; q++)
-                if (((v[k] >> (16 * q)) & 0xffffu) > (uint32_t)PART_COUNTED) s_long[atomicAdd(&s_n_long, 1)] = (uint16_t)(8 * tid + 2 * k + q);
         }
+        if (__builtin_expect(sum > (uint32_t)PART_COUNTED, 0))
+            for (int q = 0; q < 8; q++)
+                if (((v[q >> 1] >> (16 * (q & 1))) & 0xffffu) > (uint32_t)PART_COUNTED) s_long[atomicAdd(&s_n_long, 1)] = (uint16_t)(8 * tid + q);
         s_area[tid] = make_uint4(o[0], o[1], o[2], o[3]);
     }
     __syncthreads();
@@ -780,40 +804,46 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     for (int k = 0; k < SORT_ITEMS; k++)
         if (k * CT + tid < n) s_entry[part_start(part[k]) + rank[k]] = e[k];
     __syncthreads();
+    const int n_long = s_n_long;
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++)
         if (k * CT + tid < n) {
             const int lo = part_start(part[k]), hi = part_start(part[k] + 1);
             int less = 0;
-            if (hi - lo <= PART_COUNTED)
+            if (__builtin_expect(n_long > 0, 0) && hi - lo > PART_COUNTED)
+                less = (int)rank[k];  // (it stays where it is for now)
+            else
                 for (int i = lo; i < hi; i++) less += s_entry[i] < e[k] ? 1 : 0;
-            rank[k] = hi - lo <= PART_COUNTED ? (uint32_t)(lo + less) : (uint32_t)SORT_CAP;
+            rank[k] = (uint32_t)(lo + less);
         }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++)
-        if (k * CT + tid < n && rank[k] < (uint32_t)SORT_CAP) s_entry[rank[k]] = e[k];
-    const int n_long = s_n_long;
-    for (int i = w; i < n_long; i += CW) {
-        const int lo = part_start(s_long[i]), m = part_start(s_long[i] + 1u) - lo;
-        if (m <= PART_OF_WAVE) network_sort(s_entry + lo, m, lane, 64, [] { wave_sync(); });
-    }
-    for (int i = 0; i < n_long; i++) {
-        const int lo = part_start(s_long[i]), m = part_start(s_long[i] + 1u) - lo;
-        if (m > PART_OF_WAVE) network_sort(s_entry + lo, m, tid, CT, [] { __syncthreads(); });
-    }
+        if (k * CT + tid < n) s_entry[rank[k]] = e[k];
     __syncthreads();
+    if (__builtin_expect(n_long > 0, 0)) {
+        for (int i = w; i < n_long; i += CW) {
+            const int lo = part_start(s_long[i]), m = part_start(s_long[i] + 1u) - lo;
+            if (m <= PART_OF_WAVE) network_sort(s_entry + lo, m, lane, 64, [] { wave_sync(); });
+        }
+        for (int i = 0; i < n_long; i++) {
+            const int lo = part_start(s_long[i]), m = part_start(s_long[i] + 1u) - lo;
+            if (m > PART_OF_WAVE) network_sort(s_entry + lo, m, tid, CT, [] { __syncthreads(); });
+        }
+        __syncthreads();
+    }
     if (bucket) {
         // bucket[c] = first place whose suffix starts with a token code >= c: the entries before
         // it are those with codes below the interval of c
         for (int c = (int)range.code + tid; c < (int)range.end_code; c += CT) {
             const uint32_t end = cdf[c];
-            if ((int)(end >> down) < b0 || (int)(end >> down) >= b0 + nb) {
-                bucket[c] = (int32_t)((int)(end >> down) < b0 ? a : z);
+            const uint32_t in = (end >> down) - (uint32_t)b0;
+            if (in >= (uint32_t)nb) {  // (in front of the buckets, or behind them)
+                bucket[c] = (int32_t)((int32_t)in < 0 ? a : z);
                 continue;
             }
             const uint32_t key = ((end & (uint32_t)((1ull << down) - 1ull)) >> f.key_drop);  // inside the bucket
-            const uint32_t p = (((end >> down) - (uint32_t)b0) << fine) + (key >> (in_bucket - fine));
+            const uint32_t p = (in << fine) + (key >> (in_bucket - fine));
             int at = part_start(p);
             const int to = part_start(p + 1);
             while (at < to && ((uint32_t)(s_entry[at] >> low_bits) & key_mask) < key) at++;
@@ -1042,8 +1072,8 @@ struct rest_range {
 enum { REST_ANY = 0, REST_RANGES, REST_LONG, REST_ENTRIES, REST_BUCKETS };  // words of h_flag
 
 // Lists, in order, the ranges that k_code_sort can take and has not, and those that it cannot.  One workgroup.
-__global__ __launch_bounds__(CT) void k_rest_lists(const sort_range *__restrict__ first,
-                                                   const sort_range *__restrict__ last, int tiles,
+__global__ __launch_bounds__(CT) void k_rest_lists(const sort_bound *__restrict__ bounds,
+                                                   const sort_cut *__restrict__ cuts, int tiles,
                                                    sort_range *__restrict__ more, rest_range *__restrict__ rest,
                                                    uint32_t *__restrict__ out) {
     __shared__ uint32_t s_wave[CW];
@@ -1051,7 +1081,10 @@ __global__ __launch_bounds__(CT) void k_rest_lists(const sort_range *__restrict_
     for (int base = 0; base < tiles; base += CT) {
         const int t = base + (int)threadIdx.x;
         sort_range r[2] = {};
-        if (t < tiles) { r[0] = first[t]; r[1] = last[t]; }
+        if (t < tiles && !sortable(between(bounds[t], bounds[t + 1]))) {
+            r[0] = cuts[t].first;
+            r[1] = cuts[t].last;
+        }
         const bool is_rest[2] = {!sortable(r[0]), !sortable(r[1])}, is_more = r[1].at != r[1].end_at && !is_rest[1];
         uint32_t entries = 0, buckets = 0, tot;
 #pragma unroll
@@ -1282,7 +1315,7 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *hist_words = h + MAX_BINS + 1;
     *start_words = s;
     *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
-    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)((3 * sizeof(sort_range) + 2 * sizeof(rest_range)) / 4);
+    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)((2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
     *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
 
@@ -1342,24 +1375,28 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
 // The tables of ranges, in b_ranges.
 struct sort_tables {
     int tile, tiles;
-    sort_range *first, *last, *more;
-    rest_range *rest;
+    sort_bound *bounds;  // tiles + 1
+    sort_cut *cuts;
+    sort_range *more;
+    rest_range *rest;    // two for every tile
 };
 static sort_tables tables_for(const sd_ctx *c, int64_t N) {
     sort_tables t;
     t.tile = sort_tile_for(N, c->n_cu);
     t.tiles = (int)((N + t.tile - 1) / t.tile);
     t.rest = reinterpret_cast<rest_range *>(c->b_ranges);
-    t.first = reinterpret_cast<sort_range *>(t.rest + 2 * (int64_t)t.tiles);
-    t.last = t.first + t.tiles;
-    t.more = t.last + t.tiles;
+    t.bounds = reinterpret_cast<sort_bound *>(t.rest + 2 * (int64_t)t.tiles);
+    t.cuts = reinterpret_cast<sort_cut *>(t.bounds + t.tiles + 1);
+    t.more = reinterpret_cast<sort_range *>(t.cuts + t.tiles);
     return t;
 }
 
-static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_range *ranges, int n, int64_t N, entry_shape f,
+// the tiles, or n ranges `more`
+static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, const sort_range *more, int n, entry_shape f,
                         const int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (c->cfg.vocab < (1 << 21) - 1 ? k_code_sort<6> : k_code_sort<4>),
-              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, ranges, N, f, text, c->cfg.D, c->code_cdf,
+    const bool wide = c->cfg.vocab >= (1 << 21) - 1;
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (more ? (wide ? k_code_sort<4, true> : k_code_sort<6, true>) : wide ? k_code_sort<4, false> : k_code_sort<6, false>),
+              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, more, f, text, c->cfg.D, c->code_cdf,
               c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
 
@@ -1401,9 +1438,9 @@ void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     }
     const sort_tables t = tables_for(c, N);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
-              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.first, t.last, c->h_flag);
+              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, c->h_flag);
     (void)hipEventRecord(c->code_asked, st);
-    sort_ranges(c, ent1, t.first, t.tiles, N, f, text, sa, tok1, bucket, st);
+    sort_ranges(c, ent1, t, nullptr, t.tiles, f, text, sa, tok1, bucket, st);
 }
 
 // The ranges that sd_code_sort's workgroups have not taken; waits for the stream.
@@ -1413,12 +1450,12 @@ sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t
     const sort_tables t = tables_for(c, N);
     const dim3 block(CT);
     auto grid = [](int64_t n, int per) { return dim3((unsigned)((n + per - 1) / per)); };
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_lists, dim3(1), block, 0, t.first, t.last, t.tiles, t.more, t.rest, (uint32_t *)c->h_flag);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_lists, dim3(1), block, 0, t.bounds, t.cuts, t.tiles, t.more, t.rest, (uint32_t *)c->h_flag);
     if (hipEventRecord(c->code_asked, st) != hipSuccess || hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;
     const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
     const int ranges = (int)told[REST_RANGES], n = (int)told[REST_LONG];
     const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
-    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t.more, ranges, N, f, text, sa, tok1, bucket, st);
+    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, t.more, ranges, f, text, sa, tok1, bucket, st);
     if (n == 0) return SD_OK;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
     uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;
