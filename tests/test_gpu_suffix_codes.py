@@ -274,3 +274,66 @@ def test_repeated_text_costs_no_more_than_doubling(times):
     finally:
         del graph
         sd.sd_destroy(ctx)
+
+
+@pytest.mark.parametrize("n_docs,body", [(1025, 0), (6000, 30_000), (9000, 1_050_000)])
+@pytest.mark.parametrize("captured", [False, True])
+def test_more_documents_than_the_layout_keeps(n_docs, body, captured):
+    """Runs of empty documents and of documents of one token: more of them in a tile of positions (2048,
+    6144 above 2^20) than k_layout keeps the starts of (1024), in front of, between and behind
+    ordinary documents; laid out with codes and, under capture, without."""
+    import torch
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(n_docs)
+    D, vocab = 12, 500
+    short = [rng.integers(0, vocab, int(rng.integers(0, 2))).astype(np.int32) for _ in range(n_docs)]
+    short[100:1200] = [np.zeros(0, np.int32)] * len(short[100:1200])
+    long = np.array_split(rng.integers(0, vocab, body).astype(np.int32), 40) if body else []
+    at = n_docs // 3
+    docs = short[:at] + long[:20] + short[at:2 * at] + long[20:] + short[2 * at:]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in docs))
+    try:
+        if captured:
+            tokens, off, n = g._seqs(docs)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                sd.sd_index_build(g.ctx, sd.SD_SCOPE_GLOBAL, None, tokens, off, n)
+            graph.replay()
+        else:
+            g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("D", [15, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("N", [61, 62, 63, 247, 248, 249, 433, 434, 435, 1239, 1240, 1241])
+def test_entropy_around_chunks_and_waves(N, D):
+    """The common-prefix lengths are counted 16 tokens at a time, 62 entries to a wave and 248 to a
+    workgroup: documents that are one text cut around multiples of 16 (prefixes and stops there), in
+    an index that ends at a wave's or a workgroup's last entry or beside it."""
+    import oracle
+    rng = np.random.default_rng(N)
+    vocab = 300
+    base = rng.integers(0, vocab, 80).astype(np.int32)
+    docs, left = [], N
+    for n in (16, 15, 17, 32, 31, 33, 48, 47, 49, 64, 63, 65) * 2:
+        if left > n + 1:
+            docs.append(base[80 - n:] if n % 2 else base[:n])
+            left -= n + 1
+    if left:
+        docs.append(rng.integers(0, vocab, left - 1).astype(np.int32))
+    assert sum(len(d) + 1 for d in docs) == N
+    g = parity.GpuPath(vocab, D, 4, 1.0, 0.1, 1, 16, N)
+    try:
+        g.build_global(docs)
+        got, weight = g.entropy()
+    finally:
+        g.close()
+    t = oracle.Trie(D)
+    for d in docs:
+        t.add_doc(d)
+    want, want_weight = t.entropy()
+    assert weight == want_weight
+    # binary64 sums of the same terms in another order, as in test_entropy_matches_oracle
+    assert got == pytest.approx(want, rel=1e-9, abs=1e-12)
