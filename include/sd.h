@@ -19,8 +19,9 @@
  *    work; they do not synchronise the device.  sd_create, sd_destroy and
  *    sd_get_stats synchronise.  sd_index_build of the global index and
  *    sd_index_insert wait for `hip_stream` while they enqueue (once for
- *    ordinary text, to hear whether the sort coped with it, a few times more for
- *    text that repeats itself so often that it did not), unless the stream is
+ *    ordinary text, to hear whether the sort coped with it, once more for
+ *    text that repeats itself so often that it did not, and a few times where positions and tokens
+ *    need more than 47 bits together), unless the stream is
  *    being captured into a graph: then they only enqueue.  Their last kernels may
  *    still be in flight when they return.
  *  - Errors the host can see (bad arguments, sizes beyond the configured
@@ -290,11 +291,13 @@ sd_status sd_get_stats(sd_ctx *ctx, sd_stats *host_out);
  * which leaves wall-clock marks for the two sd_debug_read_*_ticks calls (calls of up to
  * SD_TICK_SLOTS requests: larger ones run the ordinary kernel).  sd_debug_profile_read
  * synchronises, reports per-kernel launch counts, total milliseconds and
- * counted bytes since the previous read, and clears them. */
+ * counted bytes since the previous read, and clears them.  The SORT kinds and CODE_SORT (ordering
+ * whole buckets in LDS) hold the sorting of a build and of an insertion's new documents alike;
+ * INSERT is their ranking in the old index and the merge. */
 enum {
     SD_K_SPECULATE = 0, SD_K_ACCEPT = 1, SD_K_APPEND = 2, SD_K_REQ_BUILD = 3, SD_K_SORT_HIST = 4,
     SD_K_SORT_SCAN = 5, SD_K_SORT_SCATTER = 6, SD_K_BUILD_OTHER = 7, SD_K_INSERT = 8,
-    SD_K_ACCEPT_SPECULATE = 9, SD_K_COUNT = 10
+    SD_K_ACCEPT_SPECULATE = 9, SD_K_CODE_SORT = 10, SD_K_COUNT = 11
 };
 #define SD_PROF_MAX_SPANS 8192
 #define SD_TICK_SLOTS 1024

@@ -59,7 +59,7 @@ SD_TICK_SLOTS = 1024   # requests the timing variant of sd_speculate keeps marks
 
 
 KERNEL_NAMES = ["speculate", "accept", "append", "req_build", "sort_hist", "sort_scan",
-                "sort_scatter", "build_other", "insert", "accept_speculate"]
+                "sort_scatter", "build_other", "insert", "accept_speculate", "code_sort"]
 
 
 class _Profile(C.Structure):

@@ -1395,7 +1395,7 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
 static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, const sort_range *more, int n, entry_shape f,
                         const int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const bool wide = c->cfg.vocab >= (1 << 21) - 1;
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (more ? (wide ? k_code_sort<4, true> : k_code_sort<6, true>) : wide ? k_code_sort<4, false> : k_code_sort<6, false>),
+    SD_LAUNCH(c, SD_K_CODE_SORT, st, (more ? (wide ? k_code_sort<4, true> : k_code_sort<6, true>) : wide ? k_code_sort<4, false> : k_code_sort<6, false>),
               dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, more, f, text, c->cfg.D, c->code_cdf,
               c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
