@@ -204,7 +204,7 @@ typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
 // rank[j] = number of old suffixes that sort before, or tie with, new suffix j.
 // Bound: dependent loads (suffix array, then text), so RANK_LANES lanes look for a suffix's place side
 // by side, each at a suffix of its own: a bucket of 17 takes two rounds instead of five, and its
-// tokens come eight at a time (32k new suffixes into 2.2M: 39 -> 14 us).
+// tokens come eight at a time (32k new suffixes into 2.2M: 39 -> 20 us).
 // A workgroup strides over the new suffixes: a grid of RANK_LANES lanes for each of them would pass
 // the 2^32 threads of a launch at 2^29 suffixes.  RANK_BLOCKS is 32 rounds of what the chip holds.
 constexpr int RANK_LANES = 8;
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ 
 // entries, the others a tile of old ones each.
 // Bound: the bytes of both arrays.  The new suffixes that go into a tile are found by a wave in three
 // rounds of loads and kept in LDS, where every old entry finds its shift (2.2M old, 32k new: 28 and
-// 5 us for old and new entries apart, 256 entries a workgroup -> 13 us, and 17 us less for the table).
+// 5 us for old and new entries apart, 256 entries a workgroup -> 16 us, and 17 us less for the table).
 constexpr int MERGE_ITEMS = 8, MERGE_TILE = TB * MERGE_ITEMS, MERGE_RANKS = 2048;
 
 // number of values in the rising rank[0..n) that are <= key; whole wave
@@ -504,8 +504,8 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 // fit, or the stream cannot be waited for, which is how the host hears whether anything is left.
 // The tokens' intervals serve until there is twice as much text as they were sampled from: an index that
 // starts empty and grows by insertion would otherwise keep those of its first document, and codes
-// made with the intervals of other text fall into few buckets.  The sample (three launches, 15 to
-// 20 us) is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
+// made with the intervals of other text fall into few buckets.  The sample (three launches, 25 us)
+// is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
 static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
                                  int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
                                  int32_t *bucket, int64_t old, hipStream_t st) {

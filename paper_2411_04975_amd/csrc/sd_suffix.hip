@@ -19,15 +19,16 @@
 //
 // Bound: the memory system.  Per position 72 bytes in order (tokens read, text and code written and
 // read, entries written and read once per pass, suffix array and second tokens written), and
-// for each one that ties one or two random cache lines, which are what costs: 10M gathers of 16 or
-// 64 bytes from a 40 MB text take 185 or 237 us, a copy of 680 MB 135 us.
+// for each one that ties one or two random cache lines a step, which are what costs: of the 0.58 ms of
+// 10M tokens copied from templates k_code_sort takes 0.34 and reads 220 bytes a position in them,
+// 6.4 TB/s (100M: 4.0 of 6.2 ms, 260 bytes, 6.6 TB/s), against 0.09 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
-// Build of 10M tokens copied from templates 1.68 -> 0.65 ms, of 10M of a Zipf law 2.89 -> 0.40 ms, of
-// 100M copied 20.7 -> 7.0 ms, against prefix doubling for everything.
+// Build of 10M tokens copied from templates 1.68 -> 0.59 ms, of 10M of a Zipf law 2.89 -> 0.32 ms, of
+// 100M copied 20.7 -> 6.2 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 
 namespace {
@@ -94,7 +95,7 @@ __device__ __forceinline__ int wave_lower_bound(AT at, int n, int64_t key) {
 // additions to one address, at some 30 ns each.
 // What it found goes into one of several copies of the counts: frequent tokens lie next to each
 // other in many vocabularies, and additions to one line queue up just the same (10M tokens of a
-// Zipf law: 75 us with one copy).
+// Zipf law: 24 us, 75 with one copy).
 constexpr int64_t SAMPLE_MIN = 4096;   // runs: a bin of a 256-way split sees 1000 of their tokens
 constexpr int SAMPLE_ONE_IN = 64;      // a token that goes unseen has a few hundred occurrences at most
 constexpr int64_t SAMPLE_MAX = 32768;  // 16 * 64 * SAMPLE_MAX + 4 * 2^24, the weights' total, is below 2^27
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 // last: document j starts at offs[j] + j.  The tile's documents are looked up once, in the offsets
 // in memory, and each position then among these in LDS.  What takes the time is the gather of the
 // intervals (one line of the L2 per position; 10M from a 512 KB table: 46 us), so the text is written
-// on the way (10M tokens, 128k of them different: 73 us together; text and codes by kernels of
+// on the way (10M tokens, 128k of them different: 71 us together; text and codes by kernels of
 // their own took 53 and 55).
 constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
 constexpr int LDS_DOCS = 1024;
