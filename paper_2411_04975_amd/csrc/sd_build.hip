@@ -523,9 +523,11 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
             sd_code_intervals(c, tokens, n_seq, n_tokens, st);
         c->code_seen = seen;
     }
-    sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st);
-    if (hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;  // (the sort is still running)
-    return *const_cast<volatile int32_t *>(c->h_flag) ? sd_code_rest(c, N, text, sa, tok1, bucket, st) : SD_OK;
+    if (!sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st) ||
+        hipEventSynchronize(c->code_asked) != hipSuccess)  // (the sort is still running)
+        return SD_ERR_HIP;
+    if (*const_cast<volatile int32_t *>(c->h_flag) && sd_code_rest(c, N, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
+    return hipGetLastError() == hipSuccess ? SD_OK : SD_ERR_HIP;
 }
 
 sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t *d_offsets,

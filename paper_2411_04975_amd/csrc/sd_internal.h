@@ -112,7 +112,7 @@ bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);
-void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
+bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);
 // what that left undone, if h_flag says so
 sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);

@@ -1404,8 +1404,8 @@ static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t
 // Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
 // given, receives the second-token column, bucket the table of first places by token code.
 // h_flag (pinned host memory, its first word zero before) becomes 1 if the text is so repetitive that
-// sd_code_rest has to follow.  code_asked is recorded where that is known.
-void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
+// sd_code_rest has to follow.  code_asked is recorded where that is known; false: it could not be.
+bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     const split_plan p = plan_for(N);
@@ -1440,8 +1440,9 @@ void sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     const sort_tables t = tables_for(c, N);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
               c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, c->h_flag);
-    (void)hipEventRecord(c->code_asked, st);
+    const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
     sort_ranges(c, ent1, t, nullptr, t.tiles, f, text, sa, tok1, bucket, st);
+    return asked;
 }
 
 // The ranges that sd_code_sort's workgroups have not taken; waits for the stream.
