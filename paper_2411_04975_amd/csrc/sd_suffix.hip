@@ -559,8 +559,8 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 // its own, and counting the lower entries of its part there.  (Copies of one text share their part, and
 // counting is quadratic in them: parts of more than PART_COUNTED entries go through a bitonic network
 // instead.  Build of 10M tokens, half of them copies of preambles, 500, 1000, 2000 of each: 1.30,
-// 1.68, 2.9 ms; 1.70, 2.64, 5.5 by counting.)  From there on a wave takes care of
-// its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
+// 1.68, 2.9 ms; 1.70, 2.64, 5.5 by counting.)  Groups of more than GROUP_OF_WAVE entries that tie are
+// split by the whole workgroup first.  From there on a wave takes care of its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
 // one place of the list, whole groups together, shows the next TOK tokens of every entry to the
 // wave through LDS, counts for each entry the group's members that sort before it, moves the
 // positions to their new places, does so for another TOK tokens (which came with the same
@@ -575,6 +575,7 @@ constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 constexpr int PART_COUNTED = 64;    // entries of a part whose order is found by counting, at most
 constexpr int PART_OF_WAVE = 512;   // of one that a wave sorts alone
+constexpr int GROUP_OF_WAVE = 256;  // of a group of ties that a wave deals with alone
 static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
 
 // What a workgroup takes: whole buckets, and the part of the bucket table that they answer for.
@@ -724,9 +725,13 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     __shared__ uint32_t s_start[SORT_BUCKETS + 1];  // places of the workgroup's buckets
     __shared__ uint32_t s_first[SORT_CAP / 32 + 4];  // bit per place: a group starts here
     __shared__ uint32_t s_done[SORT_CAP / 32];       // bit per place: see below
-    __shared__ uint64_t s_class[2][SORT_CAP / 64 + 2 * CW];
+    __shared__ uint64_t s_class[2][SORT_CAP / 64];   // of a long group: entries below and at the middle one
+    __shared__ uint32_t s_before[SORT_CAP / 64 + 1];
+    __shared__ uint32_t s_todo[SORT_CAP / GROUP_OF_WAVE];  // long groups: place, depth from bit 16 on
+    __shared__ int32_t s_n_todo;
     __shared__ uint32_t s_wave[CW];
     __shared__ uint16_t s_long[SORT_CAP / PART_COUNTED];  // parts that are not counted
+    __shared__ uint32_t s_bounds[SORT_CAP / PART_COUNTED];  // their places: first, end from bit 16 on
     __shared__ int32_t s_n_long;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
@@ -746,7 +751,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     s_area[tid] = make_uint4(0u, 0u, 0u, 0u);
     if (tid < SORT_CAP / 32 + 4) s_first[tid] = 0;
     if (tid < SORT_CAP / 32) s_done[tid] = 0;
-    if (tid == 0) s_n_long = 0;
+    if (tid == 0) s_n_long = s_n_todo = 0;
     const int n = (int)(z - a);
     uint64_t e[SORT_ITEMS];
 #pragma unroll
@@ -823,6 +828,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
         if (k * CT + tid < n) s_entry[rank[k]] = e[k];
     __syncthreads();
     if (__builtin_expect(n_long > 0, 0)) {
+        if (tid < n_long) s_bounds[tid] = (uint32_t)part_start(s_long[tid]) | (uint32_t)part_start(s_long[tid] + 1u) << 16;
         for (int i = w; i < n_long; i += CW) {
             const int lo = part_start(s_long[i]), m = part_start(s_long[i] + 1u) - lo;
             if (m <= PART_OF_WAVE) network_sort(s_entry + lo, m, lane, 64, [] { wave_sync(); });
@@ -874,7 +880,6 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
         if (k * CT + tid < n) s_pos[k * CT + tid] = pos_k[k];
     __syncthreads();
 
-    // from here on the waves are on their own
     auto next_first = [&](int x) {  // first group start at or behind place x <= n
         int i = x >> 5;
         uint32_t v = s_first[i] & (0xffffffffu << (x & 31));
@@ -883,6 +888,96 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     };
     auto set_first = [&](int x) { atomicOr(&s_first[x >> 5], 1u << (x & 31)); };
     auto is_first = [&](int x) { return (s_first[x >> 5] >> (x & 31)) & 1u; };
+    auto no_first = [&](int x, int k) {  // of the k > 32 places from x on; those behind the last one are none
+        for (int i = x >> 5; i <= (x + k - 1) >> 5 && i < SORT_CAP / 32 + 4; i++) {
+            uint32_t v = s_first[i];
+            if (i == x >> 5) v &= 0xffffffffu << (x & 31);
+            if (i == (x + k - 1) >> 5) v &= 0xffffffffu >> (31 - ((x + k - 1) & 31));
+            if (v) return false;
+        }
+        return true;
+    };
+    // how the 2 TOK tokens at q compare to those of mx and my
+    auto compare_to = [&](const int32_t *q, const token_words<TOK> &mx, const token_words<TOK> &my, bool *lt, bool *eq) {
+        int32_t unused;
+        const token_words<TOK> x = words_at<TOK>(q, &unused), y = words_at<TOK>(q + TOK, &unused);
+        const bool e1 = x.a == mx.a, e2 = x.b == mx.b, e3 = y.a == my.a, e4 = y.b == my.b;
+        *lt = !e1 ? x.a < mx.a : !e2 ? x.b < mx.b : !e3 ? y.a < my.a : y.b < my.b;
+        *eq = e1 && e2 && e3 && e4;
+    };
+    // Long groups (the entries of a group share their part): the whole workgroup splits them as split_group
+    // does, until what is left of them is short enough for a wave.  What has agreed on D tokens falls
+    // apart into single entries in the order that they have.
+    if (__builtin_expect(n_long > 0, 0)) {
+        for (int i = 0; i < n_long; i++) {
+            const uint32_t b = s_bounds[i];
+            for (int x = (int)(b & 0xffffu) + tid; x < (int)(b >> 16); x += CT)
+                if (is_first(x) && no_first(x + 1, GROUP_OF_WAVE)) s_todo[atomicAdd(&s_n_todo, 1)] = (uint32_t)x | 2u << 16;
+        }
+        for (;;) {
+            __syncthreads();
+            const int left = s_n_todo;
+            if (left == 0) break;
+            const uint32_t item = s_todo[left - 1];
+            const int p = (int)(item & 0xffffu), h = (int)(item >> 16), k = next_first(p + 1) - p;
+            int32_t unused;
+            const int32_t *mid = text + (int64_t)s_pos[p + k / 2] + h;
+            const token_words<TOK> mx = words_at<TOK>(mid, &unused), my = words_at<TOK>(mid + TOK, &unused);
+            uint32_t pos[SORT_ITEMS];
+#pragma unroll
+            for (int q = 0; q < SORT_ITEMS; q++) {
+                const int j = q * CT + tid;
+                bool lt = false, eq = false;
+                if (q * CT < k) {
+                    if (j < k) {
+                        pos[q] = s_pos[p + j];
+                        compare_to(text + (int64_t)pos[q] + h, mx, my, &lt, &eq);
+                    }
+                    const uint64_t bl = __ballot(lt), be = __ballot(eq);
+                    if (lane == 0) { s_class[0][q * CW + w] = bl; s_class[1][q * CW + w] = be; }
+                }
+            }
+            __syncthreads();
+            if (w == 0) {  // what lies before each run of 64 entries, below and equal
+                const bool some = lane * 64 < k;
+                const uint32_t v = some ? (uint32_t)__popcll(s_class[0][lane]) | (uint32_t)__popcll(s_class[1][lane]) << 16 : 0u;
+                uint32_t inc = v;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t u = __shfl_up(inc, o);
+                    if (lane >= o) inc += u;
+                }
+                s_before[lane] = inc - v;
+                if (lane == 63) s_before[64] = inc;
+            }
+            __syncthreads();
+            const int nl = (int)(s_before[64] & 0xffffu), ne = (int)(s_before[64] >> 16), next_h = h + 2 * TOK;
+#pragma unroll
+            for (int q = 0; q < SORT_ITEMS; q++) {
+                const int j = q * CT + tid, run = q * CW + w;
+                if (j < k) {
+                    const uint64_t bl = s_class[0][run], be = s_class[1][run], lt = (1ull << lane) - 1ull;
+                    const int l = (int)(s_before[run] & 0xffffu), e = (int)(s_before[run] >> 16);
+                    const bool is_equal = (be >> lane) & 1ull;
+                    const int to = p + ((bl >> lane) & 1ull ? l + __popcll(bl & lt) : is_equal ? nl + e + __popcll(be & lt) :
+                                        nl + ne + (run * 64 - l - e) + __popcll(~(bl | be) & lt));
+                    s_pos[to] = pos[q];
+                    if (is_equal && next_h >= D) set_first(to);
+                }
+            }
+            if (tid == 0) {
+                int top = left - 1;
+                if (nl > 0) set_first(p + nl);
+                if (nl + ne < k) set_first(p + nl + ne);
+                if (nl > GROUP_OF_WAVE) s_todo[top++] = item;
+                if (k - nl - ne > GROUP_OF_WAVE) s_todo[top++] = (uint32_t)(p + nl + ne) | (uint32_t)h << 16;
+                if (ne > GROUP_OF_WAVE && next_h < D) s_todo[top++] = (uint32_t)(p + nl) | (uint32_t)next_h << 16;
+                s_n_todo = top;
+            }
+        }
+    }
+
+    // from here on the waves are on their own
     const int share = (n + CW - 1) / CW;
     const int s_begin = next_first(w * share < n ? w * share : n);
     const int s_end = next_first((w + 1) * share < n ? (w + 1) * share : n);
@@ -956,40 +1051,35 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     // h on: entries below, at and above those of its middle entry, each in the order that they
     // had.  The middle part is done with these tokens, which s_done notes at its first place.
     auto split_group = [&](int p, int k, int h) {
-        uint64_t *below = s_class[0] + s_begin / 64 + w, *equal = s_class[1] + s_begin / 64 + w;
         int32_t unused;
         const int32_t *mid = text + (int64_t)s_pos[p + k / 2] + h;
         const token_words<TOK> mx = words_at<TOK>(mid, &unused), my = words_at<TOK>(mid + TOK, &unused);
+        uint32_t pos[GROUP_OF_WAVE / 64];
+        uint64_t below[GROUP_OF_WAVE / 64], equal[GROUP_OF_WAVE / 64];
         int nl = 0, ne = 0;
-        for (int c = 0; c < k; c += 64) {
+#pragma unroll
+        for (int q = 0; q < GROUP_OF_WAVE / 64; q++) {
             bool lt = false, eq = false;
-            if (c + lane < k) {
-                const uint32_t pos = s_pos[p + c + lane];
-                const int32_t *q = text + (int64_t)pos + h;
-                const token_words<TOK> x = words_at<TOK>(q, &unused), y = words_at<TOK>(q + TOK, &unused);
-                const bool e1 = x.a == mx.a, e2 = x.b == mx.b, e3 = y.a == my.a, e4 = y.b == my.b;
-                lt = !e1 ? x.a < mx.a : !e2 ? x.b < mx.b : !e3 ? y.a < my.a : y.b < my.b;
-                eq = e1 && e2 && e3 && e4;
-                sa[a + p + c + lane] = (int32_t)pos;  // (kept there while the group is moved)
+            if (q * 64 + lane < k) {
+                pos[q] = s_pos[p + q * 64 + lane];
+                compare_to(text + (int64_t)pos[q] + h, mx, my, &lt, &eq);
             }
-            const uint64_t bl = __ballot(lt), be = __ballot(eq);
-            if (lane == 0) { below[c >> 6] = bl; equal[c >> 6] = be; }
-            nl += __popcll(bl);
-            ne += __popcll(be);
+            below[q] = __ballot(lt);
+            equal[q] = __ballot(eq);
+            nl += __popcll(below[q]);
+            ne += __popcll(equal[q]);
         }
         wave_sync();
-        int l = 0, q = nl, g = nl + ne;
-        for (int c = 0; c < k; c += 64) {
-            const uint64_t all = k - c < 64 ? (1ull << (k - c)) - 1ull : ~0ull;
-            const uint64_t bl = below[c >> 6], be = equal[c >> 6], ba = all & ~(bl | be), lt = (1ull << lane) - 1ull;
-            if (c + lane < k) {
-                const uint32_t pos = (uint32_t)sa[a + p + c + lane];
-                const bool il = (bl >> lane) & 1ull, ie = (be >> lane) & 1ull;
-                s_pos[p + (il ? l + __popcll(bl & lt) : ie ? q + __popcll(be & lt) : g + __popcll(ba & lt))] = pos;
-            }
-            l += __popcll(bl);
-            q += __popcll(be);
-            g += __popcll(ba);
+        int l = 0, e = nl, g = nl + ne;
+#pragma unroll
+        for (int q = 0; q < GROUP_OF_WAVE / 64; q++) {
+            const uint64_t lt = (1ull << lane) - 1ull, above = ~(below[q] | equal[q]);
+            if (q * 64 + lane < k)
+                s_pos[p + ((below[q] >> lane) & 1ull ? l + __popcll(below[q] & lt) :
+                           (equal[q] >> lane) & 1ull ? e + __popcll(equal[q] & lt) : g + __popcll(above & lt))] = pos[q];
+            l += __popcll(below[q]);
+            e += __popcll(equal[q]);
+            g += __popcll(above);
         }
         if (lane == 0) {
             if (nl > 0) set_first(p + nl);

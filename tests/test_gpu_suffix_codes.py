@@ -63,7 +63,7 @@ def test_sizes(n, vocab, copies):
         g.close()
 
 
-@pytest.mark.parametrize("times", [63, 64, 65, 130, 511, 512, 513, 700, 1900, 4096, 4097, 5000])
+@pytest.mark.parametrize("times", [63, 64, 65, 130, 256, 257, 511, 512, 513, 700, 1900, 4096, 4097, 5000])
 def test_repeated_phrase(times):
     """A phrase of 40 tokens in front of `times` documents that go on differently, two of them alike."""
     rng = np.random.default_rng(times)
