@@ -504,8 +504,10 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 // fit, or the stream cannot be waited for, which is how the host hears whether anything is left.
 // The tokens' intervals serve until there is twice as much text as they were sampled from: an index that
 // starts empty and grows by insertion would otherwise keep those of its first document, and codes
-// made with the intervals of other text fall into few buckets.  The sample (three launches, 25 us)
-// is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
+// made with the intervals of other text fall into few buckets.  Where buckets of an insertion turned out
+// too long, the next one's intervals are its own (outputs that start alike with tokens that are rare in the
+// old text share buckets: 2000 of 100 tokens with one head of 60 into 2M: 1.45 ms, 0.48 from the second insertion on).
+// The sample (three launches, 25 us) is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
 static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
                                  int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
                                  int32_t *bucket, int64_t old, hipStream_t st) {
@@ -516,17 +518,19 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
     }
     *c->h_flag = 0;
     const int64_t seen = old > N ? old : N;
-    if (c->code_seen == 0 || seen >= 2 * c->code_seen) {
-        if (old > N)
+    if (c->code_seen == 0 || seen >= 2 * c->code_seen || c->code_misfit) {
+        if (old > N && !c->code_misfit)
             sd_code_intervals(c, c->g_text, c->g_docs, old, st);
         else
             sd_code_intervals(c, tokens, n_seq, n_tokens, st);
         c->code_seen = seen;
+        c->code_misfit = false;
     }
     if (!sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st) ||
         hipEventSynchronize(c->code_asked) != hipSuccess)  // (the sort is still running)
         return SD_ERR_HIP;
-    if (*const_cast<volatile int32_t *>(c->h_flag) && sd_code_rest(c, N, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
+    c->code_misfit = *const_cast<volatile int32_t *>(c->h_flag) != 0;
+    if (c->code_misfit && sd_code_rest(c, N, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
     return hipGetLastError() == hipSuccess ? SD_OK : SD_ERR_HIP;
 }
 

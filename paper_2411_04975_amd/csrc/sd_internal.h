@@ -66,6 +66,7 @@ struct sd_ctx {
     int32_t *code_bucket = nullptr;     // [vocab + 2]: bucket table of the documents of an insertion
     uint32_t *code_sums = nullptr;      // [chunks of tiles][bins], zero between builds
     int64_t code_seen = 0;              // positions of the text that code_cdf was sampled from; 0: of none
+    bool code_misfit = false;           // the last input had buckets that did not fit a workgroup
     uint32_t *b_starts = nullptr;       // first entry of every bucket
     uint32_t *b_ranges = nullptr;       // what each workgroup of the sort in LDS takes
     uint32_t *rest_table = nullptr;     // by bucket: which of those that are sorted by prefix doubling

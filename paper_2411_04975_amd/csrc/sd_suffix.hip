@@ -556,15 +556,19 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 // ---- ordering whole buckets in LDS ------------------------------------------------------------
 // A workgroup takes the buckets that start in its tile of the entries: codes are spread evenly, so
 // one count over equal parts of the buckets' code ranges puts every entry within a few places of
-// its own, and counting the lower entries of its part there.  (Copies of one text share their part, and
-// counting is quadratic in them: parts of more than PART_COUNTED entries go through a bitonic network
-// instead.  Build of 10M tokens, half of them copies of preambles, 500, 1000, 2000 of each: 1.30,
-// 1.68, 2.9 ms; 1.70, 2.64, 5.5 by counting.)  Groups of more than GROUP_OF_WAVE entries that tie are
-// split by the whole workgroup first.  From there on a wave takes care of its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
+// its own, and counting the lower entries of its part there.  From there on a wave takes care of
+// its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
 // one place of the list, whole groups together, shows the next TOK tokens of every entry to the
 // wave through LDS, counts for each entry the group's members that sort before it, moves the
 // positions to their new places, does so for another TOK tokens (which came with the same
 // gather), and keeps on the list what still ties.
+//
+// Copies of one text share their part of the code range and tie: counting would be quadratic in
+// them.  Parts of more than PART_COUNTED entries go through a bitonic network instead, and groups of more
+// than GROUP_OF_WAVE entries that tie are split in three by the tokens of their middle entry, by the
+// whole workgroup (128 and 512 instead of 256: up to a tenth slower).  Builds of 10M tokens, half of them
+// copies of preambles, with 200, 500, 1000, 2000 copies of each: 0.94, 1.24, 1.23, 1.56 ms; 1.16, 1.71, 2.61,
+// 5.5 by counting, each long group split by one wave.
 //
 // Tokens are compared as two 64-bit words: three of 21 bits each, two of 32 for vocabularies
 // beyond that.

@@ -185,6 +185,32 @@ def _runs(rng, n):
     return [t]
 
 
+def test_intervals_of_an_insertion_that_did_not_fit():
+    """Outputs that start alike, with tokens that are no more frequent than others in the index: heads share
+    buckets, and some are too long.  The second such insertion brings its own intervals, and one split and
+    the sort in LDS are enough for it."""
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(5)
+    D, vocab = 40, 30000
+    docs = [rng.integers(0, vocab, 400_000).astype(np.int32)]
+    batches = [_preambles(rng, vocab, 2500, 2500, 60, 20) for _ in range(2)]
+    splits = []
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in docs + batches[0] + batches[1]))
+    try:
+        g.build_global(docs)
+        for new in batches:
+            sd.sd_debug_profile(g.ctx, 1)
+            sd.sd_debug_profile_read(g.ctx)
+            g.insert_global(new)
+            splits.append(sd.sd_debug_profile_read(g.ctx)["sort_scatter"]["launches"])
+            sd.sd_debug_profile(g.ctx, 0)
+            docs = docs + new
+            _check(g, docs, D)
+        assert splits[0] > 1 and splits[1] == 1
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("name", ["one split", "two splits", "neighbours", "runs", "one token"])
 @pytest.mark.parametrize("insert", [False, True])
 def test_buckets_beyond_a_workgroup(name, insert):
