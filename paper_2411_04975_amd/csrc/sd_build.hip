@@ -209,6 +209,7 @@ typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
 // the 2^32 threads of a launch at 2^29 suffixes.  RANK_BLOCKS is 32 rounds of what the chip holds.
 constexpr int RANK_LANES = 8;
 constexpr unsigned RANK_BLOCKS = 1u << 16;
+constexpr uint32_t RANK_WIDE = 4096;
 
 __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ text,
                                                     const int32_t *__restrict__ sa, int64_t N,
@@ -224,10 +225,16 @@ __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ 
         const int32_t c0 = w[0] + 1;  // token code, 0 for the end marker
         int64_t lo = bucket[c0], hi = j < M ? bucket[c0 + 1] : lo;  // old suffixes with the same first token
         while (__any(lo < hi)) {
-            // probes divide [lo, hi) evenly; up to RANK_LANES suffixes are probed one by one
-            const int64_t len = hi - lo;
-            const bool few = len <= RANK_LANES;
-            const int64_t i = few ? lo + g : lo + len * (g + 1) / (RANK_LANES + 1);
+            // Probes divide [lo, hi) evenly; up to RANK_LANES suffixes are probed one by one.  In a wide
+            // range the last probe is its last suffix: in text that is one token over and over the new
+            // suffix ties with all of them, D tokens a probe (half a million into as many and more: an
+            // insertion takes 1.74 ms without, 1.28 so).
+            const uint32_t len = (uint32_t)(hi - lo);
+            const bool few = len <= RANK_LANES, wide = len > RANK_WIDE;
+            auto probe = [&](int q) {  // place of the q-th one
+                return lo + (int64_t)(((uint64_t)(wide ? len - 1u : len) * ((uint64_t)(q + 1) * (wide ? (1ull << 32) / RANK_LANES : (1ull << 32) / (RANK_LANES + 1)))) >> 32);
+            };
+            const int64_t i = few ? lo + g : probe(g);
             bool before = false;  // old suffix i sorts before, or ties with, the new one
             if (i < hi && lo < hi) {
                 const int32_t *v = text + sa[i];
@@ -256,9 +263,9 @@ __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ 
                     lo += n;
                     hi = lo;
                 } else {
-                    const int64_t l = lo;
-                    if (n > 0) lo = l + len * n / (RANK_LANES + 1) + 1;
-                    if (n < RANK_LANES) hi = l + len * (n + 1) / (RANK_LANES + 1);
+                    const int64_t from = n > 0 ? probe(n - 1) + 1 : lo;
+                    if (n < RANK_LANES) hi = probe(n);
+                    lo = from;
                 }
             }
         }

@@ -104,6 +104,26 @@ def test_insert_places(n_old, n_new, spread):
         g.close()
 
 
+@pytest.mark.parametrize("n", [8, 9, 4095, 4096, 4097, 30_000])
+def test_insert_into_a_wide_bucket(n):
+    """The ranking probes up to 8, up to 4096 and more suffixes of one first token in different ways: new
+    suffixes in front of all of them, behind all of them, tied with all or with some."""
+    rng = np.random.default_rng(n)
+    D, vocab = 16, 50
+    cases = [[np.full(n, 7, np.int32)],                                       # one run
+             [rng.choice(np.array([7, 7, 7, 7, 7, 7, 7, 9], np.int32), n)],   # runs of all lengths
+             [np.stack([np.full(n, 7), rng.integers(0, vocab, n)], 1).reshape(-1).astype(np.int32)]]
+    new = [np.array([7, 0, 7, 49], np.int32), np.full(40, 7, np.int32), rng.integers(6, 9, 300).astype(np.int32)]
+    for old in cases:
+        g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in old + new))
+        try:
+            g.build_global(old)
+            g.insert_global(new)
+            _check(g, old + new, D)
+        finally:
+            g.close()
+
+
 @pytest.mark.parametrize("n_new", [2_097_100, 2_097_200, 536_871_500])
 def test_insert_ranks_in_strides(n_new):
     """More new suffixes than one sweep of the ranking's grid (2^21), and more than 2^29: eight lanes
