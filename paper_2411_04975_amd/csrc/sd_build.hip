@@ -513,7 +513,7 @@ static int build_sorted_positions(sd_ctx *c, const int32_t *text, int64_t N, int
 // starts empty and grows by insertion would otherwise keep those of its first document, and codes
 // made with the intervals of other text fall into few buckets.  Where buckets of an insertion turned out
 // too long, the next one's intervals are its own (outputs that start alike with tokens that are rare in the
-// old text share buckets: 2000 of 100 tokens with one head of 60 into 2M: 1.45 ms, 0.48 from the second insertion on).
+// old text share buckets: 2000 of 100 tokens with one head of 60 into 2M: 1.3 ms, 0.48 from the second insertion on).
 // The sample (three launches, 25 us) is taken from the `old` positions in front of `text` or from the new tokens, whichever are more.
 static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq,
                                  int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1,
