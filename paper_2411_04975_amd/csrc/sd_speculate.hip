@@ -18,9 +18,9 @@
 //      and leaves their sorted suffix lists in LDS; otherwise every pattern length is
 //      searched for on its own (bucket, column, then the text).
 //   2. pattern lengths with equal occurrence counts share one expansion; the waves take such
-//      runs from a queue in LDS and grow the trees greedily, one wavefront per tree (frontier
-//      and tree in LDS, arg-max by wave-wide maxima, shortcuts for unary runs and for tied
-//      single-occurrence chains).
+//      runs from a queue in LDS and grow the trees greedily, one wavefront per tree: with one lane
+//      per suffix once the frontier's nodes have at most 64 suffixes together (grow_narrow), node
+//      by node from a frontier in LDS before that.
 //   3. every wave keeps its best tree; the best of the workgroup is written out.
 // The same kernel has a form that first settles the previous step (acceptance of the verified
 // drafts, append of the accepted tokens), and k_accept does that alone.
@@ -348,6 +348,33 @@ __device__ __forceinline__ int32_t wave_inclusive_sum(int32_t v) {
     const int row = (threadIdx.x & 63) >> 4;
     return v + (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
 }
+
+// The same for 32-bit maxima and minima, where only one scalar is wanted: shifts inside the rows, then each
+// row's last lane into the rows behind it (moves and compares are one instruction each).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t v, uint32_t none) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <typename OP>
+__device__ __forceinline__ uint32_t reduce_u32(uint32_t v, uint32_t none, OP op) {
+    v = op(v, dpp_or<0x111, 0xf>(v, none));
+    v = op(v, dpp_or<0x112, 0xf>(v, none));
+    v = op(v, dpp_or<0x114, 0xf>(v, none));
+    v = op(v, dpp_or<0x118, 0xf>(v, none));
+    v = op(v, dpp_or<0x142, 0xa>(v, none));
+    v = op(v, dpp_or<0x143, 0xc>(v, none));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t reduce_max_u32(uint32_t v) {
+    return reduce_u32(v, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+__device__ __forceinline__ uint32_t reduce_min_u32(uint32_t v) {
+    return reduce_u32(v, ~0u, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+
+__device__ __forceinline__ uint64_t ballot64(bool pred) { return __builtin_amdgcn_ballot_w64(pred); }
+// whether this lane's bit is set in a mask that is the same in all lanes
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Workgroup-shared state of one request.
 struct WgShared {
@@ -968,108 +995,25 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
     }
 }
 
-// LDS staging of one narrow part of a suffix list: the positions of up to 64 consecutive
-// suffixes and, per suffix, a window of W consecutive tokens starting at depth cb[slot].
-// Sibling branches of the speculation tree are disjoint suffix ranges and a suffix is only
-// ever asked for deeper tokens, so each slot's window moves forward only.  With W tokens per
-// slot one coalesced fill serves W levels of the tree: expansion then runs out of LDS.
+// What a wave keeps in LDS of the up to 64 suffixes that grow_narrow works on: where they start, and
+// a window of their tokens each.
 constexpr int TC_TOKENS = 512;
 constexpr int FILL_U = TC_TOKENS / 64;  // loads per lane that fill all the windows of a wave
-constexpr int CB_NONE = -(1 << 30);
-constexpr int CHAIN_MAX_M = 8;  // widest node the unary-run shortcut looks at
 constexpr int MED_MAX = 256;  // widest node whose suffixes are all read (a multiple of 64)
 
 struct Stage {
-    int32_t *pos, *cb, *tc;  // LDS: [64], [64], [TC_TOKENS]
-    int32_t *tmp;            // LDS: [128] scratch of the chain merge
-    int lo, m, wlog;         // staged range [lo, lo + m) of the suffix list, window = 1 << wlog
+    int32_t *pos, *base, *tc;  // LDS: [64], [64], [TC_TOKENS]
+    int32_t *tmp;              // LDS: [64] scratch of the searches in wide nodes
 };
 
-__device__ __forceinline__ void stage_set_width(Stage &s, int m) {
-    int p2 = 1;
-    while (p2 < m) p2 <<= 1;
-    int w = TC_TOKENS / p2;
-    if (w > 64) w = 64;
-    s.wlog = 31 - __clz(w);
-}
-
-// Stage the node [lo, lo + m) (m <= 64) and make every one of its windows cover depth d.
-// Returns the window base of this lane's suffix (lanes < m).
-__device__ __forceinline__ int stage_node(Stage &sg, const int32_t *__restrict__ sa,
-                                          const int32_t *__restrict__ text, int32_t lo, int32_t m,
-                                          int32_t d) {
-    const int lane = threadIdx.x & 63;
-    const bool in = lane < m;
-    if (!(lo >= sg.lo && lo + m <= sg.lo + sg.m)) {
-        sg.lo = lo;
-        sg.m = m;
-        stage_set_width(sg, m);
-        if (in) {
-            sg.pos[lane] = sa[lo + lane];
-            sg.cb[lane] = CB_NONE;
-        }
-        wsync();
-    }
-    const int slot0 = lo - sg.lo, slot = slot0 + lane;
-    const int W = 1 << sg.wlog;
-    int mycb = in ? sg.cb[slot] : d;
-    const bool miss = in && !(mycb <= d && d < mycb + W);
-    if (__ballot(miss)) {  // move the windows of this node's suffixes to depth d
-        wsync();
-        if (in) sg.cb[slot] = d;
-        // (at most TC_TOKENS tokens, FILL_U loads per lane, all of them in flight together: a
-        // loop of load, wait, store took a memory round trip per 64 tokens)
-        const int total = m << sg.wlog;
-        int32_t v[FILL_U];
-#pragma unroll
-        for (int u = 0; u < FILL_U; u++) {
-            const int idx = u * 64 + lane;
-            v[u] = 0;
-            if (u * 64 < total && idx < total)
-                v[u] = text[(int64_t)sg.pos[slot0 + (idx >> sg.wlog)] + d + (idx & (W - 1))];
-        }
-#pragma unroll
-        for (int u = 0; u < FILL_U; u++) {
-            const int idx = u * 64 + lane;
-            if (u * 64 < total && idx < total) sg.tc[(slot0 << sg.wlog) + idx] = v[u];
-        }
-        wsync();
-        mycb = d;
-    }
-    return mycb;
-}
-
-// Lane l: the token that all m staged suffixes from slot0 on hold at depth d + l, or -2 if they
-// differ there or a window does not reach that far (m <= M).  The window bases come from the
-// lanes' registers and all tokens are read in one round of LDS reads (the slots past m repeat
-// the last suffix).
-template <int M>
-__device__ __forceinline__ int32_t common_token(const Stage &sg, int slot0, int m, int d, int W,
-                                                int32_t mycb) {
-    const int lane = threadIdx.x & 63;
-    int32_t off[M], v[M];
-    // window base of suffix i: lane i's value of `mycb` (what stage_node returned)
-#pragma unroll
-    for (int i = 0; i < M; i++) {
-        const int ii = i < m ? i : m - 1;
-        off[i] = d + lane - __builtin_amdgcn_readlane(mycb, ii);
-    }
-#pragma unroll
-    for (int i = 0; i < M; i++) {
-        const int ii = i < m ? i : m - 1;
-        const int o = off[i] < W ? off[i] : W - 1;
-        v[i] = sg.tc[((slot0 + ii) << sg.wlog) + o];
-    }
-    int32_t tk = off[0] < W ? v[0] : -2;
-#pragma unroll
-    for (int i = 1; i < M; i++) tk = (off[i] < W && v[i] == tk) ? tk : -2;
-    return tk;
-}
-
 // Children of the node [lo, hi) at depth d (its path has d tokens), as frontier candidates with
-// score = ps * (COUNT(child) / COUNT(node)).  `hole` is the frontier slot the node came from.
+// score = ps * (COUNT(child) / COUNT(node)).  `hole` is the frontier slot the node came from.  For units
+// whose matched node has more than 64 suffixes, until what is left of them is for grow_narrow.
+// `col`, if given, holds the token at depth d of every suffix of the list (the second-token column, for the
+// node of a single token): one load instead of two that wait for each other.
 template <bool STATS>
-__device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, const int32_t *__restrict__ sa,
+__device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, const int32_t *__restrict__ col,
+                              const int32_t *__restrict__ sa,
                               const int32_t *__restrict__ text, int32_t lo, int32_t hi, int32_t d,
                               int32_t parent, double ps, double min_score, int32_t D, int den_mode,
                               unsigned &nb) {
@@ -1079,29 +1023,9 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
     }
     const int lane = threadIdx.x & 63;
     const int32_t m = hi - lo;
-    if (__builtin_expect(m <= 64, 1)) {
-        const bool in = lane < m;
-        const int mycb = stage_node(sg, sa, text, lo, m, d);
-        int32_t tok = 0x7fffffff;
-        if (in) tok = sg.tc[((lo - sg.lo + lane) << sg.wlog) + (d - mycb)];
-        if (in) SD_CNT(8);
-        // denominator of C(N): all occurrences of the node, or (den_mode 1) only those that
-        // go on, i.e. the sum over the children
-        const int32_t dn = den_mode ? m - __popcll(__ballot(in && tok < 0)) : m;
-        const double den = (double)dn;
-        int32_t prev = __shfl_up(tok, 1);
-        bool start = in && (lane == 0 || tok != prev);
-        uint64_t S = __ballot(start);
-        uint64_t above = lane == 63 ? 0ull : (S >> (lane + 1));
-        int32_t e = above ? lane + 1 + (__ffsll((unsigned long long)above) - 1) : m;
-        int32_t c = e - lane;
-        double sc = c == dn ? ps : ps * ((double)c / den);  // x / x == 1 and ps * 1 == ps exactly
-        bool cand = start && tok >= 0 && sc >= min_score;
-        frontier_put(f, hole, cand, sc, tok, parent, lo + lane, lo + e, d + 1);
-        return;
-    }
+    auto token = [&](int32_t i) -> int32_t { return col ? col[i] : text[(int64_t)sa[i] + d]; };
     if (m <= MED_MAX) {
-        // Medium node: read the next token of every suffix (all loads in flight together) and
+        // Medium node (or a narrow one): read the next token of every suffix (all loads in flight together) and
         // take the children from the run boundaries, 64 suffixes at a time.  A run that is
         // still open at the end of a group of 64 is carried into the next group.
         frontier_close(f, hole);
@@ -1110,13 +1034,13 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
 #pragma unroll
         for (int c = 0; c < MED_MAX / 64; c++) {
             const int32_t i = lo + c * 64 + lane;
-            ps_[c] = i < hi ? sa[i] : 0;
+            ps_[c] = i < hi ? col ? col[i] : sa[i] : 0;
         }
         int32_t ended = 0;
 #pragma unroll
         for (int c = 0; c < MED_MAX / 64; c++) {
             const bool in = lo + c * 64 + lane < hi;
-            tk[c] = in ? text[ps_[c] + d] : 0x7fffffff;
+            tk[c] = in ? col ? (int32_t)ps_[c] : text[ps_[c] + d] : 0x7fffffff;
             if (in) SD_CNT(8);
             ended += __popcll(__ballot(in && tk[c] < 0));
         }
@@ -1173,7 +1097,7 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
         while (l < h) {
             int32_t mid = l + ((h - l) >> 1);
             if (lane == 0) SD_CNT(8);
-            if (text[(int64_t)sa[mid] + d] < 0) l = mid + 1; else h = mid;
+            if (token(mid) < 0) l = mid + 1; else h = mid;
         }
         dn = hi - l;
         if (dn == 0) return;
@@ -1202,10 +1126,10 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
         const bool in = k < np;
         const int32_t q = (int32_t)(lo + (in ? k : 0) * stride);
         int32_t tok = 0x7fffffff;
-        if (in) tok = text[(int64_t)sa[q] + d];
+        if (in) tok = token(q);
         if (in) SD_CNT(8);
         int32_t prevtok = __shfl_up(tok, 1);
-        if (lane == 0) prevtok = k == 0 ? (int32_t)0x80000000 : text[(int64_t)sa[q - stride] + d];
+        if (lane == 0) prevtok = k == 0 ? (int32_t)0x80000000 : token(q - stride);
         if (lane == 0 && k != 0) SD_CNT(8);
         const bool change = in && tok != prevtok;
         // The run of a probed token starts in (q - stride, q] and ends behind the last probe
@@ -1249,7 +1173,7 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
                 const int64_t n = (int64_t)h - l;
                 const int32_t pt = (int32_t)(l + n * (sub + 1) / (G + 1));
                 int32_t v = 0;
-                if (go) v = text[(int64_t)sa[pt] + d];
+                if (go) v = token(pt);
                 if (go) SD_CNT(8);
                 // the answer is the first position whose token is >= (lower end) or > (upper
                 // end) the run's token: the probes that say "not yet" form a prefix
@@ -1268,14 +1192,14 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
             while (l < h) {
                 int32_t mid = l + ((h - l) >> 1);
                 SD_CNT(8);
-                if (text[(int64_t)sa[mid] + d] < tok) l = mid + 1; else h = mid;
+                if (token(mid) < tok) l = mid + 1; else h = mid;
             }
             lb = l;
             l = ub_lo; h = ub_hi;
             while (l < h) {
                 int32_t mid = l + ((h - l) >> 1);
                 SD_CNT(8);
-                if (text[(int64_t)sa[mid] + d] <= tok) l = mid + 1; else h = mid;
+                if (token(mid) <= tok) l = mid + 1; else h = mid;
             }
             ub = l;
         }
@@ -1285,37 +1209,12 @@ __device__ __forceinline__ void push_children(Frontier &f, int hole, Stage &sg, 
     }
 }
 
-// Tied single-occurrence chains.  When every frontier entry that shares the top score is a
-// node with one occurrence (at most TIE_MAX of them, all staged), each of them heads a chain
-// whose nodes all keep that score (count ratio 1/1), while everything else in the frontier
-// scores strictly lower.  The greedy rule therefore keeps taking the head with the lowest
-// (token, parent) among these chains until they end or K is reached: a merge that needs no
-// frontier traffic.  Returns false (and changes nothing) if the frontier does not have that form.
-//
-// Few chains are merged as whole sequences, one after the other (taking the best head among k
-// chains equals merging them pairwise, because (token, parent) keys are distinct).  Merging a
-// chain X into the sequence Y merged so far under "take the head with the lower (token,
-// parent)": element x_t leaves after exactly r(t) elements of Y, where r(t) is the first
-// j >= r(t-1) at which y_j does not beat x_t.  y_j beats x_t if its token is lower, or equal
-// with the lower parent index; parents are the predecessors within a chain, x_t's is x_(t-1),
-// which left after r(t-1) elements of Y, so on equal tokens y_j wins iff its predecessor's
-// place in Y is below r(t-1) (the given parents of chain heads are older than every new node
-// and decide among themselves).  Three ballots per x_t give {j : y_j < x_t}, {j : y_j == x_t}
-// and the predecessors below r(t-1) as lane masks, and r(t) follows with a few scalar bit
-// operations.  The loop runs over the elements of the chain that is added, never over the
-// sequence merged so far (which is as long as all chains before together: with the roles the
-// other way round the third chain of a merge cost as much as the rest of the expansion).
-// x_t lands at t + r(t); the elements of Y fill the positions left over, in order.  At most 63
-// nodes are taken per call (one 64-token window per chain: its head plus 63 tokens), the caller
-// comes back for more.  Per-chain state lives in the lanes of vector registers (lane q: chain q).
-constexpr int TIE_MAX = 64;
-// From this many chains on the merge goes step by step over all chains at once (below); fewer
-// chains are merged as whole sequences.  4 measured best on the synthetic workloads (2, 3, 8, 16 tried).
-constexpr int KWAY_MIN = 4;
-
 // total + s + s + ... (n times), added one by one in that order like the sequential sum of node
-// scores it stands for
+// scores it stands for.  Where both are multiples of 2^-20 (scores of 1, 1/2, 3/4 and the like) every such sum
+// is exact, and so is the product.
 __device__ __forceinline__ double add_times(double total, double s, int n) {
+    const double a = s * 1048576.0, b = total * 1048576.0;
+    if (a == rint(a) && b == rint(b)) return total + (double)n * s;
     int i = 0;
     for (; i + 8 <= n; i += 8) {
         total += s; total += s; total += s; total += s;
@@ -1323,302 +1222,6 @@ __device__ __forceinline__ double add_times(double total, double s, int n) {
     }
     for (; i < n; i++) total += s;
     return total;
-}
-
-__device__ __forceinline__ uint64_t ballot64(bool pred) { return __builtin_amdgcn_ballot_w64(pred); }
-// v with lane `idx` replaced by the uniform value `val`
-__device__ __forceinline__ int32_t set_lane(int32_t val, int idx, int32_t v) {
-    return (int)(threadIdx.x & 63) == idx ? val : v;
-}
-
-template <bool STATS>
-__device__ __forceinline__ bool tied_chains(Frontier &f, Stage &sg, const int32_t *__restrict__ text, double s,
-                            int K, int D, int &n, double &total, int32_t *t_tok, int32_t *t_par,
-                            double *t_score, bool &deepest, unsigned &nb) {
-    const int lane = threadIdx.x & 63;
-    if (f.n > 64) return false;
-    const bool have = lane < f.n;
-    const bool tie = have && f.score[lane] == s;
-    const int32_t mylo = have ? f.lo[lane] : 0, myhi = have ? f.hi[lane] : 0;
-    const bool fit = myhi - mylo == 1 && mylo >= sg.lo && mylo < sg.lo + sg.m;
-    const uint64_t T = ballot64(tie);
-    const int j = __popcll(T);
-    // a single top entry is not a tie: the unary-run shortcut takes its whole chain at once
-    if (j < 2 || j > TIE_MAX || ballot64(tie && !fit)) return false;
-    int32_t *TT = sg.tmp, *MM = sg.tmp + 64;
-    // chain q = the q-th tied entry in frontier order; its head moves into lane q
-    const int32_t etok = have ? f.tok[lane] : 0, epar = have ? f.par[lane] : 0,
-                  edep = have ? f.dep[lane] : 0;
-    const double eks = have ? f.score[lane] : 0.0;
-    if (tie) TT[__popcll(T & lanemask_lt())] = lane;
-    wsync();
-    const int srcl = lane < j ? TT[lane] : 0;
-    const int32_t ctokv = __shfl(etok, srcl), cparv = __shfl(epar, srcl), cdepv = __shfl(edep, srcl),
-                  cslotv = __shfl(mylo, srcl) - sg.lo;
-    const int32_t cposv = lane < j ? sg.pos[cslotv] : 0;
-    // Where the staged windows of all these suffixes reach from their heads down to depth D,
-    // every token the merge can ask for is in LDS already and nothing is loaded.
-    const int32_t ccbv = lane < j ? sg.cb[cslotv] : 0;
-    const bool covered = !ballot64(lane < j && !(ccbv <= cdepv && ccbv + (1 << sg.wlog) >= D));
-    // take the tied entries out of the frontier (the others keep their relative order)
-    {
-        const bool keep = have && !tie;
-        const int dst = __popcll(ballot64(keep) & lanemask_lt());
-        wsync();
-        if (keep) {
-            f.score[dst] = eks; f.tok[dst] = etok; f.par[dst] = epar; f.lo[dst] = mylo; f.hi[dst] = myhi;
-            f.dep[dst] = edep;
-        }
-        f.n -= j;
-        wsync();
-    }
-    const int n0 = uni(n), KK = uni(K);
-    if (j >= KWAY_MIN) {
-        // Many chains: one pass that takes the lowest head each step.  The heads sit
-        // in the lanes with their rank among the heads (0 = lowest key); a step takes the
-        // head of rank 0, moves every other rank up, and ranks the chain's next element among
-        // the others with one ballot.  That element's parent is the node just taken, the
-        // highest index so far, so on equal tokens every older head goes first: the ballot
-        // needs tokens only.  The chains' upcoming tokens sit in LDS (the staging windows'
-        // space, handed back afterwards), W per chain.
-        int jp2 = 1;
-        while (jp2 < j) jp2 <<= 1;
-        const int wlog = 31 - __clz(TC_TOKENS / jp2), W = 1 << wlog;
-        // Per chain (lane q < j): the head's token, parent and depth, its rank, and the tokens
-        // of the next two elements.  Tokens compare as unsigned numbers, which puts the end
-        // marker (-1) above every real token: a chain whose next element does not exist (end
-        // of the text, or the depth bound) gets the marker as its head, which is how it dies;
-        // lanes >= j start dead.  Dead heads rank behind all live ones.
-        const uint32_t DEAD = 0xffffffffu;
-        const bool chain = lane < j;
-        uint32_t htok = chain ? (uint32_t)ctokv : DEAD;
-        int32_t hpar = cparv, hdep = chain ? cdepv : 0;
-        const int32_t pos0 = cposv + cdepv;  // text index of the token of the chain's element 1
-        // (covered: the chain's staged window, whose token i stands at child index ccb + i)
-        const int base = covered ? (chain ? (cslotv << sg.wlog) - ccbv : 0) : (chain ? lane : 0) << wlog;
-        int32_t abase = 0;
-        uint32_t nexttok = DEAD, n2 = DEAD, cand = DEAD;
-        // token windows: W tokens per chain from the element after its head on
-        // (`need` <= W tokens per chain are fetched, rounded up to a power of two; all loads in
-        // flight together)
-        auto fill = [&](int need) {
-            if (covered) {  // tokens hdep, hdep + 1, ... of the staged window
-                abase = base + 1;
-                nexttok = chain ? (uint32_t)sg.tc[base + hdep] : DEAD;
-                n2 = (uint32_t)sg.tc[abase + hdep];
-                cand = hdep < D ? nexttok : DEAD;
-                return;
-            }
-            wsync();
-            int flog = 3;
-            while ((1 << flog) < need) flog++;
-            const int total = j << flog;  // <= TC_TOKENS
-            const int32_t adv = hdep - cdepv;  // elements of the chain taken so far
-            int32_t v[FILL_U];
-#pragma unroll
-            for (int u = 0; u < FILL_U; u++) {
-                const int idx = u * 64 + lane, q = (idx >> flog) & 63;
-                v[u] = 0;
-                if (u * 64 < total) {
-                    const int32_t pq = __shfl(pos0, q), aq = __shfl(adv, q);  // all lanes take part
-                    if (idx < total) {
-                        v[u] = text[(int64_t)pq + aq + (idx & ((1 << flog) - 1))];
-                        SD_CNT(4);
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < FILL_U; u++) {
-                const int idx = u * 64 + lane;
-                if (u * 64 < total && idx < total)
-                    sg.tc[((idx >> flog) << wlog) + (idx & ((1 << flog) - 1))] = v[u];
-            }
-            wsync();
-            abase = base + 1 - hdep;
-            nexttok = chain ? (uint32_t)sg.tc[base] : DEAD;
-            n2 = (uint32_t)sg.tc[base + 1];
-            cand = hdep < D ? nexttok : DEAD;
-        };
-        int32_t rank = 1 << 20;
-        if (chain) {
-            rank = 0;
-            for (int q = 0; q < j; q++) {
-                const uint32_t kt = (uint32_t)__builtin_amdgcn_readlane(ctokv, q);
-                const int32_t kp = __builtin_amdgcn_readlane(cparv, q);
-                rank += (kt < htok || (kt == htok && kp < hpar)) ? 1 : 0;
-            }
-        }
-        int nn = n0;
-        double tot = total;
-        bool done = false;
-        // a chain moves by at most one element per step and looks two elements ahead
-        const int burst = covered ? 64 : W - 2 < 64 ? W - 2 : 64;
-        while (nn < KK && !done) {
-            const int lim = KK - nn < burst ? KK - nn : burst;
-            fill(lim + 2);
-            int32_t otok = 0, opar = 0;  // lane k: the node taken in step k of this burst
-            int k = 0;
-            for (; k < lim; k++) {
-                const uint64_t first = ballot64(rank == 0);
-                if (!first) { done = true; break; }
-                const int w = __ffsll((unsigned long long)first) - 1;
-                const uint32_t wtok = (uint32_t)__builtin_amdgcn_readlane((int32_t)htok, w);
-                if (wtok == DEAD) { done = true; break; }  // no chain left
-                const int32_t wpar = __builtin_amdgcn_readlane(hpar, w);
-                const uint32_t nt = (uint32_t)__builtin_amdgcn_readlane((int32_t)cand, w);
-                otok = set_lane((int32_t)wtok, k, otok);
-                opar = set_lane(wpar, k, opar);
-                tot += s;
-                // The new head's parent is the node just taken, the highest index so far: among
-                // equal tokens every other head goes first.
-                const bool me = lane == w;
-                const bool older = !me && htok <= nt;
-                const int nr = __popcll(ballot64(older));
-                rank = me ? nr : rank - (older ? 1 : 0);
-                htok = me ? nt : htok;
-                hpar = me ? nn + k : hpar;
-                hdep += me ? 1 : 0;
-                nexttok = me ? n2 : nexttok;
-                n2 = (uint32_t)sg.tc[abase + hdep];
-                cand = hdep < D ? nexttok : DEAD;
-            }
-            if (lane < k) {
-                t_tok[nn + lane] = otok; t_par[nn + lane] = opar; t_score[nn + lane] = s;
-                SD_CNT(8);
-            }
-            nn += k;
-        }
-        // a head of depth D that was taken left its chain at depth D + 1
-        if (ballot64(chain && hdep > D)) deepest = true;
-        wsync();
-        if (!covered) sg.cb[lane] = CB_NONE;  // the staged token windows were overwritten
-        wsync();
-        n = nn;
-        total = tot;
-        return true;
-    }
-    const int room = KK - n0 < 63 ? KK - n0 : 63;
-    // chain q as a sequence: element 0 is the frontier entry, element k its k-th descendant
-    // (the token at child index cdep + k - 1); `alen` = how many elements exist
-    int32_t alenv = 0;
-    int32_t zt, zm = lane, zprev = lane - 1, zinit;
-    int lz;
-    // lane l >= 1: the token of chain q's element l (child index cdep + l - 1), from the staged
-    // window or from memory (the load for the next chain is issued before this one is used)
-    int32_t wnext = 0;
-    if (!covered)
-        wnext = text[(int64_t)__builtin_amdgcn_readlane(cposv, 0) + __builtin_amdgcn_readlane(cdepv, 0) + lane];
-    auto chain_tokens = [&](int q) -> int32_t {
-        if (covered) {
-            const int at = (__builtin_amdgcn_readlane(cslotv, q) << sg.wlog) +
-                           __builtin_amdgcn_readlane(cdepv, q) - __builtin_amdgcn_readlane(ccbv, q);
-            return sg.tc[at + (lane >= 1 ? lane - 1 : 0)];
-        }
-        const int32_t w = wnext;
-        if (q + 1 < j)
-            wnext = text[(int64_t)__builtin_amdgcn_readlane(cposv, q + 1) +
-                         __builtin_amdgcn_readlane(cdepv, q + 1) + lane];
-        return __shfl_up(w, 1);
-    };
-    {
-        const int cd = __builtin_amdgcn_readlane(cdepv, 0);
-        const int32_t up = chain_tokens(0);
-        zt = lane == 0 ? __builtin_amdgcn_readlane(ctokv, 0) : up;
-        const uint64_t bad = ballot64(lane >= 1 && (up < 0 || cd + lane - 1 >= D));
-        const int a = bad ? __ffsll((unsigned long long)bad) - 1 : 64;
-        alenv = set_lane(a, 0, alenv);
-        lz = a < room ? a : room;
-        zinit = __builtin_amdgcn_readlane(cparv, 0);
-    }
-    for (int q = 1; q < j; q++) {
-        const int cd = __builtin_amdgcn_readlane(cdepv, q);
-        const int32_t up = chain_tokens(q);
-        const int32_t yt = lane == 0 ? __builtin_amdgcn_readlane(ctokv, q) : up;
-        const uint64_t bad = ballot64(lane >= 1 && (up < 0 || cd + lane - 1 >= D));
-        const int a = bad ? __ffsll((unsigned long long)bad) - 1 : 64;
-        alenv = set_lane(a, q, alenv);
-        const int ly = a < room ? a : room;
-        const int32_t yinit = __builtin_amdgcn_readlane(cparv, q);
-        // The loop goes over the new chain X (plain: x_t's predecessor is x_(t-1)), the
-        // sequence merged so far is Y.  x_t lands at t + r(t) and r never decreases: once that
-        // reaches `room` neither x_t nor anything after it is kept, and every y_j still
-        // unplaced lands at j + t >= room as well.  Lanes the loop never reached keep myr = 64
-        // (dropped).  Equal tokens: y_j wins iff its predecessor left before x_(t-1), which
-        // left after r(t-1) elements of Y, i.e. iff that predecessor's place in Y is below
-        // r(t-1) (a head's given parent is older than every new node); for x_0 the given
-        // parents decide, and only heads of Y can win.
-        const uint64_t zmask = lz >= 64 ? ~0ull : ((1ull << lz) - 1ull);
-        const uint64_t tie0 = ballot64(zprev < 0 && zinit < yinit);
-        int r = 0;
-        int32_t myr = 64;
-        for (int t = 0; t < ly && t + r < room; t++) {  // r < 63 inside the loop
-            const int32_t xt = __builtin_amdgcn_readlane(yt, t);
-            const uint64_t lt = ballot64(zt < xt), eq = ballot64(zt == xt);
-            const uint64_t tie = t ? ballot64(zprev < r) : tie0;
-            const uint64_t wins = (lt | (eq & tie)) & zmask;
-            const uint64_t rest = ~(wins >> r);  // (never empty: wins has no bit from 63 on)
-            r += __ffsll((unsigned long long)rest) - 1;
-            myr = set_lane(r, t, myr);
-        }
-        wsync();
-        MM[lane] = -1;
-        wsync();
-        if (lane < ly && lane + myr < 64) { TT[lane + myr] = yt; MM[lane + myr] = (q << 8) | lane; }
-        wsync();
-        const int32_t mt = TT[lane], mm = MM[lane];
-        const bool hole = mm == -1;  // not taken by X: the holes take Y's elements in order
-        const int h = __popcll(ballot64(hole) & lanemask_lt());
-        const int32_t zv = __shfl(zt, h), zmv = __shfl(zm, h);
-        zt = hole ? zv : mt;
-        zm = hole ? zmv : mm;
-        lz = lz + ly < room ? lz + ly : room;
-        // predecessor links and given parents of the new sequence
-        zprev = -1;
-        for (int c = 0; c <= q; c++) {
-            const bool mine = lane < lz && (zm >> 8) == c;
-            const uint64_t mc = ballot64(mine);
-            if (mine) {
-                const uint64_t prev = mc & lanemask_lt();
-                zprev = prev ? 63 - __clzll((unsigned long long)prev) : -1;
-            }
-        }
-        zinit = __shfl(cparv, (zm >> 8) & 63);
-        wsync();
-    }
-    const bool live = lane < lz;
-    const int myc = zm >> 8;
-    if (live) {
-        t_tok[n0 + lane] = zt; t_par[n0 + lane] = zprev < 0 ? zinit : n0 + zprev; t_score[n0 + lane] = s;
-        SD_CNT(8);
-    }
-    total = add_times(total, s, lz);
-    const int nn = n0 + lz;
-    // per chain: how many elements were taken and where the last of them went
-    int32_t usedv = 0, lastv = 0;
-    for (int q = 0; q < j; q++) {
-        const uint64_t mq = ballot64(live && myc == q);
-        usedv = set_lane((int)__popcll(mq), q, usedv);
-        lastv = set_lane(mq ? 63 - (int)__clzll((unsigned long long)mq) : 0, q, lastv);
-    }
-    if (ballot64(lane < j && usedv > 0 && cdepv + usedv - 1 >= D)) deepest = true;
-    n = nn;
-    if (nn < KK) {  // chains that go on put their next element back into the frontier
-        const bool goes_on = lane < j && usedv < alenv;
-        int32_t ntok = ctokv;
-        if (goes_on && usedv > 0) {
-            ntok = text[(int64_t)cposv + cdepv + usedv - 1];
-            SD_CNT(4);
-        }
-        const uint64_t A = ballot64(goes_on);
-        if (goes_on) {
-            const int d = f.n + __popcll(A & lanemask_lt());
-            f.score[d] = s; f.tok[d] = ntok; f.par[d] = usedv > 0 ? n0 + lastv : cparv;
-            f.lo[d] = sg.lo + cslotv; f.hi[d] = sg.lo + cslotv + 1; f.dep[d] = cdepv + usedv;
-        }
-        f.n += __popcll(A);
-    }
-    wsync();
-    return true;
 }
 
 // MatchPattern on the global index, one pattern length at a time (the route taken when the
@@ -1964,6 +1567,274 @@ __device__ __forceinline__ void match_global_pair(const SpecParams &p, int32_t w
     if (restB && !dirB) match_rest<STATS>(p, wkB, plB, loB, hiB, wideB ? 1 : 2, nb);
 }
 
+// What grow_narrow starts from: the frontier's nodes, each a run of lanes (bits in `heads`: its first one), a
+// lane for every suffix.  In a head's lane: score, parent and number of suffixes of the node, and the index of
+// its token; where there is no tree yet, the matched node with index 0 and parent -1.
+struct Narrow {
+    uint64_t heads;
+    double score;
+    int32_t next, par, count;
+};
+
+// ExpandSpeculationTree where the frontier's nodes have up to 64 suffixes together, from the matched node on
+// in nearly every unit of nearly every workload.  Lane i stands for suffix i (sg.pos: where it starts).
+//
+// The frontier needs no list: its nodes are disjoint runs of suffixes, so `heads` (a bit at the first
+// suffix of each), `alive` (a bit per suffix that is in one of them) and, in the lanes, score, parent
+// and depth say all.  How many tokens a suffix shares with the one before it, found when the tokens
+// are staged, says how far the suffixes of a node go on alike (the least of those numbers inside it) and
+// where its children start (wherever that least number stands), so a node is taken with the whole
+// unary run below it, which has the node's own score, and its children come from one ballot.
+//
+// A pass deals with all nodes that hold the top score, whatever their number of suffixes.  What they lead to
+// scores strictly less (c / m with c < m), so their runs can be merged first.  The rule takes the head with
+// the lowest (token, parent), so a run that has the lowest head gives all its tokens up to the first one that
+// is no lower than the lowest of the other heads: behind equal tokens the other one is due, its parent being
+// older than the node just taken.  Runs of n tokens in no order change places some ln n times each, so the
+// merge goes by such pieces and not by elements.  (den_mode 1 lets a child score as much as its parent, where
+// suffixes end: there the merge stops where a run does.)
+//
+// Depths are counted from the matched node: the node that token `r` behind the pattern leads to has index r.
+// Tokens are staged in windows of W = 2^wlog per suffix, K of them if that many fit, from index 0 on; a run
+// that reaches its window's end takes what it has and has the window moved.
+//
+// Bound: the dependent instructions of one wave, some ten cycles each.  A frontier in LDS that was taken from
+// one node at a time (or one unary run above everything else), and merges of single-occurrence chains element
+// by element, took 1.1 us for every such node and 0.08 us for every element; a decode step of 256 requests with
+// 10M tokens behind them 24.7 us on average (22.1 so), of 64 with 2.2M 21.1 (18.7), of 512 with 100M 29.6 (25.3).
+template <bool STATS, bool TICKS>
+__device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &sh, Stage &sg,
+                                           const int32_t *__restrict__ text, const Narrow &g, int m, int pl, int K,
+                                           int n, int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
+                                           bool &deepest, uint64_t tick0, uint32_t &tick_root,
+                                           uint32_t &tick_merge, unsigned &nb) {
+    const int lane = threadIdx.x & 63;
+    const int rel_end = p.D - pl;  // nodes have indices below this
+    int wlog = 0;
+    while (wlog < 6 && (1 << wlog) < K - n) wlog++;
+    while ((m << wlog) > TC_TOKENS) wlog--;
+    const int W = 1 << wlog;
+
+    int32_t lcp = 0;   // index of the first token that this suffix does not share with the one before it
+    int32_t own = 0;   // index of its end marker
+    int32_t row = 0;   // its token with index r is at sg.tc[row + r] ...
+    int32_t wend = 0;  // ... for r below this (which bounds lcp and own as well)
+    // stages `need` tokens of the suffixes [a, a + cnt), from index base0 on (-1: from what sg.base says)
+    auto fill = [&](int a, int cnt, int base0, int need) {
+        const int total_t = cnt << wlog, off = lane & (W - 1);
+        int32_t v[FILL_U];
+#pragma unroll
+        for (int u = 0; u < FILL_U; u++) {
+            const int slot = a + ((u * 64 + lane) >> wlog);
+            v[u] = 0;
+            if (u * 64 < total_t && slot < a + cnt && off < need) {
+                v[u] = text[(int64_t)sg.pos[slot] + pl + (base0 < 0 ? sg.base[slot] : base0) + off];
+                SD_CNT(4);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < FILL_U; u++)
+            if (u * 64 < total_t && u * 64 + lane < total_t) sg.tc[(a << wlog) + u * 64 + lane] = v[u];
+        wsync();
+        const int k = lane - a, ku = k >> (6 - wlog);
+        uint64_t dm = 0, em = 0;  // of this lane's suffix and its neighbours in the same 64 tokens
+#pragma unroll
+        for (int u = 0; u < FILL_U; u++) {
+            if (u * 64 >= total_t) break;
+            const int at = (a << wlog) + u * 64 + lane - W;  // the token of the suffix before (the first one's is not asked for)
+            const int32_t prev = sg.tc[at > 0 && u * 64 + lane < total_t ? at : 0];
+            const bool in = u * 64 + lane < total_t && off < need;
+            const uint64_t d = __ballot(in && (v[u] != prev || v[u] < 0)), e = __ballot(in && v[u] < 0);
+            if (ku == u) { dm = d; em = e; }
+        }
+        if (k >= 0 && k < cnt) {
+            const int sh_ = (k & ((64 >> wlog) - 1)) << wlog;
+            const uint64_t wm = W == 64 ? ~0ull : (1ull << W) - 1ull;
+            dm = (dm >> sh_) & wm;
+            em = (em >> sh_) & wm;
+            const int base = base0 < 0 ? sg.base[lane] : base0;
+            const int l = base + (dm ? __builtin_ctzll(dm) : need), o = base + (em ? __builtin_ctzll(em) : need);
+            lcp = l < rel_end ? l : rel_end;
+            own = o < rel_end ? o : rel_end;
+            row = (lane << wlog) - base;
+            wend = base + need;
+        }
+    };
+
+    // (masks of lanes are kept as numbers, and combined as such: a ballot of a single compare costs one
+    // instruction, asking for a lane's own bit in a mask none)
+    uint64_t alive = ~0ull >> (64 - m), heads = g.heads;
+    double f_s = g.score;                                // (of a head: its score ...
+    int32_t f_r = g.next, f_par = g.par, f_c = g.count;  // ... index and parent of its next token, and its suffixes)
+    double tot = total;
+    bool deep = deepest;
+    auto range = [](int lo, int hi) -> uint64_t { return (~0ull >> (64 - (hi - lo))) << lo; };  // (not empty)
+    auto end_of = [&](int lo) -> int {  // where the node that starts at suffix lo ends
+        const uint64_t b = (heads | ~alive) & (~1ull << lo);
+        return b ? __builtin_ctzll(b) : 64;
+    };
+    auto run_end = [&](int lo, int hi) -> int {  // index of the first token that not all of [lo, hi) share
+        if (hi - lo == 1) return __builtin_amdgcn_readlane(own, lo);
+        return (int)reduce_min_u32(lane > lo && lane < hi ? (uint32_t)lcp : ~0u);
+    };
+
+    fill(0, m, n == 0 ? 0 : -1, W < K - n ? W : K - n);
+    while (n < K && heads) {
+        // The nodes T with the top score s: with den_mode 0 a score is the node's share of the suffixes but for
+        // its roundings, so more suffixes score more, and as many score the same or nearly so.
+        uint64_t T = heads;
+        double s;
+        if (p.den_mode == 0) {
+            if (T & (T - 1ull)) {
+                const uint32_t c = lane_in(heads) ? (uint32_t)f_c : 0u;
+                const uint32_t most = reduce_max_u32(c);
+                T = ballot64(c == most);
+            }
+            const int lo = __builtin_ctzll(T);
+            s = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(f_s), lo),
+                                 __builtin_amdgcn_readlane(__double2loint(f_s), lo));
+            const uint64_t same = T & ballot64(f_s == s);
+            if (__builtin_expect(same != T, 0)) {
+                s = wave_max_f64(lane_in(T) ? f_s : -__longlong_as_double(0x7ff0000000000000ll));
+                T &= ballot64(f_s == s);
+            }
+        } else {
+            s = wave_max_f64(lane_in(heads) ? f_s : -__longlong_as_double(0x7ff0000000000000ll));
+            T &= ballot64(f_s == s);
+        }
+        // Nodes are taken in non-increasing score order, so the K - n nodes still to come add at most
+        // that many times the best score left: a tree that cannot reach the best finished SCORE any more
+        // is given up (it could neither win nor tie; nor could the shorter patterns of its run, whose
+        // trees are its first nodes).  The SCORE is a sum of rounded additions, which may come out a few
+        // units in the last place above this product form (and two trees of equal nodes must tie
+        // exactly): hence the margin.
+        {
+            const double top = uni(__longlong_as_double((long long)sh.top_bits));
+            if ((tot + (double)(K - n) * s) * (1.0 + 1e-9) < top) {
+                total = 0.0;
+                return 0;
+            }
+        }
+        if (p.linear) {  // chain variant: of the nodes at hand only the best one, the one with the lowest token
+            if (T & (T - 1ull)) {
+                const uint32_t tk = lane_in(T) ? (uint32_t)sg.tc[row + f_r] : ~0u;
+                T &= ballot64(tk == reduce_min_u32(tk));
+                T &= 0ull - T;
+            }
+            const int lo = __builtin_ctzll(T);
+            alive &= range(lo, end_of(lo));
+            heads = T;
+        }
+        const uint64_t moved = T & ballot64(f_r >= wend);
+        if (__builtin_expect(moved != 0, 0)) {
+            const int lo = __builtin_ctzll(moved), hi = end_of(lo), r0 = __builtin_amdgcn_readlane(f_r, lo);
+            fill(lo, hi - lo, r0, W < K - n ? W : K - n);
+            if (run_end(lo, hi) > r0) continue;
+            T = 1ull << lo;  // (its children, which score less, are due)
+        }
+
+        const uint64_t m0 = TICKS ? wall_clock64() : 0;
+        constexpr uint32_t DEAD = 0xffffffffu;    // (above every token: a run that has ended)
+        int left = __popcll(T);                   // runs that have not
+        const bool many = left > 1;
+        uint32_t ht = DEAD;                       // a head's token ...
+        int32_t rank = lane_in(T) ? 0 : 1 << 20;  // ... and its rank among the heads
+        if (many) {
+            if (lane_in(T)) ht = (uint32_t)sg.tc[row + f_r];
+            for (uint64_t t = T; t; t &= t - 1ull) {
+                const int q = __builtin_ctzll(t);
+                const uint32_t kt = (uint32_t)__builtin_amdgcn_readlane((int32_t)ht, q);
+                const int32_t kp = __builtin_amdgcn_readlane(f_par, q);
+                rank += (kt < ht || (kt == ht && kp < f_par)) ? 1 : 0;
+            }
+        }
+        const int n0 = n;
+        uint64_t over = 0;  // the suffixes of the nodes whose runs lead to children
+        int32_t ends = -1;  // (of a head: where its run ends, once it has been asked for)
+        do {
+            const int w = __builtin_ctzll(ballot64(rank == 0));
+            int e = __builtin_amdgcn_readlane(ends, w);
+            if (e < 0) {
+                e = run_end(w, end_of(w));
+                if (lane == w) ends = e;
+            }
+            const int r = __builtin_amdgcn_readlane(f_r, w), at = __builtin_amdgcn_readlane(row, w) + r;
+            const int L = e - r < K - n ? e - r : K - n;
+            const uint32_t tk = (uint32_t)sg.tc[at + lane];  // (what lies behind the run's end is not looked at)
+            int len = L;
+            uint32_t next = DEAD;
+            if (left > 1) {  // up to the next token that is no lower than the lowest of the other heads
+                const int w1 = __builtin_ctzll(ballot64(rank == 1));
+                const uint64_t b = ballot64(tk >= (uint32_t)__builtin_amdgcn_readlane((int32_t)ht, w1)) & ~1ull;
+                const int x = b ? __builtin_ctzll(b) : 64;
+                if (x < L) {
+                    len = x;
+                    next = (uint32_t)__builtin_amdgcn_readlane((int32_t)tk, x);
+                }
+            }
+            const int32_t par = __builtin_amdgcn_readlane(f_par, w);
+            if (lane < len) {
+                t_tok[n + lane] = (int32_t)tk;
+                t_par[n + lane] = lane == 0 ? par : n + lane - 1;
+                t_score[n + lane] = s;
+            }
+            n += len;
+            if (r + len >= rel_end) deep = true;
+            if (n >= K) break;
+            // (the new head's parent is the youngest node there is: of equal tokens it comes last)
+            const uint64_t older = ballot64(ht <= next) & ~(1ull << w);
+            if (lane_in(older)) rank--;
+            if (lane == w) {
+                rank = next == DEAD ? 1 << 20 : __popcll(older);
+                ht = next;
+                f_r = r + len;
+                f_par = len > 0 ? n - 1 : par;
+            }
+            if (next == DEAD) {  // the run has ended
+                const int hi = end_of(w);
+                left--;
+                if (e >= rel_end) {
+                    heads &= ~(1ull << w);
+                    alive &= ~range(w, hi);
+                } else if (e >= __builtin_amdgcn_readlane(wend, w)) {
+                    break;  // (or rather its window)
+                } else {
+                    over |= range(w, hi);
+                    if (p.den_mode) break;
+                }
+            }
+        } while (left > 0);
+        tot = add_times(tot, s, n - n0);
+        if (TICKS && many) tick_merge += (uint32_t)(wall_clock64() - m0);
+        if (n >= K) break;
+        if (over) {
+            // children: wherever the tokens behind the run differ
+            const uint64_t firsts = heads & over, le = (2ull << lane) - 1ull, f = firsts & le;
+            const int mine = f ? 63 - __builtin_clzll(f) : 0;  // the head of this lane's node
+            const int32_t re = __shfl(f_r, mine), par = __shfl(f_par, mine);
+            int32_t dn = __shfl(f_c, mine);
+            const int32_t tok = sg.tc[lane_in(over) ? row + re : 0];
+            if (p.den_mode) {  // only the suffixes that go on
+                const uint64_t ended = over & ballot64(tok < 0);
+                dn -= __popcll((ended >> mine) & (~0ull >> (64 - dn)));
+            }
+            const uint64_t S = firsts | (over & ballot64(lcp == re)), above = (S | ~over) & ~le;
+            const int c = (above ? __builtin_ctzll(above) : 64) - lane;
+            const double sc = c == dn ? s : s * ((double)c / (double)dn);  // x / x == 1 and s * 1 == s exactly
+            const uint64_t C = S & ballot64(tok >= 0) & ballot64(sc >= p.min_score);
+            // what follows the start of a child that stays, up to the next start (the addition carries through it)
+            const uint64_t x = over & ~S, keep = C | (x & ~(x + ((C << 1) & x)));
+            heads = (heads & ~over) | C;
+            alive = (alive & ~over) | keep;
+            if (lane_in(C)) { f_s = sc; f_r = re; f_par = par; f_c = c; }
+        }
+        if (TICKS && tick_root == 0) tick_root = (uint32_t)(wall_clock64() - tick0);
+    }
+    total = tot;
+    deepest = deep;
+    return n;
+}
+
 // One unit (request b, index src: 0 global / 1 request, pattern length pl) on one wavefront:
 // ExpandSpeculationTree below the matched node into the LDS tree (t_tok, t_par, t_score).
 // Returns the number of draft nodes and leaves their SCORE in `total`; `deepest` tells whether
@@ -1979,8 +1850,7 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
     const int64_t uidx = (int64_t)b * (2 * p.P) + src * p.P + (pl - 1);
     const int K = (int)floor(p.alpha * (double)pl);
     uint32_t tick_setup = 0, tick_match = 0, tick_root = 0;
-    sg.lo = 0; sg.m = 0; sg.wlog = 0;
-
+    bool staged = false;  // (the suffixes' starts are in sg.pos)
     const int32_t *sa = nullptr, *text = nullptr;
     int32_t lo = 0, hi = 0;
     if (pl <= t && K >= 1) {
@@ -1994,11 +1864,8 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
             if (keep) {
                 const int dst = __popcll(mk & lanemask_lt());
                 sg.pos[dst] = sh.gl_pos[lane] - (pl - 2);
-                sg.cb[dst] = CB_NONE;
             }
-            sg.lo = 0;
-            sg.m = m;
-            stage_set_width(sg, m > 0 ? m : 1);
+            staged = true;
             __threadfence_block();
             wsync();
             sa = p.g_sa;  // never read: the whole list is staged
@@ -2032,17 +1899,13 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
                 uint64_t mk = __ballot(keep);
                 if (keep) {
                     int dst = w + __popcll(mk & lanemask_lt());
-                    if (narrow) { sg.pos[dst] = o.x - pl + 1; sg.cb[dst] = CB_NONE; }
+                    if (narrow) sg.pos[dst] = o.x - pl + 1;
                     else usa[dst] = o.x - pl + 1;
                     SD_CNT(4);
                 }
                 w += __popcll(mk);
             }
-            if (narrow) {  // the whole list is staged: nothing below it ever reads `usa`
-                sg.lo = 0;
-                sg.m = m;
-                stage_set_width(sg, m > 0 ? m : 1);
-            }
+            staged = narrow;  // (nothing below it ever reads `usa` then)
             __threadfence_block();
             wsync();
             lo = 0;
@@ -2056,99 +1919,83 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
     total = 0.0;
     if (TICKS) tick_match = (uint32_t)(wall_clock64() - tick0) + (uint32_t)((hi - lo) & 0);
     if (hi > lo) {
-        f.n = 0;
-        f.cap = K;
-        // Unary run below the node [blo, blo + m) of depth d, whose score is sc and whose place
-        // in the tree is cur (-1: the matched node itself): while all suffixes of the node agree
-        // on the next token and none has ended, the node has exactly one child, with the node's
-        // own score (count ratio 1).  Where nothing else in the frontier shares that score the
-        // greedy rule must take that child next, and so on down the run: the run is taken at
-        // once.
-        auto unary_run = [&](int32_t blo, int32_t m, int32_t &d, int &cur, double sc) {
-            const int32_t mycb = stage_node(sg, sa, text, blo, m, d);
-            const int slot0 = blo - sg.lo, W = 1 << sg.wlog;
-            const int32_t tk = m <= CHAIN_MAX_M / 2
-                                   ? common_token<CHAIN_MAX_M / 2>(sg, slot0, m, d, W, mycb)
-                                   : common_token<CHAIN_MAX_M>(sg, slot0, m, d, W, mycb);
-            int lim = K - n < p.D - d ? K - n : p.D - d;
-            uint64_t ok = __ballot(tk >= 0 && lane < lim);
-            int L = ~ok ? __ffsll((unsigned long long)~ok) - 1 : 64;
-            if (L > 0) {
-                if (lane < L) {
-                    t_tok[n + lane] = tk; t_par[n + lane] = cur + lane;
-                    t_score[n + lane] = sc;
-                    SD_CNT(8 * m);
-                }
-                total = add_times(total, sc, L);
-                cur += L;
-                n += L;
-                d += L;
-                if (d >= p.D) deepest = true;
+        int slots = hi - lo;  // suffixes of the frontier's nodes, all together
+        Narrow g;
+        if (__builtin_expect(slots <= 64, 1)) {  // the matched node alone
+            g.heads = 1ull;
+            g.score = 1.0;
+            g.next = 0;
+            g.par = -1;
+            g.count = slots;
+            if (!staged && lane < slots) {
+                sg.pos[lane] = sa[lo + lane];
+                SD_CNT(4);
             }
-        };
-        // The matched node first: a narrow one whose suffixes all go on alike (the usual case: a
-        // pattern seen once or a few times) has one child of score 1, which is taken with its
-        // run without going through the frontier.
-        {
-            int32_t d = pl;
-            int cur = -1;
-            if (d < p.D && hi - lo <= CHAIN_MAX_M) unary_run(lo, hi - lo, d, cur, 1.0);
-            if (n < K)
-                push_children<STATS>(f, -1, sg, sa, text, lo, hi, d, cur, 1.0, p.min_score, p.D,
-                                     p.den_mode, nb);
+        } else {
+            // Too many suffixes for the lanes: node by node, until those of the nodes that are left fit.
+            f.n = 0;
+            f.cap = K;
+            push_children<STATS>(f, -1, sg, src == 0 && pl == 1 ? p.g_tok1 : nullptr, sa, text, lo, hi, pl, -1, 1.0, p.min_score, p.D, p.den_mode, nb);
+            if (TICKS) tick_root = (uint32_t)(wall_clock64() - tick0) + (uint32_t)(f.n & 0);
+            while (n < K && f.n > 0) {
+                if (f.n <= 64) {
+                    slots = __builtin_amdgcn_readlane(wave_inclusive_sum(lane < f.n ? f.hi[lane] - f.lo[lane] : 0), 63);
+                    if (slots <= 64) break;
+                }
+                const Taken tk0 = frontier_take(f);
+                const Key best = tk0.k;
+                {  // (given up where it cannot reach the best finished SCORE: see grow_narrow)
+                    const double top = uni(__longlong_as_double((long long)sh.top_bits));
+                    if ((total + (double)(K - n) * best.s) * (1.0 + 1e-9) < top) {
+                        n = 0;
+                        total = 0.0;
+                        f.n = 0;
+                        break;
+                    }
+                }
+                if (tk0.dep >= p.D) deepest = true;
+                if (lane == 0) {
+                    t_tok[n] = best.tok; t_par[n] = best.par; t_score[n] = best.s;
+                }
+                total += best.s;
+                const int cur = n++;
+                int hole = best.idx;
+                if (p.linear) {  // chain variant: nothing but the new node's children may follow
+                    f.n = 0;
+                    hole = -1;
+                }
+                if (n < K)
+                    push_children<STATS>(f, hole, sg, nullptr, sa, text, tk0.lo, tk0.hi, tk0.dep, cur, best.s, p.min_score,
+                                         p.D, p.den_mode, nb);
+            }
+            if (n >= K || f.n == 0) slots = 0;  // done
+            if (slots > 0) {  // node e of the frontier gets the next lanes, as many as it has suffixes
+                const int32_t c = lane < f.n ? f.hi[lane] - f.lo[lane] : 0;
+                const int32_t at = wave_inclusive_sum(c) - c;
+                wsync();
+                sg.tmp[lane] = -1;
+                wsync();
+                if (lane < f.n) sg.tmp[at] = lane;
+                wsync();
+                const int32_t e = sg.tmp[lane];
+                g.heads = __ballot(e >= 0);
+                const int first = 63 - __builtin_clzll(g.heads & ((2ull << lane) - 1ull));  // (lane 0 is one)
+                const int32_t mine = __shfl(e, first);
+                g.score = f.score[mine];
+                g.par = f.par[mine];
+                g.count = f.hi[mine] - f.lo[mine];
+                g.next = f.dep[mine] - pl - 1;
+                if (lane < slots) {
+                    sg.pos[lane] = sa[f.lo[mine] + lane - first];
+                    SD_CNT(4);
+                }
+                sg.base[lane] = g.next;
+            }
         }
-        if (TICKS) tick_root = (uint32_t)(wall_clock64() - tick0) + (uint32_t)(f.n & 0);
-        while (n < K && f.n > 0) {
-            const Taken tk0 = frontier_take(f);
-            const Key best = tk0.k;
-            if (best.s < p.min_score) break;
-            // Nodes are taken in non-increasing score order, so the K - n nodes still to come
-            // add at most that many times the best score left: a tree that cannot reach the
-            // best finished SCORE any more is given up (it could neither win nor tie; nor could
-            // the shorter patterns of its run, whose trees are its first nodes).  The SCORE is a
-            // sum of rounded additions, which may come out a few units in the last place above
-            // this product form (and two trees of equal nodes must tie exactly): hence the
-            // margin.  Checked once per step here; checks inside the merges of tied chains
-            // cost more than they saved.
-            {
-                const double top = uni(__longlong_as_double((long long)sh.top_bits));
-                if ((total + (double)(K - n) * best.s) * (1.0 + 1e-9) < top) {
-                    n = 0;
-                    total = 0.0;
-                    break;
-                }
-            }
-            const int ntop = tk0.ntop;
-            if (ntop >= 2 && !p.linear) {
-                const uint64_t m0 = TICKS ? wall_clock64() : 0;
-                const bool merged = tied_chains<STATS>(f, sg, text, best.s, K, p.D, n, total, t_tok,
-                                                       t_par, t_score, deepest, nb);
-                if (TICKS) tick_setup += (uint32_t)(wall_clock64() - m0);  // time spent merging
-                if (merged) continue;
-            }
-            const int bi = best.idx;
-            const int32_t blo = tk0.lo, bhi = tk0.hi;
-            int32_t d = tk0.dep;
-            if (d >= p.D) deepest = true;
-            if (lane == 0) {
-                t_tok[n] = best.tok; t_par[n] = best.par; t_score[n] = best.s;
-            }
-            total += best.s;
-            int cur = n++;
-            int hole = bi;
-            if (p.linear) {  // chain variant: nothing but the new node's children may follow
-                f.n = 0;
-                hole = -1;
-            }
-            // (the unary run below the node, if no other entry shares the top score)
-            const int32_t m = bhi - blo;
-            if (n < K && d < p.D && m <= CHAIN_MAX_M && (ntop == 1 || p.linear))
-                unary_run(blo, m, d, cur, best.s);
-            if (n < K)
-                push_children<STATS>(f, hole, sg, sa, text, blo, bhi, d, cur, best.s, p.min_score,
-                                     p.D, p.den_mode, nb);
-            else
-                frontier_close(f, hole);  // the last node taken cannot contribute further nodes
+        if (slots > 0) {
+            wsync();
+            n = grow_narrow<STATS, TICKS>(p, sh, sg, text, g, slots, pl, K, n, t_tok, t_par, t_score, total, deepest,
+                                          tick0, tick_root, tick_setup, nb);
         }
     }
     wsync();
@@ -2590,7 +2437,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     int32_t *const ttk0 = f.dep + cap, *const tpr0 = ttk0 + cap;
     int32_t *const ttk1 = tpr0 + cap, *const tpr1 = ttk1 + cap;
     Stage sg;
-    sg.pos = tpr1 + cap; sg.cb = sg.pos + 64; sg.tc = sg.cb + 64; sg.tmp = sg.tc + TC_TOKENS;
+    sg.pos = tpr1 + cap; sg.base = sg.pos + 64; sg.tc = sg.base + 64; sg.tmp = sg.tc + TC_TOKENS;
     f.n = 0; f.cap = 0;
 
     // Pattern lengths with the same number of occurrences in an index have the same
@@ -2859,7 +2706,7 @@ sd_status launch_speculate(sd_ctx *c, const int32_t *d_slot_ids, int32_t batch, 
     const bool stats = c->prof_mode == 2, ticks = c->prof_mode == 3 && batch <= c->tick_slots;
     // per wave: frontier 6 arrays, two trees of 3 arrays, staging
     size_t lds_wave = (size_t)c->max_nodes * (3 * sizeof(double) + 9 * sizeof(int32_t)) +
-                      (64 + 64 + TC_TOKENS + 128) * sizeof(int32_t);
+                      (64 + 64 + TC_TOKENS + 64) * sizeof(int32_t);
     lds_wave = (lds_wave + 7) / 8 * 8;
     // Waves per request.  One workgroup per compute unit takes the 16 waves a workgroup can
     // have; two share SPEC_OCC waves per SIMD between them (12 each if the LDS allows: the

@@ -1514,6 +1514,70 @@ def test_tied_chain_merges(vocab, D, P, alpha, copies):
         g.close()
 
 
+def _forked(rng, vocab, m, length, run):
+    """m token sequences that fork now and then into parts of like size, after runs of up to `run` tokens."""
+    out = [[] for _ in range(m)]
+    parts = [list(range(m))]
+    while parts:
+        g = parts.pop()
+        shared = rng.integers(0, vocab, int(rng.integers(0, run + 1))).tolist()
+        for i in g:
+            out[i] += shared
+        if len(g) == 1 or len(out[g[0]]) >= length:
+            if rng.random() < 0.5:  # goes on by itself, or ends
+                for i in g:
+                    out[i] += rng.integers(0, vocab, length).tolist()
+            continue
+        k = int(rng.integers(2, 4))
+        heads = rng.permutation(vocab)[:k]
+        for q in range(k):
+            sub = g[q::k]
+            for i in sub:
+                out[i].append(int(heads[q % len(heads)]))
+            if sub:
+                parts.append(sub)
+    return [np.array(x[:length], np.int32) for x in out]
+
+
+@pytest.mark.parametrize("den_mode,linear", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("D,P,alpha,min_score,run", [
+    (64, 32, 2.0, 0.01, 12), (20, 12, 1.0, 0.0, 3), (200, 16, 6.0, 0.02, 40), (64, 8, 2.0, 0.1, 2)])
+def test_nodes_of_up_to_64_suffixes(D, P, alpha, min_score, run, den_mode, linear):
+    """Matched nodes of 1 to 64 suffixes, and a few more than that (which grow node by node until they
+    are no more than 64): windows of all widths, runs longer than a window, runs that end at the depth
+    bound, ties between nodes of several suffixes, of few tokens and of many; in either index."""
+    rng = np.random.default_rng(D * 100 + P + 10 * den_mode + linear)
+    vocab = 50
+    docs, ctxs = [], []
+    sizes = [1, 2, 3, 7, 8, 9, 16, 17, 32, 33, 63, 64, 65, 90]
+    for k, m in enumerate(sizes):
+        # (patterns of their own tokens, so that the sizes are what they say)
+        pat = (vocab + rng.integers(0, 1000, P) + 1000 * k).astype(np.int32)
+        forks = _forked(rng, 4 if k % 2 else vocab, m, 100, run)
+        if k % 3 < 2:
+            docs += [np.concatenate([pat, f]) for f in forks]
+            ctxs.append(pat)
+        else:
+            ctxs.append(np.concatenate([x for f in forks for x in (pat, f, np.array([49999], np.int32))] + [pat]))
+    B, N = len(ctxs), sum(len(d) for d in docs) + len(docs)
+    longest = max(len(c) for c in ctxs)
+    g = parity.GpuPath(50000, D, P, alpha, min_score, B, longest + 8, N + 4, den_mode, linear)
+    try:
+        g.build_global(docs)
+        g.build_requests(range(B), ctxs)
+        tg = oracle.Trie(D)
+        for d in docs:
+            tg.add_doc(d)
+        got = g.speculate(range(B))
+        want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, min_score, g.max_nodes,
+                                             den_mode=den_mode, linear=linear)
+        bad = parity.compare_trees(got, want, "D %d P %d den_mode %d linear %d" % (D, P, den_mode, linear))
+        assert not bad, "\n".join(bad)
+        assert int((want["n_nodes"] > 0).sum()) >= B - 1
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("chunk", [0, 1, 2, 3, 460])
 def test_fuzz_fused_decode_loops(chunk):
     """50 random small configurations (10 per test), four decode steps each, every step ended by
