@@ -376,11 +376,17 @@ __device__ __forceinline__ uint64_t ballot64(bool pred) { return __builtin_amdgc
 // whether this lane's bit is set in a mask that is the same in all lanes
 __device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
+constexpr int LIST_TOKENS = 1024;
+constexpr int LIST_WAVES = 4;
+constexpr int FEW = 32;
+
 // Workgroup-shared state of one request.
 struct WgShared {
     int m;           // occurrences of the context's last token
     int next;        // head of the unit queue
     int sort_flag;   // scratch of the occurrence sort
+    int few;         // the occurrences' records are in few_occ and not in scratch memory
+    uint32_t few_occ[FEW];
     unsigned long long ctr[SD_CTR_ACCEPT_REQUESTS];  // the request's drafting counters, on their way through the launch
     int n_surv;      // occurrences whose left-extension the one-token check did not settle
     int scan_done;   // waves that have put down the hits of their part of the context scan
@@ -388,16 +394,24 @@ struct WgShared {
     int early;       // the occurrences were dealt with in such parts before the barrier
     unsigned long long top_bits;  // highest SCORE of a finished tree so far (bits of the double)
     int t_new;       // context length after the append of the fused form
+    unsigned long long acc_nodes[4];  // fused form: what is accepted, for the wave that writes it
+    int acc_len, acc_bonus;
     int newtok[260]; // fused form: the tokens appended in this launch
     int cnt[72];     // [l]: occurrences whose left-extension is l; afterwards: is at least l
     int g_lo[65], g_hi[65];  // [p]: suffix-array range of the pattern of length p (global index)
-    // global index, list form (g_mode 1): the g_n2 <= 64 suffixes that start with the context's
+    // global index, list form (g_mode 1; 0: too many for that, -1: not known yet): the g_n2 <= 64 suffixes that start with the context's
     // last two tokens, in suffix-array order: where each starts and how many tokens of the
     // context's tail it matches to the left (2 .. P); gcnt[l]: how many match exactly l
     int gl_pos[64], gl_L[64], gcnt[72];
     int g_mode, g_n2;
     double best_s[16];
     int best_o[16], best_n[16];
+    // the tokens that follow the listed suffixes' last two of the context, LIST_TOKENS >> list_log of each
+    // (every pattern length's suffixes go on with the same ones), and per suffix how many of them it
+    // shares with the one before it, and from bit 8 on how many there are before its end marker
+    int list_log, list_need;
+    int gl_shared[64];
+    int gl_tok[LIST_TOKENS];
 };
 
 // MatchPattern on the per-request structure, for all pattern lengths at once, by the whole
@@ -423,7 +437,7 @@ template <bool STATS>
 __device__ __forceinline__ void occ_scan_issue(int t_old, const int32_t *__restrict__ x, WgShared &sh,
                                                ScanState &st, unsigned &nb) {
     const int tid = threadIdx.x, nthr = blockDim.x;
-    if (tid == 0) { sh.m = 0; sh.next = 0; sh.top_bits = 0; sh.n_surv = 0; sh.scan_done = 0; sh.chunk_next = 0; sh.early = 0; }
+    if (tid == 0) { sh.m = 0; sh.next = 0; sh.top_bits = 0; sh.n_surv = 0; sh.scan_done = 0; sh.chunk_next = 0; sh.few = 0; sh.g_mode = -1; sh.early = 0; }
     if (tid < 72) { sh.cnt[tid] = 0; sh.gcnt[tid] = 0; }
     // Coalesced scan, 16 bytes per load, four loads in flight per thread; rows start 256-byte
     // aligned.
@@ -605,7 +619,7 @@ __device__ __attribute__((noinline)) unsigned occ_take_chunks(int nw, int t, int
     const int m_all = __hip_atomic_load(&sh.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     int pplog = 0;
     while ((1 << pplog) < P) pplog++;
-    if (!(m_all > nw * (64 >> pplog) * 4 && m_all <= occ_cap && m_all <= nw * 64)) return 0;
+    if (!(m_all > FEW && m_all > nw * (64 >> pplog) * 4 && m_all <= occ_cap && m_all <= nw * 64)) return 0;
     uint64_t *s_key = reinterpret_cast<uint64_t *>(s_sort + occ_cap);
     if (lane == 0) sh.early = 1;  // (every wave that gets here writes the same)
     for (;;) {
@@ -618,11 +632,11 @@ __device__ __attribute__((noinline)) unsigned occ_take_chunks(int nw, int t, int
     return nb;
 }
 
-template <bool STATS, bool EARLY, class Between>
+template <bool STATS, bool EARLY, class Settle, class Between>
 __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, int t, int t_old,
                                     const int32_t *newtok, const int32_t *__restrict__ x,
                                     int2 *s_sort, WgShared &sh, ScanState &st, int32_t tail,
-                                    unsigned &nb, Between between) {
+                                    unsigned &nb, Settle settle, Between between) {
     const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
     uint32_t *occ = p.occ + (int64_t)b * p.max_ctx;
     const int4 *x4 = reinterpret_cast<const int4 *>(x);
@@ -688,6 +702,7 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
             }
         }
     }
+    settle();
     // (this wave's hits are down: the count below says when every wave's are.  The hits and
     // the count are LDS operations of one wave, which the LDS takes in the order they were
     // issued: the compiler must keep that order, nothing has to be waited for.)
@@ -717,6 +732,19 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
         const uint64_t gmask = PP >= 64 ? ~0ull : ((1ull << PP) - 1ull);
         const int32_t tl = __shfl(tail, k);  // the k-th token from the context's end (0 beyond it)
         constexpr int U = 4;
+        // A handful of occurrences, two trips of one wave: it does all there is to do with them by itself, keys
+        // asked for with the tokens in front, and leaves the records in LDS.  (Spread over the waves, sorted by the
+        // network and handed on through scratch memory they held the slowest requests up by 1.5 us.)
+        const bool few = m <= 2 * G * U && m <= FEW && !early;
+        int32_t t1 = 0, t2 = 0, t3 = 0;
+        const int kt = p.key_toks < p.D - 1 ? p.key_toks : p.D - 1;
+        if (few && wave == 0 && lane < m) {
+            const int32_t *y = x + s_sort[lane].x;
+            t1 = y[1];
+            if (kt >= 2) t2 = y[2];
+            if (kt >= 3) t3 = y[3];
+            SD_CNT(4 * kt);
+        }
         if (early) {
             // (done already, see above)
         } else if (__builtin_expect(in_lds && m > nw * G * U, 0)) {
@@ -724,8 +752,8 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
             const unsigned cnt_many = left_extensions_many<STATS>(
                 m, t, p.P, tail, x, s_sort, reinterpret_cast<int32_t *>(s_sort + occ_cap), sh);
             SD_CNT(cnt_many);
-        } else
-        for (int i0 = wave * G * U; i0 < m; i0 += nw * G * U) {
+        } else if (!few || wave == 0)
+        for (int i0 = wave * G * U; i0 < m; i0 += (few ? 1 : nw) * G * U) {
             int e[U];
             int32_t v[U];
 #pragma unroll
@@ -755,6 +783,38 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
                     SD_CNT(8);
                 }
             }
+        }
+        if (few) {
+            if (wave == 0) {
+                wsync();
+                const int c = wave_inclusive_sum(lane < p.P ? sh.cnt[p.P - lane] : 0);
+                const int2 rec = lane < m ? s_sort[lane] : make_int2(0, 0);
+                uint64_t key = ~0ull;  // (see below)
+                if (lane < m) {
+                    const uint64_t more = floor(p.alpha * (double)rec.y) > (double)p.key_toks ? 1ull : 0ull;
+                    const int kb = p.key_bits;
+                    const uint64_t a = (uint64_t)(uint32_t)(t1 + 1), b = kt >= 2 ? (uint64_t)(uint32_t)(t2 + 1) : 0ull,
+                                   d = kt >= 3 ? (uint64_t)(uint32_t)(t3 + 1) : 0ull;
+                    key = p.key_toks == 3 ? (a << (2 * kb + 1)) | (b << (kb + 1)) | (d << 1) | more : (a << (kb + 1)) | (b << 1) | more;
+                }
+                int place = 0;
+                for (int q = 0; q < m; q++) {
+                    const uint64_t kq = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(key >> 32), q) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readlane((int32_t)key, q);
+                    bool before = kq < key || (kq == key && q < lane);
+                    const bool deeper = kq == key && (key & 1) && q != lane && lane < m;
+                    if (__builtin_expect(ballot64(deeper) != 0, 0)) {
+                        const int2 rq = make_int2(__builtin_amdgcn_readlane(rec.x, q), __builtin_amdgcn_readlane(rec.y, q));
+                        if (deeper) before = occ_less<STATS>(x, rq, rec, p.D - 1, nb);
+                    }
+                    place += before ? 1 : 0;
+                }
+                if (lane < p.P) sh.cnt[p.P - lane] = c;
+                if (lane == 0) { sh.cnt[0] = m; sh.few = 1; }
+                if (lane < m) sh.few_occ[place] = occ_pack(rec);
+            }
+            __syncthreads();
+            return;
         }
     }
     __syncthreads();
@@ -997,7 +1057,7 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
 
 // What a wave keeps in LDS of the up to 64 suffixes that grow_narrow works on: where they start, and
 // a window of their tokens each.
-constexpr int TC_TOKENS = 512;
+constexpr int TC_TOKENS = 256;
 constexpr int FILL_U = TC_TOKENS / 64;  // loads per lane that fill all the windows of a wave
 constexpr int MED_MAX = 256;  // widest node whose suffixes are all read (a multiple of 64)
 
@@ -1420,6 +1480,89 @@ template <bool STATS>
 __device__ __forceinline__ void col_stage(const SpecParams &p, int32_t w1, int32_t &lo, int32_t &hi,
                                           unsigned &nb);
 
+// The suffixes with second token w1 in the first token's bucket [lo, hi): how many there are, and, if there are
+// at most 64, where the i-th one starts in lane i: the suffix array is asked for together with the column.
+struct PairList {
+    int32_t n, at;
+    unsigned nb;  // bytes asked for (counting variant)
+};
+template <bool STATS>
+__device__ __forceinline__ PairList pair_scanned(const int32_t *__restrict__ col, const int32_t *__restrict__ sa,
+                                                 int32_t w1, int32_t lo, int32_t hi) {
+    unsigned nb = 0;
+    const int lane = threadIdx.x & 63;
+    int32_t v[SCAN_MAX / 64], a[SCAN_MAX / 64];
+#pragma unroll
+    for (int c = 0; c < SCAN_MAX / 64; c++) {
+        const int32_t i = lo + c * 64 + lane;
+        v[c] = 0x7fffffff;
+        a[c] = 0;
+        if (i < hi) {
+            v[c] = col[i];
+            a[c] = sa[i];
+            SD_CNT(8);
+        }
+    }
+    int less = 0, leq = 0;
+#pragma unroll
+    for (int c = 0; c < SCAN_MAX / 64; c++) {
+        less += __popcll(ballot64(v[c] < w1));
+        leq += __popcll(ballot64(v[c] <= w1));
+    }
+    int32_t x = a[0], y = a[1];  // the 64 entries that the first one is among, and the next 64
+#pragma unroll
+    for (int c = 1; c < SCAN_MAX / 64; c++)
+        if (less >= c * 64) {
+            x = a[c];
+            y = a[c + 1 < SCAN_MAX / 64 ? c + 1 : c];
+        }
+    const int i = (less & 63) + lane;
+    const int32_t xi = __shfl(x, i & 63), yi = __shfl(y, i & 63);
+    return {leq - less, i < 64 ? xi : yi, nb};
+}
+// (through the samples, for wider buckets: see col_sampled)
+template <bool STATS>
+__device__ __attribute__((noinline)) PairList pair_sampled(const int32_t *__restrict__ col,
+                                                           const int32_t *__restrict__ samples,
+                                                           const int32_t *__restrict__ sa, int32_t w1,
+                                                           int32_t lo, int32_t hi) {
+    unsigned nb = 0;
+    const int lane = threadIdx.x & 63;
+    w1 = uni(w1); lo = uni(lo); hi = uni(hi);
+    const int32_t j0 = (lo + 15) >> 4, j1 = (hi - 1) >> 4;
+    int32_t v[SAMP_C];
+#pragma unroll
+    for (int c = 0; c < SAMP_C; c++) {
+        const int32_t j = j0 + c * 64 + lane;
+        v[c] = j <= j1 ? samples[j] : 0x7fffffff;
+        if (j <= j1) SD_CNT(4);
+    }
+    int less = 0, leq = 0;  // samples
+#pragma unroll
+    for (int c = 0; c < SAMP_C; c++) {
+        less += __popcll(ballot64(v[c] < w1));
+        leq += __popcll(ballot64(v[c] <= w1));
+    }
+    // lane 0..15: the block that holds the lower end; lane 16..31: the one that holds the upper end
+    const int32_t base0 = less == 0 ? lo : ((j0 + less - 1) << 4) + 1, base1 = leq == 0 ? lo : ((j0 + leq - 1) << 4) + 1;
+    const int32_t end0 = (j0 + less) << 4 < hi ? (j0 + less) << 4 : hi, end1 = (j0 + leq) << 4 < hi ? (j0 + leq) << 4 : hi;
+    const int32_t i = (lane < 16 ? base0 : base1) + (lane & 15);
+    const bool act = lane < 32 && i < (lane < 16 ? end0 : end1);
+    const int32_t t = act ? col[i] : 0x7fffffff;
+    int32_t at = base0 + lane < hi ? sa[base0 + lane] : 0;
+    if (act) SD_CNT(4);
+    if (base0 + lane < hi) SD_CNT(4);
+    const int below = __popcll(ballot64(t < w1) & 0xffffull), first = base0 + below;
+    const int n = base1 + (int)__popcll(ballot64(t <= w1) & 0xffff0000ull) - first;
+    if (below + n > 64 && n <= 64) {  // (not all of them among the entries at hand)
+        at = first + lane < hi ? sa[first + lane] : 0;
+        if (first + lane < hi) SD_CNT(4);
+    } else {
+        at = __shfl(at, (below + lane) & 63);
+    }
+    return {n, at, nb};
+}
+
 template <bool STATS>
 __device__ __forceinline__ void match_global(const SpecParams &p, int32_t wk, int pl, int32_t &lo, int32_t &hi,
                              unsigned &nb) {
@@ -1574,6 +1717,7 @@ struct Narrow {
     uint64_t heads;
     double score;
     int32_t next, par, count;
+    int32_t lcp, own, row, wend;  // what grow_narrow knows of a suffix whose tokens are in LDS already
 };
 
 // ExpandSpeculationTree where the frontier's nodes have up to 64 suffixes together, from the matched node on
@@ -1604,7 +1748,7 @@ struct Narrow {
 // 10M tokens behind them 24.7 us on average (22.1 so), of 64 with 2.2M 21.1 (18.7), of 512 with 100M 29.6 (25.3).
 template <bool STATS, bool TICKS>
 __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &sh, Stage &sg,
-                                           const int32_t *__restrict__ text, const Narrow &g, int m, int pl, int K,
+                                           const int32_t *__restrict__ text, const Narrow &g, bool windows, int m, int pl, int K,
                                            int n, int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
                                            bool &deepest, uint64_t tick0, uint32_t &tick_root,
                                            uint32_t &tick_merge, unsigned &nb) {
@@ -1668,6 +1812,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
     int32_t f_r = g.next, f_par = g.par, f_c = g.count;  // ... index and parent of its next token, and its suffixes)
     double tot = total;
     bool deep = deepest;
+    constexpr uint32_t DEAD = 0xffffffffu;  // (above every token: a run that has ended)
     auto range = [](int lo, int hi) -> uint64_t { return (~0ull >> (64 - (hi - lo))) << lo; };  // (not empty)
     auto end_of = [&](int lo) -> int {  // where the node that starts at suffix lo ends
         const uint64_t b = (heads | ~alive) & (~1ull << lo);
@@ -1677,14 +1822,44 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
         if (hi - lo == 1) return __builtin_amdgcn_readlane(own, lo);
         return (int)reduce_min_u32(lane > lo && lane < hi ? (uint32_t)lcp : ~0u);
     };
+    // Puts the children of nodes in their place, whose suffixes are `over` (`firsts`: the first of each) and
+    // whose runs end at index re, with last node par; dn: how many suffixes the node of a lane has.
+    auto children = [&](uint64_t over, uint64_t firsts, int32_t re, int32_t par, int32_t dn, int first, double s) {
+        const uint64_t le = (2ull << lane) - 1ull;
+        const int32_t tok = sg.tc[lane_in(over) ? row + re : 0];
+        if (p.den_mode) {  // only the suffixes that go on
+            const uint64_t ended = over & ballot64(tok < 0);
+            dn -= __popcll((ended >> first) & (~0ull >> (64 - dn)));
+        }
+        const uint64_t S = firsts | (over & ballot64(lcp == re)), above = (S | ~over) & ~le;
+        const int c = (above ? __builtin_ctzll(above) : 64) - lane;
+        const double sc = c == dn ? s : s * ((double)c / (double)dn);  // x / x == 1 and s * 1 == s exactly
+        const uint64_t C = S & ballot64(tok >= 0) & ballot64(sc >= p.min_score);
+        // what follows the start of a child that stays, up to the next start (the addition carries through it)
+        const uint64_t x = over & ~S, keep = C | (x & ~(x + ((C << 1) & x)));
+        heads = (heads & ~over) | C;
+        alive = (alive & ~over) | keep;
+        f_s = lane_in(C) ? sc : f_s;
+        f_r = lane_in(C) ? re : f_r;
+        f_par = lane_in(C) ? par : f_par;
+        f_c = lane_in(C) ? c : f_c;
+    };
 
-    fill(0, m, n == 0 ? 0 : -1, W < K - n ? W : K - n);
-    while (n < K && heads) {
+    if (windows) {
+        lcp = g.lcp < rel_end ? g.lcp : rel_end;
+        own = g.own < rel_end ? g.own : rel_end;
+        row = g.row;
+        wend = g.wend;
+    } else {
+        fill(0, m, n == 0 ? 0 : -1, W < K - n ? W : K - n);
+    }
+    while (n < K && heads) {  // (the only way out: more of them cost every pass a dozen branches)
+        const unsigned long long top_bits = sh.top_bits;  // (asked for before it is needed)
         // The nodes T with the top score s: with den_mode 0 a score is the node's share of the suffixes but for
         // its roundings, so more suffixes score more, and as many score the same or nearly so.
         uint64_t T = heads;
         double s;
-        if (p.den_mode == 0) {
+        if (__builtin_expect(p.den_mode == 0, 1)) {
             if (T & (T - 1ull)) {
                 const uint32_t c = lane_in(heads) ? (uint32_t)f_c : 0u;
                 const uint32_t most = reduce_max_u32(c);
@@ -1702,22 +1877,9 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
             s = wave_max_f64(lane_in(heads) ? f_s : -__longlong_as_double(0x7ff0000000000000ll));
             T &= ballot64(f_s == s);
         }
-        // Nodes are taken in non-increasing score order, so the K - n nodes still to come add at most
-        // that many times the best score left: a tree that cannot reach the best finished SCORE any more
-        // is given up (it could neither win nor tie; nor could the shorter patterns of its run, whose
-        // trees are its first nodes).  The SCORE is a sum of rounded additions, which may come out a few
-        // units in the last place above this product form (and two trees of equal nodes must tie
-        // exactly): hence the margin.
-        {
-            const double top = uni(__longlong_as_double((long long)sh.top_bits));
-            if ((tot + (double)(K - n) * s) * (1.0 + 1e-9) < top) {
-                total = 0.0;
-                return 0;
-            }
-        }
         if (p.linear) {  // chain variant: of the nodes at hand only the best one, the one with the lowest token
             if (T & (T - 1ull)) {
-                const uint32_t tk = lane_in(T) ? (uint32_t)sg.tc[row + f_r] : ~0u;
+                const uint32_t tk = lane_in(T) ? (uint32_t)sg.tc[row + f_r] : DEAD;
                 T &= ballot64(tk == reduce_min_u32(tk));
                 T &= 0ull - T;
             }
@@ -1729,104 +1891,117 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
         if (__builtin_expect(moved != 0, 0)) {
             const int lo = __builtin_ctzll(moved), hi = end_of(lo), r0 = __builtin_amdgcn_readlane(f_r, lo);
             fill(lo, hi - lo, r0, W < K - n ? W : K - n);
-            if (run_end(lo, hi) > r0) continue;
-            T = 1ull << lo;  // (its children, which score less, are due)
+            // (where not even the window's first token is shared, the children, which score less, are due;
+            // otherwise the pass starts again)
+            T = run_end(lo, hi) > r0 ? 0ull : 1ull << lo;
         }
-
-        const uint64_t m0 = TICKS ? wall_clock64() : 0;
-        constexpr uint32_t DEAD = 0xffffffffu;    // (above every token: a run that has ended)
-        int left = __popcll(T);                   // runs that have not
-        const bool many = left > 1;
-        uint32_t ht = DEAD;                       // a head's token ...
-        int32_t rank = lane_in(T) ? 0 : 1 << 20;  // ... and its rank among the heads
-        if (many) {
+        // Nodes are taken in non-increasing score order, so the K - n nodes still to come add at most
+        // that many times the best score left: a tree that cannot reach the best finished SCORE any more
+        // is given up (it could neither win nor tie; nor could the shorter patterns of its run, whose
+        // trees are its first nodes).  The SCORE is a sum of rounded additions, which may come out a few
+        // units in the last place above this product form (and two trees of equal nodes must tie
+        // exactly): hence the margin.
+        if ((tot + (double)(K - n) * s) * (1.0 + 1e-9) < uni(__longlong_as_double((long long)top_bits))) {
+            heads = 0;
+            n = 0;
+            tot = 0.0;
+        } else if (T == 0) {
+            // (a window was moved)
+        } else if ((T & (T - 1ull)) == 0) {
+            const int lo = __builtin_ctzll(T), hi = end_of(lo);
+            const int r = __builtin_amdgcn_readlane(f_r, lo), at = __builtin_amdgcn_readlane(row, lo) + r;
+            const int32_t tk = sg.tc[at + lane];  // (what lies behind the run's end is not looked at)
+            int32_t par = __builtin_amdgcn_readlane(f_par, lo);
+            const int e = run_end(lo, hi), L = e - r < K - n ? e - r : K - n;
+            if (lane < L) {
+                t_tok[n + lane] = tk;
+                t_par[n + lane] = lane == 0 ? par : n + lane - 1;
+                t_score[n + lane] = s;
+            }
+            tot = add_times(tot, s, L);
+            n += L;
+            par = L > 0 ? n - 1 : par;
+            deep = deep || r + L >= rel_end;
+            if (e >= rel_end) {
+                heads &= ~T;
+                alive &= ~range(lo, hi);
+            } else if (e >= __builtin_amdgcn_readlane(wend, lo)) {
+                f_r = lane == lo ? e : f_r;
+                f_par = lane == lo ? par : f_par;
+            } else if (n < K) {
+                children(range(lo, hi), T, e, par, hi - lo, lo, s);
+            }
+        } else {
+            const uint64_t m0 = TICKS ? wall_clock64() : 0;
+            int left = __popcll(T);                               // runs that have not ended
+            uint32_t ht = DEAD;                                   // a head's token ...
             if (lane_in(T)) ht = (uint32_t)sg.tc[row + f_r];
+            int32_t rank = lane_in(T) ? 0 : 1 << 20;              // ... and its rank among the heads
             for (uint64_t t = T; t; t &= t - 1ull) {
                 const int q = __builtin_ctzll(t);
                 const uint32_t kt = (uint32_t)__builtin_amdgcn_readlane((int32_t)ht, q);
                 const int32_t kp = __builtin_amdgcn_readlane(f_par, q);
                 rank += (kt < ht || (kt == ht && kp < f_par)) ? 1 : 0;
             }
-        }
-        const int n0 = n;
-        uint64_t over = 0;  // the suffixes of the nodes whose runs lead to children
-        int32_t ends = -1;  // (of a head: where its run ends, once it has been asked for)
-        do {
-            const int w = __builtin_ctzll(ballot64(rank == 0));
-            int e = __builtin_amdgcn_readlane(ends, w);
-            if (e < 0) {
-                e = run_end(w, end_of(w));
-                if (lane == w) ends = e;
-            }
-            const int r = __builtin_amdgcn_readlane(f_r, w), at = __builtin_amdgcn_readlane(row, w) + r;
-            const int L = e - r < K - n ? e - r : K - n;
-            const uint32_t tk = (uint32_t)sg.tc[at + lane];  // (what lies behind the run's end is not looked at)
-            int len = L;
-            uint32_t next = DEAD;
-            if (left > 1) {  // up to the next token that is no lower than the lowest of the other heads
-                const int w1 = __builtin_ctzll(ballot64(rank == 1));
-                const uint64_t b = ballot64(tk >= (uint32_t)__builtin_amdgcn_readlane((int32_t)ht, w1)) & ~1ull;
-                const int x = b ? __builtin_ctzll(b) : 64;
-                if (x < L) {
-                    len = x;
-                    next = (uint32_t)__builtin_amdgcn_readlane((int32_t)tk, x);
+            const int n0 = n;
+            uint64_t over = 0;  // the suffixes of the nodes whose runs lead to children
+            int32_t ends = -1;  // (of a head: where its run ends, once it has been asked for)
+            while (left > 0 && n < K) {
+                const int w = __builtin_ctzll(ballot64(rank == 0));
+                const int r = __builtin_amdgcn_readlane(f_r, w), at = __builtin_amdgcn_readlane(row, w) + r;
+                const uint32_t tk = (uint32_t)sg.tc[at + lane];
+                int e = __builtin_amdgcn_readlane(ends, w);
+                if (e < 0) {
+                    e = run_end(w, end_of(w));
+                    ends = lane == w ? e : ends;
+                }
+                int len = e - r < K - n ? e - r : K - n;
+                uint32_t next = DEAD;
+                if (left > 1) {  // up to the next token that is no lower than the lowest of the other heads
+                    const int w1 = __builtin_ctzll(ballot64(rank == 1));
+                    const uint64_t b = ballot64(tk >= (uint32_t)__builtin_amdgcn_readlane((int32_t)ht, w1)) & ~1ull;
+                    const int x = b ? __builtin_ctzll(b) : 64;
+                    if (x < len) {
+                        len = x;
+                        next = (uint32_t)__builtin_amdgcn_readlane((int32_t)tk, x);
+                    }
+                }
+                const int32_t par = __builtin_amdgcn_readlane(f_par, w);
+                if (lane < len) {
+                    t_tok[n + lane] = (int32_t)tk;
+                    t_par[n + lane] = lane == 0 ? par : n + lane - 1;
+                    t_score[n + lane] = s;
+                }
+                n += len;
+                deep = deep || r + len >= rel_end;
+                // (the new head's parent is the youngest node there is: of equal tokens it comes last)
+                const uint64_t older = ballot64(ht <= next) & ~(1ull << w);
+                const int nr = next == DEAD ? 1 << 20 : __popcll(older);
+                rank = lane == w ? nr : rank - (lane_in(older) ? 1 : 0);
+                ht = lane == w ? next : ht;
+                f_r = lane == w ? r + len : f_r;
+                f_par = lane == w ? n - 1 : f_par;
+                if (next == DEAD) {  // the run has ended (or the tree is full)
+                    const int hi = end_of(w);
+                    left--;
+                    if (e >= rel_end) {
+                        heads &= ~(1ull << w);
+                        alive &= ~range(w, hi);
+                    } else if (e >= __builtin_amdgcn_readlane(wend, w)) {
+                        left = 0;  // (or rather its window has: the others wait until that is moved)
+                    } else {
+                        over |= range(w, hi);
+                        if (p.den_mode) left = 0;
+                    }
                 }
             }
-            const int32_t par = __builtin_amdgcn_readlane(f_par, w);
-            if (lane < len) {
-                t_tok[n + lane] = (int32_t)tk;
-                t_par[n + lane] = lane == 0 ? par : n + lane - 1;
-                t_score[n + lane] = s;
+            tot = add_times(tot, s, n - n0);
+            if (over && n < K) {
+                const uint64_t firsts = heads & over, f = firsts & ((2ull << lane) - 1ull);
+                const int mine = f ? 63 - __builtin_clzll(f) : 0;  // the head of this lane's node
+                children(over, firsts, __shfl(f_r, mine), __shfl(f_par, mine), __shfl(f_c, mine), mine, s);
             }
-            n += len;
-            if (r + len >= rel_end) deep = true;
-            if (n >= K) break;
-            // (the new head's parent is the youngest node there is: of equal tokens it comes last)
-            const uint64_t older = ballot64(ht <= next) & ~(1ull << w);
-            if (lane_in(older)) rank--;
-            if (lane == w) {
-                rank = next == DEAD ? 1 << 20 : __popcll(older);
-                ht = next;
-                f_r = r + len;
-                f_par = len > 0 ? n - 1 : par;
-            }
-            if (next == DEAD) {  // the run has ended
-                const int hi = end_of(w);
-                left--;
-                if (e >= rel_end) {
-                    heads &= ~(1ull << w);
-                    alive &= ~range(w, hi);
-                } else if (e >= __builtin_amdgcn_readlane(wend, w)) {
-                    break;  // (or rather its window)
-                } else {
-                    over |= range(w, hi);
-                    if (p.den_mode) break;
-                }
-            }
-        } while (left > 0);
-        tot = add_times(tot, s, n - n0);
-        if (TICKS && many) tick_merge += (uint32_t)(wall_clock64() - m0);
-        if (n >= K) break;
-        if (over) {
-            // children: wherever the tokens behind the run differ
-            const uint64_t firsts = heads & over, le = (2ull << lane) - 1ull, f = firsts & le;
-            const int mine = f ? 63 - __builtin_clzll(f) : 0;  // the head of this lane's node
-            const int32_t re = __shfl(f_r, mine), par = __shfl(f_par, mine);
-            int32_t dn = __shfl(f_c, mine);
-            const int32_t tok = sg.tc[lane_in(over) ? row + re : 0];
-            if (p.den_mode) {  // only the suffixes that go on
-                const uint64_t ended = over & ballot64(tok < 0);
-                dn -= __popcll((ended >> mine) & (~0ull >> (64 - dn)));
-            }
-            const uint64_t S = firsts | (over & ballot64(lcp == re)), above = (S | ~over) & ~le;
-            const int c = (above ? __builtin_ctzll(above) : 64) - lane;
-            const double sc = c == dn ? s : s * ((double)c / (double)dn);  // x / x == 1 and s * 1 == s exactly
-            const uint64_t C = S & ballot64(tok >= 0) & ballot64(sc >= p.min_score);
-            // what follows the start of a child that stays, up to the next start (the addition carries through it)
-            const uint64_t x = over & ~S, keep = C | (x & ~(x + ((C << 1) & x)));
-            heads = (heads & ~over) | C;
-            alive = (alive & ~over) | keep;
-            if (lane_in(C)) { f_s = sc; f_r = re; f_par = par; f_c = c; }
+            if (TICKS) tick_merge += (uint32_t)(wall_clock64() - m0);
         }
         if (TICKS && tick_root == 0) tick_root = (uint32_t)(wall_clock64() - tick0);
     }
@@ -1850,24 +2025,40 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
     const int64_t uidx = (int64_t)b * (2 * p.P) + src * p.P + (pl - 1);
     const int K = (int)floor(p.alpha * (double)pl);
     uint32_t tick_setup = 0, tick_match = 0, tick_root = 0;
-    bool staged = false;  // (the suffixes' starts are in sg.pos)
+    bool staged = false;   // (the suffixes' starts are in sg.pos)
+    bool windows = false;  // (and their tokens in LDS)
+    Narrow g;
     const int32_t *sa = nullptr, *text = nullptr;
     int32_t lo = 0, hi = 0;
     if (pl <= t && K >= 1) {
-        if (src == 0 && pl >= 2 && uni(sh.g_mode) != 0) {
+        if (src == 0 && pl >= 2 && uni(sh.g_mode) == 1) {
             // list form: the listed suffixes that match at least pl tokens, in their order
             // (the suffix array's, i.e. sorted by what follows the pattern), staged whole
             const int n2 = uni(sh.g_n2);
-            const bool keep = lane < n2 && sh.gl_L[lane] >= pl;
-            const uint64_t mk = __ballot(keep);
+            const int in_list = lane < n2 ? lane : 0;
+            const int32_t shared = sh.gl_shared[in_list], pos = sh.gl_pos[in_list], reach = sh.gl_L[in_list];
+            const uint64_t mk = ~0ull >> (64 - n2) & ballot64(reach >= pl);
             const int m = __popcll(mk);
-            if (keep) {
-                const int dst = __popcll(mk & lanemask_lt());
-                sg.pos[dst] = sh.gl_pos[lane] - (pl - 2);
+            // (what a suffix shares with the one before it is the least of what lies between them in the list)
+            int32_t lcp = shared & 255;
+            for (uint64_t t = mk & ~(mk << 1) & ~(mk & (0ull - mk)); t; t &= t - 1ull) {
+                const int i = __builtin_ctzll(t), i0 = 63 - __builtin_clzll(mk & ((1ull << i) - 1ull));
+                const int l = (int)reduce_min_u32(lane > i0 && lane <= i ? (uint32_t)shared & 255u : ~0u);
+                if (lane == i) lcp = l;
             }
-            staged = true;
-            __threadfence_block();
+            if (lane_in(mk)) {
+                const int dst = __popcll(mk & lanemask_lt());
+                sg.pos[dst] = pos - (pl - 2);
+                sg.tmp[dst] = lane << 16 | (shared & 0xff00) | lcp;
+            }
             wsync();
+            const int32_t mine = sg.tmp[lane];
+            const int need = uni(sh.list_need);
+            g.own = (mine >> 8) & 255;
+            g.lcp = mine & 255;
+            g.row = (int32_t)(sh.gl_tok - sg.tc) + ((mine >> 16) << uni(sh.list_log));
+            g.wend = need;
+            staged = windows = true;
             sa = p.g_sa;  // never read: the whole list is staged
             text = p.g_text;
             lo = 0;
@@ -1888,12 +2079,12 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
             // a list of more than 64 occurrences goes to the request's row of scratch memory,
             // at the place the caller has assigned to this run of pattern lengths
             int32_t *usa = p.unit_sa + (int64_t)b * p.max_ctx + usa_off;
-            const bool narrow = m <= 64;
+            const bool narrow = m <= 64, few = uni(sh.few) != 0;
             int w = 0;
             for (int base = 0; base < m1; base += 64) {
                 int i = base + lane;
                 int2 o = make_int2(0, 0);
-                if (i < m1) o = occ_unpack(occ[i]);
+                if (i < m1) o = occ_unpack(few ? sh.few_occ[i] : occ[i]);
                 if (i < m1) SD_CNT(4);
                 bool keep = i < m1 && o.y >= pl;
                 uint64_t mk = __ballot(keep);
@@ -1920,7 +2111,6 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
     if (TICKS) tick_match = (uint32_t)(wall_clock64() - tick0) + (uint32_t)((hi - lo) & 0);
     if (hi > lo) {
         int slots = hi - lo;  // suffixes of the frontier's nodes, all together
-        Narrow g;
         if (__builtin_expect(slots <= 64, 1)) {  // the matched node alone
             g.heads = 1ull;
             g.score = 1.0;
@@ -1994,7 +2184,7 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh,
         }
         if (slots > 0) {
             wsync();
-            n = grow_narrow<STATS, TICKS>(p, sh, sg, text, g, slots, pl, K, n, t_tok, t_par, t_score, total, deepest,
+            n = grow_narrow<STATS, TICKS>(p, sh, sg, text, g, windows, slots, pl, K, n, t_tok, t_par, t_score, total, deepest,
                                           tick0, tick_root, tick_setup, nb);
         }
     }
@@ -2024,18 +2214,19 @@ struct AcceptArgs {
 };
 
 // Acceptance for request b on one wavefront (max_nodes <= 256): node j is accepted iff its
-// token equals the target token at its parent's position and its parent is accepted, which
-// pointer jumping over the parent links settles in at most eight rounds (trees of up to 64
-// nodes: one node per lane, links and flags in registers; larger ones in LDS).  s_tgt[257],
-// s_anc[256] and s_ok[256] are LDS of the calling wave.  With APPEND the accepted tokens and the bonus
-// token go behind the slot's context (and into s_new in LDS if that is given).  Returns the
-// slot's context length afterwards (0 for a bad slot), which only the APPEND form looks up.
+// token equals the target token at its parent's position and its parent is accepted.  accept_find says
+// which nodes that are (bits of Accepted::nodes), how many, and the bonus token; s_tgt[257],
+// s_anc[256] and s_ok[256] are LDS of the calling wave.  accept_store writes what the caller is told.
+//
 // What the acceptance reads first, for lane l: the node count, node l and target position l
-// (and position 64, which a tree of 64 nodes has), and the request's two counters.  Kept apart
-// from accept_wave so that a caller with other loads to wait for can issue these first.
+// (and position 64, which a tree of 64 nodes has).  Kept apart from accept_find so that a caller with
+// other loads to wait for can issue these first.
 struct AcceptIn {
     int32_t n, tok0, par0, tgt0, tgt64;
-    unsigned long long c_req, c_len;
+};
+struct Accepted {
+    uint64_t nodes[4];
+    int32_t len, bonus;
 };
 
 __device__ __forceinline__ AcceptIn accept_fetch(int b, const int32_t *__restrict__ n_nodes,
@@ -2050,29 +2241,19 @@ __device__ __forceinline__ AcceptIn accept_fetch(int b, const int32_t *__restric
     in.par0 = lane < max_nodes ? parents[(int64_t)b * max_nodes + lane] : -1;
     in.tgt0 = lane <= max_nodes ? tgt[lane] : 0;
     in.tgt64 = max_nodes >= 64 ? tgt[64] : 0;
-    // this request's counters of verified requests and accepted nodes (see sd_internal.h)
-    const unsigned long long *ctr = aa.counters + (int64_t)b * SD_CTR_STRIDE;
-    in.c_req = 0; in.c_len = 0;
-    if (lane == 0) { in.c_req = ctr[SD_CTR_ACCEPT_REQUESTS]; in.c_len = ctr[SD_CTR_ACCEPT_LEN]; }
     return in;
 }
 
-template <bool APPEND>
-__device__ __forceinline__ int accept_wave(int b, const AcceptIn &in,
-                                           const int32_t *__restrict__ tokens,
-                                           const int32_t *__restrict__ parents, int max_nodes,
-                                           const AcceptArgs &aa, const AppendArgs &ap, int32_t *s_tgt,
-                                           int32_t *s_anc, int32_t *s_ok, int32_t *s_new,
-                                           int32_t known_slot = -2, int32_t known_len = 0) {
+__device__ __forceinline__ Accepted accept_find(int b, const AcceptIn &in, const int32_t *__restrict__ tokens,
+                                                const int32_t *__restrict__ parents, int max_nodes,
+                                                const AcceptArgs &aa, int32_t *s_tgt, int32_t *s_anc,
+                                                int32_t *s_ok, int32_t (&mt)[4]) {
     const int lane = threadIdx.x & 63;
     const int32_t *tok = tokens + (int64_t)b * max_nodes, *par = parents + (int64_t)b * max_nodes;
     const int32_t *tgt = aa.target + (int64_t)b * (max_nodes + 1);
-    int32_t *path = aa.accept_path + (int64_t)b * max_nodes;
     int n = in.n;
-    unsigned long long *ctr = aa.counters + (int64_t)b * SD_CTR_STRIDE;
-    const unsigned long long c_req = in.c_req, c_len = in.c_len;
     const bool small = max_nodes <= 64;  // one node per lane: settled in registers, below
-    int32_t mt[4], mp[4];
+    int32_t mp[4];  // (mt[r]: token of node 64 r + lane)
     mt[0] = in.tok0; mp[0] = in.par0;
 #pragma unroll
     for (int r = 1; r < 4; r++) {
@@ -2093,19 +2274,20 @@ __device__ __forceinline__ int accept_wave(int b, const AcceptIn &in,
     int L = 0, last = -1;
     int32_t bon;
     if (small) {
-        // the same pointer jumping with the links and flags in registers, passed between
-        // lanes by permutes: no LDS round trip and no wave barrier per round
+        // One node per lane, sets of nodes as masks.  Trees are made of runs of nodes whose parent is the
+        // node before, so a round takes the good nodes whose parent is accepted together with the good
+        // runs behind them (the addition carries through a run), and there are as many rounds as runs on the
+        // accepted path.  (Pointer jumping, a round per bit of the depth with two permutes each:
+        // accepted 0.4 us later.)
         const bool wf = lane < n && mp[0] >= -1 && mp[0] < lane;
         const int32_t want = __shfl(in.tgt0, wf ? mp[0] + 1 : 0);  // (mp[0] + 1 <= lane <= 63)
-        int32_t ok = wf && mt[0] == want, anc = wf ? mp[0] : -1;
-        for (int round = 0; round < 6; round++) {  // 2^6 >= the deepest possible path
-            const bool open = anc >= 0;
-            if (!__ballot(open)) break;
-            const int src = open ? anc : lane;
-            const int32_t o2 = __shfl(ok, src), a2 = __shfl(anc, src);
-            if (open) { ok &= o2; anc = a2; }
+        const uint64_t good = ballot64(wf) & ballot64(mt[0] == want), chain = good & ballot64(mp[0] == lane - 1) & ~1ull;
+        uint64_t heads = good & ballot64(mp[0] < 0), all = 0;
+        while (heads) {
+            all |= heads | (chain & ~(chain + ((heads << 1) & chain)));
+            heads = good & ~all & ballot64(mp[0] >= 0 && ((all >> (mp[0] & 63)) & 1ull));
         }
-        am[0] = __ballot(lane < n && ok);
+        am[0] = all;
         if (am[0]) last = 63 - __clzll((unsigned long long)am[0]);
         L = __popcll(am[0]);
         bon = last + 1 < 64 ? __builtin_amdgcn_readlane(in.tgt0, (last + 1) & 63) : in.tgt64;
@@ -2156,64 +2338,45 @@ __device__ __forceinline__ int accept_wave(int b, const AcceptIn &in,
     }
     bon = s_tgt[last + 1];
     }
-    int32_t *row = nullptr;
-    int32_t old = 0, slot_of_b = 0;
-    bool slot_ok = false;
-    if (APPEND) {  // L accepted tokens and the bonus token go behind the slot's context
-        // (a caller that has looked up the slot and its length already passes them in)
-        const int32_t slot = known_slot != -2 ? known_slot : (ap.slot_ids ? ap.slot_ids[b] : b);
-        if (slot < 0 || slot >= ap.max_slots) {
-            if (lane == 0) atomicOr(&ap.err[SD_DEVERR_SLOT], 1);
-        } else {
-            slot_ok = true;
-            slot_of_b = slot;
-            old = known_slot != -2 ? known_len : ap.r_len[slot];
-            if ((int64_t)old + L + 1 > ap.max_ctx) {
-                if (lane == 0) atomicOr(&ap.err[SD_DEVERR_CTX], 1);
-            } else {
-                row = ap.r_text + (int64_t)slot * ap.stride;
-            }
-        }
-    }
+    return {{am[0], am[1], am[2], am[3]}, L, bon};
+}
+
+// Whether the accepted tokens and the bonus token fit behind the context of `old` tokens in a slot; if not,
+// or if there is no such slot, the caller hears of it from sd_get_stats.
+__device__ __forceinline__ bool append_fits(const AppendArgs &ap, int32_t slot, int32_t old, int32_t len) {
+    const bool ok = slot >= 0 && slot < ap.max_slots, fits = ok && (int64_t)old + len + 1 <= ap.max_ctx;
+    if (!fits && (threadIdx.x & 63) == 0) atomicOr(&ap.err[ok ? SD_DEVERR_CTX : SD_DEVERR_SLOT], 1);
+    return fits;
+}
+// a token as it goes into a context
+__device__ __forceinline__ int32_t append_token(const AppendArgs &ap, int32_t t) {
+    if (t >= 0 && t < ap.vocab) return t;
+    atomicOr(&ap.err[SD_DEVERR_TOKEN], 1);
+    return 0;
+}
+
+// The accepted nodes in order, how many, the bonus token; c: lane k's counter k of the request before this call.
+__device__ __forceinline__ void accept_store(int b, const Accepted &a, int max_nodes, const AcceptArgs &aa,
+                                             unsigned long long c) {
+    const int lane = threadIdx.x & 63;
+    int32_t *path = aa.accept_path + (int64_t)b * max_nodes;
     int done = 0;
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-        int j = lane + 64 * r;
-        if ((am[r] >> lane) & 1ull) {
-            const int at = done + __popcll(am[r] & lanemask_lt());
-            path[at] = j;
-            if (APPEND && row) {
-                int32_t t = mt[r];
-                if (t < 0 || t >= ap.vocab) {
-                    atomicOr(&ap.err[SD_DEVERR_TOKEN], 1);
-                    t = 0;
-                }
-                row[old + at] = t;
-                if (s_new) s_new[at] = t;
-            }
-        }
-        done += __popcll(am[r]);
+        if (lane_in(a.nodes[r])) path[done + __popcll(a.nodes[r] & lanemask_lt())] = lane + 64 * r;
+        done += __popcll(a.nodes[r]);
     }
-    for (int i = L + lane; i < max_nodes; i += 64) path[i] = -1;
+    for (int i = a.len + lane; i < max_nodes; i += 64) path[i] = -1;
     if (lane == 0) {
-        aa.accept_len[b] = L;
-        aa.bonus[b] = bon;
-        ctr[SD_CTR_ACCEPT_REQUESTS] = c_req + 1ull;
-        ctr[SD_CTR_ACCEPT_LEN] = c_len + (unsigned long long)L;
-        if (APPEND && row) {
-            int32_t t = bon;
-            if (t < 0 || t >= ap.vocab) {
-                atomicOr(&ap.err[SD_DEVERR_TOKEN], 1);
-                t = 0;
-            }
-            row[old + L] = t;
-            if (s_new) s_new[L] = t;
-            ap.r_len[slot_of_b] = old + L + 1;
-        }
+        aa.accept_len[b] = a.len;
+        aa.bonus[b] = a.bonus;
     }
-    return !slot_ok ? 0 : (row ? old + L + 1 : old);
+    if (lane == SD_CTR_ACCEPT_REQUESTS || lane == SD_CTR_ACCEPT_LEN)
+        aa.counters[(int64_t)b * SD_CTR_STRIDE + lane] = c + (unsigned long long)(lane == SD_CTR_ACCEPT_LEN ? a.len : 1);
 }
 
+// With APPEND the accepted draft tokens and the bonus token are also written behind the context
+// of the request's slot (what sd_index_append would do with them), in the same launch.
 template <bool APPEND>
 __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nodes,
                                                const int32_t *__restrict__ tokens,
@@ -2222,9 +2385,29 @@ __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nod
     __shared__ int32_t s_tgt[257];
     __shared__ int32_t s_anc[256];
     __shared__ int32_t s_ok[256];
-    const AcceptIn in = accept_fetch(blockIdx.x, n_nodes, tokens, parents, max_nodes, aa);
-    accept_wave<APPEND>(blockIdx.x, in, tokens, parents, max_nodes, aa, ap, s_tgt, s_anc, s_ok,
-                        nullptr);
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const AcceptIn in = accept_fetch(b, n_nodes, tokens, parents, max_nodes, aa);
+    const unsigned long long c = lane < SD_CTR_N ? aa.counters[(int64_t)b * SD_CTR_STRIDE + lane] : 0ull;
+    int32_t mt[4];
+    const Accepted a = accept_find(b, in, tokens, parents, max_nodes, aa, s_tgt, s_anc, s_ok, mt);
+    if (APPEND) {
+        const int32_t slot = ap.slot_ids ? ap.slot_ids[b] : b;
+        const int32_t old = slot >= 0 && slot < ap.max_slots ? ap.r_len[slot] : 0;
+        if (append_fits(ap, slot, old, a.len)) {
+            int32_t *row = ap.r_text + (int64_t)slot * ap.stride + old;
+            int done = 0;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                if (lane_in(a.nodes[r])) row[done + __popcll(a.nodes[r] & lanemask_lt())] = append_token(ap, mt[r]);
+                done += __popcll(a.nodes[r]);
+            }
+            if (lane == 0) {
+                row[a.len] = append_token(ap, a.bonus);
+                ap.r_len[slot] = old + a.len + 1;
+            }
+        }
+    }
+    accept_store(b, a, max_nodes, aa, c);
 }
 
 // GenerateCandidateTree for one request per workgroup.  All waves first build the request's
@@ -2285,7 +2468,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // third of a microsecond).  Plain loads and stores: a row belongs to one workgroup per
     // launch.
     unsigned long long ctr_old = 0;
-    if (wave == nw - 1 && lane < SD_CTR_ACCEPT_REQUESTS)
+    if (wave == nw - 1 && lane < (ACCEPT ? SD_CTR_N : SD_CTR_ACCEPT_REQUESTS))
         ctr_old = p.counters[(int64_t)b * SD_CTR_STRIDE + lane];
     int t = t_old;
     // lane k < P: the k-th token from the context's end.  Loaded now for the context as it
@@ -2293,26 +2476,30 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // that nothing has to be read back from the row once the acceptance is settled.
     int32_t tail = 0;
     if (lane < P && lane < t_old) tail = x[t_old - 1 - lane];
-    // lane k: pattern token k of the wave's first two pattern lengths (taken from the tail)
-    int32_t wkA0 = 0, wkB0 = 0;
-    auto pattern_tokens = [&]() {
-        const int plA = 1 + wave, plB = plA + nw;
-        const int32_t a = __shfl(tail, (plA - 1 - lane) & 63), bb = __shfl(tail, (plB - 1 - lane) & 63);
-        if (plA <= P && plA <= t && lane < plA) wkA0 = a;
-        if (plB <= P && plB <= t && lane < plB) wkB0 = bb;
-    };
     if (ACCEPT) {
         if (wave == 0) {
             // LDS that the occurrence sort takes over afterwards
             int32_t *s_tgt = reinterpret_cast<int32_t *>(smem), *s_anc = s_tgt + 260, *s_ok = s_anc + 256;
-            const int nl = accept_wave<true>(b, ain, out.d_tokens, out.d_parents,
-                                             out.max_nodes, aa, ap, s_tgt, s_anc, s_ok, sh.newtok,
-                                             slot, t_old);
-            if (lane == 0) sh.t_new = nl;
+            int32_t mt[4];
+            const Accepted a = accept_find(b, ain, out.d_tokens, out.d_parents, out.max_nodes, aa, s_tgt, s_anc, s_ok, mt);
+            const bool fits = append_fits(ap, slot, t_old, a.len);
+            if (fits) {
+                int done = 0;
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    if (lane_in(a.nodes[r])) sh.newtok[done + __popcll(a.nodes[r] & lanemask_lt())] = append_token(ap, mt[r]);
+                    done += __popcll(a.nodes[r]);
+                }
+                if (lane == 0) sh.newtok[a.len] = append_token(ap, a.bonus);
+            }
+            if (lane == 0) {
+                sh.t_new = fits ? t_old + a.len + 1 : t_old;
+#pragma unroll
+                for (int r = 0; r < 4; r++) sh.acc_nodes[r] = a.nodes[r];
+                sh.acc_len = a.len;
+                sh.acc_bonus = a.bonus;
+            }
         }
-        // The barrier orders the first wave's stores to the row before the other waves' loads
-        // at workgroup scope, which is all that is needed: the waves of a workgroup share one
-        // compute unit and its cache, and only this workgroup touches the row.
         __syncthreads();
         t = slot_ok ? uni(sh.t_new) : 0;
         {   // the appended tokens come first in the tail, the old tail moves back
@@ -2320,88 +2507,162 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             const int32_t moved = __shfl(tail, (lane - n_new) & 63);
             if (n_new > 0) tail = lane < P && lane < t ? (lane < n_new ? sh.newtok[n_new - 1 - lane] : moved) : 0;
         }
-        pattern_tokens();
     } else {
-        pattern_tokens();
         __syncthreads();  // the counters of the occurrence list are set
     }
     // (the counters wait in LDS for the end of the launch: two registers less to carry through
     // matching and expansion; the load is older than the tail's, which has just been waited for)
     if (wave == nw - 1 && lane < SD_CTR_ACCEPT_REQUESTS) sh.ctr[lane] = ctr_old;
+    // (the buckets of the last two tokens are asked for before the scan's words are looked at)
+    const bool two = P >= 2 && t >= 2 && p.g_N > 0;
+    int32_t bv = 0;
+    if (two && lane < 4) {
+        const int32_t w = lane < 2 ? __builtin_amdgcn_readlane(tail, 1) : __builtin_amdgcn_readlane(tail, 0);
+        bv = p.g_bucket[w + 1 + (lane & 1)];
+        SD_CNT(4);
+    }
     request_occurrences<STATS, ACCEPT>(p, b, t, t_old, sh.newtok, x, s_sort, sh, scan, tail, nb, [&]() {
-        // List form: the suffixes that start with the context's last two tokens are located
-        // once (every wave does that for itself: same loads, no barrier).  If there are at
-        // most 64 of them, every longer pattern's occurrences are among them: the waves share
-        // them out and count how far each agrees with the context's tail to the left, which
-        // settles all pattern lengths in two more rounds of loads (suffix array, text), and
-        // the expansions get their suffix lists from LDS.  Otherwise every pattern length is
-        // searched for on its own, as below.
-        if (P >= 2 && t >= 2 && p.g_N > 0) {
-            const int32_t w_last = __builtin_amdgcn_readlane(tail, 0), w_prev = __builtin_amdgcn_readlane(tail, 1);
-            const int32_t bv = lane < 4 ? p.g_bucket[(lane < 2 ? w_prev : w_last) + 1 + (lane & 1)] : 0;
-            if (lane < 4) SD_CNT(4);
-            int32_t lo2 = __builtin_amdgcn_readlane(bv, 0), hi2 = __builtin_amdgcn_readlane(bv, 1);
-            const int32_t lo1 = __builtin_amdgcn_readlane(bv, 2), hi1 = __builtin_amdgcn_readlane(bv, 3);
+        // What acceptance and append have to write, by the last wave, once it needs nothing more of what it has
+        // asked for: a wave's loads and stores are waited for in order, and the first wave, which every other
+        // one waits for, would wait for its stores with its share of the scan (0.4 us of a decode step).
+        // The barrier behind the scan orders the stores to the row before the other waves' loads at workgroup
+        // scope, which is all that is needed: the waves of a workgroup share one compute unit and its cache,
+        // and only this workgroup touches the row.
+        if (ACCEPT && wave == nw - 1) {
+            Accepted a;
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                a.nodes[r] = ((uint64_t)(uint32_t)uni((int32_t)(sh.acc_nodes[r] >> 32)) << 32) | (uint32_t)uni((int32_t)sh.acc_nodes[r]);
+            a.len = uni(sh.acc_len);
+            a.bonus = uni(sh.acc_bonus);
+            int32_t *row = ap.r_text + (int64_t)slot * ap.stride;
+            for (int i = lane; i < t - t_old; i += 64) row[t_old + i] = sh.newtok[i];
+            if (lane == 0 && t > t_old) ap.r_len[slot] = t;
+            accept_store(b, a, out.max_nodes, aa, ctr_old);
+        }
+    }, [&]() {
+        // List form: the suffixes that start with the context's last two tokens are located once, by a
+        // few waves (each for itself: no barrier, and four waves do not get into each other's way, one
+        // on a SIMD).  If there are at most 64 of them, every longer pattern's occurrences are among
+        // them: the waves share them out and count how far each agrees with the context's tail to the
+        // left, which settles all pattern lengths in one more round of loads, and the expansions get
+        // their suffix lists from LDS.  Otherwise every pattern length is searched for on its own, by all
+        // waves, which wait to hear how long the list is where the bucket does not say so (the waves that
+        // find out wait for nobody).
+        bool search = !two;
+        if (search && threadIdx.x == 0) sh.g_mode = 0;
+        if (!search) {
+            const int32_t lo2 = __builtin_amdgcn_readlane(bv, 0), hi2 = __builtin_amdgcn_readlane(bv, 1);
             // (a first token with a bucket beyond the sampled lookup's reach would cost a long
             // search here and most likely leave more than 64 suffixes: not tried)
-            const bool reach = hi2 - lo2 <= SAMPLED_MAX;
-            if (reach && lo2 < hi2) col_stage<STATS>(p, w_last, lo2, hi2, nb);
-            const int n2 = hi2 > lo2 ? hi2 - lo2 : 0;
-            if (__builtin_expect(reach && n2 <= 64, 1)) {
-                // (stored at once: two values less to keep through the loop)
-                if (threadIdx.x == 0) { sh.g_lo[1] = lo1; sh.g_hi[1] = hi1; }
-                int pplog = 0;
-                while ((1 << pplog) < P) pplog++;
-                const int PP = 1 << pplog, G = 64 >> pplog, g = lane >> pplog, k = lane & (PP - 1);
-                const uint64_t gmask = PP >= 64 ? ~0ull : ((1ull << PP) - 1ull);
-                const int32_t tl = __shfl(tail, k);
-                constexpr int U = 4;
-                for (int i0 = wave * G * U; i0 < n2; i0 += nw * G * U) {
-                    int32_t ee[U], v[U];
-#pragma unroll
-                    for (int u = 0; u < U; u++) {  // where the suffix's second token sits
-                        const int i = i0 + u * G + g;
-                        ee[u] = i < n2 ? p.g_sa[lo2 + i] + 1 : -1;
-                        if (i < n2 && k == 0) SD_CNT(4);
+            search = hi2 - lo2 > SAMPLED_MAX;
+            const int lw = nw < LIST_WAVES ? nw : LIST_WAVES;
+            if (search) {
+                if (threadIdx.x == 0) sh.g_mode = 0;
+            } else if (wave >= lw) {
+                int mode;
+                while ((mode = __hip_atomic_load(&sh.g_mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < 0) __builtin_amdgcn_s_sleep(1);
+                search = uni(mode) == 0;
+            } else {
+                int n2 = 0;
+                int32_t at_i = 0;  // lane i: where suffix i starts
+                if (lo2 < hi2) {
+                    const PairList r = hi2 - lo2 > SCAN_MAX
+                        ? pair_sampled<STATS>(p.g_tok1, p.g_tok1s, p.g_sa, __builtin_amdgcn_readlane(tail, 0), lo2, hi2)
+                        : pair_scanned<STATS>(p.g_tok1, p.g_sa, __builtin_amdgcn_readlane(tail, 0), lo2, hi2);
+                    n2 = uni(r.n);
+                    at_i = r.at;
+                    if (wave == 0) SD_CNT(r.nb);
+                }
+                search = n2 > 64;
+                if (threadIdx.x == 0) __hip_atomic_store(&sh.g_mode, search ? 0 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (!search) {
+                    if (threadIdx.x == 0) {
+                        sh.g_lo[1] = __builtin_amdgcn_readlane(bv, 2);
+                        sh.g_hi[1] = __builtin_amdgcn_readlane(bv, 3);
                     }
+                    int pplog = 0;
+                    while ((1 << pplog) < P) pplog++;
+                    const int PP = 1 << pplog, G = 64 >> pplog, g = lane >> pplog, k = lane & (PP - 1);
+                    const uint64_t gmask = PP >= 64 ? ~0ull : ((1ull << PP) - 1ull);
+                    const int32_t tl = __shfl(tail, k);
+                    // What follows the suffixes is staged for all pattern lengths together, in the same round of
+                    // loads as the tokens in front of them; a wave takes `rows` neighbouring suffixes.  (Staged by
+                    // every expansion for itself, behind the barrier, it took each of them two LDS round trips and
+                    // one to memory, some 1.0 us of its 6 to 9.)
+                    int wlog = 0;
+                    while (wlog < 6 && (1 << wlog) < p.max_nodes) wlog++;
+                    while ((n2 << wlog) > LIST_TOKENS) wlog--;
+                    const int need = 1 << wlog < p.max_nodes ? 1 << wlog : p.max_nodes;
+                    const int rows = (n2 + lw - 1) / lw, row0 = wave * rows, row1 = row0 + rows < n2 ? row0 + rows : n2;
+                    auto row = [&](int i) -> int32_t {
+                        return i >= 0 && i < row1 && lane < need ? p.g_text[__builtin_amdgcn_readlane(at_i, i & 63) + 2 + lane] : 0;
+                    };
+                    constexpr int ROWS = 4;
+                    int32_t before = row(row0 - 1), tk[ROWS];
 #pragma unroll
-                    for (int u = 0; u < U; u++) {
-                        int lim = ee[u] + 1 < P ? ee[u] + 1 : P;  // (0 for an empty place)
-                        lim = lim < t ? lim : t;
-                        const bool rd = ee[u] >= 0 && k < lim;
-                        v[u] = rd ? p.g_text[ee[u] - k] : tl;
-                        if (rd) SD_CNT(4);
-                    }
+                    for (int q = 0; q < ROWS; q++) tk[q] = row(row0 + q);
+                    constexpr int U = 4;
+                    for (int i0 = wave * G * U; i0 < n2; i0 += lw * G * U) {
+                        int32_t ee[U], v[U];
 #pragma unroll
-                    for (int u = 0; u < U; u++) {
-                        int lim = ee[u] + 1 < P ? ee[u] + 1 : P;
-                        lim = lim < t ? lim : t;
-                        const uint64_t mis = __ballot(k >= 1 && k < lim && v[u] != tl);
-                        const uint64_t gm = (mis >> (g << pplog)) & gmask;
-                        const int l = gm ? __ffsll((unsigned long long)gm) - 1 : lim;
-                        if (k == 0 && ee[u] >= 0) {
+                        for (int u = 0; u < U; u++) {  // where the suffix's second token sits
                             const int i = i0 + u * G + g;
-                            sh.gl_pos[i] = ee[u] - 1;
-                            sh.gl_L[i] = l;
-                            atomicAdd(&sh.gcnt[l], 1);
+                            const int32_t at = __shfl(at_i, i & 63);
+                            ee[u] = i < n2 ? at + 1 : -1;
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; u++) {
+                            int lim = ee[u] + 1 < P ? ee[u] + 1 : P;  // (0 for an empty place)
+                            lim = lim < t ? lim : t;
+                            const bool rd = ee[u] >= 0 && k < lim;
+                            v[u] = rd ? p.g_text[ee[u] - k] : tl;
+                            if (rd) SD_CNT(4);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; u++) {
+                            int lim = ee[u] + 1 < P ? ee[u] + 1 : P;
+                            lim = lim < t ? lim : t;
+                            const uint64_t mis = __ballot(k >= 1 && k < lim && v[u] != tl);
+                            const uint64_t gm = (mis >> (g << pplog)) & gmask;
+                            const int l = gm ? __ffsll((unsigned long long)gm) - 1 : lim;
+                            if (k == 0 && ee[u] >= 0) {
+                                const int i = i0 + u * G + g;
+                                sh.gl_pos[i] = ee[u] - 1;
+                                sh.gl_L[i] = l;
+                                atomicAdd(&sh.gcnt[l], 1);
+                            }
                         }
                     }
+                    const uint64_t in = ~0ull >> (64 - need);
+                    for (int i0 = row0; i0 < row1; i0 += ROWS) {
+                        if (i0 > row0) {
+#pragma unroll
+                            for (int q = 0; q < ROWS; q++) tk[q] = row(i0 + q);
+                        }
+#pragma unroll
+                        for (int q = 0; q < ROWS; q++) {
+                            const int i = i0 + q;
+                            if (i < row1) {
+                                const uint64_t e = in & ballot64(tk[q] < 0), d = e | (in & ballot64(tk[q] != before));
+                                if (lane < need) { sh.gl_tok[(i << wlog) + lane] = tk[q]; SD_CNT(4); }
+                                if (lane == 0) sh.gl_shared[i] = (d ? __builtin_ctzll(d) : need) | (e ? __builtin_ctzll(e) : need) << 8;
+                                before = tk[q];
+                            }
+                        }
+                    }
+                    if (threadIdx.x == 0) { sh.g_n2 = n2; sh.list_log = wlog; sh.list_need = need; }
                 }
-                if (threadIdx.x == 0) { sh.g_mode = 1; sh.g_n2 = n2; }
-                return;
             }
         }
-        if (threadIdx.x == 0) sh.g_mode = 0;
+        if (!search) return;
         for (int plA = 1 + wave; plA <= P; plA += 2 * nw) {
             const int plB = plA + nw;  // a wave takes its pattern lengths two at a time
             const bool okA = plA <= t && p.g_N > 0, okB = plB <= P && plB <= t && p.g_N > 0;
             int32_t loA = 0, hiA = 0, loB = 0, hiB = 0;
-            const bool first = plA == 1 + wave;
-            int32_t wkA = wkA0, wkB = wkB0;
-            if (!first) {
-                wkA = okA && lane < plA ? x[t - plA + lane] : 0;
-                wkB = okB && lane < plB ? x[t - plB + lane] : 0;
-            }
+            // lane k: pattern token k (from the tail: the row may not hold the appended tokens yet)
+            const int32_t ta = __shfl(tail, (plA - 1 - lane) & 63), tb = __shfl(tail, (plB - 1 - lane) & 63);
+            const int32_t wkA = okA && lane < plA ? ta : 0, wkB = okB && lane < plB ? tb : 0;
             if (okA && lane < plA) SD_CNT(4);
             if (okB && lane < plB) SD_CNT(4);
             if (okA && okB && plB <= 32)
@@ -2455,7 +2716,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // Runs: entry i stands for pattern length P - i; lane i looks at entry i.
     int cg = 0, cr = 0, cgp = -1, crp = -1;
     bool alone = true;  // the next longer pattern may reach the depth bound
-    const bool listed = uni(sh.g_mode) != 0;
+    const bool listed = uni(sh.g_mode) == 1;
     // list form: lane i (pattern length P - i) gets the number of listed suffixes that match
     // at least that many tokens (a running sum over gcnt[P], gcnt[P - 1], ...)
     const int32_t gsum = listed ? wave_inclusive_sum(lane < P ? sh.gcnt[P - lane] : 0) : 0;
@@ -2507,7 +2768,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     }
 
     if (wave == nw - 1) {  // the routes this request takes, into the row of counters (lane k: counter k)
-        const bool two = t >= 2 && P >= 2 && p.g_N > 0;
         const int add = lane == SD_CTR_GLOBAL_LIST ? (listed && two)
                         : lane == SD_CTR_GLOBAL_SEARCH ? (!listed && two)
                         : lane == SD_CTR_REQUEST_WIDE ? (wide_r != 0)
@@ -2631,14 +2891,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     flush_count<STATS>(nb, p.algo_bytes + SD_K_SPECULATE);
 }
 
-// Greedy verification walk, one wavefront per request, without walking: a node is "good" if
-// its token equals the target token at its parent; it is accepted iff it and all its
-// ancestors are good (siblings carry distinct tokens, so the accepted nodes form one path).
-// Ancestor chains are resolved by pointer jumping in LDS (log2(depth) rounds); because a
-// parent always has a lower index than its child, the path in walk order is the accepted
-// nodes in index order.
-// With APPEND the accepted draft tokens and the bonus token are also written behind the context
-// of the request's slot (what sd_index_append would do with them), in the same launch.
 }  // namespace
 
 // Scratch memory of sd_speculate_static: the occurrence records and suffix-list rows of its
