@@ -1,9 +1,8 @@
 """MI355X-native draft generation for SuffixDecoding (arxiv 2411.04975).
 
 The work is done by hand-written HIP kernels behind the C ABI declared in
-include/sd.h; this package is a thin ctypes binding with the same call names.
-There is no CPU fallback: importing the binding without the built shared
-object raises.
+include/sd.h; this package is a thin binding with the same call names.
+There is no CPU fallback: a call without the built shared objects raises.
 """
 from .binding import (SD_SCOPE_GLOBAL, SD_SCOPE_REQUESTS, SD_STATIC_SCRATCH_BYTES, SD_TICK_SLOTS,  # noqa: F401
                       SdError, Trees, lib_path, sd_accept, sd_accept_append,

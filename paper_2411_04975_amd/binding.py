@@ -1,4 +1,6 @@
-"""ctypes binding over libsd.so: argument marshalling only.
+"""Binding over libsd.so: argument marshalling only, through ctypes; the calls of a decode step go
+through csrc/sd_calls.cpp first, which marshals what is plainly right in native code (3 us a call instead
+of 11: with small batches the kernels take no longer) and leaves everything else to the code here.
 
 Every function mirrors the C entry point of the same name in include/sd.h.
 Tensors are torch CUDA (ROCm) tensors; the binding checks dtype, device,
@@ -68,6 +70,7 @@ class _Profile(C.Structure):
 
 
 _lib = None
+_calls = None   # the calls of a decode step in native code (csrc/sd_calls.cpp)
 
 
 def lib_path() -> str:
@@ -121,6 +124,10 @@ def _load():
     L.sd_debug_read_unit_ticks.argtypes = [vp, vp, C.c_int64, C.POINTER(C.c_int32)]
     L.sd_debug_read_global.restype = C.c_int
     L.sd_debug_read_global.argtypes = [vp, vp, vp, C.c_int64, C.POINTER(C.c_int64)]
+    global _calls
+    from . import _sdcalls  # (built with libsd.so)
+    _sdcalls.set_trees(Trees)
+    _calls = _sdcalls
     _lib = L
     return L
 
@@ -132,6 +139,7 @@ class _Ctx:
         self.handle = handle
         self.cfg = cfg
         self.max_nodes = int(_load().sd_max_nodes(handle))
+        self.index = int(cfg.device)
         self.device = torch.device("cuda", cfg.device)
 
 
@@ -163,6 +171,10 @@ def _stream(stream, ctx: _Ctx):
     if stream is None:
         stream = torch.cuda.current_stream(ctx.device)
     return C.c_void_p(stream.cuda_stream)
+
+
+def _raw(stream, ctx: _Ctx) -> int:
+    return torch._C._cuda_getCurrentRawStream(ctx.index) if stream is None else stream.cuda_stream
 
 
 def sd_create(vocab: int, D: int, P: int, alpha: float, min_score: float, max_batch_slots: int,
@@ -250,6 +262,10 @@ def sd_index_entropy(ctx: _Ctx, stream=None):
 
 def sd_index_append(ctx: _Ctx, slot_ids: torch.Tensor, new_tokens: torch.Tensor,
                     new_offsets: torch.Tensor, stream=None) -> None:
+    if ctx.handle is not None:
+        code = _calls.append(ctx.handle.value, ctx.index, _raw(stream, ctx), slot_ids, new_tokens, new_offsets)
+        if code is not None:
+            return _check(ctx, code)
     n = int(new_offsets.numel()) - 1 if slot_ids is None else int(slot_ids.numel())
     code = _load().sd_index_append(
         ctx.handle, _ptr(slot_ids, torch.int32, ctx, 0 if slot_ids is None else n, "slot_ids"),
@@ -267,6 +283,10 @@ def _batch_of(slot_ids, trees: "Trees") -> int:
 
 
 def sd_speculate(ctx: _Ctx, slot_ids: Optional[torch.Tensor], trees: Trees, stream=None) -> None:
+    if ctx.handle is not None:
+        code = _calls.speculate(ctx.handle.value, ctx.index, _raw(stream, ctx), slot_ids, trees)
+        if code is not None:
+            return _check(ctx, code)
     batch = _batch_of(slot_ids, trees)
     code = _load().sd_speculate(ctx.handle, _ptr(slot_ids, torch.int32, ctx, 0 if slot_ids is None else batch, "slot_ids"),
                                 batch, trees._struct(ctx, batch), _stream(stream, ctx))
@@ -284,6 +304,11 @@ def sd_speculate_static(ctx: _Ctx, slot_ids: torch.Tensor, trees: Trees, stream=
 def sd_accept(ctx: _Ctx, trees: Trees, batch: int, target_tokens: torch.Tensor,
               accept_len: torch.Tensor, accept_path: torch.Tensor, bonus: torch.Tensor,
               stream=None) -> None:
+    if ctx.handle is not None:
+        code = _calls.accept(ctx.handle.value, ctx.index, _raw(stream, ctx), trees, batch, target_tokens, accept_len,
+                              accept_path, bonus)
+        if code is not None:
+            return _check(ctx, code)
     i32 = torch.int32
     mn = trees.max_nodes
     code = _load().sd_accept(ctx.handle, trees._struct(ctx, batch), batch,
@@ -298,6 +323,11 @@ def sd_accept_append(ctx: _Ctx, trees: Trees, slot_ids: torch.Tensor, target_tok
                      accept_len: torch.Tensor, accept_path: torch.Tensor, bonus: torch.Tensor,
                      stream=None) -> None:
     """sd_accept plus sd_index_append of the accepted tokens and the bonus token, one launch."""
+    if ctx.handle is not None:
+        code = _calls.accept_append(ctx.handle.value, ctx.index, _raw(stream, ctx), trees, slot_ids, target_tokens,
+                                     accept_len, accept_path, bonus)
+        if code is not None:
+            return _check(ctx, code)
     i32 = torch.int32
     mn = trees.max_nodes
     batch = _batch_of(slot_ids, trees)
@@ -315,6 +345,11 @@ def sd_accept_append_speculate(ctx: _Ctx, trees: Trees, slot_ids: torch.Tensor,
                                accept_path: torch.Tensor, bonus: torch.Tensor, stream=None) -> None:
     """sd_accept_append of the verified drafts in `trees`, then sd_speculate of the next drafts into
     `trees`, one launch."""
+    if ctx.handle is not None:
+        code = _calls.accept_append_speculate(ctx.handle.value, ctx.index, _raw(stream, ctx), trees, slot_ids,
+                                               target_tokens, accept_len, accept_path, bonus)
+        if code is not None:
+            return _check(ctx, code)
     i32 = torch.int32
     mn = trees.max_nodes
     batch = _batch_of(slot_ids, trees)

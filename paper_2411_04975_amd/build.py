@@ -1,4 +1,5 @@
-"""Compile the HIP sources of the library for gfx950 into an in-tree shared object."""
+"""Compile the HIP sources of the library for gfx950 into an in-tree shared object, and the Python
+side's calls (csrc/sd_calls.cpp, host code) into another one beside it."""
 from __future__ import annotations
 
 import glob
@@ -8,6 +9,7 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libsd.so")
+CALLS_PATH = os.path.join(_HERE, "_sdcalls.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
@@ -29,7 +31,26 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd))
     subprocess.check_call(cmd)
     os.replace(tmp, LIB_PATH)
+    build_calls(verbose)
     return LIB_PATH
+
+
+def build_calls(verbose: bool = False) -> str:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = CALLS_PATH + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wno-unused-result",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-o", tmp, os.path.join(CSRC, "sd_calls.cpp"), "-L" + _HERE, "-l:libsd.so", "-Wl,-rpath,$ORIGIN",
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    os.replace(tmp, CALLS_PATH)
+    return CALLS_PATH
 
 
 if __name__ == "__main__":

@@ -1578,6 +1578,97 @@ def test_nodes_of_up_to_64_suffixes(D, P, alpha, min_score, run, den_mode, linea
         g.close()
 
 
+def test_calls_take_what_is_right_and_say_what_is_not():
+    """The calls of a decode step marshal plain arguments in native code and leave the rest to Python: both
+    ways give the same drafts, acceptance and contexts (a subclass of Trees, subclasses of torch.Tensor and
+    explicit streams go the second way or the first), and wrong arguments raise what they always did."""
+    import torch
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(11)
+    vocab, D, P, B = 50, 16, 8, 6
+    docs = [rng.integers(0, 5, 300).astype(np.int32) for _ in range(4)]
+    ctxs = [rng.integers(0, 5, 40).astype(np.int32) for _ in range(B)]
+    dev = torch.device("cuda", 0)
+
+    class OtherTrees(sd.Trees):
+        pass
+
+    class OtherTensor(torch.Tensor):
+        pass
+
+    def play(trees_class, wrap, stream):
+        ctx = sd.sd_create(vocab, D, P, 1.0, 0.05, B, 200, 2000)
+        try:
+            flat = torch.from_numpy(np.concatenate(docs)).to(dev)
+            off = torch.tensor(np.cumsum([0] + [len(d) for d in docs]), dtype=torch.int64, device=dev)
+            sd.sd_index_build(ctx, sd.SD_SCOPE_GLOBAL, None, flat, off, int(flat.numel()))
+            req = torch.from_numpy(np.concatenate(ctxs)).to(dev)
+            roff = torch.arange(0, 40 * B + 1, 40, dtype=torch.int64, device=dev)
+            sd.sd_index_build(ctx, sd.SD_SCOPE_REQUESTS, None, req, roff, 40 * B)
+            trees = trees_class(B, ctx.max_nodes, dev)
+            ids = wrap(torch.arange(B, dtype=torch.int32, device=dev))
+            said = [wrap(torch.from_numpy(rng2.integers(0, 5, (B, ctx.max_nodes + 1)).astype(np.int32)).to(dev))
+                    for rng2 in (np.random.default_rng(i) for i in range(3))]
+            n = wrap(torch.zeros(B, dtype=torch.int32, device=dev))
+            path = wrap(torch.zeros((B, ctx.max_nodes), dtype=torch.int32, device=dev))
+            bonus = wrap(torch.zeros(B, dtype=torch.int32, device=dev))
+            new, new_off = wrap(torch.arange(B, dtype=torch.int32, device=dev) % 5), wrap(torch.arange(B + 1, dtype=torch.int32, device=dev))
+            out = []
+
+            def keep():
+                torch.cuda.synchronize()
+                out.extend(x.cpu().numpy().copy() for x in (trees.n_nodes, trees.tokens, trees.parents, trees.scores,
+                                                             trees.match_len, trees.source, n, path, bonus))
+            sd.sd_speculate(ctx, ids, trees, stream=stream)
+            keep()
+            sd.sd_accept(ctx, trees, B, said[0], n, path, bonus, stream=stream)
+            sd.sd_index_append(ctx, ids, new, new_off, stream=stream)
+            sd.sd_speculate(ctx, None, trees, stream=stream)
+            keep()
+            sd.sd_accept_append(ctx, trees, None, said[1], n, path, bonus, stream=stream)
+            sd.sd_speculate(ctx, ids, trees, stream=stream)
+            keep()
+            sd.sd_accept_append_speculate(ctx, trees, ids, said[2], n, path, bonus, stream=stream)
+            keep()
+            i64, cpu, small = ids.long(), ids.cpu(), ids[:B - 1]
+            wide = torch.zeros((2 * B, 1), dtype=torch.int32, device=dev).expand(2 * B, 4)
+            for bad, err in ((i64, TypeError), (cpu, ValueError), (small, ValueError), (wide, ValueError), (3, TypeError), (None, ValueError)):
+                for args in ((said[2], bad, path, bonus), (said[2], n, path, bad)):
+                    with pytest.raises(err):
+                        sd.sd_accept(ctx, trees, B, *args)
+                    with pytest.raises(err):
+                        sd.sd_accept_append(ctx, trees, ids, *args)
+                    with pytest.raises(err):
+                        sd.sd_accept_append_speculate(ctx, trees, None, *args)
+                if bad is not None and bad is not small:
+                    with pytest.raises((TypeError, ValueError, AttributeError)):
+                        sd.sd_speculate(ctx, bad, trees)
+                with pytest.raises((TypeError, ValueError)):
+                    sd.sd_index_append(ctx, ids, new, bad if bad is not None else cpu)
+            with pytest.raises(ValueError):
+                sd.sd_speculate(ctx, torch.zeros(B + 1, dtype=torch.int32, device=dev), trees)
+            short = trees_class(B, ctx.max_nodes, dev)
+            short.scores = short.scores[:1]
+            with pytest.raises(ValueError):
+                sd.sd_speculate(ctx, ids, short)
+            with pytest.raises(sd.SdError):
+                sd.sd_speculate(ctx, None, trees_class(B, ctx.max_nodes - 1, dev))
+            with pytest.raises(sd.SdError):
+                sd.sd_speculate(ctx, None, trees_class(B + 1, ctx.max_nodes, dev))
+        finally:
+            sd.sd_destroy(ctx)
+        with pytest.raises(sd.SdError):
+            sd.sd_speculate(ctx, ids, trees)
+        return out
+
+    want = play(sd.Trees, lambda x: x, None)
+    assert int(want[0].sum()) > 0 and int(want[-3].sum()) > 0
+    for how in ((OtherTrees, lambda x: x, None), (sd.Trees, lambda x: x.as_subclass(OtherTensor), None),
+                (sd.Trees, lambda x: x, torch.cuda.current_stream(dev))):
+        for x, y in zip(want, play(*how)):
+            assert np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("chunk", [0, 1, 2, 3, 460])
 def test_fuzz_fused_decode_loops(chunk):
     """50 random small configurations (10 per test), four decode steps each, every step ended by
