@@ -385,6 +385,9 @@ struct WgShared {
     int m;           // occurrences of the context's last token
     int next;        // head of the unit queue
     int sort_flag;   // scratch of the occurrence sort
+    int n_runs, n_global, wide;     // expansions to make, those of the global index, and whether a list is long
+    unsigned long long start_r;     // (entries at which runs of the request's index start)
+    int run[128];
     int few;         // the occurrences' records are in few_occ and not in scratch memory
     uint32_t few_occ[FEW];
     unsigned long long ctr[SD_CTR_ACCEPT_REQUESTS];  // the request's drafting counters, on their way through the launch
@@ -659,6 +662,9 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
             }
 #pragma unroll
             for (int k = 0; k < 4; k++) {
+                if (q0 + k * nthr >= nq) break;
+                // (most words hold no hit, in no lane, and sixteen waves look at theirs side by side)
+                if (__builtin_expect((ballot64(v[k].x == last) | ballot64(v[k].y == last) | ballot64(v[k].z == last) | ballot64(v[k].w == last)) == 0, 1)) continue;
                 const int e0 = 4 * (q0 + k * nthr + tid);
                 const int h0 = v[k].x == last && e0 < t_old, h1 = v[k].y == last && e0 + 1 < t_old,
                           h2 = v[k].z == last && e0 + 2 < t_old, h3 = v[k].w == last && e0 + 3 < t_old;
@@ -2560,8 +2566,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             if (search) {
                 if (threadIdx.x == 0) sh.g_mode = 0;
             } else if (wave >= lw) {
-                int mode;
-                while ((mode = __hip_atomic_load(&sh.g_mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < 0) __builtin_amdgcn_s_sleep(1);
+                int mode = 1;  // (a bucket of 64 has no longer list)
+                if (hi2 - lo2 > 64)
+                    while ((mode = __hip_atomic_load(&sh.g_mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < 0) __builtin_amdgcn_s_sleep(6);
                 search = uni(mode) == 0;
             } else {
                 int n2 = 0;
@@ -2713,28 +2720,45 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // known after its expansion, and waiting for that would serialise the run.  Such patterns
     // are therefore taken one by one (all in parallel), and runs are formed among the shorter
     // ones, where the bound cannot interfere.
-    // Runs: entry i stands for pattern length P - i; lane i looks at entry i.
-    int cg = 0, cr = 0, cgp = -1, crp = -1;
-    bool alone = true;  // the next longer pattern may reach the depth bound
+    // Runs: entry i stands for pattern length P - i; lane i looks at entry i.  The first wave does it for all
+    // (sixteen waves doing the same side by side take each other's turns: 150 instructions, a microsecond).
     const bool listed = uni(sh.g_mode) == 1;
-    // list form: lane i (pattern length P - i) gets the number of listed suffixes that match
-    // at least that many tokens (a running sum over gcnt[P], gcnt[P - 1], ...)
-    const int32_t gsum = listed ? wave_inclusive_sum(lane < P ? sh.gcnt[P - lane] : 0) : 0;
-    const int32_t gsum_up = __shfl_up(gsum, 1);
-    if (lane < P) {
-        const int pl = P - lane;
-        cg = listed && pl >= 2 ? gsum : sh.g_hi[pl] - sh.g_lo[pl];
-        cr = sh.cnt[pl];
-        if (lane > 0) {
-            cgp = listed ? gsum_up : sh.g_hi[pl + 1] - sh.g_lo[pl + 1];
-            crp = sh.cnt[pl + 1];
-            alone = pl + 1 + (int)floor(p.alpha * (double)(pl + 1)) >= p.D;
+    if (wave == 0) {
+        int cg = 0, cr = 0, cgp = -1, crp = -1;
+        bool alone = true;  // the next longer pattern may reach the depth bound
+        // list form: lane i (pattern length P - i) gets the number of listed suffixes that match
+        // at least that many tokens (a running sum over gcnt[P], gcnt[P - 1], ...)
+        const int32_t gsum = listed ? wave_inclusive_sum(lane < P ? sh.gcnt[P - lane] : 0) : 0;
+        const int32_t gsum_up = __shfl_up(gsum, 1);
+        if (lane < P) {
+            const int pl = P - lane;
+            cg = listed && pl >= 2 ? gsum : sh.g_hi[pl] - sh.g_lo[pl];
+            cr = sh.cnt[pl];
+            if (lane > 0) {
+                cgp = listed ? gsum_up : sh.g_hi[pl + 1] - sh.g_lo[pl + 1];
+                crp = sh.cnt[pl + 1];
+                alone = pl + 1 + (int)floor(p.alpha * (double)(pl + 1)) >= p.D;
+            }
+        }
+        // a request-side list of one entry is the context's own tail: nothing follows it
+        const uint64_t start_g = __ballot(lane < P && cg > 0 && (alone || cg != cgp));
+        const uint64_t start_r = __ballot(lane < P && cr > 1 && (alone || cr != crp));
+        // run k in queue order: its longest and its shortest pattern length, and from bit 16 on the index
+        const int ng0 = __popcll(start_g);
+        auto behind = [&](uint64_t m) { const uint64_t a = m & ~((2ull << lane) - 1ull); return a ? P - __builtin_ctzll(a) + 1 : 1; };
+        if (lane_in(start_g)) sh.run[__popcll(start_g & lanemask_lt())] = (P - lane) | behind(start_g) << 8;
+        if (lane_in(start_r)) sh.run[ng0 + __popcll(start_r & lanemask_lt())] = (P - lane) | behind(start_r) << 8 | 1 << 16;
+        const uint64_t wide = start_r & ballot64(cr > 64);
+        if (lane == 0) {
+            sh.n_global = ng0;
+            sh.n_runs = ng0 + __popcll(start_r);
+            sh.next = nw;  // (the first run of a wave is that of its own number)
+            sh.wide = wide != 0;
+            sh.start_r = start_r;
         }
     }
-    // a request-side list of one entry is the context's own tail: nothing follows it
-    const uint64_t start_g = __ballot(lane < P && cg > 0 && (alone || cg != cgp));
-    const uint64_t start_r = __ballot(lane < P && cr > 1 && (alone || cr != crp));
-    const int ng = __popcll(start_g), nruns = ng + __popcll(start_r);
+    __syncthreads();
+    const int ng = uni(sh.n_global), nruns = uni(sh.n_runs);
     // A request-side suffix list of more than 64 occurrences is written to the request's row
     // of scratch memory (max_ctx words), which the runs share: going through the runs in queue
     // order, each such run gets the words behind the previous one's, and when the row is full
@@ -2742,11 +2766,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // barrier, so every list of the round before is done with.  One list always fits (it holds
     // at most as many occurrences as the context has tokens); on the workloads at hand all of
     // a request's lists fit together and there is one round.
-    const uint64_t wide_r = start_r & __ballot(lane < P && cr > 64);
+    const bool wide_r = uni(sh.wide) != 0;
     // (round, offset into the row) of the k-th request-side run
     auto place = [&](int kth, int &round, int &off) {
         int rnd = 0, used = 0, o = 0;
-        uint64_t mm = start_r;
+        const int32_t cr = lane < P ? sh.cnt[P - lane] : 0;
+        uint64_t mm = ((uint64_t)(uint32_t)uni((int32_t)(sh.start_r >> 32)) << 32) | (uint32_t)uni((int32_t)sh.start_r);
         for (int k = 0; k <= kth; k++) {
             const int i = __ffsll((unsigned long long)mm) - 1;
             mm &= mm - 1;
@@ -2761,7 +2786,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         off = o;
     };
     int n_rounds = 1, my_round = 0;
-    if (__builtin_expect(wide_r != 0, 0)) {
+    if (__builtin_expect(wide_r, 0)) {
         int off_last;
         place(nruns - ng - 1, n_rounds, off_last);
         n_rounds++;
@@ -2770,7 +2795,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     if (wave == nw - 1) {  // the routes this request takes, into the row of counters (lane k: counter k)
         const int add = lane == SD_CTR_GLOBAL_LIST ? (listed && two)
                         : lane == SD_CTR_GLOBAL_SEARCH ? (!listed && two)
-                        : lane == SD_CTR_REQUEST_WIDE ? (wide_r != 0)
+                        : lane == SD_CTR_REQUEST_WIDE ? wide_r
                         : lane == SD_CTR_OCC_IN_MEMORY ? (uni(sh.m) > p.occ_cap)
                         : lane == SD_CTR_LIST_ROUNDS ? n_rounds - 1 : 0;
         if (lane < SD_CTR_ACCEPT_REQUESTS) sh.ctr[lane] += (unsigned long long)add;
@@ -2778,33 +2803,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     const uint64_t wg2 = TICKS ? wall_clock64() : 0;
     double best_s = 0.0;
     int best_o = -1, best_n = 0, cur = 0;
-    for (;;) {
-        int g = 0;
-        if (lane == 0) g = atomicAdd(&sh.next, 1);
-        g = uni(g);
-        if (g >= nruns) break;
-        const int src = g >= ng ? 1 : 0;
+    for (int g = wave; g < nruns;) {
+        const int run = uni(sh.run[g]), src = run >> 16, p_hi = run & 255, p_lo = (run >> 8) & 255;
         int usa_off = 0;
         if (__builtin_expect(src && wide_r, 0)) {
             int rnd;
             place(g - ng, rnd, usa_off);
             for (; my_round < rnd; my_round++) __syncthreads();
         }
-        uint64_t m = src ? start_r : start_g;
-        for (int k = src ? g - ng : g; k > 0; k--) m &= m - 1;
-        const int i0 = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        const int i1 = m ? __ffsll((unsigned long long)m) - 1 : P;
-        const int p_lo = P - i1 + 1;
         // No node scores above 1, so a tree of K(p) nodes cannot reach a SCORE above K(p): a run
         // whose longest pattern has fewer nodes to give than the best finished tree already
         // scores can neither win nor tie, whatever the order, and is left out.  (Which runs
         // that hits depends on timing; the result does not.)
+        bool hopeless;
         {
             const double top = uni(__longlong_as_double((long long)sh.top_bits));
-            if (floor(p.alpha * (double)(P - i0)) < top) continue;
+            hopeless = floor(p.alpha * (double)p_hi) < top;
         }
-        for (int pl = P - i0; pl >= p_lo; pl--) {
+        for (int pl = hopeless ? 0 : p_hi; pl >= p_lo; pl--) {
             double total = 0.0;
             bool deepest = false;
             const int n = run_unit<STATS, TICKS>(p, sh, b, t, x, src, pl, usa_off, f, sg, cur ? ttk1 : ttk0,
@@ -2823,6 +2839,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 atomicMax(&sh.top_bits, (unsigned long long)__double_as_longlong(total));
             if (!deepest) break;
         }
+        int next = 0;
+        if (lane == 0) next = atomicAdd(&sh.next, 1);
+        g = uni(next);
     }
     for (; my_round < n_rounds - 1; my_round++) __syncthreads();  // the rounds this wave had no run in
     const uint64_t wg3 = TICKS ? wall_clock64() : 0;
@@ -2841,51 +2860,49 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // to its end costs a register that the expansion needs)
     const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // the winning wave: top SCORE, then the earliest unit in scan order (lane w looks at wave w;
-    // units are distinct, so the second criterion leaves one wave)
-    double ws = 0.0;
-    int wo = -1, ww = -1;
-    {
-        const double s = lane_e < nw ? sh.best_s[lane_e] : 0.0;
-        const int o = lane_e < nw ? sh.best_o[lane_e] : -1;
-        const bool valid = o >= 0;
-        const double sx = wave_max_f64(valid ? s : -__longlong_as_double(0x7ff0000000000000ll));
-        const bool top = valid && s == sx;
-        const uint32_t ox = wave_max_u32(top ? ~(uint32_t)o : 0u);
-        const uint64_t W = __ballot(top && ~(uint32_t)o == ox);
-        if (W) {
-            ww = __ffsll((unsigned long long)W) - 1;
-            ws = sx;
-            wo = (int)~ox;
+    // units are distinct, so the second criterion leaves one wave).  A wave without that score is done.
+    const double ws = uni(__longlong_as_double((long long)sh.top_bits));
+    if (wave == nw - 1 || (best_o >= 0 && best_s == ws) || (wave == 0 && ws == 0.0)) {
+        int wo = -1, ww = -1;
+        {
+            const int o = lane_e < nw ? sh.best_o[lane_e] : -1;
+            uint64_t W = ballot64(o >= 0) & ballot64(sh.best_s[lane_e & 15] == ws);
+            if (W & (W - 1ull)) W &= ballot64((uint32_t)o == reduce_min_u32(lane_in(W) ? (uint32_t)o : ~0u));
+            if (W) {
+                ww = __builtin_ctzll(W);
+                wo = __builtin_amdgcn_readlane(o, ww);
+            }
         }
-    }
-    if (wave == nw - 1 && lane_e < SD_CTR_ACCEPT_REQUESTS) {  // lane k: counter k of the drafting calls
-        const int n = ww < 0 ? 0 : sh.best_n[ww];
-        const bool tree = n > 0;
-        const int add = lane_e == SD_CTR_REQUESTS ? 1 : lane_e == SD_CTR_TREES ? tree : lane_e == SD_CTR_NODES ? n
-                        : lane_e == SD_CTR_MATCH_LEN ? (tree ? wo % p.P + 1 : 0)
-                        : lane_e == SD_CTR_FROM_REQUEST ? (tree && wo >= p.P) : 0;
-        p.counters[(int64_t)b * SD_CTR_STRIDE + lane_e] = sh.ctr[lane_e] + (unsigned long long)add;
-    }
-    if (wave == (ww < 0 ? 0 : ww)) {
-        const int n = ww < 0 ? 0 : best_n;
-        const int kept = cur ^ 1;  // the buffer the wave's best tree was left in
-        const int32_t *btk = kept ? ttk1 : ttk0, *bpr = kept ? tpr1 : tpr0;
-        const double *bsc = kept ? tsc1 : tsc0;
-        const int64_t ob = (int64_t)b * out.max_nodes;
-        for (int i = lane_e; i < out.max_nodes; i += 64) {
-            const bool live = i < n;
-            out.d_tokens[ob + i] = live ? btk[i] : -1;
-            out.d_parents[ob + i] = live ? bpr[i] : -1;
-            out.d_scores[ob + i] = live ? bsc[i] : 0.0;
-            SD_CNT(16);
+        const int wsrc = wo >= p.P ? 1 : 0, wlen = wo - wsrc * p.P + 1;
+        if (wave == nw - 1 && lane_e < SD_CTR_ACCEPT_REQUESTS) {  // lane k: counter k of the drafting calls
+            const int n = ww < 0 ? 0 : sh.best_n[ww];
+            const bool tree = n > 0;
+            const int add = lane_e == SD_CTR_REQUESTS ? 1 : lane_e == SD_CTR_TREES ? tree : lane_e == SD_CTR_NODES ? n
+                            : lane_e == SD_CTR_MATCH_LEN ? (tree ? wlen : 0)
+                            : lane_e == SD_CTR_FROM_REQUEST ? (tree && wsrc) : 0;
+            p.counters[(int64_t)b * SD_CTR_STRIDE + lane_e] = sh.ctr[lane_e] + (unsigned long long)add;
         }
-        if (lane_e == 0) {
-            out.d_n_nodes[b] = n;
-            out.d_tree_score[b] = ww >= 0 ? ws : 0.0;
-            out.d_match_len[b] = ww >= 0 ? wo % p.P + 1 : 0;
-            out.d_source[b] = ww >= 0 ? wo / p.P : -1;
-            if (out.d_use_draft) out.d_use_draft[b] = (ww >= 0 && ws > p.tau) ? 1 : 0;
-            SD_CNT(24);
+        if (wave == (ww < 0 ? 0 : ww)) {
+            const int n = ww < 0 ? 0 : best_n;
+            const int kept = cur ^ 1;  // the buffer the wave's best tree was left in
+            const int32_t *btk = kept ? ttk1 : ttk0, *bpr = kept ? tpr1 : tpr0;
+            const double *bsc = kept ? tsc1 : tsc0;
+            const int64_t ob = (int64_t)b * out.max_nodes;
+            for (int i = lane_e; i < out.max_nodes; i += 64) {
+                const bool live = i < n;
+                out.d_tokens[ob + i] = live ? btk[i] : -1;
+                out.d_parents[ob + i] = live ? bpr[i] : -1;
+                out.d_scores[ob + i] = live ? bsc[i] : 0.0;
+                SD_CNT(16);
+            }
+            if (lane_e == 0) {
+                out.d_n_nodes[b] = n;
+                out.d_tree_score[b] = ww >= 0 ? ws : 0.0;
+                out.d_match_len[b] = ww >= 0 ? wlen : 0;
+                out.d_source[b] = ww >= 0 ? wsrc : -1;
+                if (out.d_use_draft) out.d_use_draft[b] = (ww >= 0 && ws > p.tau) ? 1 : 0;
+                SD_CNT(24);
+            }
         }
     }
     flush_count<STATS>(nb, p.algo_bytes + SD_K_SPECULATE);
