@@ -1753,7 +1753,7 @@ struct Narrow {
 // by element, took 1.1 us for every such node and 0.08 us for every element; a decode step of 256 requests with
 // 10M tokens behind them 24.7 us on average (22.1 so), of 64 with 2.2M 21.1 (18.7), of 512 with 100M 29.6 (25.3).
 template <bool STATS, bool TICKS>
-__device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &sh, Stage &sg,
+__device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, Stage &sg,
                                            const int32_t *__restrict__ text, const Narrow &g, bool windows, int m, int pl, int K,
                                            int n, int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
                                            bool &deepest, uint64_t tick0, uint32_t &tick_root,
@@ -2009,6 +2009,8 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
             }
             if (TICKS) tick_merge += (uint32_t)(wall_clock64() - m0);
         }
+        // (what this tree scores already, no other one has to stay below)
+        if (lane == 0 && n < K) atomicMax(&sh.top_bits, (unsigned long long)__double_as_longlong(tot));
         if (TICKS && tick_root == 0) tick_root = (uint32_t)(wall_clock64() - tick0);
     }
     total = tot;
@@ -2021,7 +2023,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, const WgShared &
 // Returns the number of draft nodes and leaves their SCORE in `total`; `deepest` tells whether
 // a node of depth D (which may have no children) was taken.
 template <bool STATS, bool TICKS>
-__device__ __forceinline__ int run_unit(const SpecParams &p, const WgShared &sh, int b, int t,
+__device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b, int t,
                         const int32_t *__restrict__ x, int src, int pl, int usa_off, Frontier &f, Stage &sg,
                         int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
                         bool &deepest, unsigned &nb) {
@@ -2749,6 +2751,23 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         if (lane_in(start_g)) sh.run[__popcll(start_g & lanemask_lt())] = (P - lane) | behind(start_g) << 8;
         if (lane_in(start_r)) sh.run[ng0 + __popcll(start_r & lanemask_lt())] = (P - lane) | behind(start_r) << 8 | 1 << 16;
         const uint64_t wide = start_r & ballot64(cr > 64);
+        // The longest pattern's suffixes share so many tokens: as many nodes of score 1 its tree will have, and
+        // what cannot reach that SCORE need not be grown (the pattern of one token above all, whose suffixes
+        // are the most and whose tree is the smallest: it ended last in every other decode step).
+        if (listed && start_g) {
+            const int pl = P - __builtin_ctzll(start_g), in_list = lane < sh.g_n2 ? lane : 0;
+            const int32_t shared = sh.gl_shared[in_list];
+            const uint64_t mk = (~0ull >> (64 - uni(sh.g_n2))) & ballot64(sh.gl_L[in_list] >= pl);
+            if (pl >= 2 && mk) {
+                const int i0 = __builtin_ctzll(mk), i1 = 63 - __builtin_clzll(mk);
+                int least = i0 == i1 ? __builtin_amdgcn_readlane(shared, i0) >> 8
+                                     : (int)reduce_min_u32(lane > i0 && lane <= i1 ? (uint32_t)shared & 255u : ~0u);
+                const int k = (int)floor(p.alpha * (double)pl);
+                least = least < k ? least : k;
+                least = least < p.D - pl ? least : p.D - pl;
+                if (lane == 0) sh.top_bits = (unsigned long long)__double_as_longlong((double)least);
+            }
+        }
         if (lane == 0) {
             sh.n_global = ng0;
             sh.n_runs = ng0 + __popcll(start_r);
