@@ -1578,6 +1578,41 @@ def test_nodes_of_up_to_64_suffixes(D, P, alpha, min_score, run, den_mode, linea
         g.close()
 
 
+@pytest.mark.parametrize("lens", [
+    [0, 1, 2, 3, 4, 5, 7, 8, 9], [1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097], [4100, 0, 2050, 1, 4100, 3]])
+def test_contexts_of_all_lengths_take_their_rows(lens):
+    """Contexts whose lengths lie around the pieces in which rows are written (sequences start anywhere, most
+    of them not on 16 bytes), then shorter ones in the same slots, in another order: what was there before must
+    not show.  Tokens outside the vocabulary count as token 0 and are reported."""
+    rng = np.random.default_rng(len(lens) + lens[1])
+    vocab, D, P, B = 40, 20, 8, len(lens)
+    docs = [rng.integers(0, 4, 400).astype(np.int32) for _ in range(3)]
+    tg = oracle.Trie(D)
+    for d in docs:
+        tg.add_doc(d)
+    g = parity.GpuPath(vocab, D, P, 2.0, 0.05, B, max(lens) + 3, 2000)
+    try:
+        g.build_global(docs)
+        for order, some in (([*range(B)], lens), (list(rng.permutation(B)), [n // 3 for n in lens]), (list(rng.permutation(B)), lens)):
+            ctxs = [rng.integers(0, 40 if b % 2 else 4, n).astype(np.int32) for b, n in enumerate(some)]
+            g.build_requests(order, ctxs)
+            got = g.speculate(order)
+            want = parity.oracle_speculate_batch(tg, ctxs, D, P, 2.0, 0.05, g.max_nodes)
+            bad = parity.compare_trees(got, want, "lengths %s" % some)
+            assert not bad, "\n".join(bad)
+        assert g.stats()["err_bad_token"] == 0
+        ctxs = [np.where(rng.random(len(c)) < 0.2, rng.choice([-1, vocab, 2 ** 31 - 1], len(c)), c).astype(np.int32) for c in ctxs]
+        g.build_requests(range(B), ctxs)
+        got = g.speculate(range(B))
+        ctxs = [np.where((c < 0) | (c >= vocab), 0, c).astype(np.int32) for c in ctxs]
+        bad = parity.compare_trees(got, parity.oracle_speculate_batch(tg, ctxs, D, P, 2.0, 0.05, g.max_nodes), "bad tokens")
+        assert not bad, "\n".join(bad)
+        if max(lens) > 100:
+            assert g.stats()["err_bad_token"] == 1
+    finally:
+        g.close()
+
+
 def test_calls_take_what_is_right_and_say_what_is_not():
     """The calls of a decode step marshal plain arguments in native code and leave the rest to Python: both
     ways give the same drafts, acceptance and contexts (a subclass of Trees, subclasses of torch.Tensor and
