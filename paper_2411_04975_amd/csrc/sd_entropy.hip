@@ -28,38 +28,39 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// wsum += min(D, tokens from text position p up to its end marker) over all positions.  A wave takes
-// 64 neighbouring positions and reads the text behind them 64 tokens at a time: one ballot per
-// chunk marks the end markers, and every lane looks up the first one at or behind its own
-// position.  The text carries SD_TEXT_PAD >= 64 + D end markers behind position N - 1, so the
-// chunks a wave may touch (up to position base + 63 + D) exist.  A fixed number of workgroups
-// strides over the text: the total is a single address.
-__global__ __launch_bounds__(TB) void k_len_sum(const int32_t *__restrict__ text, int64_t N, int32_t D,
-                                                unsigned long long *wsum) {
-    const int lane = threadIdx.x & 63;
-    unsigned long long w = 0;
-    for (int64_t base = (int64_t)blockIdx.x * TB + (threadIdx.x - lane); base < N; base += (int64_t)gridDim.x * TB) {
-        int k = -1;  // distance to the first end marker, once known
-        for (int c = 0; c * 64 < 64 + D; c++) {
-            const unsigned long long m = __ballot(text[base + c * 64 + lane] < 0);
-            if (k < 0) {
-                // markers of chunk c at or behind this lane's position
-                const unsigned long long mm = c == 0 ? (m >> lane) << lane : m;
-                if (mm) k = c * 64 + __builtin_ctzll(mm) - lane;
+// *lost += what the last tokens of the documents lack: the sum of min(D, tokens left) over the positions is D for
+// every token, but for the k-th last one of a document, k < D, which has k, so a document of n tokens lacks
+// m D - m (m + 1) / 2 with m = min(n, D).  The end markers are the first entries of the suffix array (code 0 is the
+// lowest): a wave takes one and looks for the marker before it, 64 tokens at a time.  (Reading the text
+// behind every position instead: 40 us of the 10M index, 6 so.)
+constexpr int SHORT_TB = 1024;
+constexpr unsigned SHORT_BLOCKS = 256;  // (an addition to one address each, at some 12 ns)
+__global__ __launch_bounds__(SHORT_TB) void k_short_ends(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
+                                                   const int32_t *__restrict__ bucket, int32_t D,
+                                                   unsigned long long *lost) {
+    const int lane = threadIdx.x & 63, waves = SHORT_TB / 64;
+    const int64_t markers = bucket[1];
+    unsigned long long sum = 0;  // (the same in all lanes)
+    for (int64_t i = (int64_t)blockIdx.x * waves + (threadIdx.x >> 6); i < markers; i += (int64_t)gridDim.x * waves) {
+        const int64_t e = sa[i];
+        int m = D;
+        for (int k = 0; k < D; k += 64) {
+            const int64_t p = e - 1 - k - lane;
+            const unsigned long long b = __ballot(p < 0 || text[p < 0 ? 0 : p] < 0);
+            if (b) {
+                m = k + __builtin_ctzll(b);
+                break;
             }
-            if (__all(k >= 0 || (c + 1) * 64 - lane > D)) break;
         }
-        if (k < 0 || k > D) k = D;
-        if (base + lane < N) w += (unsigned long long)k;
+        if (m > D) m = D;
+        sum += (unsigned long long)m * D - (unsigned long long)m * (m + 1) / 2;
     }
-    const double wd = wave_sum((double)w);  // far below 2^53: exact
-    __shared__ double part[TB / 64];
-    if (lane == 0) part[threadIdx.x >> 6] = wd;
+    __shared__ unsigned long long part[SHORT_TB / 64];
+    if (lane == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < TB / 64; q++) t += part[q];
-        if (t != 0.0) atomicAdd(wsum, (unsigned long long)t);
+        for (int q = 1; q < waves; q++) sum += part[q];
+        if (sum) atomicAdd(lost, sum);
     }
 }
 
@@ -110,89 +111,123 @@ __global__ __launch_bounds__(TB) void k_lcp_len(const int32_t *__restrict__ text
     }
 }
 
-// first index j' in [j, lim] with j' == lim or lcp[j'] < d; lcp is 16-byte aligned and the walk
-// takes 16 entries per load once j is
-__device__ __forceinline__ int64_t run_end(const uint8_t *__restrict__ lcp, int64_t j, int64_t lim,
-                                           int d) {
-    while (j < lim && (j & 15)) {
-        if (lcp[j] < d) return j;
-        j++;
-    }
-    while (j + 16 <= lim) {
-        const uint4 x = *reinterpret_cast<const uint4 *>(lcp + j);
+// first index j' in [j, lim] with j' == lim or entry j' below d, of an array given as blocks of 16 entries
+template <typename INT>
+__device__ __forceinline__ INT run_end(const uint4 *__restrict__ blocks, INT j, INT lim, int d) {
+    for (INT at = j & ~(INT)15; at < lim; at += 16) {
+        const uint4 x = blocks[at >> 4];
         const uint32_t wds[4] = {x.x, x.y, x.z, x.w};
         uint32_t m = 0;
 #pragma unroll
         for (int q = 0; q < 16; q++)
             m |= (uint32_t)((int)((wds[q >> 2] >> (8 * (q & 3))) & 255u) < d) << q;
-        if (m) return j + __builtin_ctz(m);
-        j += 16;
-    }
-    while (j < lim) {
-        if (lcp[j] < d) return j;
-        j++;
+        if (at < j) m &= ~0u << (int)(j - at);
+        if (m) {
+            const INT to = at + (INT)__builtin_ctz(m);
+            return to < lim ? to : lim;
+        }
     }
     return lim;
 }
 
 // acc[0] += sum of S log2 S, acc[1] += sum of COUNT log2 COUNT (runs of two or more)
-__global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text,
+// Bound: divergent walks.  A workgroup has the common prefixes of its ENT_TILE entries and of ENT_HALO behind them
+// in LDS, where nearly every run ends, lists the ones that open a run, so that all lanes walk, and has c log2 c of
+// small c in a table (most runs are copies of one stretch).  10M entries copied from templates: 116 us; 246 with an
+// entry per lane, the array in memory and the ends of runs of depth 2 looked for in their first token's bucket.
+constexpr int ENT_TB = 1024, ENT_TILE = 4096, ENT_HALO = 512, ENT_LOGS = 256;
+constexpr unsigned ENT_BLOCKS = 512;
+
+__global__ __launch_bounds__(ENT_TB) __attribute__((amdgpu_waves_per_eu(8))) void k_entropy(const int32_t *__restrict__ text,
                                                 const int32_t *__restrict__ sa,
                                                 const int32_t *__restrict__ tok1,
                                                 const int32_t *__restrict__ bucket,
                                                 const uint8_t *__restrict__ lcp,
                                                 const uint8_t *__restrict__ len, int64_t N, int32_t D,
                                                 double *acc) {
+    __shared__ uint4 s_lcp[(ENT_TILE + ENT_HALO) / 16];
+    __shared__ double s_log[ENT_LOGS];
+    __shared__ uint16_t s_open[ENT_TILE];  // entries of the tile that open a run
+    __shared__ int32_t s_n;
+    for (int c = threadIdx.x; c < ENT_LOGS; c += ENT_TB) s_log[c] = c > 1 ? (double)c * log2((double)c) : 0.0;
+    const uint8_t *const near = reinterpret_cast<const uint8_t *>(s_lcp);
+    auto times_log = [&](int32_t c) { return c < ENT_LOGS ? s_log[c] : (double)c * log2((double)c); };
     double sS = 0.0, sC = 0.0;
     // a fixed number of workgroups strides over the entries: the two totals are single
     // addresses, and one atomic per wave of a grid as long as the array would queue up on them
-    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < N; i += (int64_t)gridDim.x * TB) {
-        const int lo = lcp[i], hi = i + 1 < N ? lcp[i + 1] : 0;
-        if (hi > lo) {
+    for (int64_t base = (int64_t)blockIdx.x * ENT_TILE; base < N; base += (int64_t)gridDim.x * ENT_TILE) {
+        __syncthreads();
+        if (threadIdx.x == 0) s_n = 0;
+        for (int q = threadIdx.x; q < (ENT_TILE + ENT_HALO) / 16; q += ENT_TB)  // (the array goes on for a while behind its last entry)
+            s_lcp[q] = base + 16 * q < N ? *reinterpret_cast<const uint4 *>(lcp + base + 16 * q) : make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        // (an index has fewer than 2^31 entries)
+        const int32_t first_at = (int32_t)base, n_all = (int32_t)N;
+        const int32_t held = base + ENT_TILE + ENT_HALO < N ? first_at + ENT_TILE + ENT_HALO : n_all;  // entries below are at hand
+        for (int k = 0; k < ENT_TILE / ENT_TB; k++) {
+            const int at = k * ENT_TB + (int)threadIdx.x, lane = threadIdx.x & 63;
+            const bool opens = base + at + 1 < N && near[at + 1] > near[at];
+            const unsigned long long b = __ballot(opens);
+            int first = 0;
+            if (lane == 0 && b) first = atomicAdd(&s_n, __popcll(b));
+            first = __shfl(first, 0);
+            if (opens) s_open[first + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)at;
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < s_n; q += ENT_TB) {
+            const int at = s_open[q], lo = near[at], hi = near[at + 1];
+            const int32_t i = first_at + at;
             const int Li = len[i];
-            int64_t j = i + 1;
+            int32_t j = i + 1;
             int d = hi;
             while (d > lo) {
-                // (few runs are that shallow, and finding the bucket is a gather)
-                const int64_t bend = d <= 2 ? bucket[text[sa[i]] + 2] : N;
-                if (d == 1) {
-                    j = bend;  // a run of depth 1 is the whole bucket of its first token
-                } else if (d == 2) {
-                    // second tokens rise along the bucket: the run ends where they pass tok1[i]
-                    const int32_t t1 = tok1[i];
-                    int64_t a = j, b = bend;
-                    while (a < b) {
-                        const int64_t m = (a + b) >> 1;
-                        if (tok1[m] <= t1) a = m + 1; else b = m;
+                if (j < held) {
+                    int n = j - first_at;
+                    const int n_held = held - first_at;
+                    for (int q = 0; q < 4 && n < n_held && near[n] >= d; q++) n++;
+                    if (n < n_held && near[n] >= d) n = run_end(s_lcp, n, n_held, d);
+                    j = first_at + n;
+                }
+                if (j >= held && j < n_all) {  // it goes on behind what is at hand
+                    if (d > 2) {
+                        j = (int32_t)run_end(reinterpret_cast<const uint4 *>(lcp), (uint32_t)j, (uint32_t)n_all, d);
+                    } else {
+                        // a run of depth 1 is the whole bucket of its first token; along it second tokens
+                        // rise, so one of depth 2 ends where they pass tok1[i]
+                        const int32_t bend = bucket[text[sa[i]] + 2];
+                        const int32_t t1 = tok1[i];
+                        int32_t from = j, to = bend;
+                        while (d == 2 && from < to) {
+                            const int32_t m = from + ((to - from) >> 1);
+                            if (tok1[m] <= t1) from = m + 1; else to = m;
+                        }
+                        j = d == 2 ? from : bend;
                     }
-                    j = a;
-                } else {
-                    j = run_end(lcp, j, bend, d);
                 }
                 // the run [i, j) is the same node chain for every depth above lcp[j]
-                const int below = j < N ? (int)lcp[j] : 0;
+                const int below = j < held ? (int)near[j - first_at] : j < n_all ? (int)lcp[j] : 0;
                 const int dn = below > lo ? below : lo;
                 const int span = d - dn;
-                const int64_t c = j - i;
-                const double tc = (double)c * log2((double)c);
+                const int32_t c = j - i;
+                const double tc = times_log(c);
                 sC += (double)span * tc;
                 // S = c at every depth below D, except where suffixes of the run stop: they
                 // sit first in it, so only at depth len[i], which can only be the top one
                 int plain = span - (d == D ? 1 : 0);
                 if (d == hi && Li == d && d < D) {
                     plain--;
-                    int64_t good = 0, step = 1;  // len[i + good] == d
-                    while (good + step < c && len[i + good + step] == d) {
+                    int32_t good = 0, step = 1;  // len[i + good] == d
+                    while (step < c - good && len[i + good + step] == d) {
                         good += step;
                         step <<= 1;
                     }
-                    int64_t bad = good + step < c ? good + step : c;  // c, or len[i + bad] != d
+                    int32_t bad = step < c - good ? good + step : c;  // c, or len[i + bad] != d
                     while (bad - good > 1) {
-                        const int64_t m = (good + bad) >> 1;
+                        const int32_t m = good + ((bad - good) >> 1);
                         if (len[i + m] == d) good = m; else bad = m;
                     }
-                    const int64_t S = c - bad;
-                    if (S >= 2) sS += (double)S * log2((double)S);
+                    const int32_t S = c - bad;
+                    if (S >= 2) sS += times_log(S);
                 }
                 sS += (double)plain * tc;
                 d = dn;
@@ -201,7 +236,7 @@ __global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text
     }
     sS = wave_sum(sS);
     sC = wave_sum(sC);
-    __shared__ double part[2][TB / 64];
+    __shared__ double part[2][ENT_TB / 64];
     if ((threadIdx.x & 63) == 0) {
         part[0][threadIdx.x >> 6] = sS;
         part[1][threadIdx.x >> 6] = sC;
@@ -209,7 +244,7 @@ __global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text
     __syncthreads();
     if (threadIdx.x == 0) {
         sS = sC = 0.0;
-        for (int q = 0; q < TB / 64; q++) {
+        for (int q = 0; q < ENT_TB / 64; q++) {
             sS += part[0][q];
             sC += part[1][q];
         }
@@ -218,24 +253,24 @@ __global__ __launch_bounds__(TB) void k_entropy(const int32_t *__restrict__ text
     }
 }
 
-inline unsigned nblk(int64_t n) { return (unsigned)((n + TB - 1) / TB); }
-
 }  // namespace
 
 sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipStream_t st) {
     const int64_t N = c->g_N;
     double acc[2] = {0.0, 0.0};
-    unsigned long long wsum = 0;
+    unsigned long long lost = 0;
     if (N > 0) {
         // N <= g_cap bytes each, in two build buffers (16-byte aligned)
         uint8_t *lcp = reinterpret_cast<uint8_t *>(c->b_flags), *len = reinterpret_cast<uint8_t *>(c->b_gid2);
         sd_fill_i32(reinterpret_cast<int32_t *>(c->d_entropy), 6, 0, st);
-        hipLaunchKernelGGL(k_len_sum, dim3(nblk(N) < 2048u ? nblk(N) : 2048u), dim3(TB), 0, st, c->g_text, N, c->cfg.D,
-                           reinterpret_cast<unsigned long long *>(c->d_entropy + 2));
+        const unsigned ends = (unsigned)((c->g_docs + SHORT_TB / 64 - 1) / (SHORT_TB / 64));
+        hipLaunchKernelGGL(k_short_ends, dim3(ends < 1u ? 1u : ends < SHORT_BLOCKS ? ends : SHORT_BLOCKS), dim3(SHORT_TB), 0, st, c->g_text, c->g_sa,
+                           c->g_bucket, c->cfg.D, reinterpret_cast<unsigned long long *>(c->d_entropy + 2));
         const int64_t per_block = TB / 64 * LCP_OUT;
         hipLaunchKernelGGL(k_lcp_len, dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st, c->g_text, c->g_sa, N,
                            c->cfg.D, lcp, len);
-        hipLaunchKernelGGL(k_entropy, dim3(nblk(N) < 4096u ? nblk(N) : 4096u), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
+        const unsigned tiles = (unsigned)((N + ENT_TILE - 1) / ENT_TILE);
+        hipLaunchKernelGGL(k_entropy, dim3(tiles < ENT_BLOCKS ? tiles : ENT_BLOCKS), dim3(ENT_TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
                            c->g_bucket, lcp, len, N, c->cfg.D, c->d_entropy);
         if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;
         double host[3];
@@ -244,12 +279,12 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
             return SD_ERR_HIP;
         acc[0] = host[0];
         acc[1] = host[1];
-        memcpy(&wsum, &host[2], sizeof(wsum));
+        memcpy(&lost, &host[2], sizeof(lost));
     }
     // the root: every token of the corpus is one observation of "what comes first"
     const double n = (double)c->g_tokens;
     const double root = n >= 2.0 ? n * log2(n) : 0.0;
-    const double weight = (double)wsum;
+    const double weight = (double)((unsigned long long)c->g_tokens * (unsigned long long)c->cfg.D - lost);
     *h_weight = weight;
     *h_mean_bits = weight > 0.0 ? (acc[0] + root - acc[1]) / weight : 0.0;
     return SD_OK;

@@ -869,6 +869,30 @@ def test_entropy_matches_oracle(case, tiny_workload):
     assert h2 == pytest.approx(ho, rel=ENTROPY_RTOL, abs=ENTROPY_ATOL)
 
 
+@pytest.mark.parametrize("n", [1, 511, 512, 1365, 4094, 4096, 4600, 9001])
+@pytest.mark.parametrize("D", [3, 64, 200])
+def test_entropy_runs_around_tiles(n, D):
+    """Runs of n suffixes at depths 1 to 3, which end inside a workgroup's tile of 4096 entries, in what it has
+    behind that, and beyond, among documents whose lengths lie around D and around 64."""
+    docs = [np.array([3, 4, 5], np.int32)] * n + [np.array([3, 4], np.int32)] * (n // 3)
+    docs += [np.arange(k, dtype=np.int32) % 7 + 10 for k in (0, 1, D - 1, D, D + 1, 63, 64, 65, 128, 129)]
+    docs = docs[-3:] + docs[:-3]
+    N = sum(len(d) for d in docs) + len(docs)
+    g = parity.GpuPath(40, D, 2, 1.0, 0.1, 1, 16, N)
+    try:
+        g.build_global(docs)
+        h, wt = g.entropy()
+    finally:
+        g.close()
+    t = oracle.Trie(D)
+    for d in docs:
+        if len(d):
+            t.add_doc(d)
+    want_h, want_w = t.entropy()
+    assert wt == want_w
+    assert abs(h - want_h) <= 1e-9 * max(abs(want_h), 1e-3), (h, want_h)
+
+
 def test_entropy_fuzz_small_corpora():
     """Seeded corpora of four shapes (random tokens; slices of one text: deep shared prefixes
     and many suffixes that stop together; runs of one token; common endings) over the range of
