@@ -313,53 +313,97 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
     }
     if (!CODES || blockIdx.x >= ntiles) return;
     __syncthreads();
-    uint32_t *row = hist + (int64_t)blockIdx.x * bins, *sum = sums + (int64_t)(blockIdx.x / per_chunk) * bins;
+    uint32_t *row = hist + (int64_t)blockIdx.x * bins, *sum = per_chunk > 0 ? sums + (int64_t)(blockIdx.x / per_chunk) * bins : nullptr;
     for (int i = tid; i < bins; i += CT) {
         const uint32_t v = s_hist[i];
         row[i] = v;
-        if (v) atomicAdd(&sum[i], v);
+        if (v && sum) atomicAdd(&sum[i], v);
     }
 }
 
-// Places instead of counts in the (tile, bin) table.  A workgroup takes a chunk of tiles, a thread
-// one or two bins: what lies before the chunk is known from the chunks' sums.  Workgroup 0 also
-// writes where the bins start.  (The table lies tile by tile: with a row per bin the tiles' stores
-// and loads were 4 bytes to a line, a quarter of the time of the 100M-entry split.)
+// Places instead of counts in the (tile, bin) table.  A workgroup takes a chunk of tiles: what lies before
+// the chunk is known from the chunks' sums.  Workgroup 0 also writes where the bins start.  (The table
+// lies tile by tile: with a row per bin the tiles' stores and loads were 4 bytes to a line, a quarter of the
+// time of the 100M-entry split.)
+// Bound: latency.  A lane takes four bins of every R-th row of the sums, then of its share of the chunk's rows, and
+// LDS brings the shares together (2.2M, 10M, 100M positions: 10.1, 13.0, 58 us with two bins to a lane and all rows
+// one after the other; 4.9, 6.8, 24 so).
 constexpr int MAX_CHUNKS = 256, MIN_PER_CHUNK = 32;
+constexpr int ROW_GROUPS = 32;  // at most
+
+struct row_share { int col, group, groups; };  // four bins of a row, 16 bytes apart; group >= groups: none
+__device__ __forceinline__ row_share share_of_rows(int bins) {
+    const int lanes = bins >> 2, groups = CT / lanes < ROW_GROUPS ? CT / lanes : ROW_GROUPS;
+    return {(int)threadIdx.x & (lanes - 1), (int)threadIdx.x / lanes, groups};
+}
+__device__ __forceinline__ uint4 operator+(uint4 a, uint4 b) { return make_uint4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+__device__ __forceinline__ const uint4 *row_of(const uint32_t *table, int bins, int64_t row) { return reinterpret_cast<const uint4 *>(table + row * bins); }
+
+// From the counts of n rows: to[d] = where the entries of bin d and row `at` start; `starts`, if given: where the
+// bin does.  Whole workgroup; area: 2 * CT uint4 of LDS, free again after the next barrier.
+__device__ __forceinline__ void bin_starts(const uint32_t *__restrict__ table, int bins, int n, int at, uint4 *area,
+                                           uint32_t *s_wave, uint32_t *to, uint32_t *__restrict__ starts) {
+    const row_share r = share_of_rows(bins);
+    uint4 all = make_uint4(0u, 0u, 0u, 0u), before = all;
+    if (r.group < r.groups) {
+#pragma unroll 8
+        for (int i = r.group; i < n; i += r.groups) {
+            const uint4 v = row_of(table, bins, i)[r.col];
+            all = all + v;
+            if (i < at) before = before + v;
+        }
+    }
+    area[threadIdx.x] = all;
+    area[CT + threadIdx.x] = before;
+    __syncthreads();
+    const uint2 *half = reinterpret_cast<const uint2 *>(area);
+    const int pairs = bins >> 1;
+    uint32_t tot;
+    uint2 a = make_uint2(0u, 0u), b = a;
+    if ((int)threadIdx.x < pairs)
+        for (int g = 0; g < r.groups; g++) {
+            const uint2 va = half[g * pairs + threadIdx.x], vb = half[2 * CT + g * pairs + threadIdx.x];
+            a = make_uint2(a.x + va.x, a.y + va.y);
+            b = make_uint2(b.x + vb.x, b.y + vb.y);
+        }
+    const uint32_t start = block_excl_scan(a.x + a.y, s_wave, &tot);
+    if ((int)threadIdx.x < pairs) {
+        const int d = 2 * (int)threadIdx.x;
+        to[d] = start + b.x;
+        to[d + 1] = start + a.x + b.y;
+        if (starts) {
+            starts[d] = start;
+            starts[d + 1] = start + a.x;
+        }
+    }
+}
 
 __global__ __launch_bounds__(CT) void k_code_places(uint32_t *__restrict__ hist, int bins, int64_t ntiles,
                                                     int per_chunk, const uint32_t *__restrict__ sums,
                                                     int chunks, uint32_t *__restrict__ starts, uint32_t N) {
+    __shared__ uint4 s_area[2 * CT];
+    __shared__ uint4 s_to[MAX_BINS / 4];
     __shared__ uint32_t s_wave[CW];
-    uint32_t before[2] = {0, 0}, all[2] = {0, 0};
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-        const int d = 2 * (int)threadIdx.x + q;
-        if (d >= bins) continue;
-#pragma unroll 8
-        for (int i = 0; i < chunks; i++) {
-            const uint32_t v = sums[(int64_t)i * bins + d];
-            all[q] += v;
-            before[q] += i < (int)blockIdx.x ? v : 0u;
-        }
-    }
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan(all[0] + all[1], s_wave, &tot);
     const int64_t t0 = (int64_t)blockIdx.x * per_chunk;
     const int n = (int)(ntiles - t0 < per_chunk ? ntiles - t0 : per_chunk);
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-        const int d = 2 * (int)threadIdx.x + q;
-        if (d >= bins) continue;
-        const uint32_t start = ex + (q ? all[0] : 0u);
-        if (blockIdx.x == 0) starts[d] = start;
-        uint32_t at = start + before[q];
-        uint32_t *col = hist + t0 * bins + d;
+    const row_share r = share_of_rows(bins);
+    const int per = (n + r.groups - 1) / r.groups, i0 = r.group * per, i1 = r.group < r.groups ? (i0 + per < n ? i0 + per : n) : i0;
+    uint4 sum = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll 8
-        for (int i = 0; i < n; i++) {
-            const uint32_t v = col[(int64_t)i * bins];
-            col[(int64_t)i * bins] = at;
-            at += v;
+    for (int i = i0; i < i1; i++) sum = sum + row_of(hist, bins, t0 + i)[r.col];
+    bin_starts(sums, bins, chunks, (int)blockIdx.x, s_area, s_wave, reinterpret_cast<uint32_t *>(s_to), blockIdx.x == 0 ? starts : nullptr);
+    __syncthreads();
+    s_area[threadIdx.x] = sum;
+    __syncthreads();
+    if (r.group < r.groups) {
+        uint4 at = s_to[r.col];
+        for (int g = 0; g < r.group; g++) at = at + s_area[g * (bins >> 2) + r.col];
+        uint4 *row = reinterpret_cast<uint4 *>(hist + t0 * bins) + r.col;
+#pragma unroll 8
+        for (int i = i0; i < i1; i++) {
+            const uint4 v = row[(int64_t)i * (bins >> 2)];
+            row[(int64_t)i * (bins >> 2)] = at;
+            at = at + v;
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) starts[bins] = N;
@@ -379,7 +423,7 @@ struct entry_shape {
 // (ITEMS = 12: two workgroups share a compute unit.)
 template <int ITEMS>
 struct split_lds {
-    uint64_t entry[CT * ITEMS];
+    alignas(16) uint64_t entry[CT * ITEMS];
     uint16_t digit[CT * ITEMS];
     uint32_t cnt[MAX_BINS], to[MAX_BINS];
     uint32_t wave[CW];
@@ -423,11 +467,14 @@ __device__ __forceinline__ void split_tile(split_lds<ITEMS> &s, const uint64_t (
 }
 
 // First split: codes in position order -> entries.  Clears the chunks' sums for the next input.
-template <int ITEMS>
+// FEW: a workgroup finds the places of its bins' entries by itself, from the counts of all tiles (that is as
+// much as k_code_places reads for a chunk, and one launch less: 16 tiles, 512 bins: 5.5 + 5.3 us -> 7.2).
+template <int ITEMS, bool FEW>
 __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ keys,
                                                    const int32_t *__restrict__ text, int64_t N, entry_shape f,
                                                    const uint32_t *__restrict__ hist, int chunks,
-                                                   uint32_t *__restrict__ sums, uint64_t *__restrict__ out) {
+                                                   uint32_t *__restrict__ sums, uint32_t *__restrict__ starts,
+                                                   uint64_t *__restrict__ out) {
     __shared__ split_lds<ITEMS> s;
     const int tid = threadIdx.x, bins = 1 << f.bits1;
     const int64_t base = (int64_t)blockIdx.x * (CT * ITEMS);
@@ -443,9 +490,16 @@ __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ 
         const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
         e[k] = (((rest << f.tok_bits) | tok) << f.pos_bits) | (uint64_t)(base + j);
     }
-    for (int i = tid; i < bins; i += CT) {
-        s.to[i] = hist[(int64_t)blockIdx.x * bins + i];
-        if ((int)blockIdx.x < chunks) sums[(int64_t)blockIdx.x * bins + i] = 0;
+    if (FEW) {
+        static_assert(!FEW || sizeof(s.entry) >= 2 * CT * sizeof(uint4), "the counts are brought together there");
+        bin_starts(hist, bins, (int)gridDim.x, (int)blockIdx.x, reinterpret_cast<uint4 *>(s.entry), s.wave, s.to,
+                   blockIdx.x == 0 ? starts : nullptr);
+        if (blockIdx.x == 0 && tid == 0) starts[bins] = (uint32_t)N;
+    } else {
+        for (int i = tid; i < bins; i += CT) {
+            s.to[i] = hist[(int64_t)blockIdx.x * bins + i];
+            if ((int)blockIdx.x < chunks) sums[(int64_t)blockIdx.x * bins + i] = 0;
+        }
     }
     split_tile<ITEMS>(s, e, digit, cnt, bins, out);
 }
@@ -572,7 +626,8 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 //
 // Tokens are compared as two 64-bit words: three of 21 bits each, two of 32 for vocabularies
 // beyond that.
-constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072;
+constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072, SORT_TILE_FEW = 256;
+constexpr int SORT_SLOTS = 1024;  // workgroups that what is less than a round of them is spread over, at most
 constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
 constexpr int SORT_PARTS = 4096;
 constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
@@ -1375,31 +1430,41 @@ __global__ __launch_bounds__(CT) void k_rest_bucket(const rest_range *__restrict
 // workgroup of k_code_sort, whole buckets, is SORT_TILE give or take one of them, and a bucket may
 // be five times as large as the average before it no longer fits.  (Buckets half that size: 100M
 // entries then take a split of 1024 ways, whose runs are 6 entries; 0.83 instead of 0.70 ms.)
-// Up to 10 bits go in one split (three launches).
-// Tiles of 6144 entries leave as runs of 24 entries per bin and more; small inputs take tiles of
-// 2048 so that they are spread over more compute units.
+// Up to 10 bits go in one split (three launches), which is then as fine as that allows, down to
+// buckets of 32 to 64: the shares can be as small.
+// Tiles of 6144 entries leave as runs of 24 entries per bin and more; inputs up to SMALL_MAX take tiles of
+// 2048, which are spread over more compute units (2.2M and 3.9M, layout and split: 22 + 13 and 30 + 22 us in tiles
+// of 6144; 20 + 13 and 28 + 17 so.  10M: 71 + 49, 71 + 51).
+constexpr int64_t SMALL_MAX = 4 << 20;
 struct split_plan {
     int bits1, bits2;
     bool small_tiles;
 };
 split_plan plan_for(int64_t N) {
-    int bits = 1;
+    int bits = 2;  // (four bins to a lane)
+    while (bits < MAX_BITS && (N >> bits) > 64) bits++;
     while (bits < 2 * MAX_BITS && (N >> bits) > 512) bits++;
     split_plan p;
     p.bits1 = bits;
     p.bits2 = 0;
     if (bits > MAX_BITS) { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
-    p.small_tiles = N <= (1 << 20);
+    p.small_tiles = N <= SMALL_MAX;
     return p;
 }
 // Entries per workgroup of k_code_sort, three of which fit a compute unit: as many whole rounds of
-// workgroups as N makes at SORT_TILE_MIN, rounded down (2.2M entries: one round instead of 1.4).
+// workgroups as N makes at SORT_TILE_MIN, rounded down (2.2M entries: one round instead of 1.4).  What is
+// less than a round is spread over all of it, down to SORT_TILE_FEW entries, 32 to a wave, or two buckets
+// (32k, 100k and 300k entries: 28.4, 24.8 and 28.4 us in tiles of 2048 and buckets of 256 to 512; 13.8, 15.6 and 20.8 so).
 int sort_tile_for(int64_t N, int n_cu) {
-    const int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
+    int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
+    if (slots > SORT_SLOTS) slots = SORT_SLOTS;
     int64_t rounds = N / (slots * SORT_TILE_MIN);
     if (rounds < 1) rounds = 1;
-    const int64_t t = (N + rounds * slots - 1) / (rounds * slots);
-    return (int)(t < SORT_TILE_MIN ? SORT_TILE_MIN : t > SORT_TILE_MAX ? SORT_TILE_MAX : t);
+    int64_t t = (N + rounds * slots - 1) / (rounds * slots);
+    const split_plan p = plan_for(N);
+    const int64_t least = 2 * (N >> (p.bits1 + p.bits2));
+    if (t < least) t = least;
+    return (int)(t < SORT_TILE_FEW ? SORT_TILE_FEW : t > SORT_TILE_MAX ? SORT_TILE_MAX : t);
 }
 constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 
@@ -1410,7 +1475,7 @@ constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
                   int64_t *range_words, int64_t *rest_words) {
     int64_t h = 0, s = 0;
-    const int64_t sizes[] = {cap, 1 << 20, (int64_t)512 << MAX_BITS};
+    const int64_t sizes[] = {cap, SMALL_MAX, ((int64_t)513 << MAX_BITS) - 1};  // (the most of one split)
     for (int64_t n : sizes) {
         if (n > cap) n = cap;
         const split_plan p = plan_for(n);
@@ -1424,7 +1489,10 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *hist_words = h + MAX_BINS + 1;
     *start_words = s;
     *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
-    *range_words = (cap / SORT_TILE_MIN + 2) * (int64_t)((2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
+    // (up to SORT_SLOTS tiles are as small as SORT_TILE_FEW, more are SORT_TILE_MIN and larger)
+    int64_t tiles = cap / SORT_TILE_FEW < SORT_SLOTS ? cap / SORT_TILE_FEW : SORT_SLOTS;
+    if (tiles < cap / SORT_TILE_MIN) tiles = cap / SORT_TILE_MIN;
+    *range_words = (tiles + 2) * (int64_t)((2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
     *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
 
@@ -1529,14 +1597,16 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     int per_chunk = (int)((ntiles + MAX_CHUNKS - 1) / MAX_CHUNKS);
     if (per_chunk < MIN_PER_CHUNK) per_chunk = MIN_PER_CHUNK;
     const int chunks = (int)((ntiles + per_chunk - 1) / per_chunk);
+    const bool few = p.small_tiles && p.bits2 == 0 && chunks == 1;
     const dim3 grid1((unsigned)ntiles), block(CT);
     SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_layout<SMALL_ITEMS, true> : k_layout<LARGE_ITEMS, true>),
               layout_grid(N, p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS), block, 0, tokens, offs, n_seq, n_tokens, text,
-              c->cfg.vocab, c->d_err, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles, per_chunk, c->code_sums);
-    SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
+              c->cfg.vocab, c->d_err, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles, few ? 0 : per_chunk, c->code_sums);
+    if (!few)
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
               c->code_sums, chunks, starts1, (uint32_t)N);
-    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (p.small_tiles ? k_code_split<SMALL_ITEMS> : k_code_split<LARGE_ITEMS>),
-              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, ent1);
+    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (few ? k_code_split<SMALL_ITEMS, true> : p.small_tiles ? k_code_split<SMALL_ITEMS, false> : k_code_split<LARGE_ITEMS, false>),
+              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, starts1, ent1);
     if (p.bits2) {
         const dim3 grid2((unsigned)(N / SPLIT2_TILE + bins1));
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;

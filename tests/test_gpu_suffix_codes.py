@@ -104,6 +104,24 @@ def test_insert_places(n_old, n_new, spread):
         g.close()
 
 
+@pytest.mark.parametrize("n", [100, 255, 257, 4095, 16_385, 65_535, 65_536, 65_537, 262_145, 4_194_304, 4_194_305])
+def test_small_shares(n):
+    """Around the sizes where tiles, bins and the workgroups' shares change: 33 tiles need places of their own,
+    buckets are as fine as a split of 1024 ways makes them, tiles of 2048 positions end at 2^22; more documents
+    in the first tiles than the layout keeps the starts of."""
+    rng = np.random.default_rng(n)
+    D = 12
+    short = [rng.integers(0, 900, int(rng.integers(0, 2))).astype(np.int32) for _ in range(min(n // 8, 9000))]
+    body = n - sum(len(d) + 1 for d in short) - 1
+    docs = short + [_text(rng, body, 900, 4)]
+    g = parity.GpuPath(900, D, 8, 1.0, 0.1, 1, 16, n)
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [8, 9, 4095, 4096, 4097, 30_000])
 def test_insert_into_a_wide_bucket(n):
     """The ranking probes up to 8, up to 4096 and more suffixes of one first token in different ways: new
@@ -326,7 +344,7 @@ def test_repeated_text_costs_no_more_than_doubling(times):
 @pytest.mark.parametrize("captured", [False, True])
 def test_more_documents_than_the_layout_keeps(n_docs, body, captured):
     """Runs of empty documents and of documents of one token: more of them in a tile of positions (2048,
-    6144 above 2^20) than k_layout keeps the starts of (1024), in front of, between and behind
+    6144 above 2^22) than k_layout keeps the starts of (1024), in front of, between and behind
     ordinary documents; laid out with codes and, under capture, without."""
     import torch
     import paper_2411_04975_amd as sd
