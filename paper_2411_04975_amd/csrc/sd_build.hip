@@ -202,74 +202,125 @@ __global__ __launch_bounds__(TB) void k_bucket(const int32_t *__restrict__ text,
 typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // rank[j] = number of old suffixes that sort before, or tie with, new suffix j.
-// Bound: dependent loads (suffix array, then text), so RANK_LANES lanes look for a suffix's place side
-// by side, each at a suffix of its own: a bucket of 17 takes two rounds instead of five, and its
-// tokens come eight at a time (32k new suffixes into 2.2M: 39 -> 20 us).
+// Bound: dependent loads (suffix array, then text) and the lines that they take.  Among up to RANK_ALONE old suffixes
+// RANK_PROBES are looked at side by side, each by four lanes: a load of theirs is 16 neighbouring tokens.  The first
+// one decides most; further ones take RANK_MORE times as many, since the kernel waits for the few that agree on many
+// tokens, and what the place's neighbours on both sides share with the new suffix is not looked at again.  Among more, a
+// lane takes a probe: a range falls to a ninth in two loads.  Before that, second tokens narrow what is more than
+// RANK_COLUMN, with one load a round and no text.
+// (32k new suffixes into 2.2M and 9M of copied text, 9M of a Zipf law, and 200k into 300k, us: a lane to a probe, 8 probes,
+// 8 tokens a load 19.9, 29.7, 17.5, 39.3; so 13.0, 15.0, 16.4, 29.1.  4 probes of four lanes 15.8, 19.4, 19.8, 8 of them 18.8,
+// 23.7, 26.9; without the second tokens 13.7, 18.8, 16.5, 28.6.)
 // A workgroup strides over the new suffixes: a grid of RANK_LANES lanes for each of them would pass
 // the 2^32 threads of a launch at 2^29 suffixes.  RANK_BLOCKS is 32 rounds of what the chip holds.
-constexpr int RANK_LANES = 8;
+constexpr int RANK_PROBES = 2, RANK_LANES = 4 * RANK_PROBES;
+constexpr int RANK_MORE = 2;
 constexpr unsigned RANK_BLOCKS = 1u << 16;
 constexpr uint32_t RANK_WIDE = 4096;
+constexpr int64_t RANK_COLUMN = 64;
+constexpr uint32_t RANK_ALONE = 256;  // (64: 16.8 instead of 15.0 for the 9M of copied text; 1024: as 256)
+
+// Compares `loads` times the tokens that the lanes of a probe take in one, 4 each, of v and w from k on.  The place of
+// the first that differ or end a document, times four, and 0: v is lower, 1: both end, 2: v is higher; NO_DIFF if
+// there is none below D.
+constexpr int NO_DIFF = 0x7fffffff;
+template <int LOADS>
+__device__ __forceinline__ int first_diff(const int32_t *__restrict__ v, const int32_t *__restrict__ w, int k, int32_t D, bool alone) {
+    // (what lies behind a suffix's end marker is text or padding and is not looked at)
+    const int step = alone ? 4 : 16, part = k + (alone ? 0 : 4 * (int)(threadIdx.x & 3));
+    tok4 x[LOADS], y[LOADS];
+#pragma unroll
+    for (int q = 0; q < LOADS; q++) {
+        x[q] = *reinterpret_cast<const tok4 *>(v + part + step * q);
+        y[q] = *reinterpret_cast<const tok4 *>(w + part + step * q);
+    }
+    int at = NO_DIFF;
+#pragma unroll
+    for (int q = LOADS - 1; q >= 0; q--)
+#pragma unroll
+        for (int i = 3; i >= 0; i--) {
+            const int32_t a = x[q][i], b = y[q][i];
+            if (a != b || a == SD_END_TOKEN) at = 4 * (part + step * q + i) + (a < b ? 0 : a == b ? 1 : 2);
+        }
+    at = at < 4 * D ? at : NO_DIFF;
+    if (alone) return at;
+    at = min(at, __shfl_xor(at, 1));
+    return min(at, __shfl_xor(at, 2));
+}
 
 __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ text,
-                                                    const int32_t *__restrict__ sa, int64_t N,
+                                                    const int32_t *__restrict__ sa,
+                                                    const int32_t *__restrict__ tok1,
                                                     const int32_t *__restrict__ bucket,
                                                     const uint32_t *__restrict__ dsa, int64_t M,
                                                     int64_t base, int32_t D,
                                                     uint32_t *__restrict__ rank) {
-    const int g = threadIdx.x & (RANK_LANES - 1), first = (threadIdx.x & 63) - g;
+    const int lane = threadIdx.x & 63, first = lane & ~(RANK_LANES - 1);
     constexpr int PER_BLOCK = TB / RANK_LANES;
     for (int64_t j0 = (int64_t)blockIdx.x * PER_BLOCK; j0 < M; j0 += (int64_t)gridDim.x * PER_BLOCK) {
         const int64_t j = j0 + threadIdx.x / RANK_LANES;
         const int32_t *w = text + base + (j < M ? dsa[j] : 0);
         const int32_t c0 = w[0] + 1;  // token code, 0 for the end marker
         int64_t lo = bucket[c0], hi = j < M ? bucket[c0 + 1] : lo;  // old suffixes with the same first token
+        if (c0 == 0) lo = hi;  // (end markers tie)
+        // A wide bucket is narrowed by the second tokens first, a probe for each lane, until what has the
+        // new suffix's is most of what is left, or few enough.
+        const int32_t second = w[1];
+        for (bool go = hi - lo > RANK_COLUMN; __any(go);) {
+            auto probe = [&](int q) { return lo + (int64_t)(((uint64_t)(hi - lo) * ((uint64_t)(q + 1) * ((1ull << 32) / (RANK_LANES + 1)))) >> 32); };
+            const int32_t t = go ? tok1[probe(lane - first)] : 0;
+            const uint64_t group = (1ull << RANK_LANES) - 1ull;
+            const int lower = __popcll((__ballot(t < second) >> first) & group), up_to = __popcll((__ballot(t <= second) >> first) & group);
+            if (go) {
+                const int64_t from = lower > 0 ? probe(lower - 1) + 1 : lo;
+                if (up_to < RANK_LANES) hi = probe(up_to);
+                lo = from;
+                go = hi - lo > RANK_COLUMN && up_to - lower <= RANK_LANES / 2;
+            }
+        }
+        int below = 1, above = 1;  // tokens shared with what lies next to [lo, hi)
         while (__any(lo < hi)) {
-            // Probes divide [lo, hi) evenly; up to RANK_LANES suffixes are probed one by one.  In a wide
+            // Probes divide [lo, hi) evenly; up to RANK_PROBES suffixes are probed one by one.  In a wide
             // range the last probe is its last suffix: in text that is one token over and over the new
             // suffix ties with all of them, D tokens a probe (half a million into as many and more: an
             // insertion takes 1.74 ms without, 1.28 so).
             const uint32_t len = (uint32_t)(hi - lo);
-            const bool few = len <= RANK_LANES, wide = len > RANK_WIDE;
+            const bool alone = len > RANK_ALONE, wide = len > RANK_WIDE;
+            const int probes = alone ? RANK_LANES : RANK_PROBES, g = alone ? lane - first : (lane - first) >> 2;
+            const bool few = len <= RANK_PROBES;
             auto probe = [&](int q) {  // place of the q-th one
-                return lo + (int64_t)(((uint64_t)(wide ? len - 1u : len) * ((uint64_t)(q + 1) * (wide ? (1ull << 32) / RANK_LANES : (1ull << 32) / (RANK_LANES + 1)))) >> 32);
+                return lo + (int64_t)(((uint64_t)(wide ? len - 1u : len) * ((uint64_t)(q + 1) * (wide ? (1ull << 32) / RANK_LANES : alone ? (1ull << 32) / (RANK_LANES + 1) : (1ull << 32) / (RANK_PROBES + 1)))) >> 32);
             };
             const int64_t i = few ? lo + g : probe(g);
-            bool before = false;  // old suffix i sorts before, or ties with, the new one
-            if (i < hi && lo < hi) {
+            int agree = 0;        // tokens that old suffix i and the new one share, if it is looked at
+            bool before = false;  // it sorts before the new one, or ties with it
+            if (i < hi && lo < hi) {  // (the same for the four lanes of a probe)
                 const int32_t *v = text + sa[i];
-                int cmp = 0;  // sign of (old suffix - new suffix) on the first D tokens
-                for (int k = 0; k < D; k += 8) {
-                    // (what lies behind a suffix's end marker is text or padding and is not looked at)
-                    const tok4 a0 = *reinterpret_cast<const tok4 *>(v + k), a1 = *reinterpret_cast<const tok4 *>(v + k + 4);
-                    const tok4 b0 = *reinterpret_cast<const tok4 *>(w + k), b1 = *reinterpret_cast<const tok4 *>(w + k + 4);
-                    const int32_t as[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                    const int32_t bs[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                    bool done = false;
-#pragma unroll
-                    for (int q = 0; q < 8; q++) {
-                        if (done || k + q >= D) continue;
-                        if (as[q] != bs[q]) { cmp = as[q] < bs[q] ? -1 : 1; done = true; }
-                        else if (as[q] == SD_END_TOKEN) done = true;
-                    }
-                    if (done) break;
-                }
-                before = cmp <= 0;
+                const int step = alone ? 4 : 16;
+                int k = min(below, above), at = first_diff<1>(v, w, k, D, alone);
+                for (k += step; at == NO_DIFF && k < D; k += step * RANK_MORE) at = first_diff<RANK_MORE>(v, w, k, D, alone);
+                agree = at == NO_DIFF ? D : at >> 2;
+                before = at == NO_DIFF || (at & 3) < 2;
             }
-            const uint64_t m = (__ballot(before) >> first) & ((1ull << RANK_LANES) - 1ull);
+            const uint64_t m = (__ballot(before && (alone || (lane & 3) == 0)) >> first) & ((1ull << RANK_LANES) - 1ull);
             const int n = __popcll(m);  // (the probes rise: the first n are the ones before)
+            const int last = __shfl(agree, first + (n > 0 ? n - 1 : 0) * (alone ? 1 : 4)), next = __shfl(agree, first + (n < probes ? n : 0) * (alone ? 1 : 4));
             if (lo < hi) {
                 if (few) {
                     lo += n;
                     hi = lo;
                 } else {
                     const int64_t from = n > 0 ? probe(n - 1) + 1 : lo;
-                    if (n < RANK_LANES) hi = probe(n);
+                    if (n > 0) below = last;
+                    if (n < probes) {
+                        hi = probe(n);
+                        above = next;
+                    }
                     lo = from;
                 }
             }
         }
-        if (g == 0 && j < M) rank[j] = (uint32_t)lo;
+        if (lane == first && j < M) rank[j] = (uint32_t)lo;
     }
 }
 
@@ -278,8 +329,9 @@ __global__ __launch_bounds__(TB) void k_insert_rank(const int32_t *__restrict__ 
 // entries, the others a tile of old ones each.
 // Bound: the bytes of both arrays.  The new suffixes that go into a tile are found by a wave in three
 // rounds of loads and kept in LDS, where every old entry finds its shift (2.2M old, 32k new: 28 and
-// 5 us for old and new entries apart, 256 entries a workgroup -> 16 us, and 17 us less for the table).
-constexpr int MERGE_ITEMS = 8, MERGE_TILE = TB * MERGE_ITEMS, MERGE_RANKS = 2048;
+// 5 us for old and new entries apart, 256 entries a workgroup -> 15 us, and 17 us less for the table; 9M: 31 us.
+// Tiles of 8 x 256: 16 and 32 us, of 16 x 256: 20 and 38).
+constexpr int MERGE_ITEMS = 6, MERGE_TILE = TB * MERGE_ITEMS, MERGE_RANKS = 2048;
 
 // number of values in the rising rank[0..n) that are <= key; whole wave
 __device__ __forceinline__ int64_t wave_count_up_to(const uint32_t *__restrict__ rank, int64_t n, int64_t key) {
@@ -611,7 +663,7 @@ sd_status sd_insert_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_
     int32_t *sa_out = (int32_t *)c->b_vals[1 - cur], *tok1_out = (int32_t *)c->b_rank;
     const int64_t rank_blocks = (M + TB / RANK_LANES - 1) / (TB / RANK_LANES);
     SD_LAUNCH(c, SD_K_INSERT, st, k_insert_rank, dim3(rank_blocks < RANK_BLOCKS ? (unsigned)rank_blocks : RANK_BLOCKS), dim3(TB), 0,
-              c->g_text, c->g_sa, N, c->g_bucket, dsa, M, N, c->cfg.D, rank);
+              c->g_text, c->g_sa, c->g_tok1, c->g_bucket, dsa, M, N, c->cfg.D, rank);
     if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;  // (the merge relies on the ranks: the index stays as it was)
     SD_LAUNCH(c, SD_K_INSERT, st, k_insert_merge, dim3(nblk(M) + (unsigned)((N + MERGE_TILE - 1) / MERGE_TILE)), dim3(TB), 0,
               c->g_sa, c->g_tok1, N, c->g_text, dsa, rank, M, N, sa_out, tok1_out, c->g_tok1s,

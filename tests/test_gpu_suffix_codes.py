@@ -122,6 +122,31 @@ def test_small_shares(n):
         g.close()
 
 
+@pytest.mark.parametrize("D", [33, 64, 81])
+@pytest.mark.parametrize("n", [1, 2, 3, 64, 65, 256, 257, 900])
+def test_insert_among_long_prefixes(n, D):
+    """n old suffixes of one first token that agree with a new one on 15 to 81 tokens: around the loads of a probe's
+    four lanes (16 tokens, then 32 at a time) and of one lane (4, then 8), and around the widths of a bucket at which the
+    ranking goes from two probes to eight (256), or looks at the second tokens first (64)."""
+    rng = np.random.default_rng(n + D)
+    vocab, head = 3000, rng.integers(1, 3000, 90).astype(np.int32)
+    head[0] = 0  # (no other token is 0)
+    depths = [1, 2, 3, 4, 5, 11, 12, 13, 15, 16, 17, 47, 48, 49, 63, 64, 65, 79, 80, 81]
+
+    def doc(i):
+        k = depths[i % len(depths)]
+        tail = rng.integers(1, vocab, int(rng.integers(0, 4))).astype(np.int32)
+        return np.concatenate([head[:k], tail])
+    old, new = [doc(i) for i in range(n)], [doc(int(i)) for i in rng.integers(0, 40, 60)] + [head]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in old + new))
+    try:
+        g.build_global(old)
+        g.insert_global(new)
+        _check(g, old + new, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [8, 9, 4095, 4096, 4097, 30_000])
 def test_insert_into_a_wide_bucket(n):
     """The ranking probes up to 8, up to 4096 and more suffixes of one first token in different ways: new
