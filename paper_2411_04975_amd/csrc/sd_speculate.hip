@@ -179,15 +179,43 @@ __device__ __forceinline__ uint64_t occ_key(const SpecParams &p, const int32_t *
                            : (t1 << (kb + 1)) | (t2 << 1) | more;
 }
 
+// The value of lane ^ M.  Within rows of 16 lanes by data-parallel moves, otherwise by a permute through the LDS.
+template <int M>
+__device__ __forceinline__ int32_t from_xor(int32_t v) {
+    constexpr int CTRL = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 3 ? 0x1B : M == 7 || M == 4 ? 0x141 : M == 8 ? 0x128 : 0x140;
+    if (M > 15) return __shfl_xor(v, M);
+    v = __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+    return M == 4 ? __builtin_amdgcn_update_dpp(v, v, 0x1B, 0xf, 0xf, false) : v;  // (7 and 3)
+}
+template <int M>
+__device__ __forceinline__ void exchange(int2 &rec, uint64_t &key) {
+    const int2 orec = make_int2(from_xor<M>(rec.x), from_xor<M>(rec.y));
+    const uint64_t okey = ((uint64_t)(uint32_t)from_xor<M>((int32_t)(key >> 32)) << 32) | (uint32_t)from_xor<M>((int32_t)key);
+    // both partners look at the same ordered pair: the lower place keeps the lower key
+    const int lane = threadIdx.x & 63;
+    const bool take = (lane ^ M) > lane ? okey < key : key < okey;
+    if (take) { rec = orec; key = okey; }
+}
+// A wave's 64 records in the order of their keys: the bitonic network.
+__device__ __forceinline__ void sort_wave(int2 &rec, uint64_t &key) {
+    exchange<1>(rec, key);
+    exchange<3>(rec, key); exchange<1>(rec, key);
+    exchange<7>(rec, key); exchange<2>(rec, key); exchange<1>(rec, key);
+    exchange<15>(rec, key); exchange<4>(rec, key); exchange<2>(rec, key); exchange<1>(rec, key);
+    exchange<31>(rec, key); exchange<8>(rec, key); exchange<4>(rec, key); exchange<2>(rec, key); exchange<1>(rec, key);
+    exchange<63>(rec, key); exchange<16>(rec, key); exchange<8>(rec, key); exchange<4>(rec, key); exchange<2>(rec, key); exchange<1>(rec, key);
+}
+
 // Sort of up to one element per thread (m is at most the workgroup's size; threads without an
 // element pass the key ~0).  Every wave first orders its own 64 elements with a bitonic network
 // whose partners are reached by lane permutes, and leaves the keys as a sorted run in LDS; an
 // element's final place is then its place in its own run plus, for every other run, the number
 // of that run's keys that go before it, found by a binary search in the run (among equal keys
-// of different runs the earlier run goes first).  That is some 250 instructions and 50 LDS
-// reads per element, all waves at work, where a network over the whole list takes 55 steps
-// with ten of them across waves (18 us for the 550 occurrences of a frequent token), and
-// counting the keys that go before an element one by one is bound by LDS bandwidth (13 us).
+// of different runs the earlier run goes first).  The bound is the latency of those reads, seven
+// of them one after the other in a run, so SIDE runs are searched side by side: the 543 occurrences of a
+// frequent token take 4.4 us, 7.5 with run after run, and a decode step of 256 low-repetition contexts of
+// 4096 tokens 28 instead of 30 us.  (A network over the whole list takes 55 steps with ten of them across
+// waves: 18 us; counting the keys that go before an element one by one is bound by LDS bandwidth: 13.)
 // Equal keys whose low bit is set must be ordered by the tokens beyond the key: such groups
 // (rare: the key holds three tokens) lie side by side after the placement and are put in order
 // by token-by-token compares in memory.  s_rec receives the sorted records; s_key and *s_flag
@@ -228,40 +256,35 @@ __device__ __forceinline__ void occ_sort_runs(int2 rec, uint64_t key, int m, int
         return;
     }
     if (busy && !presorted) {
-        for (int k = 2; k <= 64; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const int src = lane ^ (j == (k >> 1) ? k - 1 : j);
-                int2 orec;
-                orec.x = __shfl(rec.x, src);
-                orec.y = __shfl(rec.y, src);
-                const uint32_t klo = (uint32_t)__shfl((int)(uint32_t)key, src);
-                const uint32_t khi = (uint32_t)__shfl((int)(uint32_t)(key >> 32), src);
-                const uint64_t okey = ((uint64_t)khi << 32) | klo;
-                // both partners look at the same ordered pair: the lower place keeps the lower key
-                const bool take = src > lane ? okey < key : key < okey;
-                if (take) { rec = orec; key = okey; }
-            }
-        }
+        sort_wave(rec, key);
         s_key[i] = key;
     }
     if (i == 0) *s_flag = 0;
     __syncthreads();
     int place = lane;
     if (busy) {
-        const int nruns = (m + 63) >> 6;
-#pragma unroll 2
-        for (int r = 0; r < nruns; r++) {
-            if (r * 64 == w0) continue;
-            const uint64_t *run = s_key + r * 64;
-            const bool first = r * 64 < w0;  // an earlier run: its equal keys go before mine
-            int pos = 0;
+        const int others = ((m + 63) >> 6) - 1, own = w0 >> 6;
+        constexpr int SIDE = 4;  // runs searched side by side: their reads are under way together
+        for (int r0 = 0; r0 < others; r0 += SIDE) {
+            const uint64_t *at[SIDE];
+            uint64_t bound[SIDE];
 #pragma unroll
-            for (int step = 32; step > 0; step >>= 1) {
-                const uint64_t kq = run[pos + step - 1];
-                pos += (first ? kq <= key : kq < key) ? step : 0;
+            for (int q = 0; q < SIDE; q++) {
+                int r = r0 + q < others ? r0 + q : r0;
+                r += r >= own ? 1 : 0;
+                at[q] = s_key + r * 64;
+                bound[q] = key + (r < own ? 1ull : 0ull);  // (an earlier run: its equal keys go before mine; no element's key is ~0)
             }
-            const uint64_t kq = run[pos];
-            place += pos + ((first ? kq <= key : kq < key) ? 1 : 0);
+            int pos[SIDE] = {};
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+#pragma unroll
+                for (int q = 0; q < SIDE; q++) pos[q] += at[q][pos[q] + step - 1] < bound[q] ? step : 0;
+#pragma unroll
+            for (int q = 0; q < SIDE; q++) {
+                pos[q] += at[q][pos[q]] < bound[q] ? 1 : 0;
+                place += r0 + q < others ? pos[q] : 0;
+            }
         }
     }
     __syncthreads();  // all keys have been read
@@ -455,9 +478,26 @@ __device__ __forceinline__ void occ_scan_issue(int t_old, const int32_t *__restr
     st.last_old = t_old > 0 ? x[t_old - 1] : 0;
 }
 
+// Left-extension (capped at lim) of the occurrence of the last token that ends at e, from the four tokens in
+// front of it in one load: that settles what differs from the context's tail within them (nearly all occurrences of a
+// frequent token), and the context's own tail.  0: not settled.
+typedef int32_t near4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool STATS>
+__device__ __forceinline__ int near_extension(int e, int lim, int t, int32_t tail, const int32_t *__restrict__ x, unsigned &nb) {
+    if (e == t - 1) return lim;
+    if (lim <= 1) return lim;
+    if (e < 4) return 0;
+    const near4 v = *reinterpret_cast<const near4 *>(x + e - 4);
+    SD_CNT(16);
+    const bool m1 = v.w == __builtin_amdgcn_readlane(tail, 1), m2 = m1 && v.z == __builtin_amdgcn_readlane(tail, 2),
+               m3 = m2 && v.y == __builtin_amdgcn_readlane(tail, 3), m4 = m3 && v.x == __builtin_amdgcn_readlane(tail, 4);
+    const int l = 1 + (m1 ? 1 : 0) + (m2 ? 1 : 0) + (m3 ? 1 : 0) + (m4 ? 1 : 0);
+    return l >= lim ? lim : m4 ? 0 : l;
+}
+
 // Left-extensions when the last token has more occurrences than one trip of the workgroup
 // takes (a frequent token; records in LDS): most occurrences differ from the context's tail
-// in the very next token to the left.  One load per occurrence, an occurrence per thread,
+// in the next tokens to the left.  One load per occurrence, an occurrence per thread,
 // settles those; the rest is listed (in `lst`) and compared token by token as in the caller's
 // loop, PP lanes per occurrence.  Out of line: the route is rare and is kept from weighing on
 // the registers and the code layout of the usual one.  Called by every thread (barrier inside).
@@ -469,18 +509,17 @@ __device__ __attribute__((noinline)) unsigned left_extensions_many(int m, int t,
     unsigned nb = 0;
     const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
     const int wave = uni((int32_t)(tid >> 6)), nw = nthr >> 6;
-    const int32_t tl1 = __builtin_amdgcn_readlane(tail, 1);
     for (int i = tid; i < ((m + 63) & ~63); i += nthr) {
         const bool on = i < m;
-        const int e = on ? s_sort[i].x : -1;
-        const int lim = e + 1 < P ? e + 1 : P;
-        const bool rd = on && e != t - 1 && lim > 1;
-        const int32_t vv = rd ? x[e - 1] : tl1;
-        if (rd) SD_CNT(8);
-        const bool one = on && (lim <= 1 || (rd && vv != tl1));  // left-extension 1
-        const bool surv = on && !one;
-        if (one) s_sort[i].y = 1;
-        const uint64_t om = __ballot(one), sm = __ballot(surv);
+        int l = 0;
+        if (on) {
+            const int e = s_sort[i].x;
+            l = near_extension<STATS>(e, e + 1 < P ? e + 1 : P, t, tail, x, nb);
+            if (l > 0) s_sort[i].y = l;
+            if (l > 1) atomicAdd(&sh.cnt[l], 1);
+        }
+        const bool surv = on && l == 0;
+        const uint64_t om = __ballot(l == 1), sm = __ballot(surv);
         if (lane == 0 && om) atomicAdd(&sh.cnt[1], (int)__popcll(om));
         if (sm) {
             int base = 0;
@@ -517,9 +556,8 @@ __device__ __attribute__((noinline)) unsigned left_extensions_many(int m, int t,
 }
 
 // Frequent last token, occurrences [64 c, 64 c + 64) of the list in LDS on one wave: their
-// left-extensions (most differ from the context's tail in the very next token to the left,
-// which one load per occurrence settles; the rest is compared token by token, PP lanes per
-// occurrence), their sort keys, and the wave's 64-element network, which leaves records and
+// left-extensions (one load per occurrence settles those that differ from the context's tail within four
+// tokens; the rest is compared token by token, PP lanes per occurrence), their sort keys, and the wave's 64-element network, which leaves records and
 // keys as a sorted run in place.  No barrier: a wave takes such a part whenever it is free,
 // while others are still searching the global index.
 template <bool STATS>
@@ -533,18 +571,18 @@ __device__ __forceinline__ unsigned occ_chunk(int c, int m, int t, int P, int de
     const bool on = i < m;
     const int e = on ? s_sort[i].x : -1;
     const int lim = e + 1 < P ? e + 1 : P;
-    const int32_t tl1 = __builtin_amdgcn_readlane(tail, 1);
-    const bool rd = on && e != t - 1 && lim > 1;
-    const int32_t vv = rd ? x[e - 1] : tl1;
-    if (rd) SD_CNT(8);
     // the tokens behind the occurrence, for its key (rows are padded with end markers)
     const int kt = key_toks < depth ? key_toks : depth;
-    const uint64_t t1 = on ? (uint64_t)(uint32_t)(x[e + 1] + 1) : 0ull;
-    const uint64_t t2 = on && kt >= 2 ? (uint64_t)(uint32_t)(x[e + 2] + 1) : 0ull;
-    const uint64_t t3 = on && kt >= 3 ? (uint64_t)(uint32_t)(x[e + 3] + 1) : 0ull;
-    if (on) SD_CNT(4 * kt);
-    const bool one = on && (lim <= 1 || (rd && vv != tl1));  // left-extension 1
-    uint64_t sm = __ballot(on && !one);
+    near4 behind = {-1, -1, -1, -1};
+    int near_l = 0;
+    if (on) {
+        behind = *reinterpret_cast<const near4 *>(x + e + 1);
+        SD_CNT(4 * kt);
+        near_l = near_extension<STATS>(e, lim, t, tail, x, nb);
+    }
+    const uint64_t t1 = (uint64_t)(uint32_t)(behind.x + 1), t2 = kt >= 2 ? (uint64_t)(uint32_t)(behind.y + 1) : 0ull,
+                   t3 = kt >= 3 ? (uint64_t)(uint32_t)(behind.z + 1) : 0ull;
+    uint64_t sm = __ballot(on && near_l == 0);
     int pplog = 0;
     while ((1 << pplog) < P) pplog++;
     const int PP = 1 << pplog, G = 64 >> pplog, g = lane >> pplog, k = lane & (PP - 1);
@@ -572,7 +610,7 @@ __device__ __forceinline__ unsigned occ_chunk(int c, int m, int t, int P, int de
         }
     }
     wsync();
-    const int L = one ? 1 : (on ? s_sort[i].y : 0);
+    const int L = near_l > 0 ? near_l : (on ? s_sort[i].y : 0);
     if (on) atomicAdd(&sh.cnt[L], 1);
     int2 rec = make_int2(e, L);
     uint64_t key = ~0ull;
@@ -581,20 +619,7 @@ __device__ __forceinline__ unsigned occ_chunk(int c, int m, int t, int P, int de
         key = key_toks == 3 ? (t1 << (2 * key_bits + 1)) | (t2 << (key_bits + 1)) | (t3 << 1) | more
                             : (t1 << (key_bits + 1)) | (t2 << 1) | more;
     }
-    for (int kk = 2; kk <= 64; kk <<= 1) {
-        for (int j = kk >> 1; j > 0; j >>= 1) {
-            const int src = lane ^ (j == (kk >> 1) ? kk - 1 : j);
-            int2 orec;
-            orec.x = __shfl(rec.x, src);
-            orec.y = __shfl(rec.y, src);
-            const uint32_t klo = (uint32_t)__shfl((int)(uint32_t)key, src);
-            const uint32_t khi = (uint32_t)__shfl((int)(uint32_t)(key >> 32), src);
-            const uint64_t okey = ((uint64_t)khi << 32) | klo;
-            // both partners look at the same ordered pair: the lower place keeps the lower key
-            const bool take = src > lane ? okey < key : key < okey;
-            if (take) { rec = orec; key = okey; }
-        }
-    }
+    sort_wave(rec, key);
     wsync();
     s_sort[i] = rec;  // (within the room of the list's 64-entry parts: the LDS holds whole parts)
     s_key[i] = key;
@@ -739,8 +764,7 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
         const int32_t tl = __shfl(tail, k);  // the k-th token from the context's end (0 beyond it)
         constexpr int U = 4;
         // A handful of occurrences, two trips of one wave: it does all there is to do with them by itself, keys
-        // asked for with the tokens in front, and leaves the records in LDS.  (Spread over the waves, sorted by the
-        // network and handed on through scratch memory they held the slowest requests up by 1.5 us.)
+        // asked for with the tokens in front, and leaves the records in LDS, without a barrier or scratch memory.
         const bool few = m <= 2 * G * U && m <= FEW && !early;
         int32_t t1 = 0, t2 = 0, t3 = 0;
         const int kt = p.key_toks < p.D - 1 ? p.key_toks : p.D - 1;
@@ -1601,9 +1625,7 @@ __device__ __forceinline__ void col_stage(const SpecParams &p, int32_t w1, int32
         const WideOut r = col_sampled<STATS>(col, p.g_tok1s, true, w1, l, h, false, 0, 0, 0);
         l = r.loA; h = r.hiA;
         SD_CNT(r.nb);
-    } else if (h - l > SCAN_MAX) {  // (callers send such buckets elsewhere; kept for completeness)
-        range_fan_tokens<STATS>(p.g_sa, p.g_text, w1, 2, 1, LEVEL_TLOG, l, h, nb);
-    } else {
+    } else {  // (callers send wider ones elsewhere)
         int32_t v[SCAN_MAX / 64];
 #pragma unroll
         for (int c = 0; c < SCAN_MAX / 64; c++) {
@@ -2285,8 +2307,7 @@ __device__ __forceinline__ Accepted accept_find(int b, const AcceptIn &in, const
         // One node per lane, sets of nodes as masks.  Trees are made of runs of nodes whose parent is the
         // node before, so a round takes the good nodes whose parent is accepted together with the good
         // runs behind them (the addition carries through a run), and there are as many rounds as runs on the
-        // accepted path.  (Pointer jumping, a round per bit of the depth with two permutes each:
-        // accepted 0.4 us later.)
+        // accepted path.
         const bool wf = lane < n && mp[0] >= -1 && mp[0] < lane;
         const int32_t want = __shfl(in.tgt0, wf ? mp[0] + 1 : 0);  // (mp[0] + 1 <= lane <= 63)
         const uint64_t good = ballot64(wf) & ballot64(mt[0] == want), chain = good & ballot64(mp[0] == lane - 1) & ~1ull;

@@ -1104,6 +1104,54 @@ def test_global_build_captured_into_a_graph():
         g.close()
 
 
+@pytest.mark.parametrize("m", [33, 64, 65, 128, 129, 256, 257, 320, 321, 385, 577, 640, 1000, 1030])
+def test_frequent_last_tokens(m):
+    """Contexts whose last token occurs m times, some of them within the first four tokens and some behind copies of
+    1 to 11 tokens of the context's tail: left-extensions around the four tokens that are looked at first, and lists
+    of one to sixteen sorted runs (four are searched side by side).  Drafted from, and after a fused step over a corpus
+    whose buckets are too wide for the list form, where waves take parts of the list early."""
+    rng = np.random.default_rng(m)
+    vocab, D, P, alpha, ms = 9, 24, 12, 1.0, 0.02
+    ctxs = []
+    for b in range(8):
+        x = rng.integers(1, vocab, 3 * m + 40).astype(np.int32)
+        tail = x[-12:-1].copy()
+        for k in range(1, 12):  # the last token behind k of the tail's tokens, the one in front differs
+            at = 20 * k
+            if at + 14 < len(x) - 14 and k <= m // 4:
+                x[at:at + k] = tail[len(tail) - k:]
+                x[at + k] = 0
+                x[at - 1] = tail[len(tail) - k - 1] % (vocab - 1) + 1 if k < len(tail) else 1
+        x[b % 5] = 0
+        x[-1] = 0
+        left = m - int((x == 0).sum())
+        free = np.setdiff1d(np.arange(240, len(x) - 13) if m > 100 else np.arange(0, len(x) - 13), np.flatnonzero(x == 0))
+        x[rng.choice(free, left, replace=False)] = 0
+        assert int((x == 0).sum()) == m
+        ctxs.append(x)
+    docs = [rng.integers(0, vocab, 60_000).astype(np.int32)]
+    B = len(ctxs)
+    g = parity.GpuPath(vocab, D, P, alpha, ms, B, len(ctxs[0]) + 20, len(docs[0]) + 1)
+    try:
+        g.build_global(docs)
+        tg = oracle.Trie(D)
+        tg.add_doc(docs[0])
+        g.build_requests(range(B), ctxs)
+        want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, ms, g.max_nodes)
+        bad = parity.compare_trees(g.speculate(range(B)), want, "%d occurrences" % m)
+        short = [x[:-1] for x in ctxs]
+        g.build_requests(range(B), short)
+        out = g.speculate(range(B))
+        al, ap, bo, got = g.accept_append_speculate(range(B), np.zeros((B, g.max_nodes + 1), np.int32))
+        longer = [np.concatenate([short[b], out["tokens"][b][ap[b][:al[b]]], bo[b:b + 1]]).astype(np.int32) for b in range(B)]
+        assert all(x[-1] == 0 for x in longer)
+        want = parity.oracle_speculate_batch(tg, longer, D, P, alpha, ms, g.max_nodes)
+        bad += parity.compare_trees(got, want, "%d occurrences, a step on" % m)
+        assert not bad, "\n".join(bad)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [255, 256, 257, 640, 1023, 1024, 1025, 2500, 4095, 4096, 4097, 6000])
 def test_first_token_buckets_around_the_scan_limits(n):
     """The second pattern token is located inside the first token's bucket by one of three
