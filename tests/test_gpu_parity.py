@@ -1152,6 +1152,35 @@ def test_frequent_last_tokens(m):
         g.close()
 
 
+@pytest.mark.parametrize("D", [9, 12, 24, 41])
+@pytest.mark.parametrize("m", [2, 3, 17, 31, 32, 33])
+def test_few_occurrences_that_go_on_alike(m, D):
+    """m occurrences of the last token behind the same eight tokens, followed by 0 to 45 tokens of one piece: the
+    first wave orders up to 32 of them, four tokens beyond the key at a time, up to D tokens, by position where these agree."""
+    rng = np.random.default_rng(100 * m + D)
+    vocab, P, alpha, ms = 5000, 8, 2.0, 0.02
+    ctxs = []
+    for b in range(8):
+        head, cont = rng.integers(1, vocab, 8).astype(np.int32), rng.integers(1, vocab, 45).astype(np.int32)
+        lens = rng.choice([0, 1, 2, 3, 4, 6, 7, 8, 10, 11, 12, 20, 38, 39, 40, 45], m - 1) if b % 2 else np.full(m - 1, 45)
+        parts = [np.concatenate([head, [0], cont[:n], rng.integers(1, vocab, int(rng.integers(0, 3)))]) for n in lens]
+        ctxs.append(np.concatenate(parts + [head, [0]]).astype(np.int32))
+        assert int((ctxs[-1] == 0).sum()) == m
+    docs = [rng.integers(1, vocab, 500).astype(np.int32)]
+    B = len(ctxs)
+    g = parity.GpuPath(vocab, D, P, alpha, ms, B, max(len(x) for x in ctxs) + 1, 501)
+    try:
+        g.build_global(docs)
+        tg = oracle.Trie(D)
+        tg.add_doc(docs[0])
+        g.build_requests(range(B), ctxs)
+        want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, ms, g.max_nodes)
+        bad = parity.compare_trees(g.speculate(range(B)), want, "%d occurrences, D %d" % (m, D))
+        assert not bad, "\n".join(bad)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [255, 256, 257, 640, 1023, 1024, 1025, 2500, 4095, 4096, 4097, 6000])
 def test_first_token_buckets_around_the_scan_limits(n):
     """The second pattern token is located inside the first token's bucket by one of three
