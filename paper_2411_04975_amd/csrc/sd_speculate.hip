@@ -27,6 +27,7 @@
 #include <math.h>
 
 #include "sd_internal.h"
+#include "sd_plan.h"
 
 namespace {
 
@@ -2474,9 +2475,6 @@ __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nod
 // those with the top SCORE, so "best" means SCORE high, then scan position low; the waves'
 // candidates meet in LDS after a barrier and the winning wave writes its tree out, padded
 // with -1 / 0.0.  Nothing but the final tree leaves the compute unit.
-constexpr int SPEC_OCC = 6;       // waves per SIMD that one or two resident workgroups may fill
-constexpr int SPEC_RESIDENT = 4;  // workgroups per compute unit the wave count is sized for
-
 // With ACCEPT the workgroup first settles the verification of the request's previous tree (the
 // one `out` still holds, against aa.target) on its first wave, appends the accepted tokens and
 // the bonus token to the request's context, and then drafts the next tree from the extended
@@ -3043,29 +3041,14 @@ sd_status launch_speculate(sd_ctx *c, const int32_t *d_slot_ids, int32_t batch, 
     size_t lds_wave = (size_t)c->max_nodes * (3 * sizeof(double) + 9 * sizeof(int32_t)) +
                       (64 + 64 + TC_TOKENS + 64) * sizeof(int32_t);
     lds_wave = (lds_wave + 7) / 8 * 8;
-    // Waves per request.  One workgroup per compute unit takes the 16 waves a workgroup can
-    // have; two share SPEC_OCC waves per SIMD between them (12 each if the LDS allows: the
-    // registers of the kernel leave room for 7 waves per SIMD, and 14 each were not resident
-    // together); three and four likewise (8 and 6 each, or what the LDS allows).  Larger batches
-    // are throughput work: a compute unit's LDS holds about 20 waves' worth of frontier and
-    // staging at the largest tree sizes, so up to eight workgroups per compute unit get 5 waves
-    // (four resident at a time, the rest wait their turn) and more get 4 (five resident; less
-    // idle time at the workgroup's barriers).  Thinner workgroups lose: every request then
-    // takes longer and the end of the launch runs half empty.
-    const int per_cu_all = (batch + c->n_cu - 1) / c->n_cu;
-    const int per_cu = per_cu_all < SPEC_RESIDENT ? per_cu_all : SPEC_RESIDENT;
-    int nw = per_cu_all <= 2 ? 4 * SPEC_OCC / per_cu_all
-             : per_cu_all == 3 ? 8 : per_cu_all == 4 ? 6 : per_cu_all <= 8 ? 5 : 4;
-    const size_t lds_cu = c->lds_cu > 2048 * (size_t)per_cu ? c->lds_cu - 2048 * (size_t)per_cu : 0;
-    while (nw > 1 && (size_t)nw * lds_wave * per_cu > lds_cu) nw--;
-    if (nw > 16) nw = 16;
-    if (nw < 1) nw = 1;
-    size_t lds = (size_t)nw * lds_wave;
     // the occurrence sort keeps up to OCC_LDS_SORT records and their keys in the same LDS
     // before the waves take it over: as many as fit, and room for at least half of that
     const size_t rec = sizeof(int2) + sizeof(uint64_t);
-    if (lds < OCC_LDS_SORT / 2 * rec) lds = OCC_LDS_SORT / 2 * rec;
-    if (lds > c->lds_optin) return SD_ERR_CAPACITY;
+    const sd_plan plan = sd_plan_waves(batch, c->n_cu, c->lds_cu, c->lds_optin, sizeof(WgShared), lds_wave,
+                                       OCC_LDS_SORT / 2 * rec);
+    if (plan.waves < 1) return SD_ERR_CAPACITY;
+    const int nw = plan.waves;
+    const size_t lds = plan.lds;
     p.occ_cap = lds / rec < (size_t)OCC_LDS_SORT ? (int32_t)(lds / rec) : OCC_LDS_SORT;
     const dim3 grid((unsigned)batch), block(64 * nw);
     if (aa) {

@@ -1,0 +1,72 @@
+"""Trees of up to 256 nodes at batches of one to six requests per compute unit: the LDS of a launch depends on both,
+and the waves of a workgroup with it."""
+import numpy as np
+import pytest
+
+import oracle
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _text(rng, n, pool, vocab):
+    parts, have = [], 0
+    while have < n:
+        a = int(rng.integers(0, len(pool) - 20))
+        parts.append(pool[a:a + int(rng.integers(20, 160))])
+        have += len(parts[-1])
+    t = np.concatenate(parts)[:n].copy()
+    mut = rng.random(n) < 0.02
+    t[mut] = rng.integers(0, vocab, int(mut.sum()))
+    return t.astype(np.int32)
+
+
+# One request to a compute unit: around the sizes at which a wave less fits (16 waves end at 132 nodes, 15 at 142, ...
+# 10 at 229); more of them: where the workgroups of a compute unit just fit together, and just do not.
+@pytest.mark.parametrize("nodes,batch", [
+    (n, 6) for n in (132, 133, 138, 142, 143, 149, 162, 177, 194, 215, 229, 230, 239, 240, 255, 256)] + [
+    (72, 300), (73, 300), (128, 300), (136, 500), (236, 500), (66, 700), (128, 700), (256, 700), (64, 1000),
+    (78, 1000), (132, 1000), (186, 1000), (256, 1000), (106, 1300), (122, 1300), (256, 1300)])
+def test_trees_of_all_sizes(nodes, batch):
+    rng = np.random.default_rng(1000 * nodes + batch)
+    vocab, P, D, ms = 300, 64, 200, 0.002
+    alpha = (nodes + 0.5) / P
+    pool = rng.integers(0, vocab, 900)
+    docs = [_text(rng, 400, pool, vocab) for _ in range(30)]
+    ctxs = [_text(rng, int(rng.integers(1, 500)), pool, vocab) for _ in range(min(batch, 12))]
+    NV = len(ctxs)
+    of = np.arange(batch) % NV
+    g = parity.GpuPath(vocab, D, P, alpha, ms, batch, 500 + nodes + 1, sum(len(d) + 1 for d in docs))
+    try:
+        assert g.max_nodes == nodes
+        g.build_global(docs)
+        g.build_requests(range(batch), [ctxs[v] for v in of])
+        tg = oracle.Trie(D)
+        for d in docs:
+            tg.add_doc(d)
+        want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, ms, nodes)
+        bad = parity.compare_trees(g.speculate(range(batch)), {k: v[of] for k, v in want.items()}, "drafts")
+        assert not bad, "\n".join(bad)
+        # a step on: the target model follows the drafts' first children for some nodes
+        tgt = np.full((NV, nodes + 1), vocab - 1, np.int32)
+        longer, exp = [], []
+        for v in range(NV):
+            n, at = int(want["n_nodes"][v]), -1
+            for _ in range(7 * v):
+                kids = np.flatnonzero(want["parents"][v, :n] == at)
+                if not len(kids):
+                    break
+                tgt[v, at + 1] = want["tokens"][v, kids[0]]
+                at = int(kids[0])
+            L, path, bonus = oracle.accept(want["tokens"][v, :n], want["parents"][v, :n], tgt[v])
+            exp.append((L, list(path), bonus))
+            longer.append(np.concatenate([ctxs[v], want["tokens"][v, list(path)], [bonus]]).astype(np.int32))
+        al, ap, bo, got = g.accept_append_speculate(range(batch), tgt[of])
+        for b in range(batch):
+            L, path, bonus = exp[of[b]]
+            assert al[b] == L and bo[b] == bonus and list(ap[b, :L]) == path, b
+        want = parity.oracle_speculate_batch(tg, longer, D, P, alpha, ms, nodes)
+        bad = parity.compare_trees(got, {k: v[of] for k, v in want.items()}, "drafts a step on")
+        assert not bad, "\n".join(bad)
+    finally:
+        g.close()
