@@ -26,6 +26,7 @@
 // drafts, append of the accepted tokens), and k_accept does that alone.
 #include <math.h>
 
+#include "sd_handover.h"
 #include "sd_internal.h"
 #include "sd_plan.h"
 
@@ -629,8 +630,8 @@ __device__ __forceinline__ unsigned occ_chunk(int c, int m, int t, int P, int de
 
 // What a wave does with a frequent last token once its own search in the global index is over
 // (per-pattern route only, where the waves' searches take unequal times): it waits until every
-// wave's hits are down (each wave has counted itself in before it waits for anything, so the
-// wait ends; it is over long before a wave gets here), and if the list is of the kind that
+// wave's hits and the appended tokens are down (each wave has counted itself in before it waits for
+// anything, so the wait ends; it is over long before a wave gets here), and if the list is of the kind that
 // request_occurrences sorts with one element per thread, it takes parts of 64 occurrences
 // until none is left: left-extensions, keys and the per-wave part of the sort then do not wait
 // behind the workgroup's barrier for the slowest search.  Out of line: the route is rare and is
@@ -638,13 +639,11 @@ __device__ __forceinline__ unsigned occ_chunk(int c, int m, int t, int P, int de
 template <bool STATS>
 __device__ __attribute__((noinline)) unsigned occ_take_chunks(int nw, int t, int P, int depth, int occ_cap,
                                                                int key_toks, int key_bits, double alpha,
-                                                               int32_t tail, const int32_t *__restrict__ x,
+                                                               int32_t tail, const int32_t *x,
                                                                int2 *s_sort, WgShared &sh) {
     unsigned nb = 0;
     const int lane = threadIdx.x & 63;
-    while (__hip_atomic_load(&sh.scan_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < nw)
-        __builtin_amdgcn_s_sleep(1);
-    wsync();
+    wait_for_count(&sh.scan_done, nw);
     const int m_all = __hip_atomic_load(&sh.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     int pplog = 0;
     while ((1 << pplog) < P) pplog++;
@@ -663,7 +662,7 @@ __device__ __attribute__((noinline)) unsigned occ_take_chunks(int nw, int t, int
 
 template <bool STATS, bool EARLY, class Settle, class Between>
 __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, int t, int t_old,
-                                    const int32_t *newtok, const int32_t *__restrict__ x,
+                                    const int32_t *newtok, const int32_t *x,
                                     int2 *s_sort, WgShared &sh, ScanState &st, int32_t tail,
                                     unsigned &nb, Settle settle, Between between) {
     const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
@@ -735,12 +734,11 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
         }
     }
     settle();
-    // (this wave's hits are down: the count below says when every wave's are.  The hits and
-    // the count are LDS operations of one wave, which the LDS takes in the order they were
-    // issued: the compiler must keep that order, nothing has to be waited for.)
+    // (this wave's hits are down, and what settle() appends to the row if this is the wave that does: occ_take_chunks
+    // reads both on any wave, before the barrier)
     if (EARLY) {
         wsync();
-        if (lane == 0) atomicAdd(&sh.scan_done, 1);
+        if (lane == 0) count_in(&sh.scan_done);
     }
     between();
     __syncthreads();
@@ -2578,9 +2576,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         // What acceptance and append have to write, by the last wave, once it needs nothing more of what it has
         // asked for: a wave's loads and stores are waited for in order, and the first wave, which every other
         // one waits for, would wait for its stores with its share of the scan (0.4 us of a decode step).
-        // The barrier behind the scan orders the stores to the row before the other waves' loads at workgroup
-        // scope, which is all that is needed: the waves of a workgroup share one compute unit and its cache,
-        // and only this workgroup touches the row.
+        // Who reads the appended tokens from the row waits for them: the early parts of a frequent token's occurrences for
+        // the count that every wave adds itself to behind this (sd_handover.h), all others at the barrier behind
+        // the scan.  Workgroup scope is all that is needed, as only this workgroup touches the row.
         if (ACCEPT && wave == nw - 1) {
             Accepted a;
 #pragma unroll

@@ -1152,6 +1152,53 @@ def test_frequent_last_tokens(m):
         g.close()
 
 
+@pytest.mark.parametrize("m", [257, 300, 511, 900])
+def test_frequent_tokens_among_those_appended(m):
+    """A fused step whose accepted tokens hold the context's new last token once or more: these occurrences' keys are
+    made of appended tokens, read from the row by whichever wave takes the list's last part, before the barrier
+    (the lists are of the length that waves take parts of early, the buckets too wide for the list form)."""
+    rng = np.random.default_rng(m)
+    vocab, D, P, alpha, ms, B = 9, 24, 12, 1.0, 0.02, 8
+    ctxs = []
+    for _ in range(B):
+        x = rng.integers(1, vocab, 2 * m + 40).astype(np.int32)
+        x[rng.choice(len(x), m, replace=False)] = 0
+        ctxs.append(x)
+    docs = [rng.integers(0, vocab, 60_000).astype(np.int32)]
+    g = parity.GpuPath(vocab, D, P, alpha, ms, B, len(ctxs[0]) + 60, len(docs[0]) + 1)
+    try:
+        g.build_global(docs)
+        tg = oracle.Trie(D)
+        tg.add_doc(docs[0])
+        g.build_requests(range(B), ctxs)
+        want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, ms, g.max_nodes)
+        bad = parity.compare_trees(g.speculate(range(B)), want, "%d occurrences" % m)
+        inside = 0
+        for step in range(3):
+            tgt = np.zeros((B, g.max_nodes + 1), np.int32)  # (0 is also what follows the last accepted node)
+            for b in range(B):
+                n, up = int(want["n_nodes"][b]), want["parents"][b]
+                zeros = np.flatnonzero(want["tokens"][b, :n] == 0)
+                j = int(zeros[step % len(zeros)]) if len(zeros) else -1
+                while j >= 0:
+                    tgt[b, up[j] + 1] = want["tokens"][b, j]
+                    j = int(up[j])
+            al, ap, bo, got = g.accept_append_speculate(range(B), tgt)
+            for b in range(B):
+                n = int(want["n_nodes"][b])
+                L, path, bonus = oracle.accept(want["tokens"][b, :n], want["parents"][b, :n], tgt[b])
+                assert al[b] == L and bo[b] == bonus and list(ap[b, :L]) == list(path), b
+                new = want["tokens"][b, list(path)].astype(np.int32)
+                inside += int(bonus == 0 and (new == 0).any())
+                ctxs[b] = np.concatenate([ctxs[b], new, [bonus]]).astype(np.int32)
+            want = parity.oracle_speculate_batch(tg, ctxs, D, P, alpha, ms, g.max_nodes)
+            bad += parity.compare_trees(got, want, "%d occurrences, %d steps on" % (m, step + 1))
+        assert not bad, "\n".join(bad)
+        assert inside >= 8
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("D", [9, 12, 24, 41])
 @pytest.mark.parametrize("m", [2, 3, 17, 31, 32, 33])
 def test_few_occurrences_that_go_on_alike(m, D):
