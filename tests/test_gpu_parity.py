@@ -1443,18 +1443,20 @@ def test_wide_batches_on_thinner_workgroups():
     library sizes them by the batch): 775 and 3329 requests must give the trees of the oracle
     row by row, and so must a fused step at 775.  The requests are 114 distinct contexts,
     repeated over the slots: 16 drawn ones, each with 0..6 tokens cut off its end, and two of
-    three tokens only whose last token occurs about 1400 and 1650 times: thinner workgroups
-    have less LDS, so these are sorted in LDS at one width and in device memory at another."""
+    three tokens only whose last token occurs about 1150 and 1300 times: thinner workgroups
+    have less LDS (1392 records at six waves, 1024 at four), so these are sorted in LDS at one width
+    and in device memory at another."""
     import paper_2411_04975_amd as sd
     w = make_workload(scaled("tiny", alpha=2.0, min_score=0.05), seed=5)
     docs = w.docs()
     mn = w.max_nodes
     variants = [w.contexts[i % 16][:w.ctx_len - (i // 16)] for i in range(112)]
     rng = np.random.default_rng(77)
-    for share in (0.74, 0.86):
+    for share in (0.6, 0.68):
         x = np.where(rng.random(1900) < share, 7, rng.integers(8, 10, 1900)).astype(np.int32)
         x[-1] = 7
         variants.append(x)
+        assert 1024 + 50 < int((x == 7).sum()) < 1392 - 50  # (a few more tokens are appended below)
     NV = len(variants)
     tg = parity.oracle_global_trie(docs, w.D, w.vocab)
     tries = []
@@ -1477,7 +1479,10 @@ def test_wide_batches_on_thinner_workgroups():
         g.build_global(docs)
         g.build_requests(range(B), [variants[b % NV] for b in range(B)])
         for nb in (3329, 775):
+            st0 = g.stats()
             got = g.speculate(range(nb))
+            in_memory = g.stats()["spec_occ_in_memory"] - st0["spec_occ_in_memory"]
+            assert in_memory == (sum(b % NV >= NV - 2 for b in range(nb)) if nb == 3329 else 0)
             bad = parity.compare_trees(got, rows(want_v, nb), "batch %d" % nb)
             assert not bad, "\n".join(bad)
             if nb > sd.SD_TICK_SLOTS:      # the timing variant keeps marks for that many requests

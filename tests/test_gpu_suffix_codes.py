@@ -43,7 +43,10 @@ def _text(rng, n, vocab, copies):
 @pytest.mark.parametrize("n,vocab,copies", [
     (1, 50, 1), (2, 50, 1), (254, 50, 1), (257, 900, 3), (2047, 30000, 3), (2049, 30000, 3),
     (6150, 5, 40), (100_003, 128256, 4), (524_200, 128256, 3), (524_400, 300, 3),
-    (1_048_500, 128256, 9), (1_048_700, 152064, 5), (40_000, 1 << 24, 2), (40_000, (1 << 21) - 2, 2)])
+    (524_560, 128256, 3), (524_561, 128256, 3),      # 513 * 1024 - 1 positions: the most of one split; one more
+    (1_048_500, 128256, 9), (1_048_700, 152064, 5),
+    (4_188_319, 128256, 2), (4_188_320, 152064, 2),  # 2^22 positions: the most in tiles of 2048; one more
+    (40_000, 1 << 24, 2), (40_000, (1 << 21) - 2, 2)])
 def test_sizes(n, vocab, copies):
     rng = np.random.default_rng(n + copies)
     D = 24
@@ -365,7 +368,7 @@ def test_repeated_text_costs_no_more_than_doubling(times):
         sd.sd_destroy(ctx)
 
 
-@pytest.mark.parametrize("n_docs,body", [(1025, 0), (6000, 30_000), (9000, 1_050_000)])
+@pytest.mark.parametrize("n_docs,body", [(1025, 0), (6000, 30_000), (9000, 1_050_000), (9000, 4_200_000)])
 @pytest.mark.parametrize("captured", [False, True])
 def test_more_documents_than_the_layout_keeps(n_docs, body, captured):
     """Runs of empty documents and of documents of one token: more of them in a tile of positions (2048,
