@@ -84,9 +84,12 @@ def test_repeated_phrase(times):
 
 
 @pytest.mark.parametrize("n_old,n_new,spread", [
-    (1, 1, 1), (1, 3000, 1), (2047, 7, 1), (2048, 4000, 0), (2049, 300, 1), (9000, 2500, 0), (70_001, 5, 1)])
+    (1, 1, 1), (1, 3000, 1), (2047, 7, 1), (2048, 4000, 0), (2049, 300, 1), (9000, 2500, 0), (70_001, 5, 1),
+    (1534, 9, 1), (1535, 9, 1), (1536, 700, 1), (3071, 5, 1), (1500, 2046, 0), (1500, 2047, 0), (4700, 2047, 0)])
 def test_insert_places(n_old, n_new, spread):
-    """Around the tiles of the merge; without `spread` all new suffixes go between two old ones."""
+    """Around the tiles of the merge, 1536 old entries with up to 2048 new ones in LDS (a document's end is an entry
+    too: 1535 tokens fill a tile, 2046 in two documents the LDS); without `spread` all new suffixes go between two old
+    ones."""
     rng = np.random.default_rng(n_old)
     D, vocab = 16, 4000
     old = rng.integers(0, vocab, n_old).astype(np.int32)
@@ -150,10 +153,10 @@ def test_insert_among_long_prefixes(n, D):
         g.close()
 
 
-@pytest.mark.parametrize("n", [8, 9, 4095, 4096, 4097, 30_000])
+@pytest.mark.parametrize("n", [1, 2, 3, 8, 9, 64, 65, 256, 257, 4095, 4096, 4097, 30_000])
 def test_insert_into_a_wide_bucket(n):
-    """The ranking probes up to 8, up to 4096 and more suffixes of one first token in different ways: new
-    suffixes in front of all of them, behind all of them, tied with all or with some."""
+    """The ranking looks at up to 2, up to 256, up to 4096 and more suffixes of one first token in different ways,
+    and at second tokens first among more than 64: new suffixes in front of all of them, behind all of them, tied with all or with some."""
     rng = np.random.default_rng(n)
     D, vocab = 16, 50
     cases = [[np.full(n, 7, np.int32)],                                       # one run
