@@ -2730,8 +2730,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         }
         // (a frequent last token: the waves that are done with their searches early take the
         // left-extensions and the per-wave part of the occurrence sort meanwhile)
-        // (in the decode step's form of the kernel; the form without the acceptance has no
-        // register left for the call)
+        // (in the decode step's form of the kernel.  The form without the acceptance had no register left for the
+        // call when this came in; it has by now, at 78 of them, but what the call gives there has not been measured)
         if (ACCEPT) {
             const unsigned cnt_chunks = occ_take_chunks<STATS>(nw, t, P, p.D - 1, p.occ_cap, p.key_toks,
                                                                p.key_bits, p.alpha, tail, x, s_sort, sh);
