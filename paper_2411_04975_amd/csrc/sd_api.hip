@@ -33,7 +33,7 @@ void free_all(sd_ctx *c) {
     void *ptrs[] = {c->g_text, c->g_sa, c->g_bucket, c->g_tok1, c->g_tok1s, c->b_keys[0], c->b_keys[1], c->b_vals[0],
                     c->b_vals[1], c->b_rank, c->b_flags, c->b_gid2, c->b_hist, c->b_partials, c->r_text,
                     c->r_len, c->s_occ, c->s_unit_sa, c->d_err, c->s_unit_ticks, c->d_entropy,
-                    c->d_round_flag, c->code_cdf, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
+                    c->d_round_flag, c->code_cdf, c->code_blocks, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (c->h_flag) (void)hipHostFree(c->h_flag);
@@ -94,20 +94,21 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     int64_t *ib = &c->index_bytes, *sb = &c->scratch_bytes;
     ok = ok && dev_alloc(&c->g_text, cap + SD_TEXT_PAD + 64, ib);
     // g_sa / g_tok1 change places with build scratch buffers on insertion: same sizes as those
-    ok = ok && dev_alloc(&c->g_sa, cap + 64, ib);
-    ok = ok && dev_alloc(&c->g_tok1, cap + 64, ib);
+    const int64_t column = cap + SD_TEXT_PAD + 64;  // (the lines of the text and its padding have room in one)
+    ok = ok && dev_alloc(&c->g_sa, column, ib);
+    ok = ok && dev_alloc(&c->g_tok1, column, ib);
     ok = ok && dev_alloc(&c->g_tok1s, cap / 16 + 64, ib);
     ok = ok && dev_alloc(&c->g_bucket, (int64_t)cfg->vocab + 2, ib);
     ok = ok && dev_alloc(&c->b_keys[0], cap, sb) && dev_alloc(&c->b_keys[1], cap, sb);
-    ok = ok && dev_alloc(&c->b_vals[0], cap + 64, sb) && dev_alloc(&c->b_vals[1], cap + 64, sb);
-    ok = ok && dev_alloc(&c->b_rank, cap + 64, sb) && dev_alloc(&c->b_flags, cap, sb) &&
+    ok = ok && dev_alloc(&c->b_vals[0], column, sb) && dev_alloc(&c->b_vals[1], column, sb);
+    ok = ok && dev_alloc(&c->b_rank, column, sb) && dev_alloc(&c->b_flags, cap, sb) &&
          dev_alloc(&c->b_gid2, cap, sb);
     ok = ok && dev_alloc(&c->b_hist, c->b_hist_cap + code_ranges + code_starts + rest_to, sb);
     c->b_ranges = c->b_hist + c->b_hist_cap;
     c->rest_table = c->b_ranges + code_ranges;
     c->rest_to = c->rest_table + code_starts;
     ok = ok && dev_alloc(&c->b_partials, c->b_partials_cap, sb);
-    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2, sb) && dev_alloc(&c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), sb) &&
+    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2, sb) && dev_alloc(&c->code_blocks, sd_code_blocks(cfg->vocab), sb) && dev_alloc(&c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), sb) &&
          dev_alloc(&c->code_partials, sd_code_parts(cfg->vocab), sb) && dev_alloc(&c->b_starts, code_starts, sb) &&
          dev_alloc(&c->code_sums, code_sums, sb) &&
          dev_alloc(&c->code_bucket, (int64_t)cfg->vocab + 2, sb);

@@ -61,6 +61,7 @@ struct sd_ctx {
 
     // suffix sorting by codes (sd_suffix.hip)
     uint32_t *code_cdf = nullptr;       // [vocab + 2]: lower end of each token code's interval
+    uint32_t *code_blocks = nullptr;    // lower ends of blocks of tokens' intervals
     uint32_t *code_cnt = nullptr;       // [copies][vocab + 1]: counts of a sample, zero between builds
     uint32_t *code_partials = nullptr;
     int32_t *code_bucket = nullptr;     // [vocab + 2]: bucket table of the documents of an insertion
@@ -110,6 +111,7 @@ struct sd_ctx {
 void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
                   int64_t *range_words, int64_t *rest_words);
 bool sd_code_fits(int64_t N, int32_t vocab);
+int64_t sd_code_blocks(int32_t vocab); // words of code_blocks
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);

@@ -17,18 +17,18 @@
 // numbers; and the second-token column of the index comes from the entries: only suffixes that
 // tie are ever looked up in the text.
 //
-// Bound: the memory system.  Per position 72 bytes in order (tokens read, text and code written and
-// read, entries written and read once per pass, suffix array and second tokens written), and
-// for each one that ties one or two random cache lines a step, which are what costs: of the 0.58 ms of
-// 10M tokens copied from templates k_code_sort takes 0.34 and reads 220 bytes a position in them,
-// 6.4 TB/s (100M: 4.0 of 6.2 ms, 260 bytes, 6.6 TB/s), against 0.09 where few suffixes tie.
+// Bound: the memory system.  Per position 76 bytes in order (tokens read, text, codes and lines written, text and
+// codes read, entries written and read once per pass, suffix array and second tokens written), and
+// for each one that ties one random cache line a step: of the 0.46 ms of
+// 10M tokens copied from templates k_code_sort takes 0.23 and reads 124 bytes a position in them
+// (100M: 3.1 of 4.8 ms, 148 bytes), against 0.09 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
-// Build of 10M tokens copied from templates 1.68 -> 0.59 ms, of 10M of a Zipf law 2.89 -> 0.32 ms, of
-// 100M copied 20.7 -> 6.2 ms, against prefix doubling for everything.
+// Build of 10M tokens copied from templates 1.68 -> 0.46 ms, of 10M of a Zipf law 2.89 -> 0.32 ms, of
+// 100M copied 20.7 -> 4.8 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 
 namespace {
@@ -39,8 +39,7 @@ constexpr int CODE_LOOK = 16;      // tokens that a code depends on, at most
 constexpr int MAX_BITS = 10;       // of one split
 constexpr int MAX_BINS = 1 << MAX_BITS;
 
-typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef int32_t tok2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
 
 __device__ __forceinline__ void wave_sync() {
@@ -130,6 +129,7 @@ __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ 
             const uint32_t old = atomicCAS(&s_tag[h], FREE, code);
             if (old == FREE || old == code) { atomicAdd(&s_num[h], 1u); break; }
             h = (h + 1) & (TABLE - 1);
+
         }
         if (probe == 16) atomicAdd(&cnt[code], 1u);
     }
@@ -176,10 +176,18 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
 // cdf[c] = lower end of the interval of code c; clears the first copy.  Ends are multiples of
 // 2^CDF_QUANTUM (and no interval is empty, the weights' total being below 2^27): an entry may
 // lack that many of its code's last bits, and the rest still names the first token.
+//
+// Codes go by blocks of 2^shift, as many as make a table of at most CDF_BLOCKS blocks, which k_layout has in LDS.  In a
+// block without a code of more than twice the average weight, or three sightings, all codes get equal parts of the block's
+// interval: what the sample tells among them is chance for the most part (10M tokens copied from templates, k_code_sort:
+// 250 us by the sample alone, 232 so), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
+// interval, its last bit set if the block is of that kind.  (So a code's buckets are twice as full as
+// others, or have some hundred entries more; a bucket of five times the average still fits.)
 constexpr int CDF_QUANTUM = 5;
+constexpr int CDF_BLOCKS = 4096, CDF_MAX_SHIFT = 7;
 __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, int32_t n_codes,
                                                  const uint32_t *__restrict__ partials,
-                                                 uint32_t *__restrict__ cdf) {
+                                                 uint32_t *__restrict__ cdf, int shift, uint32_t *__restrict__ blocks) {
     __shared__ uint32_t s_wave[CW];
     uint32_t below = 0, all = 0;
     for (int i = threadIdx.x; i < (int)gridDim.x; i += CT) {
@@ -187,8 +195,9 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
         all += v;
         if (i < (int)blockIdx.x) below += v;
     }
+    static_assert(CDF_ITEMS == 2 && (1 << CDF_MAX_SHIFT) <= 2 * SD_WAVE, "a block is some lanes of a wave");
     const int32_t c0 = (int32_t)blockIdx.x * CDF_TILE + (int32_t)threadIdx.x * CDF_ITEMS;
-    uint32_t wgt[CDF_ITEMS], sum = 0, tot;
+    uint32_t wgt[CDF_ITEMS], sum = 0, top = 0, tot;
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
         wgt[k] = 0;
@@ -197,59 +206,136 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
             weight[c0 + k] = 0;
         }
         sum += wgt[k];
+        top = wgt[k] > top ? wgt[k] : top;
     }
     uint32_t total, base;
     (void)block_excl_scan(all, s_wave, &total);
     (void)block_excl_scan(below, s_wave, &base);
     uint32_t at = base + block_excl_scan(sum, s_wave, &tot);
+    const int lanes = 1 << (shift - 1), head = (int)(threadIdx.x & 63 & ~(unsigned)(lanes - 1));
+    uint32_t in_block = sum;
+    for (int o = 1; o < lanes; o <<= 1) {
+        in_block += __shfl_xor(in_block, o);
+        const uint32_t t = __shfl_xor(top, o);
+        top = t > top ? t : top;
+    }
+    auto end = [&](uint32_t w) { return (uint32_t)((uint64_t)w * 0x7ffffffull / total); };
+    const uint32_t first = __shfl(at, head), lo = end(first), width = end(first + in_block) - lo;
+    const int32_t b0 = c0 & ~((1 << shift) - 1);  // the block's first code
+    const bool even = b0 + (1 << shift) <= n_codes && (uint64_t)top << shift <= 2 * (uint64_t)in_block + (48ull << shift);
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
         if (c0 + k <= n_codes)
-            cdf[c0 + k] = (uint32_t)((uint64_t)at * 0x7ffffffull / total) << CDF_QUANTUM;
+            cdf[c0 + k] = (even ? lo + (uint32_t)((uint64_t)width * (uint32_t)(c0 + k - b0) >> shift) : end(at)) << CDF_QUANTUM;
         at += wgt[k];
+    }
+    if (c0 == b0 && b0 <= n_codes) {
+        blocks[b0 >> shift] = lo << CDF_QUANTUM | (even ? 1u : 0u);
+        if (b0 + (1 << shift) > n_codes) blocks[(b0 >> shift) + 1] = 0x7ffffffu << CDF_QUANTUM;
     }
 }
 
 // ---- the text, the codes of its positions, and the first split's bins per tile ------------------
 // text = documents one after the other, an end marker behind each and SD_TEXT_PAD more behind the
 // last: document j starts at offs[j] + j.  The tile's documents are looked up once, in the offsets
-// in memory, and each position then among these in LDS.  What takes the time is the gather of the
-// intervals (one line of the L2 per position; 10M from a 512 KB table: 46 us), so the text is written
-// on the way (10M tokens, 128k of them different: 71 us together; text and codes by kernels of
-// their own took 53 and 55).
+// in memory, and each position then among these in LDS.
+//
+// A position's interval comes from the table of blocks in LDS, but for blocks of unlike tokens, whose tokens
+// ask for theirs in memory.  Asking for all of them there takes a line of the L2 per position, and as many bytes of L2 as that are
+// a limit of their own: 71 us for 10M tokens, 128k of them different, and 586 for 100M, without the lines below; with the table, and
+// the lines, 58 and 464.  The table takes as little LDS as leaves room for four workgroups on a compute unit: what a
+// workgroup waits for are loads and other waves (10M, tables of 10,240, 5120 and 4096 blocks, two, three and four workgroups: 85, 67, 58;
+// 2048 blocks: 58).  Inputs of less than a few million tokens ask in memory (2.2M: 22.2, by blocks 22.8).
+//
+// Also on the way: the text once more, in lines of 128 bytes that each hold the codes of the tokens from
+// position 32 k on, as many as the line has room for (LINE_BITS_MIN bits a code or more: 40 to 64 of them), one bit string
+// with the first code's highest bit first.  Wherever a stretch of tokens begins, one line holds at least
+// 1024 / bits - 31 of them (29 of 17 bits), and bit strings compare as the tokens do: what has to look at
+// suffixes in any order reads a line each time, where 48 bytes of 32-bit tokens, twelve, are 1.34 lines.
 constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
 constexpr int LDS_DOCS = 1024;
+constexpr int LINE_POS = 32;       // positions from one line to the next: a line has as many words
+constexpr int LINE_BITS_MIN = 16;  // (a word holds parts of three codes at most)
+constexpr int LAYOUT_LOOK = 1024 / LINE_BITS_MIN - LINE_POS;  // tokens behind a round of positions that it looks at
+static_assert(LAYOUT_LOOK >= CODE_LOOK && LAYOUT_LOOK <= CT && KEY_ROUND % LINE_POS == 0, "");
 
-template <int ITEMS, bool CODES>
+enum { TEXT_ONLY = 0, CODES_DIRECT, CODES_BY_BLOCK };
+template <int ITEMS, int KIND>
 __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ tokens,
                                                const int64_t *__restrict__ offs, int32_t n_seq,
                                                int64_t n_tokens, int32_t *__restrict__ text, int32_t vocab,
                                                int32_t *err, const uint32_t *__restrict__ cdf,
+                                               const uint32_t *__restrict__ blocks, int block_shift,
                                                uint32_t *__restrict__ keys, int shift, int bins,
                                                uint32_t *__restrict__ hist, int64_t ntiles, int per_chunk,
-                                               uint32_t *__restrict__ sums) {
+                                               uint32_t *__restrict__ sums, uint32_t *__restrict__ lines, int bits) {
+    constexpr bool CODES = KIND != TEXT_ONLY;
+    __shared__ uint32_t s_block[KIND == CODES_BY_BLOCK ? CDF_BLOCKS + 1 : 1];
+    static_assert(2 * (KEY_ROUND + CODE_LOOK) >= KEY_ROUND + LAYOUT_LOOK, "");
     __shared__ uint2 s_code[CODES ? KEY_ROUND + CODE_LOOK : 1];  // (lower end, width) of each token's interval
-    __shared__ uint32_t s_hist[CODES ? MAX_BINS : 1];
+    uint32_t *s_tok = reinterpret_cast<uint32_t *>(s_code);      // before that: the tokens' codes
+    __shared__ uint32_t s_hist[CODES ? MAX_BINS / 2 : 1];        // two counts a word
     __shared__ int32_t s_start[LDS_DOCS + 1];  // documents' starts, counted from the tile's
-    __shared__ int32_t s_doc[2];
+    __shared__ int32_t s_doc[4];
     const int tid = threadIdx.x;
     const int64_t N = n_tokens + n_seq, tile0 = (int64_t)blockIdx.x * (CT * ITEMS);
     auto start_of = [&](int32_t j) -> int64_t { return j <= n_seq ? offs[j] + j : N + 1; };
-    if (tid < 128 && tile0 < N) {  // documents of the tile's first position and of its last one
-        int64_t p = tid < 64 ? tile0 : tile0 + CT * ITEMS + CODE_LOOK - 1;
-        if (p > N - 1) p = N - 1;
-        const int j = wave_lower_bound([&](int i) { return offs[i] + i; }, n_seq, p + 1) - 1;
-        if ((tid & 63) == 0) s_doc[tid >> 6] = j < 0 ? 0 : j;
-    }
+    if (KIND == CODES_BY_BLOCK)
+        for (int i = tid; i <= (vocab >> block_shift) + 1; i += CT) s_block[i] = blocks[i];
     if (CODES)
-        for (int i = tid; i < bins; i += CT) s_hist[i] = 0;
+        for (int i = tid; i < bins / 2; i += CT) s_hist[i] = 0;
+    if (tid < 4) s_doc[tid] = 0;
     __syncthreads();
-    const int32_t d0 = tile0 < N ? s_doc[0] : 0, nd = tile0 < N ? s_doc[1] - d0 + 1 : 0;
-    if (nd <= LDS_DOCS)
-        for (int i = tid; i <= nd; i += CT) {
-            const int64_t at = start_of(d0 + i) - tile0;
-            s_start[i] = at < -1 ? -1 : at > (1 << 30) ? 1 << 30 : (int32_t)at;
+    // The tile's documents, in two rounds of loads: the starts of CT of all documents tell between which two of these the
+    // tile starts, and what lies between them and some hundred behind are all of the tile's as a rule.
+    int32_t d0 = 0, nd = 0;  // the first, and how many; LDS_DOCS of them are in LDS, and the one behind
+    if (tile0 < N) {
+        const int64_t z = tile0 + CT * ITEMS + LAYOUT_LOOK < N ? tile0 + CT * ITEMS + LAYOUT_LOOK : N;
+        const int32_t step = (n_seq + CT - 1) / CT;
+        const bool front = tid > 0 && (int64_t)tid * step < n_seq && start_of(tid * step) <= tile0;
+        const int n = (int)__popcll(__ballot(front));
+        if ((tid & 63) == 0 && n) atomicAdd(&s_doc[0], n);
+        __syncthreads();
+        d0 = s_doc[0] * step;
+        int before = 0, in = 0;
+        int32_t at[2];
+        static_assert(LDS_DOCS == 2 * CT, "two to a thread");
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int i = k * CT + tid;
+            const int64_t s = start_of(d0 + i) - tile0;
+            at[k] = s < -1 ? -1 : s > (1 << 30) ? 1 << 30 : (int32_t)s;
+            before += (int)__popcll(__ballot(i > 0 && s <= 0));
+            in += (int)__popcll(__ballot(s < z - tile0));
         }
+        if ((tid & 63) == 0) {
+            if (before) atomicAdd(&s_doc[1], before);
+            if (in) atomicAdd(&s_doc[2], in);
+        }
+        __syncthreads();
+        before = s_doc[1];
+        in = s_doc[2];
+        if (in < LDS_DOCS) {
+            d0 += before;
+            nd = in - before;
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+                if (k * CT + tid >= before) s_start[k * CT + tid - before] = at[k];
+        } else {
+            if (tid < 128) {
+                const int j = wave_lower_bound([&](int i) { return offs[i] + i; }, n_seq, tid < 64 ? tile0 + 1 : z) - 1;
+                if ((tid & 63) == 0) s_doc[tid < 64 ? 0 : 3] = j < 0 ? 0 : j;
+            }
+            __syncthreads();
+            d0 = s_doc[0];
+            nd = s_doc[3] - d0 + 1;
+            if (nd <= LDS_DOCS)
+                for (int i = tid; i <= nd; i += CT) {
+                    const int64_t s = start_of(d0 + i) - tile0;
+                    s_start[i] = s < -1 ? -1 : s > (1 << 30) ? 1 << 30 : (int32_t)s;
+                }
+        }
+    }
     __syncthreads();
     // token at text position p (-1: end marker)
     auto token_at = [&](int64_t p) -> int32_t {
@@ -271,15 +357,23 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
             next = start_of(d0 + lo + 1);
         }
         const int64_t i = p - (d0 + lo);
-        return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
+                return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
     };
+    int32_t tok[5];  // of a round: every CT-th one from the thread's on, and one behind the round
+    auto ask = [&](int r) {
+        const int64_t base = tile0 + r * KEY_ROUND;
+        if (r >= ITEMS / 4 || base >= N + SD_TEXT_PAD) return;
+#pragma unroll
+        for (int k = 0; k < 4; k++) tok[k] = token_at(base + k * CT + tid);
+        tok[4] = CODES && tid < LAYOUT_LOOK ? token_at(base + KEY_ROUND + tid) : SD_END_TOKEN;
+    };
+    // the codes that word `tid` of a line (and of every 16th line behind it) holds parts of, and their shifts
+    const int word_bit = (tid & (LINE_POS - 1)) * 32, code0 = CODES ? word_bit / bits : 0;
+    const int left0 = 32 - bits + (word_bit - code0 * bits), left1 = left0 - bits, right2 = bits - left1;
+    ask(0);
     for (int r = 0; r < ITEMS / 4; r++) {
         const int64_t base = tile0 + r * KEY_ROUND;
         if (base >= N + SD_TEXT_PAD) break;
-        int32_t tok[5];
-#pragma unroll
-        for (int k = 0; k < 4; k++) tok[k] = token_at(base + k * CT + tid);
-        tok[4] = CODES && tid < CODE_LOOK ? token_at(base + KEY_ROUND + tid) : SD_END_TOKEN;
 #pragma unroll
         for (int k = 0; k < 5; k++)
             if (tok[k] != SD_END_TOKEN && (tok[k] < 0 || tok[k] >= vocab)) {
@@ -289,12 +383,39 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
 #pragma unroll
         for (int k = 0; k < 4; k++)
             if (base + k * CT + tid < N + SD_TEXT_PAD) text[base + k * CT + tid] = tok[k];
-        if (!CODES) continue;
-        u32x2 ends[5];  // (both ends in one load)
+        if (!CODES) { ask(r + 1); continue; }
+        u32x2 ends[5];  // (both ends of the token's interval)
 #pragma unroll
         for (int k = 0; k < 5; k++)
-            if (k < 4 || tid < CODE_LOOK) ends[k] = *reinterpret_cast<const u32x2 *>(cdf + (tok[k] + 1));
+            if (k < 4 || tid < CODE_LOOK) {
+                const uint32_t c = (uint32_t)(tok[k] + 1);
+                bool ask_for = true;
+                if (KIND == CODES_BY_BLOCK) {
+                    const uint32_t b = c >> block_shift, i = c & ((1u << block_shift) - 1u), e = s_block[b];
+                    const uint32_t lo = e & ~1u, width = ((s_block[b + 1] & ~1u) - lo) >> CDF_QUANTUM;
+                    ends[k].x = lo + ((uint32_t)((uint64_t)width * i >> block_shift) << CDF_QUANTUM);
+                    ends[k].y = lo + ((uint32_t)((uint64_t)width * (i + 1u) >> block_shift) << CDF_QUANTUM);
+                    ask_for = !(e & 1u);
+                }
+                if (ask_for) ends[k] = *reinterpret_cast<const u32x2 *>(cdf + c);
+            }
         __syncthreads();  // (the round before is done with the intervals)
+#pragma unroll
+        for (int k = 0; k < 5; k++)
+            if (k < 4 || tid < LAYOUT_LOOK) s_tok[k * CT + tid] = (uint32_t)(tok[k] + 1);
+        ask(r + 1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int p = k * CT + tid;
+            const uint32_t *from = s_tok + (p & ~(LINE_POS - 1)) + code0;
+            uint32_t v = from[0] << left0;
+            v |= left1 >= 0 ? from[1] << left1 : from[1] >> -left1;
+            if (left1 > 0) v |= from[2] >> right2;
+            // (not wanted before text and codes are: 10M independent tokens, the first split, 54 -> 47 us)
+            if (base + (p & ~(LINE_POS - 1)) < N + SD_TEXT_PAD) __builtin_nontemporal_store(v, &lines[base + p]);
+        }
+        __syncthreads();
 #pragma unroll
         for (int k = 0; k < 5; k++)
             if (k < 4 || tid < CODE_LOOK) s_code[k * CT + tid] = make_uint2(ends[k].x, ends[k].y - ends[k].x);
@@ -313,14 +434,15 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
             }
             const uint32_t key = (uint32_t)(low >> 32);
             keys[base + p] = key;
-            atomicAdd(&s_hist[key >> shift], 1u);
+            atomicAdd(&s_hist[key >> shift >> 1], (key >> shift) & 1u ? 1u << 16 : 1u);
         }
     }
     if (!CODES || blockIdx.x >= ntiles) return;
     __syncthreads();
     uint32_t *row = hist + (int64_t)blockIdx.x * bins, *sum = per_chunk > 0 ? sums + (int64_t)(blockIdx.x / per_chunk) * bins : nullptr;
+    static_assert(CT * ITEMS < 1 << 16, "counts of 16 bits");
     for (int i = tid; i < bins; i += CT) {
-        const uint32_t v = s_hist[i];
+        const uint32_t v = (s_hist[i >> 1] >> (16 * (i & 1))) & 0xffffu;
         row[i] = v;
         if (v && sum) atomicAdd(&sum[i], v);
     }
@@ -500,7 +622,7 @@ __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ 
 #pragma unroll
     for (int k = 0; k < ITEMS; k++) {
         const int j = k * CT + tid;
-        const uint32_t key = j < cnt ? keys[base + j] : 0u;
+        const uint32_t key = j < cnt ? __builtin_nontemporal_load(keys + base + j) : 0u;  // (once: 47 -> 44 us)
         const uint32_t tok = j < cnt ? (uint32_t)(text[base + j + 1] + 1) : 0u;
         digit[k] = key >> (32 - f.bits1);
         const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
@@ -628,10 +750,11 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 // one count over equal parts of the buckets' code ranges puts every entry within a few places of
 // its own, and counting the lower entries of its part there.  From there on a wave takes care of
 // its share of the places alone.  Places whose entries tie go on a list.  A step gives each lane
-// one place of the list, whole groups together, shows the next TOK tokens of every entry to the
-// wave through LDS, counts for each entry the group's members that sort before it, moves the
-// positions to their new places, does so for another TOK tokens (which came with the same
-// gather), and keeps on the list what still ties.
+// one place of the list, whole groups together, asks for the next 384 bits of tokens of every entry (22 tokens of 17
+// bits), a line each, orders the groups by them, moves the
+// positions to their new places, and keeps on the list what still ties.  (Twelve tokens a step from the text
+// itself, 1.34 lines, ordered by counting what is less: 348 us for 10M tokens, 4.00 ms for 100M; from lines: 260 and 3.45;
+// ordered as below: 250 and 3.13.)
 //
 // Copies of one text share their part of the code range and tie: counting would be quadratic in
 // them.  Parts of more than PART_COUNTED entries go through a bitonic network instead, and groups of more
@@ -639,9 +762,6 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 // whole workgroup (128 and 512 instead of 256: up to a tenth slower).  Builds of 10M tokens, half of them
 // copies of preambles, with 200, 500, 1000, 2000 copies of each: 0.94, 1.24, 1.23, 1.56 ms; 1.16, 1.71, 2.61,
 // 5.5 by counting, each long group split by one wave.
-//
-// Tokens are compared as two 64-bit words: three of 21 bits each, two of 32 for vocabularies
-// beyond that.
 constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072, SORT_TILE_FEW = 256;
 constexpr int SORT_SLOTS = 1024;  // workgroups that what is less than a round of them is spread over, at most
 constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
@@ -650,6 +770,7 @@ constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 constexpr int PART_COUNTED = 64;    // entries of a part whose order is found by counting, at most
 constexpr int PART_OF_WAVE = 512;   // of one that a wave sorts alone
+constexpr int WINDOW = 64 + 4;      // keys of a wave's window, and some that are above all others
 constexpr int GROUP_OF_WAVE = 256;  // of a group of ties that a wave deals with alone
 static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
 
@@ -729,18 +850,31 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
     }
 }
 
-template <int TOK>
-struct token_words { uint64_t a, b; };
-template <int TOK>
-__device__ __forceinline__ token_words<TOK> words_at(const int32_t *__restrict__ p, int32_t *second) {
-    const tok4 t = *reinterpret_cast<const tok4 *>(p);
-    *second = t.y;
-    if (TOK == 4)
-        return {((uint64_t)(uint32_t)(t.x + 1) << 32) | (uint32_t)(t.y + 1),
-                ((uint64_t)(uint32_t)(t.z + 1) << 32) | (uint32_t)(t.w + 1)};
-    const tok2 u = *reinterpret_cast<const tok2 *>(p + 4);
-    return {((uint64_t)(uint32_t)(t.x + 1) << 42) | ((uint64_t)(uint32_t)(t.y + 1) << 21) | (uint32_t)(t.z + 1),
-            ((uint64_t)(uint32_t)(t.w + 1) << 42) | ((uint64_t)(uint32_t)(u.x + 1) << 21) | (uint32_t)(u.y + 1)};
+// The text in lines, see k_layout.
+struct packed_text {
+    const uint32_t *lines;
+    int bits;  // of a code
+    int step;  // whole codes in the 128 R bits that are compared at a time
+};
+// 128 R bits of the tokens from position q on
+template <int R>
+struct token_bits { uint64_t w[2 * R]; };
+template <int R>
+__device__ __forceinline__ token_bits<R> bits_at(const packed_text &t, uint32_t q) {
+    const uint32_t bit = (q & (LINE_POS - 1)) * (uint32_t)t.bits, s = bit & 31u;
+    const uint32_t *p = t.lines + (((int64_t)(q / LINE_POS) * 32) + (bit >> 5));
+    uint32_t d[4 * R + 1];
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(p + 4 * k);
+        d[4 * k] = v.x; d[4 * k + 1] = v.y; d[4 * k + 2] = v.z; d[4 * k + 3] = v.w;
+    }
+    d[4 * R] = p[4 * R];
+    auto word = [&](int i) { return s ? __builtin_amdgcn_alignbit(d[i], d[i + 1], 32u - s) : d[i]; };
+    token_bits<R> r;
+#pragma unroll
+    for (int k = 0; k < 2 * R; k++) r.w[k] = ((uint64_t)word(2 * k) << 32) | word(2 * k + 1);
+    return r;
 }
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
@@ -785,13 +919,13 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
     }
 }
 
-template <int TOK, bool MORE>
+template <int R, bool MORE>
 __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
                                                   const uint32_t *__restrict__ starts,
                                                   const sort_bound *__restrict__ bounds,
                                                   const sort_cut *__restrict__ cuts,
                                                   const sort_range *__restrict__ more, entry_shape f,
-                                                  const int32_t *__restrict__ text, int32_t D,
+                                                  packed_text text, int32_t D,
                                                   const uint32_t *__restrict__ cdf, int32_t n_codes,
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
                                                   int32_t *__restrict__ samples, int32_t *__restrict__ bucket) {
@@ -986,13 +1120,17 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
         }
         return true;
     };
-    // how the 2 TOK tokens at q compare to those of mx and my
-    auto compare_to = [&](const int32_t *q, const token_words<TOK> &mx, const token_words<TOK> &my, bool *lt, bool *eq) {
-        int32_t unused;
-        const token_words<TOK> x = words_at<TOK>(q, &unused), y = words_at<TOK>(q + TOK, &unused);
-        const bool e1 = x.a == mx.a, e2 = x.b == mx.b, e3 = y.a == my.a, e4 = y.b == my.b;
-        *lt = !e1 ? x.a < mx.a : !e2 ? x.b < mx.b : !e3 ? y.a < my.a : y.b < my.b;
-        *eq = e1 && e2 && e3 && e4;
+    // how the tokens at q compare to those of `mid`
+    auto compare_to = [&](uint32_t q, const token_bits<R> &mid, bool *lt, bool *eq) {
+        const token_bits<R> x = bits_at<R>(text, q);
+        bool same = true, less = false;
+#pragma unroll
+        for (int k = 2 * R - 1; k >= 0; k--) {
+            less = x.w[k] < mid.w[k] || (x.w[k] == mid.w[k] && less);
+            same = same && x.w[k] == mid.w[k];
+        }
+        *lt = less;
+        *eq = same;
     };
     // Long groups (the entries of a group share their part): the whole workgroup splits them as split_group
     // does, until what is left of them is short enough for a wave.  What has agreed on D tokens falls
@@ -1009,9 +1147,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             if (left == 0) break;
             const uint32_t item = s_todo[left - 1];
             const int p = (int)(item & 0xffffu), h = (int)(item >> 16), k = next_first(p + 1) - p;
-            int32_t unused;
-            const int32_t *mid = text + (int64_t)s_pos[p + k / 2] + h;
-            const token_words<TOK> mx = words_at<TOK>(mid, &unused), my = words_at<TOK>(mid + TOK, &unused);
+            const token_bits<R> mid = bits_at<R>(text, s_pos[p + k / 2] + (uint32_t)h);
             uint32_t pos[SORT_ITEMS];
 #pragma unroll
             for (int q = 0; q < SORT_ITEMS; q++) {
@@ -1020,7 +1156,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
                 if (q * CT < k) {
                     if (j < k) {
                         pos[q] = s_pos[p + j];
-                        compare_to(text + (int64_t)pos[q] + h, mx, my, &lt, &eq);
+                        compare_to(pos[q] + (uint32_t)h, mid, &lt, &eq);
                     }
                     const uint64_t bl = __ballot(lt), be = __ballot(eq);
                     if (lane == 0) { s_class[0][q * CW + w] = bl; s_class[1][q * CW + w] = be; }
@@ -1040,7 +1176,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
                 if (lane == 63) s_before[64] = inc;
             }
             __syncthreads();
-            const int nl = (int)(s_before[64] & 0xffffu), ne = (int)(s_before[64] >> 16), next_h = h + 2 * TOK;
+            const int nl = (int)(s_before[64] & 0xffffu), ne = (int)(s_before[64] >> 16), next_h = h + text.step;
 #pragma unroll
             for (int q = 0; q < SORT_ITEMS; q++) {
                 const int j = q * CT + tid, run = q * CW + w;
@@ -1070,79 +1206,75 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     const int share = (n + CW - 1) / CW;
     const int s_begin = next_first(w * share < n ? w * share : n);
     const int s_end = next_first((w + 1) * share < n ? (w + 1) * share : n);
-    uint4 *win = s_area + w * 64;
+    uint64_t *win = reinterpret_cast<uint64_t *>(s_area) + w * WINDOW;
     uint16_t *list = reinterpret_cast<uint16_t *>(s_pos + SORT_CAP) + s_begin;
-    // place of this lane's entry among its group's lanes [lo, hi), with the group it gets there
-    struct placed { int to, less, before, same; };
-    auto place_by = [&](const token_words<TOK> &x, int lo, int hi) {  // (x is in the wave's window)
-        placed r = {lane, 0, 0, 0};
-        for (int j = lo; j < hi; j++) {
-            const uint4 o = win[j];
-            const uint64_t oa = ((uint64_t)o.y << 32) | o.x, ob = ((uint64_t)o.w << 32) | o.z;
-            const bool ea = oa == x.a, eb = ob == x.b;
-            r.less += oa < x.a || (ea && ob < x.b) ? 1 : 0;
-            r.same += ea && eb ? 1 : 0;
-            r.before += ea && eb && j < lane ? 1 : 0;
-        }
-        if (lo < hi) r.to = lo + r.less + r.before;
-        return r;
-    };
-    auto show = [&](int at, const token_words<TOK> &x) {
-        win[at] = make_uint4((uint32_t)x.a, (uint32_t)(x.a >> 32), (uint32_t)x.b, (uint32_t)(x.b >> 32));
-    };
-    // Orders the groups `first` (bits: lanes where one starts) of a window of len lanes by the 2 TOK
-    // tokens x, y of every lane's entry; lane q holds place `at`.  Moves the positions in s_pos, marks
+    if (lane < WINDOW - 64) win[64 + lane] = ~0ull;
+    // Orders the groups `first` (bits: lanes where one starts) of a window of len lanes by the
+    // tokens x of every lane's entry; lane q holds place `at`.  Moves the positions in s_pos, marks
     // new groups in s_first; true where the place's group has more than one entry still.
-    auto order = [&](uint64_t first, int len, int at, uint32_t pos, const token_words<TOK> &x,
-                     const token_words<TOK> &y, int &to) {
-        bool open = false;
-        to = lane;
-        int lo = 0, hi = 0;
-        auto group = [&]() {
-            if (lane < len) {
-                lo = 63 - __builtin_clzll(first & ((2ull << lane) - 1ull));
-                const uint64_t behind = lane == 63 ? 0ull : first >> (lane + 1);
-                hi = behind ? lane + 1 + __builtin_ctzll(behind) : 64;
-                hi = hi < len ? hi : len;
+    // An entry is compared to its group's first one only: where it differs first (by words of 32 bits), whether it is less there
+    // and the word itself make a key that says how entries go, but among those that differ from the first one at
+    // the same place and in the same way, which another round orders by the first of them.  A place is the number of
+    // lower keys (which end in the lane's number, and begin with the group's, so that there is nothing to count
+    // but what is less, four keys at a time).  (Counting by
+    // all bits, 128 at a time, takes four compares of 64 bits for what takes one here.)
+    auto order = [&](uint64_t first, int len, int at, uint32_t pos, const token_bits<R> &x) {
+        constexpr uint32_t SAME = 4 * R;
+        first |= len < 64 ? ~0ull << len : 0ull;  // (lanes without an entry: groups of one)
+        const uint64_t was = first;
+        int to = lane;  // where the lane's entry is by now
+        for (bool later = false;; later = true) {
+            const int lo = 63 - __builtin_clzll(first & ((2ull << to) - 1ull));
+            const uint64_t behind = first >> 1 >> to;
+            const int hi = behind ? to + 1 + __builtin_ctzll(behind) : 64;
+            const int head = later ? (int)(win[lo] & 63u) : lo;  // the lane of the group's first entry
+            uint64_t mine = 0, its = 0;
+            uint32_t word = SAME;
+#pragma unroll
+            for (int k = 2 * R - 1; k >= 0; k--) {
+                const uint64_t h = ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)(x.w[k] >> 32)) << 32) |
+                                   (uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)x.w[k]);
+                if (x.w[k] != h) { mine = x.w[k]; its = h; word = 2 * k; }
             }
-            open = hi - lo > 1;
-        };
-        group();
-        if (!__any(open)) return false;
-        show(lane, x);
-        wave_sync();
-        placed r = place_by(x, open ? lo : 0, open ? hi : 0);
-        to = r.to;
-        wave_sync();
-        show(to, y);
-        if (open) {
+            const bool low = (uint32_t)(mine >> 32) == (uint32_t)(its >> 32) && word != SAME;
+            const uint32_t m = low ? (uint32_t)mine : (uint32_t)(mine >> 32);
+            if (low) word++;
+            const uint32_t kind = mine < its ? word : 2 * SAME - word;  // (SAME: agrees in all words)
+            const uint64_t key = ((uint64_t)(((uint32_t)lo << 11) | (kind << 6) | (m >> 26)) << 32) | (m << 6) | (uint32_t)lane;
+            wave_sync();
+            win[to] = key;
+            wave_sync();
+            uint32_t less = 0;
+            for (int j = lo; j < hi; j += 4) {
+                const uint64_t k0 = win[j], k1 = win[j + 1], k2 = win[j + 2], k3 = win[j + 3];
+                less += k0 < key ? 1u : 0u;
+                less += k1 < key ? 1u : 0u;
+                less += k2 < key ? 1u : 0u;
+                less += k3 < key ? 1u : 0u;
+            }
+            to = lo + (int)less;
+            wave_sync();
+            win[to] = key;
+            wave_sync();
+            const uint64_t here = win[lane], before = lane > 0 ? win[lane - 1] : ~0ull;
+            const bool starts = (here ^ before) >= 64u;
+            first = __ballot(starts);
+            if (!__any(!starts && ((uint32_t)(here >> 38) & 31u) != SAME)) break;
+        }
+        if (lane < len) {
             s_pos[at + to - lane] = pos;
-            if (r.before == 0 && r.less > 0) set_first(at + to - lane);
+            if ((first & ~was) >> lane & 1ull) set_first(at);
         }
         wave_sync();
-        first = __ballot(lane < len && is_first(at));
-        group();
-        if (!__any(open)) return false;
-        const uint4 o = win[lane];
-        pos = s_pos[at];
-        const token_words<TOK> v = {((uint64_t)o.y << 32) | o.x, ((uint64_t)o.w << 32) | o.z};
-        r = place_by(v, open ? lo : 0, open ? hi : 0);
-        wave_sync();
-        if (open) {
-            s_pos[at + r.to - lane] = pos;
-            if (r.before == 0 && r.less > 0) set_first(at + r.to - lane);
-        }
-        wave_sync();
-        return lane < len && !(is_first(at) && is_first(at + 1));
+        const uint64_t alone = first & ((first >> 1) | (1ull << 63));
+        return !((alone >> lane) & 1ull);
     };
 
-    // A group too long for a window, places [p, p + k), is split in three by the 2 TOK tokens from
+    // A group too long for a window, places [p, p + k), is split in three by the tokens from
     // h on: entries below, at and above those of its middle entry, each in the order that they
     // had.  The middle part is done with these tokens, which s_done notes at its first place.
     auto split_group = [&](int p, int k, int h) {
-        int32_t unused;
-        const int32_t *mid = text + (int64_t)s_pos[p + k / 2] + h;
-        const token_words<TOK> mx = words_at<TOK>(mid, &unused), my = words_at<TOK>(mid + TOK, &unused);
+        const token_bits<R> mid = bits_at<R>(text, s_pos[p + k / 2] + (uint32_t)h);
         uint32_t pos[GROUP_OF_WAVE / 64];
         uint64_t below[GROUP_OF_WAVE / 64], equal[GROUP_OF_WAVE / 64];
         int nl = 0, ne = 0;
@@ -1151,7 +1283,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             bool lt = false, eq = false;
             if (q * 64 + lane < k) {
                 pos[q] = s_pos[p + q * 64 + lane];
-                compare_to(text + (int64_t)pos[q] + h, mx, my, &lt, &eq);
+                compare_to(pos[q] + (uint32_t)h, mid, &lt, &eq);
             }
             below[q] = __ballot(lt);
             equal[q] = __ballot(eq);
@@ -1188,7 +1320,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
         if ((open >> lane) & 1ull) list[m + __popcll(open & ((1ull << lane) - 1ull))] = (uint16_t)(s + lane);
         m += __popcll(open);
     }
-    for (int h = 2; m > 0 && h < D; h += 2 * TOK) {  // (entries that tie agree on two tokens)
+    for (int h = 2; m > 0 && h < D; h += text.step) {  // (entries that tie agree on two tokens)
         int out = 0;
         wave_sync();
         for (int at = 0; at < m;) {
@@ -1212,15 +1344,12 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
                 continue;
             }
             uint32_t pos = 0;
-            token_words<TOK> x = {0, 0}, y = {0, 0};
+            token_bits<R> x = {};
             if (lane < len) {
                 pos = s_pos[place];
-                int32_t unused;
-                x = words_at<TOK>(text + (int64_t)pos + h, &unused);
-                y = words_at<TOK>(text + (int64_t)pos + h + TOK, &unused);
+                x = bits_at<R>(text, pos + (uint32_t)h);
             }
-            int to;
-            const bool open = order(first, len, place, pos, x, y, to);
+            const bool open = order(first, len, place, pos, x);
             const uint64_t om = __ballot(open);
             if (open) list[out + __popcll(om & ((1ull << lane) - 1ull))] = (uint16_t)place;
             out += __popcll(om);
@@ -1512,6 +1641,13 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
 
+// Codes to a block of the table that k_layout has in LDS: 2^shift.
+static int block_shift(int32_t vocab) {
+    int s = 1;
+    while (s < CDF_MAX_SHIFT && ((int64_t)vocab + 1) >> s >= CDF_BLOCKS) s++;
+    return s;
+}
+int64_t sd_code_blocks(int32_t vocab) { return (((int64_t)vocab + 1) >> block_shift(vocab)) + 2; }
 int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
 constexpr int COUNT_COPIES = 8;  // of the sample's counts, where they are small
 int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? COUNT_COPIES : 1; }
@@ -1534,8 +1670,21 @@ void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t 
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (copies == 1 ? k_code_weights<1> : k_code_weights<COUNT_COPIES>), dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
               (uint32_t)ends, c->code_partials);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_cdf, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
-              c->code_partials, c->code_cdf);
+              c->code_partials, c->code_cdf, block_shift(c->cfg.vocab), c->code_blocks);
 }
+
+// Bits of a token's code in the lines, and words that a line holds from any code on (29 codes of 17 bits, 25 of 18),
+// a multiple of four of them.  (The lines lie where pairs of a radix sort go if one has to follow: k_code_sort
+// over what fits a workgroup comes before it.)
+static int line_bits(int32_t vocab) {
+    const int b = sd_bits_for((uint64_t)vocab);
+    return b < LINE_BITS_MIN ? LINE_BITS_MIN : b;
+}
+static int line_words(int bits) {
+    const int w = (LINE_POS - 1 - (LINE_POS - 1) * bits / 32) / 4 * 4;
+    return w < 12 ? w : 12;
+}
+static uint32_t *line_room(const sd_ctx *c) { return c->b_vals[1]; }
 
 static dim3 layout_grid(int64_t N, int items) { return dim3((unsigned)((N + SD_TEXT_PAD + CT * items - 1) / (CT * items))); }
 
@@ -1543,9 +1692,9 @@ void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_
                int32_t *text, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     const bool small = plan_for(N).small_tiles;
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (small ? k_layout<SMALL_ITEMS, false> : k_layout<LARGE_ITEMS, false>),
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (small ? k_layout<SMALL_ITEMS, TEXT_ONLY> : k_layout<LARGE_ITEMS, TEXT_ONLY>),
               layout_grid(N, small ? SMALL_ITEMS : LARGE_ITEMS), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
-              c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (uint32_t *)nullptr, 0, 0, (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr);
+              c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (const uint32_t *)nullptr, 0, (uint32_t *)nullptr, 0, 0, (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr, (uint32_t *)nullptr, 0);
 }
 
 // An entry's 64 bits: whether they hold what is needed of an input.
@@ -1587,10 +1736,12 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
 
 // the tiles, or n ranges `more`
 static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, const sort_range *more, int n, entry_shape f,
-                        const int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
-    const bool wide = c->cfg.vocab >= (1 << 21) - 1;
-    SD_LAUNCH(c, SD_K_CODE_SORT, st, (more ? (wide ? k_code_sort<4, true> : k_code_sort<6, true>) : wide ? k_code_sort<4, false> : k_code_sort<6, false>),
-              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, more, f, text, c->cfg.D, c->code_cdf,
+                        int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
+    const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
+    const packed_text packed = {line_room(c), bits, 128 * R / bits};
+    SD_LAUNCH(c, SD_K_CODE_SORT, st, (more ? (R == 3 ? k_code_sort<3, true> : R == 2 ? k_code_sort<2, true> : k_code_sort<1, true>) :
+                                      R == 3 ? k_code_sort<3, false> : R == 2 ? k_code_sort<2, false> : k_code_sort<1, false>),
+              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, more, f, packed, c->cfg.D, c->code_cdf,
               c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
 
@@ -1616,9 +1767,10 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     const int chunks = (int)((ntiles + per_chunk - 1) / per_chunk);
     const bool few = p.small_tiles && p.bits2 == 0 && chunks == 1;
     const dim3 grid1((unsigned)ntiles), block(CT);
-    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_layout<SMALL_ITEMS, true> : k_layout<LARGE_ITEMS, true>),
+    const bool by_block = sd_code_blocks(c->cfg.vocab) <= CDF_BLOCKS + 1;
+    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_layout<SMALL_ITEMS, CODES_DIRECT> : by_block ? k_layout<LARGE_ITEMS, CODES_BY_BLOCK> : k_layout<LARGE_ITEMS, CODES_DIRECT>),
               layout_grid(N, p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS), block, 0, tokens, offs, n_seq, n_tokens, text,
-              c->cfg.vocab, c->d_err, c->code_cdf, keys, 32 - f.bits1, bins1, hist, ntiles, few ? 0 : per_chunk, c->code_sums);
+              c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks, block_shift(c->cfg.vocab), keys, 32 - f.bits1, bins1, hist, ntiles, few ? 0 : per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab));
     if (!few)
         SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
               c->code_sums, chunks, starts1, (uint32_t)N);
@@ -1636,7 +1788,7 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
               c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, c->h_flag);
     const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
-    sort_ranges(c, ent1, t, nullptr, t.tiles, f, text, sa, tok1, bucket, st);
+    sort_ranges(c, ent1, t, nullptr, t.tiles, f, sa, tok1, bucket, st);
     return asked;
 }
 
@@ -1652,7 +1804,7 @@ sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t
     const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
     const int ranges = (int)told[REST_RANGES], n = (int)told[REST_LONG];
     const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
-    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, t.more, ranges, f, text, sa, tok1, bucket, st);
+    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, t.more, ranges, f, sa, tok1, bucket, st);
     if (n == 0) return SD_OK;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
     uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;

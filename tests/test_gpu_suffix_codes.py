@@ -432,3 +432,50 @@ def test_entropy_around_chunks_and_waves(N, D):
     assert weight == want_weight
     # binary64 sums of the same terms in another order, as in test_entropy_matches_oracle
     assert got == pytest.approx(want, rel=1e-9, abs=1e-12)
+
+
+@pytest.mark.parametrize("vocab", [300, 65_535, 65_536, 152_064, (1 << 20) - 1, 1 << 20, (1 << 21) - 1, (1 << 24) - 1, 1 << 24])
+def test_ties_by_the_bits_of_the_lines(vocab):
+    """Copies of one stretch that differ in one token, by one, at every distance that is compared and at every place within
+    a line: codes of 16 to 25 bits, three, two and one times 128 bits a step.  Sixty of them tie at the
+    start, some with several of the others' differences; their order inside a window takes several rounds."""
+    rng = np.random.default_rng(vocab)
+    D = 64
+    base = rng.integers(1, vocab - 1, D + 6).astype(np.int32)
+    docs = []
+    for k in list(range(2, D + 4)) + [0] * 5:
+        d = base.copy()
+        if k:
+            d[k] += 1 if k & 1 else -1
+        if k % 3 == 0:
+            d[min(k + 7, len(d) - 1)] = 0
+        if k % 7 == 0:
+            d[11] = vocab - 1
+        front = rng.integers(0, vocab, (5 * k) % 37).astype(np.int32)
+        docs += [np.concatenate([front, d]), np.concatenate([d[:k + 1], d])]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, 3 * sum(len(d) + 1 for d in docs))
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+        g.insert_global(docs[::-1])
+        _check(g, docs + docs[::-1], D)
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("vocab", [900, 8191, 8192, 152_064, 524_286, 524_287])
+def test_intervals_by_blocks(vocab):
+    """More than 2^22 positions: intervals by blocks of 2 to 128 codes, or in memory where that takes more blocks than the
+    table has; tokens of like frequency, and every 97th one a hundred times as frequent as the ones around it."""
+    rng = np.random.default_rng(vocab)
+    D, n = 12, 4_200_000
+    t = rng.integers(0, vocab, n).astype(np.int32)
+    some = rng.random(n) < 0.5
+    t[some] = (t[some] // 97 * 97) % (vocab // 3 + 1)
+    docs = np.split(t, np.sort(rng.integers(0, n, 3000)))
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n + len(docs))
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
