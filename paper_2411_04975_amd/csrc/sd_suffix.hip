@@ -94,12 +94,13 @@ __device__ __forceinline__ int wave_lower_bound(AT at, int n, int64_t key) {
 // additions to one address, at some 30 ns each.
 // What it found goes into one of several copies of the counts: frequent tokens lie next to each
 // other in many vocabularies, and additions to one line queue up just the same (10M tokens of a
-// Zipf law: 24 us, 75 with one copy).
+// Zipf law: 24 us, 75 with one copy), and 32 neighbouring tokens lie next to each other in the LDS table, so that lanes next
+// to each other add to one line in one go (9.5 us; 10M tokens of like frequency 14.4 -> 14.1).
 constexpr int64_t SAMPLE_MIN = 4096;   // runs: a bin of a 256-way split sees 1000 of their tokens
 constexpr int SAMPLE_ONE_IN = 64;      // a token that goes unseen has a few hundred occurrences at most
 constexpr int64_t SAMPLE_MAX = 32768;  // 16 * 64 * SAMPLE_MAX + 4 * 2^24, the weights' total, is below 2^27
 constexpr int RUNS_PER_WG = 16;
-constexpr int TABLE = 2048;
+constexpr int TABLE = 2048;  // 64 groups of 32 neighbouring tokens
 
 __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ tokens, int64_t n_tokens,
                                                     int32_t vocab, int64_t runs, int64_t C, uint32_t *__restrict__ counts,
@@ -123,13 +124,12 @@ __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ 
     for (int k = 0; k < RUNS_PER_WG / CW; k++) {
         if (tok[k] == -2) continue;
         const uint32_t code = (uint32_t)(tok[k] + 1);
-        uint32_t h = (code * 2654435761u) >> 21;
+        uint32_t h = ((code >> 5) * 2654435761u >> 26) << 5 | (code & 31u);
         int probe = 0;
         for (; probe < 16; probe++) {
             const uint32_t old = atomicCAS(&s_tag[h], FREE, code);
             if (old == FREE || old == code) { atomicAdd(&s_num[h], 1u); break; }
-            h = (h + 1) & (TABLE - 1);
-
+            h = (h + 32) & (TABLE - 1);
         }
         if (probe == 16) atomicAdd(&cnt[code], 1u);
     }
