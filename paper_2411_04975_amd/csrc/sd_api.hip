@@ -32,7 +32,7 @@ bool dev_alloc(T **p, int64_t count, int64_t *acc) {
 void free_all(sd_ctx *c) {
     void *ptrs[] = {c->g_text, c->g_sa, c->g_bucket, c->g_tok1, c->g_tok1s, c->b_keys[0], c->b_keys[1], c->b_vals[0],
                     c->b_vals[1], c->b_rank, c->b_flags, c->b_gid2, c->b_hist, c->b_partials, c->r_text,
-                    c->r_len, c->s_occ, c->s_unit_sa, c->d_err, c->s_unit_ticks, c->d_entropy,
+                    c->r_len, c->s_occ, c->s_unit_sa, c->d_err, c->s_unit_ticks,
                     c->d_round_flag, c->code_cdf, c->code_blocks, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -99,7 +99,7 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     ok = ok && dev_alloc(&c->g_tok1, column, ib);
     ok = ok && dev_alloc(&c->g_tok1s, cap / 16 + 64, ib);
     ok = ok && dev_alloc(&c->g_bucket, (int64_t)cfg->vocab + 2, ib);
-    ok = ok && dev_alloc(&c->b_keys[0], cap, sb) && dev_alloc(&c->b_keys[1], cap, sb);
+    ok = ok && dev_alloc(&c->b_keys[0], cap + 16, sb) && dev_alloc(&c->b_keys[1], cap, sb);
     ok = ok && dev_alloc(&c->b_vals[0], column, sb) && dev_alloc(&c->b_vals[1], column, sb);
     ok = ok && dev_alloc(&c->b_rank, column, sb) && dev_alloc(&c->b_flags, cap, sb) &&
          dev_alloc(&c->b_gid2, cap, sb);
@@ -117,7 +117,7 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     ok = ok && dev_alloc(&c->r_text, B * c->r_stride, sb) && dev_alloc(&c->r_len, ((B + 31) / 32) * 32 + B * SD_CTR_STRIDE * 2, sb);
     ok = ok && dev_alloc(&c->s_occ, B * ctx, sb);
     ok = ok && dev_alloc(&c->s_unit_sa, B * ctx, sb);
-    ok = ok && dev_alloc(&c->d_err, SD_DEVERR_N, sb) && dev_alloc(&c->d_entropy, 4, sb) &&
+    ok = ok && dev_alloc(&c->d_err, SD_DEVERR_N, sb) &&
          dev_alloc(&c->d_round_flag, 8, sb);
     c->tick_slots = (int32_t)(B < SD_TICK_SLOTS ? B : SD_TICK_SLOTS);
     ok = ok && dev_alloc(&c->s_unit_ticks, (int64_t)c->tick_slots * (2 * P * 4 + 16 * 8), sb);

@@ -32,16 +32,16 @@ __device__ __forceinline__ double wave_sum(double v) {
 // every token, but for the k-th last one of a document, k < D, which has k, so a document of n tokens lacks
 // m D - m (m + 1) / 2 with m = min(n, D).  The end markers are the first entries of the suffix array (code 0 is the
 // lowest): a wave takes one and looks for the marker before it, 64 tokens at a time.  (Reading the text
-// behind every position instead: 40 us of the 10M index, 6 so.)
-constexpr int SHORT_TB = 1024;
-constexpr unsigned SHORT_BLOCKS = 256;  // (an addition to one address each, at some 12 ns)
-__global__ __launch_bounds__(SHORT_TB) void k_short_ends(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
-                                                   const int32_t *__restrict__ bucket, int32_t D,
-                                                   unsigned long long *lost) {
-    const int lane = threadIdx.x & 63, waves = SHORT_TB / 64;
+// behind every position instead: 40 us of the 10M index.)
+constexpr int SHORT_BLOCKS = 256;  // (an addition to one address each, at some 12 ns)
+__device__ __forceinline__ void short_ends(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
+                                           const int32_t *__restrict__ bucket, int32_t D, int block, int blocks,
+                                           unsigned long long *lost) {
+    const int lane = threadIdx.x & 63;
+    constexpr int waves = TB / 64;
     const int64_t markers = bucket[1];
     unsigned long long sum = 0;  // (the same in all lanes)
-    for (int64_t i = (int64_t)blockIdx.x * waves + (threadIdx.x >> 6); i < markers; i += (int64_t)gridDim.x * waves) {
+    for (int64_t i = (int64_t)block * waves + (threadIdx.x >> 6); i < markers; i += (int64_t)blocks * waves) {
         const int64_t e = sa[i];
         int m = D;
         for (int k = 0; k < D; k += 64) {
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(SHORT_TB) void k_short_ends(const int32_t *__restri
         if (m > D) m = D;
         sum += (unsigned long long)m * D - (unsigned long long)m * (m + 1) / 2;
     }
-    __shared__ unsigned long long part[SHORT_TB / 64];
+    __shared__ unsigned long long part[waves];
     if (lane == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -64,47 +64,131 @@ __global__ __launch_bounds__(SHORT_TB) void k_short_ends(const int32_t *__restri
     }
 }
 
-typedef int32_t tok4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// The text in lines of 128 bytes: line k has, of the tokens from position 32 k on, where end markers are (64 bits), and then
+// the codes (token + 1, end marker 0) of as many as there is room for, 60 of 16 bits, one bit string with the first code's
+// highest bit first.  So what has to look at suffixes in any order reads one line and finds at least 960 / bits - 31 tokens in it,
+// from wherever it starts.
+constexpr int LINE_POS = 32, LINE_WORDS = 32, LINE_HEAD = 2, LINE_BITS_MIN = 16;
+constexpr int PACK_TILE = 2048, PACK_LOOK = 64;
+
+__device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N, int64_t n_lines, int bits, int64_t base,
+                                     uint32_t *__restrict__ lines) {
+    __shared__ uint32_t s_code[PACK_TILE + PACK_LOOK];
+    __shared__ uint64_t s_end[(PACK_TILE + PACK_LOOK) / 64];
+    const int tid = threadIdx.x;
+    for (int j = tid; j < PACK_TILE + PACK_LOOK; j += TB) {
+        const int64_t p = base + j;
+        const int32_t t = p < N ? text[p] : SD_END_TOKEN;
+        s_code[j] = (uint32_t)(t + 1);
+        const unsigned long long ends = __ballot(t < 0);
+        if ((tid & 63) == 0) s_end[j >> 6] = ends;
+    }
+    __syncthreads();
+    const int w = tid & (LINE_WORDS - 1), bit = (w - LINE_HEAD) * 32, c0 = w < LINE_HEAD ? 0 : bit / bits;
+    const int left0 = 32 - bits + (bit - c0 * bits), left1 = left0 - bits, right2 = bits - left1;
+#pragma unroll
+    for (int j = tid; j < PACK_TILE; j += TB) {
+        const int l = j / LINE_WORDS;
+        if (base / LINE_POS + l >= n_lines) break;
+        uint32_t v;
+        if (w < LINE_HEAD) {
+            v = reinterpret_cast<const uint32_t *>(s_end)[l + w];
+        } else {
+            const uint32_t *from = s_code + l * LINE_POS + c0;
+            v = from[0] << left0;
+            v |= left1 >= 0 ? from[1] << left1 : from[1] >> -left1;
+            if (left1 > 0) v |= from[2] >> right2;
+        }
+        lines[base + j] = v;
+    }
+}
+
+// What the kernels behind this one read: the sum that the documents' ends lack (the first SHORT_BLOCKS workgroups), a bit for
+// every place where another first token begins (in `marks`, zero before; MARK_TOKENS of them to a workgroup) and the lines.
+constexpr int MARK_TOKENS = 8 * TB;
+__global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
+                                                const int32_t *__restrict__ bucket, int64_t N, int32_t D, int32_t n_codes,
+                                                int mark_blocks, int64_t n_lines, int bits, unsigned long long *lost,
+                                                uint32_t *__restrict__ marks, uint32_t *__restrict__ lines) {
+    int b = (int)blockIdx.x;
+    if (b < SHORT_BLOCKS) {
+        short_ends(text, sa, bucket, D, b, SHORT_BLOCKS, lost);
+        return;
+    }
+    b -= SHORT_BLOCKS;
+    if (b < mark_blocks) {
+        for (int k = 0; k < MARK_TOKENS / TB; k++) {
+            const int32_t c = b * MARK_TOKENS + k * TB + (int32_t)threadIdx.x;
+            const int32_t at = c < n_codes ? bucket[c] : (int32_t)N;
+            if (at < N) atomicOr(&marks[at >> 5], 1u << (at & 31));
+        }
+        return;
+    }
+    pack(text, N, n_lines, bits, (int64_t)(b - mark_blocks) * PACK_TILE, lines);
+}
 
 // lcp[i], and len[i] where the compares with i's neighbours meet its end marker (D elsewhere): the
 // walk below asks only whether a suffix stops at a depth d < D that it shares with a neighbour.
-// Bound: gathers of text lines, one per suffix and 16 tokens.  A lane loads its own suffix only and
+// Bound: gathers of lines, one per suffix and 128 R bits of tokens (22 tokens of 17 bits).  A lane loads its own suffix only and
 // has the one before from the lane below, so a wave's 64 lanes give 62 entries: the first lane is the
-// last entry of the wave before, the last one the first entry of the wave behind.
+// last entry of the wave before, the last one the first entry of the wave behind.  Two entries that differ in the first token or
+// in the second, which the column has, need no line.
+// (Sixteen tokens of 32 bits a step, from the text itself, are one and a half lines: 280 us for 10M suffixes copied from templates.)
 constexpr int LCP_OUT = 62;
 
-__global__ __launch_bounds__(TB) void k_lcp_len(const int32_t *__restrict__ text,
-                                                const int32_t *__restrict__ sa, int64_t N, int32_t D,
+template <int R>
+__global__ __launch_bounds__(TB) void k_lcp_len(const uint32_t *__restrict__ lines, int bits, uint32_t step, uint32_t per_bit,
+                                                const int32_t *__restrict__ sa, const int32_t *__restrict__ tok1,
+                                                const uint32_t *__restrict__ marks, const int32_t *__restrict__ bucket, int64_t N, int32_t D,
                                                 uint8_t *__restrict__ lcp, uint8_t *__restrict__ len) {
     const int lane = threadIdx.x & 63;
     const int64_t i = ((int64_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6)) * LCP_OUT - 1 + lane;
     const bool here = i >= 0 && i < N;
-    const int32_t *w = text + (here ? sa[i] : 0);
-    bool open = here && i > 0 && lane > 0;  // the compare with the entry before goes on
-    int l = 0, L = D;
-    for (int k = 0; k < D; k += 16) {
+    const uint32_t p = here ? (uint32_t)sa[i] : 0u;
+    const int32_t second = here ? tok1[i] : 0, second_before = __shfl_up(second, 1);
+    const bool named = here && i >= bucket[1];  // (it is no end marker's)
+    const bool alike = named && lane > 0 && !(marks[i >> 5] >> (i & 31) & 1u);  // and the entry before starts with its token
+    bool open = alike && second == second_before && second >= 0;  // the compare with the entry before goes on
+    int l = alike ? 1 : 0, L = named && second < 0 ? 1 : D;  // (D is 2 at least)
+    for (int k = 2; k < D; k += (int)step) {
         const unsigned long long m = __ballot(open);
         if (m == 0) break;
         // this lane's tokens are asked for by itself or by the lane above
-        tok4 t[4] = {};
+        uint32_t d[4 * R + 1] = {};
+        uint64_t ends = 0;
+        const uint32_t q = p + (uint32_t)k, at = q & (LINE_POS - 1), bit = at * (uint32_t)bits + 31u;
         if (((m | m >> 1) >> lane) & 1ull) {
+            const uint32_t *line = lines + (int64_t)(q / LINE_POS) * LINE_WORDS;
+            const uint32_t *from = line + LINE_HEAD - 1 + (bit >> 5);  // 1 to 32 bits in front of the first one
 #pragma unroll
-            for (int q = 0; q < 4; q++) t[q] = *reinterpret_cast<const tok4 *>(w + k + 4 * q);
+            for (int c = 0; c < R; c++) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(from + 4 * c);
+                d[4 * c] = v.x; d[4 * c + 1] = v.y; d[4 * c + 2] = v.z; d[4 * c + 3] = v.w;
+            }
+            d[4 * R] = from[4 * R];
+            ends = *reinterpret_cast<const uint64_t *>(line) >> at;
         }
-        uint32_t end = 0, differ = 0;
+        uint32_t same = 128 * R;  // bits
 #pragma unroll
-        for (int q = 0; q < 16; q++) {
-            const int32_t a = t[q >> 2][q & 3], b = __shfl_up(a, 1);
-            end |= (uint32_t)(a < 0) << q;
-            differ |= (uint32_t)(a != b) << q;
+        for (int c = 4 * R - 1; c >= 0; c--) {
+            const uint32_t mine = __builtin_amdgcn_alignbit(d[c], d[c + 1], 31u - (bit & 31u));
+            const uint32_t x = mine ^ (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0x138 /* the lane below */, 0xf, 0xf, true);
+            const uint32_t n = (uint32_t)(x ? __builtin_clz(x) : -1) | 32u * c;
+            same = n < same ? n : same;
         }
-        differ |= end;
-        if (end && L == D && k + __builtin_ctz(end) < D) L = k + __builtin_ctz(end);
+        const uint32_t first_end = ends ? (uint32_t)__builtin_ctzll(ends) : 64u;
+        uint32_t n = same * per_bit >> 16;  // whole tokens
+        n = n < step ? n : step;
+        n = n < first_end ? n : first_end;
+        if (first_end < step && L == D && k + (int)first_end < D) L = k + (int)first_end;
         if (open) {
-            l = k + (differ ? __builtin_ctz(differ) : 16);
-            open = !differ;
+            l = k + (int)n;
+            open = n == step;
         }
     }
+    if (open && D == 2) l = 2;
     if (here && lane > 0 && lane <= LCP_OUT) {
         lcp[i] = (uint8_t)(l < D ? l : D);
         len[i] = (uint8_t)L;
@@ -262,19 +346,29 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
     if (N > 0) {
         // N <= g_cap bytes each, in two build buffers (16-byte aligned)
         uint8_t *lcp = reinterpret_cast<uint8_t *>(c->b_flags), *len = reinterpret_cast<uint8_t *>(c->b_gid2);
-        sd_fill_i32(reinterpret_cast<int32_t *>(c->d_entropy), 6, 0, st);
-        const unsigned ends = (unsigned)((c->g_docs + SHORT_TB / 64 - 1) / (SHORT_TB / 64));
-        hipLaunchKernelGGL(k_short_ends, dim3(ends < 1u ? 1u : ends < SHORT_BLOCKS ? ends : SHORT_BLOCKS), dim3(SHORT_TB), 0, st, c->g_text, c->g_sa,
-                           c->g_bucket, c->cfg.D, reinterpret_cast<unsigned long long *>(c->d_entropy + 2));
+        // the lines lie in a third one, as many words as positions and a few more
+        int bits = sd_bits_for((uint64_t)c->cfg.vocab);
+        if (bits < LINE_BITS_MIN) bits = LINE_BITS_MIN;
+        const int words = LINE_WORDS - 1 - LINE_HEAD - (LINE_POS - 1) * bits / 32, R = words >= 12 ? 3 : words >= 8 ? 2 : 1;
+        const int64_t n_lines = (N + c->cfg.D) / LINE_POS + 1;
+        uint32_t *lines = c->b_vals[1];
+        double *sums = reinterpret_cast<double *>(c->b_keys[0]);  // three, and behind them the marks
+        uint32_t *marks = reinterpret_cast<uint32_t *>(sums + 4);
+        sd_fill_i32(reinterpret_cast<int32_t *>(sums), 8 + N / 32 + 1, 0, st);
+        const int32_t n_codes = c->cfg.vocab + 1;
+        const int mark_blocks = (n_codes + MARK_TOKENS - 1) / MARK_TOKENS;
+        const int64_t pack_blocks = (n_lines * LINE_POS + PACK_TILE - 1) / PACK_TILE;
+        hipLaunchKernelGGL(k_prepare, dim3((unsigned)(SHORT_BLOCKS + mark_blocks + pack_blocks)), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_bucket, N, c->cfg.D,
+                           n_codes, mark_blocks, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
         const int64_t per_block = TB / 64 * LCP_OUT;
-        hipLaunchKernelGGL(k_lcp_len, dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st, c->g_text, c->g_sa, N,
-                           c->cfg.D, lcp, len);
+        hipLaunchKernelGGL((R == 3 ? k_lcp_len<3> : R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
+                           lines, bits, (uint32_t)(128 * R / bits), 65536u / (uint32_t)bits + 1u, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);
         const unsigned tiles = (unsigned)((N + ENT_TILE - 1) / ENT_TILE);
         hipLaunchKernelGGL(k_entropy, dim3(tiles < ENT_BLOCKS ? tiles : ENT_BLOCKS), dim3(ENT_TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
-                           c->g_bucket, lcp, len, N, c->cfg.D, c->d_entropy);
+                           c->g_bucket, lcp, len, N, c->cfg.D, sums);
         if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;
         double host[3];
-        if (hipMemcpyAsync(host, c->d_entropy, sizeof(host), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        if (hipMemcpyAsync(host, sums, sizeof(host), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return SD_ERR_HIP;
         acc[0] = host[0];

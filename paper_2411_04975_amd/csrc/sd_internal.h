@@ -90,7 +90,6 @@ struct sd_ctx {
     void *static_scratch = nullptr;  // this device's address of the library's static scratch array
     int32_t *d_err = nullptr;        // [SD_DEVERR_N]
     unsigned long long *d_counters = nullptr;  // [max_batch_slots][SD_CTR_STRIDE]
-    double *d_entropy = nullptr;     // [3] accumulators of sd_index_entropy
     int32_t *d_round_flag = nullptr; // [8] per doubling round: groups too long for the in-tile sort
 
     int n_cu = 0;                    // compute units of the device
