@@ -1807,6 +1807,10 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
                                            uint32_t &tick_merge, unsigned &nb) {
     const int lane = threadIdx.x & 63;
     const int rel_end = p.D - pl;  // nodes have indices below this
+    // (kept at hand: asked for where they are used they are a load in every pass)
+    int32_t den_mode = p.den_mode, linear = p.linear;
+    double min_score = p.min_score;
+    asm volatile("" : "+s"(den_mode), "+s"(linear), "+s"(min_score));
     int wlog = 0;
     while (wlog < 6 && (1 << wlog) < K - n) wlog++;
     while ((m << wlog) > TC_TOKENS) wlog--;
@@ -1880,14 +1884,14 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
     auto children = [&](uint64_t over, uint64_t firsts, int32_t re, int32_t par, int32_t dn, int first, double s) {
         const uint64_t le = (2ull << lane) - 1ull;
         const int32_t tok = sg.tc[lane_in(over) ? row + re : 0];
-        if (p.den_mode) {  // only the suffixes that go on
+        if (den_mode) {  // only the suffixes that go on
             const uint64_t ended = over & ballot64(tok < 0);
             dn -= __popcll((ended >> first) & (~0ull >> (64 - dn)));
         }
         const uint64_t S = firsts | (over & ballot64(lcp == re)), above = (S | ~over) & ~le;
         const int c = (above ? __builtin_ctzll(above) : 64) - lane;
         const double sc = c == dn ? s : s * ((double)c / (double)dn);  // x / x == 1 and s * 1 == s exactly
-        const uint64_t C = S & ballot64(tok >= 0) & ballot64(sc >= p.min_score);
+        const uint64_t C = S & ballot64(tok >= 0) & ballot64(sc >= min_score);
         // what follows the start of a child that stays, up to the next start (the addition carries through it)
         const uint64_t x = over & ~S, keep = C | (x & ~(x + ((C << 1) & x)));
         heads = (heads & ~over) | C;
@@ -1912,7 +1916,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
         // its roundings, so more suffixes score more, and as many score the same or nearly so.
         uint64_t T = heads;
         double s;
-        if (__builtin_expect(p.den_mode == 0, 1)) {
+        if (__builtin_expect(den_mode == 0, 1)) {
             if (T & (T - 1ull)) {
                 const uint32_t c = lane_in(heads) ? (uint32_t)f_c : 0u;
                 const uint32_t most = reduce_max_u32(c);
@@ -1930,7 +1934,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
             s = wave_max_f64(lane_in(heads) ? f_s : -__longlong_as_double(0x7ff0000000000000ll));
             T &= ballot64(f_s == s);
         }
-        if (p.linear) {  // chain variant: of the nodes at hand only the best one, the one with the lowest token
+        if (linear) {  // chain variant: of the nodes at hand only the best one, the one with the lowest token
             if (T & (T - 1ull)) {
                 const uint32_t tk = lane_in(T) ? (uint32_t)sg.tc[row + f_r] : DEAD;
                 T &= ballot64(tk == reduce_min_u32(tk));
@@ -2044,7 +2048,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
                         left = 0;  // (or rather its window has: the others wait until that is moved)
                     } else {
                         over |= range(w, hi);
-                        if (p.den_mode) left = 0;
+                        if (den_mode) left = 0;
                     }
                 }
             }
@@ -2464,6 +2468,17 @@ __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nod
     accept_store(b, a, max_nodes, aa, c);
 }
 
+// k_speculate's arguments as they lie in memory: its parameters, in their order.
+struct SpecArgs {
+    SpecParams p;
+    const int32_t *slot_ids;
+    sd_trees out;
+    int lds_per_wave;
+    AcceptArgs aa;
+    AppendArgs ap;
+};
+typedef const __attribute__((address_space(4))) SpecArgs *SpecArgsAt;
+
 // GenerateCandidateTree for one request per workgroup.  All waves first build the request's
 // occurrence lists together and match the P patterns against the global index; then each wave
 // takes runs of pattern lengths with equal counts from a queue in LDS, longest patterns first,
@@ -2480,9 +2495,8 @@ __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nod
 template <bool STATS, bool TICKS, bool ACCEPT>
 // (At least six waves per SIMD: two workgroups of twelve waves are resident together when two
 // requests share a compute unit; that is a bound on the kernel's registers.)
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_speculate(SpecParams p, const int32_t *__restrict__ slot_ids,
-                                                    sd_trees out, int lds_per_wave, AcceptArgs aa,
-                                                    AppendArgs ap) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_speculate(SpecParams, const int32_t *, sd_trees, int, AcceptArgs,
+                                                    AppendArgs) {
     extern __shared__ double smem[];
     __shared__ WgShared sh;
     // the wave index is the same in all lanes: keep it (and every LDS address derived from it)
@@ -2490,24 +2504,52 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     const int lane = threadIdx.x & 63, wave = uni((int32_t)(threadIdx.x >> 6)), nw = blockDim.x >> 6;
     const int b = blockIdx.x;
     unsigned nb = 0;
+    // The arguments are read where they lie, in three parts of the kernel each for itself (args_again).  As parameters
+    // they are all loaded at the start, where each group of them waits for the one before to be put away, and as there are more
+    // than scalar registers they wait in lanes of vector registers for their use, a move each.  (124 of those in
+    // the decode step's form, 57 so.  Decode steps of 256 requests over 10M tokens 18.9 -> 18.0 us, of 64 over 2.2M 17.8 -> 17.0,
+    // of 512 over 100M 21.3 -> 20.2, on independent tokens 27.5 -> 26.5; a draft of one request 11.9 -> 11.8.)
+    SpecArgsAt args_at = (SpecArgsAt)__builtin_amdgcn_kernarg_segment_ptr();
+    const SpecArgs *args = (const SpecArgs *)args_at;
+    auto args_again = [&]() {
+        asm volatile("" : "+s"(args_at));
+        args = (const SpecArgs *)args_at;
+    };
     // (no slot ids given: request b is slot b, and the chain of dependent loads that every
     // request starts with is one load shorter)
+    // What the first loads need, and in the form without the acceptance what the matching needs, is asked for in one go.
+    // (The address space is said because the compiler does not see any more where such a pointer comes from.  With the
+    // index's pointers here as well the decode step's form is slower again: 18.0 -> 18.4 us.)
+    typedef const __attribute__((address_space(1))) int32_t *words_at;
+    words_at slot_ids = (words_at)args->slot_ids, r_len = (words_at)args->p.r_len, r_text = (words_at)args->p.r_text;
+    int64_t r_stride = args->p.r_stride;
+    int32_t max_slots = args->p.max_slots, n_pat = args->p.P;
+    words_at in_n = nullptr, in_tok = nullptr, in_par = nullptr, in_tgt = nullptr;
+    int32_t in_max = 0;
+    if (ACCEPT) {
+        in_n = (words_at)args->out.d_n_nodes; in_tok = (words_at)args->out.d_tokens; in_par = (words_at)args->out.d_parents;
+        in_tgt = (words_at)args->aa.target; in_max = args->out.max_nodes;
+        asm volatile("" : "+s"(slot_ids), "+s"(r_len), "+s"(r_text), "+s"(r_stride), "+s"(max_slots), "+s"(n_pat),
+                          "+s"(in_n), "+s"(in_tok), "+s"(in_par), "+s"(in_tgt), "+s"(in_max));
+    } else {
+        asm volatile("" : "+s"(slot_ids), "+s"(r_len), "+s"(r_text), "+s"(r_stride), "+s"(max_slots), "+s"(n_pat));
+    }
     const int32_t slot = slot_ids ? uni(slot_ids[b]) : b;
-    const bool slot_ok = slot >= 0 && slot < p.max_slots;
-    if (!slot_ok && threadIdx.x == 0) atomicOr(&p.err[SD_DEVERR_SLOT], 1);
+    const bool slot_ok = slot >= 0 && slot < max_slots;
+    if (!slot_ok && threadIdx.x == 0) atomicOr(&args->p.err[SD_DEVERR_SLOT], 1);
     // (fused form: what the acceptance reads is asked for before anything waits for memory)
     AcceptIn ain = {};
-    if (ACCEPT && wave == 0) ain = accept_fetch(b, out.d_n_nodes, out.d_tokens, out.d_parents, out.max_nodes, aa);
+    if (ACCEPT && wave == 0) ain = accept_fetch(b, (const int32_t *)in_n, (const int32_t *)in_tok, (const int32_t *)in_par, in_max, AcceptArgs{(const int32_t *)in_tgt, nullptr, nullptr, nullptr, nullptr});
     // the context length before this launch appends anything
-    const int t_old = slot_ok ? uni(p.r_len[slot]) : 0;
-    const int32_t *x = p.r_text + (int64_t)(slot_ok ? slot : 0) * p.r_stride;
+    const int t_old = slot_ok ? uni(r_len[slot]) : 0;
+    const int32_t *x = (const int32_t *)(r_text + (int64_t)(slot_ok ? slot : 0) * r_stride);
 
     // MatchPattern on the global index for every pattern length, spread over the waves.  The
     // pattern tokens are fetched together with the context scan's first loads, and the
     // dependent loads of the matching follow once the wave has looked at its part of the scan.
     // The fused form starts the scan's loads, settles acceptance and append on the first wave
     // meanwhile, and fetches the pattern tokens once the appended tokens are in memory.
-    const int P = p.P;
+    const int P = n_pat;
     const uint64_t wg0 = TICKS ? wall_clock64() : 0;
     int2 *const s_sort = reinterpret_cast<int2 *>(smem);
     ScanState scan;
@@ -2520,7 +2562,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // launch.
     unsigned long long ctr_old = 0;
     if (wave == nw - 1 && lane < (ACCEPT ? SD_CTR_N : SD_CTR_ACCEPT_REQUESTS))
-        ctr_old = p.counters[(int64_t)b * SD_CTR_STRIDE + lane];
+        ctr_old = args->p.counters[(int64_t)b * SD_CTR_STRIDE + lane];
+    struct { words_at bucket, tok1, sa, text; int32_t N, max_nodes; } idx = {};
+    if (!ACCEPT) {
+        idx = {(words_at)args->p.g_bucket, (words_at)args->p.g_tok1, (words_at)args->p.g_sa, (words_at)args->p.g_text, args->p.g_N, args->p.max_nodes};
+        asm volatile("" : "+s"(idx.bucket), "+s"(idx.tok1), "+s"(idx.sa), "+s"(idx.text), "+s"(idx.N), "+s"(idx.max_nodes));
+    }
+    auto g_bucket = [&]() { return ACCEPT ? (words_at)args->p.g_bucket : idx.bucket; };
+    auto g_tok1 = [&]() { return (const int32_t *)(ACCEPT ? (words_at)args->p.g_tok1 : idx.tok1); };
+    auto g_sa = [&]() { return (const int32_t *)(ACCEPT ? (words_at)args->p.g_sa : idx.sa); };
+    auto g_text = [&]() { return ACCEPT ? (words_at)args->p.g_text : idx.text; };
+    auto g_N = [&]() { return ACCEPT ? args->p.g_N : idx.N; };
+    auto max_nodes = [&]() { return ACCEPT ? args->p.max_nodes : idx.max_nodes; };
     int t = t_old;
     // lane k < P: the k-th token from the context's end.  Loaded now for the context as it
     // stands; the fused form puts the tokens it appends in front afterwards, from LDS, so
@@ -2532,16 +2585,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             // LDS that the occurrence sort takes over afterwards
             int32_t *s_tgt = reinterpret_cast<int32_t *>(smem), *s_anc = s_tgt + 260, *s_ok = s_anc + 256;
             int32_t mt[4];
-            const Accepted a = accept_find(b, ain, out.d_tokens, out.d_parents, out.max_nodes, aa, s_tgt, s_anc, s_ok, mt);
-            const bool fits = append_fits(ap, slot, t_old, a.len);
+            const Accepted a = accept_find(b, ain, (const int32_t *)in_tok, (const int32_t *)in_par, in_max, AcceptArgs{(const int32_t *)in_tgt, nullptr, nullptr, nullptr, nullptr}, s_tgt, s_anc, s_ok, mt);
+            const bool fits = append_fits(args->ap, slot, t_old, a.len);
             if (fits) {
                 int done = 0;
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                    if (lane_in(a.nodes[r])) sh.newtok[done + __popcll(a.nodes[r] & lanemask_lt())] = append_token(ap, mt[r]);
+                    if (lane_in(a.nodes[r])) sh.newtok[done + __popcll(a.nodes[r] & lanemask_lt())] = append_token(args->ap, mt[r]);
                     done += __popcll(a.nodes[r]);
                 }
-                if (lane == 0) sh.newtok[a.len] = append_token(ap, a.bonus);
+                if (lane == 0) sh.newtok[a.len] = append_token(args->ap, a.bonus);
             }
             if (lane == 0) {
                 sh.t_new = fits ? t_old + a.len + 1 : t_old;
@@ -2565,14 +2618,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // matching and expansion; the load is older than the tail's, which has just been waited for)
     if (wave == nw - 1 && lane < SD_CTR_ACCEPT_REQUESTS) sh.ctr[lane] = ctr_old;
     // (the buckets of the last two tokens are asked for before the scan's words are looked at)
-    const bool two = P >= 2 && t >= 2 && p.g_N > 0;
+    const bool two = P >= 2 && t >= 2 && g_N() > 0;
     int32_t bv = 0;
     if (two && lane < 4) {
         const int32_t w = lane < 2 ? __builtin_amdgcn_readlane(tail, 1) : __builtin_amdgcn_readlane(tail, 0);
-        bv = p.g_bucket[w + 1 + (lane & 1)];
+        bv = g_bucket()[w + 1 + (lane & 1)];
         SD_CNT(4);
     }
-    request_occurrences<STATS, ACCEPT>(p, b, t, t_old, sh.newtok, x, s_sort, sh, scan, tail, nb, [&]() {
+    request_occurrences<STATS, ACCEPT>(args->p, b, t, t_old, sh.newtok, x, s_sort, sh, scan, tail, nb, [&]() {
         // What acceptance and append have to write, by the last wave, once it needs nothing more of what it has
         // asked for: a wave's loads and stores are waited for in order, and the first wave, which every other
         // one waits for, would wait for its stores with its share of the scan (0.4 us of a decode step).
@@ -2586,10 +2639,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 a.nodes[r] = ((uint64_t)(uint32_t)uni((int32_t)(sh.acc_nodes[r] >> 32)) << 32) | (uint32_t)uni((int32_t)sh.acc_nodes[r]);
             a.len = uni(sh.acc_len);
             a.bonus = uni(sh.acc_bonus);
-            int32_t *row = ap.r_text + (int64_t)slot * ap.stride;
+            int32_t *row = args->ap.r_text + (int64_t)slot * args->ap.stride;
             for (int i = lane; i < t - t_old; i += 64) row[t_old + i] = sh.newtok[i];
-            if (lane == 0 && t > t_old) ap.r_len[slot] = t;
-            accept_store(b, a, out.max_nodes, aa, ctr_old);
+            if (lane == 0 && t > t_old) args->ap.r_len[slot] = t;
+            accept_store(b, a, args->out.max_nodes, args->aa, ctr_old);
         }
     }, [&]() {
         // List form: the suffixes that start with the context's last two tokens are located once, by a
@@ -2620,8 +2673,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 int32_t at_i = 0;  // lane i: where suffix i starts
                 if (lo2 < hi2) {
                     const PairList r = hi2 - lo2 > SCAN_MAX
-                        ? pair_sampled<STATS>(p.g_tok1, p.g_tok1s, p.g_sa, __builtin_amdgcn_readlane(tail, 0), lo2, hi2)
-                        : pair_scanned<STATS>(p.g_tok1, p.g_sa, __builtin_amdgcn_readlane(tail, 0), lo2, hi2);
+                        ? pair_sampled<STATS>(g_tok1(), args->p.g_tok1s, g_sa(), __builtin_amdgcn_readlane(tail, 0), lo2, hi2)
+                        : pair_scanned<STATS>(g_tok1(), g_sa(), __builtin_amdgcn_readlane(tail, 0), lo2, hi2);
                     n2 = uni(r.n);
                     at_i = r.at;
                     if (wave == 0) SD_CNT(r.nb);
@@ -2643,12 +2696,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                     // every expansion for itself, behind the barrier, it took each of them two LDS round trips and
                     // one to memory, some 1.0 us of its 6 to 9.)
                     int wlog = 0;
-                    while (wlog < 6 && (1 << wlog) < p.max_nodes) wlog++;
+                    while (wlog < 6 && (1 << wlog) < max_nodes()) wlog++;
                     while ((n2 << wlog) > LIST_TOKENS) wlog--;
-                    const int need = 1 << wlog < p.max_nodes ? 1 << wlog : p.max_nodes;
+                    const int need = 1 << wlog < max_nodes() ? 1 << wlog : max_nodes();
                     const int rows = (n2 + lw - 1) / lw, row0 = wave * rows, row1 = row0 + rows < n2 ? row0 + rows : n2;
                     auto row = [&](int i) -> int32_t {
-                        return i >= 0 && i < row1 && lane < need ? p.g_text[__builtin_amdgcn_readlane(at_i, i & 63) + 2 + lane] : 0;
+                        return i >= 0 && i < row1 && lane < need ? g_text()[__builtin_amdgcn_readlane(at_i, i & 63) + 2 + lane] : 0;
                     };
                     constexpr int ROWS = 4;
                     int32_t before = row(row0 - 1), tk[ROWS];
@@ -2668,7 +2721,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                             int lim = ee[u] + 1 < P ? ee[u] + 1 : P;  // (0 for an empty place)
                             lim = lim < t ? lim : t;
                             const bool rd = ee[u] >= 0 && k < lim;
-                            v[u] = rd ? p.g_text[ee[u] - k] : tl;
+                            v[u] = rd ? g_text()[ee[u] - k] : tl;
                             if (rd) SD_CNT(4);
                         }
 #pragma unroll
@@ -2710,7 +2763,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         if (!search) return;
         for (int plA = 1 + wave; plA <= P; plA += 2 * nw) {
             const int plB = plA + nw;  // a wave takes its pattern lengths two at a time
-            const bool okA = plA <= t && p.g_N > 0, okB = plB <= P && plB <= t && p.g_N > 0;
+            const bool okA = plA <= t && g_N() > 0, okB = plB <= P && plB <= t && g_N() > 0;
             int32_t loA = 0, hiA = 0, loB = 0, hiB = 0;
             // lane k: pattern token k (from the tail: the row may not hold the appended tokens yet)
             const int32_t ta = __shfl(tail, (plA - 1 - lane) & 63), tb = __shfl(tail, (plB - 1 - lane) & 63);
@@ -2718,10 +2771,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             if (okA && lane < plA) SD_CNT(4);
             if (okB && lane < plB) SD_CNT(4);
             if (okA && okB && plB <= 32)
-                match_global_pair<STATS>(p, wkA, plA, wkB, plB, loA, hiA, loB, hiB, nb);
+                match_global_pair<STATS>(args->p, wkA, plA, wkB, plB, loA, hiA, loB, hiB, nb);
             else {
-                if (okA) match_global<STATS>(p, wkA, plA, loA, hiA, nb);
-                if (okB) match_global<STATS>(p, wkB, plB, loB, hiB, nb);
+                if (okA) match_global<STATS>(args->p, wkA, plA, loA, hiA, nb);
+                if (okB) match_global<STATS>(args->p, wkB, plB, loB, hiB, nb);
             }
             if (lane == 0) {
                 sh.g_lo[plA] = loA; sh.g_hi[plA] = hiA;
@@ -2733,17 +2786,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         // (in the decode step's form of the kernel.  The form without the acceptance had no register left for the
         // call when this came in; it has by now, at 78 of them, but what the call gives there has not been measured)
         if (ACCEPT) {
-            const unsigned cnt_chunks = occ_take_chunks<STATS>(nw, t, P, p.D - 1, p.occ_cap, p.key_toks,
-                                                               p.key_bits, p.alpha, tail, x, s_sort, sh);
+            const unsigned cnt_chunks = occ_take_chunks<STATS>(nw, t, P, args->p.D - 1, args->p.occ_cap, args->p.key_toks,
+                                                               args->p.key_bits, args->p.alpha, tail, x, s_sort, sh);
             SD_CNT(cnt_chunks);
         }
     });
     const uint64_t wg1 = TICKS ? wall_clock64() : 0;
+    args_again();
 
     // per-wave LDS: frontier (score, tok, par, lo, hi, dep), two trees (score, tok, par), staging
-    const int cap = p.max_nodes;
+    const int cap = args->p.max_nodes;
     Frontier f;
-    f.score = smem + (size_t)wave * (lds_per_wave / 8);
+    f.score = smem + (size_t)wave * (args->lds_per_wave / 8);
     double *const tsc0 = f.score + cap, *const tsc1 = tsc0 + cap;
     f.tok = (int32_t *)(tsc1 + cap);
     f.par = f.tok + cap; f.lo = f.par + cap; f.hi = f.lo + cap; f.dep = f.hi + cap;
@@ -2782,7 +2836,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             if (lane > 0) {
                 cgp = listed ? gsum_up : sh.g_hi[pl + 1] - sh.g_lo[pl + 1];
                 crp = sh.cnt[pl + 1];
-                alone = pl + 1 + (int)floor(p.alpha * (double)(pl + 1)) >= p.D;
+                alone = pl + 1 + (int)floor(args->p.alpha * (double)(pl + 1)) >= args->p.D;
             }
         }
         // a request-side list of one entry is the context's own tail: nothing follows it
@@ -2805,9 +2859,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 const int i0 = __builtin_ctzll(mk), i1 = 63 - __builtin_clzll(mk);
                 int least = i0 == i1 ? __builtin_amdgcn_readlane(shared, i0) >> 8
                                      : (int)reduce_min_u32(lane > i0 && lane <= i1 ? (uint32_t)shared & 255u : ~0u);
-                const int k = (int)floor(p.alpha * (double)pl);
+                const int k = (int)floor(args->p.alpha * (double)pl);
                 least = least < k ? least : k;
-                least = least < p.D - pl ? least : p.D - pl;
+                least = least < args->p.D - pl ? least : args->p.D - pl;
                 if (lane == 0) sh.top_bits = (unsigned long long)__double_as_longlong((double)least);
             }
         }
@@ -2840,7 +2894,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
             const int c = __builtin_amdgcn_readlane(cr, i);
             o = used;
             if (c > 64) {
-                if (used + c > p.max_ctx) { rnd++; o = 0; }
+                if (used + c > args->p.max_ctx) { rnd++; o = 0; }
                 used = o + c;
             }
         }
@@ -2858,7 +2912,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         const int add = lane == SD_CTR_GLOBAL_LIST ? (listed && two)
                         : lane == SD_CTR_GLOBAL_SEARCH ? (!listed && two)
                         : lane == SD_CTR_REQUEST_WIDE ? wide_r
-                        : lane == SD_CTR_OCC_IN_MEMORY ? (uni(sh.m) > p.occ_cap)
+                        : lane == SD_CTR_OCC_IN_MEMORY ? (uni(sh.m) > args->p.occ_cap)
                         : lane == SD_CTR_LIST_ROUNDS ? n_rounds - 1 : 0;
         if (lane < SD_CTR_ACCEPT_REQUESTS) sh.ctr[lane] += (unsigned long long)add;
     }
@@ -2880,16 +2934,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         bool hopeless;
         {
             const double top = uni(__longlong_as_double((long long)sh.top_bits));
-            hopeless = floor(p.alpha * (double)p_hi) < top;
+            hopeless = floor(args->p.alpha * (double)p_hi) < top;
         }
         for (int pl = hopeless ? 0 : p_hi; pl >= p_lo; pl--) {
             double total = 0.0;
             bool deepest = false;
-            const int n = run_unit<STATS, TICKS>(p, sh, b, t, x, src, pl, usa_off, f, sg, cur ? ttk1 : ttk0,
+            const int n = run_unit<STATS, TICKS>(args->p, sh, b, t, x, src, pl, usa_off, f, sg, cur ? ttk1 : ttk0,
                                           cur ? tpr1 : tpr0, cur ? tsc1 : tsc0, total, deepest, nb);
             int pstar = pl;  // shortest pattern of the run with this very tree
             if (!deepest)
-                while (pstar > p_lo && (int)floor(p.alpha * (double)(pstar - 1)) >= n) pstar--;
+                while (pstar > p_lo && (int)floor(args->p.alpha * (double)(pstar - 1)) >= n) pstar--;
             const int order = src * P + (pstar - 1);
             if (n > 0 && total > 0.0 &&
                 (best_o < 0 || total > best_s || (total == best_s && order < best_o))) {
@@ -2913,7 +2967,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         // per wave: start (absolute, low 32 bits), then ticks since the start at: occurrences
         // and global matches done, runs set up, this wave out of runs, barrier passed;
         // number of runs; occurrences of the last token
-        uint32_t *wt = p.wg_ticks + ((int64_t)b * 16 + wave) * 8;
+        uint32_t *wt = args->p.wg_ticks + ((int64_t)b * 16 + wave) * 8;
         wt[0] = (uint32_t)wg0; wt[1] = (uint32_t)(wg1 - wg0); wt[2] = (uint32_t)(wg2 - wg0);
         wt[3] = (uint32_t)(wg3 - wg0); wt[4] = (uint32_t)(wall_clock64() - wg0);
         wt[5] = (uint32_t)nruns; wt[6] = (uint32_t)sh.m; wt[7] = (uint32_t)nw;
@@ -2923,6 +2977,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // the winning wave: top SCORE, then the earliest unit in scan order (lane w looks at wave w;
     // units are distinct, so the second criterion leaves one wave).  A wave without that score is done.
+    args_again();
     const double ws = uni(__longlong_as_double((long long)sh.top_bits));
     if (wave == nw - 1 || (best_o >= 0 && best_s == ws) || (wave == 0 && ws == 0.0)) {
         int wo = -1, ww = -1;
@@ -2935,39 +2990,39 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 wo = __builtin_amdgcn_readlane(o, ww);
             }
         }
-        const int wsrc = wo >= p.P ? 1 : 0, wlen = wo - wsrc * p.P + 1;
+        const int wsrc = wo >= args->p.P ? 1 : 0, wlen = wo - wsrc * args->p.P + 1;
         if (wave == nw - 1 && lane_e < SD_CTR_ACCEPT_REQUESTS) {  // lane k: counter k of the drafting calls
             const int n = ww < 0 ? 0 : sh.best_n[ww];
             const bool tree = n > 0;
             const int add = lane_e == SD_CTR_REQUESTS ? 1 : lane_e == SD_CTR_TREES ? tree : lane_e == SD_CTR_NODES ? n
                             : lane_e == SD_CTR_MATCH_LEN ? (tree ? wlen : 0)
                             : lane_e == SD_CTR_FROM_REQUEST ? (tree && wsrc) : 0;
-            p.counters[(int64_t)b * SD_CTR_STRIDE + lane_e] = sh.ctr[lane_e] + (unsigned long long)add;
+            args->p.counters[(int64_t)b * SD_CTR_STRIDE + lane_e] = sh.ctr[lane_e] + (unsigned long long)add;
         }
         if (wave == (ww < 0 ? 0 : ww)) {
             const int n = ww < 0 ? 0 : best_n;
             const int kept = cur ^ 1;  // the buffer the wave's best tree was left in
             const int32_t *btk = kept ? ttk1 : ttk0, *bpr = kept ? tpr1 : tpr0;
             const double *bsc = kept ? tsc1 : tsc0;
-            const int64_t ob = (int64_t)b * out.max_nodes;
-            for (int i = lane_e; i < out.max_nodes; i += 64) {
+            const int64_t ob = (int64_t)b * args->out.max_nodes;
+            for (int i = lane_e; i < args->out.max_nodes; i += 64) {
                 const bool live = i < n;
-                out.d_tokens[ob + i] = live ? btk[i] : -1;
-                out.d_parents[ob + i] = live ? bpr[i] : -1;
-                out.d_scores[ob + i] = live ? bsc[i] : 0.0;
+                args->out.d_tokens[ob + i] = live ? btk[i] : -1;
+                args->out.d_parents[ob + i] = live ? bpr[i] : -1;
+                args->out.d_scores[ob + i] = live ? bsc[i] : 0.0;
                 SD_CNT(16);
             }
             if (lane_e == 0) {
-                out.d_n_nodes[b] = n;
-                out.d_tree_score[b] = ww >= 0 ? ws : 0.0;
-                out.d_match_len[b] = ww >= 0 ? wlen : 0;
-                out.d_source[b] = ww >= 0 ? wsrc : -1;
-                if (out.d_use_draft) out.d_use_draft[b] = (ww >= 0 && ws > p.tau) ? 1 : 0;
+                args->out.d_n_nodes[b] = n;
+                args->out.d_tree_score[b] = ww >= 0 ? ws : 0.0;
+                args->out.d_match_len[b] = ww >= 0 ? wlen : 0;
+                args->out.d_source[b] = ww >= 0 ? wsrc : -1;
+                if (args->out.d_use_draft) args->out.d_use_draft[b] = (ww >= 0 && ws > args->p.tau) ? 1 : 0;
                 SD_CNT(24);
             }
         }
     }
-    flush_count<STATS>(nb, p.algo_bytes + SD_K_SPECULATE);
+    flush_count<STATS>(nb, args->p.algo_bytes + SD_K_SPECULATE);
 }
 
 }  // namespace
