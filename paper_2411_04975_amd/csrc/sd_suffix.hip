@@ -929,7 +929,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
                                                   const uint32_t *__restrict__ cdf, int32_t n_codes,
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
                                                   int32_t *__restrict__ samples, int32_t *__restrict__ bucket) {
-    __shared__ uint64_t s_entry[SORT_CAP];         // later positions by place, and lists
+    __shared__ uint64_t s_entry[SORT_CAP + 4];     // later positions by place, and lists (up to three more are read)
     __shared__ uint4 s_area[SORT_PARTS / 8];       // counts per part, two per word; later windows
     __shared__ uint32_t s_start[SORT_BUCKETS + 1];  // places of the workgroup's buckets
     __shared__ uint32_t s_first[SORT_CAP / 32 + 4];  // bit per place: a group starts here
@@ -975,15 +975,22 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     int fine = 31 - __builtin_clz(SORT_PARTS / nb);
     if (fine > in_bucket) fine = in_bucket;
     const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
+    // (Looked up in the entry and not among the buckets' places, and parts counted four entries at a time: 10M independent
+    // tokens 90.8 -> 86.7 us, copied ones as before.)
+    const bool named = nb <= 1 << f.bits2;
     uint32_t part[SORT_ITEMS], rank[SORT_ITEMS];
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++) {
         const int j = k * CT + tid;
         if (j < n) {
-            int lo = 0, hi = nb;  // last bucket that starts at or before place j
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (s_start[mid] <= (uint32_t)j) lo = mid; else hi = mid;
+            int lo = 0;
+            if (named) {  // (the entry has the bucket's last bits)
+                lo = (int)(((uint32_t)(e[k] >> low_bits) >> in_bucket) - (uint32_t)b0) & ((1 << f.bits2) - 1);
+            } else {      // last bucket that starts at or before place j
+                for (int hi = nb; hi - lo > 1;) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_start[mid] <= (uint32_t)j) lo = mid; else hi = mid;
+                }
             }
             part[k] = ((uint32_t)lo << fine) + (((uint32_t)(e[k] >> low_bits) & key_mask) >> (in_bucket - fine));
             const uint32_t sh = (part[k] & 1u) * 16u;
@@ -1028,7 +1035,13 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             if (__builtin_expect(n_long > 0, 0) && hi - lo > PART_COUNTED)
                 less = (int)rank[k];  // (it stays where it is for now)
             else
-                for (int i = lo; i < hi; i++) less += s_entry[i] < e[k] ? 1 : 0;
+                for (int i = lo; i < hi; i += 4) {
+                    const uint64_t v0 = s_entry[i], v1 = s_entry[i + 1], v2 = s_entry[i + 2], v3 = s_entry[i + 3];
+                    less += v0 < e[k] ? 1 : 0;
+                    less += v1 < e[k] && i + 1 < hi ? 1 : 0;
+                    less += v2 < e[k] && i + 2 < hi ? 1 : 0;
+                    less += v3 < e[k] && i + 3 < hi ? 1 : 0;
+                }
             rank[k] = (uint32_t)(lo + less);
         }
     __syncthreads();
