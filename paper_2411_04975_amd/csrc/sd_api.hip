@@ -33,7 +33,7 @@ void free_all(sd_ctx *c) {
     void *ptrs[] = {c->g_text, c->g_sa, c->g_bucket, c->g_tok1, c->g_tok1s, c->b_keys[0], c->b_keys[1], c->b_vals[0],
                     c->b_vals[1], c->b_rank, c->b_flags, c->b_gid2, c->b_hist, c->b_partials, c->r_text,
                     c->r_len, c->s_occ, c->s_unit_sa, c->d_err, c->s_unit_ticks,
-                    c->d_round_flag, c->code_cdf, c->code_blocks, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
+                    c->d_round_flag, c->code_cdf, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (c->h_flag) (void)hipHostFree(c->h_flag);
@@ -108,10 +108,11 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     c->rest_table = c->b_ranges + code_ranges;
     c->rest_to = c->rest_table + code_starts;
     ok = ok && dev_alloc(&c->b_partials, c->b_partials_cap, sb);
-    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2, sb) && dev_alloc(&c->code_blocks, sd_code_blocks(cfg->vocab), sb) && dev_alloc(&c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), sb) &&
+    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2 + sd_code_blocks(cfg->vocab), sb) && dev_alloc(&c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), sb) &&
          dev_alloc(&c->code_partials, sd_code_parts(cfg->vocab), sb) && dev_alloc(&c->b_starts, code_starts, sb) &&
          dev_alloc(&c->code_sums, code_sums, sb) &&
          dev_alloc(&c->code_bucket, (int64_t)cfg->vocab + 2, sb);
+    if (ok) c->code_blocks = c->code_cdf + cfg->vocab + 2;
     ok = ok && hipHostMalloc((void **)&c->h_flag, 8 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess &&
          hipEventCreateWithFlags(&c->code_asked, hipEventDisableTiming) == hipSuccess;
     ok = ok && dev_alloc(&c->r_text, B * c->r_stride, sb) && dev_alloc(&c->r_len, ((B + 31) / 32) * 32 + B * SD_CTR_STRIDE * 2, sb);

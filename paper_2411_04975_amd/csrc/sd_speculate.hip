@@ -1089,6 +1089,17 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
         return;
     }
     frontier_close(f, hole);
+    if (nc > f.cap) {
+        // (children of one node, in the order of their tokens: the more suffixes the better, then the first one.  A
+        // pattern of one token has a tree of one or two nodes and dozens of candidates, 0.5 us each below.)
+        uint64_t left = C;
+        for (int k = 0; k < f.cap; k++) {
+            const uint32_t c = lane_in(left) ? (uint32_t)(hi - lo) : 0u;
+            const uint64_t most = ballot64(c == reduce_max_u32(c)) & left;
+            left &= ~(most & (0ull - most));
+        }
+        C &= ~left;
+    }
     while (C) {
         int src = __ffsll((unsigned long long)C) - 1;
         C &= C - 1;
