@@ -453,7 +453,7 @@ struct WgShared {
 // of which those from t_old on (appended meanwhile by the first wave) are taken from `newtok`
 // in LDS.  `between` is independent work of the caller (the global matches), run after this
 // wave has dealt with its part of the scan, while other waves may still be at it.
-// With EARLY every wave counts itself in (scan_done) once its hits are down, and `between` may
+// Every wave counts itself in (scan_done) once its hits are down, and `between` may
 // call occ_take_chunks, which then deals with a frequent last token's occurrences before the
 // barrier and says so in `early`.
 struct ScanState {
@@ -660,7 +660,7 @@ __device__ __attribute__((noinline)) unsigned occ_take_chunks(int nw, int t, int
     return nb;
 }
 
-template <bool STATS, bool EARLY, class Settle, class Between>
+template <bool STATS, class Settle, class Between>
 __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, int t, int t_old,
                                     const int32_t *newtok, const int32_t *x,
                                     int2 *s_sort, WgShared &sh, ScanState &st, int32_t tail,
@@ -736,16 +736,14 @@ __device__ __forceinline__ void request_occurrences(const SpecParams &p, int b, 
     settle();
     // (this wave's hits are down, and what settle() appends to the row if this is the wave that does: occ_take_chunks
     // reads both on any wave, before the barrier)
-    if (EARLY) {
-        wsync();
-        if (lane == 0) count_in(&sh.scan_done);
-    }
+    wsync();
+    if (lane == 0) count_in(&sh.scan_done);
     between();
     __syncthreads();
     const int m = sh.m;
     // (a frequent last token's occurrences may have been dealt with already, in parts of 64 by
     // the waves that came out of the caller's work early: see occ_take_chunks)
-    const bool early = EARLY && uni(sh.early) != 0;
+    const bool early = uni(sh.early) != 0;
     // A single occurrence is the context's own last token: nothing follows it, so no pattern
     // has a continuation in this index, and the counts stay at zero, which says just that.
     if (__builtin_expect(m <= 1, 1)) return;
@@ -2151,20 +2149,31 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b
             int32_t *usa = p.unit_sa + (int64_t)b * p.max_ctx + usa_off;
             const bool narrow = m <= 64, few = uni(sh.few) != 0;
             int w = 0;
-            for (int base = 0; base < m1; base += 64) {
-                int i = base + lane;
-                int2 o = make_int2(0, 0);
-                if (i < m1) o = occ_unpack(few ? sh.few_occ[i] : occ[i]);
-                if (i < m1) SD_CNT(4);
-                bool keep = i < m1 && o.y >= pl;
-                uint64_t mk = __ballot(keep);
-                if (keep) {
-                    int dst = w + __popcll(mk & lanemask_lt());
-                    if (narrow) sg.pos[dst] = o.x - pl + 1;
-                    else usa[dst] = o.x - pl + 1;
-                    SD_CNT(4);
+            // (256 records at a time, all loads of a trip in flight together: one after the other they took 3.7 us
+            // for 550 occurrences, on the slowest request's path)
+            constexpr int U = 4;
+            for (int base = 0; base < m1; base += 64 * U) {
+                uint32_t rec[U];
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int i = base + u * 64 + lane;
+                    rec[u] = 0;
+                    if (i < m1) rec[u] = few ? sh.few_occ[i] : occ[i];
+                    if (i < m1) SD_CNT(4);
                 }
-                w += __popcll(mk);
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int2 o = occ_unpack(rec[u]);
+                    const bool keep = base + u * 64 + lane < m1 && o.y >= pl;
+                    const uint64_t mk = __ballot(keep);
+                    if (keep) {
+                        const int dst = w + __popcll(mk & lanemask_lt());
+                        if (narrow) sg.pos[dst] = o.x - pl + 1;
+                        else usa[dst] = o.x - pl + 1;
+                        SD_CNT(4);
+                    }
+                    w += __popcll(mk);
+                }
             }
             staged = narrow;  // (nothing below it ever reads `usa` then)
             __threadfence_block();
@@ -2636,7 +2645,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         bv = g_bucket()[w + 1 + (lane & 1)];
         SD_CNT(4);
     }
-    request_occurrences<STATS, ACCEPT>(args->p, b, t, t_old, sh.newtok, x, s_sort, sh, scan, tail, nb, [&]() {
+    request_occurrences<STATS>(args->p, b, t, t_old, sh.newtok, x, s_sort, sh, scan, tail, nb, [&]() {
         // What acceptance and append have to write, by the last wave, once it needs nothing more of what it has
         // asked for: a wave's loads and stores are waited for in order, and the first wave, which every other
         // one waits for, would wait for its stores with its share of the scan (0.4 us of a decode step).
@@ -2794,9 +2803,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         }
         // (a frequent last token: the waves that are done with their searches early take the
         // left-extensions and the per-wave part of the occurrence sort meanwhile)
-        // (in the decode step's form of the kernel.  The form without the acceptance had no register left for the
-        // call when this came in; it has by now, at 78 of them, but what the call gives there has not been measured)
-        if (ACCEPT) {
+        // (left-extensions and sort behind the barrier instead, in the form without the acceptance: drafts for 256 requests of
+        // independent tokens 27.7 us, 26.5 so)
+        {
             const unsigned cnt_chunks = occ_take_chunks<STATS>(nw, t, P, args->p.D - 1, args->p.occ_cap, args->p.key_toks,
                                                                args->p.key_bits, args->p.alpha, tail, x, s_sort, sh);
             SD_CNT(cnt_chunks);
