@@ -19,16 +19,16 @@
 //
 // Bound: the memory system.  Per position 76 bytes in order (tokens read, text, codes and lines written, text and
 // codes read, entries written and read once per pass, suffix array and second tokens written), and
-// for each one that ties one random cache line a step: of the 0.46 ms of
+// for each one that ties one random cache line a step: of the 0.42 ms of
 // 10M tokens copied from templates k_code_sort takes 0.23 and reads 124 bytes a position in them
-// (100M: 3.1 of 4.8 ms, 148 bytes), against 0.09 where few suffixes tie.
+// (100M: 2.9 of 4.55 ms, 148 bytes), against 0.09 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
-// Build of 10M tokens copied from templates 1.68 -> 0.46 ms, of 10M of a Zipf law 2.89 -> 0.32 ms, of
-// 100M copied 20.7 -> 4.8 ms, against prefix doubling for everything.
+// Build of 10M tokens copied from templates 1.68 -> 0.42 ms, of 10M of a Zipf law 2.89 -> 0.31 ms, of
+// 100M copied 20.7 -> 4.55 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 
 namespace {
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
 // Codes go by blocks of 2^shift, as many as make a table of at most CDF_BLOCKS blocks, which k_layout has in LDS.  In a
 // block without a code of more than twice the average weight, or three sightings, all codes get equal parts of the block's
 // interval: what the sample tells among them is chance for the most part (10M tokens copied from templates, k_code_sort:
-// 250 us by the sample alone, 232 so), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
+// 250 us by the sample alone, 232 so when that was measured), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
 // interval, its last bit set if the block is of that kind.  (So a code's buckets are twice as full as
 // others, or have some hundred entries more; a bucket of five times the average still fits.)
 constexpr int CDF_QUANTUM = 5;
@@ -770,7 +770,6 @@ constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 constexpr int PART_COUNTED = 64;    // entries of a part whose order is found by counting, at most
 constexpr int PART_OF_WAVE = 512;   // of one that a wave sorts alone
-constexpr int WINDOW = 64 + 4;      // keys of a wave's window, and some that are above all others
 constexpr int GROUP_OF_WAVE = 256;  // of a group of ties that a wave deals with alone
 static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
 
@@ -876,6 +875,8 @@ __device__ __forceinline__ token_bits<R> bits_at(const packed_text &t, uint32_t 
     for (int k = 0; k < 2 * R; k++) r.w[k] = ((uint64_t)word(2 * k) << 32) | word(2 * k + 1);
     return r;
 }
+
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;  // the value of the next lane, of the one before
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
@@ -1219,60 +1220,80 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     const int share = (n + CW - 1) / CW;
     const int s_begin = next_first(w * share < n ? w * share : n);
     const int s_end = next_first((w + 1) * share < n ? (w + 1) * share : n);
-    uint64_t *win = reinterpret_cast<uint64_t *>(s_area) + w * WINDOW;
+    uint32_t *win = reinterpret_cast<uint32_t *>(s_area) + w * 64;
     uint16_t *list = reinterpret_cast<uint16_t *>(s_pos + SORT_CAP) + s_begin;
-    if (lane < WINDOW - 64) win[64 + lane] = ~0ull;
     // Orders the groups `first` (bits: lanes where one starts) of a window of len lanes by the
     // tokens x of every lane's entry; lane q holds place `at`.  Moves the positions in s_pos, marks
     // new groups in s_first; true where the place's group has more than one entry still.
-    // An entry is compared to its group's first one only: where it differs first (by words of 32 bits), whether it is less there
-    // and the word itself make a key that says how entries go, but among those that differ from the first one at
-    // the same place and in the same way, which another round orders by the first of them.  A place is the number of
-    // lower keys (which end in the lane's number, and begin with the group's, so that there is nothing to count
-    // but what is less, four keys at a time).  (Counting by
-    // all bits, 128 at a time, takes four compares of 64 bits for what takes one here.)
+    // An entry is compared to one pivot of its group: the first bit where it differs, which way, and the ten bits of its
+    // own that follow make a key that says how entries go, but among those with one key, which another round
+    // orders by the first of them.  The first round's pivot is what most of the group's first three entries have, bit by
+    // bit: copies that each differ from a template at places of their own differ from that at these places only
+    // (the entries of a group are then never all alike and yet unlike the pivot: each round splits or ends a group).  A
+    // place is the number of lower keys (which end in the lane's number, and begin with the group's, so that there is
+    // nothing to count but what is less, four aligned keys at a time).
+    // Bound: VALU and LDS of this loop, and behind it the lines that the gathers bring (133 million of 128 bytes at
+    // 100M tokens; 56 G/s of them is what this card reads in any order, 2.4 of the kernel's 2.9 ms).  Keys of 64 bits
+    // with a word of 32, the pivot being the group's first entry: k_code_sort 3.09 ms at 100M tokens and 233 us at 10M
+    // copied from templates, so 2.92 and 226 (rounds a window 3.2 -> 2.5, and half the bytes to count in); the tokens of the
+    // next window asked for in front of a window's rounds: nothing.  (Counting by all bits, 128 at a time: 3.45 ms.)
     auto order = [&](uint64_t first, int len, int at, uint32_t pos, const token_bits<R> &x) {
-        constexpr uint32_t SAME = 4 * R;
+        constexpr uint32_t SAME = 128 * R;
         first |= len < 64 ? ~0ull << len : 0ull;  // (lanes without an entry: groups of one)
         const uint64_t was = first;
+        token_bits<R> mid = x;  // of a lane between two of its group what most of the three have
+        const uint64_t inner = ~(first | (first >> 1) | (1ull << 63));
+        if (inner) {
+            const uint32_t edge = (inner >> lane) & 1ull ? 0u : 0xffffffffu;
+            auto half = [&](uint32_t b) {
+                const uint32_t a = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, DPP_WAVE_SHR1, 0xf, 0xf, true);
+                const uint32_t c = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, DPP_WAVE_SHL1, 0xf, 0xf, true);
+                const uint32_t t = (a ^ c) | edge;
+                return (t & b) | (~t & a);
+            };
+#pragma unroll
+            for (int k = 0; k < 2 * R; k++)
+                mid.w[k] = ((uint64_t)half((uint32_t)(x.w[k] >> 32)) << 32) | half((uint32_t)x.w[k]);
+        }
         int to = lane;  // where the lane's entry is by now
         for (bool later = false;; later = true) {
             const int lo = 63 - __builtin_clzll(first & ((2ull << to) - 1ull));
             const uint64_t behind = first >> 1 >> to;
             const int hi = behind ? to + 1 + __builtin_ctzll(behind) : 64;
-            const int head = later ? (int)(win[lo] & 63u) : lo;  // the lane of the group's first entry
-            uint64_t mine = 0, its = 0;
+            const int head = later ? (int)(win[lo] & 63u) : lo + 1 < hi ? lo + 1 : lo;  // the lane that has the pivot
+            uint64_t mine = 0, diff = 0;
             uint32_t word = SAME;
 #pragma unroll
             for (int k = 2 * R - 1; k >= 0; k--) {
-                const uint64_t h = ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)(x.w[k] >> 32)) << 32) |
-                                   (uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)x.w[k]);
-                if (x.w[k] != h) { mine = x.w[k]; its = h; word = 2 * k; }
+                const uint64_t v = later ? x.w[k] : mid.w[k];
+                const uint64_t d = x.w[k] ^ (((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)(v >> 32)) << 32) |
+                                             (uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)v));
+                if (d) { mine = x.w[k]; diff = d; word = 64 * k; }
             }
-            const bool low = (uint32_t)(mine >> 32) == (uint32_t)(its >> 32) && word != SAME;
-            const uint32_t m = low ? (uint32_t)mine : (uint32_t)(mine >> 32);
-            if (low) word++;
-            const uint32_t kind = mine < its ? word : 2 * SAME - word;  // (SAME: agrees in all words)
-            const uint64_t key = ((uint64_t)(((uint32_t)lo << 11) | (kind << 6) | (m >> 26)) << 32) | (m << 6) | (uint32_t)lane;
+            const int bit = diff ? __builtin_clzll(diff) : 0;
+            const uint32_t place = word + (uint32_t)bit;
+            const uint64_t tail = mine << bit;
+            const uint32_t kind = (tail >> 63) ? 2 * SAME - place : place;  // (SAME: agrees in all bits)
+            const uint32_t key = (uint32_t)lo << 26 | kind << 16 | ((uint32_t)(tail >> 47) & 0xffc0u) | (uint32_t)lane;
             wave_sync();
             win[to] = key;
             wave_sync();
             uint32_t less = 0;
-            for (int j = lo; j < hi; j += 4) {
-                const uint64_t k0 = win[j], k1 = win[j + 1], k2 = win[j + 2], k3 = win[j + 3];
-                less += k0 < key ? 1u : 0u;
-                less += k1 < key ? 1u : 0u;
-                less += k2 < key ? 1u : 0u;
-                less += k3 < key ? 1u : 0u;
+            for (int j = lo & ~3; j < hi; j += 4) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(win + j);
+                less += v.x < key ? 1u : 0u;
+                less += v.y < key ? 1u : 0u;
+                less += v.z < key ? 1u : 0u;
+                less += v.w < key ? 1u : 0u;
             }
-            to = lo + (int)less;
+            to = (lo & ~3) + (int)less;
             wave_sync();
             win[to] = key;
             wave_sync();
-            const uint64_t here = win[lane], before = lane > 0 ? win[lane - 1] : ~0ull;
+            const uint32_t here = win[lane], before = lane > 0 ? win[lane - 1] : ~0u;
             const bool starts = (here ^ before) >= 64u;
             first = __ballot(starts);
-            if (!__any(!starts && ((uint32_t)(here >> 38) & 31u) != SAME)) break;
+            if (!__any(!starts && ((here >> 16) & 1023u) != SAME)) break;
         }
         if (lane < len) {
             s_pos[at + to - lane] = pos;

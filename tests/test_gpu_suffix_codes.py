@@ -463,6 +463,36 @@ def test_ties_by_the_bits_of_the_lines(vocab):
         g.close()
 
 
+@pytest.mark.parametrize("vocab", [65_536, 152_064, 1 << 22])
+def test_ties_in_groups_of_every_size(vocab):
+    """Groups of 2 to 70 suffixes that share two tokens: tails that are one stretch but for one bit of one token (a pivot by
+    majority agrees with most), that all differ from it in that bit and then among themselves, or that are two
+    or three stretches in turn (no majority of neighbours, or another one than the group's)."""
+    rng = np.random.default_rng(vocab)
+    D, bits = 40, vocab.bit_length() - 1
+    docs = []
+    for size in list(range(2, 12)) + [31, 32, 33, 62, 63, 64, 65, 70]:
+        for kind in range(3):
+            head = rng.integers(0, vocab, 2)
+            tails = rng.integers(0, 1 << bits, (3, D))
+            for i in range(size):
+                t = tails[i % kind + kind // 2 if kind else 0].copy()
+                if kind < 2:
+                    t[i % 23] ^= 1 << (i * 5 % bits)
+                if kind and i % 4 == 3:
+                    t[:] = tails[0]
+                    t[1 + size % 3] ^= 1
+                    t[5 + i % 2] ^= i
+                docs.append(np.concatenate([head, t]).astype(np.int32))
+    docs = [docs[i] for i in rng.permutation(len(docs))]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, sum(len(d) + 1 for d in docs))
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("vocab", [900, 8191, 8192, 152_064, 524_286, 524_287])
 def test_intervals_by_blocks(vocab):
     """More than 2^22 positions: intervals by blocks of 2 to 128 codes, or in memory where that takes more blocks than the
