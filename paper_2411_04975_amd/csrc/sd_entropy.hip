@@ -200,26 +200,42 @@ template <typename INT>
 __device__ __forceinline__ INT run_end(const uint4 *__restrict__ blocks, INT j, INT lim, int d) {
     for (INT at = j & ~(INT)15; at < lim; at += 16) {
         const uint4 x = blocks[at >> 4];
-        const uint32_t wds[4] = {x.x, x.y, x.z, x.w};
-        uint32_t m = 0;
-#pragma unroll
-        for (int q = 0; q < 16; q++)
-            m |= (uint32_t)((int)((wds[q >> 2] >> (8 * (q & 3))) & 255u) < d) << q;
-        if (at < j) m &= ~0u << (int)(j - at);
-        if (m) {
-            const INT to = at + (INT)__builtin_ctz(m);
+        const uint32_t d4 = (uint32_t)d * 0x01010101u;
+        auto below = [&](uint32_t v) {  // the highest bit of each byte that is below d
+            const uint32_t low_bits = (v | 0x80808080u) - (d4 & 0x7f7f7f7fu);
+            return ((~v & d4) | (~(v ^ d4) & ~low_bits)) & 0x80808080u;
+        };
+        uint64_t lo = (uint64_t)below(x.x) | (uint64_t)below(x.y) << 32, hi = (uint64_t)below(x.z) | (uint64_t)below(x.w) << 32;
+        const int skip = at < j ? (int)(j - at) : 0;
+        if (skip >= 8) {
+            lo = 0;
+            hi &= ~0ull << (8 * (skip - 8));
+        } else {
+            lo &= ~0ull << (8 * skip);
+        }
+        if (lo | hi) {
+            const INT to = at + (INT)(lo ? __builtin_ctzll(lo) >> 3 : 8 + (__builtin_ctzll(hi) >> 3));
             return to < lim ? to : lim;
         }
     }
     return lim;
 }
 
+// c log2 c of a wide run.  (A call of its own: few take it, and in line its constants and temporaries cost the
+// walk registers at every step; k_entropy over 10M entries 117 -> 108 us.)
+__device__ __attribute__((noinline)) double times_log2(int32_t c) { return (double)c * log2((double)c); }
+
 // acc[0] += sum of S log2 S, acc[1] += sum of COUNT log2 COUNT (runs of two or more)
-// Bound: divergent walks.  A workgroup has the common prefixes of its ENT_TILE entries and of ENT_HALO behind them
-// in LDS, where nearly every run ends, lists the ones that open a run, so that all lanes walk, and has c log2 c of
-// small c in a table (most runs are copies of one stretch).  10M entries copied from templates: 116 us; 246 with an
-// entry per lane, the array in memory and the ends of runs of depth 2 looked for in their first token's bucket.
-constexpr int ENT_TB = 1024, ENT_TILE = 4096, ENT_HALO = 512, ENT_LOGS = 256;
+// Bound: divergent walks.  A workgroup has the common prefixes of a tile of entries and of ENT_HALO behind them
+// in LDS, where nearly every run ends, lists the entries that open a run, and has c log2 c of small c in a table (most
+// runs are copies of one stretch).  A step is one run: a lane that has done its entry's takes the next one of the
+// tile's list, and tiles are as long as two workgroups' lists fit a compute unit, so that few lanes are idle at the
+// end of one.  10M entries copied from templates: 60 us; 116 in tiles of 4096 with a lane's entries its own and the
+// bytes of a block compared one by one, 98 with the lanes taking entries from a list of their wave's, 72 in tiles of 19,584
+// so, 65 with one list, 60 with blocks compared four bytes at a time after two instead of four single ones (none 61,
+// three 67); 246 with an entry per lane, the array in memory and the ends of runs of depth 2 looked for in their first
+// token's bucket.
+constexpr int ENT_TB = 1024, ENT_TILE = 20480, ENT_TILE_MIN = 1024, ENT_HALO = 512, ENT_LOGS = 256;
 constexpr unsigned ENT_BLOCKS = 512;
 
 __global__ __launch_bounds__(ENT_TB) __attribute__((amdgpu_waves_per_eu(8))) void k_entropy(const int32_t *__restrict__ text,
@@ -228,29 +244,29 @@ __global__ __launch_bounds__(ENT_TB) __attribute__((amdgpu_waves_per_eu(8))) voi
                                                 const int32_t *__restrict__ bucket,
                                                 const uint8_t *__restrict__ lcp,
                                                 const uint8_t *__restrict__ len, int64_t N, int32_t D,
-                                                double *acc) {
+                                                int32_t tile, double *acc) {
     __shared__ uint4 s_lcp[(ENT_TILE + ENT_HALO) / 16];
     __shared__ double s_log[ENT_LOGS];
     __shared__ uint16_t s_open[ENT_TILE];  // entries of the tile that open a run
-    __shared__ int32_t s_n;
+    __shared__ int32_t s_n, s_take;
     for (int c = threadIdx.x; c < ENT_LOGS; c += ENT_TB) s_log[c] = c > 1 ? (double)c * log2((double)c) : 0.0;
     const uint8_t *const near = reinterpret_cast<const uint8_t *>(s_lcp);
-    auto times_log = [&](int32_t c) { return c < ENT_LOGS ? s_log[c] : (double)c * log2((double)c); };
+    auto times_log = [&](int32_t c) { return c < ENT_LOGS ? s_log[c] : times_log2(c); };
     double sS = 0.0, sC = 0.0;
     // a fixed number of workgroups strides over the entries: the two totals are single
     // addresses, and one atomic per wave of a grid as long as the array would queue up on them
-    for (int64_t base = (int64_t)blockIdx.x * ENT_TILE; base < N; base += (int64_t)gridDim.x * ENT_TILE) {
+    for (int64_t base = (int64_t)blockIdx.x * tile; base < N; base += (int64_t)gridDim.x * tile) {
         __syncthreads();
-        if (threadIdx.x == 0) s_n = 0;
-        for (int q = threadIdx.x; q < (ENT_TILE + ENT_HALO) / 16; q += ENT_TB)  // (the array goes on for a while behind its last entry)
+        if (threadIdx.x == 0) s_n = s_take = 0;
+        for (int q = threadIdx.x; q < (tile + ENT_HALO) / 16; q += ENT_TB)  // (the array goes on for a while behind its last entry)
             s_lcp[q] = base + 16 * q < N ? *reinterpret_cast<const uint4 *>(lcp + base + 16 * q) : make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
         // (an index has fewer than 2^31 entries)
         const int32_t first_at = (int32_t)base, n_all = (int32_t)N;
-        const int32_t held = base + ENT_TILE + ENT_HALO < N ? first_at + ENT_TILE + ENT_HALO : n_all;  // entries below are at hand
-        for (int k = 0; k < ENT_TILE / ENT_TB; k++) {
-            const int at = k * ENT_TB + (int)threadIdx.x, lane = threadIdx.x & 63;
-            const bool opens = base + at + 1 < N && near[at + 1] > near[at];
+        const int32_t held = base + tile + ENT_HALO < N ? first_at + tile + ENT_HALO : n_all;  // entries below are at hand
+        for (int k = 0; k < tile; k += ENT_TB) {
+            const int at = k + (int)threadIdx.x, lane = threadIdx.x & 63;
+            const bool opens = at < tile && base + at + 1 < N && near[at + 1] > near[at];
             const unsigned long long b = __ballot(opens);
             int first = 0;
             if (lane == 0 && b) first = atomicAdd(&s_n, __popcll(b));
@@ -258,17 +274,30 @@ __global__ __launch_bounds__(ENT_TB) __attribute__((amdgpu_waves_per_eu(8))) voi
             if (opens) s_open[first + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)at;
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < s_n; q += ENT_TB) {
-            const int at = s_open[q], lo = near[at], hi = near[at + 1];
-            const int32_t i = first_at + at;
-            const int Li = len[i];
-            int32_t j = i + 1;
-            int d = hi;
-            while (d > lo) {
+        const int n_open = s_n, lane = threadIdx.x & 63;
+        int lo = 0, hi = 0, d = 0, Li = 0, take = 0;
+        int32_t i = 0, j = 0;
+        for (;;) {
+            const unsigned long long idle = __ballot(d <= lo);
+            if (idle && take < n_open) {
+                if (lane == 0) take = atomicAdd(&s_take, __popcll(idle));
+                take = __builtin_amdgcn_readfirstlane(take);
+                const int q = take + __popcll(idle & ((1ull << lane) - 1ull));
+                if (d <= lo && q < n_open) {
+                    const int at = s_open[q];
+                    lo = near[at];
+                    hi = near[at + 1];
+                    i = first_at + at;
+                    Li = len[i];
+                    j = i + 1;
+                    d = hi;
+                }
+            } else if (idle == ~0ull) break;
+            if (d > lo) {
                 if (j < held) {
                     int n = j - first_at;
                     const int n_held = held - first_at;
-                    for (int q = 0; q < 4 && n < n_held && near[n] >= d; q++) n++;
+                    for (int q = 0; q < 2 && n < n_held && near[n] >= d; q++) n++;
                     if (n < n_held && near[n] >= d) n = run_end(s_lcp, n, n_held, d);
                     j = first_at + n;
                 }
@@ -363,9 +392,13 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
         const int64_t per_block = TB / 64 * LCP_OUT;
         hipLaunchKernelGGL((R == 3 ? k_lcp_len<3> : R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
                            lines, bits, (uint32_t)(128 * R / bits), 65536u / (uint32_t)bits + 1u, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);
-        const unsigned tiles = (unsigned)((N + ENT_TILE - 1) / ENT_TILE);
+        // as many rounds of workgroups as tiles of the largest size make, of tiles of one size
+        const int64_t rounds = (N + (int64_t)ENT_BLOCKS * ENT_TILE - 1) / ((int64_t)ENT_BLOCKS * ENT_TILE);
+        int64_t tile = ((N + rounds * ENT_BLOCKS - 1) / (rounds * ENT_BLOCKS) + 63) / 64 * 64;
+        if (tile < ENT_TILE_MIN) tile = ENT_TILE_MIN;
+        const unsigned tiles = (unsigned)((N + tile - 1) / tile);
         hipLaunchKernelGGL(k_entropy, dim3(tiles < ENT_BLOCKS ? tiles : ENT_BLOCKS), dim3(ENT_TB), 0, st, c->g_text, c->g_sa, c->g_tok1,
-                           c->g_bucket, lcp, len, N, c->cfg.D, sums);
+                           c->g_bucket, lcp, len, N, c->cfg.D, (int32_t)tile, sums);
         if (hipGetLastError() != hipSuccess) return SD_ERR_HIP;
         double host[3];
         if (hipMemcpyAsync(host, sums, sizeof(host), hipMemcpyDeviceToHost, st) != hipSuccess ||

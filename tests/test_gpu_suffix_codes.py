@@ -493,6 +493,46 @@ def test_ties_in_groups_of_every_size(vocab):
         g.close()
 
 
+def _entropy_of(text, D):
+    """(sum of S log2 S - sum of COUNT log2 COUNT over the nodes, weight), by counting all stretches of up to D tokens."""
+    bits, weight = 0.0, 0
+    node = np.zeros(len(text), np.int64)  # of the position's first d tokens
+    live = np.arange(len(text))
+    for d in range(D):
+        live = live[live + d < len(text)]
+        live = live[text[live + d] >= 0]
+        s = np.bincount(node[live])
+        key = node[live] * (int(text.max()) + 1) + text[live + d]
+        _, child, c = np.unique(key, return_inverse=True, return_counts=True)
+        node[live] = child
+        s, c = s[s > 1].astype(np.float64), c[c > 1].astype(np.float64)
+        bits += float((s * np.log2(s)).sum() - (c * np.log2(c)).sum())
+        weight += len(live)
+    return bits / max(weight, 1), weight
+
+
+@pytest.mark.parametrize("n,vocab,D", [
+    (1, 5, 4), (1023, 5, 6), (1024, 40, 6), (1025, 40, 130), (1537, 2, 200), (70_000, 3, 9), (300_000, 65_535, 5), (300_000, 1 << 20, 4),
+    (300_000, 1 << 24, 3), (524_288, 900, 4), (524_289, 900, 4), (10_485_760, 60, 3), (10_485_800, 60, 3), (10_485_800, 128_256, 2)])
+def test_entropy_by_tiles(n, vocab, D):
+    """Tiles of 1024 entries up to 512 of them, then longer ones, two rounds from 10,485,761 entries on; runs that end
+    in a tile, in what it holds of the next, and behind that; depths above 127; codes of 16, 17, 21 and 25 bits."""
+    rng = np.random.default_rng(n + vocab)
+    copies = rng.integers(0, vocab, max(n // 9, 1)).astype(np.int32)
+    t = np.concatenate([copies] * 9 + [rng.integers(0, vocab, 9).astype(np.int32)])[:n - 1]
+    docs = np.split(t, np.sort(rng.integers(0, len(t) + 1, 3))) if n > 1000 else [t]
+    g = parity.GpuPath(vocab, D, 1, 1.0, 0.1, 1, 16, n + 4)
+    try:
+        g.build_global(docs)
+        got, weight = g.entropy()
+    finally:
+        g.close()
+    want, want_weight = _entropy_of(np.concatenate([np.concatenate([d, [-1]]) for d in docs]), D)
+    assert weight == want_weight
+    # binary64 sums of at most 10M terms in another order
+    assert got == pytest.approx(want, rel=1e-9, abs=1e-12)
+
+
 @pytest.mark.parametrize("vocab", [900, 8191, 8192, 152_064, 524_286, 524_287])
 def test_intervals_by_blocks(vocab):
     """More than 2^22 positions: intervals by blocks of 2 to 128 codes, or in memory where that takes more blocks than the
