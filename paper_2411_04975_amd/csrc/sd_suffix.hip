@@ -611,9 +611,10 @@ __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ 
                                                    const int32_t *__restrict__ text, int64_t N, entry_shape f,
                                                    const uint32_t *__restrict__ hist, int chunks,
                                                    uint32_t *__restrict__ sums, uint32_t *__restrict__ starts,
-                                                   uint64_t *__restrict__ out) {
+                                                   uint64_t *__restrict__ out, uint32_t *__restrict__ n_lasts) {
     __shared__ split_lds<ITEMS> s;
     const int tid = threadIdx.x, bins = 1 << f.bits1;
+    if (blockIdx.x == 0 && tid == 0) *n_lasts = 0;  // (for k_code_ranges)
     const int tile = tile_of_block();
     const int64_t base = (int64_t)tile * (CT * ITEMS);
     const int cnt = (int)(N - base < CT * ITEMS ? N - base : CT * ITEMS);
@@ -763,6 +764,7 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
 // copies of preambles, with 200, 500, 1000, 2000 copies of each: 0.94, 1.24, 1.23, 1.56 ms; 1.16, 1.71, 2.61,
 // 5.5 by counting, each long group split by one wave.
 constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072, SORT_TILE_FEW = 256;
+constexpr int SORT_TILE_MANY = 3328, SORT_ROUNDS = 8;
 constexpr int SORT_SLOTS = 1024;  // workgroups that what is less than a round of them is spread over, at most
 constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
 constexpr int SORT_PARTS = 4096;
@@ -795,7 +797,9 @@ __device__ __forceinline__ sort_range between(const sort_bound &r, const sort_bo
     return {r.filled, z.bucket, r.at, z.at, r.code, z.code};
 }
 // Only a tile's last bucket can reach beyond it, so where a tile's buckets are too many entries for a
-// workgroup that bucket is kept apart as a range of its own, `last` (empty otherwise).  Only if it is too
+// workgroup that bucket is kept apart as a range of its own, `last` (empty otherwise), which a workgroup behind the
+// tiles' takes.  (Left for a launch of their own, these cost a build of 10M tokens, 300 copies of each piece, 120 us where
+// tiles are of 3255 entries: the host has to hear of them, and few workgroups sort them.)  Only if it is too
 // long by itself, or the buckets in front of it are spread over more than SORT_BUCKETS, something
 // is left that no workgroup takes.
 struct sort_cut { sort_range first, last; };  // of a tile that is not sortable as it is
@@ -807,7 +811,8 @@ struct sort_cut { sort_range first, last; };  // of a tile that is not sortable 
 __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__ starts, int64_t N, int bits,
                                                     int tile, int tiles, const uint32_t *__restrict__ cdf,
                                                     int32_t n_codes, sort_bound *__restrict__ bounds,
-                                                    sort_cut *__restrict__ cuts, int32_t *rest) {
+                                                    sort_cut *__restrict__ cuts, sort_range *__restrict__ lasts,
+                                                    uint32_t *n_lasts, int taken, int32_t *rest) {
     __shared__ sort_bound s_bound[CW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
     const int t = (int)blockIdx.x * (CW - 1) + w;
@@ -845,7 +850,13 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
     }
     if (lane == 0) {
         cuts[t] = {f, l};
-        if (l.at != l.end_at || !sortable(f)) *rest = 1;
+        bool left = !sortable(f) || !sortable(l);
+        if (l.at != l.end_at && sortable(l)) {
+            const uint32_t i = atomicAdd(n_lasts, 1u);
+            lasts[i] = l;
+            left = left || i >= (uint32_t)taken;
+        }
+        if (left) *rest = 1;
     }
 }
 
@@ -920,12 +931,13 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
     }
 }
 
-template <int R, bool MORE>
+template <int R>
 __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
                                                   const uint32_t *__restrict__ starts,
                                                   const sort_bound *__restrict__ bounds,
                                                   const sort_cut *__restrict__ cuts,
-                                                  const sort_range *__restrict__ more, entry_shape f,
+                                                  const sort_range *__restrict__ lasts,
+                                                  const uint32_t *__restrict__ n_lasts, int tiles, int skip, entry_shape f,
                                                   packed_text text, int32_t D,
                                                   const uint32_t *__restrict__ cdf, int32_t n_codes,
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
@@ -945,10 +957,17 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     __shared__ int32_t s_n_long;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
-    sort_range range = MORE ? more[blockIdx.x] : between(bounds[blockIdx.x], bounds[blockIdx.x + 1]);
-    if (!MORE && __builtin_expect(!sortable(range), 0)) {
-        range = cuts[blockIdx.x].first;
-        if (!sortable(range)) return;
+    sort_range range;
+    if ((int)blockIdx.x < tiles) {
+        range = between(bounds[blockIdx.x], bounds[blockIdx.x + 1]);
+        if (__builtin_expect(!sortable(range), 0)) {
+            range = cuts[blockIdx.x].first;
+            if (!sortable(range)) return;
+        }
+    } else {  // (behind the tiles: their last buckets that are kept apart)
+        const int i = (int)blockIdx.x - tiles + skip;
+        if (i >= (int)*n_lasts) return;
+        range = lasts[i];
     }
     const int b0 = (int)range.bucket, nb = (int)range.end - b0;
     const int64_t a = range.at, z = range.end_at;
@@ -1412,15 +1431,15 @@ struct rest_range {
     uint32_t sub;   // number of its first entry
     uint32_t ord;   // number of its first bucket among those of all these ranges
 };
-enum { REST_ANY = 0, REST_RANGES, REST_LONG, REST_ENTRIES, REST_BUCKETS };  // words of h_flag
+enum { REST_ANY = 0, REST_LASTS, REST_LONG, REST_ENTRIES, REST_BUCKETS };  // words of h_flag
 
-// Lists, in order, the ranges that k_code_sort can take and has not, and those that it cannot.  One workgroup.
+// Lists, in order, the ranges that k_code_sort cannot take.  One workgroup.
 __global__ __launch_bounds__(CT) void k_rest_lists(const sort_bound *__restrict__ bounds,
                                                    const sort_cut *__restrict__ cuts, int tiles,
-                                                   sort_range *__restrict__ more, rest_range *__restrict__ rest,
+                                                   const uint32_t *__restrict__ n_lasts, rest_range *__restrict__ rest,
                                                    uint32_t *__restrict__ out) {
     __shared__ uint32_t s_wave[CW];
-    uint32_t n_more = 0, n_rest = 0, sub = 0, ord = 0;
+    uint32_t n_rest = 0, sub = 0, ord = 0;
     for (int base = 0; base < tiles; base += CT) {
         const int t = base + (int)threadIdx.x;
         sort_range r[2] = {};
@@ -1428,20 +1447,17 @@ __global__ __launch_bounds__(CT) void k_rest_lists(const sort_bound *__restrict_
             r[0] = cuts[t].first;
             r[1] = cuts[t].last;
         }
-        const bool is_rest[2] = {!sortable(r[0]), !sortable(r[1])}, is_more = r[1].at != r[1].end_at && !is_rest[1];
+        const bool is_rest[2] = {!sortable(r[0]), !sortable(r[1])};
         uint32_t entries = 0, buckets = 0, tot;
 #pragma unroll
         for (int q = 0; q < 2; q++)
             if (is_rest[q]) { entries += r[q].end_at - r[q].at; buckets += r[q].end - r[q].bucket; }
-        const uint32_t at_more = n_more + block_excl_scan(is_more, s_wave, &tot);
-        n_more += tot;
         uint32_t at_rest = n_rest + block_excl_scan((uint32_t)is_rest[0] + (uint32_t)is_rest[1], s_wave, &tot);
         n_rest += tot;
         uint32_t at_sub = sub + block_excl_scan(entries, s_wave, &tot);
         sub += tot;
         uint32_t at_ord = ord + block_excl_scan(buckets, s_wave, &tot);
         ord += tot;
-        if (is_more) more[at_more] = r[1];
 #pragma unroll
         for (int q = 0; q < 2; q++)
             if (is_rest[q]) {
@@ -1451,7 +1467,7 @@ __global__ __launch_bounds__(CT) void k_rest_lists(const sort_bound *__restrict_
             }
     }
     if (threadIdx.x == 0) {
-        out[REST_RANGES] = n_more;
+        out[REST_LASTS] = *n_lasts;
         out[REST_LONG] = n_rest;
         out[REST_ENTRIES] = sub;
         out[REST_BUCKETS] = ord;
@@ -1634,16 +1650,25 @@ split_plan plan_for(int64_t N) {
 // workgroups as N makes at SORT_TILE_MIN, rounded down (2.2M entries: one round instead of 1.4).  What is
 // less than a round is spread over all of it, down to SORT_TILE_FEW entries, 32 to a wave, or two buckets
 // (32k, 100k and 300k entries: 28.4, 24.8 and 28.4 us in tiles of 2048 and buckets of 256 to 512; 13.8, 15.6 and 20.8 so).
+// SORT_ROUNDS rounds and more of larger tiles go in these, as few as that makes, with room behind a tile for a last bucket
+// of twice the average (100M copied entries: 2.92 ms in tiles of 2099, 2.72 in 3256; 10M, four rounds of 3255 instead of six
+// of 2170: a build of independent tokens 272 -> 265 us, of copied ones 403 -> 408, for what the last round waits for).
 int sort_tile_for(int64_t N, int n_cu) {
     int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
     if (slots > SORT_SLOTS) slots = SORT_SLOTS;
-    int64_t rounds = N / (slots * SORT_TILE_MIN);
-    if (rounds < 1) rounds = 1;
-    int64_t t = (N + rounds * slots - 1) / (rounds * slots);
     const split_plan p = plan_for(N);
-    const int64_t least = 2 * (N >> (p.bits1 + p.bits2));
-    if (t < least) t = least;
-    return (int)(t < SORT_TILE_FEW ? SORT_TILE_FEW : t > SORT_TILE_MAX ? SORT_TILE_MAX : t);
+    const int64_t average = N >> (p.bits1 + p.bits2);
+    int64_t most = SORT_CAP - 2 * average;
+    most = most > SORT_TILE_MANY ? SORT_TILE_MANY : most < SORT_TILE_MIN ? SORT_TILE_MIN : most;
+    int64_t rounds = (N + slots * most - 1) / (slots * most);
+    if (rounds < SORT_ROUNDS) {
+        most = SORT_TILE_MAX;
+        rounds = N / (slots * SORT_TILE_MIN);
+        if (rounds < 1) rounds = 1;
+    }
+    int64_t t = (N + rounds * slots - 1) / (rounds * slots);
+    if (t < 2 * average) t = 2 * average;
+    return (int)(t < SORT_TILE_FEW ? SORT_TILE_FEW : t > most ? most : t);
 }
 constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
 
@@ -1668,9 +1693,10 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     *hist_words = h + MAX_BINS + 1;
     *start_words = s;
     *sum_words = (int64_t)(MAX_CHUNKS + 1) * MAX_BINS;
-    // (up to SORT_SLOTS tiles are as small as SORT_TILE_FEW, more are SORT_TILE_MIN and larger)
+    // (up to SORT_SLOTS tiles are as small as SORT_TILE_FEW; more are SORT_TILE_MIN and larger, or as much as that in one round more)
     int64_t tiles = cap / SORT_TILE_FEW < SORT_SLOTS ? cap / SORT_TILE_FEW : SORT_SLOTS;
-    if (tiles < cap / SORT_TILE_MIN) tiles = cap / SORT_TILE_MIN;
+    const int64_t least = (int64_t)SORT_TILE_MIN * (SORT_ROUNDS - 1) / SORT_ROUNDS;
+    if (tiles < cap / least) tiles = cap / least;
     *range_words = (tiles + 2) * (int64_t)((2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
     *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
@@ -1754,7 +1780,9 @@ struct sort_tables {
     int tile, tiles;
     sort_bound *bounds;  // tiles + 1
     sort_cut *cuts;
-    sort_range *more;
+    sort_range *lasts;   // last buckets that are kept apart, in any order, one for every tile at most
+    uint32_t *n_lasts;
+    int taken;           // of them are taken with the tiles
     rest_range *rest;    // two for every tile
 };
 static sort_tables tables_for(const sd_ctx *c, int64_t N) {
@@ -1764,19 +1792,21 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
     t.rest = reinterpret_cast<rest_range *>(c->b_ranges);
     t.bounds = reinterpret_cast<sort_bound *>(t.rest + 2 * (int64_t)t.tiles);
     t.cuts = reinterpret_cast<sort_cut *>(t.bounds + t.tiles + 1);
-    t.more = reinterpret_cast<sort_range *>(t.cuts + t.tiles);
+    t.lasts = reinterpret_cast<sort_range *>(t.cuts + t.tiles);
+    t.n_lasts = reinterpret_cast<uint32_t *>(t.lasts + t.tiles);
+    t.taken = t.tiles / 4 < 16 ? 16 : t.tiles / 4;
     return t;
 }
 
-// the tiles, or n ranges `more`
-static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, const sort_range *more, int n, entry_shape f,
+// The tiles and the first of the last buckets that are kept apart (workgroups for a quarter as many as there are tiles:
+// one that finds nothing is over at once), or n last buckets behind those.
+static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, int n, entry_shape f,
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
     const packed_text packed = {line_room(c), bits, 128 * R / bits};
-    SD_LAUNCH(c, SD_K_CODE_SORT, st, (more ? (R == 3 ? k_code_sort<3, true> : R == 2 ? k_code_sort<2, true> : k_code_sort<1, true>) :
-                                      R == 3 ? k_code_sort<3, false> : R == 2 ? k_code_sort<2, false> : k_code_sort<1, false>),
-              dim3((unsigned)n), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, more, f, packed, c->cfg.D, c->code_cdf,
-              c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
+    SD_LAUNCH(c, SD_K_CODE_SORT, st, (R == 3 ? k_code_sort<3> : R == 2 ? k_code_sort<2> : k_code_sort<1>),
+              dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
+              n ? t.taken : 0, f, packed, c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
 
 // Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
@@ -1808,8 +1838,9 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     if (!few)
         SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
               c->code_sums, chunks, starts1, (uint32_t)N);
+    const sort_tables t = tables_for(c, N);
     SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (few ? k_code_split<SMALL_ITEMS, true> : p.small_tiles ? k_code_split<SMALL_ITEMS, false> : k_code_split<LARGE_ITEMS, false>),
-              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, starts1, ent1);
+              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, starts1, ent1, t.n_lasts);
     if (p.bits2) {
         const dim3 grid2((unsigned)(N / SPLIT2_TILE + bins1));
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
@@ -1818,11 +1849,10 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
         SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, bins1, shift, bins2, hist2, ent2);
         ent1 = ent2;
     }
-    const sort_tables t = tables_for(c, N);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
-              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, c->h_flag);
+              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, t.lasts, t.n_lasts, t.taken, c->h_flag);
     const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
-    sort_ranges(c, ent1, t, nullptr, t.tiles, f, sa, tok1, bucket, st);
+    sort_ranges(c, ent1, t, 0, f, sa, tok1, bucket, st);
     return asked;
 }
 
@@ -1833,12 +1863,12 @@ sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t
     const sort_tables t = tables_for(c, N);
     const dim3 block(CT);
     auto grid = [](int64_t n, int per) { return dim3((unsigned)((n + per - 1) / per)); };
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_lists, dim3(1), block, 0, t.bounds, t.cuts, t.tiles, t.more, t.rest, (uint32_t *)c->h_flag);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_lists, dim3(1), block, 0, t.bounds, t.cuts, t.tiles, t.n_lasts, t.rest, (uint32_t *)c->h_flag);
     if (hipEventRecord(c->code_asked, st) != hipSuccess || hipEventSynchronize(c->code_asked) != hipSuccess) return SD_ERR_HIP;
     const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
-    const int ranges = (int)told[REST_RANGES], n = (int)told[REST_LONG];
+    const int more = (int)told[REST_LASTS] - t.taken, n = (int)told[REST_LONG];
     const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
-    if (ranges > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, t.more, ranges, f, sa, tok1, bucket, st);
+    if (more > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, more, f, sa, tok1, bucket, st);
     if (n == 0) return SD_OK;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
     uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;

@@ -533,6 +533,27 @@ def test_entropy_by_tiles(n, vocab, D):
     assert got == pytest.approx(want, rel=1e-9, abs=1e-12)
 
 
+@pytest.mark.parametrize("n,copies", [(30_000, 700), (300_000, 300), (300_000, 1100), (300_000, 2300), (300_000, 4000), (2_700_000, 900),
+                                      (2_700_000, 3900), (2_700_000, 4200)])
+def test_buckets_apart(n, copies):
+    """Pieces of 12 tokens in any order, each `copies` times: buckets that do not fit behind a tile's others and are
+    kept apart, of some tiles, or of more than a quarter of them (a second launch); at 4200 copies none fits a workgroup.
+    2.7M positions are two rounds of tiles, and insertions have tiles of their own."""
+    rng = np.random.default_rng(n + copies)
+    D, vocab = 20, 60_000
+    pieces = rng.integers(0, vocab, (max(n // (12 * copies), 2), 12)).astype(np.int32)
+    t = pieces[rng.permutation(np.repeat(np.arange(len(pieces)), copies))].reshape(-1)[:n]
+    docs, more = np.split(t, [len(t) // 3]), [t[:len(t) // 4]]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, 2 * n + 8)
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+        g.insert_global(more)
+        _check(g, docs + more, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("vocab", [900, 8191, 8192, 152_064, 524_286, 524_287])
 def test_intervals_by_blocks(vocab):
     """More than 2^22 positions: intervals by blocks of 2 to 128 codes, or in memory where that takes more blocks than the
