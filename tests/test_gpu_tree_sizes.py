@@ -70,3 +70,31 @@ def test_trees_of_all_sizes(nodes, batch):
         assert not bad, "\n".join(bad)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("den_mode,linear", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("nodes", [1, 2, 5, 16, 63, 64])
+def test_more_candidates_than_a_tree_has_room_for(nodes, den_mode, linear):
+    """Nodes with 1 to 300 children, of which most score alike: what does not fit the frontier is left out by score and
+    token, the lowest of the equals staying, at the root and below it, among up to 64 suffixes and among more."""
+    rng = np.random.default_rng(1000 * nodes + 10 * den_mode + linear)
+    vocab, D, P = 700, 12, 2
+    docs, contexts = [], []
+    for head, (children, most) in enumerate([(1, 1), (nodes, 1), (nodes + 1, 1), (nodes + 2, 2), (64, 1), (65, 1), (150, 2), (300, 3)]):
+        for x in rng.permutation(np.arange(20, 320))[:children]:
+            for _ in range(int(rng.integers(1, most + 1))):
+                docs.append(np.array([head, x] + list(rng.integers(320, 324, 3)), np.int32))
+        contexts += [np.array([400 + head, head], np.int32), np.array([head], np.int32)]
+    docs = [docs[i] for i in rng.permutation(len(docs))]
+    alpha = nodes / 2.0
+    g = parity.GpuPath(vocab, D, P, alpha, 0.0, len(contexts), 8, sum(len(d) + 1 for d in docs), den_mode=den_mode, linear=linear)
+    try:
+        g.build_global(docs)
+        g.build_requests(range(len(contexts)), contexts)
+        got = g.speculate(range(len(contexts)))
+        tg = parity.oracle_global_trie(docs, D, vocab)
+        want = parity.oracle_speculate_batch(tg, contexts, D, P, alpha, 0.0, int(np.floor(alpha * P)), den_mode=den_mode, linear=linear)
+        bad = parity.compare_trees(got, want, "%d nodes" % nodes)
+        assert not bad, "\n".join(bad)
+    finally:
+        g.close()
