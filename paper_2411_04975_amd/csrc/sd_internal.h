@@ -51,7 +51,7 @@ struct sd_ctx {
 
     // build scratch (sized for g_cap)
     uint64_t *b_keys[2] = {nullptr, nullptr};
-    uint32_t *b_vals[2] = {nullptr, nullptr};
+    uint32_t *b_vals[2] = {nullptr, nullptr};  // the second one also: the text in lines (sd_suffix.hip, sd_entropy.hip)
     uint32_t *b_rank = nullptr;
     uint32_t *b_flags = nullptr;     // group numbers by place (one of two buffers, see b_gid2)
     uint32_t *b_gid2 = nullptr;      // the other one: a doubling round reads one and writes the other

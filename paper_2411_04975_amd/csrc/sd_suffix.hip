@@ -21,14 +21,14 @@
 // codes read, entries written and read once per pass, suffix array and second tokens written), and
 // for each one that ties one random cache line a step: of the 0.42 ms of
 // 10M tokens copied from templates k_code_sort takes 0.23 and reads 124 bytes a position in them
-// (100M: 2.9 of 4.55 ms, 148 bytes), against 0.09 where few suffixes tie.
+// (100M: 2.7 of 4.4 ms, 149 bytes), against 0.09 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
 // Build of 10M tokens copied from templates 1.68 -> 0.42 ms, of 10M of a Zipf law 2.89 -> 0.31 ms, of
-// 100M copied 20.7 -> 4.55 ms, against prefix doubling for everything.
+// 100M copied 20.7 -> 4.4 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 
 namespace {
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
 // Codes go by blocks of 2^shift, as many as make a table of at most CDF_BLOCKS blocks, which k_layout has in LDS.  In a
 // block without a code of more than twice the average weight, or three sightings, all codes get equal parts of the block's
 // interval: what the sample tells among them is chance for the most part (10M tokens copied from templates, k_code_sort:
-// 250 us by the sample alone, 232 so when that was measured), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
+// 250 us by the sample alone, 232 so, ordered by 64-bit keys), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
 // interval, its last bit set if the block is of that kind.  (So a code's buckets are twice as full as
 // others, or have some hundred entries more; a bucket of five times the average still fits.)
 constexpr int CDF_QUANTUM = 5;
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 // A position's interval comes from the table of blocks in LDS, but for blocks of unlike tokens, whose tokens
 // ask for theirs in memory.  Asking for all of them there takes a line of the L2 per position, and as many bytes of L2 as that are
 // a limit of their own: 71 us for 10M tokens, 128k of them different, and 586 for 100M, without the lines below; with the table, and
-// the lines, 58 and 464.  The table takes as little LDS as leaves room for four workgroups on a compute unit: what a
+// the lines, 58 and 470.  The table takes as little LDS as leaves room for four workgroups on a compute unit: what a
 // workgroup waits for are loads and other waves (10M, tables of 10,240, 5120 and 4096 blocks, two, three and four workgroups: 85, 67, 58;
 // 2048 blocks: 58).  Inputs of less than a few million tokens ask in memory (2.2M: 22.2, by blocks 22.8).
 //
@@ -1252,9 +1252,9 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     // place is the number of lower keys (which end in the lane's number, and begin with the group's, so that there is
     // nothing to count but what is less, four aligned keys at a time).
     // Bound: VALU and LDS of this loop, and behind it the lines that the gathers bring (133 million of 128 bytes at
-    // 100M tokens; 56 G/s of them is what this card reads in any order, 2.4 of the kernel's 2.9 ms).  Keys of 64 bits
+    // 100M tokens; 56 G/s of them is what this card reads in any order, 2.4 of the kernel's 2.7 ms).  Keys of 64 bits
     // with a word of 32, the pivot being the group's first entry: k_code_sort 3.09 ms at 100M tokens and 233 us at 10M
-    // copied from templates, so 2.92 and 226 (rounds a window 3.2 -> 2.5, and half the bytes to count in); the tokens of the
+    // copied from templates, so 2.92 and 226, in tiles of 2099 and 2170 (rounds a window 3.2 -> 2.5, and half the bytes to count in); the tokens of the
     // next window asked for in front of a window's rounds: nothing.  (Counting by all bits, 128 at a time: 3.45 ms.)
     auto order = [&](uint64_t first, int len, int at, uint32_t pos, const token_bits<R> &x) {
         constexpr uint32_t SAME = 128 * R;
