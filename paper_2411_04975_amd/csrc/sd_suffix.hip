@@ -357,7 +357,7 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
             next = start_of(d0 + lo + 1);
         }
         const int64_t i = p - (d0 + lo);
-                return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
+        return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
     };
     int32_t tok[5];  // of a round: every CT-th one from the thread's on, and one behind the round
     auto ask = [&](int r) {
