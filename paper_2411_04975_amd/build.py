@@ -11,9 +11,9 @@ CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libsd.so")
 CALLS_PATH = os.path.join(_HERE, "_sdcalls.so")
 
-# (The kernels' atomic additions are made by one lane already where that pays.  The compiler's own code for it, around
-# every one of them, stands in the way of a wave that is alone on its SIMD: decode steps of 64 requests 16.9 us with
-# it and 16.6 without, drafts for 256 requests 17.5 and 17.2, for 512 20.3 and 19.8, for one 11.4 and 11.2.)
+# (Where several lanes add to one address the kernels let one lane do it.  The compiler's own code for that, around
+# every atomic addition, stands in the way of a wave that is alone on its SIMD: decode steps of 64 requests 16.9 us with
+# it and 16.6 without, drafts for 256 requests 17.5 and 17.2, for 512 20.3 and 19.8; for one no more than runs differ.)
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
     "-fno-fast-math", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -462,7 +462,7 @@ __global__ __launch_bounds__(TB) void k_req_build(const int32_t *__restrict__ sl
             }
         if (i < stride) *reinterpret_cast<tok4r *>(row + i) = t[k];  // (a stride is a multiple of 64)
     }
-    if (bad) atomicOr(&err[SD_DEVERR_TOKEN], 1);
+    sd_report(&err[SD_DEVERR_TOKEN], bad);
     if (blockIdx.y == 0 && threadIdx.x == 0) r_len[slot] = (int32_t)len;
 }
 
@@ -486,14 +486,16 @@ __global__ __launch_bounds__(64) void k_req_append(const int32_t *__restrict__ s
         return;
     }
     int32_t *row = r_text + (int64_t)slot * stride;
+    bool bad = false;
     for (int32_t i = threadIdx.x; i < k; i += 64) {
         int32_t t = new_tokens[b + i];
         if (t < 0 || t >= vocab) {
-            atomicOr(&err[SD_DEVERR_TOKEN], 1);
+            bad = true;
             t = 0;
         }
         row[old + i] = t;
     }
+    sd_report(&err[SD_DEVERR_TOKEN], bad);
     __syncthreads();  // every lane has read `old` before it changes
     if (threadIdx.x == 0) r_len[slot] = old + k;
 }

@@ -2426,7 +2426,8 @@ __device__ __forceinline__ bool append_fits(const AppendArgs &ap, int32_t slot, 
     if (!fits && (threadIdx.x & 63) == 0) atomicOr(&ap.err[ok ? SD_DEVERR_CTX : SD_DEVERR_SLOT], 1);
     return fits;
 }
-// a token as it goes into a context
+// a token as it goes into a context (of a request only the bonus token can be outside the vocabulary, accepted ones being drafted ones:
+// one report a request at most)
 __device__ __forceinline__ int32_t append_token(const AppendArgs &ap, int32_t t) {
     if (t >= 0 && t < ap.vocab) return t;
     atomicOr(&ap.err[SD_DEVERR_TOKEN], 1);
