@@ -570,3 +570,62 @@ def test_intervals_by_blocks(vocab):
         _check(g, docs, D)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("vocab", [1, 7, 8, 9, 63, 511, 512, 513, 2048, 2049, 5000])
+@pytest.mark.parametrize("every", [1, 5, 700])
+def test_entropy_where_first_tokens_begin(vocab, every):
+    """Every code with an entry or two, with one in five or 700 only: eight codes to a lane, 512 to a wave, 2048 to a
+    workgroup, and their first entries in one word of marks, in neighbouring ones, or far apart."""
+    rng = np.random.default_rng(vocab + every)
+    used = np.arange(vocab)[::-every]
+    for many in (1, 40):
+        t = np.concatenate([used, rng.choice(used, len(used)), np.full(many, used[len(used) // 2])]).astype(np.int32)
+        t = t[rng.permutation(len(t))]
+        docs = np.split(np.concatenate([t, t[:len(t) // 2]]), [len(t) // 3])
+        text = np.concatenate([np.concatenate([d, [-1]]) for d in docs])
+        g = parity.GpuPath(vocab, 6, 1, 1.0, 0.1, 1, 16, len(text))
+        try:
+            g.build_global(docs)
+            got, weight = g.entropy()
+        finally:
+            g.close()
+        want, want_weight = _entropy_of(text, 6)
+        assert weight == want_weight
+        assert got == pytest.approx(want, rel=1e-9, abs=1e-12)  # (binary64 sums in another order)
+
+
+@pytest.mark.parametrize("n,vocab,factor", [(1000, 1 << 17, 1.6), (20_000, 1 << 17, 1.6), (4_000_000, 1 << 24, 2.5)])
+def test_entropy_of_few_entries_and_many_tokens(n, vocab, factor):
+    """The vocabulary's size costs no more than a pass over it: the entropy against that of the same text, its tokens numbered in a
+    vocabulary of as many as occur.  (With an addition for every code: 20, 2.4 and 4 times as long; so 1.0, 1.0 and 1.7, where codes of 25 bits are compared 5 a step.)"""
+    import torch
+    import paper_2411_04975_amd as sd
+    dev = torch.device("cuda", 0)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    pool = torch.randint(0, vocab, (n // 4,), generator=gen, device=dev)
+    t = torch.cat([pool[torch.randint(0, max(len(pool) - 100, 1), (n // 100 + 1, 1), generator=gen, device=dev) +
+                        torch.arange(min(100, len(pool)), device=dev)].reshape(-1)])[:n]
+    few, dense = torch.unique(t, return_inverse=True)
+    off = torch.tensor([0, len(t)], device=dev)
+
+    def best(tokens, vocab):
+        ctx = sd.sd_create(vocab, 64, 32, 1.0, 0.1, 1, 64, len(tokens) + 1, 0)
+        try:
+            sd.sd_index_build(ctx, sd.SD_SCOPE_GLOBAL, None, tokens.to(torch.int32), off, len(tokens))
+            us = []
+            for _ in range(8):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                out = sd.sd_index_entropy(ctx)
+                b.record()
+                torch.cuda.synchronize()
+                us.append(a.elapsed_time(b) * 1e3)
+        finally:
+            sd.sd_destroy(ctx)
+        return min(us), out
+    (all_us, all_out), (few_us, few_out) = best(t, vocab), best(dense, len(few))
+    print("%d entries: %.1f us, %d codes %.1f" % (n, few_us, vocab, all_us))
+    assert all_out[1] == few_out[1] and all_out[0] == pytest.approx(few_out[0], rel=1e-9)
+    assert all_us < factor * few_us
