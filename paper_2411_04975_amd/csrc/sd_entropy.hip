@@ -106,43 +106,40 @@ __device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N
 }
 
 // A bit in `marks` (zero before) for every place where another first token begins: bucket[c], for the codes c that have an
-// entry.  Every thread takes eight neighbouring codes, whose places are in order, and brings what falls in one word
-// together; the last word of each is brought together over the wave.  (An addition for every code, with an entry or
-// without, is one to a few words for most codes of a small index or a large vocabulary: k_prepare over 1000 entries and a vocabulary of
-// 128k 801 us, 4.4 so; over 10M entries and one of 2^24 812 and 55; of 128k 24 either way.)
-constexpr int MARK_CODES = 8;
-__device__ __forceinline__ void mark_starts(const int32_t *__restrict__ bucket, int32_t n_codes, int64_t first,
+// entry.  A wave takes 64 neighbouring codes at a time, whose places are in order, and brings together what falls in
+// one word, if it is more than a few.  (An addition for every code, with an entry or without, is one to a few words for most codes of a small index
+// or a large vocabulary: k_prepare over 1000 entries and a vocabulary of 128k 801 us, 7.6 so; over 10M entries and one of 2^24
+// 812 and 57; of 128k 22 either way.)
+constexpr int MARK_TOKENS = 8 * TB;
+__device__ __forceinline__ void mark_starts(const int32_t *__restrict__ bucket, int32_t n_codes, int32_t first,
                                             uint32_t *__restrict__ marks) {
     const int lane = threadIdx.x & 63;
-    const int64_t c0 = first + (int64_t)threadIdx.x * MARK_CODES;
-    int32_t at[MARK_CODES + 1];
+    int32_t at[MARK_TOKENS / TB], next[MARK_TOKENS / TB];
 #pragma unroll
-    for (int k = 0; k <= MARK_CODES; k++) at[k] = bucket[c0 + k < n_codes ? c0 + k : n_codes];  // (the last one: all entries)
-    int32_t word = at[0] >> 5;
-    uint32_t bits = 0;
+    for (int k = 0; k < MARK_TOKENS / TB; k++) {
+        const int32_t c = first + k * TB + (int32_t)threadIdx.x;
+        at[k] = bucket[c < n_codes ? c : n_codes];  // (the last one: all entries)
+        next[k] = bucket[c < n_codes ? c + 1 : n_codes];
+    }
 #pragma unroll
-    for (int k = 0; k < MARK_CODES; k++) {
-        if (at[k] == at[k + 1]) continue;
-        if (at[k] >> 5 != word) {
-            if (bits) atomicOr(&marks[word], bits);
-            word = at[k] >> 5;
-            bits = 0;
+    for (int k = 0; k < MARK_TOKENS / TB; k++) {
+        const int32_t word = at[k] >> 5, before = __shfl_up(word, 1);
+        uint32_t bits = at[k] != next[k] ? 1u << (at[k] & 31) : 0u;
+        const bool joins = lane > 0 && before == word;
+        const bool many = __popcll(__ballot(bits != 0u && joins)) > 4;
+        if (many) {  // (words go up with the lanes, so equal ones are neighbours)
+            for (int o = 1; o < 64; o <<= 1) {
+                const int32_t other = __shfl_down(word, o);
+                const uint32_t more = __shfl_down(bits, o);
+                if (lane + o < 64 && other == word) bits |= more;
+            }
         }
-        bits |= 1u << (at[k] & 31);
+        if (bits && !(many && joins)) atomicOr(&marks[word], bits);
     }
-    // (words go up with the lanes, so equal ones are neighbours)
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t other = __shfl_down(word, o);
-        const uint32_t more = __shfl_down(bits, o);
-        if (lane + o < 64 && other == word) bits |= more;
-    }
-    const int32_t before = __shfl_up(word, 1);
-    if (bits && (lane == 0 || before != word)) atomicOr(&marks[word], bits);
 }
 
 // What the kernels behind this one read: the sum that the documents' ends lack (the first SHORT_BLOCKS workgroups), where
 // another first token begins (MARK_TOKENS codes to a workgroup) and the lines.
-constexpr int MARK_TOKENS = MARK_CODES * TB;
 __global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
                                                 const int32_t *__restrict__ bucket, int64_t N, int32_t D, int32_t n_codes,
                                                 int mark_blocks, int64_t n_lines, int bits, unsigned long long *lost,
@@ -154,7 +151,7 @@ __global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text
     }
     b -= SHORT_BLOCKS;
     if (b < mark_blocks) {
-        mark_starts(bucket, n_codes, (int64_t)b * MARK_TOKENS, marks);
+        mark_starts(bucket, n_codes, b * MARK_TOKENS, marks);
         return;
     }
     pack(text, N, n_lines, bits, (int64_t)(b - mark_blocks) * PACK_TILE, lines);

@@ -575,7 +575,7 @@ def test_intervals_by_blocks(vocab):
 @pytest.mark.parametrize("vocab", [1, 7, 8, 9, 63, 511, 512, 513, 2048, 2049, 5000])
 @pytest.mark.parametrize("every", [1, 5, 700])
 def test_entropy_where_first_tokens_begin(vocab, every):
-    """Every code with an entry or two, with one in five or 700 only: eight codes to a lane, 512 to a wave, 2048 to a
+    """Every code with an entry or two, with one in five or 700 only: 64 codes to a wave at a time, 2048 to a
     workgroup, and their first entries in one word of marks, in neighbouring ones, or far apart."""
     rng = np.random.default_rng(vocab + every)
     used = np.arange(vocab)[::-every]
