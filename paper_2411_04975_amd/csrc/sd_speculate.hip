@@ -2489,7 +2489,7 @@ __global__ __launch_bounds__(64) void k_accept(const int32_t *__restrict__ n_nod
     accept_store(b, a, max_nodes, aa, c);
 }
 
-// k_speculate's arguments as they lie in memory: its parameters, in their order.
+// k_speculate's arguments: its only parameter, so that they lie in the argument segment as they are here.
 struct SpecArgs {
     SpecParams p;
     const int32_t *slot_ids;
@@ -2516,8 +2516,7 @@ typedef const __attribute__((address_space(4))) SpecArgs *SpecArgsAt;
 template <bool STATS, bool TICKS, bool ACCEPT>
 // (At least six waves per SIMD: two workgroups of twelve waves are resident together when two
 // requests share a compute unit; that is a bound on the kernel's registers.)
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_speculate(SpecParams, const int32_t *, sd_trees, int, AcceptArgs,
-                                                    AppendArgs) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_speculate(SpecArgs) {
     extern __shared__ double smem[];
     __shared__ WgShared sh;
     // the wave index is the same in all lanes: keep it (and every LDS address derived from it)
@@ -2529,7 +2528,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // they are all loaded at the start, where each group of them waits for the one before to be put away, and as there are more
     // than scalar registers they wait in lanes of vector registers for their use, a move each.  (124 of those in
     // the decode step's form, 57 so.  Decode steps of 256 requests over 10M tokens 18.9 -> 18.0 us, of 64 over 2.2M 17.8 -> 17.0,
-    // of 512 over 100M 21.3 -> 20.2, on independent tokens 27.5 -> 26.5; a draft of one request 11.9 -> 11.8.)
+    // of 512 over 100M 21.3 -> 20.2, on independent tokens 27.5 -> 26.5; a draft of one request by no more than runs differ.)
     SpecArgsAt args_at = (SpecArgsAt)__builtin_amdgcn_kernarg_segment_ptr();
     const SpecArgs *args = (const SpecArgs *)args_at;
     auto args_again = [&]() {
@@ -3125,26 +3124,19 @@ sd_status launch_speculate(sd_ctx *c, const int32_t *d_slot_ids, int32_t batch, 
     const size_t lds = plan.lds;
     p.occ_cap = lds / rec < (size_t)OCC_LDS_SORT ? (int32_t)(lds / rec) : OCC_LDS_SORT;
     const dim3 grid((unsigned)batch), block(64 * nw);
+    SpecArgs args{p, d_slot_ids, out, (int)lds_wave, AcceptArgs{}, AppendArgs{}};
     if (aa) {
-        sd_span sp(c, SD_K_ACCEPT_SPECULATE, st);
-        const AppendArgs ap{d_slot_ids, c->r_text, c->r_len, c->r_stride, c->cfg.max_ctx_tokens,
-                            c->cfg.max_batch_slots, c->cfg.vocab, c->d_err};
-        hipLaunchKernelGGL((k_speculate<false, false, true>), grid, block, lds, st, p, d_slot_ids, out,
-                           (int)lds_wave, *aa, ap);
-    } else {
-        sd_span sp(c, SD_K_SPECULATE, st);
-        const AcceptArgs none{};
-        const AppendArgs nap{};
-        if (stats)
-            hipLaunchKernelGGL((k_speculate<true, false, false>), grid, block, lds, st, p, d_slot_ids,
-                               out, (int)lds_wave, none, nap);
-        else if (ticks)
-            hipLaunchKernelGGL((k_speculate<false, true, false>), grid, block, lds, st, p, d_slot_ids,
-                               out, (int)lds_wave, none, nap);
-        else
-            hipLaunchKernelGGL((k_speculate<false, false, false>), grid, block, lds, st, p, d_slot_ids,
-                               out, (int)lds_wave, none, nap);
+        args.aa = *aa;
+        args.ap = AppendArgs{d_slot_ids, c->r_text, c->r_len, c->r_stride, c->cfg.max_ctx_tokens,
+                             c->cfg.max_batch_slots, c->cfg.vocab, c->d_err};
     }
+    // (the kernel reads SpecArgs from the start of its argument segment: of any other parameter list this is an error)
+    void (*const kernel)(SpecArgs) = aa      ? k_speculate<false, false, true>
+                                     : stats ? k_speculate<true, false, false>
+                                     : ticks ? k_speculate<false, true, false>
+                                             : k_speculate<false, false, false>;
+    sd_span sp(c, aa ? SD_K_ACCEPT_SPECULATE : SD_K_SPECULATE, st);
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, args);
     return hipGetLastError() == hipSuccess ? SD_OK : SD_ERR_HIP;
 }
 
