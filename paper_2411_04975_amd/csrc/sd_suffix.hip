@@ -30,6 +30,7 @@
 // Build of 10M tokens copied from templates 1.68 -> 0.42 ms, of 10M of a Zipf law 2.89 -> 0.31 ms, of
 // 100M copied 20.7 -> 4.4 ms, against prefix doubling for everything.
 #include "sd_internal.h"
+#include "sd_sample.h"
 
 namespace {
 
@@ -96,9 +97,6 @@ __device__ __forceinline__ int wave_lower_bound(AT at, int n, int64_t key) {
 // other in many vocabularies, and additions to one line queue up just the same (10M tokens of a
 // Zipf law: 24 us, 75 with one copy), and 32 neighbouring tokens lie next to each other in the LDS table, so that lanes next
 // to each other add to one line in one go (9.5 us; 10M tokens of like frequency 14.4 -> 14.1).
-constexpr int64_t SAMPLE_MIN = 4096;   // runs: a bin of a 256-way split sees 1000 of their tokens
-constexpr int SAMPLE_ONE_IN = 64;      // a token that goes unseen has a few hundred occurrences at most
-constexpr int64_t SAMPLE_MAX = 32768;  // 16 * 64 * SAMPLE_MAX + 4 * 2^24, the weights' total, is below 2^27
 constexpr int RUNS_PER_WG = 16;
 constexpr int TABLE = 2048;  // 64 groups of 32 neighbouring tokens
 
@@ -163,7 +161,7 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
                 n += v[q];
                 if (q > 0) counts[(int64_t)q * n_codes + c] = 0;
             }
-            n = 16u * (c == 0 ? ends : n) + 4u;
+            n = SIGHTING * (c == 0 ? ends : n) + UNSEEN;
             counts[c] = n;
             sum += n;
         }
@@ -178,16 +176,16 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
 // lack that many of its code's last bits, and the rest still names the first token.
 //
 // Codes go by blocks of 2^shift, as many as make a table of at most CDF_BLOCKS blocks, which k_layout has in LDS.  In a
-// block without a code of more than twice the average weight, or three sightings, all codes get equal parts of the block's
+// block without a code of more than twice the average weight and `slack` (three sightings, see sd_sample.h), all codes get equal parts of the block's
 // interval: what the sample tells among them is chance for the most part (10M tokens copied from templates, k_code_sort:
 // 250 us by the sample alone, 232 so, ordered by 64-bit keys), and k_layout finds their intervals by itself.  blocks[b] = lower end of the block's
 // interval, its last bit set if the block is of that kind.  (So a code's buckets are twice as full as
-// others, or have some hundred entries more; a bucket of five times the average still fits.)
+// others, or have some two hundred entries more.)
 constexpr int CDF_QUANTUM = 5;
 constexpr int CDF_BLOCKS = 4096, CDF_MAX_SHIFT = 7;
 __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, int32_t n_codes,
                                                  const uint32_t *__restrict__ partials,
-                                                 uint32_t *__restrict__ cdf, int shift, uint32_t *__restrict__ blocks) {
+                                                 uint32_t *__restrict__ cdf, int shift, uint32_t slack, uint32_t *__restrict__ blocks) {
     __shared__ uint32_t s_wave[CW];
     uint32_t below = 0, all = 0;
     for (int i = threadIdx.x; i < (int)gridDim.x; i += CT) {
@@ -222,7 +220,7 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
     auto end = [&](uint32_t w) { return (uint32_t)((uint64_t)w * 0x7ffffffull / total); };
     const uint32_t first = __shfl(at, head), lo = end(first), width = end(first + in_block) - lo;
     const int32_t b0 = c0 & ~((1 << shift) - 1);  // the block's first code
-    const bool even = b0 + (1 << shift) <= n_codes && (uint64_t)top << shift <= 2 * (uint64_t)in_block + (48ull << shift);
+    const bool even = b0 + (1 << shift) <= n_codes && (uint64_t)top << shift <= 2 * (uint64_t)in_block + ((uint64_t)slack << shift);
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
         if (c0 + k <= n_codes)
@@ -1719,10 +1717,7 @@ int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? COUNT_COPIES : 1
 // `tokens`: n_seq documents' tokens one after the other, or a text that holds them (its end markers
 // are not counted).
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st) {
-    const int64_t runs = (n_tokens + 63) / 64;
-    int64_t C = runs / SAMPLE_ONE_IN > SAMPLE_MIN ? runs / SAMPLE_ONE_IN : SAMPLE_MIN;
-    if (C > SAMPLE_MAX) C = SAMPLE_MAX;
-    if (C > runs) C = runs;
+    const int64_t runs = (n_tokens + 63) / 64, C = sd_sample_runs(n_tokens);
     int64_t ends = n_tokens > 0 ? (int64_t)((double)n_seq * (double)(C * 64) / (double)n_tokens) + 1 : 1;
     if (ends > (1 << 20)) ends = 1 << 20;
     const int32_t n_codes = c->cfg.vocab + 1;
@@ -1734,7 +1729,7 @@ void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t 
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (copies == 1 ? k_code_weights<1> : k_code_weights<COUNT_COPIES>), dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
               (uint32_t)ends, c->code_partials);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_cdf, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
-              c->code_partials, c->code_cdf, block_shift(c->cfg.vocab), c->code_blocks);
+              c->code_partials, c->code_cdf, block_shift(c->cfg.vocab), sd_even_slack(n_tokens), c->code_blocks);
 }
 
 // Bits of a token's code in the lines, and words that a line holds from any code on (29 codes of 17 bits, 25 of 18),
