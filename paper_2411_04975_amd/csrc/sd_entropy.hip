@@ -73,6 +73,30 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int LINE_POS = 32, LINE_WORDS = 32, LINE_HEAD = 2, LINE_BITS_MIN = 16;
 constexpr int PACK_TILE = 2048, PACK_LOOK = 64;
 
+// How many times 128 bits k_lcp_len compares at a time, how many whole codes these are, and a factor for the number of
+// whole codes in n of these bits, n * per_bit >> 16.
+struct line_step { int R, step; uint32_t per_bit; };
+constexpr line_step line_step_of(int bits) {
+    const int words = LINE_WORDS - 1 - LINE_HEAD - (LINE_POS - 1) * bits / 32, R = words >= 12 ? 3 : words >= 8 ? 2 : 1;
+    return {R, 128 * R / bits, 65536u / (uint32_t)bits + 1u};
+}
+// From a line's last position on there are the words that are read and the codes that are compared, and the parts of codes
+// that a word is packed of are of three that the tile has at hand.
+constexpr bool lines_hold() {
+    for (int bits = LINE_BITS_MIN; bits <= SD_CODE_BITS_MAX; bits++) {
+        const line_step s = line_step_of(bits);
+        const int last = (LINE_POS - 1) * bits, room = 32 * (LINE_WORDS - LINE_HEAD);
+        if (s.step < 1 || LINE_HEAD - 1 + ((last + 31) >> 5) + 4 * s.R >= LINE_WORDS || last + s.step * bits > room) return false;
+        if (LINE_POS + s.step > 64) return false;  // (end markers are told of as many)
+        for (int n = 0; n <= 128 * s.R; n++)
+            if ((int)(n * s.per_bit >> 16) != n / bits) return false;
+        for (int at = 0; at < room; at += 32)
+            if ((at + 31) / bits - at / bits > 2 || (at + 31) / bits >= LINE_POS + PACK_LOOK) return false;
+    }
+    return true;
+}
+static_assert(lines_hold(), "");
+
 __device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N, int64_t n_lines, int bits, int64_t base,
                                      uint32_t *__restrict__ lines) {
     __shared__ uint32_t s_code[PACK_TILE + PACK_LOOK];
@@ -406,7 +430,7 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
         // the lines lie in a third one, as many words as positions and a few more
         int bits = sd_bits_for((uint64_t)c->cfg.vocab);
         if (bits < LINE_BITS_MIN) bits = LINE_BITS_MIN;
-        const int words = LINE_WORDS - 1 - LINE_HEAD - (LINE_POS - 1) * bits / 32, R = words >= 12 ? 3 : words >= 8 ? 2 : 1;
+        const line_step step = line_step_of(bits);
         const int64_t n_lines = (N + c->cfg.D) / LINE_POS + 1;
         uint32_t *lines = c->b_vals[1];
         double *sums = reinterpret_cast<double *>(c->b_keys[0]);  // three, and behind them the marks
@@ -418,8 +442,8 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
         hipLaunchKernelGGL(k_prepare, dim3((unsigned)(SHORT_BLOCKS + mark_blocks + pack_blocks)), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_bucket, N, c->cfg.D,
                            n_codes, mark_blocks, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
         const int64_t per_block = TB / 64 * LCP_OUT;
-        hipLaunchKernelGGL((R == 3 ? k_lcp_len<3> : R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
-                           lines, bits, (uint32_t)(128 * R / bits), 65536u / (uint32_t)bits + 1u, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);
+        hipLaunchKernelGGL((step.R == 3 ? k_lcp_len<3> : step.R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
+                           lines, bits, (uint32_t)step.step, step.per_bit, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);
         // as many rounds of workgroups as tiles of the largest size make, of tiles of one size
         const int64_t rounds = (N + (int64_t)ENT_BLOCKS * ENT_TILE - 1) / ((int64_t)ENT_BLOCKS * ENT_TILE);
         int64_t tile = ((N + rounds * ENT_BLOCKS - 1) / (rounds * ENT_BLOCKS) + 63) / 64 * 64;

@@ -8,6 +8,7 @@
 #include "../../include/sd.h"
 
 #define SD_WAVE 64
+#define SD_CODE_BITS_MAX 25  // of a token's code, 0 .. vocab, vocab being 2^24 at most
 #define SD_TEXT_PAD 512      // sentinel tokens kept after the last real position of a text
 #define SD_END_TOKEN (-1)    // sentinel: sorts below every token and never matches one
 

@@ -1739,10 +1739,27 @@ static int line_bits(int32_t vocab) {
     const int b = sd_bits_for((uint64_t)vocab);
     return b < LINE_BITS_MIN ? LINE_BITS_MIN : b;
 }
-static int line_words(int bits) {
+static constexpr int line_words(int bits) {
     const int w = (LINE_POS - 1 - (LINE_POS - 1) * bits / 32) / 4 * 4;
     return w < 12 ? w : 12;
 }
+// From a line's last position on there are the words that bits_at reads and the codes that are compared, and the parts of codes
+// that k_layout puts into a word are of three that it has at hand.
+static constexpr bool lines_hold(int bits) {
+    const int R = line_words(bits) / 4, step = R > 0 ? 128 * R / bits : 0, last = (LINE_POS - 1) * bits;
+    bool ok = step > 0 && (last >> 5) + 4 * R < LINE_POS && last + 128 * R <= 32 * LINE_POS;
+    for (int w = 0; w < LINE_POS; w++) {
+        const int c0 = 32 * w / bits, c1 = (32 * w + 31) / bits;
+        ok = ok && c1 - c0 <= 2 && c1 < LINE_POS + LAYOUT_LOOK;
+    }
+    return ok;
+}
+static constexpr bool lines_hold() {
+    for (int bits = LINE_BITS_MIN; bits <= SD_CODE_BITS_MAX; bits++)
+        if (!lines_hold(bits)) return false;
+    return true;
+}
+static_assert(lines_hold(), "");
 static uint32_t *line_room(const sd_ctx *c) { return c->b_vals[1]; }
 
 static dim3 layout_grid(int64_t N, int items) { return dim3((unsigned)((N + SD_TEXT_PAD + CT * items - 1) / (CT * items))); }
