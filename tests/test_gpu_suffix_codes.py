@@ -536,9 +536,9 @@ def test_entropy_by_tiles(n, vocab, D):
 @pytest.mark.parametrize("n,copies", [(30_000, 700), (300_000, 300), (300_000, 1100), (300_000, 2300), (300_000, 4000), (2_700_000, 900),
                                       (2_700_000, 3900), (2_700_000, 4200)])
 def test_buckets_apart(n, copies):
-    """Pieces of 12 tokens in any order, each `copies` times: buckets that do not fit behind a tile's others and are
-    kept apart, of some tiles, or of more than a quarter of them (a second launch); at 4200 copies none fits a workgroup.
-    2.7M positions are two rounds of tiles, and insertions have tiles of their own."""
+    """Pieces of 12 tokens in any order, each `copies` times: buckets that hardly fit behind a tile's others, or are kept apart of
+    some tiles (of how many, and in which launch they are taken: test_buckets_apart_by_launch); at 4200 copies none fits a
+    workgroup.  2.7M positions are two rounds of tiles, and insertions have tiles of their own."""
     rng = np.random.default_rng(n + copies)
     D, vocab = 20, 60_000
     pieces = rng.integers(0, vocab, (max(n // (12 * copies), 2), 12)).astype(np.int32)
@@ -550,6 +550,60 @@ def test_buckets_apart(n, copies):
         _check(g, docs, D)
         g.insert_global(more)
         _check(g, docs + more, D)
+    finally:
+        g.close()
+
+
+def _check_on_gpu(g, docs, D):
+    """As _check, for indexes of tens of millions of positions."""
+    import torch
+    import paper_2411_04975_amd as sd
+    text, sa = (torch.from_numpy(x).to(g.dev) for x in sd.sd_debug_read_global(g.ctx))
+    want = np.concatenate([np.concatenate([d, [-1]]) for d in docs]).astype(np.int32)
+    assert bool((text == torch.from_numpy(want).to(g.dev)).all())
+    seen = torch.zeros(len(want), dtype=torch.uint8, device=g.dev)
+    seen[sa.long()] = 1
+    assert sa.numel() == len(want) and bool(seen.all())
+    pad = torch.cat((text, torch.full((D,), -1, dtype=torch.int32, device=g.dev)))
+    a, b = sa[:-1].long(), sa[1:].long()
+    for k in range(D):
+        x, y = pad[a + k], pad[b + k]
+        assert not bool((x > y).any()), k
+        same = (x == y) & (x >= 0)
+        a, b = a[same], b[same]
+
+
+@pytest.mark.parametrize("n,copies,launches", [
+    (2_700_000, 900, 1), (2_700_000, 2100, 2), (2_700_000, 1500, 1), (20_000_000, 700, 1), (20_000_000, 1050, 1), (20_000_000, 2100, 2)])
+def test_buckets_apart_by_launch(n, copies, launches):
+    """Suffixes that share two tokens are in one bucket: here they come `copies` at a time, one such bucket after the other, and a
+    tile ends with the last one that starts in it.  Of 2100 entries two start in nearly half of the tiles of 3072 or 3256, and 4200
+    are more than a workgroup takes: that bucket is kept apart, of more than a quarter of the tiles, and a
+    second launch has to follow (and, where two of them share a bucket, prefix doubling).  Of 1500 and 1050 it is a tile in twenty or in ten, which the first launch's last workgroups take; of 900
+    and 700 hardly one.  20M positions are eight rounds of the larger tiles.  The index and the drafts from it are right either way."""
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(n + copies)
+    D, vocab = 20, 60_000
+    pieces = rng.integers(0, vocab, (n // (12 * copies), 12)).astype(np.int32)
+    t = pieces[rng.permutation(np.repeat(np.arange(len(pieces)), copies))].reshape(-1)
+    docs = np.split(t, [len(t) // 3])
+    contexts = [np.concatenate([pieces[i], pieces[j][:k]]) for i, j, k in ((0, 1, 5), (2, 3, 11), (4, 4, 1), (5, 6, 12))]
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, len(contexts), 32, 2 * len(t) + 4)
+    try:
+        for add in [g.build_global] + [g.insert_global] * (n < 10_000_000):
+            sd.sd_debug_profile(g.ctx, 1)
+            add(docs)
+            made = sd.sd_debug_profile_read(g.ctx)
+            sd.sd_debug_profile(g.ctx, 0)
+            assert made["code_sort"]["launches"] == launches
+        if n < 10_000_000:
+            docs = docs + docs
+        _check_on_gpu(g, docs, D)
+        g.build_requests(range(len(contexts)), contexts)
+        got = g.speculate(range(len(contexts)))
+        tg = parity.oracle_global_trie(docs, D, vocab, contexts, 8)
+        want = parity.oracle_speculate_batch(tg, contexts, D, 8, 1.0, 0.1, g.max_nodes)
+        assert not parity.compare_trees(got, want)
     finally:
         g.close()
 
