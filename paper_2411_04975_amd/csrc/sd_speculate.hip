@@ -1087,16 +1087,31 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
         return;
     }
     frontier_close(f, hole);
-    if (nc > f.cap) {
-        // (children of one node, in the order of their tokens: the more suffixes the better, then the first one.  A
-        // pattern of one token has a tree of one or two nodes and dozens of candidates, 0.5 us each below.)
+    if (__builtin_expect(nc > f.cap, 0)) {
+        // (children of one node, in the order of their tokens: the more suffixes the better, then the first one.  Those that
+        // stay or those that don't are looked for, whichever are fewer, 0.06 us each, and what stays goes in at once at a
+        // root.  A pattern of one token has a tree of one or two nodes and dozens of candidates, 0.5 us each below.  60 children
+        // and 56 nodes: 82.9 us one by one, 84.9 with those that stay looked for, 67.7 so; 17 and 16: 34.7, 35.0 and 33.8.)
+        const int over = nc - f.cap;
+        const bool best = f.cap <= over;
         uint64_t left = C;
-        for (int k = 0; k < f.cap; k++) {
-            const uint32_t c = lane_in(left) ? (uint32_t)(hi - lo) : 0u;
-            const uint64_t most = ballot64(c == reduce_max_u32(c)) & left;
-            left &= ~(most & (0ull - most));
+#pragma unroll 1
+        for (int k = best ? f.cap : over; k > 0; k--) {
+            const uint32_t c = best ? (uint32_t)(hi - lo) : ~(uint32_t)(hi - lo), v = lane_in(left) ? c : 0u;
+            const uint64_t most = ballot64(v == reduce_max_u32(v)) & left;
+            left &= ~(best ? most & (0ull - most) : 1ull << (63 - __builtin_clzll(most)));
         }
-        C &= ~left;
+        C = best ? C & ~left : left;
+        if (f.n == 0) {
+            const int s = __popcll(C & lanemask_lt());
+            if (lane_in(C)) {
+                f.score[s] = sc; f.tok[s] = tok; f.par[s] = par; f.lo[s] = lo; f.hi[s] = hi;
+                f.dep[s] = dep;
+            }
+            f.n = f.cap;
+            C = 0;
+            wsync();
+        }
     }
     while (C) {
         int src = __ffsll((unsigned long long)C) - 1;

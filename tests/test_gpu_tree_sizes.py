@@ -98,3 +98,45 @@ def test_more_candidates_than_a_tree_has_room_for(nodes, den_mode, linear):
         assert not bad, "\n".join(bad)
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("nodes", [2, 16, 31, 33, 40, 56, 61])
+def test_one_candidate_too_many(nodes):
+    """A root whose first 64 suffixes have one child more than the tree has nodes, or three, against one with as many as it has:
+    what does not fit is left out, of the equals the last ones, and costs no more than a look at it (put in one by one:
+    1.2 times as long with 16 nodes, 1.4 with 56)."""
+    import torch
+    import paper_2411_04975_amd as sd
+    vocab, D, B, head = 400, 6, 64, 1
+    us = {}
+    for extra in (0, 1, 3) if nodes + 4 <= 64 else (0, 1):
+        kids = nodes + extra + 1  # (the last one goes on behind the 64 and enters by itself)
+        counts = np.full(kids, 64 // kids)
+        counts[:64 - counts.sum()] += 1
+        docs = [[head, 10 + i, 300 + j % 3] for i, n in enumerate(counts) for j in range(n)] + [[head, 9 + kids, 303]] * 20
+        docs = [np.array(docs[i], np.int32) for i in np.random.default_rng(kids).permutation(len(docs))]
+        contexts = [np.array([350, head], np.int32)] * B
+        g = parity.GpuPath(vocab, D, 1, float(nodes), 0.0, B, 8, sum(len(d) + 1 for d in docs))
+        try:
+            g.build_global(docs)
+            g.build_requests(range(B), contexts)
+            got = g.speculate(range(B))
+            want = parity.oracle_speculate_batch(parity.oracle_global_trie(docs, D, vocab), contexts[:1], D, 1, float(nodes), 0.0, nodes)
+            bad = parity.compare_trees(got, {k: np.repeat(v, B, 0) for k, v in want.items()})
+            assert not bad, "\n".join(bad)
+            out = sd.Trees(B, nodes, g.dev)
+            times = []
+            for _ in range(8):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                for _ in range(50):
+                    sd.sd_speculate(g.ctx, None, out)
+                b.record()
+                torch.cuda.synchronize()
+                times.append(a.elapsed_time(b) * 20)
+            us[extra] = min(times)
+        finally:
+            g.close()
+    print("%d nodes:" % nodes, us)
+    if nodes >= 16:
+        assert max(us.values()) < 1.12 * us[0]
