@@ -31,29 +31,48 @@ __device__ __forceinline__ double wave_sum(double v) {
 // *lost += what the last tokens of the documents lack: the sum of min(D, tokens left) over the positions is D for
 // every token, but for the k-th last one of a document, k < D, which has k, so a document of n tokens lacks
 // m D - m (m + 1) / 2 with m = min(n, D).  The end markers are the first entries of the suffix array (code 0 is the
-// lowest): a wave takes one and looks for the marker before it, 64 tokens at a time.  (Reading the text
-// behind every position instead: 40 us of the 10M index.)
-constexpr int SHORT_BLOCKS = 256;  // (an addition to one address each, at some 12 ns)
+// lowest): a wave takes up to 64 of them, a lane each, and looks for the markers before SHORT_AT_ONCE at a time, 64 tokens of each
+// in a load.  (Reading the text behind every position instead: 40 us of the 10M index.)
+// Bound: loads that wait for each other, so it is markers in flight that count: 2M documents of a token, 16 waves to a compute unit and
+// a marker to a wave, 365 us, four waves 1200, so 103.
+constexpr int SHORT_AT_ONCE = 8;
+constexpr int64_t SHORT_BLOCKS = 256, SHORT_BLOCKS_MANY = 1024;  // (an addition to one address each, at some 12 ns: many for 16 trips and more)
 __device__ __forceinline__ void short_ends(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
                                            const int32_t *__restrict__ bucket, int32_t D, int block, int blocks,
                                            unsigned long long *lost) {
     const int lane = threadIdx.x & 63;
     constexpr int waves = TB / 64;
-    const int64_t markers = bucket[1];
+    static_assert(64 % SHORT_AT_ONCE == 0, "");
+    const int64_t markers = bucket[1], n_waves = (int64_t)blocks * waves;
+    int64_t per = (markers + n_waves - 1) / n_waves;
+    per = per < 64 ? per : 64;
     unsigned long long sum = 0;  // (the same in all lanes)
-    for (int64_t i = (int64_t)block * waves + (threadIdx.x >> 6); i < markers; i += (int64_t)blocks * waves) {
-        const int64_t e = sa[i];
-        int m = D;
-        for (int k = 0; k < D; k += 64) {
-            const int64_t p = e - 1 - k - lane;
-            const unsigned long long b = __ballot(p < 0 || text[p < 0 ? 0 : p] < 0);
-            if (b) {
-                m = k + __builtin_ctzll(b);
-                break;
+    for (int64_t i = ((int64_t)block * waves + (threadIdx.x >> 6)) * per; i < markers; i += n_waves * per) {
+        const int n = (int)(markers - i < per ? markers - i : per);
+        const int32_t at = lane < n ? sa[i + lane] : 0;  // (0: nothing before it, which lacks nothing)
+        for (int j = 0; j < n; j += SHORT_AT_ONCE) {
+            int32_t e[SHORT_AT_ONCE];
+            bool ends[SHORT_AT_ONCE];
+#pragma unroll
+            for (int u = 0; u < SHORT_AT_ONCE; u++) {
+                e[u] = __builtin_amdgcn_readlane(at, j + u);
+                const int32_t p = e[u] - 1 - lane;
+                ends[u] = text[p < 0 ? 0 : p] < 0 || p < 0;
+            }
+#pragma unroll
+            for (int u = 0; u < SHORT_AT_ONCE; u++) {
+                unsigned long long b = __ballot(ends[u]);
+                int k = 0;
+                while (!b && k + 64 < D) {
+                    k += 64;
+                    const int32_t p = e[u] - 1 - k - lane;
+                    b = __ballot(text[p < 0 ? 0 : p] < 0 || p < 0);
+                }
+                int m = b ? k + __builtin_ctzll(b) : D;
+                if (m > D) m = D;
+                sum += (unsigned long long)m * D - (unsigned long long)m * (m + 1) / 2;
             }
         }
-        if (m > D) m = D;
-        sum += (unsigned long long)m * D - (unsigned long long)m * (m + 1) / 2;
     }
     __shared__ unsigned long long part[waves];
     if (lane == 0) part[threadIdx.x >> 6] = sum;
@@ -162,18 +181,18 @@ __device__ __forceinline__ void mark_starts(const int32_t *__restrict__ bucket, 
     }
 }
 
-// What the kernels behind this one read: the sum that the documents' ends lack (the first SHORT_BLOCKS workgroups), where
+// What the kernels behind this one read: the sum that the documents' ends lack (the first `end_blocks` workgroups), where
 // another first token begins (MARK_TOKENS codes to a workgroup) and the lines.
 __global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
                                                 const int32_t *__restrict__ bucket, int64_t N, int32_t D, int32_t n_codes,
-                                                int mark_blocks, int64_t n_lines, int bits, unsigned long long *lost,
+                                                int end_blocks, int mark_blocks, int64_t n_lines, int bits, unsigned long long *lost,
                                                 uint32_t *__restrict__ marks, uint32_t *__restrict__ lines) {
     int b = (int)blockIdx.x;
-    if (b < SHORT_BLOCKS) {
-        short_ends(text, sa, bucket, D, b, SHORT_BLOCKS, lost);
+    if (b < end_blocks) {
+        short_ends(text, sa, bucket, D, b, end_blocks, lost);
         return;
     }
-    b -= SHORT_BLOCKS;
+    b -= end_blocks;
     if (b < mark_blocks) {
         mark_starts(bucket, n_codes, b * MARK_TOKENS, marks);
         return;
@@ -438,9 +457,12 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
         sd_fill_i32(reinterpret_cast<int32_t *>(sums), 8 + N / 32 + 1, 0, st);
         const int32_t n_codes = c->cfg.vocab + 1;
         const int mark_blocks = (n_codes + MARK_TOKENS - 1) / MARK_TOKENS;
+        const int64_t ends = (c->g_docs + TB / 64 * SHORT_AT_ONCE - 1) / (TB / 64 * SHORT_AT_ONCE);
+        const int64_t many = ends / 16 < SHORT_BLOCKS_MANY ? ends / 16 : SHORT_BLOCKS_MANY;
+        const int end_blocks = (int)(ends < 1 ? 1 : ends < SHORT_BLOCKS ? ends : many > SHORT_BLOCKS ? many : SHORT_BLOCKS);
         const int64_t pack_blocks = (n_lines * LINE_POS + PACK_TILE - 1) / PACK_TILE;
-        hipLaunchKernelGGL(k_prepare, dim3((unsigned)(SHORT_BLOCKS + mark_blocks + pack_blocks)), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_bucket, N, c->cfg.D,
-                           n_codes, mark_blocks, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
+        hipLaunchKernelGGL(k_prepare, dim3((unsigned)(end_blocks + mark_blocks + pack_blocks)), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_bucket, N, c->cfg.D,
+                           n_codes, end_blocks, mark_blocks, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
         const int64_t per_block = TB / 64 * LCP_OUT;
         hipLaunchKernelGGL((step.R == 3 ? k_lcp_len<3> : step.R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
                            lines, bits, (uint32_t)step.step, step.per_bit, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);

@@ -683,3 +683,59 @@ def test_entropy_of_few_entries_and_many_tokens(n, vocab, factor):
     print("%d entries: %.1f us, %d codes %.1f" % (n, few_us, vocab, all_us))
     assert all_out[1] == few_out[1] and all_out[0] == pytest.approx(few_out[0], rel=1e-9)
     assert all_us < factor * few_us
+
+
+@pytest.mark.parametrize("docs", [1, 7, 8, 9, 64, 1023, 1024, 1025, 8192, 8193, 66_000, 140_000, 600_000])
+@pytest.mark.parametrize("D", [3, 64, 65, 200])
+def test_entropy_of_short_documents(docs, D):
+    """Up to 64 end markers to a wave, eight of them at a time, of 256 workgroups and of up to 1024: documents without a token, with a
+    few, and of about D; positions lack what their document has too little of."""
+    rng = np.random.default_rng(docs + D)
+    lens = rng.integers(0, 3, docs)
+    few = rng.integers(0, docs, min(docs, 300))
+    lens[few] = rng.integers(max(D - 2, 0), D + 3, len(few))
+    lens[few[0]] = 700
+    t = rng.integers(0, 50_000, int(lens.sum())).astype(np.int32)
+    ends = np.cumsum(lens)
+    left = np.repeat(ends, lens) - np.arange(len(t))
+    g = parity.GpuPath(60_000, D, 1, 1.0, 0.1, 1, 16, len(t) + docs + int(lens[:5].sum()) + 5)
+    try:
+        g.build_global(np.split(t, ends[:-1]))
+        _, weight = g.entropy()
+        assert weight == np.minimum(left, D).sum()
+        g.insert_global(np.split(t, ends[:-1])[:5])
+        n = int(lens[:5].sum())
+        _, weight = g.entropy()
+        assert weight == np.minimum(left, D).sum() + np.minimum(left[:n], D).sum()
+    finally:
+        g.close()
+
+
+def test_entropy_of_many_documents_costs_no_more_than_of_few():
+    """2M tokens in documents of one each against one document: 2M end markers beside half as many positions that
+    are compared.  (A marker to a wave, four waves to a compute unit: 20 times as long; so 2.5.)"""
+    import torch
+    import paper_2411_04975_amd as sd
+    dev = torch.device("cuda", 0)
+    n, us = 2_000_000, {}
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(1)
+    t = torch.randint(0, 128_256, (n,), generator=gen, device=dev, dtype=torch.int32)
+    for docs in (1, n):
+        off = torch.arange(0, n + 1, n // docs, device=dev)
+        ctx = sd.sd_create(128_256, 32, 16, 1.0, 0.1, 1, 64, n + docs + 1, 0)
+        try:
+            sd.sd_index_build(ctx, sd.SD_SCOPE_GLOBAL, None, t, off, n)
+            best = []
+            for _ in range(8):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                sd.sd_index_entropy(ctx)
+                b.record()
+                torch.cuda.synchronize()
+                best.append(a.elapsed_time(b) * 1e3)
+            us[docs] = min(best)
+        finally:
+            sd.sd_destroy(ctx)
+    print(us)
+    assert us[n] < 5 * us[1]
