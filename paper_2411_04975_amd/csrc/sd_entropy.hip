@@ -121,11 +121,21 @@ __device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N
     __shared__ uint32_t s_code[PACK_TILE + PACK_LOOK];
     __shared__ uint64_t s_end[(PACK_TILE + PACK_LOOK) / 64];
     const int tid = threadIdx.x;
-    for (int j = tid; j < PACK_TILE + PACK_LOOK; j += TB) {
-        const int64_t p = base + j;
-        const int32_t t = p < N ? text[p] : SD_END_TOKEN;
-        s_code[j] = (uint32_t)(t + 1);
-        const unsigned long long ends = __ballot(t < 0);
+    // (all loads of the tile in flight together)
+    static_assert(PACK_TILE % TB == 0 && PACK_LOOK <= TB && PACK_LOOK % 64 == 0, "a wave has all of its last tokens or none");
+    constexpr int ITEMS = PACK_TILE / TB + 1;
+    int32_t t[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const int64_t p = base + k * TB + tid;
+        t[k] = (k < ITEMS - 1 || tid < PACK_LOOK) && p < N ? text[p] : SD_END_TOKEN;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const int j = k * TB + tid;
+        if (k == ITEMS - 1 && tid >= PACK_LOOK) break;
+        s_code[j] = (uint32_t)(t[k] + 1);
+        const unsigned long long ends = __ballot(t[k] < 0);
         if ((tid & 63) == 0) s_end[j >> 6] = ends;
     }
     __syncthreads();
@@ -153,19 +163,23 @@ __device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N
 // one word, if it is more than a few.  (An addition for every code, with an entry or without, is one to a few words for most codes of a small index
 // or a large vocabulary: k_prepare over 1000 entries and a vocabulary of 128k 801 us, 7.6 so; over 10M entries and one of 2^24
 // 812 and 57; of 128k 22 either way.)
-constexpr int MARK_TOKENS = 8 * TB;
+// A lane has MARK_FEW codes in up to MARK_FEW_BLOCKS workgroups and MARK_MANY in more: on few compute units what a lane does one after
+// the other is what k_prepare waits for (700k entries, 32k codes 8.9 us by eights, 6.4 by twos), and many workgroups
+// cost more than that (2^24 codes 18.7 and 28.4).
+constexpr int MARK_FEW = 2, MARK_MANY = 8, MARK_FEW_BLOCKS = 512;
+template <int ITEMS>
 __device__ __forceinline__ void mark_starts(const int32_t *__restrict__ bucket, int32_t n_codes, int32_t first,
                                             uint32_t *__restrict__ marks) {
     const int lane = threadIdx.x & 63;
-    int32_t at[MARK_TOKENS / TB], next[MARK_TOKENS / TB];
+    int32_t at[ITEMS], next[ITEMS];
 #pragma unroll
-    for (int k = 0; k < MARK_TOKENS / TB; k++) {
+    for (int k = 0; k < ITEMS; k++) {
         const int32_t c = first + k * TB + (int32_t)threadIdx.x;
         at[k] = bucket[c < n_codes ? c : n_codes];  // (the last one: all entries)
         next[k] = bucket[c < n_codes ? c + 1 : n_codes];
     }
 #pragma unroll
-    for (int k = 0; k < MARK_TOKENS / TB; k++) {
+    for (int k = 0; k < ITEMS; k++) {
         const int32_t word = at[k] >> 5, before = __shfl_up(word, 1);
         uint32_t bits = at[k] != next[k] ? 1u << (at[k] & 31) : 0u;
         const bool joins = lane > 0 && before == word;
@@ -182,10 +196,10 @@ __device__ __forceinline__ void mark_starts(const int32_t *__restrict__ bucket, 
 }
 
 // What the kernels behind this one read: the sum that the documents' ends lack (the first `end_blocks` workgroups), where
-// another first token begins (MARK_TOKENS codes to a workgroup) and the lines.
+// another first token begins (`mark_blocks` workgroups) and the lines.
 __global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text, const int32_t *__restrict__ sa,
                                                 const int32_t *__restrict__ bucket, int64_t N, int32_t D, int32_t n_codes,
-                                                int end_blocks, int mark_blocks, int64_t n_lines, int bits, unsigned long long *lost,
+                                                int end_blocks, int mark_blocks, int mark_each, int64_t n_lines, int bits, unsigned long long *lost,
                                                 uint32_t *__restrict__ marks, uint32_t *__restrict__ lines) {
     int b = (int)blockIdx.x;
     if (b < end_blocks) {
@@ -194,7 +208,8 @@ __global__ __launch_bounds__(TB) void k_prepare(const int32_t *__restrict__ text
     }
     b -= end_blocks;
     if (b < mark_blocks) {
-        mark_starts(bucket, n_codes, b * MARK_TOKENS, marks);
+        if (mark_each == MARK_FEW) mark_starts<MARK_FEW>(bucket, n_codes, b * MARK_FEW * TB, marks);
+        else mark_starts<MARK_MANY>(bucket, n_codes, b * MARK_MANY * TB, marks);
         return;
     }
     pack(text, N, n_lines, bits, (int64_t)(b - mark_blocks) * PACK_TILE, lines);
@@ -456,13 +471,14 @@ sd_status sd_entropy_impl(sd_ctx *c, double *h_mean_bits, double *h_weight, hipS
         uint32_t *marks = reinterpret_cast<uint32_t *>(sums + 4);
         sd_fill_i32(reinterpret_cast<int32_t *>(sums), 8 + N / 32 + 1, 0, st);
         const int32_t n_codes = c->cfg.vocab + 1;
-        const int mark_blocks = (n_codes + MARK_TOKENS - 1) / MARK_TOKENS;
+        const int mark_each = n_codes <= MARK_FEW_BLOCKS * MARK_FEW * TB ? MARK_FEW : MARK_MANY;
+        const int mark_blocks = (n_codes + mark_each * TB - 1) / (mark_each * TB);
         const int64_t ends = (c->g_docs + TB / 64 * SHORT_AT_ONCE - 1) / (TB / 64 * SHORT_AT_ONCE);
         const int64_t many = ends / 16 < SHORT_BLOCKS_MANY ? ends / 16 : SHORT_BLOCKS_MANY;
         const int end_blocks = (int)(ends < 1 ? 1 : ends < SHORT_BLOCKS ? ends : many > SHORT_BLOCKS ? many : SHORT_BLOCKS);
         const int64_t pack_blocks = (n_lines * LINE_POS + PACK_TILE - 1) / PACK_TILE;
         hipLaunchKernelGGL(k_prepare, dim3((unsigned)(end_blocks + mark_blocks + pack_blocks)), dim3(TB), 0, st, c->g_text, c->g_sa, c->g_bucket, N, c->cfg.D,
-                           n_codes, end_blocks, mark_blocks, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
+                           n_codes, end_blocks, mark_blocks, mark_each, n_lines, bits, reinterpret_cast<unsigned long long *>(sums + 2), marks, lines);
         const int64_t per_block = TB / 64 * LCP_OUT;
         hipLaunchKernelGGL((step.R == 3 ? k_lcp_len<3> : step.R == 2 ? k_lcp_len<2> : k_lcp_len<1>), dim3((unsigned)((N + per_block - 1) / per_block)), dim3(TB), 0, st,
                            lines, bits, (uint32_t)step.step, step.per_bit, c->g_sa, c->g_tok1, marks, c->g_bucket, N, c->cfg.D, lcp, len);

@@ -685,6 +685,28 @@ def test_entropy_of_few_entries_and_many_tokens(n, vocab, factor):
     assert all_us < factor * few_us
 
 
+@pytest.mark.parametrize("vocab", [511, 512, 262_142, 262_143, 262_144, 264_191, 264_192])
+def test_entropy_marks_a_few_codes_to_a_lane(vocab):
+    """Two codes to a lane up to 512 workgroups, 262,144 codes, and eight from there on: an index whose tokens are the vocabulary's
+    last ones, and others around the ends of the workgroups."""
+    rng = np.random.default_rng(vocab)
+    used = np.unique(np.concatenate([np.arange(vocab - 400, vocab), rng.integers(0, vocab, 3000), np.arange(511, vocab, 512), np.arange(510, vocab, 2048)]))
+    used = used[used >= 0]
+    t = used[rng.integers(0, len(used), 3 * len(used))].astype(np.int32)
+    t = np.concatenate([t, t[:len(t) // 2], used.astype(np.int32)])
+    docs = np.split(t, [len(t) // 3])
+    text = np.concatenate([np.concatenate([d, [-1]]) for d in docs])
+    g = parity.GpuPath(vocab, 6, 1, 1.0, 0.1, 1, 16, len(text))
+    try:
+        g.build_global(docs)
+        got, weight = g.entropy()
+    finally:
+        g.close()
+    want, want_weight = _entropy_of(text, 6)
+    assert weight == want_weight
+    assert got == pytest.approx(want, rel=1e-9, abs=1e-12)  # (binary64 sums in another order)
+
+
 @pytest.mark.parametrize("docs", [1, 7, 8, 9, 64, 1023, 1024, 1025, 8192, 8193, 66_000, 140_000, 600_000])
 @pytest.mark.parametrize("D", [3, 64, 65, 200])
 def test_entropy_of_short_documents(docs, D):
