@@ -17,7 +17,7 @@
 // numbers; and the second-token column of the index comes from the entries: only suffixes that
 // tie are ever looked up in the text.
 //
-// Bound: the memory system.  Per position 76 bytes in order (tokens read, text, codes and lines written, text and
+// Bound: the memory system.  Per position 72 bytes in order (tokens read, text, codes and lines written, text and
 // codes read, entries written and read once per pass, suffix array and second tokens written), and
 // for each one that ties one random cache line a step: of the 0.42 ms of
 // 10M tokens copied from templates k_code_sort takes 0.23 and reads 124 bytes a position in them
@@ -1655,6 +1655,8 @@ split_plan plan_for(int64_t N) {
 // SORT_ROUNDS rounds and more of larger tiles go in these, as few as that makes, with room behind a tile for a last bucket
 // of twice the average (100M copied entries: 2.92 ms in tiles of 2099, 2.72 in 3256; 10M, four rounds of 3255 instead of six
 // of 2170: a build of independent tokens 272 -> 265 us, of copied ones 403 -> 408, for what the last round waits for).
+// Eight rounds are 18M positions on this chip.  Builds of 18.5M, 24M and 40M copied tokens 765, 967 and 1555 us in the smaller
+// tiles, 746, 949 and 1542 in the larger ones; of independent tokens 474, 623 and 995; 467, 594 and 950.
 int sort_tile_for(int64_t N, int n_cu) {
     int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
     if (slots > SORT_SLOTS) slots = SORT_SLOTS;
@@ -1815,7 +1817,7 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
 }
 
 // The tiles and the first of the last buckets that are kept apart (workgroups for a quarter as many as there are tiles:
-// one that finds nothing is over at once), or n last buckets behind those.
+// one that finds nothing is over at once; builds of 3M to 40M tokens by no more than runs differ), or n last buckets behind those.
 static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, int n, entry_shape f,
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
