@@ -162,7 +162,7 @@ __device__ __forceinline__ void pack(const int32_t *__restrict__ text, int64_t N
 // entry.  A wave takes 64 neighbouring codes at a time, whose places are in order, and brings together what falls in
 // one word, if it is more than a few.  (An addition for every code, with an entry or without, is one to a few words for most codes of a small index
 // or a large vocabulary: k_prepare over 1000 entries and a vocabulary of 128k 801 us, 7.6 so; over 10M entries and one of 2^24
-// 812 and 57; of 128k 22 either way.)
+// 812 and 57; of 128k the same either way.)
 // A lane has MARK_FEW codes in up to MARK_FEW_BLOCKS workgroups and MARK_MANY in more: on few compute units what a lane does one after
 // the other is what k_prepare waits for (700k entries, 32k codes 8.9 us by eights, 6.4 by twos), and many workgroups
 // cost more than that (2^24 codes 18.7 and 28.4).
