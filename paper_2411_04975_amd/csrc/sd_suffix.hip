@@ -32,6 +32,8 @@
 #include "sd_internal.h"
 #include "sd_sample.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int CT = 512;            // threads of a workgroup, everywhere in this file
@@ -48,16 +50,27 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// inclusive prefix sum over the wave, by data-parallel moves: inside rows of 16 lanes, then across them
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    auto from = [&](auto ctrl, auto rows) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0xf> all;
+    v += from(integral_constant<int, 0x111>(), all);  // the value 1, 2, 4, 8 lanes before
+    v += from(integral_constant<int, 0x112>(), all);
+    v += from(integral_constant<int, 0x114>(), all);
+    v += from(integral_constant<int, 0x118>(), all);
+    v += from(integral_constant<int, 0x142>(), integral_constant<int, 0xa>());  // the last lane of the row before
+    v += from(integral_constant<int, 0x143>(), integral_constant<int, 0xc>());  // lane 31
+    return v;
+}
+
 // exclusive prefix sum of one value per thread over the workgroup, and the total; two barriers
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_wave /*[CW]*/,
                                                     uint32_t *total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
+    const uint32_t inc = wave_incl_scan(v);
     if (lane == 63) s_wave[w] = inc;
     __syncthreads();
     uint32_t base = 0, tot = 0;
@@ -653,12 +666,17 @@ __device__ __forceinline__ bin_place first_bin(const uint32_t *__restrict__ star
 
 constexpr int SPLIT2_ITEMS = 12, SPLIT2_TILE = CT * SPLIT2_ITEMS;
 
-// Second split, inside every bin of the first one, tile by tile of the bin.  The tiles of all bins are
+// Second split, inside every bin of the first one, tile by tile of the bin: a tile's entries are ordered by digit where
+// they lie, and a row of the tile says where each digit's begin.  Who wants a bucket takes its share from each of the
+// bin's tiles (7 of them and 44 entries from each on average at 10M entries, 32 and 12 at 100M; k_code_sort takes some 2000 to
+// 3000 entries of neighbouring buckets), so nothing has to be counted before entries can move: hist, places and split
+// were 14 + 6.5 + 33 us at 10M and 174 + 28 + 336 at 100M.
+// The tiles of all bins are
 // numbered: bin b's from start / SPLIT2_TILE + b on, which leaves room for what the bins before it have.
 // A workgroup takes one number and looks up whose it is, if anyone's.  (A bin holds as much as its
 // codes do, and all of a text that is one token over and over: a fixed share of the grid for each bin
-// left that to 8 workgroups of 2048, 10M tokens: 1.2 ms in the count, 1.7 in the split.)
-// The counts of tile number g lie in row g: (g, digit).
+// left that to 8 workgroups of 2048, 10M tokens: 1.7 ms in the split.)
+// The row of tile number g is row g.
 __device__ __forceinline__ int first_tile(uint32_t start, int bin) { return (int)(start / SPLIT2_TILE) + bin; }
 
 struct bin_tile { int64_t at; int cnt; };  // the entries; none: no such tile
@@ -678,74 +696,69 @@ __device__ __forceinline__ bin_tile tile_of(const uint32_t *__restrict__ starts1
     return {(int64_t)s_first[0] + skip, left <= 0 ? 0 : left < SPLIT2_TILE ? (int)left : SPLIT2_TILE};
 }
 
-__global__ __launch_bounds__(CT) void k_code_hist2(const uint64_t *__restrict__ in,
-                                                   const uint32_t *__restrict__ starts1, int bins1, int shift,
-                                                   int bins2, uint32_t *__restrict__ hist2) {
-    __shared__ uint32_t s_hist[MAX_BINS];
+// rows: [tile][digit], where the digit's entries begin, counted from the tile's first.
+__global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__ in,
+                                                    const uint32_t *__restrict__ starts1, int bins1, int shift,
+                                                    int bins2, uint16_t *__restrict__ rows,
+                                                    uint64_t *__restrict__ out) {
+    __shared__ alignas(16) uint64_t s_entry[SPLIT2_TILE];
+    __shared__ uint32_t s_cnt[MAX_BINS];
+    __shared__ uint32_t s_wave[CW];
+    static_assert(SPLIT2_TILE < 1 << 16, "places of 16 bits");
     const int tid = threadIdx.x;
-    for (int i = tid; i < bins2; i += CT) s_hist[i] = 0;
-    const bin_tile t = tile_of(starts1, bins1, (int)blockIdx.x);
+    const int g = tile_of_block();
+    for (int i = tid; i < bins2; i += CT) s_cnt[i] = 0;
+    const bin_tile t = tile_of(starts1, bins1, g);
     if (t.cnt == 0) return;
     uint64_t e[SPLIT2_ITEMS];
+    uint32_t rank[SPLIT2_ITEMS];
+    auto digit = [&](uint64_t v) { return (uint32_t)(v >> shift) & ((uint32_t)bins2 - 1u); };
 #pragma unroll
     for (int k = 0; k < SPLIT2_ITEMS; k++) e[k] = k * CT + tid < t.cnt ? in[t.at + k * CT + tid] : 0ull;
 #pragma unroll
     for (int k = 0; k < SPLIT2_ITEMS; k++)
-        if (k * CT + tid < t.cnt) atomicAdd(&s_hist[(uint32_t)(e[k] >> shift) & ((uint32_t)bins2 - 1u)], 1u);
+        if (k * CT + tid < t.cnt) rank[k] = atomicAdd(&s_cnt[digit(e[k])], 1u);
     __syncthreads();
-    for (int i = tid; i < bins2; i += CT) hist2[(int64_t)blockIdx.x * bins2 + i] = s_hist[i];
+    const int d = 2 * tid;  // MAX_BINS / CT digits per thread
+    const uint32_t a = d < bins2 ? s_cnt[d] : 0u, b = d < bins2 ? s_cnt[d + 1] : 0u;
+    uint32_t tot;
+    const uint32_t ex = block_excl_scan(a + b, s_wave, &tot);
+    if (d < bins2) {
+        s_cnt[d] = ex;
+        s_cnt[d + 1] = ex + a;
+        *reinterpret_cast<uint32_t *>(rows + (int64_t)g * bins2 + d) = ex | (ex + a) << 16;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SPLIT2_ITEMS; k++)
+        if (k * CT + tid < t.cnt) s_entry[s_cnt[digit(e[k])] + rank[k]] = e[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SPLIT2_ITEMS; k++)
+        if (k * CT + tid < t.cnt) out[t.at + k * CT + tid] = s_entry[k * CT + tid];
 }
 
-// one workgroup per bin of the first split: places of its tiles' digits, and of its buckets
-__global__ __launch_bounds__(CT) void k_code_places2(const uint32_t *__restrict__ starts1, int bins2,
-                                                     uint32_t *__restrict__ hist2,
+// One workgroup per bin of the first split: where its buckets start, in the order in which k_code_sort leaves the
+// entries.  (The entries of lower digits are what lies in front of a digit in each tile.)
+__global__ __launch_bounds__(CT) void k_code_starts2(const uint32_t *__restrict__ starts1, int bins2,
+                                                     const uint16_t *__restrict__ rows,
                                                      uint32_t *__restrict__ starts, uint32_t N) {
-    __shared__ uint32_t s_wave[CW];
-    const int bin = blockIdx.x;
+    const int bin = blockIdx.x, d = 2 * (int)threadIdx.x;
     const bin_place p = first_bin(starts1, bin);
     const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
-    uint32_t *row = hist2 + (int64_t)first_tile(p.start, bin) * bins2;
-    uint32_t all[2] = {0, 0}, tot;
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-        const int d = 2 * (int)threadIdx.x + q;
-        if (d >= bins2) continue;
-#pragma unroll 8
-        for (int i = 0; i < nt; i++) all[q] += row[(int64_t)i * bins2 + d];
-    }
-    uint32_t at = p.start + block_excl_scan(all[0] + all[1], s_wave, &tot);
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-        const int d = 2 * (int)threadIdx.x + q;
-        if (d >= bins2) continue;
-        starts[(int64_t)bin * bins2 + d] = at;
+    const uint16_t *row = rows + (int64_t)first_tile(p.start, bin) * bins2 + d;
+    if (d < bins2) {
+        uint32_t at[2] = {p.start, p.start};
 #pragma unroll 8
         for (int i = 0; i < nt; i++) {
-            const uint32_t v = row[(int64_t)i * bins2 + d];
-            row[(int64_t)i * bins2 + d] = at;
-            at += v;
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(row + (int64_t)i * bins2);
+            at[0] += v & 0xffffu;
+            at[1] += v >> 16;
         }
+        starts[(int64_t)bin * bins2 + d] = at[0];
+        starts[(int64_t)bin * bins2 + d + 1] = at[1];
     }
     if (bin == (int)gridDim.x - 1 && threadIdx.x == 0) starts[(int64_t)gridDim.x * bins2] = N;
-}
-
-__global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__ in,
-                                                    const uint32_t *__restrict__ starts1, int bins1, int shift,
-                                                    int bins2, const uint32_t *__restrict__ hist2,
-                                                    uint64_t *__restrict__ out) {
-    __shared__ split_lds<SPLIT2_ITEMS> s;
-    const int tid = threadIdx.x;
-    const int g = tile_of_block();
-    const bin_tile t = tile_of(starts1, bins1, g);
-    if (t.cnt == 0) return;
-    uint64_t e[SPLIT2_ITEMS];
-    uint32_t digit[SPLIT2_ITEMS];
-#pragma unroll
-    for (int k = 0; k < SPLIT2_ITEMS; k++) e[k] = k * CT + tid < t.cnt ? in[t.at + k * CT + tid] : 0ull;
-#pragma unroll
-    for (int k = 0; k < SPLIT2_ITEMS; k++) digit[k] = (uint32_t)(e[k] >> shift) & ((uint32_t)bins2 - 1u);
-    for (int i = tid; i < bins2; i += CT) s.to[i] = hist2[(int64_t)g * bins2 + i];
-    split_tile<SPLIT2_ITEMS>(s, e, digit, t.cnt, bins2, out);
 }
 
 // ---- ordering whole buckets in LDS ------------------------------------------------------------
@@ -806,6 +819,46 @@ __device__ __forceinline__ sort_range between(const sort_bound &r, const sort_bo
 // is left that no workgroup takes.
 struct sort_cut { sort_range first, last; };  // of a tile that is not sortable as it is
 
+// What the second split has left, see there.  rows = nullptr: there was none, entries lie in the order of their buckets.
+struct split_rows {
+    const uint32_t *starts1;
+    const uint16_t *rows;
+};
+// Where the entries of a workgroup's buckets lie: a piece in each of their bin's tiles, in the bin's order.
+struct sort_pieces {
+    uint32_t n;              // 0: the workgroup looks for them itself
+    uint32_t from[SD_WAVE];  // of a piece: where it lies, less the place of its first entry, counted from the workgroup's first
+    uint16_t last[SD_WAVE];  // the place of its last entry
+};
+
+// One wave: the pieces of the range f, if it is of one bin or two neighbouring ones, of up to 64 tiles together, and its buckets'
+// last bits tell them apart.
+__device__ __forceinline__ void find_pieces(const split_rows &split, int bits2, const sort_range &f, sort_pieces *to) {
+    const int lane = threadIdx.x & 63, bins2 = 1 << bits2, B0 = (int)f.bucket >> bits2, B1 = (int)(f.end - 1) >> bits2;
+    const bin_place p0 = first_bin(split.starts1, B0), p1 = B1 > B0 ? first_bin(split.starts1, B1) : bin_place{0u, 0u};
+    const int nt0 = (int)((p0.size + SPLIT2_TILE - 1) / SPLIT2_TILE), nt1 = (int)((p1.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+    uint32_t from = 0, len = 0;
+    const bool easy = B1 - B0 <= 1 && nt0 + nt1 <= SD_WAVE && (int)(f.end - f.bucket) <= bins2;
+    if (easy && lane < nt0 + nt1) {
+        const bool second = lane >= nt0;
+        const bin_place p = second ? p1 : p0;
+        const int B = second ? B1 : B0, t = second ? lane - nt0 : lane;
+        const int d0 = B == B0 ? (int)f.bucket & (bins2 - 1) : 0, d1 = B == B1 ? ((int)(f.end - 1) & (bins2 - 1)) + 1 : bins2;
+        const uint16_t *row = split.rows + (int64_t)(first_tile(p.start, B) + t) * bins2;
+        const uint32_t left = p.size - (uint32_t)t * SPLIT2_TILE, at = row[d0];
+        len = (d1 < bins2 ? row[d1] : left < (uint32_t)SPLIT2_TILE ? left : (uint32_t)SPLIT2_TILE) - at;
+        from = p.start + (uint32_t)t * SPLIT2_TILE + at;
+    }
+    const uint32_t inc = wave_incl_scan(len);
+    const uint64_t some = __ballot(len != 0);
+    if (lane == 0) to->n = (uint32_t)__popcll(some);
+    if (len) {
+        const int i = __popcll(some & ((1ull << lane) - 1ull));
+        to->from[i] = from - (inc - len);
+        to->last[i] = (uint16_t)(inc - 1u);
+    }
+}
+
 // The tiles' bounds, and the cuts where they are needed; *rest tells the host that there is more to do
 // than k_code_sort over the tiles.
 // A wave finds where a tile's buckets start; the eighth wave of a workgroup looks at the next workgroup's
@@ -814,7 +867,8 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
                                                     int tile, int tiles, const uint32_t *__restrict__ cdf,
                                                     int32_t n_codes, sort_bound *__restrict__ bounds,
                                                     sort_cut *__restrict__ cuts, sort_range *__restrict__ lasts,
-                                                    uint32_t *n_lasts, int taken, int32_t *rest) {
+                                                    uint32_t *n_lasts, int taken, int32_t *rest, split_rows split, int bits2,
+                                                    sort_pieces *__restrict__ pieces) {
     __shared__ sort_bound s_bound[CW];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
     const int t = (int)blockIdx.x * (CW - 1) + w;
@@ -840,7 +894,10 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
     if (w == CW - 1 || t >= tiles) return;
     const sort_bound z = s_bound[w + 1];
     sort_range f = between(s_bound[w], z);
-    if (sortable(f)) return;
+    if (sortable(f)) {
+        if (split.rows && f.at != f.end_at) find_pieces(split, bits2, f, pieces + t);
+        return;
+    }
     const uint32_t b = (uint32_t)wave_lower_bound(start, buckets, (int64_t)z.at) - 1;  // of the last entry
     sort_range l = {b, b, z.at, z.at, z.code, z.code};
     f.end = b + 1;
@@ -934,7 +991,7 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
 }
 
 template <int R>
-__global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ in,
+__global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict__ in, split_rows split, const sort_pieces *__restrict__ pieces,
                                                   const uint32_t *__restrict__ starts,
                                                   const sort_bound *__restrict__ bounds,
                                                   const sort_cut *__restrict__ cuts,
@@ -960,10 +1017,13 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int down = 32 - f.bits1 - f.bits2, low_bits = f.pos_bits + f.tok_bits;
     sort_range range;
+    bool found = false;  // pieces[] has where its entries lie
     if ((int)blockIdx.x < tiles) {
         range = between(bounds[blockIdx.x], bounds[blockIdx.x + 1]);
+        found = split.rows && pieces[blockIdx.x].n != 0;
         if (__builtin_expect(!sortable(range), 0)) {
             range = cuts[blockIdx.x].first;
+            found = false;
             if (!sortable(range)) return;
         }
     } else {  // (behind the tiles: their last buckets that are kept apart)
@@ -984,14 +1044,71 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     if (tid < SORT_CAP / 32) s_done[tid] = 0;
     if (tid == 0) s_n_long = s_n_todo = 0;
     const int n = (int)(z - a);
+    const uint32_t start = tid <= nb ? starts[b0 + tid] : 0u;
+    const bool named = nb <= 1 << f.bits2;  // the entries have so many of their buckets' last bits that these tell them apart
     uint64_t e[SORT_ITEMS];
+    int base[SORT_ITEMS];
+    if (split.rows) {
+        uint32_t *s_from = reinterpret_cast<uint32_t *>(s_entry);           // of a piece, as above
+        int16_t *s_base = reinterpret_cast<int16_t *>(s_from + SORT_CAP);   // its bin's first bucket, counted from b0
+        uint64_t *s_ends = s_entry + 3 * SORT_CAP / 4;                      // a bit per place: a piece ends here
+        static_assert(sizeof(s_entry) >= SORT_CAP * 6 + SORT_CAP / 8 && SORT_CAP == 64 * 64, "");
+        if (w == 0) s_ends[lane] = 0;
+        if (found) {
+            if (w == 0 && lane < (int)pieces[blockIdx.x].n) {
+                const uint32_t last = pieces[blockIdx.x].last[lane];
+                s_from[lane] = pieces[blockIdx.x].from[lane];
+                atomicOr(reinterpret_cast<uint32_t *>(s_ends) + (last >> 5), 1u << (last & 31));
+            }
+        } else {
+            const int bins2 = 1 << f.bits2, B0 = b0 >> f.bits2, B1 = ((int)range.end - 1) >> f.bits2;
+            uint32_t done = 0, n_pieces = 0;
+            for (int B = B0; B <= B1; B++) {
+                const bin_place p = first_bin(split.starts1, B);
+                const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+                const int d0 = B == B0 ? b0 & (bins2 - 1) : 0, d1 = B == B1 ? (((int)range.end - 1) & (bins2 - 1)) + 1 : bins2;
+                const uint16_t *rows = split.rows + (int64_t)first_tile(p.start, B) * bins2;
+                for (int t0 = 0; t0 < nt; t0 += CT) {
+                    const int t = t0 + tid;
+                    uint32_t from = 0, len = 0, tot;
+                    if (t < nt) {
+                        const uint32_t left = p.size - (uint32_t)t * SPLIT2_TILE;
+                        from = rows[(int64_t)t * bins2 + d0];
+                        len = (d1 < bins2 ? rows[(int64_t)t * bins2 + d1] : left < SPLIT2_TILE ? left : SPLIT2_TILE) - from;
+                    }
+                    const uint32_t ex = block_excl_scan(len | (len ? 1u << 16 : 0u), s_wave, &tot);
+                    if (len) {
+                        const uint32_t to = done + (ex & 0xffffu), last = to + len - 1;
+                        s_base[n_pieces + (ex >> 16)] = (int16_t)((B << f.bits2) - b0);
+                        s_from[n_pieces + (ex >> 16)] = p.start + (uint32_t)t * SPLIT2_TILE + from - to;
+                        atomicOr(reinterpret_cast<uint32_t *>(s_ends) + (last >> 5), 1u << (last & 31));
+                    }
+                    done += tot & 0xffffu;
+                    n_pieces += tot >> 16;
+                }
+            }
+        }
+        __syncthreads();
+        const uint64_t ends = s_ends[lane];
+        const uint32_t before = wave_incl_scan((uint32_t)__popcll(ends)) - (uint32_t)__popcll(ends);  // pieces that end in front of the lane's 64 places
 #pragma unroll
-    for (int k = 0; k < SORT_ITEMS; k++) {
-        const int j = k * CT + tid;
-        e[k] = j < n ? in[a + j] : 0ull;
+        for (int k = 0; k < SORT_ITEMS; k++) {
+            const int j = k * CT + tid, q = k * CW + w;
+            const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)ends, q), hi = __builtin_amdgcn_readlane((int)(uint32_t)(ends >> 32), q);
+            const uint32_t piece = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, (uint32_t)__builtin_amdgcn_readlane((int)before, q)));
+            e[k] = j < n ? in[s_from[piece] + (uint32_t)j] : 0ull;
+            base[k] = !named && j < n ? (int)s_base[piece] : 0;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < SORT_ITEMS; k++) {
+            const int j = k * CT + tid;
+            e[k] = j < n ? in[a + j] : 0ull;
+        }
     }
-    for (int i = tid; i <= nb; i += CT) s_start[i] = (uint32_t)(starts[b0 + i] - a);
-    __syncthreads();
+    if (tid <= nb) s_start[tid] = start - (uint32_t)a;
+    for (int i = CT + tid; i <= nb; i += CT) s_start[i] = starts[b0 + i] - (uint32_t)a;
+    if (!split.rows) __syncthreads();
     // parts: 2^fine per bucket
     const int in_bucket = f.key_bits - f.bits2;
     int fine = 31 - __builtin_clz(SORT_PARTS / nb);
@@ -999,15 +1116,16 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
     const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
     // (Looked up in the entry and not among the buckets' places, and parts counted four entries at a time: 10M independent
     // tokens 90.8 -> 86.7 us, copied ones as before.)
-    const bool named = nb <= 1 << f.bits2;
     uint32_t part[SORT_ITEMS], rank[SORT_ITEMS];
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++) {
         const int j = k * CT + tid;
         if (j < n) {
             int lo = 0;
-            if (named) {  // (the entry has the bucket's last bits)
+            if (named) {
                 lo = (int)(((uint32_t)(e[k] >> low_bits) >> in_bucket) - (uint32_t)b0) & ((1 << f.bits2) - 1);
+            } else if (split.rows) {
+                lo = base[k] + ((int)((uint32_t)(e[k] >> low_bits) >> in_bucket) & ((1 << f.bits2) - 1));
             } else {      // last bucket that starts at or before place j
                 for (int hi = nb; hi - lo > 1;) {
                     const int mid = (lo + hi) >> 1;
@@ -1201,12 +1319,7 @@ __global__ __launch_bounds__(CT) void k_code_sort(const uint64_t *__restrict__ i
             if (w == 0) {  // what lies before each run of 64 entries, below and equal
                 const bool some = lane * 64 < k;
                 const uint32_t v = some ? (uint32_t)__popcll(s_class[0][lane]) | (uint32_t)__popcll(s_class[1][lane]) << 16 : 0u;
-                uint32_t inc = v;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t u = __shfl_up(inc, o);
-                    if (lane >= o) inc += u;
-                }
+                const uint32_t inc = wave_incl_scan(v);
                 s_before[lane] = inc - v;
                 if (lane == 63) s_before[64] = inc;
             }
@@ -1573,12 +1686,7 @@ __global__ __launch_bounds__(CT) void k_rest_keys(const uint32_t *__restrict__ c
     __syncthreads();
     if (threadIdx.x < 64) {
         const uint32_t v = s_at[threadIdx.x];
-        uint32_t inc = v;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t u = __shfl_up(inc, o);
-            if (lane >= o) inc += u;
-        }
+        const uint32_t inc = wave_incl_scan(v);
         s_at[threadIdx.x] = to[blockIdx.x] + inc - v;
     }
     __syncthreads();
@@ -1689,7 +1797,7 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
         const split_plan p = plan_for(n);
         const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
         int64_t x = ((n + tile - 1) / tile) << p.bits1;
-        if (p.bits2) x += (n / SPLIT2_TILE + (1ll << p.bits1) + 1) << p.bits2;
+        if (p.bits2) x += (((n / SPLIT2_TILE + (1ll << p.bits1)) << p.bits2) / 2) + (1ll << p.bits1) + 16;
         h = x > h ? x : h;
         const int64_t y = (1ll << (p.bits1 + p.bits2)) + 1;
         s = y > s ? y : s;
@@ -1701,7 +1809,7 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     int64_t tiles = cap / SORT_TILE_FEW < SORT_SLOTS ? cap / SORT_TILE_FEW : SORT_SLOTS;
     const int64_t least = (int64_t)SORT_TILE_MIN * (SORT_ROUNDS - 1) / SORT_ROUNDS;
     if (tiles < cap / least) tiles = cap / least;
-    *range_words = (tiles + 2) * (int64_t)((2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
+    *range_words = (tiles + 2) * (int64_t)((sizeof(sort_pieces) + 2 * sizeof(rest_range) + sizeof(sort_cut) + sizeof(sort_range) + sizeof(sort_bound)) / 4);
     *rest_words = (cap + REST_TILE - 1) / REST_TILE + 1;
 }
 
@@ -1793,6 +1901,12 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
+// Tables of a split in two, in b_hist: where the bins of the first split start, the rows of the second one's tiles.
+static int64_t starts1_words(entry_shape f) { return ((1ll << f.bits1) + 1 + 3) / 4 * 4; }
+static int64_t rows2_words(int64_t N, entry_shape f) { return (((N / SPLIT2_TILE + (1ll << f.bits1)) << f.bits2) / 2 + 3) / 4 * 4; }
+static uint32_t *starts1_room(const sd_ctx *c) { return c->b_hist; }
+static uint16_t *rows2_room(const sd_ctx *c, entry_shape f) { return reinterpret_cast<uint16_t *>(c->b_hist + starts1_words(f)); }
+
 // The tables of ranges, in b_ranges.
 struct sort_tables {
     int tile, tiles;
@@ -1802,12 +1916,14 @@ struct sort_tables {
     uint32_t *n_lasts;
     int taken;           // of them are taken with the tiles
     rest_range *rest;    // two for every tile
+    sort_pieces *pieces; // of every tile, after a split in two
 };
 static sort_tables tables_for(const sd_ctx *c, int64_t N) {
     sort_tables t;
     t.tile = sort_tile_for(N, c->n_cu);
     t.tiles = (int)((N + t.tile - 1) / t.tile);
-    t.rest = reinterpret_cast<rest_range *>(c->b_ranges);
+    t.pieces = reinterpret_cast<sort_pieces *>(c->b_ranges);
+    t.rest = reinterpret_cast<rest_range *>(t.pieces + t.tiles);
     t.bounds = reinterpret_cast<sort_bound *>(t.rest + 2 * (int64_t)t.tiles);
     t.cuts = reinterpret_cast<sort_cut *>(t.bounds + t.tiles + 1);
     t.lasts = reinterpret_cast<sort_range *>(t.cuts + t.tiles);
@@ -1822,8 +1938,10 @@ static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
     const packed_text packed = {line_room(c), bits, 128 * R / bits};
+    const split_rows split = {starts1_room(c), f.bits2 ? rows2_room(c, f) : nullptr};
     SD_LAUNCH(c, SD_K_CODE_SORT, st, (R == 3 ? k_code_sort<3> : R == 2 ? k_code_sort<2> : k_code_sort<1>),
-              dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
+              dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries,
+              split, t.pieces, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
               n ? t.taken : 0, f, packed, c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
 
@@ -1842,8 +1960,9 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     const int64_t ntiles = (N + tile - 1) / tile;
     uint32_t *keys = c->b_flags;
     uint64_t *ent1 = c->b_keys[0], *ent2 = c->b_keys[1];
-    uint32_t *hist = c->b_hist, *starts1 = f.bits2 ? hist + ntiles * bins1 : c->b_starts;
-    uint32_t *hist2 = hist + ntiles * bins1 + bins1 + 1;
+    uint32_t *hist = c->b_hist, *starts1 = f.bits2 ? starts1_room(c) : c->b_starts;
+    uint16_t *rows2 = rows2_room(c, f);
+    hist = c->b_hist + (f.bits2 ? starts1_words(f) + rows2_words(N, f) : 0);
     int per_chunk = (int)((ntiles + MAX_CHUNKS - 1) / MAX_CHUNKS);
     if (per_chunk < MIN_PER_CHUNK) per_chunk = MIN_PER_CHUNK;
     const int chunks = (int)((ntiles + per_chunk - 1) / per_chunk);
@@ -1862,13 +1981,13 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     if (p.bits2) {
         const dim3 grid2((unsigned)(N / SPLIT2_TILE + bins1));
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
-        SD_LAUNCH(c, SD_K_SORT_HIST, st, k_code_hist2, grid2, block, 0, ent1, starts1, bins1, shift, bins2, hist2);
-        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places2, dim3(bins1), block, 0, starts1, bins2, hist2, c->b_starts, (uint32_t)N);
-        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, bins1, shift, bins2, hist2, ent2);
+        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, bins1, shift, bins2, rows2, ent2);
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_starts2, dim3(bins1), block, 0, starts1, bins2, rows2, c->b_starts, (uint32_t)N);
         ent1 = ent2;
     }
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
-              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, t.lasts, t.n_lasts, t.taken, c->h_flag);
+              c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, t.lasts, t.n_lasts, t.taken, c->h_flag,
+              split_rows{starts1_room(c), f.bits2 ? rows2_room(c, f) : nullptr}, f.bits2, t.pieces);
     const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
     sort_ranges(c, ent1, t, 0, f, sa, tok1, bucket, st);
     return asked;
