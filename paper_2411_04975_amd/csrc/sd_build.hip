@@ -612,7 +612,7 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
         hipEventSynchronize(c->code_asked) != hipSuccess)  // (the sort is still running)
         return SD_ERR_HIP;
     c->code_misfit = *const_cast<volatile int32_t *>(c->h_flag) != 0;
-    if (c->code_misfit && sd_code_rest(c, N, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
+    if (c->code_misfit && sd_code_rest(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
     return hipGetLastError() == hipSuccess ? SD_OK : SD_ERR_HIP;
 }
 

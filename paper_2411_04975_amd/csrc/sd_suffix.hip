@@ -196,6 +196,8 @@ __global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ coun
 // others, or have some two hundred entries more.)
 constexpr int CDF_QUANTUM = 5;
 constexpr int CDF_BLOCKS = 4096, CDF_MAX_SHIFT = 7;
+// (What is left over behind the last of them belongs to no code.  Every code has a weight of UNSEEN and more of less than 2^27: no part is empty.)
+__device__ __forceinline__ uint32_t even_part(uint32_t width, int shift) { return width >> shift; }
 __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, int32_t n_codes,
                                                  const uint32_t *__restrict__ partials,
                                                  uint32_t *__restrict__ cdf, int shift, uint32_t slack, uint32_t *__restrict__ blocks) {
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
         if (c0 + k <= n_codes)
-            cdf[c0 + k] = (even ? lo + (uint32_t)((uint64_t)width * (uint32_t)(c0 + k - b0) >> shift) : end(at)) << CDF_QUANTUM;
+            cdf[c0 + k] = (even ? lo + even_part(width, shift) * (uint32_t)(c0 + k - b0) : end(at)) << CDF_QUANTUM;
         at += wgt[k];
     }
     if (c0 == b0 && b0 <= n_codes) {
@@ -248,15 +250,15 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 
 // ---- the text, the codes of its positions, and the first split's bins per tile ------------------
 // text = documents one after the other, an end marker behind each and SD_TEXT_PAD more behind the
-// last: document j starts at offs[j] + j.  The tile's documents are looked up once, in the offsets
-// in memory, and each position then among these in LDS.
+// last: document j starts at offs[j] + j.  The tile's end markers are bits in LDS: how many lie in front of a position says which
+// token it has (looked up among documents' starts by bisection, a position at a time: 73.8 -> 68.4 us for 10M tokens, with 1024 threads).
 //
 // A position's interval comes from the table of blocks in LDS, but for blocks of unlike tokens, whose tokens
 // ask for theirs in memory.  Asking for all of them there takes a line of the L2 per position, and as many bytes of L2 as that are
-// a limit of their own: 71 us for 10M tokens, 128k of them different, and 586 for 100M, without the lines below; with the table, and
-// the lines, 58 and 470.  The table takes as little LDS as leaves room for four workgroups on a compute unit: what a
-// workgroup waits for are loads and other waves (10M, tables of 10,240, 5120 and 4096 blocks, two, three and four workgroups: 85, 67, 58;
-// 2048 blocks: 58).  Inputs of less than a few million tokens ask in memory (2.2M: 22.2, by blocks 22.8).
+// a limit of their own (without the split and the lines: 71 us for 10M tokens, 128k of them different, and 58 with the table).
+// Bound: vector instructions (half of the time, 120 per 64 positions) and the latency of the loads, between barriers, of three workgroups on a
+// compute unit; 10M and 100M tokens 65 and 525 us, 24 bytes a position are 48 and 480 at the copy's rate.  (1024 threads, two workgroups: 68 and 630; tiles of 4096
+// so: 75 and 740, for the second split's pieces are shorter too.)  Inputs of less than a few million tokens ask for intervals in memory (2.2M: 22.2, by blocks 22.8).
 //
 // Also on the way: the text once more, in lines of 128 bytes that each hold the codes of the tokens from
 // position 32 k on, as many as the line has room for (LINE_BITS_MIN bits a code or more: 40 to 64 of them), one bit string
@@ -264,199 +266,236 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 // 1024 / bits - 31 of them (29 of 17 bits), and bit strings compare as the tokens do: what has to look at
 // suffixes in any order reads a line each time, where 48 bytes of 32-bit tokens, twelve, are 1.34 lines.
 constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
-constexpr int LDS_DOCS = 1024;
 constexpr int LINE_POS = 32;       // positions from one line to the next: a line has as many words
 constexpr int LINE_BITS_MIN = 16;  // (a word holds parts of three codes at most)
 constexpr int LAYOUT_LOOK = 1024 / LINE_BITS_MIN - LINE_POS;  // tokens behind a round of positions that it looks at
 static_assert(LAYOUT_LOOK >= CODE_LOOK && LAYOUT_LOOK <= CT && KEY_ROUND % LINE_POS == 0, "");
 
 enum { TEXT_ONLY = 0, CODES_DIRECT, CODES_BY_BLOCK };
-template <int ITEMS, int KIND>
-__global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ tokens,
+
+// The bits of an entry, from the lowest: position, code of the second token, code of the suffix
+// without its first bits1 bits and perhaps without a few of its last ones.
+struct entry_shape {
+    int bits1, bits2;         // of the code: split off by the first and by the second split
+    int pos_bits, tok_bits;
+    int key_bits, key_drop;   // of the code: in the entry, and left out below
+};
+__device__ __forceinline__ uint64_t entry_of(const entry_shape &f, uint32_t key, uint32_t second, int64_t pos) {
+    const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
+    return (((rest << f.tok_bits) | second) << f.pos_bits) | (uint64_t)pos;
+}
+
+// What k_layout has in LDS round by round, and then, entries that it splits.
+template <int T, int ROUNDS, int KIND, bool SPLIT>
+struct layout_lds {
+    static constexpr int MARKS = (ROUNDS * KEY_ROUND + LAYOUT_LOOK + 63) / 64;
+    union {
+        struct {
+            uint2 code[KIND == TEXT_ONLY ? 1 : KEY_ROUND + CODE_LOOK];  // (lower end, width) of each token's interval
+            uint32_t tok[KIND == TEXT_ONLY ? 1 : KEY_ROUND + LAYOUT_LOOK];
+            uint32_t block[KIND == CODES_BY_BLOCK ? CDF_BLOCKS + 1 : 1];
+            uint64_t mark[MARKS];         // bit per position: an end marker
+            uint32_t before[MARKS];       // end markers in front of 64 positions
+        };
+        alignas(16) uint64_t entry[SPLIT ? ROUNDS * KEY_ROUND : 1];
+    };
+    uint32_t hist[KIND == TEXT_ONLY ? 1 : MAX_BINS / 2];  // two counts a word
+    uint32_t wave[T / SD_WAVE];
+    int32_t doc[3];  // [2]: a token is outside the vocabulary
+};
+
+// T threads take ROUNDS rounds of KEY_ROUND positions.  SPLIT: the first split is done on the way.  A tile's entries are ordered by
+// digit and leave as a tile of `out`, with a row that says where each digit's begin; who wants a bin takes its
+// share from every tile (24 entries in tiles of 6144 and 256 bins).  (The codes themselves written, counted by tile, the
+// counts made places, codes read again and entries moved there: 58 + 7 + 45 us at 10M, 470 + 26 + 555 at 100M.)
+template <int T, int ROUNDS, int KIND, bool SPLIT>
+__global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t *__restrict__ tokens,
                                                const int64_t *__restrict__ offs, int32_t n_seq,
                                                int64_t n_tokens, int32_t *__restrict__ text, int32_t vocab,
                                                int32_t *err, const uint32_t *__restrict__ cdf,
                                                const uint32_t *__restrict__ blocks, int block_shift,
-                                               uint32_t *__restrict__ keys, int shift, int bins,
+                                               uint32_t *__restrict__ keys, entry_shape f,
+                                               uint64_t *__restrict__ out, uint16_t *__restrict__ rows,
                                                uint32_t *__restrict__ hist, int64_t ntiles, int per_chunk,
                                                uint32_t *__restrict__ sums, uint32_t *__restrict__ lines, int bits) {
     constexpr bool CODES = KIND != TEXT_ONLY;
-    __shared__ uint32_t s_block[KIND == CODES_BY_BLOCK ? CDF_BLOCKS + 1 : 1];
-    static_assert(2 * (KEY_ROUND + CODE_LOOK) >= KEY_ROUND + LAYOUT_LOOK, "");
-    __shared__ uint2 s_code[CODES ? KEY_ROUND + CODE_LOOK : 1];  // (lower end, width) of each token's interval
-    uint32_t *s_tok = reinterpret_cast<uint32_t *>(s_code);      // before that: the tokens' codes
-    __shared__ uint32_t s_hist[CODES ? MAX_BINS / 2 : 1];        // two counts a word
-    __shared__ int32_t s_start[LDS_DOCS + 1];  // documents' starts, counted from the tile's
-    __shared__ int32_t s_doc[5];  // [4]: a token is outside the vocabulary
+    constexpr int PER = KEY_ROUND / T, TILE = ROUNDS * KEY_ROUND;
+    __shared__ layout_lds<T, ROUNDS, KIND, SPLIT> s;
     const int tid = threadIdx.x;
-    const int64_t N = n_tokens + n_seq, tile0 = (int64_t)blockIdx.x * (CT * ITEMS);
-    auto start_of = [&](int32_t j) -> int64_t { return j <= n_seq ? offs[j] + j : N + 1; };
+    const int64_t N = n_tokens + n_seq, tile0 = (int64_t)blockIdx.x * TILE;
+    const int bins = 1 << f.bits1, shift = 32 - f.bits1;
+    constexpr int MARKS = layout_lds<T, ROUNDS, KIND, SPLIT>::MARKS;
     if (KIND == CODES_BY_BLOCK)
-        for (int i = tid; i <= (vocab >> block_shift) + 1; i += CT) s_block[i] = blocks[i];
+        for (int i = tid; i <= (vocab >> block_shift) + 1; i += T) s.block[i] = blocks[i];
     if (CODES)
-        for (int i = tid; i < bins / 2; i += CT) s_hist[i] = 0;
-    if (tid < 5) s_doc[tid] = 0;
+        for (int i = tid; i < bins / 2; i += T) s.hist[i] = 0;
+    if (tid < MARKS) s.mark[tid] = 0;
+    if (tid < 3) s.doc[tid] = 0;
     __syncthreads();
-    // The tile's documents, in two rounds of loads: the starts of CT of all documents tell between which two of these the
-    // tile starts, and what lies between them and some hundred behind are all of the tile's as a rule.
-    int32_t d0 = 0, nd = 0;  // the first, and how many; LDS_DOCS of them are in LDS, and the one behind
+    // The tile's end markers, in two rounds of loads: the ends of T of all documents tell between which two of these the
+    // tile starts, and what ends behind that is the tile's or in front of it.
     if (tile0 < N) {
-        const int64_t z = tile0 + CT * ITEMS + LAYOUT_LOOK < N ? tile0 + CT * ITEMS + LAYOUT_LOOK : N;
-        const int32_t step = (n_seq + CT - 1) / CT;
-        const bool front = tid > 0 && (int64_t)tid * step < n_seq && start_of(tid * step) <= tile0;
+        const int64_t z = tile0 + TILE + LAYOUT_LOOK;
+        const int32_t step = (n_seq + T - 1) / T;
+        auto end_of = [&](int32_t j) -> int64_t { return offs[j + 1] + j; };
+        const bool front = tid > 0 && (int64_t)tid * step < n_seq && end_of(tid * step - 1) < tile0;
         const int n = (int)__popcll(__ballot(front));
-        if ((tid & 63) == 0 && n) atomicAdd(&s_doc[0], n);
+        if ((tid & 63) == 0 && n) atomicAdd(&s.doc[0], n);
         __syncthreads();
-        d0 = s_doc[0] * step;
-        int before = 0, in = 0;
-        int32_t at[2];
-        static_assert(LDS_DOCS == 2 * CT, "two to a thread");
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int i = k * CT + tid;
-            const int64_t s = start_of(d0 + i) - tile0;
-            at[k] = s < -1 ? -1 : s > (1 << 30) ? 1 << 30 : (int32_t)s;
-            before += (int)__popcll(__ballot(i > 0 && s <= 0));
-            in += (int)__popcll(__ballot(s < z - tile0));
+        for (int32_t j0 = s.doc[0] * step;; j0 += T) {
+            const int64_t e = j0 + tid < n_seq ? end_of(j0 + tid) : z;
+            const int n_front = (int)__popcll(__ballot(e < tile0));
+            if ((tid & 63) == 0 && n_front) atomicAdd(&s.doc[1], n_front);
+            if (e >= tile0 && e < z) atomicOr(reinterpret_cast<uint32_t *>(s.mark) + ((e - tile0) >> 5), 1u << ((e - tile0) & 31));
+            if (!__syncthreads_and(e < z)) break;
         }
-        if ((tid & 63) == 0) {
-            if (before) atomicAdd(&s_doc[1], before);
-            if (in) atomicAdd(&s_doc[2], in);
-        }
-        __syncthreads();
-        before = s_doc[1];
-        in = s_doc[2];
-        if (in < LDS_DOCS) {
-            d0 += before;
-            nd = in - before;
-#pragma unroll
-            for (int k = 0; k < 2; k++)
-                if (k * CT + tid >= before) s_start[k * CT + tid - before] = at[k];
-        } else {
-            if (tid < 128) {
-                const int j = wave_lower_bound([&](int i) { return offs[i] + i; }, n_seq, tid < 64 ? tile0 + 1 : z) - 1;
-                if ((tid & 63) == 0) s_doc[tid < 64 ? 0 : 3] = j < 0 ? 0 : j;
+        static_assert(MARKS <= 2 * SD_WAVE, "two words to a lane");
+        if (tid < 64) {
+            const uint32_t a = tid < MARKS ? (uint32_t)__popcll(s.mark[tid]) : 0u, b = 64 + tid < MARKS ? (uint32_t)__popcll(s.mark[64 + tid]) : 0u;
+            const uint32_t inc = wave_incl_scan(a), all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            if (tid < MARKS) s.before[tid] = inc - a;
+            if (MARKS > 64) {
+                const uint32_t more = wave_incl_scan(b);
+                if (64 + tid < MARKS) s.before[64 + tid] = all + more - b;
             }
-            __syncthreads();
-            d0 = s_doc[0];
-            nd = s_doc[3] - d0 + 1;
-            if (nd <= LDS_DOCS)
-                for (int i = tid; i <= nd; i += CT) {
-                    const int64_t s = start_of(d0 + i) - tile0;
-                    s_start[i] = s < -1 ? -1 : s > (1 << 30) ? 1 << 30 : (int32_t)s;
-                }
         }
     }
     __syncthreads();
-    // token at text position p (-1: end marker)
-    auto token_at = [&](int64_t p) -> int32_t {
-        if (p >= N) return SD_END_TOKEN;
-        int32_t lo = 0, hi = nd;  // last document that starts at or before p
-        int64_t next;
-        if (nd <= LDS_DOCS) {
-            const int32_t q = (int32_t)(p - tile0);
-            while (hi - lo > 1) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (s_start[mid] <= q) lo = mid; else hi = mid;
-            }
-            next = tile0 + s_start[lo + 1];
-        } else {
-            while (hi - lo > 1) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (start_of(d0 + mid) <= p) lo = mid; else hi = mid;
-            }
-            next = start_of(d0 + lo + 1);
-        }
-        const int64_t i = p - (d0 + lo);
-        return p == next - 1 || i < 0 || i >= n_tokens ? SD_END_TOKEN : tokens[i];
+    const int32_t skipped = (int32_t)tile0 - (s.doc[0] * ((n_seq + T - 1) / T) + s.doc[1]);  // tokens in front of the tile
+    // token at text position tile0 + q (-1: end marker); a wave's q are the lanes of a word of marks
+    auto token_at = [&](int q) -> int32_t {
+        const uint64_t m = s.mark[q >> 6];
+        const int32_t i = skipped + q - (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, s.before[q >> 6]));
+        return tile0 + q >= N || (m >> (q & 63)) & 1ull || (uint32_t)i >= (uint32_t)n_tokens ? SD_END_TOKEN : tokens[i];
     };
-    int32_t tok[5];  // of a round: every CT-th one from the thread's on, and one behind the round
+    int32_t tok[PER + 1];  // of a round: every T-th one from the thread's on, and one behind the round
     auto ask = [&](int r) {
         const int64_t base = tile0 + r * KEY_ROUND;
-        if (r >= ITEMS / 4 || base >= N + SD_TEXT_PAD) return;
+        if (r >= ROUNDS || base >= N + SD_TEXT_PAD) return;
 #pragma unroll
-        for (int k = 0; k < 4; k++) tok[k] = token_at(base + k * CT + tid);
-        tok[4] = CODES && tid < LAYOUT_LOOK ? token_at(base + KEY_ROUND + tid) : SD_END_TOKEN;
+        for (int k = 0; k < PER; k++) tok[k] = token_at(r * KEY_ROUND + k * T + tid);
+        tok[PER] = CODES && tid < LAYOUT_LOOK ? token_at((r + 1) * KEY_ROUND + tid) : SD_END_TOKEN;
     };
     // the codes that word `tid` of a line (and of every 16th line behind it) holds parts of, and their shifts
     const int word_bit = (tid & (LINE_POS - 1)) * 32, code0 = CODES ? word_bit / bits : 0;
     const int left0 = 32 - bits + (word_bit - code0 * bits), left1 = left0 - bits, right2 = bits - left1;
+    uint32_t key_of[SPLIT ? ROUNDS * PER : 1], second[SPLIT ? ROUNDS * PER : 1], rank[SPLIT ? ROUNDS * PER : 1];
     ask(0);
-    for (int r = 0; r < ITEMS / 4; r++) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
         const int64_t base = tile0 + r * KEY_ROUND;
         if (base >= N + SD_TEXT_PAD) break;
 #pragma unroll
-        for (int k = 0; k < 5; k++)
+        for (int k = 0; k <= PER; k++)
             if (tok[k] != SD_END_TOKEN && (tok[k] < 0 || tok[k] >= vocab)) {
-                s_doc[4] = 1;  // (1M tokens, every hundredth one such: 93 us, 199 with a report each)
+                s.doc[2] = 1;  // (1M tokens, every hundredth one such: 93 us, 199 with a report each)
                 tok[k] = 0;
             }
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-            if (base + k * CT + tid < N + SD_TEXT_PAD) text[base + k * CT + tid] = tok[k];
+        for (int k = 0; k < PER; k++)
+            if (base + k * T + tid < N + SD_TEXT_PAD) text[base + k * T + tid] = tok[k];
         if (!CODES) { ask(r + 1); continue; }
-        u32x2 ends[5];  // (both ends of the token's interval)
+        u32x2 ends[PER + 1];  // (both ends of the token's interval)
 #pragma unroll
-        for (int k = 0; k < 5; k++)
-            if (k < 4 || tid < CODE_LOOK) {
+        for (int k = 0; k <= PER; k++)
+            if (k < PER || tid < CODE_LOOK) {
                 const uint32_t c = (uint32_t)(tok[k] + 1);
                 bool ask_for = true;
                 if (KIND == CODES_BY_BLOCK) {
-                    const uint32_t b = c >> block_shift, i = c & ((1u << block_shift) - 1u), e = s_block[b];
-                    const uint32_t lo = e & ~1u, width = ((s_block[b + 1] & ~1u) - lo) >> CDF_QUANTUM;
-                    ends[k].x = lo + ((uint32_t)((uint64_t)width * i >> block_shift) << CDF_QUANTUM);
-                    ends[k].y = lo + ((uint32_t)((uint64_t)width * (i + 1u) >> block_shift) << CDF_QUANTUM);
+                    const uint32_t b = c >> block_shift, i = c & ((1u << block_shift) - 1u), e = s.block[b];
+                    const uint32_t lo = e & ~1u, part = even_part(((s.block[b + 1] & ~1u) - lo) >> CDF_QUANTUM, block_shift);
+                    ends[k].x = lo + ((part * i) << CDF_QUANTUM);
+                    ends[k].y = ends[k].x + (part << CDF_QUANTUM);
                     ask_for = !(e & 1u);
                 }
                 if (ask_for) ends[k] = *reinterpret_cast<const u32x2 *>(cdf + c);
             }
-        __syncthreads();  // (the round before is done with the intervals)
+        if (r > 0) __syncthreads();  // (the round before is done with what is in LDS)
 #pragma unroll
-        for (int k = 0; k < 5; k++)
-            if (k < 4 || tid < LAYOUT_LOOK) s_tok[k * CT + tid] = (uint32_t)(tok[k] + 1);
+        for (int k = 0; k <= PER; k++)
+            if (k < PER || tid < LAYOUT_LOOK) s.tok[k * T + tid] = (uint32_t)(tok[k] + 1);
+#pragma unroll
+        for (int k = 0; k <= PER; k++)
+            if (k < PER || tid < CODE_LOOK) s.code[k * T + tid] = make_uint2(ends[k].x, ends[k].y - ends[k].x);
         ask(r + 1);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int p = k * CT + tid;
-            const uint32_t *from = s_tok + (p & ~(LINE_POS - 1)) + code0;
+        for (int k = 0; k < PER; k++) {
+            const int p = k * T + tid;
+            const uint32_t *from = s.tok + (p & ~(LINE_POS - 1)) + code0;
             uint32_t v = from[0] << left0;
             v |= left1 >= 0 ? from[1] << left1 : from[1] >> -left1;
             if (left1 > 0) v |= from[2] >> right2;
             // (not wanted before text and codes are: 10M independent tokens, the first split, 54 -> 47 us)
             if (base + (p & ~(LINE_POS - 1)) < N + SD_TEXT_PAD) __builtin_nontemporal_store(v, &lines[base + p]);
         }
-        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 5; k++)
-            if (k < 4 || tid < CODE_LOOK) s_code[k * CT + tid] = make_uint2(ends[k].x, ends[k].y - ends[k].x);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int p = k * CT + tid;
+        for (int k = 0; k < PER; k++) {
+            const int p = k * T + tid;
             if (base + p >= N) break;
-            uint2 c = s_code[p];
+            uint2 c = s.code[p];
             uint64_t low = (uint64_t)c.x << 32;
             uint32_t width = c.y;
             for (int j = 1; j < CODE_LOOK && width > 3u; j++) {
-                c = s_code[p + j];
+                c = s.code[p + j];
                 low += (uint64_t)width * c.x;
                 width = (uint32_t)(((uint64_t)width * c.y) >> 32);
             }
             const uint32_t key = (uint32_t)(low >> 32);
-            keys[base + p] = key;
-            atomicAdd(&s_hist[key >> shift >> 1], (key >> shift) & 1u ? 1u << 16 : 1u);
+            if (!SPLIT || keys) keys[base + p] = key;
+            const uint32_t sh = ((key >> shift) & 1u) * 16u, was = atomicAdd(&s.hist[key >> shift >> 1], 1u << sh);
+            if (SPLIT) {
+                key_of[r * PER + k] = key;
+                second[r * PER + k] = s.tok[p + 1];
+                rank[r * PER + k] = (was >> sh) & 0xffffu;
+            }
         }
     }
     __syncthreads();
-    if (tid == 0 && s_doc[4]) atomicOr(&err[SD_DEVERR_TOKEN], 1);
+    if (tid == 0 && s.doc[2]) atomicOr(&err[SD_DEVERR_TOKEN], 1);
     if (!CODES || blockIdx.x >= ntiles) return;
-    uint32_t *row = hist + (int64_t)blockIdx.x * bins, *sum = per_chunk > 0 ? sums + (int64_t)(blockIdx.x / per_chunk) * bins : nullptr;
-    static_assert(CT * ITEMS < 1 << 16, "counts of 16 bits");
-    for (int i = tid; i < bins; i += CT) {
-        const uint32_t v = (s_hist[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-        row[i] = v;
-        if (v && sum) atomicAdd(&sum[i], v);
+    uint32_t *sum = per_chunk > 0 ? sums + (int64_t)(blockIdx.x / per_chunk) * bins : nullptr;
+    static_assert(TILE < 1 << 16, "counts of 16 bits");
+    if (!SPLIT) {
+        uint32_t *row = hist + (int64_t)blockIdx.x * bins;
+        for (int i = tid; i < bins; i += T) {
+            const uint32_t v = (s.hist[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+            row[i] = v;
+            if (v && sum) atomicAdd(&sum[i], v);
+        }
+        return;
+    }
+    static_assert(T >= MAX_BINS / 2, "a word of counts to a thread");
+    {
+        const uint32_t v = tid < bins / 2 ? s.hist[tid] : 0u, a = v & 0xffffu, b = v >> 16;
+        const uint32_t inc = wave_incl_scan(a + b);
+        if ((tid & 63) == 63) s.wave[tid >> 6] = inc;
+        __syncthreads();
+        uint32_t ex = inc - a - b;
+#pragma unroll
+        for (int i = 0; i < T / SD_WAVE; i++) ex += i < tid >> 6 ? s.wave[i] : 0u;
+        if (tid < bins / 2) {
+            const uint32_t at = ex | (ex + a) << 16;
+            s.hist[tid] = at;
+            reinterpret_cast<uint32_t *>(rows + (int64_t)blockIdx.x * bins)[tid] = at;
+            if (a) atomicAdd(&sum[2 * tid], a);
+            if (b) atomicAdd(&sum[2 * tid + 1], b);
+        }
+        __syncthreads();
+    }
+    const int cnt = (int)(N - tile0 < TILE ? N - tile0 : TILE);
+#pragma unroll
+    for (int k = 0; k < (SPLIT ? ROUNDS * PER : 0); k++) {
+        const int p = (k / PER) * KEY_ROUND + (k % PER) * T + tid;
+        const uint32_t digit = key_of[k] >> shift;
+        if (p < cnt) s.entry[((s.hist[digit >> 1] >> ((digit & 1u) * 16u)) & 0xffffu) + rank[k]] = entry_of(f, key_of[k], second[k], tile0 + p);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < (SPLIT ? ROUNDS * PER / 2 : 0); k++) {
+        const int j = 2 * (k * T + tid);
+        if (j + 1 < cnt) *reinterpret_cast<ulonglong2 *>(out + tile0 + j) = *reinterpret_cast<const ulonglong2 *>(s.entry + j);
+        else if (j < cnt) out[tile0 + j] = s.entry[j];
     }
 }
 
@@ -468,6 +507,7 @@ __global__ __launch_bounds__(CT) void k_layout(const int32_t *__restrict__ token
 // LDS brings the shares together (2.2M, 10M, 100M positions: 10.1, 13.0, 58 us with two bins to a lane and all rows
 // one after the other; 4.9, 6.8, 24 so).
 constexpr int MAX_CHUNKS = 256, MIN_PER_CHUNK = 32;
+constexpr int MAX_PER_CHUNK = 4096;  // (of 6144 positions: 2^31 positions are 1366 a chunk)
 constexpr int ROW_GROUPS = 32;  // at most
 
 struct row_share { int col, group, groups; };  // four bins of a row, 16 bytes apart; group >= groups: none
@@ -549,14 +589,6 @@ __global__ __launch_bounds__(CT) void k_code_places(uint32_t *__restrict__ hist,
 }
 
 // ---- splitting entries by a digit of the code --------------------------------------------------
-// The bits of an entry, from the lowest: position, code of the second token, code of the suffix
-// without its first bits1 bits and perhaps without a few of its last ones.
-struct entry_shape {
-    int bits1, bits2;         // of the code: split off by the first and by the second split
-    int pos_bits, tok_bits;
-    int key_bits, key_drop;   // of the code: in the entry, and left out below
-};
-
 // Orders the tile's entries by digit in LDS, then writes them out as runs of neighbouring lanes.
 // Entries of a digit leave in whatever order their LDS additions happen: nothing relies on it.
 // (ITEMS = 12: two workgroups share a compute unit.)
@@ -641,8 +673,7 @@ __global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ 
         if (j < cnt) key = FEW ? keys[base + j] : __builtin_nontemporal_load(keys + base + j);  // (once: 47 -> 44 us)
         const uint32_t tok = j < cnt ? (uint32_t)(text[base + j + 1] + 1) : 0u;
         digit[k] = key >> (32 - f.bits1);
-        const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
-        e[k] = (((rest << f.tok_bits) | tok) << f.pos_bits) | (uint64_t)(base + j);
+        e[k] = entry_of(f, key, tok, base + j);
     }
     if (FEW) {
         static_assert(!FEW || sizeof(s.entry) >= 2 * CT * sizeof(uint4), "the counts are brought together there");
@@ -679,45 +710,120 @@ constexpr int SPLIT2_ITEMS = 12, SPLIT2_TILE = CT * SPLIT2_ITEMS;
 // The row of tile number g is row g.
 __device__ __forceinline__ int first_tile(uint32_t start, int bin) { return (int)(start / SPLIT2_TILE) + bin; }
 
-struct bin_tile { int64_t at; int cnt; };  // the entries; none: no such tile
-__device__ __forceinline__ bin_tile tile_of(const uint32_t *__restrict__ starts1, int bins1, int g) {
-    __shared__ uint32_t s_first[2], s_size;
-    for (int b = threadIdx.x; b < bins1; b += CT) {
-        const bin_place p = first_bin(starts1, b);
-        const int f = first_tile(p.start, b);
-        if (f <= g && g < first_tile(p.start + p.size, b + 1)) {  // (of one bin: numbers rise)
-            s_first[0] = p.start;
-            s_first[1] = (uint32_t)(g - f);
-            s_size = p.size;
+// A tile of a bin: its place and what it takes of which bin, from the chunk of k_layout's tiles where its first entry lies.
+struct bin_tile {
+    uint32_t at, cnt;     // cnt = 0: no such tile
+    uint32_t bin;
+    uint32_t chunk_tile;  // the chunk's first
+    uint32_t skip;        // entries of the bin in the chunk in front of it
+};
+
+// A workgroup per chunk of k_layout's tiles: which tiles of the second split start among the chunk's entries.  Workgroup 0 also
+// writes where the bins start.  Bound: latency.
+__global__ __launch_bounds__(CT) void k_code_tiles(const uint32_t *__restrict__ sums, int bins, int per_chunk, int chunks,
+                                                   uint32_t *__restrict__ starts, uint32_t N, bin_tile *__restrict__ tiles, int n_tiles) {
+    __shared__ uint4 s_area[2 * CT];
+    __shared__ uint32_t s_to[MAX_BINS], s_start[MAX_BINS + 1];
+    __shared__ uint32_t s_wave[CW];
+    const int chunk = (int)blockIdx.x;
+    uint32_t own[2];
+#pragma unroll
+    for (int q = 0; q < 2; q++) own[q] = q * CT + (int)threadIdx.x < bins ? sums[(int64_t)chunk * bins + q * CT + threadIdx.x] : 0u;
+    bin_starts(sums, bins, chunks, chunk, s_area, s_wave, s_to, s_start);
+    if (threadIdx.x == 0) s_start[bins] = N;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int d = q * CT + (int)threadIdx.x;
+        if (d >= bins) continue;
+        const uint32_t start = s_start[d], size = s_start[d + 1] - start, rel = s_to[d] - start, first = (uint32_t)first_tile(start, d);
+        for (uint32_t i = (rel + SPLIT2_TILE - 1) / SPLIT2_TILE; i * SPLIT2_TILE < rel + own[q]; i++) {
+            const uint32_t skip = i * SPLIT2_TILE, left = size - skip;
+            tiles[first + i] = {start + skip, left < SPLIT2_TILE ? left : SPLIT2_TILE, (uint32_t)d, (uint32_t)(chunk * per_chunk), skip - rel};
+        }
+        if (chunk == 0) {
+            const uint32_t next = d + 1 < bins ? (uint32_t)first_tile(start + size, d + 1) : (uint32_t)n_tiles;
+            for (uint32_t g = first + (size + SPLIT2_TILE - 1) / SPLIT2_TILE; g < next; g++) tiles[g].cnt = 0;
+            starts[d] = start;
+            if (d == 0) starts[bins] = N;
         }
     }
-    __syncthreads();
-    const int64_t skip = (int64_t)s_first[1] * SPLIT2_TILE, left = (int64_t)s_size - skip;
-    return {(int64_t)s_first[0] + skip, left <= 0 ? 0 : left < SPLIT2_TILE ? (int)left : SPLIT2_TILE};
 }
 
-// rows: [tile][digit], where the digit's entries begin, counted from the tile's first.
-__global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__ in,
-                                                    const uint32_t *__restrict__ starts1, int bins1, int shift,
+// rows: [tile][digit], where the digit's entries begin, counted from the tile's first; rows1 those of k_layout's tiles of tile1.
+// Also clears the chunks' sums for the next input.
+__global__ __launch_bounds__(CT, 6) void k_code_split2(const uint64_t *__restrict__ in, const uint16_t *__restrict__ rows1, int bins1,
+                                                    int64_t N, int tile1, const bin_tile *__restrict__ tiles, int n_tiles, int per_bin, int shift,
                                                     int bins2, uint16_t *__restrict__ rows,
-                                                    uint64_t *__restrict__ out) {
+                                                    uint64_t *__restrict__ out, uint32_t *__restrict__ sums, int chunks,
+                                                    uint32_t *__restrict__ n_lasts) {
     __shared__ alignas(16) uint64_t s_entry[SPLIT2_TILE];
     __shared__ uint32_t s_cnt[MAX_BINS];
-    __shared__ uint32_t s_wave[CW];
+    __shared__ uint32_t s_wave[CW], s_front;
     static_assert(SPLIT2_TILE < 1 << 16, "places of 16 bits");
-    const int tid = threadIdx.x;
-    const int g = tile_of_block();
-    for (int i = tid; i < bins2; i += CT) s_cnt[i] = 0;
-    const bin_tile t = tile_of(starts1, bins1, g);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if ((int)blockIdx.x < chunks)  // (chunks of 32 tiles and more, six to a tile at most: there are as many workgroups)
+        for (int i = tid; i < bins1; i += CT) sums[(int64_t)blockIdx.x * bins1 + i] = 0;
+    if (blockIdx.x == 0 && tid == 0) *n_lasts = 0;  // (for k_code_ranges)
+    // (A die takes neighbouring bins, and of these the tiles of the same places together: where a run of one ends the next one's
+    // begins, in the same line.)
+    const int n = ((int)gridDim.x >> 3), x = (int)blockIdx.x & 7, k = (int)blockIdx.x >> 3, columns = n / per_bin;
+    const int g = x * n + (k % columns) * per_bin + k / columns;
+    if (g >= n_tiles) return;
+    const bin_tile t = tiles[g];
     if (t.cnt == 0) return;
+    const int cnt = (int)t.cnt;
+    for (int i = tid; i < bins2; i += CT) s_cnt[i] = 0;
+    // pieces, one of each of k_layout's tiles that has any of the bin: where it lies, less the place of its first entry, and a
+    // bit per place, a piece ends here
+    constexpr int WORDS = SPLIT2_TILE / 64;
+    uint32_t *s_from = reinterpret_cast<uint32_t *>(s_entry);
+    uint64_t *s_ends = s_entry + SPLIT2_TILE - WORDS;
+    static_assert(4 * (SPLIT2_TILE + MAX_PER_CHUNK) <= 8 * (SPLIT2_TILE - WORDS) && WORDS > 64 && WORDS <= 128, "");
+    if (tid < WORDS) s_ends[tid] = 0;
+    const int64_t ntiles = (N + tile1 - 1) / tile1;
+    const uint32_t lo = t.skip, hi = t.skip + t.cnt;
+    uint32_t seen = 0, pieces = 0;
+    for (int64_t at = t.chunk_tile; seen < hi && at < ntiles; at += CT) {
+        const int64_t i = at + tid;
+        uint32_t from = 0, len = 0, tot;
+        if (i < ntiles) {
+            const uint16_t *row = rows1 + i * bins1 + t.bin;
+            from = row[0];
+            len = ((int)t.bin + 1 < bins1 ? (uint32_t)row[1] : (uint32_t)(N - i * tile1 < tile1 ? N - i * tile1 : tile1)) - from;
+        }
+        static_assert((int64_t)CT * 6144 < 1 << 22 && CT < 1 << 10, "entries and pieces in a word");
+        const uint32_t ex = block_excl_scan(len | (len ? 1u << 22 : 0u), s_wave, &tot), first = seen + (ex & 0x3fffffu), end = first + len;
+        if (len && end > lo && first < hi) {
+            const uint32_t a = first < lo ? lo : first, last = (end < hi ? end : hi) - lo - 1u, q = pieces + (ex >> 22);
+            s_from[q] = (uint32_t)(i * tile1) + from + (a - first) - (a - lo);
+            atomicOr(reinterpret_cast<uint32_t *>(s_ends) + (last >> 5), 1u << (last & 31));
+            if (a == lo) s_front = q;
+        }
+        seen += tot & 0x3fffffu;
+        pieces += tot >> 22;
+    }
+    __syncthreads();
     uint64_t e[SPLIT2_ITEMS];
     uint32_t rank[SPLIT2_ITEMS];
+    {
+        const uint64_t ends[2] = {s_ends[lane], lane < WORDS - 64 ? s_ends[64 + lane] : 0ull};
+        uint32_t before[2];  // pieces that end in front of the lane's 64 places
+        before[0] = wave_incl_scan((uint32_t)__popcll(ends[0]));
+        before[1] = wave_incl_scan((uint32_t)__popcll(ends[1])) + (uint32_t)__builtin_amdgcn_readlane((int)before[0], 63) - (uint32_t)__popcll(ends[1]) + s_front;
+        before[0] += s_front - (uint32_t)__popcll(ends[0]);
+#pragma unroll
+        for (int k = 0; k < SPLIT2_ITEMS; k++) {
+            const int j = k * CT + tid, h = k * CW / 64, q = k * CW + w - 64 * h;
+            const uint32_t m0 = __builtin_amdgcn_readlane((int)(uint32_t)ends[h], q), m1 = __builtin_amdgcn_readlane((int)(uint32_t)(ends[h] >> 32), q);
+            const uint32_t piece = __builtin_amdgcn_mbcnt_hi(m1, __builtin_amdgcn_mbcnt_lo(m0, (uint32_t)__builtin_amdgcn_readlane((int)before[h], q)));
+            e[k] = j < cnt ? in[s_from[piece] + (uint32_t)j] : 0ull;
+        }
+    }
     auto digit = [&](uint64_t v) { return (uint32_t)(v >> shift) & ((uint32_t)bins2 - 1u); };
 #pragma unroll
-    for (int k = 0; k < SPLIT2_ITEMS; k++) e[k] = k * CT + tid < t.cnt ? in[t.at + k * CT + tid] : 0ull;
-#pragma unroll
     for (int k = 0; k < SPLIT2_ITEMS; k++)
-        if (k * CT + tid < t.cnt) rank[k] = atomicAdd(&s_cnt[digit(e[k])], 1u);
+        if (k * CT + tid < cnt) rank[k] = atomicAdd(&s_cnt[digit(e[k])], 1u);
     __syncthreads();
     const int d = 2 * tid;  // MAX_BINS / CT digits per thread
     const uint32_t a = d < bins2 ? s_cnt[d] : 0u, b = d < bins2 ? s_cnt[d + 1] : 0u;
@@ -731,11 +837,12 @@ __global__ __launch_bounds__(CT) void k_code_split2(const uint64_t *__restrict__
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < SPLIT2_ITEMS; k++)
-        if (k * CT + tid < t.cnt) s_entry[s_cnt[digit(e[k])] + rank[k]] = e[k];
+        if (k * CT + tid < cnt) s_entry[s_cnt[digit(e[k])] + rank[k]] = e[k];
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < SPLIT2_ITEMS; k++)
-        if (k * CT + tid < t.cnt) out[t.at + k * CT + tid] = s_entry[k * CT + tid];
+        // (not wanted before the lines that neighbours share are: 36.4 -> 33.2 and 516 -> 499 us)
+        if (k * CT + tid < cnt) __builtin_nontemporal_store(s_entry[k * CT + tid], out + (int64_t)t.at + k * CT + tid);
 }
 
 // One workgroup per bin of the first split: where its buckets start, in the order in which k_code_sort leaves the
@@ -1782,7 +1889,10 @@ int sort_tile_for(int64_t N, int n_cu) {
     if (t < 2 * average) t = 2 * average;
     return (int)(t < SORT_TILE_FEW ? SORT_TILE_FEW : t > most ? most : t);
 }
-constexpr int SMALL_ITEMS = 4, LARGE_ITEMS = 12;
+constexpr int SMALL_ITEMS = 4;
+constexpr int SMALL_ROUNDS = 1, LARGE_ROUNDS = 3, LARGE_THREADS = 512;
+static_assert(((1ll << 31) / (LARGE_ROUNDS * KEY_ROUND) + MAX_CHUNKS - 1) / MAX_CHUNKS <= MAX_PER_CHUNK, "");
+int64_t layout_tile(const split_plan &p) { return (int64_t)KEY_ROUND * (p.small_tiles ? SMALL_ROUNDS : LARGE_ROUNDS); }
 
 }  // namespace
 
@@ -1795,9 +1905,12 @@ void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_
     for (int64_t n : sizes) {
         if (n > cap) n = cap;
         const split_plan p = plan_for(n);
-        const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
-        int64_t x = ((n + tile - 1) / tile) << p.bits1;
-        if (p.bits2) x += (((n / SPLIT2_TILE + (1ll << p.bits1)) << p.bits2) / 2) + (1ll << p.bits1) + 16;
+        const int64_t tile = layout_tile(p), ntiles = (n + tile - 1) / tile;
+        int64_t x = ntiles << p.bits1;
+        if (p.bits2) {
+            const int64_t tiles = n / SPLIT2_TILE + (1ll << p.bits1);
+            x = x / 2 + (tiles << p.bits2) / 2 + (1ll << p.bits1) + tiles * (int64_t)(sizeof(bin_tile) / 4) + 64;
+        }
         h = x > h ? x : h;
         const int64_t y = (1ll << (p.bits1 + p.bits2)) + 1;
         s = y > s ? y : s;
@@ -1872,15 +1985,16 @@ static constexpr bool lines_hold() {
 static_assert(lines_hold(), "");
 static uint32_t *line_room(const sd_ctx *c) { return c->b_vals[1]; }
 
-static dim3 layout_grid(int64_t N, int items) { return dim3((unsigned)((N + SD_TEXT_PAD + CT * items - 1) / (CT * items))); }
+static dim3 layout_grid(int64_t N, int64_t tile) { return dim3((unsigned)((N + SD_TEXT_PAD + tile - 1) / tile)); }
 
 void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                int32_t *text, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
-    const bool small = plan_for(N).small_tiles;
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (small ? k_layout<SMALL_ITEMS, TEXT_ONLY> : k_layout<LARGE_ITEMS, TEXT_ONLY>),
-              layout_grid(N, small ? SMALL_ITEMS : LARGE_ITEMS), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
-              c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (const uint32_t *)nullptr, 0, (uint32_t *)nullptr, 0, 0, (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr, (uint32_t *)nullptr, 0);
+    const split_plan p = plan_for(N);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (p.small_tiles ? k_layout<CT, SMALL_ROUNDS, TEXT_ONLY, false> : k_layout<CT, LARGE_ROUNDS, TEXT_ONLY, false>),
+              layout_grid(N, layout_tile(p)), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
+              c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (const uint32_t *)nullptr, 0, (uint32_t *)nullptr, entry_shape{}, (uint64_t *)nullptr, (uint16_t *)nullptr,
+              (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr, (uint32_t *)nullptr, 0);
 }
 
 // An entry's 64 bits: whether they hold what is needed of an input.
@@ -1901,11 +2015,25 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
-// Tables of a split in two, in b_hist: where the bins of the first split start, the rows of the second one's tiles.
-static int64_t starts1_words(entry_shape f) { return ((1ll << f.bits1) + 1 + 3) / 4 * 4; }
-static int64_t rows2_words(int64_t N, entry_shape f) { return (((N / SPLIT2_TILE + (1ll << f.bits1)) << f.bits2) / 2 + 3) / 4 * 4; }
-static uint32_t *starts1_room(const sd_ctx *c) { return c->b_hist; }
-static uint16_t *rows2_room(const sd_ctx *c, entry_shape f) { return reinterpret_cast<uint16_t *>(c->b_hist + starts1_words(f)); }
+// Tables of a split in two, in b_hist.
+struct split_tables {
+    uint32_t *starts1;  // where the bins of the first split start
+    uint16_t *rows1;    // of k_layout's tiles
+    uint16_t *rows2;    // of the second split's
+    bin_tile *tiles;    // these
+    int n_tiles;
+};
+static split_tables split_tables_for(const sd_ctx *c, int64_t N, const entry_shape &f) {
+    auto up = [](int64_t words) { return (words + 3) / 4 * 4; };
+    split_tables t;
+    const int64_t tile = layout_tile(plan_for(N)), bins = 1ll << f.bits1;
+    t.n_tiles = (int)(N / SPLIT2_TILE + bins);
+    t.starts1 = c->b_hist;
+    t.rows1 = reinterpret_cast<uint16_t *>(t.starts1 + up(bins + 1));
+    t.rows2 = t.rows1 + 2 * up((N + tile - 1) / tile * bins / 2);
+    t.tiles = reinterpret_cast<bin_tile *>(t.rows2 + 2 * up(((int64_t)t.n_tiles << f.bits2) / 2));
+    return t;
+}
 
 // The tables of ranges, in b_ranges.
 struct sort_tables {
@@ -1934,15 +2062,28 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
 
 // The tiles and the first of the last buckets that are kept apart (workgroups for a quarter as many as there are tiles:
 // one that finds nothing is over at once; builds of 3M to 40M tokens by no more than runs differ), or n last buckets behind those.
-static void sort_ranges(sd_ctx *c, const uint64_t *entries, const sort_tables &t, int n, entry_shape f,
+static void sort_ranges(sd_ctx *c, const uint64_t *entries, int64_t N, const sort_tables &t, int n, entry_shape f,
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
     const packed_text packed = {line_room(c), bits, 128 * R / bits};
-    const split_rows split = {starts1_room(c), f.bits2 ? rows2_room(c, f) : nullptr};
+    const split_tables two = split_tables_for(c, N, f);
+    const split_rows split = {two.starts1, f.bits2 ? two.rows2 : nullptr};
     SD_LAUNCH(c, SD_K_CODE_SORT, st, (R == 3 ? k_code_sort<3> : R == 2 ? k_code_sort<2> : k_code_sort<1>),
               dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries,
               split, t.pieces, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
               n ? t.taken : 0, f, packed, c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
+}
+
+// k_layout with codes: split into `entries` and rows1, or codes and counts.
+static void layout_codes(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens, int32_t *text, entry_shape f,
+                         uint32_t *keys, uint64_t *entries, uint16_t *rows1, uint32_t *hist, int64_t ntiles, int per_chunk, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq;
+    const split_plan p = plan_for(N);
+    const bool by_block = sd_code_blocks(c->cfg.vocab) <= CDF_BLOCKS + 1;
+    SD_LAUNCH(c, SD_K_SORT_HIST, st, (!p.bits2 ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT, false> : p.small_tiles ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT, true> :
+                                      by_block ? k_layout<LARGE_THREADS, LARGE_ROUNDS, CODES_BY_BLOCK, true> : k_layout<LARGE_THREADS, LARGE_ROUNDS, CODES_DIRECT, true>),
+              layout_grid(N, layout_tile(p)), dim3(p.small_tiles ? CT : LARGE_THREADS), 0, tokens, offs, n_seq, n_tokens, text, c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks,
+              block_shift(c->cfg.vocab), keys, f, entries, rows1, hist, ntiles, per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab));
 }
 
 // Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
@@ -1956,45 +2097,44 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     entry_shape f;
     (void)shape_for(N, c->cfg.vocab, &f);
     const int bins1 = 1 << f.bits1, bins2 = 1 << f.bits2;
-    const int64_t tile = (int64_t)CT * (p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS);
-    const int64_t ntiles = (N + tile - 1) / tile;
-    uint32_t *keys = c->b_flags;
+    const int64_t tile = layout_tile(p), ntiles = (N + tile - 1) / tile;
     uint64_t *ent1 = c->b_keys[0], *ent2 = c->b_keys[1];
-    uint32_t *hist = c->b_hist, *starts1 = f.bits2 ? starts1_room(c) : c->b_starts;
-    uint16_t *rows2 = rows2_room(c, f);
-    hist = c->b_hist + (f.bits2 ? starts1_words(f) + rows2_words(N, f) : 0);
     int per_chunk = (int)((ntiles + MAX_CHUNKS - 1) / MAX_CHUNKS);
     if (per_chunk < MIN_PER_CHUNK) per_chunk = MIN_PER_CHUNK;
     const int chunks = (int)((ntiles + per_chunk - 1) / per_chunk);
-    const bool few = p.small_tiles && p.bits2 == 0 && chunks == 1;
-    const dim3 grid1((unsigned)ntiles), block(CT);
-    const bool by_block = sd_code_blocks(c->cfg.vocab) <= CDF_BLOCKS + 1;
-    SD_LAUNCH(c, SD_K_SORT_HIST, st, (p.small_tiles ? k_layout<SMALL_ITEMS, CODES_DIRECT> : by_block ? k_layout<LARGE_ITEMS, CODES_BY_BLOCK> : k_layout<LARGE_ITEMS, CODES_DIRECT>),
-              layout_grid(N, p.small_tiles ? SMALL_ITEMS : LARGE_ITEMS), block, 0, tokens, offs, n_seq, n_tokens, text,
-              c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks, block_shift(c->cfg.vocab), keys, 32 - f.bits1, bins1, hist, ntiles, few ? 0 : per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab));
-    if (!few)
-        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
-              c->code_sums, chunks, starts1, (uint32_t)N);
+    const dim3 block(CT);
     const sort_tables t = tables_for(c, N);
-    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (few ? k_code_split<SMALL_ITEMS, true> : p.small_tiles ? k_code_split<SMALL_ITEMS, false> : k_code_split<LARGE_ITEMS, false>),
-              grid1, block, 0, keys, text, N, f, hist, chunks, c->code_sums, starts1, ent1, t.n_lasts);
+    const split_tables two = split_tables_for(c, N, f);
     if (p.bits2) {
-        const dim3 grid2((unsigned)(N / SPLIT2_TILE + bins1));
+        layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, nullptr, ent1, two.rows1, nullptr, ntiles, per_chunk, st);
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_tiles, dim3(chunks), block, 0, c->code_sums, bins1, per_chunk, chunks, two.starts1, (uint32_t)N, two.tiles, two.n_tiles);
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
-        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, grid2, block, 0, ent1, starts1, bins1, shift, bins2, rows2, ent2);
-        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_starts2, dim3(bins1), block, 0, starts1, bins2, rows2, c->b_starts, (uint32_t)N);
+        const int per_bin = (two.n_tiles + bins1 - 1) / bins1, columns = (two.n_tiles + 8 * per_bin - 1) / (8 * per_bin);
+        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, dim3((unsigned)(8 * columns * per_bin)), block, 0, ent1, two.rows1, bins1, N, (int)tile, two.tiles, two.n_tiles, per_bin, shift, bins2, two.rows2, ent2,
+                  c->code_sums, chunks, t.n_lasts);
+        SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_starts2, dim3(bins1), block, 0, two.starts1, bins2, two.rows2, c->b_starts, (uint32_t)N);
         ent1 = ent2;
+    } else {
+        uint32_t *keys = c->b_flags, *hist = c->b_hist;
+        const bool few = chunks == 1;
+        layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, keys, nullptr, nullptr, hist, ntiles, few ? 0 : per_chunk, st);
+        if (!few)
+            SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
+                      c->code_sums, chunks, c->b_starts, (uint32_t)N);
+        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (few ? k_code_split<SMALL_ITEMS, true> : k_code_split<SMALL_ITEMS, false>),
+                  dim3((unsigned)ntiles), block, 0, keys, text, N, f, hist, chunks, c->code_sums, c->b_starts, ent1, t.n_lasts);
     }
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
               c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, t.lasts, t.n_lasts, t.taken, c->h_flag,
-              split_rows{starts1_room(c), f.bits2 ? rows2_room(c, f) : nullptr}, f.bits2, t.pieces);
+              split_rows{two.starts1, f.bits2 ? two.rows2 : nullptr}, f.bits2, t.pieces);
     const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
-    sort_ranges(c, ent1, t, 0, f, sa, tok1, bucket, st);
+    sort_ranges(c, ent1, N, t, 0, f, sa, tok1, bucket, st);
     return asked;
 }
 
 // The ranges that sd_code_sort's workgroups have not taken; waits for the stream.
-sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
+sd_status sd_code_rest(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq;
     entry_shape f;
     (void)shape_for(N, c->cfg.vocab, &f);
     const sort_tables t = tables_for(c, N);
@@ -2005,11 +2145,12 @@ sd_status sd_code_rest(sd_ctx *c, int64_t N, int32_t *text, int32_t *sa, int32_t
     const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
     const int more = (int)told[REST_LASTS] - t.taken, n = (int)told[REST_LONG];
     const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
-    if (more > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], t, more, f, sa, tok1, bucket, st);
+    if (more > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], N, t, more, f, sa, tok1, bucket, st);
     if (n == 0) return SD_OK;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
     uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;
     const int64_t tiles = (N + REST_TILE - 1) / REST_TILE;
+    if (f.bits2) layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, codes, nullptr, nullptr, nullptr, 0, 0, st);  // (a split in two keeps no codes by position)
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_table, grid((int64_t)1 << bits, CT), block, 0, t.rest, n, 1 << bits, table);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_count, dim3((unsigned)tiles), block, 0, codes, N, down, table, to);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_scan, dim3(1), block, 0, to, tiles);
