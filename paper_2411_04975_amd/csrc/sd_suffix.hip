@@ -276,17 +276,23 @@ enum { TEXT_ONLY = 0, CODES_DIRECT, CODES_BY_BLOCK };
 // The bits of an entry, from the lowest: position, code of the second token, code of the suffix
 // without its first bits1 bits and perhaps without a few of its last ones.
 struct entry_shape {
-    int bits1, bits2;         // of the code: split off by the first and by the second split
+    int bits1, bits2;         // of the code: split off by k_layout and by the second split; bits1 = 0: by k_layout, there is no other
     int pos_bits, tok_bits;
     int key_bits, key_drop;   // of the code: in the entry, and left out below
+    __host__ __device__ bool one_split() const { return bits1 == 0; }
+    __host__ __device__ int lead() const { return bits1 ? bits1 : bits2; }  // what k_layout splits off
 };
-__device__ __forceinline__ uint64_t entry_of(const entry_shape &f, uint32_t key, uint32_t second, int64_t pos) {
+// Where there is one split only, k_layout's entries have the position in the tile alone, so that all of the code has room.
+constexpr int TILE_POS_BITS = 11;
+static_assert(KEY_ROUND == 1 << TILE_POS_BITS && 64 - TILE_POS_BITS - SD_CODE_BITS_MAX >= 32 - 5, "");
+__device__ __forceinline__ uint64_t entry_of(const entry_shape &f, uint32_t key, uint32_t second, int64_t tile0, int p) {
     const uint64_t rest = (key & (0xffffffffu >> f.bits1)) >> f.key_drop;
-    return (((rest << f.tok_bits) | second) << f.pos_bits) | (uint64_t)pos;
+    if (f.one_split()) return (((rest << f.tok_bits) | second) << TILE_POS_BITS) | (uint32_t)p;
+    return (((rest << f.tok_bits) | second) << f.pos_bits) | (uint64_t)(tile0 + p);
 }
 
 // What k_layout has in LDS round by round, and then, entries that it splits.
-template <int T, int ROUNDS, int KIND, bool SPLIT>
+template <int T, int ROUNDS, int KIND>
 struct layout_lds {
     static constexpr int MARKS = (ROUNDS * KEY_ROUND + LAYOUT_LOOK + 63) / 64;
     union {
@@ -297,18 +303,18 @@ struct layout_lds {
             uint64_t mark[MARKS];         // bit per position: an end marker
             uint32_t before[MARKS];       // end markers in front of 64 positions
         };
-        alignas(16) uint64_t entry[SPLIT ? ROUNDS * KEY_ROUND : 1];
+        alignas(16) uint64_t entry[KIND == TEXT_ONLY ? 1 : ROUNDS * KEY_ROUND];
     };
     uint32_t hist[KIND == TEXT_ONLY ? 1 : MAX_BINS / 2];  // two counts a word
     uint32_t wave[T / SD_WAVE];
     int32_t doc[3];  // [2]: a token is outside the vocabulary
 };
 
-// T threads take ROUNDS rounds of KEY_ROUND positions.  SPLIT: the first split is done on the way.  A tile's entries are ordered by
+// T threads take ROUNDS rounds of KEY_ROUND positions.  Entries are split on the way: a tile's entries are ordered by
 // digit and leave as a tile of `out`, with a row that says where each digit's begin; who wants a bin takes its
 // share from every tile (24 entries in tiles of 6144 and 256 bins).  (The codes themselves written, counted by tile, the
 // counts made places, codes read again and entries moved there: 58 + 7 + 45 us at 10M, 470 + 26 + 555 at 100M.)
-template <int T, int ROUNDS, int KIND, bool SPLIT>
+template <int T, int ROUNDS, int KIND>
 __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t *__restrict__ tokens,
                                                const int64_t *__restrict__ offs, int32_t n_seq,
                                                int64_t n_tokens, int32_t *__restrict__ text, int32_t vocab,
@@ -316,15 +322,15 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
                                                const uint32_t *__restrict__ blocks, int block_shift,
                                                uint32_t *__restrict__ keys, entry_shape f,
                                                uint64_t *__restrict__ out, uint16_t *__restrict__ rows,
-                                               uint32_t *__restrict__ hist, int64_t ntiles, int per_chunk,
-                                               uint32_t *__restrict__ sums, uint32_t *__restrict__ lines, int bits) {
+                                               int64_t ntiles, int per_chunk, uint32_t *__restrict__ sums,
+                                               uint32_t *__restrict__ lines, int bits, uint32_t *__restrict__ n_lasts) {
     constexpr bool CODES = KIND != TEXT_ONLY;
     constexpr int PER = KEY_ROUND / T, TILE = ROUNDS * KEY_ROUND;
-    __shared__ layout_lds<T, ROUNDS, KIND, SPLIT> s;
+    __shared__ layout_lds<T, ROUNDS, KIND> s;
     const int tid = threadIdx.x;
     const int64_t N = n_tokens + n_seq, tile0 = (int64_t)blockIdx.x * TILE;
-    const int bins = 1 << f.bits1, shift = 32 - f.bits1;
-    constexpr int MARKS = layout_lds<T, ROUNDS, KIND, SPLIT>::MARKS;
+    const int bins = 1 << f.lead(), shift = 32 - f.lead();
+    constexpr int MARKS = layout_lds<T, ROUNDS, KIND>::MARKS;
     if (KIND == CODES_BY_BLOCK)
         for (int i = tid; i <= (vocab >> block_shift) + 1; i += T) s.block[i] = blocks[i];
     if (CODES)
@@ -379,7 +385,8 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
     // the codes that word `tid` of a line (and of every 16th line behind it) holds parts of, and their shifts
     const int word_bit = (tid & (LINE_POS - 1)) * 32, code0 = CODES ? word_bit / bits : 0;
     const int left0 = 32 - bits + (word_bit - code0 * bits), left1 = left0 - bits, right2 = bits - left1;
-    uint32_t key_of[SPLIT ? ROUNDS * PER : 1], second[SPLIT ? ROUNDS * PER : 1], rank[SPLIT ? ROUNDS * PER : 1];
+    constexpr int ITEMS = CODES ? ROUNDS * PER : 0;
+    uint32_t key_of[ITEMS + 1], second[ITEMS + 1], rank[ITEMS + 1];
     ask(0);
 #pragma unroll
     for (int r = 0; r < ROUNDS; r++) {
@@ -442,29 +449,19 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
                 width = (uint32_t)(((uint64_t)width * c.y) >> 32);
             }
             const uint32_t key = (uint32_t)(low >> 32);
-            if (!SPLIT || keys) keys[base + p] = key;
+            if (keys) keys[base + p] = key;
             const uint32_t sh = ((key >> shift) & 1u) * 16u, was = atomicAdd(&s.hist[key >> shift >> 1], 1u << sh);
-            if (SPLIT) {
-                key_of[r * PER + k] = key;
-                second[r * PER + k] = s.tok[p + 1];
-                rank[r * PER + k] = (was >> sh) & 0xffffu;
-            }
+            key_of[r * PER + k] = key;
+            second[r * PER + k] = s.tok[p + 1];
+            rank[r * PER + k] = (was >> sh) & 0xffffu;
         }
     }
     __syncthreads();
     if (tid == 0 && s.doc[2]) atomicOr(&err[SD_DEVERR_TOKEN], 1);
     if (!CODES || blockIdx.x >= ntiles) return;
-    uint32_t *sum = per_chunk > 0 ? sums + (int64_t)(blockIdx.x / per_chunk) * bins : nullptr;
+    if (blockIdx.x == 0 && tid == 0) *n_lasts = 0;  // (for k_code_ranges)
+    uint32_t *sum = sums + (int64_t)(per_chunk > 0 ? blockIdx.x / per_chunk : 0) * bins;
     static_assert(TILE < 1 << 16, "counts of 16 bits");
-    if (!SPLIT) {
-        uint32_t *row = hist + (int64_t)blockIdx.x * bins;
-        for (int i = tid; i < bins; i += T) {
-            const uint32_t v = (s.hist[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-            row[i] = v;
-            if (v && sum) atomicAdd(&sum[i], v);
-        }
-        return;
-    }
     static_assert(T >= MAX_BINS / 2, "a word of counts to a thread");
     {
         const uint32_t v = tid < bins / 2 ? s.hist[tid] : 0u, a = v & 0xffffu, b = v >> 16;
@@ -478,34 +475,28 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
             const uint32_t at = ex | (ex + a) << 16;
             s.hist[tid] = at;
             reinterpret_cast<uint32_t *>(rows + (int64_t)blockIdx.x * bins)[tid] = at;
-            if (a) atomicAdd(&sum[2 * tid], a);
-            if (b) atomicAdd(&sum[2 * tid + 1], b);
+            if (a && per_chunk > 0) atomicAdd(&sum[2 * tid], a);
+            if (b && per_chunk > 0) atomicAdd(&sum[2 * tid + 1], b);
         }
         __syncthreads();
     }
     const int cnt = (int)(N - tile0 < TILE ? N - tile0 : TILE);
 #pragma unroll
-    for (int k = 0; k < (SPLIT ? ROUNDS * PER : 0); k++) {
+    for (int k = 0; k < ITEMS; k++) {
         const int p = (k / PER) * KEY_ROUND + (k % PER) * T + tid;
         const uint32_t digit = key_of[k] >> shift;
-        if (p < cnt) s.entry[((s.hist[digit >> 1] >> ((digit & 1u) * 16u)) & 0xffffu) + rank[k]] = entry_of(f, key_of[k], second[k], tile0 + p);
+        if (p < cnt) s.entry[((s.hist[digit >> 1] >> ((digit & 1u) * 16u)) & 0xffffu) + rank[k]] = entry_of(f, key_of[k], second[k], tile0, p);
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < (SPLIT ? ROUNDS * PER / 2 : 0); k++) {
+    for (int k = 0; k < ITEMS / 2; k++) {
         const int j = 2 * (k * T + tid);
         if (j + 1 < cnt) *reinterpret_cast<ulonglong2 *>(out + tile0 + j) = *reinterpret_cast<const ulonglong2 *>(s.entry + j);
         else if (j < cnt) out[tile0 + j] = s.entry[j];
     }
 }
 
-// Places instead of counts in the (tile, bin) table.  A workgroup takes a chunk of tiles: what lies before
-// the chunk is known from the chunks' sums.  Workgroup 0 also writes where the bins start.  (The table
-// lies tile by tile: with a row per bin the tiles' stores and loads were 4 bytes to a line, a quarter of the
-// time of the 100M-entry split.)
-// Bound: latency.  A lane takes four bins of every R-th row of the sums, then of its share of the chunk's rows, and
-// LDS brings the shares together (2.2M, 10M, 100M positions: 10.1, 13.0, 58 us with two bins to a lane and all rows
-// one after the other; 4.9, 6.8, 24 so).
+// Chunks of tiles, whose entries by bin k_layout adds up.
 constexpr int MAX_CHUNKS = 256, MIN_PER_CHUNK = 32;
 constexpr int MAX_PER_CHUNK = 4096;  // (of 6144 positions: 2^31 positions are 1366 a chunk)
 constexpr int ROW_GROUPS = 32;  // at most
@@ -557,138 +548,7 @@ __device__ __forceinline__ void bin_starts(const uint32_t *__restrict__ table, i
     }
 }
 
-__global__ __launch_bounds__(CT) void k_code_places(uint32_t *__restrict__ hist, int bins, int64_t ntiles,
-                                                    int per_chunk, const uint32_t *__restrict__ sums,
-                                                    int chunks, uint32_t *__restrict__ starts, uint32_t N) {
-    __shared__ uint4 s_area[2 * CT];
-    __shared__ uint4 s_to[MAX_BINS / 4];
-    __shared__ uint32_t s_wave[CW];
-    const int64_t t0 = (int64_t)blockIdx.x * per_chunk;
-    const int n = (int)(ntiles - t0 < per_chunk ? ntiles - t0 : per_chunk);
-    const row_share r = share_of_rows(bins);
-    const int per = (n + r.groups - 1) / r.groups, i0 = r.group * per, i1 = r.group < r.groups ? (i0 + per < n ? i0 + per : n) : i0;
-    uint4 sum = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll 8
-    for (int i = i0; i < i1; i++) sum = sum + row_of(hist, bins, t0 + i)[r.col];
-    bin_starts(sums, bins, chunks, (int)blockIdx.x, s_area, s_wave, reinterpret_cast<uint32_t *>(s_to), blockIdx.x == 0 ? starts : nullptr);
-    __syncthreads();
-    s_area[threadIdx.x] = sum;
-    __syncthreads();
-    if (r.group < r.groups) {
-        uint4 at = s_to[r.col];
-        for (int g = 0; g < r.group; g++) at = at + s_area[g * (bins >> 2) + r.col];
-        uint4 *row = reinterpret_cast<uint4 *>(hist + t0 * bins) + r.col;
-#pragma unroll 8
-        for (int i = i0; i < i1; i++) {
-            const uint4 v = row[(int64_t)i * (bins >> 2)];
-            row[(int64_t)i * (bins >> 2)] = at;
-            at = at + v;
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) starts[bins] = N;
-}
-
-// ---- splitting entries by a digit of the code --------------------------------------------------
-// Orders the tile's entries by digit in LDS, then writes them out as runs of neighbouring lanes.
-// Entries of a digit leave in whatever order their LDS additions happen: nothing relies on it.
-// (ITEMS = 12: two workgroups share a compute unit.)
-template <int ITEMS>
-struct split_lds {
-    alignas(16) uint64_t entry[CT * ITEMS];
-    uint16_t digit[CT * ITEMS];
-    uint32_t cnt[MAX_BINS], to[MAX_BINS];
-    uint32_t wave[CW];
-};
-
-// Which tile a workgroup takes.  Workgroups go to the eight compute dies in turn, and neighbouring tiles write
-// neighbouring entries of a bin: where they do so through different L2s, every line at the end of a run is written in
-// parts by two dies (runs of 12 entries, as 100M entries have, are hardly anything else).  So a die takes neighbouring tiles.
-// 100M entries, first and second split, and the count between them: 667, 529 and 211 us with the tile of the workgroup's
-// number; 555, 335 and 169 so.  10M, the splits: 49.7 and 34.4; 46.5 and 33.4.
-__device__ __forceinline__ int tile_of_block() {
-    const int n = (int)gridDim.x, b = (int)blockIdx.x, x = b & 7, q = n >> 3, r = n & 7;
-    return x * q + (x < r ? x : r) + (b >> 3);
-}
-
-// `to` holds where the tile's first entry of each digit goes
-template <int ITEMS>
-__device__ __forceinline__ void split_tile(split_lds<ITEMS> &s, const uint64_t (&e)[ITEMS],
-                                           const uint32_t (&digit)[ITEMS], int cnt, int bins,
-                                           uint64_t *__restrict__ out) {
-    const int tid = threadIdx.x;
-    for (int i = tid; i < bins; i += CT) s.cnt[i] = 0;
-    __syncthreads();
-    uint32_t rank[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; k++)
-        if (k * CT + tid < cnt) rank[k] = atomicAdd(&s.cnt[digit[k]], 1u);
-    __syncthreads();
-    {
-        const int d = 2 * tid;  // MAX_BINS / CT digits per thread
-        const uint32_t a = d < bins ? s.cnt[d] : 0u, b = d + 1 < bins ? s.cnt[d + 1] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan(a + b, s.wave, &tot);
-        if (d < bins) { s.cnt[d] = ex; s.to[d] -= ex; }
-        if (d + 1 < bins) { s.cnt[d + 1] = ex + a; s.to[d + 1] -= ex + a; }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < ITEMS; k++)
-        if (k * CT + tid < cnt) {
-            const uint32_t at = s.cnt[digit[k]] + rank[k];
-            s.entry[at] = e[k];
-            s.digit[at] = (uint16_t)digit[k];
-        }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < ITEMS; k++) {
-        const int j = k * CT + tid;
-        if (j < cnt) out[s.to[s.digit[j]] + (uint32_t)j] = s.entry[j];
-    }
-}
-
-// First split: codes in position order -> entries.  Clears the chunks' sums for the next input.
-// FEW: a workgroup finds the places of its bins' entries by itself, from the counts of all tiles (that is as
-// much as k_code_places reads for a chunk, and one launch less: 16 tiles, 512 bins: 5.5 + 5.3 us -> 7.2).
-template <int ITEMS, bool FEW>
-__global__ __launch_bounds__(CT) void k_code_split(const uint32_t *__restrict__ keys,
-                                                   const int32_t *__restrict__ text, int64_t N, entry_shape f,
-                                                   const uint32_t *__restrict__ hist, int chunks,
-                                                   uint32_t *__restrict__ sums, uint32_t *__restrict__ starts,
-                                                   uint64_t *__restrict__ out, uint32_t *__restrict__ n_lasts) {
-    __shared__ split_lds<ITEMS> s;
-    const int tid = threadIdx.x, bins = 1 << f.bits1;
-    if (blockIdx.x == 0 && tid == 0) *n_lasts = 0;  // (for k_code_ranges)
-    // (FEW: what was laid out is still in the L2 of the die that did so, the workgroup of the same number.  50k entries: 9.0 us
-    // by tile_of_block, 7.5 so; 10k 5.3 either way; 500k 7.2 by tile_of_block and 8.8 so.)
-    const int tile = FEW ? (int)blockIdx.x : tile_of_block();
-    const int64_t base = (int64_t)tile * (CT * ITEMS);
-    const int cnt = (int)(N - base < CT * ITEMS ? N - base : CT * ITEMS);
-    uint64_t e[ITEMS];
-    uint32_t digit[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; k++) {
-        const int j = k * CT + tid;
-        uint32_t key = 0;
-        if (j < cnt) key = FEW ? keys[base + j] : __builtin_nontemporal_load(keys + base + j);  // (once: 47 -> 44 us)
-        const uint32_t tok = j < cnt ? (uint32_t)(text[base + j + 1] + 1) : 0u;
-        digit[k] = key >> (32 - f.bits1);
-        e[k] = entry_of(f, key, tok, base + j);
-    }
-    if (FEW) {
-        static_assert(!FEW || sizeof(s.entry) >= 2 * CT * sizeof(uint4), "the counts are brought together there");
-        bin_starts(hist, bins, (int)gridDim.x, tile, reinterpret_cast<uint4 *>(s.entry), s.wave, s.to,
-                   tile == 0 ? starts : nullptr);
-        if (tile == 0 && tid == 0) starts[bins] = (uint32_t)N;
-    } else {
-        for (int i = tid; i < bins; i += CT) {
-            s.to[i] = hist[(int64_t)tile * bins + i];
-            if ((int)blockIdx.x < chunks) sums[(int64_t)blockIdx.x * bins + i] = 0;
-        }
-    }
-    split_tile<ITEMS>(s, e, digit, cnt, bins, out);
-}
-
+// ---- the second split ---------------------------------------------------------------------------
 // A bin of the first split: where it starts and how long it is.
 struct bin_place { uint32_t start, size; };
 __device__ __forceinline__ bin_place first_bin(const uint32_t *__restrict__ starts1, int bin) {
@@ -752,11 +612,11 @@ __global__ __launch_bounds__(CT) void k_code_tiles(const uint32_t *__restrict__ 
 
 // rows: [tile][digit], where the digit's entries begin, counted from the tile's first; rows1 those of k_layout's tiles of tile1.
 // Also clears the chunks' sums for the next input.
+// (Entries of a digit end up in whatever order their LDS additions happen: nothing relies on it.)
 __global__ __launch_bounds__(CT, 6) void k_code_split2(const uint64_t *__restrict__ in, const uint16_t *__restrict__ rows1, int bins1,
                                                     int64_t N, int tile1, const bin_tile *__restrict__ tiles, int n_tiles, int per_bin, int shift,
                                                     int bins2, uint16_t *__restrict__ rows,
-                                                    uint64_t *__restrict__ out, uint32_t *__restrict__ sums, int chunks,
-                                                    uint32_t *__restrict__ n_lasts) {
+                                                    uint64_t *__restrict__ out, uint32_t *__restrict__ sums, int chunks) {
     __shared__ alignas(16) uint64_t s_entry[SPLIT2_TILE];
     __shared__ uint32_t s_cnt[MAX_BINS];
     __shared__ uint32_t s_wave[CW], s_front;
@@ -764,7 +624,6 @@ __global__ __launch_bounds__(CT, 6) void k_code_split2(const uint64_t *__restric
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if ((int)blockIdx.x < chunks)  // (chunks of 32 tiles and more, six to a tile at most: there are as many workgroups)
         for (int i = tid; i < bins1; i += CT) sums[(int64_t)blockIdx.x * bins1 + i] = 0;
-    if (blockIdx.x == 0 && tid == 0) *n_lasts = 0;  // (for k_code_ranges)
     // (A die takes neighbouring bins, and of these the tiles of the same places together: where a run of one ends the next one's
     // begins, in the same line.)
     const int n = ((int)gridDim.x >> 3), x = (int)blockIdx.x & 7, k = (int)blockIdx.x >> 3, columns = n / per_bin;
@@ -926,10 +785,15 @@ __device__ __forceinline__ sort_range between(const sort_bound &r, const sort_bo
 // is left that no workgroup takes.
 struct sort_cut { sort_range first, last; };  // of a tile that is not sortable as it is
 
-// What the second split has left, see there.  rows = nullptr: there was none, entries lie in the order of their buckets.
+// What the last split has left: bins' tiles, whose entries are ordered by digit, and their rows.  (Where there is one split only, all is one bin.)
 struct split_rows {
-    const uint32_t *starts1;
+    const uint32_t *starts1;  // nullptr: one bin
     const uint16_t *rows;
+    uint32_t N;
+    int tile, bits2;
+    __device__ bin_place bin(int b) const { return starts1 ? first_bin(starts1, b) : bin_place{0u, N}; }
+    __device__ int tiles(const bin_place &p) const { return (int)((p.size + (uint32_t)tile - 1u) / (uint32_t)tile); }
+    __device__ const uint16_t *row(const bin_place &p, int b) const { return rows + ((int64_t)(starts1 ? first_tile(p.start, b) : 0) << bits2); }
 };
 // Where the entries of a workgroup's buckets lie: a piece in each of their bin's tiles, in the bin's order.
 struct sort_pieces {
@@ -940,10 +804,11 @@ struct sort_pieces {
 
 // One wave: the pieces of the range f, if it is of one bin or two neighbouring ones, of up to 64 tiles together, and its buckets'
 // last bits tell them apart.
-__device__ __forceinline__ void find_pieces(const split_rows &split, int bits2, const sort_range &f, sort_pieces *to) {
-    const int lane = threadIdx.x & 63, bins2 = 1 << bits2, B0 = (int)f.bucket >> bits2, B1 = (int)(f.end - 1) >> bits2;
-    const bin_place p0 = first_bin(split.starts1, B0), p1 = B1 > B0 ? first_bin(split.starts1, B1) : bin_place{0u, 0u};
-    const int nt0 = (int)((p0.size + SPLIT2_TILE - 1) / SPLIT2_TILE), nt1 = (int)((p1.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+__device__ __forceinline__ void find_pieces(const split_rows &split, const sort_range &f, sort_pieces *to) {
+    const int lane = threadIdx.x & 63, bins2 = 1 << split.bits2, B0 = (int)f.bucket >> split.bits2, B1 = (int)(f.end - 1) >> split.bits2;
+    const bin_place p0 = split.bin(B0), p1 = B1 > B0 ? split.bin(B1) : bin_place{0u, 0u};
+    const int nt0 = split.tiles(p0), nt1 = split.tiles(p1);
+    const uint32_t tile = (uint32_t)split.tile;
     uint32_t from = 0, len = 0;
     const bool easy = B1 - B0 <= 1 && nt0 + nt1 <= SD_WAVE && (int)(f.end - f.bucket) <= bins2;
     if (easy && lane < nt0 + nt1) {
@@ -951,10 +816,10 @@ __device__ __forceinline__ void find_pieces(const split_rows &split, int bits2, 
         const bin_place p = second ? p1 : p0;
         const int B = second ? B1 : B0, t = second ? lane - nt0 : lane;
         const int d0 = B == B0 ? (int)f.bucket & (bins2 - 1) : 0, d1 = B == B1 ? ((int)(f.end - 1) & (bins2 - 1)) + 1 : bins2;
-        const uint16_t *row = split.rows + (int64_t)(first_tile(p.start, B) + t) * bins2;
-        const uint32_t left = p.size - (uint32_t)t * SPLIT2_TILE, at = row[d0];
-        len = (d1 < bins2 ? row[d1] : left < (uint32_t)SPLIT2_TILE ? left : (uint32_t)SPLIT2_TILE) - at;
-        from = p.start + (uint32_t)t * SPLIT2_TILE + at;
+        const uint16_t *row = split.row(p, B) + (int64_t)t * bins2;
+        const uint32_t left = p.size - (uint32_t)t * tile, at = row[d0];
+        len = (d1 < bins2 ? row[d1] : left < tile ? left : tile) - at;
+        from = p.start + (uint32_t)t * tile + at;
     }
     const uint32_t inc = wave_incl_scan(len);
     const uint64_t some = __ballot(len != 0);
@@ -970,25 +835,57 @@ __device__ __forceinline__ void find_pieces(const split_rows &split, int bits2, 
 // than k_code_sort over the tiles.
 // A wave finds where a tile's buckets start; the eighth wave of a workgroup looks at the next workgroup's
 // first tile.  (On its own, before the sort: the host hears from it while the sort is running.)
-__global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__ starts, int64_t N, int bits,
+// ONE: after one split a workgroup also adds up, digit by digit, what lies in front in each tile: where the buckets start.
+template <bool ONE>
+__global__ __launch_bounds__(CT) void k_code_ranges(uint32_t *__restrict__ starts, int64_t N, int bits,
                                                     int tile, int tiles, const uint32_t *__restrict__ cdf,
                                                     int32_t n_codes, sort_bound *__restrict__ bounds,
                                                     sort_cut *__restrict__ cuts, sort_range *__restrict__ lasts,
-                                                    uint32_t *n_lasts, int taken, int32_t *rest, split_rows split, int bits2,
+                                                    uint32_t *n_lasts, int taken, int32_t *rest, split_rows split,
                                                     sort_pieces *__restrict__ pieces) {
     __shared__ sort_bound s_bound[CW];
+    __shared__ uint32_t s_starts[ONE ? MAX_BINS + 1 : 1];
+    __shared__ uint2 s_area[ONE ? CT : 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, buckets = 1 << bits;
     const int t = (int)blockIdx.x * (CW - 1) + w;
-    auto start = [&](int i) { return (int64_t)starts[i]; };
+    if (ONE) {
+        const int pairs = buckets >> 1, nt = split.tiles({0u, split.N}), most = CT / pairs, groups = most < nt ? most : nt;
+        const int col = (int)threadIdx.x & (pairs - 1), group = (int)threadIdx.x / pairs;
+        uint2 at = make_uint2(0u, 0u);
+        if (group < groups) {
+#pragma unroll 8
+            for (int i = group; i < nt; i += groups) {
+                const uint32_t v = reinterpret_cast<const uint32_t *>(split.rows + (int64_t)i * buckets)[col];
+                at.x += v & 0xffffu;
+                at.y += v >> 16;
+            }
+        }
+        s_area[threadIdx.x] = at;
+        __syncthreads();
+        if ((int)threadIdx.x < pairs) {
+            for (int g = 1; g < groups; g++) {
+                const uint2 v = s_area[g * pairs + threadIdx.x];
+                at = make_uint2(at.x + v.x, at.y + v.y);
+            }
+            s_starts[2 * threadIdx.x] = at.x;
+            s_starts[2 * threadIdx.x + 1] = at.y;
+        }
+        if (threadIdx.x == 0) s_starts[buckets] = (uint32_t)N;
+        __syncthreads();
+        if (blockIdx.x == 0)
+            for (int i = (int)threadIdx.x; i <= buckets; i += CT) starts[i] = s_starts[i];
+    }
+    auto start_of = [&](int i) { return ONE ? s_starts[i] : starts[i]; };
+    auto start = [&](int i) { return (int64_t)start_of(i); };
     auto code_of = [&](int b) {  // first token whose interval starts in bucket b or behind it
         return (uint32_t)wave_lower_bound([&](int i) { return (int64_t)cdf[i]; }, n_codes + 1, (int64_t)b << (32 - bits));
     };
     if (t <= tiles) {
         const int b = t == tiles ? buckets : wave_lower_bound(start, buckets, (int64_t)t * tile);
-        const uint32_t at = starts[b];
+        const uint32_t at = start_of(b);
         int filled = b;
         if (b < buckets) {
-            const uint64_t m = __ballot(b + 1 + lane > buckets || starts[b + 1 + lane] > at);
+            const uint64_t m = __ballot(b + 1 + lane > buckets || start_of(b + 1 + lane) > at);
             filled = m ? b + __builtin_ctzll(m) : wave_lower_bound(start, buckets, (int64_t)at + 1) - 1;
         }
         const uint32_t c = t == tiles ? (uint32_t)(n_codes + 1) : code_of(b);
@@ -1002,14 +899,14 @@ __global__ __launch_bounds__(CT) void k_code_ranges(const uint32_t *__restrict__
     const sort_bound z = s_bound[w + 1];
     sort_range f = between(s_bound[w], z);
     if (sortable(f)) {
-        if (split.rows && f.at != f.end_at) find_pieces(split, bits2, f, pieces + t);
+        if (f.at != f.end_at) find_pieces(split, f, pieces + t);
         return;
     }
     const uint32_t b = (uint32_t)wave_lower_bound(start, buckets, (int64_t)z.at) - 1;  // of the last entry
     sort_range l = {b, b, z.at, z.at, z.code, z.code};
     f.end = b + 1;
     if (f.end_at - f.at > (uint32_t)SORT_CAP) {
-        l = {b, b + 1, starts[b], z.at, code_of((int)b), z.code};
+        l = {b, b + 1, start_of((int)b), z.at, code_of((int)b), z.code};
         f.end_at = l.at;
         f.end_code = l.code;
         f.end = f.at == l.at ? f.bucket : (uint32_t)wave_lower_bound(start, buckets, (int64_t)l.at);
@@ -1110,7 +1007,6 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                                                   int32_t *__restrict__ samples, int32_t *__restrict__ bucket) {
     __shared__ uint64_t s_entry[SORT_CAP + 4];     // later positions by place, and lists (up to three more are read)
     __shared__ uint4 s_area[SORT_PARTS / 8];       // counts per part, two per word; later windows
-    __shared__ uint32_t s_start[SORT_BUCKETS + 1];  // places of the workgroup's buckets
     __shared__ uint32_t s_first[SORT_CAP / 32 + 4];  // bit per place: a group starts here
     __shared__ uint32_t s_done[SORT_CAP / 32];       // bit per place: see below
     __shared__ uint64_t s_class[2][SORT_CAP / 64];   // of a long group: entries below and at the middle one
@@ -1127,7 +1023,7 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
     bool found = false;  // pieces[] has where its entries lie
     if ((int)blockIdx.x < tiles) {
         range = between(bounds[blockIdx.x], bounds[blockIdx.x + 1]);
-        found = split.rows && pieces[blockIdx.x].n != 0;
+        found = pieces[blockIdx.x].n != 0;
         if (__builtin_expect(!sortable(range), 0)) {
             range = cuts[blockIdx.x].first;
             found = false;
@@ -1152,10 +1048,11 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
     if (tid == 0) s_n_long = s_n_todo = 0;
     const int n = (int)(z - a);
     const uint32_t start = tid <= nb ? starts[b0 + tid] : 0u;
+    const bool one = f.one_split();
     const bool named = nb <= 1 << f.bits2;  // the entries have so many of their buckets' last bits that these tell them apart
     uint64_t e[SORT_ITEMS];
-    int base[SORT_ITEMS];
-    if (split.rows) {
+    uint32_t lo_of[SORT_ITEMS];  // one split: its tile's first position; entries that lack their bin: their bin's first bucket
+    {
         uint32_t *s_from = reinterpret_cast<uint32_t *>(s_entry);           // of a piece, as above
         int16_t *s_base = reinterpret_cast<int16_t *>(s_from + SORT_CAP);   // its bin's first bucket, counted from b0
         uint64_t *s_ends = s_entry + 3 * SORT_CAP / 4;                      // a bit per place: a piece ends here
@@ -1170,24 +1067,25 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
         } else {
             const int bins2 = 1 << f.bits2, B0 = b0 >> f.bits2, B1 = ((int)range.end - 1) >> f.bits2;
             uint32_t done = 0, n_pieces = 0;
+            const uint32_t tile = (uint32_t)split.tile;
             for (int B = B0; B <= B1; B++) {
-                const bin_place p = first_bin(split.starts1, B);
-                const int nt = (int)((p.size + SPLIT2_TILE - 1) / SPLIT2_TILE);
+                const bin_place p = split.bin(B);
+                const int nt = split.tiles(p);
                 const int d0 = B == B0 ? b0 & (bins2 - 1) : 0, d1 = B == B1 ? (((int)range.end - 1) & (bins2 - 1)) + 1 : bins2;
-                const uint16_t *rows = split.rows + (int64_t)first_tile(p.start, B) * bins2;
+                const uint16_t *rows = split.row(p, B);
                 for (int t0 = 0; t0 < nt; t0 += CT) {
                     const int t = t0 + tid;
                     uint32_t from = 0, len = 0, tot;
                     if (t < nt) {
-                        const uint32_t left = p.size - (uint32_t)t * SPLIT2_TILE;
+                        const uint32_t left = p.size - (uint32_t)t * tile;
                         from = rows[(int64_t)t * bins2 + d0];
-                        len = (d1 < bins2 ? rows[(int64_t)t * bins2 + d1] : left < SPLIT2_TILE ? left : SPLIT2_TILE) - from;
+                        len = (d1 < bins2 ? rows[(int64_t)t * bins2 + d1] : left < tile ? left : tile) - from;
                     }
                     const uint32_t ex = block_excl_scan(len | (len ? 1u << 16 : 0u), s_wave, &tot);
                     if (len) {
                         const uint32_t to = done + (ex & 0xffffu), last = to + len - 1;
                         s_base[n_pieces + (ex >> 16)] = (int16_t)((B << f.bits2) - b0);
-                        s_from[n_pieces + (ex >> 16)] = p.start + (uint32_t)t * SPLIT2_TILE + from - to;
+                        s_from[n_pieces + (ex >> 16)] = p.start + (uint32_t)t * tile + from - to;
                         atomicOr(reinterpret_cast<uint32_t *>(s_ends) + (last >> 5), 1u << (last & 31));
                     }
                     done += tot & 0xffffu;
@@ -1203,49 +1101,35 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
             const int j = k * CT + tid, q = k * CW + w;
             const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)ends, q), hi = __builtin_amdgcn_readlane((int)(uint32_t)(ends >> 32), q);
             const uint32_t piece = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, (uint32_t)__builtin_amdgcn_readlane((int)before, q)));
-            e[k] = j < n ? in[s_from[piece] + (uint32_t)j] : 0ull;
-            base[k] = !named && j < n ? (int)s_base[piece] : 0;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < SORT_ITEMS; k++) {
-            const int j = k * CT + tid;
-            e[k] = j < n ? in[a + j] : 0ull;
+            const uint32_t from = j < n ? s_from[piece] + (uint32_t)j : 0u;
+            e[k] = j < n ? in[from] : 0ull;
+            lo_of[k] = named ? from & ~(uint32_t)(KEY_ROUND - 1) : j < n ? (uint32_t)(int)s_base[piece] : 0u;
         }
     }
-    if (tid <= nb) s_start[tid] = start - (uint32_t)a;
-    for (int i = CT + tid; i <= nb; i += CT) s_start[i] = starts[b0 + i] - (uint32_t)a;
-    if (!split.rows) __syncthreads();
     // parts: 2^fine per bucket
     const int in_bucket = f.key_bits - f.bits2;
     int fine = 31 - __builtin_clz(SORT_PARTS / nb);
     if (fine > in_bucket) fine = in_bucket;
     const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
-    // (Looked up in the entry and not among the buckets' places, and parts counted four entries at a time: 10M independent
+    // (A bucket is looked up in the entry, and parts are counted four entries at a time: 10M independent
     // tokens 90.8 -> 86.7 us, copied ones as before.)
+    const int code_at = one ? TILE_POS_BITS + f.tok_bits : low_bits;
     uint32_t part[SORT_ITEMS], rank[SORT_ITEMS];
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++) {
         const int j = k * CT + tid;
         if (j < n) {
-            int lo = 0;
-            if (named) {
-                lo = (int)(((uint32_t)(e[k] >> low_bits) >> in_bucket) - (uint32_t)b0) & ((1 << f.bits2) - 1);
-            } else if (split.rows) {
-                lo = base[k] + ((int)((uint32_t)(e[k] >> low_bits) >> in_bucket) & ((1 << f.bits2) - 1));
-            } else {      // last bucket that starts at or before place j
-                for (int hi = nb; hi - lo > 1;) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_start[mid] <= (uint32_t)j) lo = mid; else hi = mid;
-                }
-            }
-            part[k] = ((uint32_t)lo << fine) + (((uint32_t)(e[k] >> low_bits) & key_mask) >> (in_bucket - fine));
+            const uint32_t code = (uint32_t)(e[k] >> code_at);
+            const int last = (int)(code >> in_bucket) & ((1 << f.bits2) - 1);  // the bucket's last bits
+            const int lo = named ? (last - b0) & ((1 << f.bits2) - 1) : (int)lo_of[k] + last;
+            part[k] = ((uint32_t)lo << fine) + ((code & key_mask) >> (in_bucket - fine));
+            if (one) e[k] = (e[k] >> TILE_POS_BITS) << f.pos_bits | (lo_of[k] + ((uint32_t)e[k] & (uint32_t)(KEY_ROUND - 1)));  // (the bucket's bits may leave)
             const uint32_t sh = (part[k] & 1u) * 16u;
             rank[k] = (atomicAdd(&cnt[part[k] >> 1], 1u << sh) >> sh) & 0xffffu;
         }
     }
     for (int i = tid; i <= nb; i += CT) {
-        const uint32_t p = s_start[i];  // (a bucket's first place; the last one ends the last group)
+        const uint32_t p = (i < CT ? start : starts[b0 + i]) - (uint32_t)a;  // (a bucket's first place; the last one ends the last group)
         atomicOr(&s_first[p >> 5], 1u << (p & 31));
     }
     __syncthreads();
@@ -1842,12 +1726,15 @@ __global__ __launch_bounds__(CT) void k_rest_bucket(const rest_range *__restrict
 // workgroup of k_code_sort, whole buckets, is SORT_TILE give or take one of them, and a bucket may
 // be five times as large as the average before it no longer fits.  (Buckets half that size: 100M
 // entries then take a split of 1024 ways, whose runs are 6 entries; 0.83 instead of 0.70 ms.)
-// Up to 10 bits go in one split (three launches), which is then as fine as that allows, down to
-// buckets of 32 to 64: the shares can be as small.
-// Tiles of 6144 entries leave as runs of 24 entries per bin and more; inputs up to SMALL_MAX take tiles of
-// 2048, which are spread over more compute units (2.2M and 3.9M, layout and split: 22 + 13 and 30 + 22 us in tiles
-// of 6144; 20 + 13 and 28 + 17 so.  10M: 71 + 49, 71 + 51).
-constexpr int64_t SMALL_MAX = 4 << 20;
+// Up to ONE_SPLIT_MAX positions k_layout's split is the only one, which then is as fine as 10 bits allow, down to
+// buckets of 32 to 64: the shares can be as small.  (A workgroup of k_code_ranges and one of the sort then look at all tiles' rows: builds of
+// 140k, 262k, 400k and 500k tokens 52, 60, 71 and 77 us in one split, 63, 66, 73 and 75 in two; with one split by counts, places
+// and moves, two launches more: 59 to 62, -, -, 75.)
+// Tiles of 6144 entries leave as runs of 12 entries per bin and more; inputs up to SMALL_MAX take tiles of
+// 2048, which are spread over more compute units (2.2M and 3.9M, codes and split apart: 22 + 13 and 30 + 22 us in tiles
+// of 6144; 20 + 13 and 28 + 17 so).
+constexpr int64_t SMALL_MAX = 4 << 20, ONE_SPLIT_MAX = 224 * KEY_ROUND;
+static_assert(ONE_SPLIT_MAX <= (int64_t)CT * KEY_ROUND, "a thread to a tile");
 struct split_plan {
     int bits1, bits2;
     bool small_tiles;
@@ -1857,9 +1744,8 @@ split_plan plan_for(int64_t N) {
     while (bits < MAX_BITS && (N >> bits) > 64) bits++;
     while (bits < 2 * MAX_BITS && (N >> bits) > 512) bits++;
     split_plan p;
-    p.bits1 = bits;
-    p.bits2 = 0;
-    if (bits > MAX_BITS) { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
+    if (N > ONE_SPLIT_MAX) { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
+    else { p.bits1 = 0; p.bits2 = bits; }
     p.small_tiles = N <= SMALL_MAX;
     return p;
 }
@@ -1889,8 +1775,7 @@ int sort_tile_for(int64_t N, int n_cu) {
     if (t < 2 * average) t = 2 * average;
     return (int)(t < SORT_TILE_FEW ? SORT_TILE_FEW : t > most ? most : t);
 }
-constexpr int SMALL_ITEMS = 4;
-constexpr int SMALL_ROUNDS = 1, LARGE_ROUNDS = 3, LARGE_THREADS = 512;
+constexpr int SMALL_ROUNDS = 1, LARGE_ROUNDS = 3;
 static_assert(((1ll << 31) / (LARGE_ROUNDS * KEY_ROUND) + MAX_CHUNKS - 1) / MAX_CHUNKS <= MAX_PER_CHUNK, "");
 int64_t layout_tile(const split_plan &p) { return (int64_t)KEY_ROUND * (p.small_tiles ? SMALL_ROUNDS : LARGE_ROUNDS); }
 
@@ -1901,16 +1786,13 @@ int64_t layout_tile(const split_plan &p) { return (int64_t)KEY_ROUND * (p.small_
 void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
                   int64_t *range_words, int64_t *rest_words) {
     int64_t h = 0, s = 0;
-    const int64_t sizes[] = {cap, SMALL_MAX, ((int64_t)513 << MAX_BITS) - 1};  // (the most of one split)
+    const int64_t sizes[] = {cap, SMALL_MAX, ONE_SPLIT_MAX};
     for (int64_t n : sizes) {
         if (n > cap) n = cap;
         const split_plan p = plan_for(n);
         const int64_t tile = layout_tile(p), ntiles = (n + tile - 1) / tile;
-        int64_t x = ntiles << p.bits1;
-        if (p.bits2) {
-            const int64_t tiles = n / SPLIT2_TILE + (1ll << p.bits1);
-            x = x / 2 + (tiles << p.bits2) / 2 + (1ll << p.bits1) + tiles * (int64_t)(sizeof(bin_tile) / 4) + 64;
-        }
+        const int64_t tiles = p.bits1 ? n / SPLIT2_TILE + (1ll << p.bits1) : 0;
+        const int64_t x = (ntiles << (p.bits1 ? p.bits1 : p.bits2)) / 2 + (tiles << p.bits2) / 2 + (1ll << p.bits1) + tiles * (int64_t)(sizeof(bin_tile) / 4) + 64;
         h = x > h ? x : h;
         const int64_t y = (1ll << (p.bits1 + p.bits2)) + 1;
         s = y > s ? y : s;
@@ -1991,10 +1873,10 @@ void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_
                int32_t *text, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
     const split_plan p = plan_for(N);
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (p.small_tiles ? k_layout<CT, SMALL_ROUNDS, TEXT_ONLY, false> : k_layout<CT, LARGE_ROUNDS, TEXT_ONLY, false>),
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (p.small_tiles ? k_layout<CT, SMALL_ROUNDS, TEXT_ONLY> : k_layout<CT, LARGE_ROUNDS, TEXT_ONLY>),
               layout_grid(N, layout_tile(p)), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
               c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (const uint32_t *)nullptr, 0, (uint32_t *)nullptr, entry_shape{}, (uint64_t *)nullptr, (uint16_t *)nullptr,
-              (uint32_t *)nullptr, (int64_t)0, 1, (uint32_t *)nullptr, (uint32_t *)nullptr, 0);
+              (int64_t)0, 0, (uint32_t *)nullptr, (uint32_t *)nullptr, 0, (uint32_t *)nullptr);
 }
 
 // An entry's 64 bits: whether they hold what is needed of an input.
@@ -2004,10 +1886,10 @@ static bool shape_for(int64_t N, int32_t vocab, entry_shape *f) {
     f->bits2 = p.bits2;
     f->pos_bits = sd_bits_for((uint64_t)(N - 1));
     f->tok_bits = sd_bits_for((uint64_t)vocab);
-    f->key_bits = 64 - f->pos_bits - f->tok_bits;
+    f->key_bits = 64 - (p.bits1 ? f->pos_bits : TILE_POS_BITS) - f->tok_bits;
     if (f->key_bits > 32 - p.bits1) f->key_bits = 32 - p.bits1;
     f->key_drop = 32 - p.bits1 - f->key_bits;
-    return f->key_drop <= CDF_QUANTUM;
+    return f->key_drop <= CDF_QUANTUM && (p.bits1 || f->key_bits - f->bits2 <= 64 - f->pos_bits - f->tok_bits);
 }
 
 bool sd_code_fits(int64_t N, int32_t vocab) {
@@ -2015,22 +1897,24 @@ bool sd_code_fits(int64_t N, int32_t vocab) {
     return shape_for(N, vocab, &f);
 }
 
-// Tables of a split in two, in b_hist.
+// Tables of the splits, in b_hist.
 struct split_tables {
     uint32_t *starts1;  // where the bins of the first split start
     uint16_t *rows1;    // of k_layout's tiles
     uint16_t *rows2;    // of the second split's
     bin_tile *tiles;    // these
     int n_tiles;
+    split_rows last;    // what the last split leaves
 };
 static split_tables split_tables_for(const sd_ctx *c, int64_t N, const entry_shape &f) {
     auto up = [](int64_t words) { return (words + 3) / 4 * 4; };
     split_tables t;
-    const int64_t tile = layout_tile(plan_for(N)), bins = 1ll << f.bits1;
-    t.n_tiles = (int)(N / SPLIT2_TILE + bins);
+    const int64_t tile = layout_tile(plan_for(N));
+    t.n_tiles = f.one_split() ? 0 : (int)(N / SPLIT2_TILE + (1ll << f.bits1));
     t.starts1 = c->b_hist;
-    t.rows1 = reinterpret_cast<uint16_t *>(t.starts1 + up(bins + 1));
-    t.rows2 = t.rows1 + 2 * up((N + tile - 1) / tile * bins / 2);
+    t.rows1 = reinterpret_cast<uint16_t *>(t.starts1 + up((1ll << f.bits1) + 1));
+    t.rows2 = t.rows1 + 2 * up(((N + tile - 1) / tile << f.lead()) / 2);
+    t.last = f.one_split() ? split_rows{nullptr, t.rows1, (uint32_t)N, (int)tile, f.bits2} : split_rows{t.starts1, t.rows2, (uint32_t)N, SPLIT2_TILE, f.bits2};
     t.tiles = reinterpret_cast<bin_tile *>(t.rows2 + 2 * up(((int64_t)t.n_tiles << f.bits2) / 2));
     return t;
 }
@@ -2066,24 +1950,20 @@ static void sort_ranges(sd_ctx *c, const uint64_t *entries, int64_t N, const sor
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
     const packed_text packed = {line_room(c), bits, 128 * R / bits};
-    const split_tables two = split_tables_for(c, N, f);
-    const split_rows split = {two.starts1, f.bits2 ? two.rows2 : nullptr};
     SD_LAUNCH(c, SD_K_CODE_SORT, st, (R == 3 ? k_code_sort<3> : R == 2 ? k_code_sort<2> : k_code_sort<1>),
               dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries,
-              split, t.pieces, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
+              split_tables_for(c, N, f).last, t.pieces, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
               n ? t.taken : 0, f, packed, c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
 }
 
-// k_layout with codes: split into `entries` and rows1, or codes and counts.
+// k_layout with codes, split into `entries` and rows1; entries = nullptr: the codes by position into `keys`, and no more.
 static void layout_codes(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens, int32_t *text, entry_shape f,
-                         uint32_t *keys, uint64_t *entries, uint16_t *rows1, uint32_t *hist, int64_t ntiles, int per_chunk, hipStream_t st) {
-    const int64_t N = n_tokens + n_seq;
-    const split_plan p = plan_for(N);
+                         uint32_t *keys, uint64_t *entries, uint16_t *rows1, int per_chunk, uint32_t *n_lasts, hipStream_t st) {
+    const int64_t N = n_tokens + n_seq, tile = layout_tile(plan_for(N));
     const bool by_block = sd_code_blocks(c->cfg.vocab) <= CDF_BLOCKS + 1;
-    SD_LAUNCH(c, SD_K_SORT_HIST, st, (!p.bits2 ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT, false> : p.small_tiles ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT, true> :
-                                      by_block ? k_layout<LARGE_THREADS, LARGE_ROUNDS, CODES_BY_BLOCK, true> : k_layout<LARGE_THREADS, LARGE_ROUNDS, CODES_DIRECT, true>),
-              layout_grid(N, layout_tile(p)), dim3(p.small_tiles ? CT : LARGE_THREADS), 0, tokens, offs, n_seq, n_tokens, text, c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks,
-              block_shift(c->cfg.vocab), keys, f, entries, rows1, hist, ntiles, per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab));
+    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (plan_for(N).small_tiles ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT> : by_block ? k_layout<CT, LARGE_ROUNDS, CODES_BY_BLOCK> : k_layout<CT, LARGE_ROUNDS, CODES_DIRECT>),
+              layout_grid(N, tile), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text, c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks,
+              block_shift(c->cfg.vocab), keys, f, entries, rows1, entries ? (N + tile - 1) / tile : 0, per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab), n_lasts);
 }
 
 // Lays the documents out in `text` and sorts its N >= 1 positions into sa; tok1 (with samples), if
@@ -2105,28 +1985,19 @@ bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t
     const dim3 block(CT);
     const sort_tables t = tables_for(c, N);
     const split_tables two = split_tables_for(c, N, f);
-    if (p.bits2) {
-        layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, nullptr, ent1, two.rows1, nullptr, ntiles, per_chunk, st);
+    layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, nullptr, ent1, two.rows1, f.one_split() ? 0 : per_chunk, t.n_lasts, st);
+    if (!f.one_split()) {
         SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_tiles, dim3(chunks), block, 0, c->code_sums, bins1, per_chunk, chunks, two.starts1, (uint32_t)N, two.tiles, two.n_tiles);
         const int shift = f.pos_bits + f.tok_bits + f.key_bits - f.bits2;
         const int per_bin = (two.n_tiles + bins1 - 1) / bins1, columns = (two.n_tiles + 8 * per_bin - 1) / (8 * per_bin);
         SD_LAUNCH(c, SD_K_SORT_SCATTER, st, k_code_split2, dim3((unsigned)(8 * columns * per_bin)), block, 0, ent1, two.rows1, bins1, N, (int)tile, two.tiles, two.n_tiles, per_bin, shift, bins2, two.rows2, ent2,
-                  c->code_sums, chunks, t.n_lasts);
+                  c->code_sums, chunks);
         SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_starts2, dim3(bins1), block, 0, two.starts1, bins2, two.rows2, c->b_starts, (uint32_t)N);
         ent1 = ent2;
-    } else {
-        uint32_t *keys = c->b_flags, *hist = c->b_hist;
-        const bool few = chunks == 1;
-        layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, keys, nullptr, nullptr, hist, ntiles, few ? 0 : per_chunk, st);
-        if (!few)
-            SD_LAUNCH(c, SD_K_SORT_SCAN, st, k_code_places, dim3(chunks), block, 0, hist, bins1, ntiles, per_chunk,
-                      c->code_sums, chunks, c->b_starts, (uint32_t)N);
-        SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (few ? k_code_split<SMALL_ITEMS, true> : k_code_split<SMALL_ITEMS, false>),
-                  dim3((unsigned)ntiles), block, 0, keys, text, N, f, hist, chunks, c->code_sums, c->b_starts, ent1, t.n_lasts);
     }
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_ranges, dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (f.one_split() ? k_code_ranges<true> : k_code_ranges<false>), dim3((unsigned)((t.tiles + CW - 2) / (CW - 1))), block, 0,
               c->b_starts, N, f.bits1 + f.bits2, t.tile, t.tiles, c->code_cdf, c->cfg.vocab + 1, t.bounds, t.cuts, t.lasts, t.n_lasts, t.taken, c->h_flag,
-              split_rows{two.starts1, f.bits2 ? two.rows2 : nullptr}, f.bits2, t.pieces);
+              two.last, t.pieces);
     const bool asked = hipEventRecord(c->code_asked, st) == hipSuccess;
     sort_ranges(c, ent1, N, t, 0, f, sa, tok1, bucket, st);
     return asked;
@@ -2145,12 +2016,12 @@ sd_status sd_code_rest(sd_ctx *c, const int32_t *tokens, const int64_t *offs, in
     const volatile uint32_t *told = reinterpret_cast<const volatile uint32_t *>(c->h_flag);
     const int more = (int)told[REST_LASTS] - t.taken, n = (int)told[REST_LONG];
     const uint32_t S = told[REST_ENTRIES], buckets = told[REST_BUCKETS];
-    if (more > 0) sort_ranges(c, c->b_keys[f.bits2 ? 1 : 0], N, t, more, f, sa, tok1, bucket, st);
+    if (more > 0) sort_ranges(c, c->b_keys[f.one_split() ? 0 : 1], N, t, more, f, sa, tok1, bucket, st);
     if (n == 0) return SD_OK;
     const int bits = f.bits1 + f.bits2, down = 32 - bits, rank_bits = sd_bits_for((uint64_t)N);
     uint32_t *codes = c->b_flags, *rank = c->b_rank, *place = c->b_gid2, *table = c->rest_table, *to = c->rest_to;
     const int64_t tiles = (N + REST_TILE - 1) / REST_TILE;
-    if (f.bits2) layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, codes, nullptr, nullptr, nullptr, 0, 0, st);  // (a split in two keeps no codes by position)
+    layout_codes(c, tokens, offs, n_seq, n_tokens, text, f, codes, nullptr, nullptr, 0, nullptr, st);  // (nothing keeps the codes by position)
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_table, grid((int64_t)1 << bits, CT), block, 0, t.rest, n, 1 << bits, table);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_count, dim3((unsigned)tiles), block, 0, codes, N, down, table, to);
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_rest_scan, dim3(1), block, 0, to, tiles);

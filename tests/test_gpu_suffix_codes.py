@@ -110,6 +110,25 @@ def test_insert_places(n_old, n_new, spread):
         g.close()
 
 
+@pytest.mark.parametrize("vocab", [900, 1 << 24])
+@pytest.mark.parametrize("n", [2048, 2049, 131_072, 131_073, 458_752, 458_753])
+def test_pieces_of_tiles(n, vocab):
+    """Around the sizes where the workgroups' shares come from one more tile: from a second one, from more than the
+    64 that are listed for a workgroup, and from tiles of a second split; with codes of 25 bits too, which leave
+    no room for a position beside all of a suffix's code.  Runs of one token make buckets that are kept apart, whose
+    pieces the sort finds by itself."""
+    rng = np.random.default_rng(n + vocab)
+    D = 24
+    docs = [_text(rng, n // 2, vocab, 4), np.full(min(n // 3, 5000), 7, np.int32)]
+    docs.append(_text(rng, n - sum(len(d) for d in docs) - 3, vocab, 2))
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n)
+    try:
+        g.build_global(docs)
+        _check(g, docs, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [100, 255, 257, 4095, 16_385, 65_535, 65_536, 65_537, 262_145, 4_194_304, 4_194_305])
 def test_small_shares(n):
     """Around the sizes where tiles, bins and the workgroups' shares change: 33 tiles need places of their own,
