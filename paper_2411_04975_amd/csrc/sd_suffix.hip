@@ -268,6 +268,7 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
 constexpr int KEY_ROUND = CT * 4;  // positions whose tokens' intervals are in LDS at a time
 constexpr int LINE_POS = 32;       // positions from one line to the next: a line has as many words
 constexpr int LINE_BITS_MIN = 16;  // (a word holds parts of three codes at most)
+constexpr int LINE_FIRST_BIT = 1;  // of the first code: see bits_at
 constexpr int LAYOUT_LOOK = 1024 / LINE_BITS_MIN - LINE_POS;  // tokens behind a round of positions that it looks at
 static_assert(LAYOUT_LOOK >= CODE_LOOK && LAYOUT_LOOK <= CT && KEY_ROUND % LINE_POS == 0, "");
 
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
         tok[PER] = CODES && tid < LAYOUT_LOOK ? token_at((r + 1) * KEY_ROUND + tid) : SD_END_TOKEN;
     };
     // the codes that word `tid` of a line (and of every 16th line behind it) holds parts of, and their shifts
-    const int word_bit = (tid & (LINE_POS - 1)) * 32, code0 = CODES ? word_bit / bits : 0;
+    const int word_bit = (tid & (LINE_POS - 1)) * 32 - LINE_FIRST_BIT, code0 = CODES && word_bit > 0 ? word_bit / bits : 0;
     const int left0 = 32 - bits + (word_bit - code0 * bits), left1 = left0 - bits, right2 = bits - left1;
     constexpr int ITEMS = CODES ? ROUNDS * PER : 0;
     uint32_t key_of[ITEMS + 1], second[ITEMS + 1], rank[ITEMS + 1];
@@ -934,8 +935,10 @@ template <int R>
 struct token_bits { uint64_t w[2 * R]; };
 template <int R>
 __device__ __forceinline__ token_bits<R> bits_at(const packed_text &t, uint32_t q) {
-    const uint32_t bit = (q & (LINE_POS - 1)) * (uint32_t)t.bits, s = bit & 31u;
-    const uint32_t *p = t.lines + (((int64_t)(q / LINE_POS) * 32) + (bit >> 5));
+    // (From the word that has the bit in front of the first one on, so that every shift is one of 0 to 31 bits to the right: a
+    // select less for each word.)
+    const uint32_t before = __umul24(q & (LINE_POS - 1), (uint32_t)t.bits) + (LINE_FIRST_BIT - 1), s = ~before & 31u;
+    const uint32_t *p = t.lines + (((int64_t)(q / LINE_POS) * 32) + (before >> 5));
     uint32_t d[4 * R + 1];
 #pragma unroll
     for (int k = 0; k < R; k++) {
@@ -943,7 +946,7 @@ __device__ __forceinline__ token_bits<R> bits_at(const packed_text &t, uint32_t 
         d[4 * k] = v.x; d[4 * k + 1] = v.y; d[4 * k + 2] = v.z; d[4 * k + 3] = v.w;
     }
     d[4 * R] = p[4 * R];
-    auto word = [&](int i) { return s ? __builtin_amdgcn_alignbit(d[i], d[i + 1], 32u - s) : d[i]; };
+    auto word = [&](int i) { return __builtin_amdgcn_alignbit(d[i], d[i + 1], s); };
     token_bits<R> r;
 #pragma unroll
     for (int k = 0; k < 2 * R; k++) r.w[k] = ((uint64_t)word(2 * k) << 32) | word(2 * k + 1);
@@ -1381,18 +1384,14 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                 mid.w[k] = ((uint64_t)half((uint32_t)(x.w[k] >> 32)) << 32) | half((uint32_t)x.w[k]);
         }
         int to = lane;  // where the lane's entry is by now
-        for (bool later = false;; later = true) {
-            const int lo = 63 - __builtin_clzll(first & ((2ull << to) - 1ull));
-            const uint64_t behind = first >> 1 >> to;
-            const int hi = behind ? to + 1 + __builtin_ctzll(behind) : 64;
-            const int head = later ? (int)(win[lo] & 63u) : lo + 1 < hi ? lo + 1 : lo;  // the lane that has the pivot
+        // A round; `head`: the lane that has the pivot.  True if there has to be another one.
+        auto round = [&](const token_bits<R> &pivot, int lo, int hi, int head) {
             uint64_t mine = 0, diff = 0;
             uint32_t word = SAME;
 #pragma unroll
             for (int k = 2 * R - 1; k >= 0; k--) {
-                const uint64_t v = later ? x.w[k] : mid.w[k];
-                const uint64_t d = x.w[k] ^ (((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)(v >> 32)) << 32) |
-                                             (uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)v));
+                const uint64_t d = x.w[k] ^ (((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)(pivot.w[k] >> 32)) << 32) |
+                                             (uint32_t)__builtin_amdgcn_ds_bpermute(head * 4, (int)(uint32_t)pivot.w[k]));
                 if (d) { mine = x.w[k]; diff = d; word = 64 * k; }
             }
             const int bit = diff ? __builtin_clzll(diff) : 0;
@@ -1418,7 +1417,19 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
             const uint32_t here = win[lane], before = lane > 0 ? win[lane - 1] : ~0u;
             const bool starts = (here ^ before) >= 64u;
             first = __ballot(starts);
-            if (!__any(!starts && ((here >> 16) & 1023u) != SAME)) break;
+            return __any(!starts && ((here >> 16) & 1023u) != SAME) != 0;
+        };
+        auto start_of = [&]() { return 63 - __builtin_clzll(first & ((2ull << to) - 1ull)); };
+        auto end_of = [&]() {
+            const uint64_t behind = first >> 1 >> to;
+            return behind ? to + 1 + __builtin_ctzll(behind) : 64;
+        };
+        int lo = start_of(), hi = end_of();
+        if (round(mid, lo, hi, lo + 1 < hi ? lo + 1 : lo)) {
+            do {
+                lo = start_of();
+                hi = end_of();
+            } while (round(x, lo, hi, (int)(win[lo] & 63u)));
         }
         if (lane < len) {
             s_pos[at + to - lane] = pos;
@@ -1484,7 +1495,7 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
         wave_sync();
         for (int at = 0; at < m;) {
             int len = m - at < 64 ? m - at : 64;
-            const int place = lane < len ? list[at + lane] : 0;
+            int place = lane < len ? list[at + lane] : 0;
             const uint64_t first = __ballot(lane < len && is_first(place));
             if (len == 64 && at + 64 < m && !is_first(list[at + 64])) len = 63 - __builtin_clzll(first);
             len = __builtin_amdgcn_readfirstlane(len);
@@ -1502,12 +1513,9 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                 wave_sync();
                 continue;
             }
-            uint32_t pos = 0;
-            token_bits<R> x = {};
-            if (lane < len) {
-                pos = s_pos[place];
-                x = bits_at<R>(text, pos + (uint32_t)h);
-            }
+            if (lane >= len) place = __builtin_amdgcn_readlane(place, len - 1);  // (its line is asked for anyhow; nothing comes of it)
+            const uint32_t pos = s_pos[place];
+            const token_bits<R> x = bits_at<R>(text, pos + (uint32_t)h);
             const bool open = order(first, len, place, pos, x);
             const uint64_t om = __ballot(open);
             if (open) list[out + __popcll(om & ((1ull << lane) - 1ull))] = (uint16_t)place;
@@ -1851,10 +1859,10 @@ static constexpr int line_words(int bits) {
 // From a line's last position on there are the words that bits_at reads and the codes that are compared, and the parts of codes
 // that k_layout puts into a word are of three that it has at hand.
 static constexpr bool lines_hold(int bits) {
-    const int R = line_words(bits) / 4, step = R > 0 ? 128 * R / bits : 0, last = (LINE_POS - 1) * bits;
+    const int R = line_words(bits) / 4, step = R > 0 ? 128 * R / bits : 0, last = (LINE_POS - 1) * bits + LINE_FIRST_BIT;
     bool ok = step > 0 && (last >> 5) + 4 * R < LINE_POS && last + 128 * R <= 32 * LINE_POS;
     for (int w = 0; w < LINE_POS; w++) {
-        const int c0 = 32 * w / bits, c1 = (32 * w + 31) / bits;
+        const int c0 = w ? (32 * w - LINE_FIRST_BIT) / bits : 0, c1 = (32 * w + 31 - LINE_FIRST_BIT) / bits;
         ok = ok && c1 - c0 <= 2 && c1 < LINE_POS + LAYOUT_LOOK;
     }
     return ok;
