@@ -745,17 +745,22 @@ __global__ __launch_bounds__(CT) void k_code_starts2(const uint32_t *__restrict_
 // whole workgroup (128 and 512 instead of 256: up to a tenth slower).  Builds of 10M tokens, half of them
 // copies of preambles, with 200, 500, 1000, 2000 copies of each: 0.94, 1.24, 1.23, 1.56 ms; 1.16, 1.71, 2.61,
 // 5.5 by counting, each long group split by one wave.
+//
+// Bound: vector instructions (in 83 to 88% of the time some SIMD's issue) and, where suffixes tie, the lines that are
+// gathered.  Registers and LDS are held to what four workgroups on a compute unit have, with part and place in a word and the
+// counts of 3072 parts (three workgroups, 4096 parts, every entry of a part compared to where the part ends: builds of 10M copied tokens as
+// now, of 10M independent ones 263 -> 243 us, of 100M copied ones 3.80 -> 3.67 ms).
 constexpr int SORT_TILE_MIN = 2048, SORT_TILE_MAX = 3072, SORT_TILE_FEW = 256;
-constexpr int SORT_TILE_MANY = 3328, SORT_ROUNDS = 8;
+constexpr int SORT_TILE_MANY = 3328, SORT_ROUNDS = 3;
 constexpr int SORT_SLOTS = 1024;  // workgroups that what is less than a round of them is spread over, at most
 constexpr int SORT_CAP = 4096;   // entries of a workgroup, at most
-constexpr int SORT_PARTS = 4096;
+constexpr int SORT_PARTS = 3072;
 constexpr int SORT_BUCKETS = 1024;  // of a workgroup, at most
 constexpr int SORT_ITEMS = SORT_CAP / CT;
 constexpr int PART_COUNTED = 64;    // entries of a part whose order is found by counting, at most
 constexpr int PART_OF_WAVE = 512;   // of one that a wave sorts alone
 constexpr int GROUP_OF_WAVE = 256;  // of a group of ties that a wave deals with alone
-static_assert(SORT_PARTS == 8 * CT && SORT_PARTS * 2 == CW * 64 * 16, "8 parts a thread; the waves' windows lie where the counts were");
+static_assert(SORT_PARTS == 6 * CT && SORT_PARTS * 2 >= CW * 64 * 4, "6 parts a thread; the waves' windows lie where the counts were");
 
 // What a workgroup takes: whole buckets, and the part of the bucket table that they answer for.
 struct sort_range {
@@ -998,7 +1003,7 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
 }
 
 template <int R>
-__global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict__ in, split_rows split, const sort_pieces *__restrict__ pieces,
+__global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict__ in, split_rows split, const sort_pieces *__restrict__ pieces,
                                                   const uint32_t *__restrict__ starts,
                                                   const sort_bound *__restrict__ bounds,
                                                   const sort_cut *__restrict__ cuts,
@@ -1009,11 +1014,9 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                                                   int32_t *__restrict__ sa, int32_t *__restrict__ tok1,
                                                   int32_t *__restrict__ samples, int32_t *__restrict__ bucket) {
     __shared__ uint64_t s_entry[SORT_CAP + 4];     // later positions by place, and lists (up to three more are read)
-    __shared__ uint4 s_area[SORT_PARTS / 8];       // counts per part, two per word; later windows
+    __shared__ alignas(16) uint32_t s_area[SORT_PARTS / 2 + 1];  // counts per part, two per word; later windows
     __shared__ uint32_t s_first[SORT_CAP / 32 + 4];  // bit per place: a group starts here
     __shared__ uint32_t s_done[SORT_CAP / 32];       // bit per place: see below
-    __shared__ uint64_t s_class[2][SORT_CAP / 64];   // of a long group: entries below and at the middle one
-    __shared__ uint32_t s_before[SORT_CAP / 64 + 1];
     __shared__ uint32_t s_todo[SORT_CAP / GROUP_OF_WAVE];  // long groups: place, depth from bit 16 on
     __shared__ int32_t s_n_todo;
     __shared__ uint32_t s_wave[CW];
@@ -1044,8 +1047,9 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
             for (int c = (int)range.code + tid; c < (int)range.end_code; c += CT) bucket[c] = (int32_t)a;
         return;
     }
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(s_area);
-    s_area[tid] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t *cnt = s_area;
+#pragma unroll
+    for (int k = 0; k < 3; k++) s_area[3 * tid + k] = 0;
     if (tid < SORT_CAP / 32 + 4) s_first[tid] = 0;
     if (tid < SORT_CAP / 32) s_done[tid] = 0;
     if (tid == 0) s_n_long = s_n_todo = 0;
@@ -1109,15 +1113,16 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
             lo_of[k] = named ? from & ~(uint32_t)(KEY_ROUND - 1) : j < n ? (uint32_t)(int)s_base[piece] : 0u;
         }
     }
-    // parts: 2^fine per bucket
-    const int in_bucket = f.key_bits - f.bits2;
-    int fine = 31 - __builtin_clz(SORT_PARTS / nb);
-    if (fine > in_bucket) fine = in_bucket;
+    // parts: as many of equal code range to every bucket
+    const int in_bucket = f.key_bits - f.bits2, top_bits = in_bucket < 12 ? in_bucket : 12;
+    const uint32_t parts = (uint32_t)(SORT_PARTS / nb);
+    auto part_of = [&](int b, uint32_t code) { return __umul24((uint32_t)b, parts) + (__umul24(code >> (in_bucket - top_bits), parts) >> top_bits); };
     const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
     // (A bucket is looked up in the entry, and parts are counted four entries at a time: 10M independent
     // tokens 90.8 -> 86.7 us, copied ones as before.)
     const int code_at = one ? TILE_POS_BITS + f.tok_bits : low_bits;
-    uint32_t part[SORT_ITEMS], rank[SORT_ITEMS];
+    uint32_t part[SORT_ITEMS];  // and, from bit 16 on, the place in it
+    static_assert(SORT_CAP <= 1 << 16 && SORT_PARTS <= 1 << 16, "");
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++) {
         const int j = k * CT + tid;
@@ -1125,10 +1130,9 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
             const uint32_t code = (uint32_t)(e[k] >> code_at);
             const int last = (int)(code >> in_bucket) & ((1 << f.bits2) - 1);  // the bucket's last bits
             const int lo = named ? (last - b0) & ((1 << f.bits2) - 1) : (int)lo_of[k] + last;
-            part[k] = ((uint32_t)lo << fine) + ((code & key_mask) >> (in_bucket - fine));
+            const uint32_t p = part_of(lo, code & key_mask), sh = (p & 1u) * 16u;
             if (one) e[k] = (e[k] >> TILE_POS_BITS) << f.pos_bits | (lo_of[k] + ((uint32_t)e[k] & (uint32_t)(KEY_ROUND - 1)));  // (the bucket's bits may leave)
-            const uint32_t sh = (part[k] & 1u) * 16u;
-            rank[k] = (atomicAdd(&cnt[part[k] >> 1], 1u << sh) >> sh) & 0xffffu;
+            part[k] = p | ((atomicAdd(&cnt[p >> 1], 1u << sh) >> sh) & 0xffffu) << 16;
         }
     }
     for (int i = tid; i <= nb; i += CT) {
@@ -1137,37 +1141,55 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
     }
     __syncthreads();
     {
-        const uint4 q = s_area[tid];
-        const uint32_t v[4] = {q.x, q.y, q.z, q.w};
-        uint32_t sum = 0, tot, o[4];
+        const uint32_t v[3] = {s_area[3 * tid], s_area[3 * tid + 1], s_area[3 * tid + 2]};
+        uint32_t sum = 0, tot, o[3];
 #pragma unroll
-        for (int k = 0; k < 4; k++) sum += (v[k] & 0xffffu) + (v[k] >> 16);
+        for (int k = 0; k < 3; k++) sum += (v[k] & 0xffffu) + (v[k] >> 16);
         uint32_t at = block_excl_scan(sum, s_wave, &tot);
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
+        for (int k = 0; k < 3; k++) {
             const uint32_t mid = at + (v[k] & 0xffffu);
             o[k] = at | (mid << 16);
             at = mid + (v[k] >> 16);
         }
         if (__builtin_expect(sum > (uint32_t)PART_COUNTED, 0))
-            for (int q = 0; q < 8; q++)
-                if (((v[q >> 1] >> (16 * (q & 1))) & 0xffffu) > (uint32_t)PART_COUNTED) s_long[atomicAdd(&s_n_long, 1)] = (uint16_t)(8 * tid + q);
-        s_area[tid] = make_uint4(o[0], o[1], o[2], o[3]);
-    }
-    __syncthreads();
-    auto part_start = [&](uint32_t p) -> int { return p < SORT_PARTS ? (int)((cnt[p >> 1] >> ((p & 1u) * 16u)) & 0xffffu) : n; };
+            for (int q = 0; q < 6; q++)
+                if (((v[q >> 1] >> (16 * (q & 1))) & 0xffffu) > (uint32_t)PART_COUNTED) s_long[atomicAdd(&s_n_long, 1)] = (uint16_t)(6 * tid + q);
 #pragma unroll
-    for (int k = 0; k < SORT_ITEMS; k++)
-        if (k * CT + tid < n) s_entry[part_start(part[k]) + rank[k]] = e[k];
+        for (int k = 0; k < 3; k++) s_area[3 * tid + k] = o[k];
+    }
+    if (tid == 0) s_area[SORT_PARTS / 2] = (uint32_t)n;
     __syncthreads();
-    const int n_long = s_n_long;
+    auto part_start = [&](uint32_t p) -> int { return (int)((cnt[p >> 1] >> ((p & 1u) * 16u)) & 0xffffu); };
+    uint32_t span[SORT_ITEMS];  // of the entry's part: first place, end from bit 16 on
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++)
         if (k * CT + tid < n) {
-            const int lo = part_start(part[k]), hi = part_start(part[k] + 1);
+            const uint32_t p = part[k] & 0xffffu;
+            span[k] = __builtin_amdgcn_alignbit(cnt[(p >> 1) + 1], cnt[p >> 1], (p & 1u) * 16u);
+            part[k] = (span[k] & 0xffffu) + (part[k] >> 16);  // (now the place)
+            s_entry[part[k]] = e[k];
+        }
+    if (tid < 4 && n + tid < SORT_CAP + 4) s_entry[n + tid] = ~0ull;
+    __syncthreads();
+    const int n_long = s_n_long;
+    // Where all buckets are of one bin, entries of later parts are no less: what is read beyond a part needs no looking at its end.
+    const bool rising = !one && (b0 ^ ((int)range.end - 1)) >> f.bits2 == 0;
+#pragma unroll
+    for (int k = 0; k < SORT_ITEMS; k++)
+        if (k * CT + tid < n) {
+            const int lo = (int)(span[k] & 0xffffu), hi = (int)(span[k] >> 16);
             int less = 0;
             if (__builtin_expect(n_long > 0, 0) && hi - lo > PART_COUNTED)
-                less = (int)rank[k];  // (it stays where it is for now)
+                continue;  // (it stays where it is for now)
+            if (rising)
+                for (int i = lo; i < hi; i += 4) {
+                    const uint64_t v0 = s_entry[i], v1 = s_entry[i + 1], v2 = s_entry[i + 2], v3 = s_entry[i + 3];
+                    less += v0 < e[k] ? 1 : 0;
+                    less += v1 < e[k] ? 1 : 0;
+                    less += v2 < e[k] ? 1 : 0;
+                    less += v3 < e[k] ? 1 : 0;
+                }
             else
                 for (int i = lo; i < hi; i += 4) {
                     const uint64_t v0 = s_entry[i], v1 = s_entry[i + 1], v2 = s_entry[i + 2], v3 = s_entry[i + 3];
@@ -1176,12 +1198,12 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                     less += v2 < e[k] && i + 2 < hi ? 1 : 0;
                     less += v3 < e[k] && i + 3 < hi ? 1 : 0;
                 }
-            rank[k] = (uint32_t)(lo + less);
+            part[k] = (uint32_t)(lo + less);
         }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++)
-        if (k * CT + tid < n) s_entry[rank[k]] = e[k];
+        if (k * CT + tid < n) s_entry[part[k]] = e[k];
     __syncthreads();
     if (__builtin_expect(n_long > 0, 0)) {
         if (tid < n_long) s_bounds[tid] = (uint32_t)part_start(s_long[tid]) | (uint32_t)part_start(s_long[tid] + 1u) << 16;
@@ -1215,7 +1237,7 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
                     continue;
                 }
                 const uint32_t key = ((end[q] & (uint32_t)((1ull << down) - 1ull)) >> f.key_drop);  // inside the bucket
-                const uint32_t p = (in << fine) + (key >> (in_bucket - fine));
+                const uint32_t p = part_of((int)in, key);
                 auto below = [&](int i) { return ((uint32_t)(s_entry[i] >> low_bits) & key_mask) < key; };
                 int at = part_start(p), to = part_start(p + 1);
                 while (to - at > 8) {
@@ -1234,7 +1256,7 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
         if (k * CT >= n) break;
         const uint64_t v = j < n ? s_entry[j] : 0ull;
         const uint64_t before = j > 0 && j < n ? s_entry[j - 1] : 0ull;
-        const uint64_t m = __ballot(j < n && (v >> f.pos_bits) != (before >> f.pos_bits));
+        const uint64_t m = __ballot(j < n && (v ^ before) >> f.pos_bits != 0);
         if (lane < 2 && (uint32_t)(m >> (32 * lane))) atomicOr(&s_first[(j >> 6) * 2 + lane], (uint32_t)(m >> (32 * lane)));
         pos_k[k] = (uint32_t)(v & ((1ull << f.pos_bits) - 1ull));
         if (tok1 && j < n) {
@@ -1282,6 +1304,10 @@ __global__ __launch_bounds__(CT, 6) void k_code_sort(const uint64_t *__restrict_
     // Long groups (the entries of a group share their part): the whole workgroup splits them as split_group
     // does, until what is left of them is short enough for a wave.  What has agreed on D tokens falls
     // apart into single entries in the order that they have.
+    // (where the counts were, which nothing needs any more)
+    uint64_t (*s_class)[SORT_CAP / 64] = reinterpret_cast<uint64_t (*)[SORT_CAP / 64]>(s_area);  // [2]: of a long group: entries below and at the middle one
+    uint32_t *s_before = s_area + 4 * (SORT_CAP / 64);                                           // [SD_WAVE + 1]
+    static_assert(SORT_PARTS / 2 >= 4 * (SORT_CAP / 64) + SD_WAVE + 1 && SORT_CAP <= SD_WAVE * SD_WAVE, "");
     if (__builtin_expect(n_long > 0, 0)) {
         for (int i = 0; i < n_long; i++) {
             const uint32_t b = s_bounds[i];
@@ -1757,17 +1783,15 @@ split_plan plan_for(int64_t N) {
     p.small_tiles = N <= SMALL_MAX;
     return p;
 }
-// Entries per workgroup of k_code_sort, three of which fit a compute unit: as many whole rounds of
-// workgroups as N makes at SORT_TILE_MIN, rounded down (2.2M entries: one round instead of 1.4).  What is
+// Entries per workgroup of k_code_sort, four of which fit a compute unit: as many whole rounds of
+// workgroups as N makes at SORT_TILE_MIN, rounded down.  What is
 // less than a round is spread over all of it, down to SORT_TILE_FEW entries, 32 to a wave, or two buckets
 // (32k, 100k and 300k entries: 28.4, 24.8 and 28.4 us in tiles of 2048 and buckets of 256 to 512; 13.8, 15.6 and 20.8 so).
 // SORT_ROUNDS rounds and more of larger tiles go in these, as few as that makes, with room behind a tile for a last bucket
-// of twice the average (100M copied entries: 2.92 ms in tiles of 2099, 2.72 in 3256; 10M, four rounds of 3255 instead of six
-// of 2170: a build of independent tokens 272 -> 265 us, of copied ones 403 -> 408, for what the last round waits for).
-// Eight rounds are 18M positions on this chip.  Builds of 18.5M, 24M and 40M copied tokens 765, 967 and 1555 us in the smaller
-// tiles, 746, 949 and 1542 in the larger ones; of independent tokens 474, 623 and 995; 467, 594 and 950.
+// of twice the average (builds of 2.6M, 8M and 14M copied tokens in three rounds of larger tiles from nine million positions on or from 19 million:
+// 148, 315 and 506 us; 150, 319 and 515; of independent tokens 185 and 288; 188 and 293 at 8M and 14M).
 int sort_tile_for(int64_t N, int n_cu) {
-    int64_t slots = (int64_t)3 * (n_cu > 0 ? n_cu : 1);
+    int64_t slots = (int64_t)4 * (n_cu > 0 ? n_cu : 1);
     if (slots > SORT_SLOTS) slots = SORT_SLOTS;
     const split_plan p = plan_for(N);
     const int64_t average = N >> (p.bits1 + p.bits2);
@@ -1776,8 +1800,9 @@ int sort_tile_for(int64_t N, int n_cu) {
     int64_t rounds = (N + slots * most - 1) / (slots * most);
     if (rounds < SORT_ROUNDS) {
         most = SORT_TILE_MAX;
+        const int64_t least = (N + slots * most - 1) / (slots * most);
         rounds = N / (slots * SORT_TILE_MIN);
-        if (rounds < 1) rounds = 1;
+        if (rounds < least) rounds = least;
     }
     int64_t t = (N + rounds * slots - 1) / (rounds * slots);
     if (t < 2 * average) t = 2 * average;
@@ -1948,11 +1973,11 @@ static sort_tables tables_for(const sd_ctx *c, int64_t N) {
     t.cuts = reinterpret_cast<sort_cut *>(t.bounds + t.tiles + 1);
     t.lasts = reinterpret_cast<sort_range *>(t.cuts + t.tiles);
     t.n_lasts = reinterpret_cast<uint32_t *>(t.lasts + t.tiles);
-    t.taken = t.tiles / 4 < 16 ? 16 : t.tiles / 4;
+    t.taken = t.tiles / 5 < 16 ? 16 : t.tiles / 5;
     return t;
 }
 
-// The tiles and the first of the last buckets that are kept apart (workgroups for a quarter as many as there are tiles:
+// The tiles and the first of the last buckets that are kept apart (workgroups for a fifth as many as there are tiles:
 // one that finds nothing is over at once; builds of 3M to 40M tokens by no more than runs differ), or n last buckets behind those.
 static void sort_ranges(sd_ctx *c, const uint64_t *entries, int64_t N, const sort_tables &t, int n, entry_shape f,
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
