@@ -1002,7 +1002,8 @@ __device__ __forceinline__ void network_sort(uint64_t *x, int m, int t, int n_t,
     }
 }
 
-template <int R>
+// ONE: after one split (a kernel of its own, for what an entry of such a split needs done costs the others a tenth of their instructions).
+template <int R, bool ONE>
 __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict__ in, split_rows split, const sort_pieces *__restrict__ pieces,
                                                   const uint32_t *__restrict__ starts,
                                                   const sort_bound *__restrict__ bounds,
@@ -1055,8 +1056,7 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
     if (tid == 0) s_n_long = s_n_todo = 0;
     const int n = (int)(z - a);
     const uint32_t start = tid <= nb ? starts[b0 + tid] : 0u;
-    const bool one = f.one_split();
-    const bool named = nb <= 1 << f.bits2;  // the entries have so many of their buckets' last bits that these tell them apart
+    const bool named = ONE || nb <= 1 << f.bits2;  // the entries have so many of their buckets' last bits that these tell them apart
     uint64_t e[SORT_ITEMS];
     uint32_t lo_of[SORT_ITEMS];  // one split: its tile's first position; entries that lack their bin: their bin's first bucket
     {
@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
     const uint32_t key_mask = (uint32_t)((1ull << in_bucket) - 1ull);
     // (A bucket is looked up in the entry, and parts are counted four entries at a time: 10M independent
     // tokens 90.8 -> 86.7 us, copied ones as before.)
-    const int code_at = one ? TILE_POS_BITS + f.tok_bits : low_bits;
+    const int code_at = ONE ? TILE_POS_BITS + f.tok_bits : low_bits;
     uint32_t part[SORT_ITEMS];  // and, from bit 16 on, the place in it
     static_assert(SORT_CAP <= 1 << 16 && SORT_PARTS <= 1 << 16, "");
 #pragma unroll
@@ -1131,7 +1131,7 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
             const int last = (int)(code >> in_bucket) & ((1 << f.bits2) - 1);  // the bucket's last bits
             const int lo = named ? (last - b0) & ((1 << f.bits2) - 1) : (int)lo_of[k] + last;
             const uint32_t p = part_of(lo, code & key_mask), sh = (p & 1u) * 16u;
-            if (one) e[k] = (e[k] >> TILE_POS_BITS) << f.pos_bits | (lo_of[k] + ((uint32_t)e[k] & (uint32_t)(KEY_ROUND - 1)));  // (the bucket's bits may leave)
+            if (ONE) e[k] = (e[k] >> TILE_POS_BITS) << f.pos_bits | (lo_of[k] + ((uint32_t)e[k] & (uint32_t)(KEY_ROUND - 1)));  // (the bucket's bits may leave)
             part[k] = p | ((atomicAdd(&cnt[p >> 1], 1u << sh) >> sh) & 0xffffu) << 16;
         }
     }
@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
     __syncthreads();
     const int n_long = s_n_long;
     // Where all buckets are of one bin, entries of later parts are no less: what is read beyond a part needs no looking at its end.
-    const bool rising = !one && (b0 ^ ((int)range.end - 1)) >> f.bits2 == 0;
+    const bool rising = !ONE && (b0 ^ ((int)range.end - 1)) >> f.bits2 == 0;
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++)
         if (k * CT + tid < n) {
@@ -1250,6 +1250,9 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
         }
     }
     uint32_t pos_k[SORT_ITEMS];
+    int32_t *tok1_here = tok1 + a, *samples_here = samples + ((a + tid) >> 4);
+    const bool sampled = ((a + tid) & 15) == 0;
+    static_assert(CT % 16 == 0, "");
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; k++) {
         const int j = k * CT + tid;
@@ -1261,8 +1264,8 @@ __global__ __launch_bounds__(CT, 8) void k_code_sort(const uint64_t *__restrict_
         pos_k[k] = (uint32_t)(v & ((1ull << f.pos_bits) - 1ull));
         if (tok1 && j < n) {
             const int32_t second = (int32_t)((uint32_t)(v >> f.pos_bits) & ((1u << f.tok_bits) - 1u)) - 1;
-            tok1[a + j] = second;
-            if (((a + j) & 15) == 0) samples[(a + j) >> 4] = second;
+            tok1_here[j] = second;
+            if (sampled) samples_here[k * (CT / 16)] = second;
         }
     }
     __syncthreads();
@@ -1983,7 +1986,8 @@ static void sort_ranges(sd_ctx *c, const uint64_t *entries, int64_t N, const sor
                         int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int bits = line_bits(c->cfg.vocab), R = line_words(bits) / 4;
     const packed_text packed = {line_room(c), bits, 128 * R / bits};
-    SD_LAUNCH(c, SD_K_CODE_SORT, st, (R == 3 ? k_code_sort<3> : R == 2 ? k_code_sort<2> : k_code_sort<1>),
+    SD_LAUNCH(c, SD_K_CODE_SORT, st, (f.one_split() ? (R == 3 ? k_code_sort<3, true> : R == 2 ? k_code_sort<2, true> : k_code_sort<1, true>)
+                                                 : (R == 3 ? k_code_sort<3, false> : R == 2 ? k_code_sort<2, false> : k_code_sort<1, false>)),
               dim3((unsigned)(n ? n : t.tiles + t.taken)), dim3(CT), 0, entries,
               split_tables_for(c, N, f).last, t.pieces, c->b_starts, t.bounds, t.cuts, t.lasts, t.n_lasts, n ? 0 : t.tiles,
               n ? t.taken : 0, f, packed, c->cfg.D, c->code_cdf, c->cfg.vocab + 1, sa, tok1, c->g_tok1s, bucket);
