@@ -16,7 +16,8 @@ struct sd_plan {
 
 // requests: of the launch, one workgroup each; lds_cu: LDS of a compute unit; lds_dyn_max: the most dynamic LDS
 // that a launch may ask for; lds_static: what the kernel holds besides; lds_wave: a wave's frontier, trees and
-// staging; lds_least: what the occurrence sort needs whatever the waves do.
+// staging; lds_least: what the occurrence sort needs whatever the waves do; lds_most: what it can use, of LDS that would
+// lie idle (where all workgroups of a compute unit are resident).
 //
 // One workgroup per compute unit takes the 16 waves a workgroup can have; two share SD_PLAN_OCC waves per
 // SIMD between them (12 each: the kernel's registers leave room for 6 per SIMD); three and four get 8
@@ -34,14 +35,15 @@ struct sd_plan {
 //   180 nodes  1000            3 x 3  41.9    2 x 4  36.9     4096   3 x 3   111    2 x 4  99.1
 //   256 nodes   700            2 x 3  57.5    4 x 2  48.0     4096   2 x 3   152    4 x 2   167
 inline sd_plan sd_plan_waves(int requests, int n_cu, size_t lds_cu, size_t lds_dyn_max, size_t lds_static,
-                             size_t lds_wave, size_t lds_least) {
+                             size_t lds_wave, size_t lds_least, size_t lds_most = 0) {
     const int per_cu = (requests + n_cu - 1) / n_cu;
     int most = per_cu <= 2 ? 4 * SD_PLAN_OCC / per_cu : per_cu == 3 ? 8 : per_cu == 4 ? 6 : per_cu <= 8 ? 5 : 4;
     if (most > 16) most = 16;
     int r = per_cu < SD_PLAN_RESIDENT ? per_cu : SD_PLAN_RESIDENT, fit = 0;
+    size_t dyn = 0;
     for (;; r--) {  // the waves of a workgroup if r of them are to be resident
         const size_t share = lds_cu / (size_t)r / SD_LDS_PIECE * SD_LDS_PIECE;
-        size_t dyn = share > lds_static ? share - lds_static : 0;
+        dyn = share > lds_static ? share - lds_static : 0;
         if (dyn > lds_dyn_max) dyn = lds_dyn_max;
         fit = dyn >= lds_least ? (int)(dyn / lds_wave) : 0;
         if (r == 1 || (fit >= 2 && (per_cu > 8 || fit * r >= 8))) break;
@@ -51,5 +53,6 @@ inline sd_plan sd_plan_waves(int requests, int n_cu, size_t lds_cu, size_t lds_d
     p.resident = r;
     p.lds = (size_t)p.waves * lds_wave;
     if (p.lds < lds_least) p.lds = lds_least;
+    if (r == per_cu && p.lds < lds_most) p.lds = lds_most < dyn ? lds_most : dyn;
     return p;
 }

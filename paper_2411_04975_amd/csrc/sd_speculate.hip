@@ -936,9 +936,12 @@ __device__ __forceinline__ bool key_better(const Key &a, const Key &b) {
     return a.par < b.par;
 }
 
+// (Parents, plus one, and depths are bytes, nodes being 256 and D 255 at most: with 60 bytes a node a launch of many requests with trees of 64 nodes
+// had five workgroups of four waves on a compute unit; 48 make that six.)
 struct Frontier {
     double *score;
-    int32_t *tok, *par, *lo, *hi, *dep;
+    int32_t *tok, *lo, *hi;
+    uint8_t *par1, *dep;
     int n, cap;
 };
 
@@ -953,7 +956,7 @@ __device__ __forceinline__ Key frontier_pick(const Frontier &f, bool want_best) 
     if (f.n <= PICK_SCAN_MAX) {  // a handful of entries: every lane scans them all (broadcast reads)
         for (int i = 0; i < f.n; i++) {
             Key k;
-            k.s = f.score[i]; k.tok = f.tok[i]; k.par = f.par[i]; k.idx = i;
+            k.s = f.score[i]; k.tok = f.tok[i]; k.par = (int32_t)f.par1[i] - 1; k.idx = i;
             if (mine.idx < 0 || (want_best ? key_better(k, mine) : key_better(mine, k))) mine = k;
         }
         mine.s = uni(mine.s); mine.tok = uni(mine.tok); mine.par = uni(mine.par);
@@ -962,7 +965,7 @@ __device__ __forceinline__ Key frontier_pick(const Frontier &f, bool want_best) 
     }
     for (int i = lane; i < f.n; i += 64) {
         Key k;
-        k.s = f.score[i]; k.tok = f.tok[i]; k.par = f.par[i]; k.idx = i;
+        k.s = f.score[i]; k.tok = f.tok[i]; k.par = (int32_t)f.par1[i] - 1; k.idx = i;
         if (mine.idx < 0 || (want_best ? key_better(k, mine) : key_better(mine, k))) mine = k;
     }
     const bool valid = mine.idx >= 0;
@@ -1021,7 +1024,7 @@ __device__ __forceinline__ Taken frontier_take(const Frontier &f) {
     const bool valid = lane < f.n;
     const int li = valid ? lane : 0;
     const double ms = f.score[li];
-    const int32_t mtok = f.tok[li], mpar = f.par[li], mlo = f.lo[li], mhi = f.hi[li], mdep = f.dep[li];
+    const int32_t mtok = f.tok[li], mpar = (int32_t)f.par1[li] - 1, mlo = f.lo[li], mhi = f.hi[li], mdep = f.dep[li];
     const double ninf = -__longlong_as_double(0x7ff0000000000000ll);
     const double sx = wave_max_f64(valid ? ms : ninf);
     uint64_t T = __ballot(valid && ms == sx);
@@ -1054,7 +1057,7 @@ __device__ __forceinline__ void frontier_close(Frontier &f, int hole) {
     if (hole < 0) return;
     const int last = f.n - 1;
     if (hole != last && (threadIdx.x & 63) == 0) {
-        f.score[hole] = f.score[last]; f.tok[hole] = f.tok[last]; f.par[hole] = f.par[last];
+        f.score[hole] = f.score[last]; f.tok[hole] = f.tok[last]; f.par1[hole] = f.par1[last];
         f.lo[hole] = f.lo[last]; f.hi[hole] = f.hi[last]; f.dep[hole] = f.dep[last];
     }
     f.n = last;
@@ -1079,8 +1082,8 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
         if (cand) {
             int j = __popcll(C & lanemask_lt());
             int s = hole >= 0 ? (j == 0 ? hole : f.n + j - 1) : f.n + j;
-            f.score[s] = sc; f.tok[s] = tok; f.par[s] = par; f.lo[s] = lo; f.hi[s] = hi;
-            f.dep[s] = dep;
+            f.score[s] = sc; f.tok[s] = tok; f.par1[s] = (uint8_t)(par + 1); f.lo[s] = lo; f.hi[s] = hi;
+            f.dep[s] = (uint8_t)dep;
         }
         f.n = stay + nc;
         wsync();
@@ -1105,8 +1108,8 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
         if (f.n == 0) {
             const int s = __popcll(C & lanemask_lt());
             if (lane_in(C)) {
-                f.score[s] = sc; f.tok[s] = tok; f.par[s] = par; f.lo[s] = lo; f.hi[s] = hi;
-                f.dep[s] = dep;
+                f.score[s] = sc; f.tok[s] = tok; f.par1[s] = (uint8_t)(par + 1); f.lo[s] = lo; f.hi[s] = hi;
+                f.dep[s] = (uint8_t)dep;
             }
             f.n = f.cap;
             C = 0;
@@ -1127,8 +1130,8 @@ __device__ __forceinline__ void frontier_put(Frontier &f, int hole, bool cand, d
             if (key_better(nk, worst)) s = worst.idx;
         }
         if (s >= 0 && lane == 0) {
-            f.score[s] = nk.s; f.tok[s] = nk.tok; f.par[s] = nk.par; f.lo[s] = nlo; f.hi[s] = nhi;
-            f.dep[s] = ndep;
+            f.score[s] = nk.s; f.tok[s] = nk.tok; f.par1[s] = (uint8_t)(nk.par + 1); f.lo[s] = nlo; f.hi[s] = nhi;
+            f.dep[s] = (uint8_t)ndep;
         }
         wsync();
     }
@@ -1141,8 +1144,8 @@ constexpr int FILL_U = TC_TOKENS / 64;  // loads per lane that fill all the wind
 constexpr int MED_MAX = 256;  // widest node whose suffixes are all read (a multiple of 64)
 
 struct Stage {
-    int32_t *pos, *base, *tc;  // LDS: [64], [64], [TC_TOKENS]
-    int32_t *tmp;              // LDS: [64] scratch of the searches in wide nodes
+    int32_t *pos, *tc;   // LDS: [64], [TC_TOKENS]
+    int32_t *tmp, *base; // LDS: [64] scratch of the searches in wide nodes, and, in the same place once these are over, what grow_narrow starts from
 };
 
 // Children of the node [lo, hi) at depth d (its path has d tokens), as frontier candidates with
@@ -1826,7 +1829,7 @@ struct Narrow {
 template <bool STATS, bool TICKS>
 __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, Stage &sg,
                                            const int32_t *__restrict__ text, const Narrow &g, bool windows, int m, int pl, int K,
-                                           int n, int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
+                                           int n, int32_t *t_tok, uint8_t *t_par1, double *t_score, double &total,
                                            bool &deepest, uint64_t tick0, uint32_t &tick_root,
                                            uint32_t &tick_merge, unsigned &nb) {
     const int lane = threadIdx.x & 63;
@@ -1996,7 +1999,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
             const int e = run_end(lo, hi), L = e - r < K - n ? e - r : K - n;
             if (lane < L) {
                 t_tok[n + lane] = tk;
-                t_par[n + lane] = lane == 0 ? par : n + lane - 1;
+                t_par1[n + lane] = (uint8_t)(lane == 0 ? par + 1 : n + lane);
                 t_score[n + lane] = s;
             }
             tot = add_times(tot, s, L);
@@ -2050,7 +2053,7 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
                 const int32_t par = __builtin_amdgcn_readlane(f_par, w);
                 if (lane < len) {
                     t_tok[n + lane] = (int32_t)tk;
-                    t_par[n + lane] = lane == 0 ? par : n + lane - 1;
+                    t_par1[n + lane] = (uint8_t)(lane == 0 ? par + 1 : n + lane);
                     t_score[n + lane] = s;
                 }
                 n += len;
@@ -2094,13 +2097,13 @@ __device__ __forceinline__ int grow_narrow(const SpecParams &p, WgShared &sh, St
 }
 
 // One unit (request b, index src: 0 global / 1 request, pattern length pl) on one wavefront:
-// ExpandSpeculationTree below the matched node into the LDS tree (t_tok, t_par, t_score).
+// ExpandSpeculationTree below the matched node into the LDS tree (t_tok, t_par1: parents plus one, t_score).
 // Returns the number of draft nodes and leaves their SCORE in `total`; `deepest` tells whether
 // a node of depth D (which may have no children) was taken.
 template <bool STATS, bool TICKS>
 __device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b, int t,
                         const int32_t *__restrict__ x, int src, int pl, int usa_off, Frontier &f, Stage &sg,
-                        int32_t *t_tok, int32_t *t_par, double *t_score, double &total,
+                        int32_t *t_tok, uint8_t *t_par1, double *t_score, double &total,
                         bool &deepest, unsigned &nb) {
     const int lane = threadIdx.x & 63;
     deepest = false;
@@ -2239,7 +2242,7 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b
                 }
                 if (tk0.dep >= p.D) deepest = true;
                 if (lane == 0) {
-                    t_tok[n] = best.tok; t_par[n] = best.par; t_score[n] = best.s;
+                    t_tok[n] = best.tok; t_par1[n] = (uint8_t)(best.par + 1); t_score[n] = best.s;
                 }
                 total += best.s;
                 const int cur = n++;
@@ -2266,7 +2269,7 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b
                 const int first = 63 - __builtin_clzll(g.heads & ((2ull << lane) - 1ull));  // (lane 0 is one)
                 const int32_t mine = __shfl(e, first);
                 g.score = f.score[mine];
-                g.par = f.par[mine];
+                g.par = (int32_t)f.par1[mine] - 1;
                 g.count = f.hi[mine] - f.lo[mine];
                 g.next = f.dep[mine] - pl - 1;
                 if (lane < slots) {
@@ -2278,7 +2281,7 @@ __device__ __forceinline__ int run_unit(const SpecParams &p, WgShared &sh, int b
         }
         if (slots > 0) {
             wsync();
-            n = grow_narrow<STATS, TICKS>(p, sh, sg, text, g, windows, slots, pl, K, n, t_tok, t_par, t_score, total, deepest,
+            n = grow_narrow<STATS, TICKS>(p, sh, sg, text, g, windows, slots, pl, K, n, t_tok, t_par1, t_score, total, deepest,
                                           tick0, tick_root, tick_setup, nb);
         }
     }
@@ -2829,17 +2832,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     const uint64_t wg1 = TICKS ? wall_clock64() : 0;
     args_again();
 
-    // per-wave LDS: frontier (score, tok, par, lo, hi, dep), two trees (score, tok, par), staging
+    // per-wave LDS: frontier (score, tok, lo, hi, par, dep), two trees (score, tok, par), staging
     const int cap = args->p.max_nodes;
     Frontier f;
     f.score = smem + (size_t)wave * (args->lds_per_wave / 8);
     double *const tsc0 = f.score + cap, *const tsc1 = tsc0 + cap;
     f.tok = (int32_t *)(tsc1 + cap);
-    f.par = f.tok + cap; f.lo = f.par + cap; f.hi = f.lo + cap; f.dep = f.hi + cap;
-    int32_t *const ttk0 = f.dep + cap, *const tpr0 = ttk0 + cap;
-    int32_t *const ttk1 = tpr0 + cap, *const tpr1 = ttk1 + cap;
+    f.lo = f.tok + cap; f.hi = f.lo + cap;
+    int32_t *const ttk0 = f.hi + cap, *const ttk1 = ttk0 + cap;
     Stage sg;
-    sg.pos = tpr1 + cap; sg.base = sg.pos + 64; sg.tc = sg.base + 64; sg.tmp = sg.tc + TC_TOKENS;
+    sg.pos = ttk1 + cap; sg.tc = sg.pos + 64; sg.tmp = sg.tc + TC_TOKENS; sg.base = sg.tmp;
+    f.par1 = reinterpret_cast<uint8_t *>(sg.tmp + 64); f.dep = f.par1 + cap;
+    uint8_t *const tpr0 = f.dep + cap, *const tpr1 = tpr0 + cap;
     f.n = 0; f.cap = 0;
 
     // Pattern lengths with the same number of occurrences in an index have the same
@@ -3037,13 +3041,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         if (wave == (ww < 0 ? 0 : ww)) {
             const int n = ww < 0 ? 0 : best_n;
             const int kept = cur ^ 1;  // the buffer the wave's best tree was left in
-            const int32_t *btk = kept ? ttk1 : ttk0, *bpr = kept ? tpr1 : tpr0;
+            const int32_t *btk = kept ? ttk1 : ttk0;
+            const uint8_t *bpr = kept ? tpr1 : tpr0;
             const double *bsc = kept ? tsc1 : tsc0;
             const int64_t ob = (int64_t)b * args->out.max_nodes;
             for (int i = lane_e; i < args->out.max_nodes; i += 64) {
                 const bool live = i < n;
                 args->out.d_tokens[ob + i] = live ? btk[i] : -1;
-                args->out.d_parents[ob + i] = live ? bpr[i] : -1;
+                args->out.d_parents[ob + i] = live ? (int32_t)bpr[i] - 1 : -1;
                 args->out.d_scores[ob + i] = live ? bsc[i] : 0.0;
                 SD_CNT(16);
             }
@@ -3126,14 +3131,14 @@ sd_status launch_speculate(sd_ctx *c, const int32_t *d_slot_ids, int32_t batch, 
     // (the timing variant indexes its marks by request: only calls that the buffers have room for)
     const bool stats = c->prof_mode == 2, ticks = c->prof_mode == 3 && batch <= c->tick_slots;
     // per wave: frontier 6 arrays, two trees of 3 arrays, staging
-    size_t lds_wave = (size_t)c->max_nodes * (3 * sizeof(double) + 9 * sizeof(int32_t)) +
-                      (64 + 64 + TC_TOKENS + 64) * sizeof(int32_t);
+    size_t lds_wave = (size_t)c->max_nodes * (3 * sizeof(double) + 5 * sizeof(int32_t) + 4 * sizeof(uint8_t)) +
+                      (64 + TC_TOKENS + 64) * sizeof(int32_t);
     lds_wave = (lds_wave + 7) / 8 * 8;
     // the occurrence sort keeps up to OCC_LDS_SORT records and their keys in the same LDS
     // before the waves take it over: as many as fit, and room for at least half of that
     const size_t rec = sizeof(int2) + sizeof(uint64_t);
     const sd_plan plan = sd_plan_waves(batch, c->n_cu, c->lds_cu, c->lds_optin, sizeof(WgShared), lds_wave,
-                                       OCC_LDS_SORT / 2 * rec);
+                                       OCC_LDS_SORT / 2 * rec, OCC_LDS_SORT * rec);
     if (plan.waves < 1) return SD_ERR_CAPACITY;
     const int nw = plan.waves;
     const size_t lds = plan.lds;
