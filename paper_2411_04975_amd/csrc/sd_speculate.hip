@@ -3138,7 +3138,7 @@ sd_status launch_speculate(sd_ctx *c, const int32_t *d_slot_ids, int32_t batch, 
     // before the waves take it over: as many as fit, and room for at least half of that
     const size_t rec = sizeof(int2) + sizeof(uint64_t);
     const sd_plan plan = sd_plan_waves(batch, c->n_cu, c->lds_cu, c->lds_optin, sizeof(WgShared), lds_wave,
-                                       OCC_LDS_SORT / 2 * rec, OCC_LDS_SORT * rec);
+                                       OCC_LDS_SORT / 2 * rec, OCC_LDS_SORT * rec, 4 * SD_PLAN_OCC);
     if (plan.waves < 1) return SD_ERR_CAPACITY;
     const int nw = plan.waves;
     const size_t lds = plan.lds;

@@ -76,3 +76,39 @@ def test_the_launch_plans_with_the_lds_of_the_kernel():
     kernel = src[src.index("void k_speculate("):]
     kernel = kernel[:kernel.index("\n}\n")]
     assert re.findall(r"__shared__ ([^;]*);", kernel) == ["double smem[]", "WgShared sh"]
+
+
+def test_the_waves_that_are_resident():
+    """The launch's own call, with a node of 48 bytes: six workgroups of four waves and the kernel's registers, LDS that would lie idle for the
+    occurrence sort, and a launch that the device takes for every tree size."""
+    src = """
+#include <stdio.h>
+#include <initializer_list>
+#include "%s/sd_plan.h"
+int main() {
+    for (int nodes = 1; nodes <= 256; nodes++)
+        for (int q : {1, 256, 257, 512, 768, 769, 1024, 1025, 1280, 1281, 1536, 2048, 2049, 4096, 8192, 100000}) {
+            const size_t wave = (48 * (size_t)nodes + 4 * (2 * 64 + 256) + 7) / 8 * 8;
+            const sd_plan p = sd_plan_waves(q, %d, %d, %d - 8104 - 256, 8104, wave, %d, 2 * %d, 24);
+            printf("%%d %%d %%zu %%d %%d %%zu\\n", nodes, q, wave, p.waves, p.resident, p.lds);
+        }
+}
+""" % (CSRC, CUS, LDS, LDS, LEAST, LEAST)
+    import tempfile
+    with tempfile.TemporaryDirectory() as d:
+        path = os.path.join(d, "plan.cpp")
+        open(path, "w").write(src)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-o", os.path.join(d, "plan"), path], check=True)
+        out = subprocess.run([os.path.join(d, "plan")], capture_output=True, text=True, check=True).stdout
+    waves_at = {}
+    for nodes, q, wave, waves, resident, lds in (map(int, line.split()) for line in out.splitlines()):
+        at = (nodes, q, waves, resident, lds)
+        assert 1 <= waves <= 16 and resident >= 1 and lds >= LEAST and lds >= waves * wave, at
+        assert lds <= LDS - 8104 - 256, at
+        whole = -(-(lds + 8104) // PIECE) * PIECE
+        assert resident * whole <= LDS and resident <= -(-q // CUS), at
+        waves_at[nodes, q] = waves
+        if (nodes, q) == (64, 8192):
+            assert LDS // whole == 6
+    assert [waves_at[64, q] for q in (1024, 1025, 1280, 1281, 2048, 8192)] == [6, 5, 5, 4, 4, 4]
+    assert [waves_at[32, q] for q in (1024, 1025, 1280, 1281, 2048, 8192)] == [6, 4, 4, 4, 4, 4]
