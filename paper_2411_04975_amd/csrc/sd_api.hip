@@ -87,7 +87,7 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     const int64_t scan_n = c->b_hist_cap > cap ? c->b_hist_cap : cap;
     c->b_partials_cap = (scan_n + 4095) / 4096 + 1;
     int64_t code_hist, code_starts, code_sums, code_ranges, rest_to;
-    sd_code_room(cap, &code_hist, &code_starts, &code_sums, &code_ranges, &rest_to);
+    sd_code_room(cap, cfg->vocab, &code_hist, &code_starts, &code_sums, &code_ranges, &rest_to);
     if (code_hist > c->b_hist_cap) c->b_hist_cap = code_hist;
     c->b_hist_cap = (c->b_hist_cap + 15) / 16 * 16;  // (the small tables of the sort follow in the same allocation)
     bool ok = true;

@@ -108,7 +108,7 @@ struct sd_ctx {
 
 // ---- launchers implemented in the other translation units ---------------
 // suffix sorting by codes: room for its tables, intervals from a sample of the tokens, the sort
-void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
+void sd_code_room(int64_t cap, int32_t vocab, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
                   int64_t *range_words, int64_t *rest_words);
 bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_blocks(int32_t vocab); // words of code_blocks

@@ -1766,23 +1766,27 @@ __global__ __launch_bounds__(CT) void k_rest_bucket(const rest_range *__restrict
 // Up to ONE_SPLIT_MAX positions k_layout's split is the only one, which then is as fine as 10 bits allow, down to
 // buckets of 32 to 64: the shares can be as small.  (A workgroup of k_code_ranges and one of the sort then look at all tiles' rows: builds of
 // 140k, 262k, 400k and 500k tokens 52, 60, 71 and 77 us in one split, 63, 66, 73 and 75 in two; with one split by counts, places
-// and moves, two launches more: 59 to 62, -, -, 75.)
+// and moves, two launches more: 59 to 62, -, -, 75.  Prefix doubling, where the entries of two splits have no room, takes several times that.)
 // Tiles of 6144 entries leave as runs of 12 entries per bin and more; inputs up to SMALL_MAX take tiles of
 // 2048, which are spread over more compute units (2.2M and 3.9M, codes and split apart: 22 + 13 and 30 + 22 us in tiles
 // of 6144; 20 + 13 and 28 + 17 so).
 constexpr int64_t SMALL_MAX = 4 << 20, ONE_SPLIT_MAX = 224 * KEY_ROUND;
-static_assert(ONE_SPLIT_MAX <= (int64_t)CT * KEY_ROUND, "a thread to a tile");
+static_assert(ONE_SPLIT_MAX <= (512ll << MAX_BITS) && (513ll << MAX_BITS) <= (int64_t)CT * KEY_ROUND, "a thread to a tile");
 struct split_plan {
     int bits1, bits2;
     bool small_tiles;
 };
-split_plan plan_for(int64_t N) {
+int pos_bits_for(int64_t N) { return sd_bits_for((uint64_t)(N - 1)); }
+split_plan plan_for(int64_t N, int tok_bits) {
     int bits = 2;  // (four bins to a lane)
     while (bits < MAX_BITS && (N >> bits) > 64) bits++;
     while (bits < 2 * MAX_BITS && (N >> bits) > 512) bits++;
     split_plan p;
-    if (N > ONE_SPLIT_MAX) { p.bits1 = (bits + 1) / 2; p.bits2 = bits / 2; }
-    else { p.bits1 = 0; p.bits2 = bits; }
+    p.bits1 = (bits + 1) / 2;
+    p.bits2 = bits / 2;
+    // (what the first of two splits leaves of a code has no room beside positions and tokens of 43 bits and more, and 1024 ways are enough)
+    const bool no_room = bits == MAX_BITS && 32 - p.bits1 - CDF_QUANTUM > 64 - pos_bits_for(N) - tok_bits;
+    if (N <= ONE_SPLIT_MAX || no_room) { p.bits1 = 0; p.bits2 = bits; }
     p.small_tiles = N <= SMALL_MAX;
     return p;
 }
@@ -1793,10 +1797,9 @@ split_plan plan_for(int64_t N) {
 // SORT_ROUNDS rounds and more of larger tiles go in these, as few as that makes, with room behind a tile for a last bucket
 // of twice the average (builds of 2.6M, 8M and 14M copied tokens in three rounds of larger tiles from nine million positions on or from 19 million:
 // 148, 315 and 506 us; 150, 319 and 515; of independent tokens 185 and 288; 188 and 293 at 8M and 14M).
-int sort_tile_for(int64_t N, int n_cu) {
+int sort_tile_for(int64_t N, const split_plan &p, int n_cu) {
     int64_t slots = (int64_t)4 * (n_cu > 0 ? n_cu : 1);
     if (slots > SORT_SLOTS) slots = SORT_SLOTS;
-    const split_plan p = plan_for(N);
     const int64_t average = N >> (p.bits1 + p.bits2);
     int64_t most = SORT_CAP - 2 * average;
     most = most > SORT_TILE_MANY ? SORT_TILE_MANY : most < SORT_TILE_MIN ? SORT_TILE_MIN : most;
@@ -1819,13 +1822,13 @@ int64_t layout_tile(const split_plan &p) { return (int64_t)KEY_ROUND * (p.small_
 
 // Room that the tables of an input of up to `cap` positions take: words of b_hist, b_starts (and of
 // rest_table), code_sums, b_ranges and rest_to.
-void sd_code_room(int64_t cap, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
+void sd_code_room(int64_t cap, int32_t vocab, int64_t *hist_words, int64_t *start_words, int64_t *sum_words,
                   int64_t *range_words, int64_t *rest_words) {
     int64_t h = 0, s = 0;
-    const int64_t sizes[] = {cap, SMALL_MAX, ONE_SPLIT_MAX};
+    const int64_t sizes[] = {cap, SMALL_MAX, (513ll << MAX_BITS) - 1, ONE_SPLIT_MAX};
     for (int64_t n : sizes) {
         if (n > cap) n = cap;
-        const split_plan p = plan_for(n);
+        const split_plan p = plan_for(n, sd_bits_for((uint64_t)vocab));
         const int64_t tile = layout_tile(p), ntiles = (n + tile - 1) / tile;
         const int64_t tiles = p.bits1 ? n / SPLIT2_TILE + (1ll << p.bits1) : 0;
         const int64_t x = (ntiles << (p.bits1 ? p.bits1 : p.bits2)) / 2 + (tiles << p.bits2) / 2 + (1ll << p.bits1) + tiles * (int64_t)(sizeof(bin_tile) / 4) + 64;
@@ -1908,7 +1911,7 @@ static dim3 layout_grid(int64_t N, int64_t tile) { return dim3((unsigned)((N + S
 void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                int32_t *text, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
-    const split_plan p = plan_for(N);
+    const split_plan p = plan_for(N, sd_bits_for((uint64_t)c->cfg.vocab));
     SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (p.small_tiles ? k_layout<CT, SMALL_ROUNDS, TEXT_ONLY> : k_layout<CT, LARGE_ROUNDS, TEXT_ONLY>),
               layout_grid(N, layout_tile(p)), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text,
               c->cfg.vocab, c->d_err, (const uint32_t *)nullptr, (const uint32_t *)nullptr, 0, (uint32_t *)nullptr, entry_shape{}, (uint64_t *)nullptr, (uint16_t *)nullptr,
@@ -1917,11 +1920,11 @@ void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_
 
 // An entry's 64 bits: whether they hold what is needed of an input.
 static bool shape_for(int64_t N, int32_t vocab, entry_shape *f) {
-    const split_plan p = plan_for(N);
+    f->tok_bits = sd_bits_for((uint64_t)vocab);
+    f->pos_bits = pos_bits_for(N);
+    const split_plan p = plan_for(N, f->tok_bits);
     f->bits1 = p.bits1;
     f->bits2 = p.bits2;
-    f->pos_bits = sd_bits_for((uint64_t)(N - 1));
-    f->tok_bits = sd_bits_for((uint64_t)vocab);
     f->key_bits = 64 - (p.bits1 ? f->pos_bits : TILE_POS_BITS) - f->tok_bits;
     if (f->key_bits > 32 - p.bits1) f->key_bits = 32 - p.bits1;
     f->key_drop = 32 - p.bits1 - f->key_bits;
@@ -1945,7 +1948,7 @@ struct split_tables {
 static split_tables split_tables_for(const sd_ctx *c, int64_t N, const entry_shape &f) {
     auto up = [](int64_t words) { return (words + 3) / 4 * 4; };
     split_tables t;
-    const int64_t tile = layout_tile(plan_for(N));
+    const int64_t tile = layout_tile(plan_for(N, f.tok_bits));
     t.n_tiles = f.one_split() ? 0 : (int)(N / SPLIT2_TILE + (1ll << f.bits1));
     t.starts1 = c->b_hist;
     t.rows1 = reinterpret_cast<uint16_t *>(t.starts1 + up((1ll << f.bits1) + 1));
@@ -1968,7 +1971,7 @@ struct sort_tables {
 };
 static sort_tables tables_for(const sd_ctx *c, int64_t N) {
     sort_tables t;
-    t.tile = sort_tile_for(N, c->n_cu);
+    t.tile = sort_tile_for(N, plan_for(N, sd_bits_for((uint64_t)c->cfg.vocab)), c->n_cu);
     t.tiles = (int)((N + t.tile - 1) / t.tile);
     t.pieces = reinterpret_cast<sort_pieces *>(c->b_ranges);
     t.rest = reinterpret_cast<rest_range *>(t.pieces + t.tiles);
@@ -1996,9 +1999,11 @@ static void sort_ranges(sd_ctx *c, const uint64_t *entries, int64_t N, const sor
 // k_layout with codes, split into `entries` and rows1; entries = nullptr: the codes by position into `keys`, and no more.
 static void layout_codes(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens, int32_t *text, entry_shape f,
                          uint32_t *keys, uint64_t *entries, uint16_t *rows1, int per_chunk, uint32_t *n_lasts, hipStream_t st) {
-    const int64_t N = n_tokens + n_seq, tile = layout_tile(plan_for(N));
+    const int64_t N = n_tokens + n_seq;
+    const split_plan p = plan_for(N, f.tok_bits);
+    const int64_t tile = layout_tile(p);
     const bool by_block = sd_code_blocks(c->cfg.vocab) <= CDF_BLOCKS + 1;
-    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (plan_for(N).small_tiles ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT> : by_block ? k_layout<CT, LARGE_ROUNDS, CODES_BY_BLOCK> : k_layout<CT, LARGE_ROUNDS, CODES_DIRECT>),
+    SD_LAUNCH(c, SD_K_SORT_SCATTER, st, (p.small_tiles ? k_layout<CT, SMALL_ROUNDS, CODES_DIRECT> : by_block ? k_layout<CT, LARGE_ROUNDS, CODES_BY_BLOCK> : k_layout<CT, LARGE_ROUNDS, CODES_DIRECT>),
               layout_grid(N, tile), dim3(CT), 0, tokens, offs, n_seq, n_tokens, text, c->cfg.vocab, c->d_err, c->code_cdf, c->code_blocks,
               block_shift(c->cfg.vocab), keys, f, entries, rows1, entries ? (N + tile - 1) / tile : 0, per_chunk, c->code_sums, line_room(c), line_bits(c->cfg.vocab), n_lasts);
 }
@@ -2010,9 +2015,9 @@ static void layout_codes(sd_ctx *c, const int32_t *tokens, const int64_t *offs, 
 bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st) {
     const int64_t N = n_tokens + n_seq;
-    const split_plan p = plan_for(N);
     entry_shape f;
     (void)shape_for(N, c->cfg.vocab, &f);
+    const split_plan p = plan_for(N, f.tok_bits);
     const int bins1 = 1 << f.bits1, bins2 = 1 << f.bits2;
     const int64_t tile = layout_tile(p), ntiles = (N + tile - 1) / tile;
     uint64_t *ent1 = c->b_keys[0], *ent2 = c->b_keys[1];

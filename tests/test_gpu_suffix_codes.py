@@ -111,19 +111,26 @@ def test_insert_places(n_old, n_new, spread):
 
 
 @pytest.mark.parametrize("vocab", [900, 1 << 24])
-@pytest.mark.parametrize("n", [2048, 2049, 131_072, 131_073, 458_752, 458_753])
+@pytest.mark.parametrize("n", [2048, 2049, 131_072, 131_073, 458_752, 458_753, 525_311, 525_312])
 def test_pieces_of_tiles(n, vocab):
     """Around the sizes where the workgroups' shares come from one more tile: from a second one, from more than the
     64 that are listed for a workgroup, and from tiles of a second split; with codes of 25 bits too, which leave
-    no room for a position beside all of a suffix's code.  Runs of one token make buckets that are kept apart, whose
+    no room for a position beside all of a suffix's code: two splits of 2^10 bins leave them none, so one is taken as long as
+    it goes that far, and prefix doubling behind that.  Runs of one token make buckets that are kept apart, whose
     pieces the sort finds by itself."""
+    import paper_2411_04975_amd as sd
     rng = np.random.default_rng(n + vocab)
     D = 24
     docs = [_text(rng, n // 2, vocab, 4), np.full(min(n // 3, 5000), 7, np.int32)]
     docs.append(_text(rng, n - sum(len(d) for d in docs) - 3, vocab, 2))
     g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n)
     try:
+        sd.sd_debug_profile(g.ctx, 1)
+        sd.sd_debug_profile_read(g.ctx)
         g.build_global(docs)
+        made = sd.sd_debug_profile_read(g.ctx)
+        sd.sd_debug_profile(g.ctx, 0)
+        assert (made["code_sort"]["launches"] > 0) == (vocab < 1 << 24 or n <= 525_311)
         _check(g, docs, D)
     finally:
         g.close()
