@@ -2,11 +2,34 @@
 #include <math.h>
 #include <stdio.h>
 
+#include <chrono>
 #include <new>
 
 #include "sd_internal.h"
 
 void sd_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st);
+
+// The word is looked at for as long as the stream has work: all the time for the first two milliseconds, which most builds
+// take less than, and then between looks at the stream, which also says if a kernel never ran.
+bool sd_hear(const sd_ctx *c, uint32_t number, uint32_t *what, hipStream_t st) {
+    using clock = std::chrono::steady_clock;
+    auto heard = [&] {
+        const uint32_t v = __atomic_load_n(c->h_told + SD_TOLD, __ATOMIC_ACQUIRE);
+        *what = v & 1u;
+        return v >> 1 == number;
+    };
+    auto look = clock::now() + std::chrono::milliseconds(2);
+    for (uint32_t n = 1;; n++) {
+        if (heard()) return true;
+        __builtin_ia32_pause();
+        if (n % 64 || clock::now() < look) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess) return heard();
+        if (e != hipErrorNotReady) return false;
+        (void)hipGetLastError();  // (that it is not ready)
+        look = clock::now() + std::chrono::microseconds(100);
+    }
+}
 
 namespace {
 
@@ -36,7 +59,7 @@ void free_all(sd_ctx *c) {
                     c->d_round_flag, c->code_cdf, c->code_cnt, c->code_partials, c->b_starts, c->code_sums, c->code_bucket};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
-    if (c->h_flag) (void)hipHostFree(c->h_flag);
+    if (c->h_told) (void)hipHostFree(c->h_told);
     if (c->code_asked) (void)hipEventDestroy(c->code_asked);
     if (c->d_algo_bytes) (void)hipFree(c->d_algo_bytes);
     if (c->prof_ev) {
@@ -113,8 +136,9 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
          dev_alloc(&c->code_sums, code_sums, sb) &&
          dev_alloc(&c->code_bucket, (int64_t)cfg->vocab + 2, sb);
     if (ok) c->code_blocks = c->code_cdf + cfg->vocab + 2;
-    ok = ok && hipHostMalloc((void **)&c->h_flag, 8 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess &&
+    ok = ok && hipHostMalloc((void **)&c->h_told, SD_TOLD_WORDS * sizeof(uint32_t), hipHostMallocDefault) == hipSuccess &&
          hipEventCreateWithFlags(&c->code_asked, hipEventDisableTiming) == hipSuccess;
+    if (ok) memset(c->h_told, 0, SD_TOLD_WORDS * sizeof(uint32_t));
     ok = ok && dev_alloc(&c->r_text, B * c->r_stride, sb) && dev_alloc(&c->r_len, ((B + 31) / 32) * 32 + B * SD_CTR_STRIDE * 2, sb);
     ok = ok && dev_alloc(&c->s_occ, B * ctx, sb);
     ok = ok && dev_alloc(&c->s_unit_sa, B * ctx, sb);

@@ -504,16 +504,6 @@ inline unsigned nblk(int64_t n) { return (unsigned)((n + TB - 1) / TB); }
 
 }  // namespace
 
-// A stream that is being captured into a graph cannot be waited for.
-static bool stream_can_wait(hipStream_t st) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return cs == hipStreamCaptureStatusNone;
-}
-
 // Sorts the N positions of `text` (documents with an end marker after each, padding behind)
 // by their suffixes, compared on at least D tokens.  Returns which of b_vals[0/1] holds the
 // sorted positions (-1: a HIP call failed).
@@ -598,7 +588,6 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
         sd_layout(c, tokens, offs, n_seq, n_tokens, text, st);
         return SD_ERR_STATE;
     }
-    *c->h_flag = 0;
     const int64_t seen = old > N ? old : N;
     if (c->code_seen == 0 || seen >= 2 * c->code_seen || c->code_misfit) {
         if (old > N && !c->code_misfit)
@@ -608,10 +597,10 @@ static sd_status layout_and_sort(sd_ctx *c, const int32_t *tokens, const int64_t
         c->code_seen = seen;
         c->code_misfit = false;
     }
-    if (!sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st) ||
-        hipEventSynchronize(c->code_asked) != hipSuccess)  // (the sort is still running)
-        return SD_ERR_HIP;
-    c->code_misfit = *const_cast<volatile int32_t *>(c->h_flag) != 0;
+    const uint32_t number = sd_code_sort(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st);
+    uint32_t left = 0;
+    if (hipGetLastError() != hipSuccess || !sd_hear(c, number, &left, st)) return SD_ERR_HIP;  // (the sort is still running)
+    c->code_misfit = left != 0;
     if (c->code_misfit && sd_code_rest(c, tokens, offs, n_seq, n_tokens, text, sa, tok1, bucket, st) != SD_OK) return SD_ERR_HIP;
     return hipGetLastError() == hipSuccess ? SD_OK : SD_ERR_HIP;
 }

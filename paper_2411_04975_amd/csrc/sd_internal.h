@@ -12,6 +12,8 @@
 #define SD_TEXT_PAD 512      // sentinel tokens kept after the last real position of a text
 #define SD_END_TOKEN (-1)    // sentinel: sorts below every token and never matches one
 
+// words of sd_ctx::h_told: the number of the kernel that has told something (31 bits, and a bit of what it has told), what it has told besides
+enum { SD_TOLD = 0, SD_TOLD_SUMS = 8, SD_TOLD_WORDS = 16 };
 // sticky device-side error flags (indices into sd_ctx::d_err)
 enum { SD_DEVERR_TOKEN = 0, SD_DEVERR_SLOT = 1, SD_DEVERR_CTX = 2, SD_DEVERR_N = 4 };
 // device-side counters reported by sd_get_stats (indices into sd_ctx::d_counters, in the
@@ -73,8 +75,9 @@ struct sd_ctx {
     uint32_t *b_ranges = nullptr;       // what each workgroup of the sort in LDS takes
     uint32_t *rest_table = nullptr;     // by bucket: which of those that are sorted by prefix doubling
     uint32_t *rest_to = nullptr;        // by tile of positions: how many lie in those before it
-    hipEvent_t code_asked = nullptr;    // where h_flag is known
-    int32_t *h_flag = nullptr;          // pinned, 8 words: what the sort in LDS leaves to be done
+    hipEvent_t code_asked = nullptr;    // where the words of h_told behind the first one are known
+    uint32_t *h_told = nullptr;         // pinned, SD_TOLD_WORDS: what kernels tell the host while others are running
+    uint32_t told_last = 0;             // number of the last kernel that was to tell something
 
     // ---- per-request contexts -----------------------------------------
     int32_t *r_text = nullptr;       // [max_batch_slots][r_stride], SD_END_TOKEN after the context
@@ -115,9 +118,9 @@ int64_t sd_code_blocks(int32_t vocab); // words of code_blocks
 int64_t sd_code_parts(int32_t vocab);  // words of code_partials
 int sd_code_copies(int32_t vocab);     // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);
-bool sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
+uint32_t sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);
-// what that left undone, if h_flag says so
+// what that left undone, if it says so
 sd_status sd_code_rest(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens, int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);
 // the documents' text alone
 void sd_layout(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
@@ -137,6 +140,21 @@ void sd_group_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64
 // that differs from keys[i] >> old_shift (0: everywhere)
 void sd_place_ranks(sd_ctx *c, const uint64_t *keys, const uint32_t *vals, int64_t n, const uint32_t *place,
                     int old_shift, uint32_t *rank, hipStream_t st);
+
+// A stream that is being captured into a graph cannot be waited for.
+static inline bool stream_can_wait(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
+}
+
+// A kernel's number, under which it tells the host something, in h_told[SD_TOLD]; and what it has told, once it has.
+// false: something went wrong on the stream, or all of it is over without a word from that kernel.
+static inline uint32_t sd_next_number(sd_ctx *c) { return c->told_last = (c->told_last + 1) & 0x7fffffffu; }
+bool sd_hear(const sd_ctx *c, uint32_t number, uint32_t *what, hipStream_t st);
 
 sd_status sd_build_global_impl(sd_ctx *c, const int32_t *d_tokens, const int64_t *d_offsets,
                                int32_t n_seq, int64_t n_tokens, hipStream_t st);
