@@ -131,8 +131,8 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     c->rest_table = c->b_ranges + code_ranges;
     c->rest_to = c->rest_table + code_starts;
     ok = ok && dev_alloc(&c->b_partials, c->b_partials_cap, sb);
-    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2 + sd_code_blocks(cfg->vocab), sb) && dev_alloc(&c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), sb) &&
-         dev_alloc(&c->code_partials, sd_code_parts(cfg->vocab), sb) && dev_alloc(&c->b_starts, code_starts, sb) &&
+    ok = ok && dev_alloc(&c->code_cdf, (int64_t)cfg->vocab + 2 + sd_code_blocks(cfg->vocab), sb) && dev_alloc(&c->code_cnt, sd_code_counts(cfg->vocab, cap), sb) &&
+         dev_alloc(&c->code_partials, sd_code_partials(cfg->vocab), sb) && dev_alloc(&c->b_starts, code_starts, sb) &&
          dev_alloc(&c->code_sums, code_sums, sb) &&
          dev_alloc(&c->code_bucket, (int64_t)cfg->vocab + 2, sb);
     if (ok) c->code_blocks = c->code_cdf + cfg->vocab + 2;
@@ -164,7 +164,7 @@ sd_status sd_create(const sd_config *cfg, sd_ctx **out) {
     sd_fill_i32(c->r_len, B, 0, nullptr);
     sd_fill_i32(c->d_err, SD_DEVERR_N, 0, nullptr);
     sd_fill_i32((int32_t *)c->code_sums, code_sums, 0, nullptr);
-    sd_fill_i32((int32_t *)c->code_cnt, ((int64_t)cfg->vocab + 1) * sd_code_copies(cfg->vocab), 0, nullptr);
+    sd_fill_i32((int32_t *)c->code_cnt, sd_code_counts(cfg->vocab, cap), 0, nullptr);
     sd_fill_i32((int32_t *)c->d_algo_bytes, 2 * SD_K_COUNT, 0, nullptr);
     // the counters live behind the context lengths, in the same allocation: every workgroup
     // reads its length at its start, so the counters' page is one the compute unit has seen

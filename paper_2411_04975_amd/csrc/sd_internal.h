@@ -65,8 +65,8 @@ struct sd_ctx {
     // suffix sorting by codes (sd_suffix.hip)
     uint32_t *code_cdf = nullptr;       // [vocab + 2]: lower end of each token code's interval
     uint32_t *code_blocks = nullptr;    // lower ends of blocks of tokens' intervals
-    uint32_t *code_cnt = nullptr;       // [copies][vocab + 1]: counts of a sample, zero between builds
-    uint32_t *code_partials = nullptr;
+    uint32_t *code_cnt = nullptr;       // lists of a sample's tokens, or its counts [vocab + 1], which are zero between builds
+    uint32_t *code_partials = nullptr;  // [tiles of codes]: their weights, where the sample is counted
     int32_t *code_bucket = nullptr;     // [vocab + 2]: bucket table of the documents of an insertion
     uint32_t *code_sums = nullptr;      // [chunks of tiles][bins], zero between builds
     int64_t code_seen = 0;              // positions of the text that code_cdf was sampled from; 0: of none
@@ -115,8 +115,8 @@ void sd_code_room(int64_t cap, int32_t vocab, int64_t *hist_words, int64_t *star
                   int64_t *range_words, int64_t *rest_words);
 bool sd_code_fits(int64_t N, int32_t vocab);
 int64_t sd_code_blocks(int32_t vocab); // words of code_blocks
-int64_t sd_code_parts(int32_t vocab);  // words of code_partials
-int sd_code_copies(int32_t vocab);     // of code_cnt
+int64_t sd_code_partials(int32_t vocab);  // words of code_partials
+int64_t sd_code_counts(int32_t vocab, int64_t cap);  // of code_cnt
 void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t n_tokens, hipStream_t st);
 uint32_t sd_code_sort(sd_ctx *c, const int32_t *tokens, const int64_t *offs, int32_t n_seq, int64_t n_tokens,
                   int32_t *text, int32_t *sa, int32_t *tok1, int32_t *bucket, hipStream_t st);

@@ -106,85 +106,102 @@ __device__ __forceinline__ int wave_lower_bound(AT at, int n, int64_t key) {
 // Counts of a sample of the tokens: C runs of 64 of them, evenly spread.  A workgroup counts its
 // runs in an LDS table first: a frequent token would otherwise be tens of thousands of atomic
 // additions to one address, at some 30 ns each.
-// What it found goes into one of several copies of the counts: frequent tokens lie next to each
-// other in many vocabularies, and additions to one line queue up just the same (10M tokens of a
-// Zipf law: 24 us, 75 with one copy), and 32 neighbouring tokens lie next to each other in the LDS table, so that lanes next
-// to each other add to one line in one go (9.5 us; 10M tokens of like frequency 14.4 -> 14.1).
-constexpr int RUNS_PER_WG = 16;
-constexpr int TABLE = 2048;  // 64 groups of 32 neighbouring tokens
+//
+// LISTS (vocabularies of up to LISTS_MAX): what it has found it writes down by tiles of CDF_TILE codes, with a row that says
+// where each tile's begin and how many tokens lie in front of them, and the workgroup of k_code_cdf that has the tile adds its share of all lists up in LDS.  (Added to counts in memory, eight copies of
+// them, a line of the L2 an addition, of which it does some 28 G/s, and the copies added up by tile in a launch of their own: 10M tokens, 262k of them in the sample, 14.3 + 5.3 + 4.9 us
+// with k_code_cdf, 7.2 + 6.3 so, 10M of a Zipf law 9.8 + 5.2 + 5.0 and 4.9 + 10.2, 100M 61 + 5.4 + 4.9 and 16.3 + 13.)  Larger vocabularies are counted in memory: a list of a wave's tokens by thousands of tiles is no shorter than that.
+// Run number i of C lies at i * runs / C = i * apart + i * rest / C (C being 2^15 at most, and runs of 64 tokens 2^25).
+constexpr int RUNS_PER_WG = 16, TOKENS_PER_WG = 64 * RUNS_PER_WG;
+constexpr int TABLE_BITS = 11, TABLE = 1 << TABLE_BITS;  // 64 groups of 32 neighbouring tokens
+constexpr int CDF_ITEMS = 2, CDF_TILE = CT * CDF_ITEMS;
+constexpr int32_t LISTS_MAX = 1 << 18;
+constexpr int CDF_TILES = LISTS_MAX / CDF_TILE + 1;
+constexpr int LIST_CODE_BITS = 19;  // of an entry: the code, and from there on how often it was seen
+static_assert((1ll << LIST_CODE_BITS) > LISTS_MAX && TOKENS_PER_WG < 1 << (32 - LIST_CODE_BITS) && TOKENS_PER_WG < 1 << 16 && CDF_TILES <= CT, "");
 
+template <bool LISTS>
 __global__ __launch_bounds__(CT) void k_code_sample(const int32_t *__restrict__ tokens, int64_t n_tokens,
-                                                    int32_t vocab, int64_t runs, int64_t C, uint32_t *__restrict__ counts,
-                                                    int copies, int32_t n_codes) {
+                                                    int32_t vocab, uint32_t apart, uint32_t rest, uint32_t C, uint32_t *__restrict__ counts,
+                                                    uint32_t *__restrict__ lists, uint32_t *__restrict__ rows, int parts) {
     __shared__ uint32_t s_tag[TABLE], s_num[TABLE];
+    __shared__ uint32_t s_at[LISTS ? CDF_TILES : 1];  // of a tile: entries, and how often they were seen from bit 16 on; then both in front of it
+    __shared__ uint32_t s_wave[CW];
     constexpr uint32_t FREE = 0xffffffffu;
-    for (int i = threadIdx.x; i < TABLE; i += CT) { s_tag[i] = FREE; s_num[i] = 0; }
-    __syncthreads();
-    uint32_t *cnt = counts + (int64_t)(blockIdx.x & (unsigned)(copies - 1)) * n_codes;
+    constexpr int RUNS = RUNS_PER_WG / CW, SLOTS = TABLE / CT;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t tok[RUNS_PER_WG / CW];
+    int32_t tok[RUNS];
 #pragma unroll
-    for (int k = 0; k < RUNS_PER_WG / CW; k++) {
-        const int64_t run = (int64_t)blockIdx.x * RUNS_PER_WG + k * CW + w;
-        const int64_t p = run < C ? (run * runs / C) * 64 + lane : n_tokens;
+    for (int k = 0; k < RUNS; k++) {
+        const uint32_t run = blockIdx.x * RUNS_PER_WG + (uint32_t)(k * CW + w);
+        const int64_t p = run < C ? (int64_t)(run * apart + run * rest / C) * 64 + lane : n_tokens;
         tok[k] = p < n_tokens ? tokens[p] : -2;
-        if (tok[k] < 0) tok[k] = -2;       // (end markers of a text)
-        if (tok[k] >= vocab) tok[k] = 0;  // (as it goes into the text)
     }
+    for (int i = threadIdx.x; i < TABLE; i += CT) { s_tag[i] = FREE; s_num[i] = 0; }
+    if (LISTS && threadIdx.x < CDF_TILES) s_at[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t code[SLOTS + RUNS], num[SLOTS + RUNS];  // a thread's slots of the table, and its tokens that found no room in it
 #pragma unroll
-    for (int k = 0; k < RUNS_PER_WG / CW; k++) {
-        if (tok[k] == -2) continue;
-        const uint32_t code = (uint32_t)(tok[k] + 1);
-        uint32_t h = ((code >> 5) * 2654435761u >> 26) << 5 | (code & 31u);
+    for (int k = 0; k < RUNS; k++) {
+        num[SLOTS + k] = 0;
+        if (tok[k] < 0) continue;         // (end markers of a text)
+        if (tok[k] >= vocab) tok[k] = 0;  // (as it goes into the text)
+        code[SLOTS + k] = (uint32_t)(tok[k] + 1);
+        uint32_t h = ((code[SLOTS + k] >> 5) * 2654435761u >> (32 - (TABLE_BITS - 5))) << 5 | (code[SLOTS + k] & 31u);
         int probe = 0;
         for (; probe < 16; probe++) {
-            const uint32_t old = atomicCAS(&s_tag[h], FREE, code);
-            if (old == FREE || old == code) { atomicAdd(&s_num[h], 1u); break; }
+            const uint32_t old = atomicCAS(&s_tag[h], FREE, code[SLOTS + k]);
+            if (old == FREE || old == code[SLOTS + k]) { atomicAdd(&s_num[h], 1u); break; }
             h = (h + 32) & (TABLE - 1);
         }
-        if (probe == 16) atomicAdd(&cnt[code], 1u);
+        if (probe == 16) num[SLOTS + k] = 1;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < TABLE; i += CT)
-        if (s_num[i]) atomicAdd(&cnt[s_tag[i]], s_num[i]);
+    uint32_t rank[SLOTS + RUNS];
+#pragma unroll
+    for (int k = 0; k < SLOTS + RUNS; k++) {
+        if (k < SLOTS) {
+            num[k] = s_num[k * CT + threadIdx.x];
+            code[k] = s_tag[k * CT + threadIdx.x];
+        }
+        if (num[k] == 0) continue;
+        if (LISTS) rank[k] = atomicAdd(&s_at[code[k] / CDF_TILE], 1u | num[k] << 16) & 0xffffu;
+        else atomicAdd(&counts[code[k]], num[k]);
+    }
+    if (!LISTS) return;
+    __syncthreads();
+    const int i = (int)threadIdx.x;
+    uint32_t tot;
+    const uint32_t ex = block_excl_scan(i < parts ? s_at[i] : 0u, s_wave, &tot);
+    if (i < parts) s_at[i] = ex;
+    if (i <= parts) rows[(int64_t)blockIdx.x * (parts + 1) + i] = ex;  // (the last one: all of them)
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SLOTS + RUNS; k++)
+        if (num[k]) lists[(int64_t)blockIdx.x * TOKENS_PER_WG + (s_at[code[k] / CDF_TILE] & 0xffffu) + rank[k]] = code[k] | num[k] << LIST_CODE_BITS;
 }
 
 // A token that the sample has not seen gets a quarter of the weight of one sighting: among 1e5
 // tokens of like frequency an eighth goes unseen by two draws per token, and the suffixes that
 // start with such a token share its interval.
-constexpr int CDF_ITEMS = 2, CDF_TILE = CT * CDF_ITEMS;
+__device__ __forceinline__ uint32_t weight_of(int32_t c, uint32_t n, uint32_t ends) { return SIGHTING * (c == 0 ? ends : n) + UNSEEN; }
 
-// weight[c], in place of the first copy's count (of the end marker: `ends`); clears the other copies
-// (A copy after the other, a load each, took 6.8 us for 128k tokens and 9.5 for 152k; all of them at once: 5.2 and 5.3.)
-template <int COPIES>
-__global__ __launch_bounds__(CT) void k_code_weights(uint32_t *__restrict__ counts,
-                                                     int32_t n_codes, uint32_t ends,
+// The weights of a tile's codes added up, where the sample has not done that: for large vocabularies.
+__global__ __launch_bounds__(CT) void k_code_weights(const uint32_t *__restrict__ counts, int32_t n_codes, uint32_t ends,
                                                      uint32_t *__restrict__ partials) {
     __shared__ uint32_t s_wave[CW];
     uint32_t sum = 0;
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
         const int32_t c = (int32_t)blockIdx.x * CDF_TILE + k * CT + (int32_t)threadIdx.x;
-        if (c < n_codes) {
-            uint32_t v[COPIES], n = 0;
-#pragma unroll
-            for (int q = 0; q < COPIES; q++) v[q] = counts[(int64_t)q * n_codes + c];
-#pragma unroll
-            for (int q = 0; q < COPIES; q++) {
-                n += v[q];
-                if (q > 0) counts[(int64_t)q * n_codes + c] = 0;
-            }
-            n = SIGHTING * (c == 0 ? ends : n) + UNSEEN;
-            counts[c] = n;
-            sum += n;
-        }
+        if (c < n_codes) sum += weight_of(c, counts[c], ends);
     }
     uint32_t tot;
     (void)block_excl_scan(sum, s_wave, &tot);
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-// cdf[c] = lower end of the interval of code c; clears the first copy.  Ends are multiples of
+// cdf[c] = lower end of the interval of code c, from the lists or from the counts in memory, which it clears.  Ends are multiples of
 // 2^CDF_QUANTUM (and no interval is empty, the weights' total being below 2^27): an entry may
 // lack that many of its code's last bits, and the rest still names the first token.
 //
@@ -198,33 +215,103 @@ constexpr int CDF_QUANTUM = 5;
 constexpr int CDF_BLOCKS = 4096, CDF_MAX_SHIFT = 7;
 // (What is left over behind the last of them belongs to no code.  Every code has a weight of UNSEEN and more of less than 2^27: no part is empty.)
 __device__ __forceinline__ uint32_t even_part(uint32_t width, int shift) { return width >> shift; }
-__global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, int32_t n_codes,
+constexpr int CDF_HELPERS = CT;  // threads that only add up lists (10M tokens of a Zipf law, most of whose lists is the first tile's, 11.5 us without and 10.2 so)
+constexpr uint32_t LIST_LANES = 4;
+template <bool LISTS>
+__global__ __launch_bounds__(CT + (LISTS ? CDF_HELPERS : 0)) void k_code_cdf(uint32_t *__restrict__ counts, int32_t n_codes, uint32_t ends,
+                                                 const uint32_t *__restrict__ lists, const uint32_t *__restrict__ rows, int n_lists,
                                                  const uint32_t *__restrict__ partials,
                                                  uint32_t *__restrict__ cdf, int shift, uint32_t slack, uint32_t *__restrict__ blocks) {
-    __shared__ uint32_t s_wave[CW];
-    uint32_t below = 0, all = 0;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += CT) {
-        const uint32_t v = partials[i];
-        all += v;
-        if (i < (int)blockIdx.x) below += v;
-    }
+    constexpr int WAVES = LISTS ? (CT + CDF_HELPERS) / SD_WAVE : CW;
+    __shared__ uint3 s_wave[WAVES];
+    __shared__ uint32_t s_count[LISTS ? CDF_TILE : 1];
     static_assert(CDF_ITEMS == 2 && (1 << CDF_MAX_SHIFT) <= 2 * SD_WAVE, "a block is some lanes of a wave");
+    const int parts = (int)gridDim.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t c0 = (int32_t)blockIdx.x * CDF_TILE + (int32_t)threadIdx.x * CDF_ITEMS;
-    uint32_t wgt[CDF_ITEMS], sum = 0, top = 0, tot;
+    uint32_t below = 0, all = 0;  // sightings in lower tiles and in all, or weights
+    if (LISTS) {
+        for (int i = threadIdx.x; i < CDF_TILE; i += CT + CDF_HELPERS) s_count[i] = 0;
+        __syncthreads();
+        // LIST_LANES lanes to a list: of its part, a few entries where the tokens are of like frequency and some hundred where
+        // many of them are in the tile, the first ones and then more at a time
+        const int share = (n_lists + WAVES - 1) / WAVES, end = (w + 1) * share < n_lists ? (w + 1) * share : n_lists;
+        const uint32_t q = (uint32_t)lane & (LIST_LANES - 1);
+        struct { uint32_t at, to, all; } row, next = {};
+        auto ask = [&](int g) {
+            const uint32_t *r = rows + (int64_t)g * (parts + 1);
+            next = {};
+            if (g < end) next = {r[blockIdx.x], r[blockIdx.x + 1], r[parts]};
+        };
+        int g = w * share + lane / (int)LIST_LANES;
+        ask(g);
+        for (; __any(g < end); g += SD_WAVE / (int)LIST_LANES) {
+            row = next;
+            ask(g + SD_WAVE / (int)LIST_LANES);
+            if (q == 0) {
+                all += row.all >> 16;
+                below += row.at >> 16;
+            }
+            const uint32_t *list = lists + (int64_t)(g < end ? g : 0) * TOKENS_PER_WG;
+            const uint32_t to = row.to & 0xffffu;
+            uint32_t o = (row.at & 0xffffu) + 4 * q;
+            auto add = [&](auto at_once) {
+                constexpr int N = decltype(at_once)::value;
+                u32x4 e[N];  // (up to three more than there are: of the next list or of the rows)
+#pragma unroll
+                for (int u = 0; u < N; u++)
+                    if (o + 4 * LIST_LANES * u < to) e[u] = *reinterpret_cast<const u32x4 *>(list + o + 4 * LIST_LANES * u);
+#pragma unroll
+                for (int u = 0; u < N; u++)
+#pragma unroll
+                    for (int k = 0; k < 4; k++)
+                        if (o + 4 * LIST_LANES * u + k < to) atomicAdd(&s_count[e[u][k] & (CDF_TILE - 1)], e[u][k] >> LIST_CODE_BITS);
+                o += 4 * LIST_LANES * N;
+            };
+            add(std::integral_constant<int, 1>());
+            while (__any(o < to)) add(std::integral_constant<int, 6>());
+        }
+        __syncthreads();
+    } else {
+        for (int i = threadIdx.x; i < parts; i += CT) {
+            const uint32_t v = partials[i];
+            all += v;
+            if (i < (int)blockIdx.x) below += v;
+        }
+    }
+    uint32_t n[CDF_ITEMS] = {};
+    if (threadIdx.x < CT)
+#pragma unroll
+        for (int k = 0; k < CDF_ITEMS; k++)
+            if (c0 + k < n_codes) {
+                n[k] = LISTS ? s_count[threadIdx.x * CDF_ITEMS + k] : counts[c0 + k];
+                if (!LISTS) counts[c0 + k] = 0;
+            }
+    uint32_t wgt[CDF_ITEMS], sum = 0, top = 0;
 #pragma unroll
     for (int k = 0; k < CDF_ITEMS; k++) {
-        wgt[k] = 0;
-        if (c0 + k < n_codes) {
-            wgt[k] = weight[c0 + k];
-            weight[c0 + k] = 0;
-        }
+        wgt[k] = c0 + k < n_codes ? weight_of(c0 + k, n[k], ends) : 0u;
         sum += wgt[k];
         top = wgt[k] > top ? wgt[k] : top;
     }
-    uint32_t total, base;
-    (void)block_excl_scan(all, s_wave, &total);
-    (void)block_excl_scan(below, s_wave, &base);
-    uint32_t at = base + block_excl_scan(sum, s_wave, &tot);
+    const uint32_t inc = wave_incl_scan(sum), all_inc = wave_incl_scan(all), below_inc = wave_incl_scan(below);
+    if (lane == 63) s_wave[w] = make_uint3(inc, all_inc, below_inc);
+    __syncthreads();
+    if (w >= CW) return;
+    uint32_t total = 0, at = 0;
+#pragma unroll
+    for (int i = 0; i < WAVES; i++) {
+        const uint3 v = s_wave[i];
+        total += v.y;
+        at += v.z;
+    }
+    if (LISTS) {  // (sightings, of codes other than the end marker's)
+        const int32_t codes = (int32_t)blockIdx.x * CDF_TILE;
+        total = SIGHTING * (total + ends) + UNSEEN * (uint32_t)n_codes;
+        at = SIGHTING * (at + (codes > 0 ? ends : 0u)) + UNSEEN * (uint32_t)(codes < n_codes ? codes : n_codes);
+    }
+    at += inc - sum;
+#pragma unroll
+    for (int i = 0; i < CW; i++) at += i < w ? s_wave[i].x : 0u;
     const int lanes = 1 << (shift - 1), head = (int)(threadIdx.x & 63 & ~(unsigned)(lanes - 1));
     uint32_t in_block = sum;
     for (int o = 1; o < lanes; o <<= 1) {
@@ -232,7 +319,13 @@ __global__ __launch_bounds__(CT) void k_code_cdf(uint32_t *__restrict__ weight, 
         const uint32_t t = __shfl_xor(top, o);
         top = t > top ? t : top;
     }
-    auto end = [&](uint32_t w) { return (uint32_t)((uint64_t)w * 0x7ffffffull / total); };
+    // w * 0x7ffffff / total, rounded down, for w of up to total.  (As a division of 64 bits, four of which a thread has, k_code_cdf takes 7.1 us, 6.3 so.)
+    const double scale = (double)0x7ffffff / (double)total;
+    auto end = [&](uint32_t w) {
+        const uint32_t q = (uint32_t)((double)w * scale);  // (or one more or less)
+        const int64_t r = (int64_t)((uint64_t)w * 0x7ffffffull) - (int64_t)((uint64_t)q * total);
+        return r < 0 ? q - 1u : r >= (int64_t)total ? q + 1u : q;
+    };
     const uint32_t first = __shfl(at, head), lo = end(first), width = end(first + in_block) - lo;
     const int32_t b0 = c0 & ~((1 << shift) - 1);  // the block's first code
     const bool even = b0 + (1 << shift) <= n_codes && (uint64_t)top << shift <= 2 * (uint64_t)in_block + ((uint64_t)slack << shift);
@@ -1860,9 +1953,15 @@ static int block_shift(int32_t vocab) {
     return s;
 }
 int64_t sd_code_blocks(int32_t vocab) { return (((int64_t)vocab + 1) >> block_shift(vocab)) + 2; }
-int64_t sd_code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }
-constexpr int COUNT_COPIES = 8;  // of the sample's counts, where they are small
-int sd_code_copies(int32_t vocab) { return vocab <= (1 << 18) ? COUNT_COPIES : 1; }
+static int64_t code_parts(int32_t vocab) { return ((int64_t)vocab + 1) / CDF_TILE + 1; }  // the last one also writes cdf[n_codes]
+static bool by_lists(int32_t vocab) { return vocab <= LISTS_MAX; }
+// The lists and behind them their rows, or counts.
+int64_t sd_code_counts(int32_t vocab, int64_t cap) {
+    if (!by_lists(vocab)) return (int64_t)vocab + 1;
+    const int64_t n = (sd_sample_runs(cap) + RUNS_PER_WG - 1) / RUNS_PER_WG;
+    return n * TOKENS_PER_WG + n * (code_parts(vocab) + 1);
+}
+int64_t sd_code_partials(int32_t vocab) { return by_lists(vocab) ? 0 : code_parts(vocab); }
 
 // `tokens`: n_seq documents' tokens one after the other, or a text that holds them (its end markers
 // are not counted).
@@ -1871,14 +1970,16 @@ void sd_code_intervals(sd_ctx *c, const int32_t *tokens, int64_t n_seq, int64_t 
     int64_t ends = n_tokens > 0 ? (int64_t)((double)n_seq * (double)(C * 64) / (double)n_tokens) + 1 : 1;
     if (ends > (1 << 20)) ends = 1 << 20;
     const int32_t n_codes = c->cfg.vocab + 1;
-    const int copies = sd_code_copies(c->cfg.vocab);
-    const unsigned parts = (unsigned)sd_code_parts(c->cfg.vocab);  // the last one also writes cdf[n_codes]
+    const bool lists = by_lists(c->cfg.vocab);
+    const unsigned parts = (unsigned)code_parts(c->cfg.vocab), n_lists = (unsigned)((C + RUNS_PER_WG - 1) / RUNS_PER_WG);
+    uint32_t *rows = c->code_cnt + (int64_t)n_lists * TOKENS_PER_WG;
     if (C > 0)
-        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_sample, dim3((unsigned)((C + RUNS_PER_WG - 1) / RUNS_PER_WG)), dim3(CT), 0,
-                  tokens, n_tokens, c->cfg.vocab, runs, C, c->code_cnt, copies, n_codes);
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (copies == 1 ? k_code_weights<1> : k_code_weights<COUNT_COPIES>), dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
-              (uint32_t)ends, c->code_partials);
-    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_cdf, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes,
+        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (lists ? k_code_sample<true> : k_code_sample<false>), dim3(n_lists), dim3(CT), 0,
+                  tokens, n_tokens, c->cfg.vocab, (uint32_t)(runs / C), (uint32_t)(runs % C), (uint32_t)C, c->code_cnt, c->code_cnt, rows, (int)parts);
+    if (!lists)
+        SD_LAUNCH(c, SD_K_BUILD_OTHER, st, k_code_weights, dim3(parts), dim3(CT), 0, c->code_cnt, n_codes, (uint32_t)ends, c->code_partials);
+    SD_LAUNCH(c, SD_K_BUILD_OTHER, st, (lists ? k_code_cdf<true> : k_code_cdf<false>), dim3(parts), dim3(CT + (lists ? CDF_HELPERS : 0)), 0,
+              c->code_cnt, n_codes, (uint32_t)ends, c->code_cnt, rows, (int)n_lists,
               c->code_partials, c->code_cdf, block_shift(c->cfg.vocab), sd_even_slack(n_tokens), c->code_blocks);
 }
 

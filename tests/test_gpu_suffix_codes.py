@@ -136,6 +136,34 @@ def test_pieces_of_tiles(n, vocab):
         g.close()
 
 
+@pytest.mark.parametrize("kind", ["few", "column"])
+@pytest.mark.parametrize("vocab", [1023, 1024, 262_143, 262_144, 262_145])
+def test_the_sample_that_intervals_come_from(vocab, kind):
+    """Vocabularies of one tile of codes and a code more, and up to the largest whose sample is taken down in lists, with most of
+    the text in tokens of the last codes, or in tokens 32 apart, of which a workgroup's table has not room for all.  The sort copes with such
+    text in one launch only if the intervals are in proportion."""
+    import paper_2411_04975_amd as sd
+    rng = np.random.default_rng(vocab)
+    D, n = 24, 300_000
+    if kind == "few":
+        tokens = np.where(rng.random(n) < 0.8, vocab - 1 - rng.integers(0, 40, n) ** 2 // 50, rng.integers(0, vocab, n))
+    else:
+        tokens = rng.integers(0, (vocab - 7 + 31) // 32, n) * 32 + 7
+    docs = np.split(tokens.astype(np.int32), range(1000, n, 1000))
+    g = parity.GpuPath(vocab, D, 8, 1.0, 0.1, 1, 16, n + len(docs))
+    try:
+        for _ in range(2):  # (the second one over what the first one has left in the tables)
+            sd.sd_debug_profile(g.ctx, 1)
+            sd.sd_debug_profile_read(g.ctx)
+            g.build_global(docs)
+            made = sd.sd_debug_profile_read(g.ctx)
+            sd.sd_debug_profile(g.ctx, 0)
+            assert made["code_sort"]["launches"] == 1 and made["sort_hist"]["launches"] == 0
+            _check(g, docs, D)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("n", [100, 255, 257, 4095, 16_385, 65_535, 65_536, 65_537, 262_145, 4_194_304, 4_194_305])
 def test_small_shares(n):
     """Around the sizes where tiles, bins and the workgroups' shares change: 33 tiles need places of their own,
