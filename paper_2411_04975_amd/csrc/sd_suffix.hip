@@ -17,18 +17,18 @@
 // numbers; and the second-token column of the index comes from the entries: only suffixes that
 // tie are ever looked up in the text.
 //
-// Bound: the memory system.  Per position 72 bytes in order (tokens read, text, codes and lines written, text and
-// codes read, entries written and read once per pass, suffix array and second tokens written), and
-// for each one that ties one random cache line a step: of the 0.42 ms of
-// 10M tokens copied from templates k_code_sort takes 0.23 and reads 124 bytes a position in them
-// (100M: 2.7 of 4.4 ms, 149 bytes), against 0.09 where few suffixes tie.
+// Bound: the memory system.  Per position 52 bytes in order (tokens read, text, entries and lines written, entries
+// read and written by a second split, read once more, suffix array and second tokens written), and
+// for each one that ties one random cache line a step: of the 0.35 ms of
+// 10M tokens copied from templates k_code_sort takes 0.22 and reads 129 bytes a position in them
+// (100M: 2.4 of 3.5 ms, 153 bytes), against 0.07 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
-// Build of 10M tokens copied from templates 1.68 -> 0.42 ms, of 10M of a Zipf law 2.89 -> 0.31 ms, of
-// 100M copied 20.7 -> 4.4 ms, against prefix doubling for everything.
+// Build of 10M tokens copied from templates 1.68 -> 0.37 ms, of 10M of a Zipf law 2.89 -> 0.23 ms, of
+// 100M copied 20.7 -> 3.6 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 #include "sd_sample.h"
 
@@ -433,15 +433,18 @@ __global__ __launch_bounds__(T, ROUNDS > 1 ? 6 : 8) void k_layout(const int32_t 
     if (tid < 3) s.doc[tid] = 0;
     __syncthreads();
     // The tile's end markers, in two rounds of loads: the ends of T of all documents tell between which two of these the
-    // tile starts, and what ends behind that is the tile's or in front of it.
+    // tile starts, and what ends behind that is the tile's or in front of it.  (Up to T documents in one: insertions into 2.2M with the build
+    // 394.2 -> 392.6 us, two builds and insertions of less 138.0 -> 136.8 and 100.7 -> 99.3.)
     if (tile0 < N) {
         const int64_t z = tile0 + TILE + LAYOUT_LOOK;
         const int32_t step = (n_seq + T - 1) / T;
         auto end_of = [&](int32_t j) -> int64_t { return offs[j + 1] + j; };
-        const bool front = tid > 0 && (int64_t)tid * step < n_seq && end_of(tid * step - 1) < tile0;
-        const int n = (int)__popcll(__ballot(front));
-        if ((tid & 63) == 0 && n) atomicAdd(&s.doc[0], n);
-        __syncthreads();
+        if (step > 1) {
+            const bool front = tid > 0 && (int64_t)tid * step < n_seq && end_of(tid * step - 1) < tile0;
+            const int n = (int)__popcll(__ballot(front));
+            if ((tid & 63) == 0 && n) atomicAdd(&s.doc[0], n);
+            __syncthreads();
+        }
         for (int32_t j0 = s.doc[0] * step;; j0 += T) {
             const int64_t e = j0 + tid < n_seq ? end_of(j0 + tid) : z;
             const int n_front = (int)__popcll(__ballot(e < tile0));
