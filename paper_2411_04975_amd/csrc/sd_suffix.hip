@@ -20,14 +20,14 @@
 // Bound: the memory system.  Per position 52 bytes in order (tokens read, text, entries and lines written, entries
 // read and written by a second split, read once more, suffix array and second tokens written), and
 // for each one that ties one random cache line a step: of the 0.35 ms of
-// 10M tokens copied from templates k_code_sort takes 0.22 and reads 129 bytes a position in them
-// (100M: 2.4 of 3.5 ms, 153 bytes), against 0.07 where few suffixes tie.
+// 10M tokens copied from templates k_code_sort takes 0.22 and reads 126 bytes a position in them
+// (100M: 2.4 of 3.5 ms, 151 bytes), against 0.07 where few suffixes tie.
 //
 // Buckets that are too large for a workgroup (thousands of suffixes that share some twenty bits of
 // code: a token over and over, one preamble in front of thousands of documents) are left when all others
 // are sorted, and go through prefix doubling on their own.
 //
-// Build of 10M tokens copied from templates 1.68 -> 0.37 ms, of 10M of a Zipf law 2.89 -> 0.23 ms, of
+// Build of 10M tokens copied from templates 1.68 -> 0.36 ms, of 10M of a Zipf law 2.89 -> 0.23 ms, of
 // 100M copied 20.7 -> 3.6 ms, against prefix doubling for everything.
 #include "sd_internal.h"
 #include "sd_sample.h"
